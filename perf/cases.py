@@ -285,8 +285,9 @@ def tolerance(case):
     if call == "build":
         return "exact"         # bins, ids and codes: one vector in another bin moves every list behind it
     if call == "brute":
-        # whole numbers below 2^24 are exact in any order; floats: 5.0e-6, 1.8e-5 at most, 2.6e-4 of the ids (near ties)
-        return {"rel": 1e-6, "max": 1e-5, "differ": 1e-3} if case["data"] == "bytes" else {"rel": 2e-5, "max": 1e-4, "differ": 1e-3}
+        # whole numbers below 2^24 are exact in any order; floats: 5.0e-6, 1.8e-5 at most, and of the ids (near ties) 2.6e-4
+        # with ten results, 1.6e-3 with 84
+        return {"rel": 1e-6, "max": 1e-5, "differ": 1e-3} if case["data"] == "bytes" else {"rel": 2e-5, "max": 1e-4, "differ": 6e-3}
     if call == "train":
         # one vector that changes its cell moves two centroids: 2.0e-4, 6.5e-3 at most on whole-number vectors; on floats
         # the iterations amplify it (0.29), so that only equal assignments can be compared
