@@ -306,8 +306,8 @@ int pqt_query_batch_exact(pqt_index* index, const float* queries, int64_t nq, in
 /*
  * pqt_brute_force -- Eq. 1 itself: the k exact nearest database vectors of every query, by
  * brute force over the attached vectors (pqt_index_set_vectors); the paper's "strong baseline"
- * (Table 1) and the ground truth for recall.  Distances are ||q||^2 + ||x||^2 - 2 q.x in fp32
- * (exact for integer-valued data with norms below 2^24); results ascend by (distance, id).
+ * (Table 1) and the ground truth for recall.  Distances are sums of (q - x)^2 in fp32 (exact for
+ * integer-valued data with distances below 2^24); results ascend by (distance, id).
  *   queries device nq x D fp32; out_ids device nq x k int64; out_dists device nq x k fp32;
  *   1 <= k <= min(N, 256).  Asynchronous on hip_stream except for workspace growth.
  * Errors: PQT_EINVAL (no vectors attached, k or nq out of range, null), PQT_ENOMEM, PQT_EHIP.

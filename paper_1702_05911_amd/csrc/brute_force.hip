@@ -1,252 +1,835 @@
-// Exact nearest neighbours by brute force (Eq. 1; the paper's "strong baseline" of Table 1): the
-// squared distances of every query to every database vector, and per query the k smallest by
-// (distance, id).  Doubles as the ground truth for recall.
+// Exact nearest neighbours by brute force (Eq. 1; the paper's "strong baseline" of Table 1): per query the k
+// database vectors of smallest squared distance, by (distance, id).  Doubles as the ground truth for recall.
 //
-// The database is walked in chunks.  Per chunk
-//   * bf_distance_kernel: a dense contraction on the matrix cores.  A workgroup of 256 threads computes
-//     a 128 x 128 tile of q.x with v_mfma_f32_16x16x4_f32 (fp32 in, fp32 accumulate), each wavefront a
-//     64 x 64 quarter as 4 x 4 MFMA tiles; operands are staged through LDS sixteen dimensions at a
-//     time (byte vectors are widened while staging; the next step's pieces are fetched during the MFMAs); the epilogue forms ||q||^2 + ||x||^2 - 2 q.x.
-//   * bf_select_kernel: one workgroup per query scans its row of distances once (16 bytes per thread
-//     and step), keeps what beats the k-th best so far in an LDS buffer, and re-selects the k best
-//     whenever the buffer may fill.  Chunks
-//     arrive in id order, so an equal distance that arrives later has the larger id and never wins.
+// A dense contraction finds the few vectors that can be among the k nearest, and only those get their exact fp32
+// distance.  The contraction runs on the bf16 matrix cores, eight times the flops of the fp32 ones: a number is
+// cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly, queries of bytes too.
+// With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), every value s~ that the
+// matrix cores give is within E(q) of s: dropped piece products, one rounding of the running sum per matrix
+// instruction, and the norm (see error_terms in launch_brute_force).  If a is an upper bound of the k-th smallest s~
+// among the vectors seen, every vector of the true result has s~ <= a + 2E.  So
+//   * the database is walked in chunks, in the order i -> (i * step) mod N with step / N near the golden ratio: every
+//     prefix of the order is spread evenly over the database, whatever order the vectors are stored in;
+//   * bf_filter_*_kernel contracts a chunk with all queries.  Vectors go from memory through registers, where they are
+//     cut, into LDS in the operand layout of v_mfma_f32_32x32x16_bf16 (the queries are laid out once, by
+//     pack_queries_kernel): no copy of the database in another format exists.  The first chunk (kDense vectors) is written
+//     out; from then on only pairs with s~ <= a + 2E are kept: the accumulators start at -||x||^2 / 2, a maximum of 16
+//     values and one comparison decide for 16 pairs, and a lane appends what passes to a list of its own, so that no
+//     counter is shared (a query belongs to one column of one wavefront);
+//   * bf_select_kernel, one workgroup per query, bounds the k-th smallest s~ by a 1024-bin histogram and keeps what
+//     can still matter; after the last chunk it computes the exact distances sum (y - x)^2 of that list
+//     (k and a few more) in fp32 and sorts them.
+// Chunks grow by a factor, so that about k times that factor pairs pass per chunk and query.  A query whose lists
+// overflow (heavily tied or non-finite data) is searched by bf_scan_kernel, exact distances to all vectors.
+//
+// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 2.9 = 0.88 PFLOP/s, selection 0.49); with
+// the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
+// 0.90 ms (contraction 0.79 = 1.0 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
 #include "pqt_device.hpp"
 #include "pqt_kernels.hpp"
+#include "row_distance.hpp"
 
 namespace pqt {
+namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));    // (arrays of HIP's uint4 end up in scratch memory)
 
-constexpr int kBfTile = 128;       // queries and database vectors per workgroup tile
-constexpr int kBfKc = 16;          // dimensions staged per step
 constexpr int kBfThreads = 256;
-constexpr int kBfLdsStride = kBfKc + 1;
+constexpr int kDense = 4096;           // vectors of the first chunk; also the entries a select workgroup holds in LDS
+constexpr int kFrag = 512;             // bf16 values of one fragment: 32 rows x 16 dimensions
+constexpr int kStatRows = 64;          // database vectors per LDS tile of the stationary kernel
+constexpr int kGenRows = 256, kGenQueries = 128;   // workgroup tile of the general kernel
 
-// squared norms of n rows of D elements
-template <typename Elem>
-__global__ void row_norms_kernel(const Elem* x, int64_t n, int D, float* out) {
+__device__ __forceinline__ v16f mfma(bf16x8 a, bf16x8 b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16v8, a), __builtin_bit_cast(bf16v8, b), c, 0, 0, 0);
+}
+
+__global__ void fill_word_kernel(uint32_t* out, uint32_t value) { *out = value; }
+
+__global__ void bf_begin_kernel(BruteArgs g) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const Elem* row = x + (size_t)i * D;
-    float s = 0.0f;
-    for (int d = 0; d < D; ++d) {
-        const float v = (float)row[d];
-        s = fmaf(v, v, s);
-    }
-    out[i] = s;
+    if (i < kBfControl) g.control[i] = 0u;
+    if (i < g.nq) g.flagged[i] = 0u;
 }
 
-// Eight consecutive elements of a row as floats (one 8- or 32-byte piece when the row allows it).
-__device__ __forceinline__ void load8(const float* p, bool aligned, float (&v)[8]) {
-    if (aligned) {
-        const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    } else {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = p[c];
-    }
+__device__ __forceinline__ uint32_t pack2(float a, float b) {      // two floats to bf16, nearest even
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
-__device__ __forceinline__ void load8(const uint8_t* p, bool aligned, float (&v)[8]) {
-    if (aligned) {
-        const uint2 w = *reinterpret_cast<const uint2*>(p);
-        v[0] = (float)(w.x & 0xffu); v[1] = (float)((w.x >> 8) & 0xffu); v[2] = (float)((w.x >> 16) & 0xffu); v[3] = (float)(w.x >> 24);
-        v[4] = (float)(w.y & 0xffu); v[5] = (float)((w.y >> 8) & 0xffu); v[6] = (float)((w.y >> 16) & 0xffu); v[7] = (float)(w.y >> 24);
-    } else {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = (float)p[c];
-    }
-}
+__device__ __forceinline__ float low_value(uint32_t pair) { return __uint_as_float(pair << 16); }
+__device__ __forceinline__ float high_value(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
-// A thread's piece of a 128-row x 16-dimension tile: row t/2, dimensions (t%2)*8 .. +8 of step k0, as
-// floats in registers; rows past nrows and dimensions past D are zero.
-template <typename Elem>
-__device__ __forceinline__ void fetch_piece(const Elem* base, int64_t row0, int64_t nrows, int D, int k0, int tid, float (&v)[8]) {
-    const int r = tid >> 1, c0 = (tid & 1) * 8;
-    const int64_t row = row0 + r;
+// Queries -> fragments of two pieces (h, then m): one workgroup per tile of 32 queries, its wavefronts share the steps of
+// 16 dimensions; lane l holds query l % 32, dimensions 8 * (l / 32) .. + 8 of a step.  Also ||q||, and control[kBfSecond]
+// is set when a query has a second piece that is not zero.
+__global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
+    __shared__ float red[kBfThreads / kWave][32];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, D = g.D, KS = g.KS;
+    const int64_t tile = blockIdx.x, q = tile * 32 + (lane & 31);
+    const bool have = q < g.nq;
+    const float* row = g.queries + (have ? (size_t)q * D : 0);
+    float norm = 0.0f;
+    uint32_t second = 0;
+#pragma unroll 4
+    for (int ks = wave; ks < KS; ks += kBfThreads / kWave) {
+        const int d = have ? ks * 16 + 8 * (lane >> 5) : D;               // D is a multiple of four
+        const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float4 v0 = d < D ? *reinterpret_cast<const float4*>(row + d) : z;
+        const float4 v1 = d + 4 < D ? *reinterpret_cast<const float4*>(row + d + 4) : z;
+        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        u32x4 h, m;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = 0.0f;
-    if (row < nrows) {
-        const Elem* p = base + (size_t)row * D + k0 + c0;
-        if (k0 + c0 + 8 <= D) {
-            load8(p, D % 8 == 0, v);                  // pieces are aligned when every row is a whole number of them
-        } else {
-            for (int c = 0; c < 8 && k0 + c0 + c < D; ++c) v[c] = (float)p[c];
+        for (int c = 0; c < 4; ++c) {
+            norm = fmaf(v[2 * c + 1], v[2 * c + 1], fmaf(v[2 * c], v[2 * c], norm));
+            h[c] = pack2(v[2 * c], v[2 * c + 1]);
+            m[c] = pack2(v[2 * c] - low_value(h[c]), v[2 * c + 1] - high_value(h[c]));
+            second |= m[c] & 0x7fff7fffu;
         }
+        u32x4* out = reinterpret_cast<u32x4*>(g.qfrag) + (tile * KS + ks) * (2 * kFrag / 8) + lane;
+        out[0] = h;
+        out[kFrag / 8] = m;
     }
-}
-__device__ __forceinline__ void store_piece(const float (&v)[8], float* dst, int tid) {
-    const int r = tid >> 1, c0 = (tid & 1) * 8;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) dst[r * kBfLdsStride + c0 + c] = v[c];
-}
-
-template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void bf_distance_kernel(BruteArgs g, int64_t x0, int64_t nx) {
-    __shared__ float As[kBfTile * kBfLdsStride];
-    __shared__ float Bs[kBfTile * kBfLdsStride];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t q0 = (int64_t)blockIdx.y * kBfTile;          // first query of the tile
-    const int64_t c0 = (int64_t)blockIdx.x * kBfTile;          // first database vector of the tile, within the chunk
-    const Elem* X = reinterpret_cast<const Elem*>(g.vectors) + (size_t)x0 * g.D;
-    const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;    // this wavefront's quarter
-    const int row = lane & 15, kq = lane >> 4;
-    v4f acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    // the pieces of the next step are fetched into registers while the matrix cores work on this one
-    float pa[8], pb[8];
-    fetch_piece<float>(g.queries, q0, g.nq, g.D, 0, tid, pa);
-    fetch_piece<Elem>(X, c0, nx, g.D, 0, tid, pb);
-    for (int k0 = 0; k0 < g.D; k0 += kBfKc) {
-        __syncthreads();                                        // the tiles of the step before are no longer read
-        store_piece(pa, As, tid);
-        store_piece(pb, Bs, tid);
-        __syncthreads();
-        if (k0 + kBfKc < g.D) {
-            fetch_piece<float>(g.queries, q0, g.nq, g.D, k0 + kBfKc, tid, pa);
-            fetch_piece<Elem>(X, c0, nx, g.D, k0 + kBfKc, tid, pb);
-        }
-#pragma unroll
-        for (int kk = 0; kk < kBfKc; kk += 4) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[(wr + i * 16 + row) * kBfLdsStride + kk + kq];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[(wc + j * 16 + row) * kBfLdsStride + kk + kq];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    // D[row = 4*(lane/16) + r][col = lane%16] of every 16 x 16 tile
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = c0 + wc + j * 16 + row;
-            if (col >= nx) continue;
-            const float xn = g.xnorm[x0 + col];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t q = q0 + wr + i * 16 + 4 * kq + r;
-                if (q < g.nq) g.dist[(size_t)q * g.chunk + col] = (g.qnorm[q] + xn) - 2.0f * acc[i][j][r];
-            }
-        }
-}
-
-constexpr int kBfSelThreads = 512;
-constexpr int kBfBuf = 3840;       // pending entries the LDS buffer holds besides the k best (k <= 256:
-                                   // together at most 4096 keys, eight per thread of the sort)
-
-// best: nq x k keys (ordered distance bits << 32 | id), ascending, ~0 = none yet
-__global__ __launch_bounds__(kBfSelThreads) void bf_select_kernel(BruteArgs g, int64_t x0, int64_t nx, int first, int last) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);       // next_pow2(k + kBfBuf)
-    uint32_t* counter = reinterpret_cast<uint32_t*>(keys + next_pow2(g.k + kBfBuf));
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), k = g.k;
-    const int64_t q = blockIdx.x;
-    const float* row = g.dist + (size_t)q * g.chunk;
-    for (int e = tid; e < k; e += kBfSelThreads) keys[e] = first ? ~0ull : g.best[(size_t)q * k + e];
-    if (tid == 0) counter[0] = 0;
+    norm += __shfl_xor(norm, 32, kWave);
+    if (lane < 32) red[wave][lane] = norm;
     __syncthreads();
-    uint32_t tau = (uint32_t)(keys[k - 1] >> 32);             // distance bits of the k-th best (all ones: none)
-    auto reselect = [&](uint32_t pending) {                     // keep the k smallest of the k best and the pending entries
-        const int n = k + (int)pending, npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
-        for (int e = n + tid; e < npad; e += kBfSelThreads) keys[e] = ~0ull;
-        block_sort_lds<8>(keys, npad, tid, kBfSelThreads);
-        tau = (uint32_t)(keys[k - 1] >> 32);
-        if (tid == 0) counter[0] = 0;
-        __syncthreads();
-    };
-    if (g.chunk % 4 == 0) {
-        // rows are 16-byte aligned: four distances per thread and step, the next piece in flight while this
-        // one is examined; one barrier per 2048 distances
-        const float4* row4 = reinterpret_cast<const float4*>(row);
-        const int64_t n4 = (nx + 3) / 4;                       // a last partial piece stays inside the row
-        float4 next = tid < n4 ? row4[tid] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        for (int64_t b4 = 0; b4 < n4; b4 += kBfSelThreads) {
-            const int64_t i4 = b4 + tid;
-            const float4 v = next;
-            if (i4 + kBfSelThreads < n4) next = row4[i4 + kBfSelThreads];
-            const float vals[4] = {v.x, v.y, v.z, v.w};
-            uint32_t kb[4], cnt = 0;
-            bool tk[4];
+    if (tid < 32) {
+        float n2 = 0.0f;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                kb[c] = mono_key(vals[c]);
-                tk[c] = i4 < n4 && i4 * 4 + c < nx && kb[c] < tau;
-                cnt += tk[c] ? 1u : 0u;
+        for (int w = 0; w < kBfThreads / kWave; ++w) n2 += red[w][tid];
+        g.qnorm[q] = sqrtf(n2);
+    }
+    if (__any(second != 0) && lane == 0) g.control[kBfSecond] = 1u;
+}
+
+// Half squared norms of the database vectors and, in the word behind them, the bits of the largest norm (a little
+// enlarged; never negative, so bits order as values).  A group of lanes per row, 16 bytes per lane and step.
+template <typename Elem>
+__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, float* out) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    constexpr int pe = 16 / (int)sizeof(Elem);
+    const int npieces = D / pe, lpr = lanes_per_row(npieces), per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
+    const int64_t nwaves = (int64_t)gridDim.x * (kBfThreads / kWave);
+    float top = 0.0f;
+    for (int64_t r0 = ((int64_t)blockIdx.x * (kBfThreads / kWave) + wave) * per_wave; r0 < n; r0 += nwaves * per_wave) {
+        const int64_t r = r0 + sub;
+        float s = 0.0f;
+        if (r < n)
+            for (int piece = l; piece < npieces; piece += lpr) {
+                const u32x4 w = reinterpret_cast<const u32x4*>(x + (size_t)r * D)[piece];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (sizeof(Elem) == 4) {
+                        const float v = __uint_as_float(w[j]);
+                        s = fmaf(v, v, s);
+                    } else {
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const float v = (float)((w[j] >> (8 * b)) & 0xffu);
+                            s = fmaf(v, v, s);
+                        }
+                    }
+                }
             }
-            const uint32_t incl = wave_inclusive_sum(cnt, lane);
-            const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
-            if (total) {                                        // same for the whole wavefront
-                uint32_t at = 0;
-                if (lane == kWave - 1) at = atomicAdd(counter, total);
-                at = (uint32_t)__shfl((int)at, kWave - 1, kWave) + incl - cnt;
+        for (int off = 1; off < lpr; off <<= 1) s += __shfl_xor(s, off, kWave);
+        if (r < n && l == 0) out[r] = 0.5f * s;
+        top = fmaxf(top, r < n ? s : 0.0f);
+        if (r < n && s != s) top = __builtin_inff();
+    }
+    const uint32_t bits = wave_max_u32(__float_as_uint(1.001f * sqrtf(top)));
+    if (lane == 0) atomicMax(reinterpret_cast<uint32_t*>(out) + n, bits);
+}
+
+// bound of |s~ - s| for a query of norm qn and database vectors of norm up to xm
+__device__ __forceinline__ float error_bound(const BruteArgs& g, float qn, float xm) { return g.err_dot * qn * xm + g.err_norm * xm * xm; }
+
+// -(a + 2E) of a query: what an accumulator has to reach to be kept
+__device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {
+    if (q >= g.nq || g.flagged[q]) return __builtin_inff();
+    return -(g.edge[q] + 2.0f * error_bound(g, g.qnorm[q], g.xhalf[g.N]));
+}
+
+// One 32 x 32 tile of accumulators: lane l holds query column l % 32 and database rows 8 * (r / 4) + 4 * (l / 32) + r % 4.
+// DENSE: all values go to out (s~ of the query's row of kDense values).  Else those that reach `from` are appended to the
+// lane's list (row of the chunk, s~).
+template <bool DENSE>
+__device__ __forceinline__ void take_tile(const v16f& acc, float from, uint32_t row0, float* dense, uint2* list, int cap, uint32_t& count) {
+    if (DENSE) {
+        if (!dense) return;
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (tk[c]) keys[k + at++] = ((unsigned long long)kb[c] << 32) | (uint32_t)(x0 + i4 * 4 + c);
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<float4*>(dense + row0 + 8 * i) = make_float4(-acc[4 * i], -acc[4 * i + 1], -acc[4 * i + 2], -acc[4 * i + 3]);
+        return;
+    }
+    float top = acc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) top = fmaxf(top, acc[r]);
+    if (top >= from) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (acc[r] >= from) {
+                if (count < (uint32_t)cap) list[count] = make_uint2(row0 + 8 * (r >> 2) + (r & 3), __float_as_uint(-acc[r]));
+                ++count;
+            }
+    }
+}
+
+// Workgroups go to the eight chiplets in turn; the query groups that read the same database tiles are put on one chiplet,
+// one after the other, so that its L2 holds a tile for all of them (splits a multiple of eight; else in plain order).
+__device__ __forceinline__ void place_of_workgroup(int b, int splits, int groups, int& split, int& group) {
+    if (splits % 8) {
+        split = b % splits;
+        group = b / splits;
+    } else {
+        const int l = b / 8;
+        group = l % groups;
+        split = l / groups * 8 + b % 8;
+    }
+}
+
+// Byte vectors of at most 128 dimensions: a wavefront keeps its 64 queries in registers (KS steps, QP pieces) for the
+// whole launch, and the workgroup's 256 queries share the database tiles that stream through LDS, two in turn.  Per
+// tile of 64 vectors a wavefront reads 16 KB of LDS for 2 * 2 * KS matrix instructions of 32 cycles each, half the LDS
+// rate, and widens 2 KB of bytes (two instructions per three bytes, a fifth of the matrix time and beside it).  Three
+// workgroups fit a compute unit, so others compute while one passes its barrier or examines its sums.
+// LDS: 16 bytes of (row, step, half) lie in slot row ^ step of the fragment's half: eight lanes bring a row's eight steps
+// and would all hit the same banks.
+template <int KS, int QP, bool DENSE>
+__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(BruteArgs g) {
+    if ((QP == 2) != (g.control[kBfSecond] != 0u)) return;         // the launch of the other number of pieces has this work
+    __shared__ __align__(16) uint16_t xs[2][kStatRows / 32 * KS * kFrag];
+    __shared__ __align__(16) float hs[2][kStatRows];
+    constexpr int kPieces = (kStatRows * KS + kBfThreads - 1) / kBfThreads;    // 16-byte pieces of a tile per thread
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int splits = g.splits;
+    int split, group;
+    place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
+    const int64_t q0 = (int64_t)group * 256 + wave * 64;
+    bf16x8 bq[QP][2][KS];
+    float from[2];
+    uint32_t count[2] = {0, 0};
+    uint2* list[2];
+    float* dense[2];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+        const int64_t q = q0 + ct * 32 + (lane & 31);
+#pragma unroll
+        for (int p = 0; p < QP; ++p)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                bq[p][ct][ks] = reinterpret_cast<const bf16x8*>(g.qfrag)[((q0 / 32 + ct) * KS + ks) * (2 * kFrag / 8) + p * (kFrag / 8) + lane];
+        from[ct] = DENSE ? 0.0f : keep_from(g, q);
+        list[ct] = g.lists + ((size_t)q * g.segs + split * 2 + (lane >> 5)) * g.seg_cap;
+        dense[ct] = DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr;
+    }
+    const int ntile = (int)((g.chunk_rows + kStatRows - 1) / kStatRows), D16 = g.D / 16;
+    // the pieces this thread brings: piece i is step sk[i] of row sr[i] of the tile
+    const uint8_t* X = static_cast<const uint8_t*>(g.vectors);
+    int sr[kPieces], sk[kPieces];
+    uint32_t slot[kPieces];
+    bool mine[kPieces];
+    uint64_t id[kPieces], hid;                 // vectors of those rows; of row tid (the norms)
+    const uint64_t move = ((uint64_t)splits * kStatRows) % g.N * g.step % g.N;
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+        const int e = i * kBfThreads + tid;
+        mine[i] = e < kStatRows * KS;
+        // rows four apart within a wavefront's instruction, so that row ^ step takes all sixteen bank groups
+        const int r = e / KS;
+        sk[i] = e - r * KS;
+        sr[i] = KS == 8 ? (r & 32) | (r & 7) << 2 | (r >> 3 & 3) : r & (kStatRows - 1);
+        slot[i] = (((uint32_t)sr[i] >> 5) * KS + sk[i]) * 64u + (((uint32_t)sr[i] & 31u) ^ (uint32_t)sk[i]);
+        id[i] = ((g.chunk_pos + (uint64_t)split * kStatRows + sr[i]) % g.N) * g.step % g.N;
+    }
+    hid = ((g.chunk_pos + (uint64_t)split * kStatRows + (tid & (kStatRows - 1))) % g.N) * g.step % g.N;
+    u32x4 piece[kPieces];
+    float hx = 0.0f;
+    auto fetch = [&](int t) {                  // tile t, then the ids move on to tile t + splits
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const u32x4 v = reinterpret_cast<const u32x4*>(X + id[i] * (uint64_t)g.D)[sk[i] < D16 ? sk[i] : 0];
+            piece[i] = sk[i] < D16 ? v : zero;
+            id[i] += move;
+            id[i] -= id[i] >= g.N ? g.N : 0;
+        }
+        hx = (int64_t)t * kStatRows + (tid & (kStatRows - 1)) < g.chunk_rows ? g.xhalf[hid] : __builtin_inff();   // such rows enter no list
+        hid += move;
+        hid -= hid >= g.N ? g.N : 0;
+    };
+    fetch(split);                              // (past the last tile: some vectors, unused; always loading keeps them in registers)
+    int buf = 0;
+    for (int t = split; t < ntile; t += splits, buf ^= 1) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            u32x4 w0, w1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t b = piece[i][j];
+                const uint32_t p0 = pack2((float)(b & 0xffu), (float)((b >> 8) & 0xffu)), p1 = pack2((float)((b >> 16) & 0xffu), (float)(b >> 24));
+                if (j < 2) { w0[2 * j] = p0; w0[2 * j + 1] = p1; }
+                else { w1[2 * j - 4] = p0; w1[2 * j - 3] = p1; }
+            }
+            if (mine[i]) {
+                reinterpret_cast<u32x4*>(xs[buf])[slot[i]] = w0;
+                reinterpret_cast<u32x4*>(xs[buf])[slot[i] + 32] = w1;
+            }
+        }
+        if (tid < kStatRows) hs[buf][tid] = -hx;
+        __syncthreads();                       // the tile before the last is read by nobody any more: one barrier per tile
+        fetch(t + splits);
+#pragma unroll
+        for (int rt = 0; rt < kStatRows / 32; ++rt) {
+            v16f c;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 h = *reinterpret_cast<const float4*>(&hs[buf][rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                c[4 * i] = h.x; c[4 * i + 1] = h.y; c[4 * i + 2] = h.z; c[4 * i + 3] = h.w;
+            }
+            v16f acc0 = c, acc1 = c;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const bf16x8 a = reinterpret_cast<const bf16x8*>(xs[buf])[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
+#pragma unroll
+                for (int p = 0; p < QP; ++p) {
+                    acc0 = mfma(a, bq[p][0][ks], acc0);
+                    acc1 = mfma(a, bq[p][1][ks], acc1);
+                }
+            }
+            const uint32_t row0 = (uint32_t)t * kStatRows + rt * 32 + 4 * (lane >> 5);
+            take_tile<DENSE>(acc0, from[0], row0, dense[0], list[0], g.seg_cap, count[0]);
+            take_tile<DENSE>(acc1, from[1], row0, dense[1], list[1], g.seg_cap, count[1]);
+        }
+    }
+    if (!DENSE) {
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+            const int64_t q = q0 + ct * 32 + (lane & 31);
+            g.seg_count[(size_t)q * g.segs + split * 2 + (lane >> 5)] = count[ct];
+        }
+    }
+}
+
+// Any dimension: both operands stream through LDS, 16 dimensions a step.  The workgroup's tile is 256 vectors x 128
+// queries, a wavefront's 64 x 128 (128 accumulator registers); with two pieces on both sides a step is 24 matrix
+// instructions (h.h, h.m, m.h) for 12 KB of LDS reads per wavefront.  A workgroup takes every splits-th tile of vectors;
+// the steps of all its tiles are one sequence, so the next step's pieces are under way across tile borders too.
+// Rows arrive as 64 bytes of floats per step, four lanes each, and are cut on their way into LDS (three instructions per
+// element, a quarter of the matrix time and beside it); byte rows (more than 128 dimensions) as 16 bytes, one lane each.
+template <typename Elem, bool DENSE>
+__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
+    constexpr bool kFloats = sizeof(Elem) == 4;
+    constexpr int XP = kFloats ? 2 : 1;                                        // pieces per value
+    constexpr int kX = kGenRows / 32, kQ = kGenQueries / 32;                   // 32-row tiles of the workgroup's tile
+    constexpr int kXPieces = kFloats ? 4 : 1, kQPieces = kQ * 2 * kFrag / 8 / kBfThreads;
+    __shared__ __align__(16) uint16_t xs[2][kX * XP * kFrag];
+    __shared__ __align__(16) uint16_t qs[2][kQ * 2 * kFrag];
+    __shared__ __align__(16) float hs[2][kGenRows];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int KS = g.KS, splits = g.splits;
+    int split, group;
+    place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
+    const int64_t q0 = (int64_t)group * kGenQueries;
+    __shared__ float from[kGenQueries];
+    if (!DENSE && tid < kGenQueries) from[tid] = keep_from(g, q0 + tid);      // (read after the first step's barrier)
+    uint32_t count[kQ];
+#pragma unroll
+    for (int ct = 0; ct < kQ; ++ct) count[ct] = 0;
+    const int ntile = (int)((g.chunk_rows + kGenRows - 1) / kGenRows);
+    const u32x4* qf = reinterpret_cast<const u32x4*>(g.qfrag);
+    constexpr int kTileQ = 2 * kFrag / 8;                                      // 16-byte pieces of a 32-query tile's step
+    // the rows this thread brings 16 bytes of: (tid / 4) + 64 i, bytes 16 (tid % 4) of a step's 64; or row tid
+    const int rl = kFloats ? tid >> 2 : tid, c4 = kFloats ? tid & 3 : 0;
+    const uint64_t move = ((uint64_t)splits * kGenRows) % g.N * g.step % g.N;
+    uint64_t id[kXPieces], hid;
+#pragma unroll
+    for (int i = 0; i < kXPieces; ++i) id[i] = ((g.chunk_pos + (uint64_t)split * kGenRows + rl + 64 * i) % g.N) * g.step % g.N;
+    hid = ((g.chunk_pos + (uint64_t)split * kGenRows + tid) % g.N) * g.step % g.N;
+    struct Step { u32x4 x[kXPieces], q[kQPieces]; };
+    int fks = 0;                               // the step fetched next, of the tile the ids stand for
+    auto fetch = [&](Step& f) {                // (past the last tile: some vectors, unused; always loading keeps the pieces in registers)
+        const int d = fks * 16 + 4 * c4;
+        const bool in = d < g.D;               // D is a multiple of what a thread brings
+#pragma unroll
+        for (int i = 0; i < kXPieces; ++i) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const Elem*>(g.vectors) + id[i] * (uint64_t)g.D + (in ? d : 0));
+            f.x[i] = in ? v : zero;
+        }
+#pragma unroll
+        for (int i = 0; i < kQPieces; ++i) {
+            const int e = i * kBfThreads + tid, ct = e / kTileQ;
+            f.q[i] = qf[((size_t)(q0 / 32 + ct) * KS + fks) * kTileQ + e % kTileQ];
+        }
+        if (++fks == KS) {
+            fks = 0;
+#pragma unroll
+            for (int i = 0; i < kXPieces; ++i) {
+                id[i] += move;
+                id[i] -= id[i] >= g.N ? g.N : 0;
+            }
+        }
+    };
+    v16f acc[2][kQ];
+    auto step = [&](Step& f, int buf, bool first, float hx, float* hs) {
+        if constexpr (kFloats) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {      // row r = rl + 64 i: 8 bytes of either piece
+                const int r = rl + 64 * i;
+                const float v0 = __uint_as_float(f.x[i][0]), v1 = __uint_as_float(f.x[i][1]), v2 = __uint_as_float(f.x[i][2]), v3 = __uint_as_float(f.x[i][3]);
+                const uint32_t h0 = pack2(v0, v1), h1 = pack2(v2, v3);
+                uint16_t* at = xs[buf] + (r >> 5) * 2 * kFrag + (c4 >> 1) * 256 + (r & 31) * 8 + (c4 & 1) * 4;
+                *reinterpret_cast<uint2*>(at) = make_uint2(h0, h1);
+                *reinterpret_cast<uint2*>(at + kFrag) =
+                    make_uint2(pack2(v0 - low_value(h0), v1 - high_value(h0)), pack2(v2 - low_value(h1), v3 - high_value(h1)));
+            }
+        } else {
+            u32x4 w0, w1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t b = f.x[0][j];
+                const uint32_t p0 = pack2((float)(b & 0xffu), (float)((b >> 8) & 0xffu)), p1 = pack2((float)((b >> 16) & 0xffu), (float)(b >> 24));
+                if (j < 2) { w0[2 * j] = p0; w0[2 * j + 1] = p1; }
+                else { w1[2 * j - 4] = p0; w1[2 * j - 3] = p1; }
+            }
+            u32x4* at = reinterpret_cast<u32x4*>(xs[buf]) + (rl >> 5) * (kFrag / 8) + (rl & 31);
+            at[0] = w0;
+            at[32] = w1;
+        }
+#pragma unroll
+        for (int i = 0; i < kQPieces; ++i) reinterpret_cast<u32x4*>(qs[buf])[i * kBfThreads + tid] = f.q[i];
+        if (first) hs[tid] = -hx;
+        __syncthreads();
+        fetch(f);
+        if (first) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                v16f c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 h = *reinterpret_cast<const float4*>(&hs[wave * 64 + rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                    c[4 * i] = h.x; c[4 * i + 1] = h.y; c[4 * i + 2] = h.z; c[4 * i + 3] = h.w;
+                }
+#pragma unroll
+                for (int ct = 0; ct < kQ; ++ct) acc[rt][ct] = c;
+            }
+        }
+        bf16x8 a[2][XP];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int p = 0; p < XP; ++p)
+                a[rt][p] = reinterpret_cast<const bf16x8*>(xs[buf])[((wave * 2 + rt) * XP + p) * (kFrag / 8) + lane];
+#pragma unroll
+        for (int ct = 0; ct < kQ; ++ct) {
+            const bf16x8 h = reinterpret_cast<const bf16x8*>(qs[buf])[ct * kTileQ + lane];
+            const bf16x8 m = reinterpret_cast<const bf16x8*>(qs[buf])[ct * kTileQ + kFrag / 8 + lane];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                acc[rt][ct] = mfma(a[rt][0], h, acc[rt][ct]);
+                acc[rt][ct] = mfma(a[rt][0], m, acc[rt][ct]);
+                if (XP > 1) acc[rt][ct] = mfma(a[rt][XP - 1], h, acc[rt][ct]);
+            }
+        }
+    };
+    // two steps are under way in registers: a step is 0.3 - 0.6 us of matrix work, less than a load takes
+    Step f0, f1;
+    fetch(f0);
+    fetch(f1);
+    int half = 0;
+    bool odd = false;                          // which of the two holds the next step
+    for (int t = split; t < ntile; t += splits, half ^= 1) {
+        const float hx = (int64_t)t * kGenRows + tid < g.chunk_rows ? g.xhalf[hid] : __builtin_inff();    // such rows enter no list
+        hid += move;
+        hid -= hid >= g.N ? g.N : 0;
+        int ks = 0;
+        if (odd) {
+            step(f1, 1, true, hx, hs[half]);
+            ks = 1;
+        }
+        for (; ks + 1 < KS; ks += 2) {
+            step(f0, 0, ks == 0, hx, hs[half]);
+            step(f1, 1, false, hx, hs[half]);
+        }
+        odd = ks < KS;
+        if (odd) step(f0, 0, ks == 0, hx, hs[half]);
+#pragma unroll
+        for (int ct = 0; ct < kQ; ++ct) {
+            const int64_t q = q0 + ct * 32 + (lane & 31);
+            uint2* list = g.lists + ((size_t)q * g.segs + split * 8 + wave * 2 + (lane >> 5)) * g.seg_cap;
+            float* dense = DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+                take_tile<DENSE>(acc[rt][ct], DENSE ? 0.0f : from[ct * 32 + (lane & 31)], (uint32_t)t * kGenRows + wave * 64 + rt * 32 + 4 * (lane >> 5), dense, list, g.seg_cap, count[ct]);
+        }
+    }
+    if (!DENSE) {
+#pragma unroll
+        for (int ct = 0; ct < kQ; ++ct)
+            g.seg_count[(size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + split * 8 + wave * 2 + (lane >> 5)] = count[ct];
+    }
+}
+
+constexpr int kSelectBins = 1024;
+
+__host__ __device__ inline int best_capacity(int k) { return 2 * k + 256 < 1024 ? 2 * k + 256 : 1024; }
+
+// One workgroup per query: what is kept of the list so far and of the chunk's new pairs (dense: of the first chunk's
+// values); after the last chunk the exact distances of the kept vectors and the k best of them.
+// Entries: bits of s~ << 32 | place in the database order.  (Bins are equal pieces of the value range, not of the bit
+// patterns: s~ changes sign, and most of the patterns between its smallest and largest value are next to zero.)
+template <typename Elem>
+__global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int dense, int last) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // kDense
+    __shared__ uint32_t hist[kSelectBins];
+    __shared__ uint32_t part[kBfThreads / kWave];
+    __shared__ float bounds[2 * kBfThreads / kWave];
+    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k;
+    const int64_t q = blockIdx.x;
+    if (g.flagged[q]) return;
+    unsigned long long* best = g.best + (size_t)q * best_capacity(k);
+    if (tid == 0) {
+        misc[3] = misc[4] = 0u;
+    }
+    for (int e = tid; e < kSelectBins; e += kBfThreads) hist[e] = 0u;
+    __syncthreads();
+
+    // ---- everything into LDS -----------------------------------------------------------------------------------
+    int n;
+    if (dense) {
+        n = (int)g.chunk_rows;
+        const float* row = g.dense + (size_t)q * kDense;
+        for (int e = tid; e < n; e += kBfThreads) keys[e] = ((unsigned long long)__float_as_uint(row[e]) << 32) | (uint32_t)e;
+    } else {
+        const int nb = (int)g.best_count[q];
+        for (int e = tid; e < nb; e += kBfThreads) keys[e] = best[e];
+        n = nb;
+        for (int s0 = 0; s0 < g.segs; s0 += kBfThreads) {
+            const int s = s0 + tid;
+            const uint32_t c = s < g.segs ? g.seg_count[(size_t)q * g.segs + s] : 0u;
+            uint32_t total;
+            const uint32_t at = (uint32_t)n + block_exclusive_sum(min(c, (uint32_t)kDense), part, total);
+            if (c > (uint32_t)g.seg_cap || (uint32_t)n + total > (uint32_t)kDense) misc[4] = 1u;
+            __syncthreads();                         // (its next change comes after a barrier that everyone reaches past this test)
+            if (misc[4]) break;
+            const uint2* list = g.lists + ((size_t)q * g.segs + s) * g.seg_cap;
+            for (uint32_t i = 0; i < c; ++i)
+                keys[at + i] = ((unsigned long long)list[i].y << 32) | (uint32_t)(g.chunk_pos + list[i].x);
+            n += (int)total;
+        }
+    }
+    __syncthreads();
+    const float xm = g.xhalf[g.N];
+    const float err = error_bound(g, g.qnorm[q], xm);
+    auto give_up = [&]() {                           // to the exact scan
+        if (tid == 0) {
+            g.flagged[q] = 1u;
+            g.todo[atomicAdd(&g.control[kBfTodo], 1u)] = (uint32_t)q;
+        }
+    };
+    if (misc[4] || !(err < 1e30f)) {                 // the same for the whole workgroup; below it every s~ is finite
+        give_up();
+        return;
+    }
+    // ---- an upper bound of the k-th smallest: the end of its bin ---------------------------------------------------
+    auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
+    float lo = __builtin_inff(), hi = -__builtin_inff();
+    for (int e = tid; e < n; e += kBfThreads) {
+        lo = fminf(lo, value(e));
+        hi = fmaxf(hi, value(e));
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, off, kWave));
+        hi = fmaxf(hi, __shfl_xor(hi, off, kWave));
+    }
+    if (lane == 0) {
+        bounds[2 * wave] = lo;
+        bounds[2 * wave + 1] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kBfThreads / kWave; ++w) {
+        lo = fminf(lo, bounds[2 * w]);
+        hi = fmaxf(hi, bounds[2 * w + 1]);
+    }
+    const float scale = hi > lo ? (float)kSelectBins / (hi - lo) : 0.0f;
+    for (int e = tid; e < n; e += kBfThreads) atomicAdd(&hist[min((int)((value(e) - lo) * scale), kSelectBins - 1)], 1u);
+    __syncthreads();
+    {
+        constexpr int bpt = kSelectBins / kBfThreads;
+        uint32_t h[bpt], sum = 0, total;
+#pragma unroll
+        for (int j = 0; j < bpt; ++j) sum += h[j] = hist[tid * bpt + j];
+        uint32_t c = block_exclusive_sum(sum, part, total);
+#pragma unroll
+        for (int j = 0; j < bpt; ++j) {
+            if (c < (uint32_t)k && (uint32_t)k <= c + h[j]) misc[2] = (uint32_t)(tid * bpt + j);
+            c += h[j];
+        }
+    }
+    __syncthreads();
+    // the end of the bin, and E for the rounding of the bin numbers (a few units of the values' last place; E is more)
+    const float edge = fminf(hi, lo + (scale > 0.0f ? (float)(misc[2] + 1u) / scale : 0.0f) + err);
+    const float keep = edge + 2.0f * err;
+    // ---- keep what can still be among the k nearest ---------------------------------------------------------------
+    const int cap = best_capacity(k);
+    for (int e0 = 0; e0 < n; e0 += kBfThreads) {     // in place: entry e moves to a place <= e that has been read
+        const int e = e0 + tid;
+        const unsigned long long key = e < n ? keys[e] : ~0ull;
+        const bool take = e < n && __uint_as_float((uint32_t)(key >> 32)) <= keep;
+        const unsigned long long m = __ballot(take);
+        uint32_t at = 0;
+        __syncthreads();                             // this round's entries have been read
+        if (lane == 0 && m) at = atomicAdd(&misc[3], (uint32_t)__popcll(m));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (take) keys[at] = key;
+    }
+    __syncthreads();
+    n = (int)misc[3];
+    if (n > cap) {
+        give_up();
+        return;
+    }
+    if (!last) {
+        for (int e = tid; e < n; e += kBfThreads) best[e] = keys[e];
+        if (tid == 0) {
+            g.best_count[q] = (uint32_t)n;
+            g.edge[q] = edge;
+        }
+        return;
+    }
+    // ---- exact distances of the kept vectors, the k best by (distance, id) ------------------------------------------
+    float4* sy = reinterpret_cast<float4*>(smem + sizeof(unsigned long long) * kDense);        // D floats
+    const int D = g.D;
+    for (int c4 = tid; c4 < D / 4; c4 += kBfThreads) sy[c4] = reinterpret_cast<const float4*>(g.queries + (size_t)q * D)[c4];
+    const int npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
+    for (int e = n + tid; e < npad; e += kBfThreads) keys[e] = ~0ull;
+    __syncthreads();
+    const int lpr = lanes_per_row(D / Piece<Elem>::kElems);
+    const int per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
+#pragma unroll 2
+    for (int e0 = 0; e0 < n; e0 += per_wave * (kBfThreads / kWave)) {
+        const int e = e0 + wave * per_wave + sub;
+        const int64_t id = e < n ? (int64_t)(((uint64_t)(uint32_t)keys[e] * g.step) % g.N) : -1;
+        const float d = row_distance(reinterpret_cast<const Elem*>(g.vectors), id, D, reinterpret_cast<const float*>(sy), lpr, l);
+        if (e < n && l == 0) keys[e] = ((unsigned long long)mono_key(d) << 32) | (uint32_t)id;
+    }
+    block_sort_lds<4>(keys, npad, tid, kBfThreads);
+    for (int e = tid; e < k; e += kBfThreads) {
+        const unsigned long long key = keys[e];
+        g.out_ids[(size_t)q * k + e] = (int64_t)(uint32_t)key;
+        g.out_dists[(size_t)q * k + e] = mono_inv((uint32_t)(key >> 32));
+    }
+}
+
+// The queries the filter gave up on: exact distances to every vector, what beats the k-th best so far is kept in LDS and
+// the k best are selected again whenever that may fill.  One workgroup per query at a time.
+template <typename Elem>
+__global__ __launch_bounds__(kBfThreads) void bf_scan_kernel(BruteArgs g) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // kBfScanKeys
+    float4* sy = reinterpret_cast<float4*>(smem + sizeof(unsigned long long) * kBfScanKeys);
+    __shared__ uint32_t pending;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k, D = g.D;
+    const int lpr = lanes_per_row(D / Piece<Elem>::kElems);
+    const int per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
+    const int per_iter = per_wave * (kBfThreads / kWave);
+    const uint32_t ntodo = g.control[kBfTodo];
+    for (uint32_t i = blockIdx.x; i < ntodo; i += gridDim.x) {
+        const int64_t q = g.todo[i];
+        __syncthreads();
+        for (int c4 = tid; c4 < D / 4; c4 += kBfThreads) sy[c4] = reinterpret_cast<const float4*>(g.queries + (size_t)q * D)[c4];
+        for (int e = tid; e < k; e += kBfThreads) keys[e] = ~0ull;
+        if (tid == 0) pending = 0u;
+        __syncthreads();
+        uint32_t tau = 0xffffffffu;
+        for (int64_t x0 = 0; x0 < (int64_t)g.N; x0 += 4 * per_iter) {
+#pragma unroll 2
+            for (int it = 0; it < 4; ++it) {
+                const int64_t row = x0 + it * per_iter + wave * per_wave + sub;
+                const bool have = row < (int64_t)g.N;
+                const float d = row_distance(reinterpret_cast<const Elem*>(g.vectors), have ? row : -1, D, reinterpret_cast<const float*>(sy), lpr, l);
+                const uint32_t kb = mono_key(d);
+                // vectors come in id order: an equal distance that arrives later has the larger id and never wins
+                if (have && l == 0 && kb < tau) keys[k + atomicAdd(&pending, 1u)] = ((unsigned long long)kb << 32) | (uint32_t)row;
             }
             __syncthreads();
-            const uint32_t pending = counter[0];
-            if (pending + 4 * kBfSelThreads > (uint32_t)kBfBuf || b4 + kBfSelThreads >= n4) reselect(pending);
+            const uint32_t np = pending;
+            __syncthreads();
+            if (np + 4u * (uint32_t)per_iter > (uint32_t)(kBfScanKeys - k) || x0 + 4 * per_iter >= (int64_t)g.N) {
+                const int n = k + (int)np, npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
+                for (int e = n + tid; e < npad; e += kBfThreads) keys[e] = ~0ull;
+                if (tid == 0) pending = 0u;
+                block_sort_lds<8>(keys, npad, tid, kBfThreads);
+                tau = (uint32_t)(keys[k - 1] >> 32);
+                __syncthreads();
+            }
         }
-    } else
-    for (int64_t base = 0; base < nx; base += kBfSelThreads) {
-        const int64_t c = base + tid;
-        bool take = false;
-        unsigned long long key = 0;
-        if (c < nx) {
-            const uint32_t kb = mono_key(row[c]);
-            take = kb < tau;
-            key = ((unsigned long long)kb << 32) | (uint32_t)(x0 + c);
-        }
-        const unsigned long long m = __ballot(take);
-        if (take) {
-            const int leader = __ffsll((long long)m) - 1;
-            uint32_t at = 0;
-            if (lane == leader) at = atomicAdd(counter, (uint32_t)__popcll(m));
-            at = (uint32_t)__shfl((int)at, leader, kWave);
-            keys[k + at + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = key;
-        }
-        __syncthreads();
-        const uint32_t pending = counter[0];
-        if (pending + kBfSelThreads > (uint32_t)kBfBuf || base + kBfSelThreads >= nx) reselect(pending);
-    }
-    if (last) {
-        for (int e = tid; e < k; e += kBfSelThreads) {
+        for (int e = tid; e < k; e += kBfThreads) {
             const unsigned long long key = keys[e];
             g.out_ids[(size_t)q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
             g.out_dists[(size_t)q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
         }
-    } else {
-        for (int e = tid; e < k; e += kBfSelThreads) g.best[(size_t)q * k + e] = keys[e];
     }
 }
 
-hipError_t launch_row_norms(const void* x, int elem_bytes, int64_t n, int D, float* out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const unsigned tb = 256, nb = (unsigned)((n + tb - 1) / tb);
-    if (elem_bytes == 4) hipLaunchKernelGGL(row_norms_kernel<float>, dim3(nb), dim3(tb), 0, s, static_cast<const float*>(x), n, D, out);
-    else hipLaunchKernelGGL(row_norms_kernel<uint8_t>, dim3(nb), dim3(tb), 0, s, static_cast<const uint8_t*>(x), n, D, out);
+uint64_t gcd_u64(uint64_t a, uint64_t b) {
+    while (b) {
+        const uint64_t t = a % b;
+        a = b;
+        b = t;
+    }
+    return a;
+}
+
+int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
+
+// How one call is cut: sizes of the workspace's pieces and the launch shapes.
+struct Plan {
+    bool stationary;
+    int KS;
+    int64_t batch, batch_pad;        // queries at a time, padded to whole workgroup tiles
+    int groups, splits, segs, seg_cap;
+    int growth;
+};
+
+Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
+    Plan p;
+    p.KS = (D + 15) / 16;
+    p.stationary = elem_bytes == 1 && p.KS <= 8;
+    if (p.stationary && p.KS != 6) p.KS = 8;                        // compiled for 96 and 128 dimensions
+    const int tile = p.stationary ? 256 : kGenQueries;
+    p.batch = nq < 16384 ? nq : 16384;
+    p.batch_pad = round_up(p.batch, tile);
+    p.groups = (int)(p.batch_pad / tile);
+    // as many workgroups as are resident at once (three or two per compute unit): no second round of a few
+    const int slots = p.stationary ? 768 : 512;
+    p.splits = p.groups >= slots ? 1 : slots / p.groups;
+    if (p.splits > 8) p.splits -= p.splits % 8;
+    p.segs = p.splits * (p.stationary ? 2 : 8);
+    // Chunks grow by this factor, and about k times as many pairs pass per chunk and query.  A pair costs a wavefront some
+    // tens of cycles, a chunk more about 15 us: many queries take a small factor, few queries as large a one as the
+    // select workgroup's LDS allows (twice k * growth + the list kept so far).
+    const int most = 1600 / k < 2 ? 2 : (1600 / k > 64 ? 64 : 1600 / k);
+    p.growth = p.batch * k < 200000 ? most : (most < 4 ? most : 4);
+    p.seg_cap = 4 * ((k * p.growth + p.segs - 1) / p.segs) + 16;
+    return p;
+}
+
+struct Carver {
+    unsigned char* base;
+    size_t used = 0;
+    template <typename T>
+    T* take(size_t count) {
+        T* p = base ? reinterpret_cast<T*>(base + used) : nullptr;
+        used += (count * sizeof(T) + 255) / 256 * 256;
+        return p;
+    }
+};
+
+size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
+    Carver c{base};
+    BruteArgs v = {};
+    v.control = c.take<uint32_t>(kBfControl);
+    v.flagged = c.take<uint32_t>(p.batch_pad);
+    v.todo = c.take<uint32_t>(p.batch_pad);
+    v.qnorm = c.take<float>(p.batch_pad);
+    v.edge = c.take<float>(p.batch_pad);
+    v.best_count = c.take<uint32_t>(p.batch_pad);
+    v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
+    v.dense = c.take<float>((size_t)p.batch_pad * kDense);
+    v.seg_count = c.take<uint32_t>((size_t)p.batch_pad * p.segs);
+    v.lists = c.take<uint2>((size_t)p.batch_pad * p.segs * p.seg_cap);
+    v.best = c.take<unsigned long long>((size_t)p.batch_pad * best_capacity(k));
+    if (a) *a = v;
+    return c.used;
+}
+
+template <typename Elem, bool DENSE>
+void launch_filter(const Plan& p, const BruteArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)(p.splits * p.groups)), block(kBfThreads);
+    if (p.stationary && p.KS == 6) {
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<6, 1, DENSE>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<6, 2, DENSE>), grid, block, 0, s, a);
+    } else if (p.stationary) {
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<8, 1, DENSE>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<8, 2, DENSE>), grid, block, 0, s, a);
+    } else {
+        hipLaunchKernelGGL((bf_filter_kernel<Elem, DENSE>), grid, block, 0, s, a);
+    }
+}
+
+template <typename Elem>
+hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int64_t* out_ids, float* out_dists, hipStream_t s) {
+    const size_t select_lds = sizeof(unsigned long long) * kDense + sizeof(float) * a.D;
+    const size_t scan_lds = sizeof(unsigned long long) * kBfScanKeys + sizeof(float) * a.D;
+    hipError_t e;
+    if (select_lds + 8192 > 64 * 1024 || scan_lds + 64 > 64 * 1024) {
+        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(bf_select_kernel<Elem>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)select_lds)) != hipSuccess) return e;
+        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(bf_scan_kernel<Elem>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)scan_lds)) != hipSuccess) return e;
+    }
+    for (int64_t b0 = 0; b0 < nq; b0 += p.batch) {
+        a.nq = nq - b0 < p.batch ? nq - b0 : p.batch;
+        a.queries = queries + (size_t)b0 * a.D;
+        a.out_ids = out_ids + (size_t)b0 * a.k;
+        a.out_dists = out_dists + (size_t)b0 * a.k;
+        hipLaunchKernelGGL(bf_begin_kernel, dim3((unsigned)((a.nq + kBfControl + 255) / 256)), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(kBfThreads), 0, s, a);
+        for (uint64_t pos = 0; pos < a.N;) {
+            const bool dense = pos == 0;
+            uint64_t rows = dense ? (uint64_t)kDense : pos * (uint64_t)p.growth;
+            if (rows > a.N - pos) rows = a.N - pos;
+            a.chunk_pos = pos;
+            a.chunk_rows = (int64_t)rows;
+            if (dense) launch_filter<Elem, true>(p, a, s);
+            else launch_filter<Elem, false>(p, a, s);
+            pos += rows;
+            hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, pos >= a.N ? 1 : 0);
+        }
+        hipLaunchKernelGGL((bf_scan_kernel<Elem>), dim3((unsigned)(a.nq < 1024 ? a.nq : 1024)), dim3(kBfThreads), scan_lds, s, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace
+
+size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k) {
+    return carve(make_plan(nq, D, elem_bytes, k), k, nullptr, nullptr);
+}
+
+hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(fill_word_kernel, dim3(1), dim3(1), 0, s, reinterpret_cast<uint32_t*>(out) + N, 0u);
+    const dim3 grid((unsigned)(N / 16 + 1 < 4096 ? N / 16 + 1 : 4096)), block(kBfThreads);
+    if (elem_bytes == 1) hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, out);
+    else hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, static_cast<const float*>(vectors), (int64_t)N, D, out);
     return hipGetLastError();
 }
 
-size_t brute_select_lds_bytes(int k) { return sizeof(unsigned long long) * next_pow2(k + kBfBuf) + 16; }
-
-hipError_t launch_brute_chunk(const BruteArgs& a, int64_t x0, int64_t nx, bool first, bool last, hipStream_t s) {
-    const dim3 grid((unsigned)((nx + kBfTile - 1) / kBfTile), (unsigned)((a.nq + kBfTile - 1) / kBfTile));
-    if (a.elem_bytes == 4) hipLaunchKernelGGL(bf_distance_kernel<float>, grid, dim3(kBfThreads), 0, s, a, x0, nx);
-    else hipLaunchKernelGGL(bf_distance_kernel<uint8_t>, grid, dim3(kBfThreads), 0, s, a, x0, nx);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(bf_select_kernel, dim3((unsigned)a.nq), dim3(kBfSelThreads), brute_select_lds_bytes(a.k), s, a, x0, nx,
-                       first ? 1 : 0, last ? 1 : 0);
-    return hipGetLastError();
+hipError_t launch_brute_force(const void* vectors, const float* half_norms, int elem_bytes, uint64_t N, int D, const float* queries,
+                              int64_t nq, int k, void* workspace, int64_t* out_ids, float* out_dists, hipStream_t s) {
+    const Plan p = make_plan(nq, D, elem_bytes, k);
+    BruteArgs a;
+    carve(p, k, static_cast<unsigned char*>(workspace), &a);
+    a.vectors = vectors; a.xhalf = half_norms; a.N = N; a.D = D; a.k = k; a.KS = p.KS;
+    a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
+    a.step = (uint64_t)((double)N * 0.6180339887498949) | 1u;
+    while (gcd_u64(a.step, N) != 1) a.step += 2;
+    // |s~ - s|: with u = 2^-9 the rounding unit of bf16, a second piece leaves u^2 of a number, the product of two second
+    // pieces is u^2 of a product: u^2 for byte vectors (the query's remainder), 3 u^2 for floats, each times ||q|| ||x||
+    // (Cauchy-Schwarz), with 3 % for the terms of higher order.  The running sum is rounded once per matrix
+    // instruction (2^-23 covers truncation; 16 more for what happens inside one), and its size is at most
+    // ||q|| ||x|| + ||x||^2 / 2.  The norm's own sum has D / 64 + 16 roundings.
+    const int pieces = elem_bytes == 1 ? 2 : 3;
+    const float u2 = 1.03f / 262144.0f, rounding = (float)(pieces * p.KS + 16) / 8388608.0f;
+    a.err_dot = (elem_bytes == 1 ? 1.0f : 3.0f) * u2 + rounding;
+    a.err_norm = 0.5f * (rounding + (float)(D / 64 + 16) / 16777216.0f);
+    return elem_bytes == 1 ? run<uint8_t>(p, a, queries, nq, out_ids, out_dists, s) : run<float>(p, a, queries, nq, out_ids, out_dists, s);
 }
 
 }  // namespace pqt

@@ -11,52 +11,11 @@
 // sorted by the workgroup.
 #include "pqt_device.hpp"
 #include "pqt_kernels.hpp"
+#include "row_distance.hpp"
 
 namespace pqt {
 
 constexpr int kExactThreads = 256;
-
-// One 16-byte piece of a row: kPiece<Elem> elements; adds their squared differences to acc in
-// ascending dimension.  y points at the query's elements of the same dimensions (LDS).
-template <typename Elem>
-struct Piece;
-template <>
-struct Piece<float> {
-    static constexpr int kElems = 4;
-    static __device__ __forceinline__ float add(const float* row, int piece, const float* y, float acc) {
-        const float4 x = reinterpret_cast<const float4*>(row)[piece];
-        const float4 v = reinterpret_cast<const float4*>(y)[piece];
-        float d = v.x - x.x;
-        acc = fmaf(d, d, acc);
-        d = v.y - x.y;
-        acc = fmaf(d, d, acc);
-        d = v.z - x.z;
-        acc = fmaf(d, d, acc);
-        d = v.w - x.w;
-        return fmaf(d, d, acc);
-    }
-};
-template <>
-struct Piece<uint8_t> {
-    static constexpr int kElems = 16;
-    static __device__ __forceinline__ float add(const uint8_t* row, int piece, const float* y, float acc) {
-        const uint4 x = reinterpret_cast<const uint4*>(row)[piece];
-        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float4 v = reinterpret_cast<const float4*>(y)[piece * 4 + j];
-            float d = v.x - (float)(w[j] & 0xffu);
-            acc = fmaf(d, d, acc);
-            d = v.y - (float)((w[j] >> 8) & 0xffu);
-            acc = fmaf(d, d, acc);
-            d = v.z - (float)((w[j] >> 16) & 0xffu);
-            acc = fmaf(d, d, acc);
-            d = v.w - (float)(w[j] >> 24);
-            acc = fmaf(d, d, acc);
-        }
-        return acc;
-    }
-};
 
 template <typename Elem>
 __global__ __launch_bounds__(kExactThreads) void exact_rerank_kernel(ExactArgs g) {
@@ -73,11 +32,7 @@ __global__ __launch_bounds__(kExactThreads) void exact_rerank_kernel(ExactArgs g
     for (int e = ks + tid; e < npad; e += kExactThreads) keys[e] = ~0ull;
     __syncthreads();
 
-    // lanes per row: a power of two, at most 64, one 16-byte piece per lane and step if possible
-    constexpr int pe = Piece<Elem>::kElems;
-    const int npieces = D / pe;                      // D is a multiple of the piece (checked by the launcher)
-    int lpr = 1;
-    while (lpr < kWave && lpr < npieces) lpr <<= 1;
+    const int lpr = lanes_per_row(D / Piece<Elem>::kElems);      // D is a multiple of the piece (checked by the launcher)
     const int rows_per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
     const int rows_per_iter = rows_per_wave * (kExactThreads / kWave);
     const float* y = reinterpret_cast<const float*>(sy);
@@ -85,12 +40,7 @@ __global__ __launch_bounds__(kExactThreads) void exact_rerank_kernel(ExactArgs g
     for (int c0 = 0; c0 < ks; c0 += rows_per_iter) {
         const int c = c0 + wave * rows_per_wave + sub;
         const int64_t id = c < ks ? g.short_ids[q * ks + c] : -1;
-        float acc = 0.0f;
-        if (id >= 0) {
-            const Elem* row = X + (size_t)id * D;
-            for (int piece = l; piece < npieces; piece += lpr) acc = Piece<Elem>::add(row, piece, y, acc);
-        }
-        for (int off = 1; off < lpr; off <<= 1) acc += __shfl_xor(acc, off, kWave);   // same order in every lane
+        const float acc = row_distance(X, id, D, y, lpr, l);
         if (c < ks && l == 0)
             keys[c] = id >= 0 ? (((unsigned long long)mono_key(acc) << 32) | (uint32_t)id) : ~0ull;
     }

@@ -154,24 +154,47 @@ struct ExactArgs {
 size_t exact_lds_bytes(int D, int k_short);
 hipError_t launch_exact_rerank(const ExactArgs& a, hipStream_t s);
 
+// Brute force: see brute_force.hip.  Words of BruteArgs::control:
+enum { kBfSecond = 0,          // a query has a second bf16 piece
+       kBfTodo = 1,            // queries in todo[]
+       kBfControl = 64 };
+constexpr int kBfScanKeys = 2048;   // entries a scanning workgroup holds: the k best and what is pending
 struct BruteArgs {
-    int64_t nq;
-    int D, k;
-    int elem_bytes;               // 4: fp32 vectors, 1: uint8 vectors
-    int64_t chunk;                // database vectors per pass = row stride of dist
+    int64_t nq;                   // queries of the batch
+    uint64_t N;
+    int D, k, KS;                 // KS: steps of 16 dimensions
     const float* queries;         // nq x D
     const void* vectors;          // N x D
-    const float* qnorm;           // nq
-    const float* xnorm;           // N
-    float* dist;                  // nq x chunk
-    unsigned long long* best;     // nq x k running result between passes
+    const float* xhalf;           // ||x||^2 / 2 of every vector, and behind them the largest ||x||
     int64_t* out_ids;             // nq x k
     float* out_dists;             // nq x k
+    uint64_t step;                // the database order: place i is vector (i * step) mod N
+    float err_dot, err_norm;      // error bound: err_dot ||q|| X + err_norm X^2, X the largest ||x||
+    // the current chunk: chunk_rows vectors from place chunk_pos on
+    uint64_t chunk_pos;
+    int64_t chunk_rows;
+    // workspace
+    uint32_t* control;
+    uint32_t* flagged;            // nq: 1 = left to the exact scan
+    uint32_t* todo;               // those queries
+    float* qnorm;                 // ||q||
+    float* edge;                  // upper bound of the k-th smallest value so far
+    uint32_t* best_count;         // entries of best
+    uint16_t* qfrag;              // queries, two bf16 pieces, operand layout
+    float* dense;                 // values of the first chunk, a row per query
+    int splits;                   // workgroups that share a query group's database tiles
+    int segs, seg_cap;            // lists per query and entries per list
+    uint32_t* seg_count;          // nq x segs: pairs that passed (may exceed seg_cap: overflow)
+    uint2* lists;                 // nq x segs x seg_cap: (row of the chunk, value)
+    unsigned long long* best;     // what is kept between chunks
 };
-hipError_t launch_row_norms(const void* x, int elem_bytes, int64_t n, int D, float* out, hipStream_t s);
-size_t brute_select_lds_bytes(int k);
-// distances of all queries to database vectors x0 .. x0+nx-1, then the running k best
-hipError_t launch_brute_chunk(const BruteArgs& a, int64_t x0, int64_t nx, bool first, bool last, hipStream_t s);
+// workspace of one call, in bytes
+size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k);
+// half squared norms of the vectors and, behind them, the largest norm: N + 1 floats
+hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s);
+// the k nearest of N vectors (4: fp32, 1: uint8 elements) to every query; k <= min(N, 256)
+hipError_t launch_brute_force(const void* vectors, const float* half_norms, int elem_bytes, uint64_t N, int D, const float* queries,
+                              int64_t nq, int k, void* workspace, int64_t* out_ids, float* out_dists, hipStream_t s);
 
 // raise the dynamic-LDS ceiling of each kernel (once per device)
 hipError_t configure_traverse(size_t max_dynamic_lds);

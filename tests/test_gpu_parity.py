@@ -778,6 +778,67 @@ def test_brute_force(pqt, tiny, tmp_path):
         pqt.pqt_index_free(gix)
 
 
+@pytest.mark.parametrize("kind, N, D, nq, k", [
+    ("bytes", 255, 16, 1, 255),            # one partial chunk, k close to N
+    ("bytes", 4096, 96, 257, 100),         # exactly the first chunk; one query past a workgroup's 256
+    ("bytes", 4097, 128, 64, 256),         # one vector in the second chunk, largest k
+    ("bytes", 70_001, 160, 129, 33),       # more dimensions than the stationary kernel takes
+    ("bytes, real queries", 30_000, 128, 65, 50),     # queries with a second bf16 piece
+    ("floats", 4100, 4, 3, 7),             # one step of sixteen dimensions, three quarters padding
+    ("floats", 20_011, 20, 128, 128),      # an odd number of steps, the last one partial
+    ("floats", 9_000, 200, 130, 10),
+    ("ties", 30_000, 128, 9, 50),          # all vectors equal: the lists overflow, the exact scan answers
+    ("ties, floats", 5_000, 36, 5, 3),
+    ("sorted", 40_000, 128, 40, 100),      # vectors stored in order of their first dimension
+    ("huge", 5_000, 32, 4, 5),             # squares overflow: the exact scan answers
+])
+def test_brute_force_edges(pqt, kind, N, D, nq, k):
+    """The filter's tile and chunk edges against distances in float64 (on the GPU by torch).  A distance is a sum
+    of D squares in fp32: relative error below (D + 2) 2^-24, no floor; ids are those of an ascending sort of the
+    call's own distances, and the k-th distance is the true one to that bound."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    dev = torch.device("cuda")
+    if "floats" in kind or kind == "huge":
+        X = torch.rand((N, D), generator=gen, device=dev) * (1e25 if kind == "huge" else 1.0)
+        Y = torch.rand((nq, D), generator=gen, device=dev) * (1e25 if kind == "huge" else 1.0)
+    else:
+        X = torch.randint(0, 256, (N, D), generator=gen, device=dev, dtype=torch.int64).to(torch.uint8)
+        Y = torch.randint(0, 256, (nq, D), generator=gen, device=dev, dtype=torch.int64).float()
+        if "real" in kind:
+            Y = Y + torch.rand((nq, D), generator=gen, device=dev)
+    if "ties" in kind:
+        X[:] = X[0]
+    if kind == "sorted":
+        X = X[torch.argsort(X[:, 0].to(torch.int32), stable=True)].contiguous()
+    ix = pqt.pqt_index_from_arrays(dict(
+        N=N, H=1, D=D, P=1, k1=1, k2=1, M=1, T=1, C=256, C1=np.zeros((1, 1, D)), C2=np.zeros((1, 1, 1, D)),
+        tbl_i=np.zeros((1, 256)), tbl_j=np.zeros((1, 256)), tbl_lam=np.zeros((1, 256)), cc=np.zeros((1, 1, 1)),
+        offsets=np.array([0, N]), ids=np.arange(N), codes=np.zeros((N, 1))))
+    try:
+        pqt.pqt_index_set_vectors(ix, X)
+        for rep in range(2):                                 # the second call works in the first one's memory
+            ids, d = pqt.pqt_brute_force(ix, Y, k)
+            torch.cuda.synchronize()
+            if kind == "huge":
+                assert torch.isinf(d).all() and torch.equal(ids, torch.arange(k, device=dev).expand(nq, k))
+                continue
+            true = torch.stack([((X.double() - y) ** 2).sum(1) for y in Y.double()])
+            bound = (D + 2) * 2.0 ** -24
+            own = true.gather(1, ids)
+            assert (d.double() - own).abs().le(bound * own).all()
+            assert (d.double() - true.sort(1).values[:, :k]).abs().le(2 * bound * own).all()
+            order = torch.argsort(ids, dim=1, stable=True)
+            order = order.gather(1, torch.argsort(d.gather(1, order), dim=1, stable=True))
+            assert torch.equal(order, torch.arange(k, device=dev).expand(nq, k)), "not sorted by (distance, id)"
+            assert all(len(set(r)) == k for r in ids.cpu().tolist())
+            if "bytes" == kind or "ties" == kind or "sorted" == kind:      # whole numbers: exact
+                key = true * N + torch.arange(N, device=dev)               # (distance, id), exact in float64
+                assert torch.equal(ids, key.sort(1).indices[:, :k])
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
