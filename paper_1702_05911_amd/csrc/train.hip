@@ -9,7 +9,7 @@
 //
 // Everything per vector runs in the kernels below.  Results do not depend on the order in which the
 // hardware schedules work: assignments break ties by the smaller centroid number, cell sums are taken
-// over the members in ascending vector order in fixed slices (double precision), re-seeding takes the
+// over the members in ascending vector order in fixed chunks (double precision), re-seeding takes the
 // farthest vector with the smallest number.
 #include <hipcub/hipcub.hpp>
 
@@ -29,6 +29,10 @@ namespace pqt {
 namespace {
 
 constexpr int kTrainThreads = 256;
+constexpr int kTile = kTrainThreads;       // vectors a workgroup works on at a time, one per thread
+constexpr int kSlab = 32;                  // dimensions staged in LDS at a time
+constexpr int kSlabStride = kSlab + 4;     // a lane's 16-byte reads fall into different banks
+constexpr uint32_t kMaxChunks = 2048;      // chunks of vectors aimed at: eight workgroups per compute unit
 
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
     for (int off = 32; off > 0; off >>= 1) {
@@ -40,76 +44,352 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
     return v;
 }
 
+// One batch of Lloyd runs: G groups of k centroids each, G / P groups per tree part.  Level 1 has one group per part (all
+// vectors), level 2 one per level-1 cell.  Vectors are named by their position in their part's member list.
+struct LloydArgs {
+    const float* X;              // n x D
+    uint64_t n;
+    int D, dp, P, G, k;
+    int kp;                      // k rounded up to the centroids a thread works on at a time
+    int wide;                    // rows and slices are 16-byte aligned
+    const uint32_t* members;     // [P][n]: position -> vector number (ascending inside a group); null: the same
+    const uint2* range;          // [G]: the group's positions
+    const uint32_t* chunk_off;   // [G + 1]: the group's chunks
+    const uint4* chunks;         // (group, first position, end): consecutive pieces of a group
+    uint8_t* frozen;             // [G]
+    float* cen;                  // [G][k][dp]
+    float* cenI;                 // [G][ceil(dp / 4)][kp][4]: four dimensions of all centroids side by side
+    double* sums;                // [chunk][k][dp]
+    uint32_t* counts;            // [chunk][k]
+    float* dmin;                 // [P][n]
+    uint32_t* label;             // [P][n]: written instead of sums when not null
+};
+
+__device__ __forceinline__ void put_centroid(const LloydArgs& g, int grp, int j, int d, float v) {
+    g.cen[((size_t)grp * g.k + j) * g.dp + d] = v;
+    g.cenI[(((size_t)grp * ((g.dp + 3) / 4) + d / 4) * g.kp + j) * 4 + d % 4] = v;
+}
+
 // Start centroids of every group (Sec. 2.1: Lloyd iterations need a start): k members at evenly spaced
 // places of the group's member list.  A group with no more than k members is frozen: its members are
 // centroids themselves, the remaining centroids repeat the members' mean (the parent centroid when
 // the group is empty).  One workgroup per group.
-__global__ __launch_bounds__(kTrainThreads) void lloyd_init_kernel(const float* X, int D, int col0, int dp,
-                                                                    const uint32_t* members, const uint32_t* grp_off,
-                                                                    int k, const float* parent, float* cen, float* cenT,
-                                                                    uint8_t* frozen) {
-    const int g = blockIdx.x, tid = threadIdx.x;
-    const uint32_t lo = grp_off[g], hi = grp_off[g + 1];
-    const uint32_t ng = hi - lo;
-    if (tid == 0) frozen[g] = ng <= (uint32_t)k ? 1 : 0;
+__global__ __launch_bounds__(kTrainThreads) void lloyd_init_kernel(LloydArgs g, const float* parent) {
+    const int grp = blockIdx.x, tid = threadIdx.x, dp = g.dp, k = g.k;
+    const int p = grp / (g.G / g.P), col0 = p * dp;
+    const uint2 rg = g.range[grp];
+    const uint32_t ng = rg.y - rg.x;
+    const uint32_t* mem = g.members ? g.members + (size_t)p * g.n : nullptr;
+    if (tid == 0) g.frozen[grp] = ng <= (uint32_t)k ? 1 : 0;
+    const size_t words = (size_t)((dp + 3) / 4) * g.kp * 4;       // the padding stays zero
+    for (size_t e = tid; e < words; e += kTrainThreads) g.cenI[(size_t)grp * words + e] = 0.0f;
+    __syncthreads();
     for (int e = tid; e < k * dp; e += kTrainThreads) {
         const int j = e / dp, d = e - j * dp;
         float v;
         if (ng > (uint32_t)k) {
-            const uint32_t at = lo + (uint32_t)(((unsigned long long)j * ng) / (unsigned)k);
-            const uint32_t row = members ? members[at] : at;
-            v = X[(size_t)row * D + col0 + d];
+            const uint32_t at = rg.x + (uint32_t)(((unsigned long long)j * ng) / (unsigned)k);
+            v = g.X[(size_t)(mem ? mem[at] : at) * g.D + col0 + d];
         } else if ((uint32_t)j < ng) {
-            const uint32_t row = members ? members[lo + j] : lo + j;
-            v = X[(size_t)row * D + col0 + d];
+            v = g.X[(size_t)(mem ? mem[rg.x + j] : rg.x + j) * g.D + col0 + d];
         } else if (ng == 0) {
-            v = parent ? parent[(size_t)g * dp + d] : 0.0f;
+            v = parent ? parent[(size_t)grp * dp + d] : 0.0f;
         } else {
             double s = 0.0;
-            for (uint32_t r = lo; r < hi; ++r) s += (double)X[(size_t)(members ? members[r] : r) * D + col0 + d];
+            for (uint32_t r = rg.x; r < rg.y; ++r) s += (double)g.X[(size_t)(mem ? mem[r] : r) * g.D + col0 + d];
             v = (float)(s / (double)ng);
         }
-        cen[((size_t)g * k + j) * dp + d] = v;
-        cenT[((size_t)g * dp + d) * k + j] = v;
+        put_centroid(g, grp, j, d, v);
     }
 }
 
-// Nearest centroid of every vector among the k centroids of its group: one wavefront per vector, one
-// lane per centroid (several rounds when k > 64); plain sums of squared differences, dimensions in
-// ascending order; ties go to the smaller centroid number.  cenT holds the centroids of a group with
-// the centroid number fastest, so the lanes of a wavefront read consecutive words.
-__global__ __launch_bounds__(kTrainThreads) void lloyd_assign_kernel(const float* X, int64_t n, int D, int col0, int dp,
-                                                                      const float* cenT, int k, const uint32_t* group,
-                                                                      uint32_t* label, float* dmin) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t nwaves = (int64_t)gridDim.x * (kTrainThreads / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (kTrainThreads / kWave) + threadIdx.x / kWave; v < n; v += nwaves) {
-        const uint32_t g = group ? group[v] : 0u;
-        const float* xr = X + (size_t)v * D + col0;
-        const float* ct = cenT + (size_t)g * dp * k;
-        unsigned long long best = ~0ull;
-        for (int j0 = 0; j0 < k; j0 += kWave) {
-            const int j = j0 + lane;
-            float acc = 0.0f;
-            for (int d0 = 0; d0 < dp; d0 += kWave) {
-                const float xc = (d0 + lane < dp) ? xr[d0 + lane] : 0.0f;
-                const int nd = dp - d0 < kWave ? dp - d0 : kWave;
-                for (int dd = 0; dd < nd; ++dd) {
-                    const float xs = __shfl(xc, dd, kWave);
-                    const float c = j < k ? ct[(size_t)(d0 + dd) * k + j] : 0.0f;
-                    const float diff = xs - c;
-                    acc = fmaf(diff, diff, acc);
+// The chunks of every group: pieces of `rows` members.  One workgroup; at most 1024 groups (four parts, 256 cells).
+__global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, int G, uint32_t rows, uint32_t* chunk_off, uint4* chunks) {
+    __shared__ uint32_t part[1024 / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint2 mine = tid < G ? range[tid] : make_uint2(0u, 0u);
+    uint32_t total;
+    const uint32_t at = block_exclusive_sum((uint32_t)(((uint64_t)(mine.y - mine.x) + rows - 1) / rows), part, total);
+    if (tid < G) chunk_off[tid] = at;
+    if (tid == 0) chunk_off[G] = total;
+    for (int l = 0; l < kWave; ++l) {                        // a wavefront writes its groups one after the other
+        const int grp = wave * kWave + l;
+        if (grp >= G) break;
+        const uint32_t lo = (uint32_t)__shfl((int)mine.x, l, kWave), hi = (uint32_t)__shfl((int)mine.y, l, kWave);
+        const uint32_t first = (uint32_t)__shfl((int)at, l, kWave);
+        for (uint64_t c = lane, s = (uint64_t)lo + (uint64_t)lane * rows; s < hi; c += kWave, s += (uint64_t)kWave * rows)
+            chunks[first + c] = make_uint4((uint32_t)grp, (uint32_t)s, (uint32_t)(s + rows < hi ? s + rows : hi), 0u);
+    }
+}
+
+// One Lloyd iteration over one chunk: the nearest centroid of every vector among the k of its group (plain sums of squared
+// differences, dimensions in ascending order; ties go to the smaller centroid number), then the sum and number of
+// the members of every cell, in double precision, members in ascending order in a fixed split.
+// A thread has one vector, whose values come from LDS 32 dimensions at a time, and KB running distances; the
+// centroids are the same for the whole workgroup and come through the scalar cache.  The sums are taken from the vectors
+// once more (they are in L2): the tile's vectors are ordered by cell, a wavefront adds up one cell's.
+// Bound by the two vector instructions per value and centroid (10 us of an iteration's 36 at 100,000 vectors x 128, 16
+// centroids), the staging of the vectors from the last-level cache (8 us) and the sums (9 us).  One wavefront per vector with
+// one lane per centroid, all vectors sorted by cell in every iteration: 35.9 ms for the whole of pqt_train on 100,000
+// vectors x 128 (16 and 8 centroids, 20 iterations, line table), against 2.8.  Staging by wavefront with the next slab in
+// registers was slower (41 us an iteration): its registers cost a resident workgroup.
+template <int KB>
+__global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) {
+    typedef const __attribute__((address_space(4))) float* scalar_floats;
+    __shared__ __align__(16) float sx[kTile * kSlabStride];
+    __shared__ uint32_t srow[kTile], order[kTile], part[kTrainThreads / kWave];
+    extern __shared__ uint32_t cnt[];                        // [wavefront][cell]: members, then their first place in `order`
+    if (blockIdx.x >= g.chunk_off[g.G]) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    constexpr int nwaves = kTrainThreads / kWave;
+    const uint4 chunk = g.chunks[blockIdx.x];
+    const int grp = __builtin_amdgcn_readfirstlane((int)chunk.x);
+    const uint32_t lo = chunk.y, hi = chunk.z;
+    if (!g.label && g.frozen[grp]) return;
+    const int dp = g.dp, k = g.k, nd4 = (dp + 3) / 4;
+    const int p = grp / (g.G / g.P), col0 = p * dp;
+    const uint32_t* mem = g.members ? g.members + (size_t)p * g.n : nullptr;
+    for (uint64_t t0 = lo; t0 < hi; t0 += kTile) {
+        const int m = (int)(hi - t0 < kTile ? hi - t0 : kTile);
+        if (tid < m) srow[tid] = mem ? mem[t0 + tid] : (uint32_t)t0 + (uint32_t)tid;
+        for (int e = tid; e < nwaves * k; e += kTrainThreads) cnt[e] = 0u;
+        uint32_t best = 0xffffffffu, cell = 0u;
+        bool first = true;
+        for (int j0 = 0; j0 < k; j0 += KB) {
+            float acc[KB];
+#pragma unroll
+            for (int j = 0; j < KB; ++j) acc[j] = 0.0f;
+            for (int d0 = 0; d0 < dp; d0 += kSlab) {
+                __syncthreads();
+                if (first || dp > kSlab) {
+                    if (g.wide) {
+// all pieces are asked for before the first is waited for: what a thread may not read it reads from the
+                        // start of a row it may
+                        float4 v[kSlab / 4];
+#pragma unroll
+                        for (int u = 0; u < kSlab / 4; ++u) {
+                            const int e = tid + u * kTrainThreads, r = e / (kSlab / 4), d = d0 + 4 * (e % (kSlab / 4));
+                            v[u] = *reinterpret_cast<const float4*>(g.X + (size_t)srow[r < m ? r : 0] * g.D + col0 + (d < dp ? d : 0));
+                        }
+#pragma unroll
+                        for (int u = 0; u < kSlab / 4; ++u) {
+                            const int e = tid + u * kTrainThreads, r = e / (kSlab / 4), d = d0 + 4 * (e % (kSlab / 4));
+                            if (r >= m || d >= dp) v[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            *reinterpret_cast<float4*>(sx + r * kSlabStride + (d - d0)) = v[u];
+                        }
+                    } else {
+                        for (int e = tid; e < kTile * kSlab; e += kTrainThreads) {
+                            const int r = e / kSlab, d = d0 + e % kSlab;
+                            sx[r * kSlabStride + (d - d0)] = r < m && d < dp ? g.X[(size_t)srow[r] * g.D + col0 + d] : 0.0f;
+                        }
+                    }
+                }
+                first = false;
+                __syncthreads();
+                const int steps = min(kSlab / 4, nd4 - d0 / 4);
+                scalar_floats c = (scalar_floats)(uintptr_t)(g.cenI + (((size_t)grp * nd4 + d0 / 4) * g.kp + j0) * 4);
+                for (int s = 0; s < steps; ++s, c += (size_t)g.kp * 4) {
+                    const float4 x = *reinterpret_cast<const float4*>(sx + tid * kSlabStride + 4 * s);
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) {
+                        float diff = x.x - c[4 * j];
+                        acc[j] = fmaf(diff, diff, acc[j]);
+                        diff = x.y - c[4 * j + 1];
+                        acc[j] = fmaf(diff, diff, acc[j]);
+                        diff = x.z - c[4 * j + 2];
+                        acc[j] = fmaf(diff, diff, acc[j]);
+                        diff = x.w - c[4 * j + 3];
+                        acc[j] = fmaf(diff, diff, acc[j]);
+                    }
                 }
             }
-            const unsigned long long key = j < k ? (((unsigned long long)mono_key(acc) << 32) | (unsigned)j) : ~0ull;
-            best = key < best ? key : best;
+#pragma unroll
+            for (int j = 0; j < KB; ++j) {
+                const uint32_t key = mono_key(acc[j]);
+                if (j0 + j < k && (key < best || (j0 + j == 0))) {
+                    best = key;
+                    cell = (uint32_t)(j0 + j);
+                }
+            }
         }
-        best = wave_min_u64(best);
-        if (lane == 0) {
-            label[v] = g * (uint32_t)k + (uint32_t)best;
-            dmin[v] = mono_inv((uint32_t)(best >> 32));
+        if (tid < m) g.dmin[(size_t)p * g.n + t0 + tid] = mono_inv(best);
+        if (g.label) {
+            if (tid < m) g.label[(size_t)p * g.n + t0 + tid] = cell;
+            continue;
         }
+        // ---- the tile's vectors ordered by cell: a lane's place among the same cell's of its wavefront, then the counts ----
+        unsigned long long same = __ballot(tid < m);
+        for (int b = 1; b < k; b <<= 1) {
+            const unsigned long long set = __ballot((cell & (uint32_t)b) != 0u);
+            same &= (cell & (uint32_t)b) ? set : ~set;
+        }
+        const int before = __popcll(same & ((1ull << lane) - 1ull));
+        if (tid < m && before == 0) cnt[wave * k + (int)cell] = (uint32_t)__popcll(same);
+        __syncthreads();
+        const int per = (k + kTrainThreads - 1) / kTrainThreads;
+        uint32_t here = 0, total;
+        for (int j = tid * per; j < min(k, (tid + 1) * per); ++j)
+            for (int w = 0; w < nwaves; ++w) here += cnt[w * k + j];
+        uint32_t place = block_exclusive_sum(here, part, total);
+        for (int j = tid * per; j < min(k, (tid + 1) * per); ++j)
+            for (int w = 0; w < nwaves; ++w) {
+                const uint32_t c = cnt[w * k + j];
+                cnt[w * k + j] = place;
+                place += c;
+            }
+        __syncthreads();
+        if (tid < m) order[cnt[wave * k + (int)cell] + (uint32_t)before] = srow[tid];
+        __syncthreads();
+        // ---- sums: one wavefront per cell and piece of the dimensions; several vectors side by side when the piece is short ----
+        const bool more = t0 != lo;                          // a later tile adds to what the first one wrote
+        const int units = g.wide ? dp / 4 : dp;
+        int span = 1;
+        while (span < units && span < kWave) span <<= 1;
+        const int pieces = (units + span - 1) / span, rl = kWave / span, r = lane / span, dl = lane & (span - 1);
+        for (int job = wave; job < k * pieces; job += nwaves) {
+            const int j = job / pieces, unit = (job - j * pieces) * span + dl;
+            const int a = (int)cnt[j], b = j + 1 < k ? (int)cnt[j + 1] : m;
+            double* out = g.sums + ((size_t)blockIdx.x * k + j) * dp;
+            if (g.wide) {
+                const float* col = g.X + col0 + 4 * (unit < units ? unit : 0);
+                double acc[4] = {0.0, 0.0, 0.0, 0.0};
+                constexpr int kFlight = 8;                   // rows asked for before the first is waited for
+                for (int e0 = a; e0 < b; e0 += kFlight * rl) {
+                    float4 v[kFlight];
+#pragma unroll
+                    for (int u = 0; u < kFlight; ++u)
+                        v[u] = *reinterpret_cast<const float4*>(col + (size_t)order[min(e0 + u * rl + r, b - 1)] * g.D);
+#pragma unroll
+                    for (int u = 0; u < kFlight; ++u)
+                        if (e0 + u * rl + r < b) {
+                            acc[0] += (double)v[u].x;
+                            acc[1] += (double)v[u].y;
+                            acc[2] += (double)v[u].z;
+                            acc[3] += (double)v[u].w;
+                        }
+                }
+                for (int off = span; off < kWave; off <<= 1)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] += __shfl_xor(acc[c], off, kWave);
+                if (r == 0 && unit < units)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) out[4 * unit + c] = more ? out[4 * unit + c] + acc[c] : acc[c];
+            } else {
+                double acc = 0.0;
+                if (unit < units)
+                    for (int e = a + r; e < b; e += rl) acc += (double)g.X[(size_t)order[e] * g.D + col0 + unit];
+                for (int off = span; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+                if (r == 0 && unit < units) out[unit] = more ? out[unit] + acc : acc;
+            }
+            if (lane == 0 && job == j * pieces) {
+                uint32_t* n = g.counts + (size_t)blockIdx.x * k + j;
+                *n = more ? *n + (uint32_t)(b - a) : (uint32_t)(b - a);
+            }
+        }
+        __syncthreads();
     }
+}
+
+// Sum over the workgroup, returned to every thread.
+__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part) {
+    uint32_t total;
+    (void)block_exclusive_sum(v, part, total);
+    __syncthreads();
+    return total;
+}
+
+// centroid = mean of its members (the chunks added in ascending order in a fixed split); the cells of a frozen or empty
+// group keep what they hold.  An empty cell is re-seeded with the member of its group that lies farthest from its
+// centroid (ties: the smaller vector number); that vector then counts as at distance zero, so the next empty cell of the
+// group takes another one.  One workgroup per cell and 64 dimensions.
+__global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
+    __shared__ double red[1024];
+    __shared__ uint32_t part[1024 / kWave];
+    __shared__ unsigned long long far_part[1024 / kWave];
+    const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), k = g.k, dp = g.dp;
+    const int grp = blockIdx.x / k, j = blockIdx.x - grp * k, p = grp / (g.G / g.P);
+    const uint32_t c0 = g.chunk_off[grp], c1 = g.chunk_off[grp + 1];
+    const uint8_t keep = g.frozen[grp];
+    if (keep || c0 == c1) return;
+    const int d = blockIdx.y * kWave + lane, r = tid / kWave, rl = nt / kWave;
+    uint32_t mine = 0;
+    for (uint32_t c = c0 + tid; c < c1; c += nt) mine += g.counts[(size_t)c * k + j];
+    double acc = 0.0;
+    constexpr int kFlight = 8;                               // chunks asked for before the first is waited for
+    const double* col = g.sums + (size_t)j * dp + (d < dp ? d : 0);
+    for (uint32_t e = c0; e < c1; e += kFlight * rl) {
+        double v[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) v[u] = col[(size_t)min(e + u * rl + r, c1 - 1) * k * dp];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u)
+            if (e + u * rl + r < c1) acc += v[u];
+    }
+    red[tid] = acc;
+    const uint32_t count = block_sum(mine, part);
+    if (count > 0) {
+        if (r == 0 && d < dp) {
+            double t = 0.0;
+            for (int s = 0; s < rl; ++s) t += red[s * kWave + lane];
+            put_centroid(g, grp, j, d, (float)(t / (double)count));
+        }
+        return;
+    }
+    // this is empty cell number `nth` of its group: it gets the nth farthest member
+    const uint2 rg = g.range[grp];
+    const float* dist = g.dmin + (size_t)p * g.n;
+    int nth = 0;
+    for (int i = 0; i < j; ++i) {
+        uint32_t c_i = 0;
+        for (uint32_t c = c0 + tid; c < c1; c += nt) c_i += g.counts[(size_t)c * k + i];
+        if (block_sum(c_i, part) == 0) ++nth;
+    }
+    unsigned long long bound = ~0ull;
+    uint32_t at = rg.x;                                      // none but zeros left: the first member
+    for (int pass = 0; pass <= nth; ++pass) {
+        unsigned long long best = 0ull;
+        for (uint64_t e = (uint64_t)rg.x + tid; e < rg.y; e += nt) {
+            const uint32_t dk = mono_key(dist[e]);
+            const unsigned long long key = ((unsigned long long)dk << 32) | (0xffffffffu - (uint32_t)e);
+            if (dk > mono_key(0.0f) && key < bound) best = key > best ? key : best;
+        }
+        best = ~wave_min_u64(~best);
+        __syncthreads();
+        if (lane == 0) far_part[tid / kWave] = best;
+        __syncthreads();
+        for (int s = 0; s < rl; ++s) best = far_part[s] > best ? far_part[s] : best;
+        if (best == 0ull) {
+            at = rg.x;
+            break;
+        }
+        at = 0xffffffffu - (uint32_t)best;
+        bound = best;
+    }
+    if (r == 0 && d < dp)
+        put_centroid(g, grp, j, d, g.X[(size_t)(g.members ? g.members[(size_t)p * g.n + at] : at) * g.D + (size_t)p * dp + d]);
+}
+
+// range[p * k1 + c] = the positions of level-1 cell c in its part's sorted labels
+__global__ void cell_ranges_kernel(const uint32_t* sorted, uint64_t n, int P, int k1, uint2* range) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= P * k1) return;
+    const uint32_t* s = sorted + (size_t)(e / k1) * n;
+    const uint32_t c = (uint32_t)(e % k1);
+    uint32_t at[2];
+    for (int b = 0; b < 2; ++b) {                            // first position whose label is not below c + b
+        uint64_t lo = 0, hi = n;
+        while (lo < hi) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (s[mid] < c + (uint32_t)b) lo = mid + 1; else hi = mid;
+        }
+        at[b] = (uint32_t)lo;
+    }
+    range[e] = make_uint2(at[0], at[1]);
+}
+
+__global__ void whole_range_kernel(uint32_t n, int P, uint2* range) {
+    if ((int)threadIdx.x < P) range[threadIdx.x] = make_uint2(0u, n);
 }
 
 __global__ void iota_u32_kernel(uint32_t* out, uint32_t n) {
@@ -117,168 +397,99 @@ __global__ void iota_u32_kernel(uint32_t* out, uint32_t n) {
     if (i < n) out[i] = i;
 }
 
-__global__ void count_labels_kernel(const uint32_t* label, uint32_t n, uint32_t* counts) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(&counts[label[i]], 1u);           // integer counts: the order of the additions does not matter
-}
-
-__global__ void fill_u32_kernel(uint32_t* out, uint32_t n, uint32_t value) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = value;
-}
-
-// Sum of the members of cell blockIdx.x inside slice blockIdx.y of its member list (members sorted by
-// vector number), per dimension, in double precision.  Threads are laid out as (row lane, dimension):
-// a row lane adds every rl-th member in ascending order, then the row lanes are added in ascending order.
-__global__ __launch_bounds__(kTrainThreads) void lloyd_accumulate_kernel(const float* X, int D, int col0, int dp,
-                                                                          const uint32_t* sorted_idx, const uint32_t* seg_off,
-                                                                          int S, double* partial) {
-    __shared__ double red[kTrainThreads];
-    const int c = blockIdx.x, s = blockIdx.y, tid = threadIdx.x;
-    const uint32_t lo = seg_off[c], hi = seg_off[c + 1];
-    const uint32_t len = hi - lo, chunk = (len + (uint32_t)S - 1) / (uint32_t)S;
-    const uint32_t a = lo + (uint32_t)s * chunk < hi ? lo + (uint32_t)s * chunk : hi;
-    const uint32_t b = a + chunk < hi ? a + chunk : hi;
-    int dw = 1;
-    while (dw < dp && dw < kTrainThreads) dw <<= 1;        // dimensions handled side by side
-    const int rl = kTrainThreads / dw, r = tid / dw, dl = tid - r * dw;
-    for (int d0 = 0; d0 < dp; d0 += dw) {
-        const int d = d0 + dl;
-        double acc = 0.0;
-        if (d < dp)
-            for (uint32_t e = a + (uint32_t)r; e < b; e += (uint32_t)rl) acc += (double)X[(size_t)sorted_idx[e] * D + col0 + d];
-        red[tid] = acc;
-        __syncthreads();
-        if (r == 0 && d < dp) {
-            double t = 0.0;
-            for (int rr = 0; rr < rl; ++rr) t += red[rr * dw + dl];
-            partial[((size_t)c * S + s) * dp + d] = t;
-        }
-        __syncthreads();
-    }
-}
-
-// centroid = mean of its members (the slices added in ascending order); an empty cell and the cells of a
-// frozen group keep what they hold
-__global__ void lloyd_finalize_kernel(const double* partial, int S, const uint32_t* seg_off, uint32_t cells, int dp, int k,
-                                      const uint8_t* frozen, float* cen, float* cenT) {
-    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (size_t)cells * dp) return;
-    const uint32_t c = (uint32_t)(e / dp);
-    const int d = (int)(e - (size_t)c * dp);
-    const uint32_t g = c / (uint32_t)k, j = c - g * (uint32_t)k;
-    const uint32_t cnt = seg_off[c + 1] - seg_off[c];
-    if (cnt == 0 || frozen[g]) return;
-    double t = 0.0;
-    for (int s = 0; s < S; ++s) t += partial[((size_t)c * S + s) * dp + d];
-    const float v = (float)(t / (double)cnt);
-    cen[e] = v;
-    cenT[((size_t)g * dp + d) * k + j] = v;
-}
-
-// An empty cell is re-seeded with the member of its group that lies farthest from its centroid (ties:
-// the smaller vector number); that vector then counts as at distance zero, so the next empty cell of
-// the group takes another one.  One workgroup per group, its empty cells one after the other.
-__global__ __launch_bounds__(kTrainThreads) void lloyd_reseed_kernel(const float* X, int D, int col0, int dp,
-                                                                      const uint32_t* sorted_idx, const uint32_t* seg_off, int k,
-                                                                      const uint8_t* frozen, float* dmin, float* cen, float* cenT) {
-    __shared__ unsigned long long red[kTrainThreads / kWave];
-    __shared__ uint32_t far_row;
-    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
-    const uint32_t glo = seg_off[(size_t)g * k], ghi = seg_off[(size_t)(g + 1) * k];
-    if (frozen[g] || ghi == glo) return;
-    for (int j = 0; j < k; ++j) {
-        const uint32_t c = (uint32_t)g * (uint32_t)k + (uint32_t)j;
-        if (seg_off[c + 1] != seg_off[c]) continue;                         // same for the whole workgroup
-        unsigned long long best = 0ull;
-        for (uint32_t e = glo + (uint32_t)tid; e < ghi; e += kTrainThreads) {
-            const uint32_t row = sorted_idx[e];
-            const unsigned long long key = ((unsigned long long)mono_key(dmin[row]) << 32) | (0xffffffffu - row);
-            best = key > best ? key : best;
-        }
-        best = ~wave_min_u64(~best);                                        // maximum over the wavefront
-        if (lane == 0) red[tid / kWave] = best;
-        __syncthreads();
-        if (tid == 0) {
-            unsigned long long m = red[0];
-            for (int w = 1; w < kTrainThreads / kWave; ++w) m = red[w] > m ? red[w] : m;
-            far_row = 0xffffffffu - (uint32_t)m;
-        }
-        __syncthreads();
-        const uint32_t row = far_row;
-        for (int d = tid; d < dp; d += kTrainThreads) {
-            const float v = X[(size_t)row * D + col0 + d];
-            cen[(size_t)c * dp + d] = v;
-            cenT[((size_t)g * dp + d) * k + j] = v;
-        }
-        if (tid == 0) dmin[row] = 0.0f;
-        __syncthreads();                                                    // the next empty cell sees it
-    }
-}
-
-// The nearest line of every training sub-vector (Sec. 3.3 "Offline computation"): one wavefront per
-// vector, the centroid pairs i < j spread over the lanes.  With b^2, a^2 the vector's level-1 distances
-// to c_i, c_j of sub-part m and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) /
+// The nearest line of every training sub-vector (Sec. 3.3 "Offline computation").  With b^2, a^2 the vector's level-1
+// distances to c_i, c_j of sub-part m and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) /
 // (2 c^2) and misses the vector by b^2 - lambda^2 c^2.  Smallest (error, pair number) wins; pairs of
-// coinciding centroids never do.  key[m][v] = pair number << 32 | ordered bits of lambda (sorting these
-// orders the votes by line, then by lambda); 0xffffffff.. when the sub-part has no usable pair.
-__global__ __launch_bounds__(kTrainThreads) void line_vote_kernel(const float* a, int64_t n, int M, int k1, const uint16_t* pair_ij,
-                                                                   int npairs, const float* cc, unsigned long long* keys,
-                                                                   int64_t key_stride, int64_t key_base) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t v = (int64_t)blockIdx.x * (kTrainThreads / kWave) + threadIdx.x / kWave;
-    if (v >= n) return;
-    const float* av = a + (size_t)v * M * k1;
-    for (int m = 0; m < M; ++m) {
-        unsigned long long best = ~0ull;
-        for (int pid = lane; pid < npairs; pid += kWave) {
-            const int i = pair_ij[2 * pid], j = pair_ij[2 * pid + 1];
-            const float c2 = cc[((size_t)m * k1 + i) * k1 + j];
-            if (!(c2 > 0.0f)) continue;
-            const float b2 = av[m * k1 + i], a2 = av[m * k1 + j];
-            const float lam = ((b2 - a2) + c2) / (2.0f * c2);
-            const float err = fmaf(-lam * lam, c2, b2);
-            const unsigned long long key = ((unsigned long long)mono_key(err) << 32) | (unsigned)pid;
-            best = key < best ? key : best;
-        }
-        best = wave_min_u64(best);
-        if (lane == 0) {
-            unsigned long long out = ~0ull;
-            if (best != ~0ull) {
-                const int pid = (int)(uint32_t)best;
-                const int i = pair_ij[2 * pid], j = pair_ij[2 * pid + 1];
-                const float c2 = cc[((size_t)m * k1 + i) * k1 + j];
-                const float b2 = av[m * k1 + i], a2 = av[m * k1 + j];
-                const float lam = ((b2 - a2) + c2) / (2.0f * c2);
-                out = ((unsigned long long)(uint32_t)pid << 32) | mono_key(lam);
-            }
-            keys[(size_t)m * key_stride + key_base + v] = out;
+// coinciding centroids never do.  key[m][v] = sub-part << 48 | pair number << 32 | ordered bits of lambda (sorting these
+// orders the votes by sub-part, line, then lambda); pair number 0xffff when the sub-part has no usable pair.
+// One lane per vector, one sub-part per workgroup: the pair is the same for a wavefront and comes through the scalar
+// cache, the distances of its 64 vectors lie in LDS with the vector fastest, so no two lanes meet in a bank and nothing is
+// compared across lanes (100,000 x 8 sub-parts x 120 pairs: 103 us; with the pairs spread over the lanes 276).
+struct LinePair {
+    uint32_t ij;                 // i | j << 16
+    float c2;
+};
+constexpr int kVoteStride = kWave + 1;
+__global__ __launch_bounds__(kTrainThreads) void line_vote_kernel(const float* a, int64_t n, int M, int k1, const LinePair* pairs,
+                                                                   int npairs, unsigned long long* keys, int64_t key_stride,
+                                                                   int64_t key_base) {
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_words;
+    extern __shared__ float dist[];                          // [wavefront][centroid][vector]
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int m = blockIdx.y;
+    const int64_t v0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * kWave;
+    float* mine = dist + (size_t)wave * k1 * kVoteStride;
+    for (int e = lane; e < k1 * kWave; e += kWave) {         // consecutive lanes: consecutive centroids of a vector
+        const int v = e / k1, i = e - v * k1;
+        mine[i * kVoteStride + v] = v0 + v < n ? a[((size_t)(v0 + v) * M + m) * k1 + i] : 0.0f;
+    }
+    wave_lds_order();
+    const LinePair* pm = pairs + (size_t)m * npairs;
+    uint32_t best = 0xffffffffu;
+    int best_pid = -1;
+    scalar_words w = (scalar_words)(uintptr_t)pm;
+    for (int pid = 0; pid < npairs; ++pid) {
+        const uint32_t ij = w[2 * pid];
+        const float c2 = __uint_as_float(w[2 * pid + 1]);
+        if (!(c2 > 0.0f)) continue;                          // the same for the wavefront
+        const float b2 = mine[(ij & 0xffffu) * kVoteStride + lane], a2 = mine[(ij >> 16) * kVoteStride + lane];
+        const float lam = ((b2 - a2) + c2) / (2.0f * c2);
+        const uint32_t key = mono_key(fmaf(-lam * lam, c2, b2));
+        if (key < best || best_pid < 0) {
+            best = key;
+            best_pid = pid;
         }
     }
+    if (v0 + lane >= n) return;
+    unsigned long long out = 0xffffffffffffull;
+    if (best_pid >= 0) {
+        const LinePair pr = pm[best_pid];
+        const float b2 = mine[(pr.ij & 0xffffu) * kVoteStride + lane], a2 = mine[(pr.ij >> 16) * kVoteStride + lane];
+        const float lam = ((b2 - a2) + pr.c2) / (2.0f * pr.c2);
+        out = ((unsigned long long)(uint32_t)best_pid << 32) | mono_key(lam);
+    }
+    keys[(size_t)m * key_stride + key_base + v0 + lane] = ((unsigned long long)m << 48) | out;
 }
 
-struct DeviceBuffers {      // everything pqt_train allocates on the GPU, released together
-    std::vector<void*> ptrs;
-    ~DeviceBuffers() {
-        for (void* p : ptrs) (void)hipFree(p);
+// first[m][q] = where line q's votes start among the sorted votes of sub-part m (m counted within the batch), q = 0..npairs
+__global__ void line_ranges_kernel(const unsigned long long* sorted, uint32_t nt, int m0, int m1, uint32_t npairs, uint32_t* first) {
+    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t per = (uint64_t)npairs + 1;
+    if (e >= (uint64_t)(m1 - m0) * per) return;
+    const int m = (int)(e / per);
+    const unsigned long long want = ((unsigned long long)(m0 + m) << 48) | ((unsigned long long)(e % per) << 32);
+    const unsigned long long* s = sorted + (size_t)m * nt;
+    uint32_t lo = 0, hi = nt;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (s[mid] < want) lo = mid + 1; else hi = mid;
     }
+    first[e] = lo;
+}
+
+// lam[e] = the lambda of sorted vote at[e] (the votes of sub-part e / 256 of the batch)
+__global__ void pick_votes_kernel(const unsigned long long* sorted, uint32_t nt, const uint32_t* at, int n, float* lam) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < n) lam[e] = mono_inv((uint32_t)sorted[(size_t)(e / 256) * nt + at[e]]);
+}
+
+// Everything pqt_train holds on the GPU: asked for first, then one allocation.
+struct Arena {
+    std::vector<std::pair<void**, size_t>> parts;
+    size_t bytes = 0;
+    void* base = nullptr;
+    ~Arena() { (void)hipFree(base); }
     template <typename Tp>
-    hipError_t alloc(Tp** out, size_t count) {
-        void* p = nullptr;
-        const hipError_t e = hipMalloc(&p, (count ? count : 1) * sizeof(Tp));
-        if (e == hipSuccess) ptrs.push_back(p);
-        *out = static_cast<Tp*>(p);
+    void want(Tp** out, size_t count) {
+        parts.emplace_back(reinterpret_cast<void**>(out), bytes);
+        bytes += (count * sizeof(Tp) + 255) / 256 * 256;
+    }
+    hipError_t allocate() {
+        const hipError_t e = hipMalloc(&base, bytes ? bytes : 1);
+        if (e == hipSuccess)
+            for (const auto& p : parts) *p.first = static_cast<unsigned char*>(base) + p.second;
         return e;
     }
-};
-
-struct LloydScratch {
-    uint32_t *label = nullptr, *label_sorted = nullptr, *idx = nullptr, *idx_sorted = nullptr, *counts = nullptr, *seg_off = nullptr;
-    float* dmin = nullptr;
-    double* partial = nullptr;
-    uint8_t* frozen = nullptr;
-    void* cub_temp = nullptr;
-    size_t cub_bytes = 0;
 };
 
 int log2_ceil(uint32_t v) {
@@ -287,41 +498,57 @@ int log2_ceil(uint32_t v) {
     return b;
 }
 
-// labels -> members of every cell in ascending vector order (idx_sorted) and the cells' offsets
-hipError_t sort_by_label(const LloydScratch& w, uint32_t n, uint32_t cells, hipStream_t st) {
-    const unsigned tb = 256;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((cells + 1 + tb - 1) / tb), dim3(tb), 0, st, w.counts, cells + 1, 0u);
-    hipLaunchKernelGGL(count_labels_kernel, dim3((n + tb - 1) / tb), dim3(tb), 0, st, w.label, n, w.counts);
-    size_t bytes = w.cub_bytes;
-    hipError_t e = hipcub::DeviceScan::ExclusiveSum(w.cub_temp, bytes, w.counts, w.seg_off, (int)(cells + 1), st);
-    if (e != hipSuccess) return e;
-    bytes = w.cub_bytes;
-    e = hipcub::DeviceRadixSort::SortPairs(w.cub_temp, bytes, w.label, w.label_sorted, w.idx, w.idx_sorted, (int)n, 0,
-                                           log2_ceil(cells), st);
-    return e == hipSuccess ? hipGetLastError() : e;
+// Centroids a thread of lloyd_step_kernel works on at a time: a multiple of eight, at most 32 (its running distances are
+// registers), so that the rounds over k leave less than eight of them unused each.
+int centroid_block(int k) {
+    const int rounds = (k + 31) / 32;
+    return ((k + rounds - 1) / rounds + 7) / 8 * 8;
+}
+int padded_centroids(int k) {
+    const int kb = centroid_block(k);
+    return (k + kb - 1) / kb * kb;
 }
 
-// Lloyd iterations for G groups of k centroids each; cen / cenT hold the start and receive the result.
-hipError_t lloyd_run(const float* X, uint32_t n, int D, int col0, int dp, int G, int k, const uint32_t* group, int iters,
-                     float* cen, float* cenT, const LloydScratch& w, int S, hipStream_t st) {
-    const uint32_t cells = (uint32_t)G * (uint32_t)k;
-    const unsigned assign_blocks = (unsigned)std::min<uint64_t>(((uint64_t)n + 3) / 4, 65536);
-    for (int it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(lloyd_assign_kernel, dim3(assign_blocks), dim3(kTrainThreads), 0, st, X, (int64_t)n, D, col0, dp,
-                           cenT, k, group, w.label, w.dmin);
-        hipError_t e = sort_by_label(w, n, cells, st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(lloyd_accumulate_kernel, dim3(cells, S), dim3(kTrainThreads), 0, st, X, D, col0, dp, w.idx_sorted,
-                           w.seg_off, S, w.partial);
-        const size_t ne = (size_t)cells * dp;
-        hipLaunchKernelGGL(lloyd_finalize_kernel, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, st, w.partial, S, w.seg_off,
-                           cells, dp, k, w.frozen, cen, cenT);
-        hipLaunchKernelGGL(lloyd_reseed_kernel, dim3(G), dim3(kTrainThreads), 0, st, X, D, col0, dp, w.idx_sorted, w.seg_off, k,
-                           w.frozen, w.dmin, cen, cenT);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+// Vectors per chunk (a workgroup of lloyd_step_kernel): one tile, or more where that would be more chunks than keep the
+// chip busy, or more than 64 MB of cell sums.
+uint64_t chunk_rows(uint64_t n, int P, int G, int k, int dp) {
+    uint64_t rows = kTile;
+    while (rows < n && rows < (1ull << 30) && ((uint64_t)P * ((n + rows - 1) / rows) > kMaxChunks ||
+                        ((uint64_t)P * ((n + rows - 1) / rows) + (uint64_t)G) * (uint64_t)k * (uint64_t)dp > (8ull << 20)))
+        rows *= 2;
+    return rows;
+}
+uint64_t chunk_limit(uint64_t n, uint64_t rows, int P, int G) { return (uint64_t)P * ((n + rows - 1) / rows) + (uint64_t)G; }
+
+hipError_t launch_step(const LloydArgs& g, uint64_t chunks, hipStream_t st) {
+    const dim3 grid((unsigned)chunks), block(kTrainThreads);
+    const size_t lds = sizeof(uint32_t) * (kTrainThreads / kWave) * (size_t)g.k;
+    switch (centroid_block(g.k)) {
+        case 8: hipLaunchKernelGGL(lloyd_step_kernel<8>, grid, block, lds, st, g); break;
+        case 16: hipLaunchKernelGGL(lloyd_step_kernel<16>, grid, block, lds, st, g); break;
+        case 24: hipLaunchKernelGGL(lloyd_step_kernel<24>, grid, block, lds, st, g); break;
+        default: hipLaunchKernelGGL(lloyd_step_kernel<32>, grid, block, lds, st, g); break;
     }
-    return hipSuccess;
+    return hipGetLastError();
+}
+
+// Lloyd iterations for the groups of g, from start centroids to the result in g.cen / g.cenI.
+hipError_t lloyd_run(const LloydArgs& g, const float* parent, uint64_t rows, int iters, uint32_t* chunk_off, uint4* chunks,
+                     hipStream_t st) {
+    const uint64_t limit = chunk_limit(g.n, rows, g.P, g.G);
+    hipLaunchKernelGGL(lloyd_init_kernel, dim3((unsigned)g.G), dim3(kTrainThreads), 0, st, g, parent);
+    hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, st, g.range, g.G, (uint32_t)rows, chunk_off, chunks);
+    hipError_t e = hipGetLastError();
+    // a group's chunks are split over the wavefronts of a workgroup: sixteen where there are many of them
+    const unsigned threads = limit / (unsigned)g.G >= 64 ? 1024 : 256;
+    for (int it = 0; it < iters && e == hipSuccess; ++it) {
+        e = launch_step(g, limit, st);
+        if (e != hipSuccess) break;
+        hipLaunchKernelGGL(lloyd_update_kernel, dim3((unsigned)(g.G * g.k), (unsigned)((g.dp + kWave - 1) / kWave)), dim3(threads), 0,
+                           st, g);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // Code points per line by the largest-remainder method, in whole numbers: line q with use[q] of `total`
@@ -369,74 +596,108 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     const uint32_t n = (uint32_t)tp->n;
     const int dp = (int)(D / P), ds = (int)(D / M);
     const uint32_t cells1 = k1, cells2 = k1 * k2;
-    const int S1 = (int)std::max<uint32_t>(1, std::min<uint32_t>(64, 2048 / cells1));
-    const int S2 = (int)std::max<uint32_t>(1, std::min<uint32_t>(64, 2048 / cells2));
-    DeviceBuffers mem;
-    LloydScratch w;
-    float *cen1 = nullptr, *cen1T = nullptr, *cen2 = nullptr, *cen2T = nullptr;
-    uint32_t *label1 = nullptr, *members1 = nullptr, *grp_off1 = nullptr, *grp_whole = nullptr;
-    const size_t npartial = std::max((size_t)cells1 * S1, (size_t)cells2 * S2) * dp;
-    HIP_TRY(mem.alloc(&w.label, n));
-    HIP_TRY(mem.alloc(&w.label_sorted, n));
-    HIP_TRY(mem.alloc(&w.idx, n));
-    HIP_TRY(mem.alloc(&w.idx_sorted, n));
-    HIP_TRY(mem.alloc(&w.counts, (size_t)cells2 + 1));
-    HIP_TRY(mem.alloc(&w.seg_off, (size_t)cells2 + 1));
-    HIP_TRY(mem.alloc(&w.dmin, n));
-    HIP_TRY(mem.alloc(&w.partial, npartial));
-    HIP_TRY(mem.alloc(&w.frozen, (size_t)k1 + 1));
-    HIP_TRY(mem.alloc(&cen1, (size_t)k1 * dp));
-    HIP_TRY(mem.alloc(&cen1T, (size_t)k1 * dp));
-    HIP_TRY(mem.alloc(&cen2, (size_t)cells2 * dp));
-    HIP_TRY(mem.alloc(&cen2T, (size_t)cells2 * dp));
-    HIP_TRY(mem.alloc(&label1, n));
-    HIP_TRY(mem.alloc(&members1, n));
-    HIP_TRY(mem.alloc(&grp_off1, (size_t)k1 + 1));
-    HIP_TRY(mem.alloc(&grp_whole, 2));
-    {
-        size_t b1 = 0, b2 = 0;
-        HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, b1, w.counts, w.seg_off, (int)(cells2 + 1), st));
-        HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, b2, w.label, w.label_sorted, w.idx, w.idx_sorted, (int)n, 0, 32, st));
-        w.cub_bytes = std::max(b1, b2);
-        HIP_TRY(mem.alloc(reinterpret_cast<unsigned char**>(&w.cub_temp), w.cub_bytes));
+    const uint32_t npairs = k1 * (k1 - 1) / 2;
+    const uint32_t nt = npairs ? (uint32_t)tp->n_table : 0u;
+    const size_t nd4 = ((size_t)dp + 3) / 4;
+    LloydArgs l1 = {}, l2 = {};
+    l1.X = vectors; l1.n = n; l1.D = (int)D; l1.dp = dp; l1.P = (int)P;
+    l1.wide = reinterpret_cast<uintptr_t>(vectors) % 16 == 0 && D % 4 == 0 && dp % 4 == 0;
+    l2 = l1;
+    l1.G = (int)P; l1.k = (int)k1; l1.kp = padded_centroids((int)k1);
+    l2.G = (int)(P * k1); l2.k = (int)k2; l2.kp = padded_centroids((int)k2);
+    const uint64_t rows1 = chunk_rows(n, (int)P, l1.G, l1.k, dp), rows2 = chunk_rows(n, (int)P, l2.G, l2.k, dp);
+    const uint64_t limit1 = chunk_limit(n, rows1, (int)P, l1.G), limit2 = chunk_limit(n, rows2, (int)P, l2.G);
+    Arena mem;
+    double* sums = nullptr;
+    uint32_t *counts = nullptr, *label = nullptr, *label_sorted = nullptr, *idx = nullptr, *members = nullptr, *chunk_off = nullptr;
+    uint4* chunks = nullptr;
+    float* dmin = nullptr;
+    uint2 *range1 = nullptr, *range2 = nullptr;
+    unsigned char *cub_temp = nullptr, *sort_temp = nullptr;
+    mem.want(&sums, (size_t)std::max(limit1 * k1, limit2 * k2) * dp);
+    mem.want(&counts, (size_t)std::max(limit1 * k1, limit2 * k2));
+    mem.want(&label, (size_t)P * n);
+    mem.want(&label_sorted, (size_t)P * n);
+    mem.want(&idx, n);
+    mem.want(&members, (size_t)P * n);
+    mem.want(&dmin, (size_t)P * n);
+    mem.want(&chunk_off, (size_t)l2.G + 1);
+    mem.want(&chunks, (size_t)std::max(limit1, limit2));
+    mem.want(&range1, P);
+    mem.want(&range2, (size_t)P * k1);
+    mem.want(&l1.frozen, P);
+    mem.want(&l2.frozen, (size_t)P * k1);
+    mem.want(&l1.cen, (size_t)P * cells1 * dp);
+    mem.want(&l1.cenI, (size_t)P * nd4 * l1.kp * 4);
+    mem.want(&l2.cen, (size_t)P * cells2 * dp);
+    mem.want(&l2.cenI, (size_t)P * k1 * nd4 * l2.kp * 4);
+    size_t cub_bytes = 0;
+    HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, cub_bytes, label, label_sorted, idx, members, (int)n, 0, log2_ceil(cells1), st));
+    mem.want(&cub_temp, cub_bytes);
+    // the line table: the votes of as many sub-parts as fit 2^27 keys are sorted together
+    LinePair* pair_dev = nullptr;
+    float* lam_dev = nullptr;
+    unsigned long long *keys = nullptr, *keys_sorted = nullptr;
+    uint32_t *first_dev = nullptr, *at_dev = nullptr;
+    const uint32_t batch = nt ? std::min<uint32_t>(M, std::max<uint32_t>(1, (1u << 27) / nt)) : 0u;
+    const int key_bits = 48 + log2_ceil(M);
+    size_t sort_bytes = 0;
+    if (nt) {
+        HIP_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, keys, keys_sorted, (int)(batch * nt), 0, key_bits, st));
+        mem.want(&sort_temp, sort_bytes);
+        mem.want(&pair_dev, (size_t)M * npairs);
+        mem.want(&keys, (size_t)M * nt);
+        mem.want(&keys_sorted, (size_t)batch * nt);
+        mem.want(&first_dev, (size_t)batch * (npairs + 1));
+        mem.want(&at_dev, (size_t)batch * 256);
+        mem.want(&lam_dev, (size_t)batch * 256);
     }
-    const unsigned tb = 256;
-    hipLaunchKernelGGL(iota_u32_kernel, dim3((n + tb - 1) / tb), dim3(tb), 0, st, w.idx, n);
-    const uint32_t whole[2] = {0u, n};
-    HIP_TRY(hipMemcpyAsync(grp_whole, whole, sizeof(whole), hipMemcpyHostToDevice, st));     // one group: the whole sample
-    HIP_TRY(hipStreamSynchronize(st));                   // `whole` is on this stack frame
+    HIP_TRY(mem.allocate());
+    l1.range = range1; l2.range = range2;
+    l2.members = members;
+    l1.chunk_off = l2.chunk_off = chunk_off;
+    l1.chunks = l2.chunks = chunks;
+    l1.sums = l2.sums = sums; l1.counts = l2.counts = counts; l1.dmin = l2.dmin = dmin;
+    std::vector<float> C1, C2, cc;
+    std::vector<LinePair> pair_host;
+    std::vector<uint32_t> first, at;
+    std::vector<float> lam;
+    try {
+        C1.resize((size_t)P * k1 * dp);
+        C2.resize((size_t)P * cells2 * dp);
+        cc.resize((size_t)M * k1 * k1);
+        pair_host.resize(nt ? (size_t)M * npairs : 0);
+        first.resize((size_t)batch * (npairs + 1));
+        at.resize((size_t)batch * 256);
+        lam.resize((size_t)batch * 256);
+    } catch (const std::bad_alloc&) {
+        return fail(PQT_ENOMEM, "host allocation failed");
+    }
 
-    std::vector<float> C1((size_t)P * k1 * dp), C2((size_t)P * cells2 * dp);
-    const unsigned assign_blocks = (unsigned)std::min<uint64_t>(((uint64_t)n + 3) / 4, 65536);
-    for (uint32_t p = 0; p < P; ++p) {
-        const int col0 = (int)p * dp;
-        // ---- level 1: one group, k1 centroids ---------------------------------------------------------
-        hipLaunchKernelGGL(lloyd_init_kernel, dim3(1), dim3(kTrainThreads), 0, st, vectors, (int)D, col0, dp,
-                           (const uint32_t*)nullptr, grp_whole, (int)k1, (const float*)nullptr, cen1, cen1T, w.frozen);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(lloyd_run(vectors, n, (int)D, col0, dp, 1, (int)k1, nullptr, (int)tp->iters, cen1, cen1T, w, S1, st));
-        // ---- the cells of the finished quantiser: members in ascending vector order -------------------------
-        hipLaunchKernelGGL(lloyd_assign_kernel, dim3(assign_blocks), dim3(kTrainThreads), 0, st, vectors, (int64_t)n, (int)D, col0, dp,
-                           cen1T, (int)k1, (const uint32_t*)nullptr, w.label, w.dmin);
-        HIP_TRY(sort_by_label(w, n, cells1, st));
-        HIP_TRY(hipMemcpyAsync(label1, w.label, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(members1, w.idx_sorted, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(grp_off1, w.seg_off, sizeof(uint32_t) * (k1 + 1), hipMemcpyDeviceToDevice, st));
-        // ---- level 2: k1 groups (the cells), k2 centroids each, trained side by side ---------------------------
-        hipLaunchKernelGGL(lloyd_init_kernel, dim3(k1), dim3(kTrainThreads), 0, st, vectors, (int)D, col0, dp, members1, grp_off1,
-                           (int)k2, cen1, cen2, cen2T, w.frozen);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(lloyd_run(vectors, n, (int)D, col0, dp, (int)k1, (int)k2, label1, (int)tp->iters, cen2, cen2T, w, S2, st));
-        HIP_TRY(hipMemcpyAsync(C1.data() + (size_t)p * k1 * dp, cen1, sizeof(float) * k1 * dp, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(C2.data() + (size_t)p * cells2 * dp, cen2, sizeof(float) * cells2 * dp, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-    }
+    const unsigned tb = 256;
+    hipLaunchKernelGGL(iota_u32_kernel, dim3((n + tb - 1) / tb), dim3(tb), 0, st, idx, n);
+    hipLaunchKernelGGL(whole_range_kernel, dim3(1), dim3(kWave), 0, st, n, (int)P, range1);
+    // ---- level 1: one group per tree part, k1 centroids ------------------------------------------------
+    HIP_TRY(lloyd_run(l1, nullptr, rows1, (int)tp->iters, chunk_off, chunks, st));
+    // ---- the cells of the finished quantisers: members in ascending vector order --------------------------
+    LloydArgs cells = l1;
+    cells.label = label;
+    HIP_TRY(launch_step(cells, limit1, st));
+    for (uint32_t p = 0; p < P; ++p)
+        HIP_TRY(hipcub::DeviceRadixSort::SortPairs(cub_temp, cub_bytes, label + (size_t)p * n, label_sorted + (size_t)p * n, idx,
+                                                   members + (size_t)p * n, (int)n, 0, log2_ceil(cells1), st));
+    hipLaunchKernelGGL(cell_ranges_kernel, dim3((P * k1 + tb - 1) / tb), dim3(tb), 0, st, label_sorted, (uint64_t)n, (int)P, (int)k1, range2);
+    HIP_TRY(hipGetLastError());
+    // ---- level 2: the cells of all parts, k2 centroids each, trained side by side ---------------------------
+    HIP_TRY(lloyd_run(l2, l1.cen, rows2, (int)tp->iters, chunk_off, chunks, st));
+    HIP_TRY(hipMemcpyAsync(C1.data(), l1.cen, C1.size() * sizeof(float), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(C2.data(), l2.cen, C2.size() * sizeof(float), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
     memcpy(C1_out, C1.data(), C1.size() * sizeof(float));
     memcpy(C2_out, C2.data(), C2.size() * sizeof(float));
 
     // ---- distances between the level-1 centroids of every sub-part (Sec. 3.3: the table of c^2) -----------
     const size_t per = M / P;
-    std::vector<float> cc((size_t)M * k1 * k1);
     for (size_t m = 0; m < M; ++m) {
         const size_t p = m / per, lo = m * ds - p * dp;
         for (size_t s = 0; s < k1; ++s)
@@ -453,9 +714,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     if (tbl_i) memset(tbl_i, 0, (size_t)M * 256);
     if (tbl_j) memset(tbl_j, 0, (size_t)M * 256);
     if (tbl_lambda) memset(tbl_lambda, 0, (size_t)M * 256 * sizeof(float));
-    const uint32_t npairs = k1 * (k1 - 1) / 2;
-    const uint32_t nt = (uint32_t)tp->n_table;
-    if (nt == 0 || npairs == 0) return PQT_OK;
+    if (nt == 0) return PQT_OK;
 
     // ---- line table: level-1 distances of the first n_table vectors by the query path's own traversal kernel
     // (an index without vectors carries the codebooks to the GPU), then one vote per sub-vector ---------------------
@@ -475,24 +734,18 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     } holder{ix};
     if (pqt::traverse_lds_bytes(D, P, k1, k2, M, 1) > ix->lds_limit)
         return fail(PQT_EUNSUPPORTED, "pqt_train: D=%u exceeds the LDS budget of the traversal", D);
-    std::vector<uint16_t> pair_host((size_t)npairs * 2);
     {
         size_t e = 0;
-        for (uint32_t i = 0; i < k1; ++i)
-            for (uint32_t j = i + 1; j < k1; ++j) {
-                pair_host[e++] = (uint16_t)i;
-                pair_host[e++] = (uint16_t)j;
-            }
+        for (size_t m = 0; m < M; ++m)
+            for (uint32_t i = 0; i < k1; ++i)
+                for (uint32_t j = i + 1; j < k1; ++j) pair_host[e++] = LinePair{i | (j << 16), cc[(m * k1 + i) * k1 + j]};
     }
-    uint16_t* pair_dev = nullptr;
-    float* cc_dev = nullptr;
-    unsigned long long *keys = nullptr, *keys_sorted = nullptr;
-    HIP_TRY(mem.alloc(&pair_dev, pair_host.size()));
-    HIP_TRY(mem.alloc(&cc_dev, cc.size()));
-    HIP_TRY(mem.alloc(&keys, (size_t)M * nt));
-    HIP_TRY(mem.alloc(&keys_sorted, (size_t)nt));
-    HIP_TRY(hipMemcpyAsync(pair_dev, pair_host.data(), pair_host.size() * sizeof(uint16_t), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(cc_dev, cc.data(), cc.size() * sizeof(float), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(pair_dev, pair_host.data(), pair_host.size() * sizeof(LinePair), hipMemcpyHostToDevice, st));
+    // four wavefronts a workgroup while their distances fit the LDS that every launch may ask for
+    const unsigned vote_waves = k1 <= 60 ? 4 : 1;
+    const size_t vote_lds = sizeof(float) * vote_waves * k1 * kVoteStride;
+    if (vote_lds > 64 * 1024)
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(line_vote_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)vote_lds));
     const int64_t chunk = 1 << 17;
     for (int64_t s = 0; s < (int64_t)nt; s += chunk) {
         const int64_t mrows = (int64_t)nt - s < chunk ? (int64_t)nt - s : chunk;
@@ -503,56 +756,56 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
         ta.C1 = ix->C1; ta.c1n = ix->c1n; ta.C2 = ix->C2; ta.C2t = ix->C2t;
         ta.a = ix->ws_a; ta.L_d = ix->ws_Ld; ta.L_id = ix->ws_Lid; ta.sel_tap = nullptr; ta.counters = nullptr;
         HIP_TRY(pqt::launch_traverse(ta, st));
-        constexpr int per_block = kTrainThreads / kWave;
-        hipLaunchKernelGGL(line_vote_kernel, dim3((unsigned)((mrows + per_block - 1) / per_block)), dim3(kTrainThreads), 0, st,
-                           ix->ws_a, mrows, (int)M, (int)k1, pair_dev, (int)npairs, cc_dev, keys, (int64_t)nt, s);
+        const int64_t per_block = (int64_t)vote_waves * kWave;
+        hipLaunchKernelGGL(line_vote_kernel, dim3((unsigned)((mrows + per_block - 1) / per_block), M), dim3(vote_waves * kWave), vote_lds, st,
+                           ix->ws_a, mrows, (int)M, (int)k1, pair_dev, (int)npairs, keys, (int64_t)nt, s);
         HIP_TRY(hipGetLastError());
     }
-    size_t sort_bytes = 0;
-    HIP_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, keys, keys_sorted, (int)nt, 0, 64, st));
-    void* sort_temp = nullptr;
-    HIP_TRY(mem.alloc(reinterpret_cast<unsigned char**>(&sort_temp), sort_bytes));
-    std::vector<unsigned long long> votes;
-    try {
-        votes.resize(nt);
-    } catch (const std::bad_alloc&) {
-        return fail(PQT_ENOMEM, "host allocation failed");
-    }
-    for (uint32_t m = 0; m < M; ++m) {
-        HIP_TRY(hipcub::DeviceRadixSort::SortKeys(sort_temp, sort_bytes, keys + (size_t)m * nt, keys_sorted, (int)nt, 0, 64, st));
-        HIP_TRY(hipMemcpyAsync(votes.data(), keys_sorted, sizeof(unsigned long long) * nt, hipMemcpyDeviceToHost, st));
+    for (uint32_t m0 = 0; m0 < M; m0 += batch) {
+        const uint32_t m1 = std::min(M, m0 + batch);
+        HIP_TRY(hipcub::DeviceRadixSort::SortKeys(sort_temp, sort_bytes, keys + (size_t)m0 * nt, keys_sorted, (int)((m1 - m0) * nt), 0,
+                                                  key_bits, st));
+        const size_t nfirst = (size_t)(m1 - m0) * (npairs + 1);
+        hipLaunchKernelGGL(line_ranges_kernel, dim3((unsigned)((nfirst + tb - 1) / tb)), dim3(tb), 0, st, keys_sorted, nt, (int)m0, (int)m1,
+                           npairs, first_dev);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(first.data(), first_dev, nfirst * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        // votes per line and where each line's lambdas start (the keys are sorted by line, then lambda)
-        std::vector<uint64_t> use(npairs, 0), first(npairs, 0);
-        uint64_t total = 0;
-        for (uint32_t e = 0; e < nt; ++e) {
-            const uint32_t q = (uint32_t)(votes[e] >> 32);
-            if (q >= npairs) break;                          // sub-vectors without a usable line sort last
-            if (use[q]++ == 0) first[q] = e;
-            ++total;
-        }
-        if (total == 0) continue;
-        const std::vector<uint32_t> alloc = share_out(use, total, 256);
         // a line's code points sit at the (t + 1/2) / alloc quantiles of its lambdas; lines in pair order and
         // lambdas ascending, so the entries come out ordered by (i, j, lambda)
-        uint32_t c = 0;
-        for (uint32_t q = 0; q < npairs && c < 256; ++q)
-            for (uint32_t t = 0; t < alloc[q] && c < 256; ++t, ++c) {
-                uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
-                if (pos >= use[q]) pos = use[q] - 1;
-                const uint32_t bits = (uint32_t)votes[first[q] + pos];
-                const uint32_t u = (bits & 0x80000000u) ? (bits & 0x7fffffffu) : ~bits;      // ordered bits -> float
-                float lam;
-                memcpy(&lam, &u, sizeof(lam));
-                tbl_i[(size_t)m * 256 + c] = (uint8_t)pair_host[2 * q];
-                tbl_j[(size_t)m * 256 + c] = (uint8_t)pair_host[2 * q + 1];
-                tbl_lambda[(size_t)m * 256 + c] = lam;
+        for (uint32_t m = m0; m < m1; ++m) {
+            const uint32_t* fm = first.data() + (size_t)(m - m0) * (npairs + 1);
+            uint32_t* am = at.data() + (size_t)(m - m0) * 256;
+            std::fill(am, am + 256, 0u);
+            const uint64_t total = fm[npairs];               // sub-vectors without a usable line sort last
+            if (total == 0) continue;
+            std::vector<uint64_t> use(npairs);
+            for (uint32_t q = 0; q < npairs; ++q) use[q] = fm[q + 1] - fm[q];
+            const std::vector<uint32_t> alloc = share_out(use, total, 256);
+            uint32_t c = 0;
+            for (uint32_t q = 0; q < npairs && c < 256; ++q)
+                for (uint32_t t = 0; t < alloc[q] && c < 256; ++t, ++c) {
+                    uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
+                    if (pos >= use[q]) pos = use[q] - 1;
+                    am[c] = fm[q] + (uint32_t)pos;
+                    tbl_i[(size_t)m * 256 + c] = (uint8_t)pair_host[q].ij;
+                    tbl_j[(size_t)m * 256 + c] = (uint8_t)(pair_host[q].ij >> 16);
+                }
+            for (; c > 0 && c < 256; ++c) {                  // (cannot happen when total > 0; kept total)
+                am[c] = am[c - 1];
+                tbl_i[(size_t)m * 256 + c] = tbl_i[(size_t)m * 256 + c - 1];
+                tbl_j[(size_t)m * 256 + c] = tbl_j[(size_t)m * 256 + c - 1];
             }
-        for (; c > 0 && c < 256; ++c) {                      // (cannot happen when total > 0; kept total)
-            tbl_i[(size_t)m * 256 + c] = tbl_i[(size_t)m * 256 + c - 1];
-            tbl_j[(size_t)m * 256 + c] = tbl_j[(size_t)m * 256 + c - 1];
-            tbl_lambda[(size_t)m * 256 + c] = tbl_lambda[(size_t)m * 256 + c - 1];
         }
+        const int npick = (int)(m1 - m0) * 256;
+        HIP_TRY(hipMemcpyAsync(at_dev, at.data(), sizeof(uint32_t) * npick, hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(pick_votes_kernel, dim3((unsigned)((npick + tb - 1) / tb)), dim3(tb), 0, st, keys_sorted, nt, at_dev, npick, lam_dev);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(lam.data(), lam_dev, sizeof(float) * npick, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        for (uint32_t m = m0; m < m1; ++m)
+            if (first[(size_t)(m - m0) * (npairs + 1) + npairs] > 0)
+                memcpy(tbl_lambda + (size_t)m * 256, lam.data() + (size_t)(m - m0) * 256, 256 * sizeof(float));
     }
     return PQT_OK;
 }

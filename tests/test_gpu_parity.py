@@ -778,6 +778,41 @@ def test_brute_force(pqt, tiny, tmp_path):
         pqt.pqt_index_free(gix)
 
 
+@pytest.mark.parametrize("n, D, P, k1, k2, distinct, offset, iters", [
+    (255, 6, 2, 3, 2, 0, 0, 1),            # odd slices (no 16-byte rows), one vector short of a tile
+    (257, 8, 1, 33, 5, 0, 0, 1),           # one vector in the second tile; centroids in two rounds
+    (1000, 72, 2, 8, 40, 0, 0, 1),         # two slabs of dimensions, the second partial; cells with fewer than k2 members
+    (5000, 64, 2, 16, 8, 0, 1, 1),         # vectors that do not start at a multiple of 16 bytes
+    (700, 520, 2, 2, 9, 0, 0, 1),          # a wavefront sums a cell in two pieces
+    (300, 8, 2, 20, 4, 6, 0, 3),           # fewer distinct vectors than centroids: cells run empty and are re-seeded
+    (5, 8, 2, 7, 3, 0, 0, 2),              # fewer vectors than centroids
+    (600_001, 8, 2, 2, 2, 0, 0, 1),        # more tiles than workgroups: a workgroup adds up several
+])
+def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
+    """Tile, slab and piece edges of the training kernels against the oracle's Lloyd iterations.  Whole numbers up to 255:
+    level-1 distances of the first iteration are exact; a centroid is a double-precision mean rounded to fp32 (relative
+    2^-24, so 1e-6).  The members of the level-2 runs are those of the GPU's own level-1 centroids; a vector whose two
+    nearest are closer than fp32 resolves would be a failure of the draw (none with this seed)."""
+    import torch
+    rng = np.random.default_rng(11)
+    X = rng.integers(0, 256, (n, D)).astype(np.float32)
+    if distinct:
+        X = X[:distinct][rng.integers(0, distinct, n)]
+    buf = torch.empty((n * D + offset,), dtype=torch.float32, device="cuda")
+    Xd = buf[offset:].view(n, D)
+    Xd.copy_(torch.from_numpy(X))
+    got = pqt.pqt_train(Xd, P=P, k1=k1, k2=k2, M=P, iters=iters, n_table=0)
+    dp = D // P
+    for p in range(P):
+        Xp = X[:, p * dp:(p + 1) * dp].astype(np.float64)
+        np.testing.assert_allclose(got["C1"][p], B.lloyd(Xp, k1, iters), rtol=1e-6, atol=0)
+        lab = np.argmin(B.sqdist_matrix(Xp, got["C1"][p].astype(np.float64)), axis=1)
+        for i in range(k1):
+            sub = Xp[lab == i]
+            want = B.lloyd(sub, k2, iters) if len(sub) else np.repeat(got["C1"][p, i][None], k2, axis=0)
+            np.testing.assert_allclose(got["C2"][p, i], want, rtol=1e-6, atol=0)
+
+
 @pytest.mark.parametrize("kind, N, D, nq, k", [
     ("bytes", 255, 16, 1, 255),            # one partial chunk, k close to N
     ("bytes", 4096, 96, 257, 100),         # exactly the first chunk; one query past a workgroup's 256
