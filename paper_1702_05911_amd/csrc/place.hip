@@ -1,0 +1,391 @@
+// The offline phase's per-vector work (Sec. 3.1 "bin map", Sec. 3.3 "Offline computation"): every database vector is put into
+// its bin (nearest level-1 cluster of every tree part, nearest child of that cluster) and gets its line-quantisation code;
+// every training vector votes for its nearest lines.  All of it starts from the level-1 sub-part distances of Sec. 3.3's last
+// paragraph, so one kernel does it, and the distances never leave the chip.
+//
+// One workgroup per 64 vectors.  A wavefront takes a sub-part: the [64 x ds] . [ds x k1] products on the matrix cores (the
+// traversal's instruction, order and rounding, so a vector falls into the bin the query path looks for it in), distances to
+// LDS with the vector fastest; then a lane owns a vector and walks the code points (or lines), which are the same for
+// the wavefront and come through the scalar cache, and nothing is compared across lanes.  Sub-part distances are added to
+// the part's in ascending order; level 2 spreads (vector, child) pairs over the lanes, children of a cluster interleaved.
+//
+// Bound by vector instructions (half of its cycles; six per vector, sub-part and code point) and LDS reads (two of them).
+// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 2.1 ms; the traversal kernel with w = 1 (one wavefront
+// per list, 8 of 64 lanes at work), its distances written and read back, and one wavefront per vector for the codes took
+// 7.0.  With staged values and distances side by side in LDS three workgroups instead of five fit a compute unit: 2.9.
+#include "pqt_device.hpp"
+#include "pqt_kernels.hpp"
+
+namespace pqt {
+namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) uint32_t* scalar_words;
+
+constexpr int kPlaceRows = kWave;              // vectors of a workgroup: one per lane
+constexpr int kRowStride = kPlaceRows + 1;     // of a centroid's distances
+constexpr int kSlab = 32;                      // dimensions of a sub-part staged at a time
+
+struct PlaceLds {
+    int st;                                    // row stride of a staged slab (floats): an odd number of 16-byte pieces
+    size_t a_stride;                           // of a wavefront's distances (floats)
+    size_t off_x, off_a, off_d1, off_sel, off_leaf, off_code, total;
+};
+
+__host__ __device__ inline PlaceLds place_layout(int ds, int P, int k1, int code_bytes, int waves, bool votes) {
+    PlaceLds L;
+    const int pieces = ((ds < kSlab ? ds : kSlab) + 3) / 4;
+    L.st = 4 * (pieces | 1);
+    size_t o = 0;
+    L.off_x = o;    o += sizeof(float) * waves * kPlaceRows * L.st;
+    // the distances of up to 32 centroids come out of one pass over the staged values and take their place
+    const size_t x_bytes = sizeof(float) * kPlaceRows * L.st, a_bytes = sizeof(float) * k1 * kRowStride;
+    L.a_stride = (k1 <= 32 && x_bytes > a_bytes ? x_bytes : a_bytes) / sizeof(float);
+    if (k1 <= 32) o = 0;
+    L.off_a = o;    o += sizeof(float) * waves * L.a_stride;
+    L.off_d1 = o;   o += votes ? 0 : sizeof(float) * k1 * kRowStride;
+    o = (o + 7) & ~size_t(7);
+    L.off_sel = o;  o += votes ? 0 : sizeof(unsigned long long) * P * kPlaceRows;
+    L.off_leaf = o; o += votes ? 0 : sizeof(unsigned long long) * P * kPlaceRows;
+    L.off_code = o; o += votes ? 0 : (size_t)kPlaceRows * code_bytes;
+    L.total = (o + 15) & ~size_t(15);
+    return L;
+}
+
+// Level-1 distances of the workgroup's vectors in sub-part m, by one wavefront: at[i * kRowStride + v].
+// WIDE: rows are read in 16-byte pieces.  Vectors past the end repeat the last one.
+template <bool WIDE>
+__device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0, int nv, int m, int st, float* xs, float* at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int k1 = g.k1, dp = g.D / g.P, ds = g.D / g.M, per = g.M / g.P;
+    const int p = m / per, lo = m * ds - p * dp;
+    const int ntiles = (k1 + 15) / 16, row = lane & 15, kq = lane >> 4;
+    const float* x = g.x + (size_t)v0 * g.D + (size_t)m * ds;
+    float norm = 0.0f;                                       // of vector `lane`
+    for (int nt = 0; nt < ntiles; nt += 2) {
+        const bool two = nt + 1 < ntiles;                    // two tiles of 16 centroids per pass over the values
+        v4f acc[2][4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int k0 = 0; k0 < ds; k0 += kSlab) {
+            const int width = ds - k0 < kSlab ? ds - k0 : kSlab;
+            if (nt == 0 || ds > kSlab) {
+                wave_lds_order();
+                if (WIDE) {
+                    const int pieces = width / 4;
+                    int shift = 0;
+                    while ((1 << shift) < pieces) ++shift;
+                    const int c = min(lane & ((1 << shift) - 1), pieces - 1), r0 = lane >> shift, step = kWave >> shift;
+#pragma unroll 4
+                    for (int r = r0; r < kPlaceRows; r += step)
+                        *reinterpret_cast<float4*>(xs + r * st + 4 * c) =
+                            *reinterpret_cast<const float4*>(x + (size_t)min(r, nv - 1) * g.D + k0 + 4 * c);
+                } else {
+                    const int c = lane & (kSlab - 1);
+                    if (c < ((width + 3) & ~3))
+                        for (int r = lane / kSlab; r < kPlaceRows; r += kWave / kSlab)
+                            xs[r * st + c] = c < width ? x[(size_t)min(r, nv - 1) * g.D + k0 + c] : 0.0f;
+                }
+                wave_lds_order();
+                if (nt == 0)
+                    for (int d = 0; d < width; ++d) norm = fmaf(xs[lane * st + d], xs[lane * st + d], norm);
+            }
+            // the centroid values of eight steps are fetched together, so that their latencies overlap
+            float bv[2][8];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int col = (nt + t) * 16 + row;
+                const float* brow = g.C1 + ((size_t)p * k1 + (col < k1 ? col : 0)) * dp + lo;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int kd = k0 + 4 * u + kq;
+                    bv[t][u] = (t == 0 || two) && kd < ds && col < k1 ? brow[kd] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (4 * u < width) {                         // uniform
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float av = xs[(r * 16 + row) * st + 4 * u + kq];
+                        acc[0][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[0][u], acc[0][r], 0, 0, 0);
+                        if (two) acc[1][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[1][u], acc[1][r], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int col = (nt + t) * 16 + row;
+            const float cn = g.c1n[m * k1 + (col < k1 ? col : 0)];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = r * 16 + 4 * kq + j;
+                    const float xn = __shfl(norm, v, kWave);
+                    if (col < k1 && (t == 0 || two)) at[col * kRowStride + v] = (xn + cn) - 2.0f * acc[t][r][j];
+                }
+        }
+    }
+    wave_lds_order();
+}
+
+// The nearest of the 256 code points of a sub-part: the smallest (Eq. 9 value, number).  Eight values at a time only
+// their minimum is compared; the eight that hold the smallest are looked at again.
+__device__ __forceinline__ uint32_t nearest_code(const CodeEntry* table, const float* at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    scalar_words w = (scalar_words)(uintptr_t)table;
+    auto value = [&](uint32_t ij, float lam, float kc) {
+        const float b2 = at[(ij & 0xffu) * kRowStride + lane], a2 = at[((ij >> 8) & 0xffu) * kRowStride + lane];
+        return fmaf(lam, a2 - b2, b2) + kc;
+    };
+    float best = __builtin_inff();
+    int block = 0;
+    for (int c = 0; c < 256; c += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = value(w[3 * (c + u)], __uint_as_float(w[3 * (c + u) + 1]), __uint_as_float(w[3 * (c + u) + 2]));
+        const float low = fminf(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])), fminf(fminf(v[4], v[5]), fminf(v[6], v[7])));
+        if (low < best) {
+            best = low;
+            block = c;
+        }
+    }
+    uint32_t code = (uint32_t)block;
+#pragma unroll
+    for (int u = 7; u >= 0; --u) {
+        const CodeEntry e = table[block + u];
+        if (value(e.ij, e.lam, e.kc) == best) code = (uint32_t)(block + u);
+    }
+    if (__any(!(best < __builtin_inff()))) {                 // no finite value: by the order of the keys, as everywhere
+        uint32_t low = 0xffffffffu, first = 0u;
+        for (int c = 0; c < 256; ++c) {
+            const uint32_t key = mono_key(value(w[3 * c], __uint_as_float(w[3 * c + 1]), __uint_as_float(w[3 * c + 2])));
+            if (key < low || c == 0) {
+                low = key;
+                first = (uint32_t)c;
+            }
+        }
+        if (!(best < __builtin_inff())) code = first;
+    }
+    return code;
+}
+
+// (pair, lambda) codes (Sec. 3.3 "Offline computation"; Eq. 7 stored directly).  A code stands for the
+// point (1 - lambda) c_i + lambda c_j with lambda = (level - 96) / 16; a sub-vector gets the code of
+// the nearest such point.  With b^2, a^2 its own distances to c_i, c_j and c^2 = ||c_i - c_j||^2, the projection on the line
+// is at (b^2 - a^2 + c^2) / (2 c^2); the level nearest to it (clamped to a byte) is the line's nearest
+// code point, whose distance is Eq. 9 on the same values.  The smallest (distance, pair number) wins;
+// pairs with c^2 = 0 never do.  `table` holds the pairs (entry = pair number, kc = c^2).
+__device__ __forceinline__ uint32_t nearest_pair(const CodeEntry* table, int npairs, const float* at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    scalar_words w = (scalar_words)(uintptr_t)table;
+    uint32_t low = 0xffffffffu;
+    int best = -1;
+    uint32_t best_level = 96;                                // no usable pair: pair 0 at lambda = 0
+    for (int c = 0; c < npairs; ++c) {
+        const uint32_t ij = w[3 * c];
+        const float kc = __uint_as_float(w[3 * c + 2]);
+        if (!(kc > 0.0f)) continue;                          // the same for the wavefront
+        const float b2 = at[(ij & 0xffu) * kRowStride + lane], a2 = at[((ij >> 8) & 0xffu) * kRowStride + lane];
+        const float proj = ((b2 - a2) + kc) / (2.0f * kc);
+        const float level = fminf(fmaxf(floorf(fmaf(proj, 16.0f, 96.5f)), 0.0f), 255.0f);
+        const float lam = fmaf(level, 0.0625f, -6.0f);
+        const uint32_t key = mono_key(fmaf(fmaf(lam, lam, -lam), kc, fmaf(lam, a2 - b2, b2)));
+        if (key < low || best < 0) {
+            low = key;
+            best = c;
+            best_level = (uint32_t)level;
+        }
+    }
+    return (uint32_t)(best < 0 ? 0 : best) | (best_level << 8);
+}
+
+// The nearest line of a training sub-vector (Sec. 3.3 "Offline computation").  With b^2, a^2 its level-1 distances to c_i, c_j
+// and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) / (2 c^2) and misses the vector by
+// b^2 - lambda^2 c^2.  Smallest (error, pair number) wins; pairs of coinciding centroids never do.  Returns
+// pair number << 32 | ordered bits of lambda; pair number 0xffff when the sub-part has no usable pair.
+__device__ __forceinline__ unsigned long long nearest_line(const LinePair* pairs, int npairs, const float* at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    scalar_words w = (scalar_words)(uintptr_t)pairs;
+    uint32_t low = 0xffffffffu;
+    int best = -1;
+    for (int c = 0; c < npairs; ++c) {
+        const uint32_t ij = w[2 * c];
+        const float c2 = __uint_as_float(w[2 * c + 1]);
+        if (!(c2 > 0.0f)) continue;                          // the same for the wavefront
+        const float b2 = at[(ij & 0xffffu) * kRowStride + lane], a2 = at[(ij >> 16) * kRowStride + lane];
+        const float lam = ((b2 - a2) + c2) / (2.0f * c2);
+        const uint32_t key = mono_key(fmaf(-lam * lam, c2, b2));
+        if (key < low || best < 0) {
+            low = key;
+            best = c;
+        }
+    }
+    if (best < 0) return 0xffffffffffffull;
+    const LinePair pr = pairs[best];
+    const float b2 = at[(pr.ij & 0xffffu) * kRowStride + lane], a2 = at[(pr.ij >> 16) * kRowStride + lane];
+    const float lam = ((b2 - a2) + pr.c2) / (2.0f * pr.c2);
+    return ((unsigned long long)(uint32_t)best << 32) | mono_key(lam);
+}
+
+enum { kTableCodes, kPairCodes, kVotes };
+
+template <int MODE, bool WIDE>
+__global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), nt = blockDim.x, waves = nt / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int D = g.D, P = g.P, k1 = g.k1, k2 = g.k2, M = g.M, dp = D / P, per = M / P;
+    const int64_t v0 = (int64_t)blockIdx.x * kPlaceRows;
+    const int nv = (int)(g.n - v0 < kPlaceRows ? g.n - v0 : kPlaceRows);
+    float* xs = reinterpret_cast<float*>(smem + L.off_x) + (size_t)wave * (k1 <= 32 ? L.a_stride : (size_t)kPlaceRows * L.st);
+    float* a0 = reinterpret_cast<float*>(smem + L.off_a);
+    float* d1 = reinterpret_cast<float*>(smem + L.off_d1);
+    unsigned long long* sel = reinterpret_cast<unsigned long long*>(smem + L.off_sel);
+    unsigned long long* leaf = reinterpret_cast<unsigned long long*>(smem + L.off_leaf);
+    uint8_t* code = smem + L.off_code;
+    float* at = a0 + (size_t)wave * L.a_stride;
+    if (MODE != kVotes)
+        for (int e = tid; e < P * kPlaceRows; e += nt) sel[e] = leaf[e] = ~0ull;
+
+    for (int m0 = 0; m0 < M; m0 += waves) {
+        const int m = m0 + wave;
+        if (m < M) {
+            subpart_distances<WIDE>(g, v0, nv, m, L.st, xs, at);
+            if (MODE == kVotes) {
+                const unsigned long long vote = nearest_line(g.pairs + (size_t)m * g.npairs, g.npairs, at);
+                if (lane < nv) g.keys[(size_t)m * g.n + v0 + lane] = ((unsigned long long)m << 48) | vote;
+            } else if (MODE == kTableCodes) {
+                code[lane * M + m] = (uint8_t)nearest_code(g.table + (size_t)m * 256, at);
+            } else {
+                const uint32_t c = nearest_pair(g.table + (size_t)m * 256, g.npairs, at);
+                code[(lane * M + m) * 2] = (uint8_t)c;
+                code[(lane * M + m) * 2 + 1] = (uint8_t)(c >> 8);
+            }
+        }
+        if (MODE == kVotes) continue;
+        __syncthreads();
+        // the parts' distances: sub-parts in ascending order; a wavefront has its own centroids throughout
+        for (int s = 0; s < waves && m0 + s < M; ++s) {
+            const int q = (m0 + s) % per;
+            const float* as = a0 + (size_t)s * L.a_stride + lane;
+            unsigned long long best = ~0ull;
+            for (int i = wave; i < k1; i += waves) {
+                float sum = as[i * kRowStride];
+                if (q > 0) sum += d1[i * kRowStride + lane];
+                d1[i * kRowStride + lane] = sum;
+                const unsigned long long key = ((unsigned long long)mono_key(sum) << 32) | (unsigned)i;
+                best = key < best ? key : best;
+            }
+            if (q == per - 1) atomicMin(&sel[(m0 + s) / per * kPlaceRows + lane], best);
+        }
+        __syncthreads();
+    }
+    if (MODE == kVotes) return;
+
+    // ---- level 2: the children of the nearest cluster, plain squared differences, dimensions in ascending order ----
+    const int nd4 = dp / 4;
+    for (int p = 0; p < P; ++p)
+        for (int e = tid; e < kPlaceRows * k2; e += nt) {
+            const int v = e / k2, j = e - v * k2;
+            if (v >= nv) continue;
+            const uint32_t i = (uint32_t)sel[p * kPlaceRows + v];
+            const float* y = g.x + (size_t)(v0 + v) * D + (size_t)p * dp;
+            float acc = 0.0f;
+            if (WIDE && g.C2t) {
+                const float4* c = reinterpret_cast<const float4*>(g.C2t) + ((size_t)p * k1 + i) * nd4 * k2 + j;
+#pragma unroll 4
+                for (int d = 0; d < nd4; ++d) {
+                    const float4 yv = *reinterpret_cast<const float4*>(y + 4 * d), cv = c[(size_t)d * k2];
+                    float diff = yv.x - cv.x;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.y - cv.y;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.z - cv.z;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.w - cv.w;
+                    acc = fmaf(diff, diff, acc);
+                }
+            } else {
+                const float* c = g.C2 + (((size_t)p * k1 + i) * k2 + j) * dp;
+                for (int d = 0; d < dp; ++d) {
+                    const float diff = y[d] - c[d];
+                    acc = fmaf(diff, diff, acc);
+                }
+            }
+            atomicMin(&leaf[p * kPlaceRows + v], ((unsigned long long)mono_key(acc) << 32) | (i * (uint32_t)k2 + (uint32_t)j));
+        }
+    __syncthreads();
+    if (tid < nv) {
+        unsigned long long lin = 0;
+        for (int p = 0; p < P; ++p) lin = lin * g.k1k2 + (uint32_t)leaf[p * kPlaceRows + tid];
+        g.slots[v0 + tid] = (uint32_t)(lin % g.H);
+    }
+    const int cb = M * (MODE == kPairCodes ? 2 : 1), bytes = nv * cb;
+    uint8_t* out = g.codes + (size_t)v0 * cb;
+    if (((uintptr_t)out & 3u) == 0 && bytes % 4 == 0)
+        for (int e = tid; e < bytes / 4; e += nt) reinterpret_cast<uint32_t*>(out)[e] = reinterpret_cast<const uint32_t*>(code)[e];
+    else
+        for (int e = tid; e < bytes; e += nt) out[e] = code[e];
+}
+
+template <int MODE>
+hipError_t launch_mode(const PlaceArgs& a, hipStream_t s) {
+    const int ds = a.D / a.M, cb = a.M * (MODE == kPairCodes ? 2 : 1);
+    const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && ds % 4 == 0;
+    // wavefronts per workgroup: those that leave a compute unit the most, none without a sub-part
+    int waves = 1;
+    size_t most = 0;
+    for (int w = 4; w >= 1; w /= 2) {
+        const size_t lds = place_layout(ds, a.P, a.k1, cb, w, MODE == kVotes).total;
+        if (lds > kMaxLds || (w > a.M && w > 1)) continue;
+        const size_t resident = (size_t)w * (kMaxLds / lds);
+        if (resident > most) {
+            most = resident;
+            waves = w;
+        }
+    }
+    const PlaceLds L = place_layout(ds, a.P, a.k1, cb, waves, MODE == kVotes);
+    const void* fn = wide ? reinterpret_cast<const void*>(place_kernel<MODE, true>) : reinterpret_cast<const void*>(place_kernel<MODE, false>);
+    if (L.total > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.total);
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid((unsigned)((a.n + kPlaceRows - 1) / kPlaceRows)), block((unsigned)waves * kWave);
+    if (wide) hipLaunchKernelGGL((place_kernel<MODE, true>), grid, block, L.total, s, a, L);
+    else hipLaunchKernelGGL((place_kernel<MODE, false>), grid, block, L.total, s, a, L);
+    return hipGetLastError();
+}
+
+// squared norms of the level-1 centroids' sub-parts, added up in double precision as the host does
+__global__ void subpart_norms_kernel(const float* C1, int D, int P, int k1, int M, float* c1n) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= M * k1) return;
+    const int m = e / k1, i = e - m * k1, dp = D / P, ds = D / M, p = m / (M / P);
+    const float* c = C1 + ((size_t)p * k1 + i) * dp + (m * ds - p * dp);
+    double s = 0.0;
+    for (int d = 0; d < ds; ++d) s = __dadd_rn(s, __dmul_rn((double)c[d], (double)c[d]));
+    c1n[e] = (float)s;
+}
+
+}  // namespace
+
+hipError_t launch_place(const PlaceArgs& a, bool pair_codes, hipStream_t s) {
+    if (a.n <= 0) return hipSuccess;
+    return pair_codes ? launch_mode<kPairCodes>(a, s) : launch_mode<kTableCodes>(a, s);
+}
+
+hipError_t launch_votes(const PlaceArgs& a, hipStream_t s) { return a.n > 0 ? launch_mode<kVotes>(a, s) : hipSuccess; }
+
+hipError_t launch_subpart_norms(const float* C1, int D, int P, int k1, int M, float* c1n, hipStream_t s) {
+    hipLaunchKernelGGL(subpart_norms_kernel, dim3((unsigned)((M * k1 + 255) / 256)), dim3(256), 0, s, C1, D, P, k1, M, c1n);
+    return hipGetLastError();
+}
+
+}  // namespace pqt

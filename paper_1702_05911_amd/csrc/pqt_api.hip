@@ -172,15 +172,15 @@ extern "C" {
 
 const char* pqt_last_error(void) { return pqt_host::error_buffer(); }
 
-int pqt_index_from_arrays(const pqt_index_arrays* a, int location, int device, pqt_index** out) {
-    if (!a || !out) return fail(PQT_EINVAL, "pqt_index_from_arrays: null argument");
-    *out = nullptr;
+// lists = false: the index gets no lists (no pointer array, ids or codes; N counts as 0), a builder brings them later
+static int make_index(const pqt_index_arrays* a, int location, int device, bool lists, pqt_index** out) {
     if (location != PQT_HOST && location != PQT_DEVICE)
         return fail(PQT_EINVAL, "pqt_index_from_arrays: location must be PQT_HOST or PQT_DEVICE");
     if (a->code_format != PQT_CODES_TABLE && a->code_format != PQT_CODES_PAIR_LAMBDA)
         return fail(PQT_EINVAL, "pqt_index_from_arrays: code_format %u", a->code_format);
     const bool pair_codes = a->code_format == PQT_CODES_PAIR_LAMBDA;   // the line table is not used then
-    if (!a->C1 || !a->C2 || !a->cc || !a->offsets || (a->N > 0 && (!a->ids || !a->codes)) ||
+    static const uint32_t no_offsets[2] = {0u, 0u};
+    if (!a->C1 || !a->C2 || !a->cc || (lists && !a->offsets) || (a->N > 0 && (!a->ids || !a->codes)) ||
         (!pair_codes && (!a->tbl_i || !a->tbl_j || !a->tbl_lambda)))
         return fail(PQT_EINVAL, "pqt_index_from_arrays: null array");
     const pqt_index_arrays& h = *a;
@@ -210,7 +210,7 @@ int pqt_index_from_arrays(const pqt_index_arrays* a, int location, int device, p
         off = off_copy.data();
     }
     uint64_t nonempty = 0;
-    vrc = pqt_host::check_arrays(h.k1, h.M, h.N, h.H, h.code_format, off, h.tbl_i, h.tbl_j,
+    vrc = pqt_host::check_arrays(h.k1, h.M, h.N, lists ? h.H : 1, h.code_format, lists ? off : no_offsets, h.tbl_i, h.tbl_j,
                                  location == PQT_HOST ? h.codes : nullptr, &nonempty, why);
     if (vrc != PQT_OK) return fail(vrc, "%s", why.c_str());
     const size_t ntab = (size_t)h.M * 256;
@@ -321,15 +321,37 @@ int pqt_index_from_arrays(const pqt_index_arrays* a, int location, int device, p
         (c2t.size() && (rc = upload(&ix->C2t, c2t.data(), c2t.size() * 4, hipMemcpyHostToDevice, &ix->bytes_index))) ||
         (rc = upload(&ix->table, table.data(), table.size() * sizeof(pqt::CodeEntry), hipMemcpyHostToDevice,
                      &ix->bytes_index)) ||
-        (rc = upload(&ix->offsets, h.offsets, ((size_t)h.H + 1) * 4, big, &ix->bytes_index)) ||
-        (rc = upload(&ix->ids, h.ids, (size_t)h.N * 4, big, &ix->bytes_index)) ||
-        (rc = upload(&ix->codes, h.codes, (size_t)h.N * code_bytes, big, &ix->bytes_index))) {
+        (lists && ((rc = upload(&ix->offsets, h.offsets, ((size_t)h.H + 1) * 4, big, &ix->bytes_index)) ||
+                   (rc = upload(&ix->ids, h.ids, (size_t)h.N * 4, big, &ix->bytes_index)) ||
+                   (rc = upload(&ix->codes, h.codes, (size_t)h.N * code_bytes, big, &ix->bytes_index))))) {
         pqt_index_free(ix);
         return rc;
     }
     *out = ix;
     return PQT_OK;
 }
+
+int pqt_index_from_arrays(const pqt_index_arrays* a, int location, int device, pqt_index** out) {
+    if (!a || !out) return fail(PQT_EINVAL, "pqt_index_from_arrays: null argument");
+    *out = nullptr;
+    return make_index(a, location, device, true, out);
+}
+
+}  // extern "C"
+
+int pqt_host::make_index_without_lists(const pqt_index_arrays* params, int device, pqt_index** out) {
+    *out = nullptr;
+    pqt_index_arrays a = *params;
+    a.N = 0;
+    a.offsets = nullptr;
+    a.ids = nullptr;
+    a.codes = nullptr;
+    const int rc = make_index(&a, PQT_HOST, device, false, out);
+    if (rc == PQT_OK) (*out)->bytes_index += ((uint64_t)a.H + 1) * 4;      // the pointer array it will hold
+    return rc;
+}
+
+extern "C" {
 
 int pqt_index_load(const char* path, int device, pqt_index** out) {
     if (!path || !out) return fail(PQT_EINVAL, "pqt_index_load: null argument");

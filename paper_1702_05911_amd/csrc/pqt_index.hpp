@@ -36,6 +36,9 @@ struct DeviceGuard {   // make the index's GPU current for the duration of a cal
 // grows the per-batch workspace of an index to nq queries with lists of R entries
 int ensure_workspace(pqt_index* ix, int64_t nq, int R);
 
+// an index with codebooks and tables only (host arrays; N, offsets, ids and codes of `params` are ignored): the builder's
+int make_index_without_lists(const pqt_index_arrays* params, int device, pqt_index** out);
+
 }  // namespace pqt_host
 
 struct pqt_index {

@@ -41,6 +41,37 @@ struct TraverseArgs {
 size_t traverse_lds_bytes(int D, int P, int k1, int k2, int M, int w);
 hipError_t launch_traverse(const TraverseArgs& a, hipStream_t s);
 
+// One pair of level-1 centroids of a sub-part: i | j << 16, ||c_i - c_j||^2.
+struct LinePair {
+    uint32_t ij;
+    float c2;
+};
+
+// Offline phase: bin slots and codes of n vectors (launch_place), or their line votes (launch_votes).
+struct PlaceArgs {
+    const float* x;           // n x D
+    int64_t n;
+    int D, P, k1, k2, M;
+    const float* C1;          // P x k1 x dp
+    const float* c1n;         // M x k1
+    // launch_place
+    const float* C2;          // P x k1 x k2 x dp
+    const float* C2t;         // as TraverseArgs
+    const CodeEntry* table;   // M x 256 (pair codes: entry = pair number)
+    int npairs;               // k1 (k1 - 1) / 2 (pair codes and votes)
+    uint32_t k1k2;
+    uint64_t H;
+    uint8_t* codes;           // n x code bytes
+    uint32_t* slots;          // n
+    // launch_votes
+    const LinePair* pairs;    // M x npairs
+    unsigned long long* keys; // M x n: sub-part << 48 | pair << 32 | ordered bits of lambda (pair 0xffff: no usable pair)
+};
+hipError_t launch_place(const PlaceArgs& a, bool pair_codes, hipStream_t s);
+hipError_t launch_votes(const PlaceArgs& a, hipStream_t s);
+// c1n of level-1 centroids on the GPU
+hipError_t launch_subpart_norms(const float* C1, int D, int P, int k1, int M, float* c1n, hipStream_t s);
+
 struct RankArgs {
     int64_t nq;
     int P, R, T, C;

@@ -17,9 +17,11 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <string>
 #include <vector>
 
 #include "pqt_device.hpp"
+#include "pqt_host.hpp"
 #include "pqt_index.hpp"
 
 using pqt_host::DeviceGuard;
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, i
 // Bound by the two vector instructions per value and centroid (10 us of an iteration's 36 at 100,000 vectors x 128, 16
 // centroids), the staging of the vectors from the last-level cache (8 us) and the sums (9 us).  One wavefront per vector with
 // one lane per centroid, all vectors sorted by cell in every iteration: 35.9 ms for the whole of pqt_train on 100,000
-// vectors x 128 (16 and 8 centroids, 20 iterations, line table), against 2.8.  Staging by wavefront with the next slab in
+// vectors x 128 (16 and 8 centroids, 20 iterations, line table), against 2.1.  Staging by wavefront with the next slab in
 // registers was slower (41 us an iteration): its registers cost a resident workgroup.
 template <int KB>
 __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) {
@@ -397,60 +399,6 @@ __global__ void iota_u32_kernel(uint32_t* out, uint32_t n) {
     if (i < n) out[i] = i;
 }
 
-// The nearest line of every training sub-vector (Sec. 3.3 "Offline computation").  With b^2, a^2 the vector's level-1
-// distances to c_i, c_j of sub-part m and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) /
-// (2 c^2) and misses the vector by b^2 - lambda^2 c^2.  Smallest (error, pair number) wins; pairs of
-// coinciding centroids never do.  key[m][v] = sub-part << 48 | pair number << 32 | ordered bits of lambda (sorting these
-// orders the votes by sub-part, line, then lambda); pair number 0xffff when the sub-part has no usable pair.
-// One lane per vector, one sub-part per workgroup: the pair is the same for a wavefront and comes through the scalar
-// cache, the distances of its 64 vectors lie in LDS with the vector fastest, so no two lanes meet in a bank and nothing is
-// compared across lanes (100,000 x 8 sub-parts x 120 pairs: 103 us; with the pairs spread over the lanes 276).
-struct LinePair {
-    uint32_t ij;                 // i | j << 16
-    float c2;
-};
-constexpr int kVoteStride = kWave + 1;
-__global__ __launch_bounds__(kTrainThreads) void line_vote_kernel(const float* a, int64_t n, int M, int k1, const LinePair* pairs,
-                                                                   int npairs, unsigned long long* keys, int64_t key_stride,
-                                                                   int64_t key_base) {
-    typedef const __attribute__((address_space(4))) uint32_t* scalar_words;
-    extern __shared__ float dist[];                          // [wavefront][centroid][vector]
-    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int m = blockIdx.y;
-    const int64_t v0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) * kWave;
-    float* mine = dist + (size_t)wave * k1 * kVoteStride;
-    for (int e = lane; e < k1 * kWave; e += kWave) {         // consecutive lanes: consecutive centroids of a vector
-        const int v = e / k1, i = e - v * k1;
-        mine[i * kVoteStride + v] = v0 + v < n ? a[((size_t)(v0 + v) * M + m) * k1 + i] : 0.0f;
-    }
-    wave_lds_order();
-    const LinePair* pm = pairs + (size_t)m * npairs;
-    uint32_t best = 0xffffffffu;
-    int best_pid = -1;
-    scalar_words w = (scalar_words)(uintptr_t)pm;
-    for (int pid = 0; pid < npairs; ++pid) {
-        const uint32_t ij = w[2 * pid];
-        const float c2 = __uint_as_float(w[2 * pid + 1]);
-        if (!(c2 > 0.0f)) continue;                          // the same for the wavefront
-        const float b2 = mine[(ij & 0xffffu) * kVoteStride + lane], a2 = mine[(ij >> 16) * kVoteStride + lane];
-        const float lam = ((b2 - a2) + c2) / (2.0f * c2);
-        const uint32_t key = mono_key(fmaf(-lam * lam, c2, b2));
-        if (key < best || best_pid < 0) {
-            best = key;
-            best_pid = pid;
-        }
-    }
-    if (v0 + lane >= n) return;
-    unsigned long long out = 0xffffffffffffull;
-    if (best_pid >= 0) {
-        const LinePair pr = pm[best_pid];
-        const float b2 = mine[(pr.ij & 0xffffu) * kVoteStride + lane], a2 = mine[(pr.ij >> 16) * kVoteStride + lane];
-        const float lam = ((b2 - a2) + pr.c2) / (2.0f * pr.c2);
-        out = ((unsigned long long)(uint32_t)best_pid << 32) | mono_key(lam);
-    }
-    keys[(size_t)m * key_stride + key_base + v0 + lane] = ((unsigned long long)m << 48) | out;
-}
-
 // first[m][q] = where line q's votes start among the sorted votes of sub-part m (m counted within the batch), q = 0..npairs
 __global__ void line_ranges_kernel(const unsigned long long* sorted, uint32_t nt, int m0, int m1, uint32_t npairs, uint32_t* first) {
     const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -599,6 +547,13 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     const uint32_t npairs = k1 * (k1 - 1) / 2;
     const uint32_t nt = npairs ? (uint32_t)tp->n_table : 0u;
     const size_t nd4 = ((size_t)dp + 3) / 4;
+    if (nt) {                                                // (the table serves an index of these sizes)
+        std::string why;
+        const int rc = pqt_host::check_sizes(D, P, k1, k2, M, 0, 1, 1, 1, PQT_CODES_TABLE, nullptr, why);
+        if (rc != PQT_OK) return fail(rc, "%s", why.c_str());
+        if (traverse_lds_bytes(D, P, k1, k2, M, 1) > kMaxLds)
+            return fail(PQT_EUNSUPPORTED, "pqt_train: D=%u exceeds the LDS budget of the traversal", D);
+    }
     LloydArgs l1 = {}, l2 = {};
     l1.X = vectors; l1.n = n; l1.D = (int)D; l1.dp = dp; l1.P = (int)P;
     l1.wide = reinterpret_cast<uintptr_t>(vectors) % 16 == 0 && D % 4 == 0 && dp % 4 == 0;
@@ -636,7 +591,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     mem.want(&cub_temp, cub_bytes);
     // the line table: the votes of as many sub-parts as fit 2^27 keys are sorted together
     LinePair* pair_dev = nullptr;
-    float* lam_dev = nullptr;
+    float *c1n_dev = nullptr, *lam_dev = nullptr;
     unsigned long long *keys = nullptr, *keys_sorted = nullptr;
     uint32_t *first_dev = nullptr, *at_dev = nullptr;
     const uint32_t batch = nt ? std::min<uint32_t>(M, std::max<uint32_t>(1, (1u << 27) / nt)) : 0u;
@@ -646,6 +601,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
         HIP_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, keys, keys_sorted, (int)(batch * nt), 0, key_bits, st));
         mem.want(&sort_temp, sort_bytes);
         mem.want(&pair_dev, (size_t)M * npairs);
+        mem.want(&c1n_dev, (size_t)M * k1);
         mem.want(&keys, (size_t)M * nt);
         mem.want(&keys_sorted, (size_t)batch * nt);
         mem.want(&first_dev, (size_t)batch * (npairs + 1));
@@ -716,24 +672,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     if (tbl_lambda) memset(tbl_lambda, 0, (size_t)M * 256 * sizeof(float));
     if (nt == 0) return PQT_OK;
 
-    // ---- line table: level-1 distances of the first n_table vectors by the query path's own traversal kernel
-    // (an index without vectors carries the codebooks to the GPU), then one vote per sub-vector ---------------------
-    std::vector<uint32_t> zeros(2, 0u);
-    std::vector<uint8_t> zt((size_t)M * 256, 0);
-    std::vector<float> zl((size_t)M * 256, 0.0f);
-    pqt_index_arrays ea = {};
-    ea.N = 0; ea.H = 1; ea.D = D; ea.P = P; ea.k1 = k1; ea.k2 = k2; ea.M = M; ea.T = 1; ea.C = 1;
-    ea.C1 = C1.data(); ea.C2 = C2.data(); ea.tbl_i = zt.data(); ea.tbl_j = zt.data(); ea.tbl_lambda = zl.data();
-    ea.cc = cc.data(); ea.offsets = zeros.data(); ea.ids = nullptr; ea.codes = nullptr; ea.code_format = PQT_CODES_TABLE;
-    pqt_index* ix = nullptr;
-    int rc = pqt_index_from_arrays(&ea, PQT_HOST, device, &ix);
-    if (rc) return rc;
-    struct IndexHolder {
-        pqt_index* ix;
-        ~IndexHolder() { pqt_index_free(ix); }
-    } holder{ix};
-    if (pqt::traverse_lds_bytes(D, P, k1, k2, M, 1) > ix->lds_limit)
-        return fail(PQT_EUNSUPPORTED, "pqt_train: D=%u exceeds the LDS budget of the traversal", D);
+    // ---- line table: one vote per sub-vector of the first n_table, by the kernel that encodes vectors ------------------
     {
         size_t e = 0;
         for (size_t m = 0; m < M; ++m)
@@ -741,26 +680,12 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
                 for (uint32_t j = i + 1; j < k1; ++j) pair_host[e++] = LinePair{i | (j << 16), cc[(m * k1 + i) * k1 + j]};
     }
     HIP_TRY(hipMemcpyAsync(pair_dev, pair_host.data(), pair_host.size() * sizeof(LinePair), hipMemcpyHostToDevice, st));
-    // four wavefronts a workgroup while their distances fit the LDS that every launch may ask for
-    const unsigned vote_waves = k1 <= 60 ? 4 : 1;
-    const size_t vote_lds = sizeof(float) * vote_waves * k1 * kVoteStride;
-    if (vote_lds > 64 * 1024)
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(line_vote_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)vote_lds));
-    const int64_t chunk = 1 << 17;
-    for (int64_t s = 0; s < (int64_t)nt; s += chunk) {
-        const int64_t mrows = (int64_t)nt - s < chunk ? (int64_t)nt - s : chunk;
-        if ((rc = pqt_host::ensure_workspace(ix, mrows, (int)k2))) return rc;
-        pqt::TraverseArgs ta;
-        ta.queries = vectors + (size_t)s * D; ta.nq = mrows;
-        ta.D = (int)D; ta.P = (int)P; ta.k1 = (int)k1; ta.k2 = (int)k2; ta.M = (int)M; ta.w = 1;
-        ta.C1 = ix->C1; ta.c1n = ix->c1n; ta.C2 = ix->C2; ta.C2t = ix->C2t;
-        ta.a = ix->ws_a; ta.L_d = ix->ws_Ld; ta.L_id = ix->ws_Lid; ta.sel_tap = nullptr; ta.counters = nullptr;
-        HIP_TRY(pqt::launch_traverse(ta, st));
-        const int64_t per_block = (int64_t)vote_waves * kWave;
-        hipLaunchKernelGGL(line_vote_kernel, dim3((unsigned)((mrows + per_block - 1) / per_block), M), dim3(vote_waves * kWave), vote_lds, st,
-                           ix->ws_a, mrows, (int)M, (int)k1, pair_dev, (int)npairs, keys, (int64_t)nt, s);
-        HIP_TRY(hipGetLastError());
-    }
+    PlaceArgs pa = {};
+    pa.x = vectors; pa.n = nt;
+    pa.D = (int)D; pa.P = (int)P; pa.k1 = (int)k1; pa.k2 = (int)k2; pa.M = (int)M;
+    pa.C1 = l1.cen; pa.c1n = c1n_dev; pa.pairs = pair_dev; pa.npairs = (int)npairs; pa.keys = keys;
+    HIP_TRY(launch_subpart_norms(l1.cen, (int)D, (int)P, (int)k1, (int)M, c1n_dev, st));
+    HIP_TRY(launch_votes(pa, st));
     for (uint32_t m0 = 0; m0 < M; m0 += batch) {
         const uint32_t m1 = std::min(M, m0 + batch);
         HIP_TRY(hipcub::DeviceRadixSort::SortKeys(sort_temp, sort_bytes, keys + (size_t)m0 * nt, keys_sorted, (int)((m1 - m0) * nt), 0,

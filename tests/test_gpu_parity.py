@@ -614,6 +614,55 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
         assert e.value.code == pqt.PQT_EFORMAT
 
 
+@pytest.mark.parametrize("N, D, P, k1, k2, M, fmt, offset", [
+    (63, 16, 2, 16, 8, 4, 0, 0),           # one vector short of a workgroup; one tile of centroids
+    (65, 24, 2, 17, 3, 4, 0, 0),           # one vector in the second workgroup; a second, nearly empty tile of centroids
+    (200, 48, 1, 33, 2, 1, 0, 0),          # one sub-part of two slabs, centroids in two passes over them
+    (130, 40, 4, 5, 7, 8, 0, 0),           # four tree parts, pieces of one sub-part each
+    (129, 30, 2, 6, 4, 6, 0, 0),           # sub-parts of five dimensions: no 16-byte rows
+    (100, 16, 2, 8, 1, 4, 0, 1),           # vectors that do not start at a multiple of 16 bytes
+    (70, 16, 1, 256, 2, 2, 0, 0),          # the most centroids
+    (131, 12, 1, 4, 300, 3, 0, 0),         # more children than threads
+    (67, 16, 2, 20, 7, 4, 1, 0),           # (pair, lambda) codes
+    (90, 6, 2, 3, 2, 6, 1, 1),             # sub-parts of one dimension
+])
+def test_builder_edges(pqt, N, D, P, k1, k2, M, fmt, offset):
+    """Bins, codes and lists at the edges of the placing kernel's tiles, slabs and passes, against the oracle.  Codebooks,
+    vectors and lambdas are small whole numbers and multiples of 1/16, so that every distance is exact in fp32 and float64
+    and the results are equal, ties included; slots are hashed for the odd H."""
+    import torch
+    rng = np.random.default_rng(5)
+    top = 8 if fmt else 16
+    dp = D // P
+    X = rng.integers(0, top, (N, D)).astype(np.float32)
+    C1 = rng.integers(0, top, (P, k1, dp)).astype(np.float32)
+    C2 = rng.integers(0, top, (P, k1, k2, dp)).astype(np.float32)
+    ti, tj = (rng.integers(0, k1, (M, 256)).astype(np.uint8) for _ in range(2))
+    tl = (rng.integers(-8, 25, (M, 256)) / 16.0).astype(np.float32)
+    H = max(1, min((k1 * k2) ** P, 1001))
+    params = dict(N=N, H=H, D=D, P=P, k1=k1, k2=k2, M=M, T=16, C=16, C1=C1, C2=C2, tbl_i=ti, tbl_j=tj, tbl_lam=tl,
+                  cc=B.pair_table(C1, M), code_format=fmt)
+    buf = torch.empty((N * D + offset,), dtype=torch.float32, device="cuda")
+    Xd = buf[offset:].view(N, D)
+    Xd.copy_(torch.from_numpy(X))
+    b = pqt.pqt_builder_create(params, 0)
+    cut = N // 3
+    pqt.pqt_builder_add(b, Xd[:cut])                                 # the second piece starts at an odd row
+    pqt.pqt_builder_add(b, Xd[cut:])
+    ix = pqt.pqt_builder_finish(b)
+    pqt.pqt_builder_free(b)
+    try:
+        got = {n: t.cpu().numpy() for n, t in pqt.pqt_index_export(ix, ("offsets", "ids", "codes")).items()}
+        offsets, ids = B.inverted_lists(B.bin_slots_batch(X, C1, C2, H), H)
+        np.testing.assert_array_equal(got["offsets"], offsets)
+        np.testing.assert_array_equal(got["ids"], ids)
+        codes = B.encode_pair_lambda(X, C1, M) if fmt else B.encode_batch(X, C1, M, ti, tj, tl)
+        np.testing.assert_array_equal(got["codes"], codes[ids])
+        assert pqt.pqt_index_info(ix)["bytes_index"] >= 4 * (H + 1) + N * (4 + codes.shape[1])
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_pair_lambda_native_builder(pqt, tiny_pair, tmp_path):
     """pqt_builder_* with (pair, lambda) codes: every code names a point that is (within fp32 rounding of
     the level-1 distances it is computed from) as near as the nearest code point, with the level nearest
