@@ -162,8 +162,8 @@ int pqt_train(const pqt_train_params* params, const float* vectors, int device, 
  * of vectors that will be added and whose offsets / ids / codes are ignored.
  *   pqt_builder_create  copies the codebooks to GPU `device`.
  *   pqt_builder_add     takes n more vectors (device, n x D row-major fp32; they get the next
- *                       n ids), sorts them into bins with the query path's own traversal
- *                       kernel and encodes them; asynchronous on hip_stream.  Any number of
+ *                       n ids), sorts them into bins with the query path's own level-1
+ *                       distances and encodes them; asynchronous on hip_stream.  Any number of
  *                       calls; the total must be N.
  *   pqt_builder_finish  orders the ids by (slot, id), builds the pointer array, permutes the
  *                       codes, and returns the finished index (released with
