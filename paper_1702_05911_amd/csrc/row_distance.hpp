@@ -12,24 +12,22 @@ struct Piece;
 template <>
 struct Piece<float> {
     static constexpr int kElems = 4;
-    static __device__ __forceinline__ float add(const float* row, int piece, const float* y, float acc) {
-        const float4 x = reinterpret_cast<const float4*>(row)[piece];
+    static __device__ __forceinline__ float add(uint4 x, int piece, const float* y, float acc) {
         const float4 v = reinterpret_cast<const float4*>(y)[piece];
-        float d = v.x - x.x;
+        float d = v.x - __uint_as_float(x.x);
         acc = fmaf(d, d, acc);
-        d = v.y - x.y;
+        d = v.y - __uint_as_float(x.y);
         acc = fmaf(d, d, acc);
-        d = v.z - x.z;
+        d = v.z - __uint_as_float(x.z);
         acc = fmaf(d, d, acc);
-        d = v.w - x.w;
+        d = v.w - __uint_as_float(x.w);
         return fmaf(d, d, acc);
     }
 };
 template <>
 struct Piece<uint8_t> {
     static constexpr int kElems = 16;
-    static __device__ __forceinline__ float add(const uint8_t* row, int piece, const float* y, float acc) {
-        const uint4 x = reinterpret_cast<const uint4*>(row)[piece];
+    static __device__ __forceinline__ float add(uint4 x, int piece, const float* y, float acc) {
         const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -63,7 +61,8 @@ __device__ __forceinline__ float row_distance(const Elem* X, int64_t row, int D,
     float acc = 0.0f;
     if (row >= 0) {
         const Elem* x = X + (size_t)row * D;
-        for (int piece = l; piece < npieces; piece += lpr) acc = Piece<Elem>::add(x, piece, y, acc);
+        for (int piece = l; piece < npieces; piece += lpr)
+            acc = Piece<Elem>::add(reinterpret_cast<const uint4*>(x)[piece], piece, y, acc);
     }
     for (int off = 1; off < lpr; off <<= 1) acc += __shfl_xor(acc, off, kWave);
     return acc;

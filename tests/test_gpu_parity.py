@@ -453,6 +453,49 @@ def test_exact_rerank_of_short_list(pqt, tiny, tmp_path):
         pqt.pqt_index_free(gix)
 
 
+def _whole_number_index(pqt, N, D, P, k1, k2, M, H=None, T=64, C=1024, fmt=0, distinct=None, seed=3):
+    """An index over whole-number vectors built by the library, and its vectors: (index, X on the GPU)."""
+    import torch
+    from paper_1702_05911_amd import builder
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    X = torch.randint(0, 32, (N, D), generator=gen, device="cuda").float()
+    if distinct:
+        X = X[torch.randint(0, distinct, (N,), generator=gen, device="cuda")].contiguous()
+    return builder.build_index_native(X, P=P, k1=k1, k2=k2, M=M, H=H, T=T, C=C, iters=4, code_format=fmt), X
+
+
+@pytest.mark.parametrize("D, stored, k_short, k, distinct", [
+    (16, "u8", 1, 1, 0),                   # a row is one piece: 64 rows per wavefront
+    (48, "u8", 1000, 100, 0),              # three pieces: one lane of four idle
+    (128, "u8", 1024, 1024, 0),            # the longest list, all of it returned
+    (20, "f32", 257, 63, 0),               # five pieces
+    (260, "f32", 65, 64, 0),               # more pieces than lanes
+    (32, "u8", 900, 50, 3),                # three different vectors: a bin holds hundreds, all are sorted
+    (32, "f32", 700, 699, 0),              # more results asked for than some queries have
+])
+def test_exact_rerank_edges(pqt, D, stored, k_short, k, distinct):
+    """Row widths, list lengths and ties of the exact re-ranking: whole numbers, so the distances are exact and the result
+    is a sort of the short list by (distance, id)."""
+    import torch
+    ix, X = _whole_number_index(pqt, 5000, D, 2, 4, 2, 2, T=64, C=1024 if k_short != 700 else 700, distinct=distinct)
+    try:
+        if k_short == 700:
+            pqt.pqt_set_budget(ix, 3, 700)                           # three tuples: fewer candidates than results
+        pqt.pqt_index_set_vectors(ix, X.to(torch.uint8) if stored == "u8" else X)
+        Y = X[:9] + 1.0
+        short, _ = pqt.pqt_query_batch(ix, Y, k_short, 3)
+        ids, d = pqt.pqt_query_batch_exact(ix, Y, k_short, k, 3)
+        short = torch.sort(torch.where(short < 0, 1 << 40, short), dim=1).values
+        have = short < (1 << 40)
+        true = ((X.double()[torch.where(have, short, 0)] - Y.double()[:, None]) ** 2).sum(2)
+        true = torch.where(have, true, float("inf"))
+        order = torch.argsort(true, dim=1, stable=True)[:, :k]
+        assert torch.equal(torch.where(have, short, -1).gather(1, order), ids)
+        assert torch.equal(true.gather(1, order).float(), d)
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_native_builder(pqt, tiny, tmp_path):
     """pqt_builder_*: vectors streamed in ragged chunks; the saved index satisfies the oracle's
     definitions (bin of every vector, nearest code point, sorted lists) and answers queries exactly as
