@@ -2,6 +2,8 @@
 // last kernel): LDS layout, workgroup shape, and the dispatch to the kernel variant for the index's code
 // width.  The kernel itself is in rerank_kernel.hpp, compiled per code width in rerank_table*.hip and
 // rerank_pair*.hip.
+#include <algorithm>
+
 #include "pqt_device.hpp"
 #include "rank_head_device.hpp"
 #include "rerank_variants.hpp"
@@ -20,7 +22,8 @@ static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, 
     // at offset 0: lookups need no base register.
     // One float per table entry, or (b^2, a^2 - b^2, c^2, -) per centroid pair for (pair, lambda) codes.
     L.lut = (uint32_t)o;       o += code_format == 1 ? sizeof(float4) * ((size_t)M << pair_table_shift(k1)) : sizeof(float) * M * 256;
-    L.surv = (uint32_t)o;      o += sizeof(unsigned long long) * L.scap;
+    // the survivors are collected when the last score is known: they take the table's place
+    L.surv = 0;                o = std::max(o, sizeof(unsigned long long) * (size_t)L.scap);
     L.hist = (uint32_t)o;      o += sizeof(uint32_t) * kHistSize;
     L.part = (uint32_t)o;      o += sizeof(uint32_t) * threads;      // scan scratch of the exact selection
     // everything above is free while a workgroup runs the full bin ranking of its query, which uses
@@ -79,13 +82,16 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
         switch (taps || a.M % 2 ? 0 : a.M / 2) {
             case 2: return launch_rerank_pair2(a, L, rk, RL, taps, f, s);
             case 4: return launch_rerank_pair4(a, L, rk, RL, taps, f, s);
+            case 6: return launch_rerank_pair6(a, L, rk, RL, taps, f, s);
             case 8: return launch_rerank_pair8(a, L, rk, RL, taps, f, s);
+            case 16: return launch_rerank_pair16(a, L, rk, RL, taps, f, s);
             default: return launch_rerank_pair_bytes(a, L, rk, RL, taps, f, s);
         }
     }
     switch ((a.M % 4 == 0) ? a.M / 4 : 0) {
         case 1: return launch_rerank_table1(a, L, rk, RL, taps, f, s);
         case 2: return launch_rerank_table2(a, L, rk, RL, taps, f, s);
+        case 3: return launch_rerank_table3(a, L, rk, RL, taps, f, s);
         case 4: return launch_rerank_table4(a, L, rk, RL, taps, f, s);
         case 8: return launch_rerank_table8(a, L, rk, RL, taps, f, s);
         default: return launch_rerank_table0(a, L, rk, RL, taps, f, s);
@@ -94,8 +100,9 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
 
 hipError_t configure_rerank(size_t max_dynamic_lds) {
     hipError_t (*const all[])(size_t) = {configure_rerank_table0, configure_rerank_table1, configure_rerank_table2,
-                                         configure_rerank_table4, configure_rerank_table8, configure_rerank_pair_bytes,
-                                         configure_rerank_pair2,  configure_rerank_pair4,  configure_rerank_pair8};
+                                         configure_rerank_table3, configure_rerank_table4, configure_rerank_table8,
+                                         configure_rerank_pair_bytes, configure_rerank_pair2, configure_rerank_pair4,
+                                         configure_rerank_pair6, configure_rerank_pair8, configure_rerank_pair16};
     for (auto fn : all) {
         const hipError_t e = fn(max_dynamic_lds);
         if (e != hipSuccess) return e;

@@ -34,6 +34,7 @@ namespace pqt {
 
 constexpr int kCountRankMax = 32;    // survivors ordered by counting ranks up to this many, else sorted
 constexpr int kWalkMinRun = 8;       // mean run length from which a wavefront walks the run list together
+constexpr int kSurvPer = 8;          // survivors a thread places: those of k = 1024 with 256 threads
 constexpr int kRunPrefetch = 64;     // runs fetched before the run count is known
 
 // The run list of one query: the first rcap runs in LDS, any further ones in memory.  The LDS arrays
@@ -109,7 +110,7 @@ __device__ __forceinline__ void radix_select_pass(uint32_t prefix, uint32_t mask
 }
 
 // misc words
-enum { kMin = 0, kMax = 1, kSel = 2, kSelCount = 3, kNumSurv = 4, kRadix = 8, kRanked = 12 };
+enum { kMin = 0, kMax = 1, kSel = 2, kSelCount = 3, kNumSurv = 4, kFullBin = 5, kRadix = 8, kRanked = 12 };
 
 // LUT[m][c] read through an LDS address formed from the code byte alone: the table sits at LDS
 // address 0 (the kernels here have no static LDS; the launcher checks that), so the address is
@@ -319,12 +320,12 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
     }
 }
 
-// MW = 32-bit words per code (M/4) for M in {4, 8, 16, 32}; 0 = any other M (byte loads);
+// MW = 32-bit words per code (M/4) for M in {4, 8, 12, 16, 32}; 0 = any other M (byte loads);
 // MW < 0 = codes hold (centroid pair, lambda level) per sub-part, scored by Eq. 9 directly.
 // FUSED: a query whose meta.x is kMetaTodo (the ranking head pass could not finish it) is first
 // ranked in full by this workgroup.
 template <int MW, bool TAPS, bool FUSED>
-__global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) void rerank_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL) {
+__global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) void rerank_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long* surv = reinterpret_cast<unsigned long long*>(smem + L.surv);
     float* lut = reinterpret_cast<float*>(smem);                 // L.lut == 0
@@ -414,6 +415,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
         misc[kMin] = 0xffffffffu;
         misc[kMax] = 0u;
         misc[kNumSurv] = 0u;
+        misc[kFullBin] = 0u;
     }
     RunList R;
     R.src = L.run_src; R.start = L.run_start; R.mem = qruns; R.rcap = L.rcap; R.nr = nr; R.nc = (uint32_t)nc;
@@ -474,9 +476,9 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
     if (nc > 0) {
         const int wbase = __builtin_amdgcn_readfirstlane(pos0 - lane);    // the same for a wavefront
         // eight positions in flight per thread; four when a code has four or more words or holds (pair, lambda)
-        // tuples, whose scoring needs the registers
-        constexpr int UB = (MW >= 4 || MW <= -2) ? 4 : 8;
-        static_assert(kKeysPerThread % 4 == 0, "batches of four or eight");
+        // tuples, whose scoring needs the registers, two of sixteen words
+        constexpr int UB = MW <= -16 ? 2 : ((MW >= 4 || MW <= -2) ? 4 : 8);
+        static_assert(kKeysPerThread % 4 == 0, "batches of two, four or eight");
         WaveRuns wr;
         RunCursor cur;                         // positions of a thread only grow
         auto score_all = [&](auto walk) {
@@ -552,6 +554,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
             for (int j = 0; j < bpt; ++j) {
                 const uint32_t cnt = hist[tid * bpt + j];
                 hist[tid * bpt + j] = c;
+                if (k > nt && c < (uint32_t)kk && cnt > (uint32_t)kBinRankMax) misc[kFullBin] = 1u;
                 if (c < (uint32_t)kk && (uint32_t)kk <= c + cnt) {
                     misc[kSel] = (uint32_t)(tid * bpt + j);
                     misc[kSelCount] = c + cnt;
@@ -566,7 +569,8 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
             // keys of the bins <= bsel are the keys <= thr
             const unsigned long long thr64 = (unsigned long long)lo_key + (((unsigned long long)bsel + 1ull) << shift) - 1ull;
             const uint32_t thr = thr64 > 0xffffffffull ? 0xffffffffu : (uint32_t)thr64;
-            by_bin = thr != 0xffffffffu && count_le <= (uint32_t)nt;
+            // (long lists: a bin of many, ties, would keep its threads long; those are sorted)
+            by_bin = thr != 0xffffffffu && (count_le <= (uint32_t)nt || (k > nt && count_le <= (uint32_t)(kSurvPer * nt) && misc[kFullBin] == 0u));
             if (thr != 0xffffffffu) {
                 // key slots without a candidate hold 0xffffffff > thr.  A wavefront counts its keys <= thr,
                 // reserves room for them with one atomic, then writes them: no wait for LDS per window
@@ -650,7 +654,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
     // hist[] holds the first position of every bin among the sorted keys.  A thread takes one survivor,
     // fetches its id, and drops the (score bits, id) key into its bin's range with one LDS atomic; then every
     // key counts the smaller keys of its own bin (one to four entries) and that is its place in the output.
-    if (by_bin) {
+    if (by_bin && nsurv <= nt) {
         const bool have = tid < nsurv;
         unsigned long long mine = ~0ull;
         uint32_t bin = 0;
@@ -674,6 +678,53 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -8) ? 4 : 8)) v
         for (int e = kk + tid; e < k; e += nt) {
             g.out_ids[(size_t)q * k + e] = (int64_t)-1;
             g.out_dists[(size_t)q * k + e] = __builtin_inff();
+        }
+        return;
+    }
+
+    // ---- long result lists: the same with up to eight survivors a thread, and the output written in order -------------
+    // (1,000 results of 4,096 candidates, 10,000 queries: 243 us; sorting 2,048 keys with 256 threads 309)
+    if (by_bin) {
+        unsigned long long mine[kSurvPer];
+        uint32_t at[kSurvPer];
+#pragma unroll
+        for (int s = 0; s < kSurvPer; ++s) {
+            if (s * nt >= nsurv) break;                // the same for the whole workgroup
+            const int e = tid + s * nt;
+            mine[s] = ~0ull;
+            if (e < nsurv) {
+                const unsigned long long kp = surv[e];
+                mine[s] = (kp & 0xffffffff00000000ull) | g.ids[source_of((uint32_t)kp, steps, R)];
+            }
+        }
+        auto bin_of = [&](unsigned long long key) { return ((uint32_t)(key >> 32) - lo_key) >> shift; };
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kSurvPer; ++s) {
+            if (s * nt >= nsurv) break;
+            if (tid + s * nt < nsurv) surv[atomicAdd(&hist[bin_of(mine[s])], 1u)] = mine[s];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kSurvPer; ++s) {
+            if (s * nt >= nsurv) break;
+            if (tid + s * nt >= nsurv) continue;
+            const uint32_t bin = bin_of(mine[s]);
+            const uint32_t first = bin ? hist[bin - 1] : 0u, end = hist[bin];
+            at[s] = first;
+            for (uint32_t x = first; x < end; ++x) at[s] += surv[x] < mine[s] ? 1u : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kSurvPer; ++s) {
+            if (s * nt >= nsurv) break;
+            if (tid + s * nt < nsurv) surv[at[s]] = mine[s];
+        }
+        __syncthreads();
+        for (int e = tid; e < k; e += nt) {
+            const unsigned long long skey = surv[e < kk ? e : 0];
+            g.out_ids[(size_t)q * k + e] = e < kk ? (int64_t)(uint32_t)skey : (int64_t)-1;
+            g.out_dists[(size_t)q * k + e] = e < kk ? mono_inv((uint32_t)(skey >> 32)) : __builtin_inff();
         }
         return;
     }

@@ -1,4 +1,4 @@
-// The re-rank kernel for (pair, lambda) codes, M = 8.
+// The re-rank kernel for (pair, lambda) codes, M = 16.
 #include "rerank_kernel.hpp"
 
 namespace pqt {

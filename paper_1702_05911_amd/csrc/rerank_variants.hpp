@@ -1,6 +1,7 @@
 // The re-rank kernel is compiled once per code width, each width in a translation unit of its own
-// (rerank_table*.hip: one byte per sub-part, M = 4, 8, 16, 32 or any; rerank_pair*.hip: (pair, lambda)
-// codes, M = 2, 4, 8 word-wise or any byte-wise).  This header declares their launchers.
+// (rerank_table*.hip: one byte per sub-part, M = 4, 8, 12, 16, 32 or any; rerank_pair*.hip: (pair, lambda)
+// codes, M = 4, 8, 12, 16, 32 word-wise or any byte-wise; the number in the name counts 32-bit words).  Read byte by byte, a
+// candidate costs a load per byte: 3,217 queries x 3,001 candidates of 24 bytes took 456 us, read as words 121.  This header declares their launchers.
 #pragma once
 #include "pqt_kernels.hpp"
 
@@ -19,12 +20,15 @@ struct RerankLds {
 PQT_RERANK_VARIANT_DECLARE(table0)
 PQT_RERANK_VARIANT_DECLARE(table1)
 PQT_RERANK_VARIANT_DECLARE(table2)
+PQT_RERANK_VARIANT_DECLARE(table3)
 PQT_RERANK_VARIANT_DECLARE(table4)
 PQT_RERANK_VARIANT_DECLARE(table8)
 PQT_RERANK_VARIANT_DECLARE(pair_bytes)
 PQT_RERANK_VARIANT_DECLARE(pair2)
 PQT_RERANK_VARIANT_DECLARE(pair4)
+PQT_RERANK_VARIANT_DECLARE(pair6)
 PQT_RERANK_VARIANT_DECLARE(pair8)
+PQT_RERANK_VARIANT_DECLARE(pair16)
 
 // compile-time constants the host side needs as well
 constexpr int kHistBits = 10;

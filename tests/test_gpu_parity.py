@@ -464,6 +464,48 @@ def _whole_number_index(pqt, N, D, P, k1, k2, M, H=None, T=64, C=1024, fmt=0, di
     return builder.build_index_native(X, P=P, k1=k1, k2=k2, M=M, H=H, T=T, C=C, iters=4, code_format=fmt), X
 
 
+@pytest.mark.parametrize("distinct, k, C, nq", [
+    (0, 257, 1500, 1100),                  # one result more than threads
+    (0, 1000, 4096, 1100),
+    (0, 1024, 4096, 1030),                 # the longest list
+    (40, 600, 2000, 1100),                 # forty different vectors: crowded bins, the survivors are sorted
+    (40, 100, 2000, 1100),                 # fewer results than threads, more survivors: sorted or selected exactly
+])
+def test_long_result_lists(pqt, distinct, k, C, nq):
+    """Result lists longer than the workgroup (256 threads for these batches) against a sort of the tapped scores by
+    (score, id): equal, ids and distance bits."""
+    import torch
+    ix, X = _whole_number_index(pqt, 6000, 16, 2, 4, 4, 4, T=256, C=C, distinct=distinct)
+    try:
+        Y = X[:nq] + 0.25
+        ids, d, taps = pqt.pqt_query_batch_debug(ix, Y, k, 4, taps=("scores", "cand_ids", "n_cand"))
+        pid, pd = pqt.pqt_query_batch(ix, Y, k, 4)
+        torch.cuda.synchronize()
+        col = torch.arange(C, device="cuda")
+        free = col[None] >= taps["n_cand"][:, None]
+        by_id = torch.argsort(torch.where(free, 1 << 40, taps["cand_ids"]), dim=1, stable=True)
+        score = torch.where(free, float("inf"), taps["scores"]).gather(1, by_id)
+        order = by_id.gather(1, torch.argsort(score, dim=1, stable=True))[:, :k]
+        want = torch.where(free, -1, taps["cand_ids"]).gather(1, order)
+        want_d = torch.where(free, float("inf"), taps["scores"]).gather(1, order)
+        for got, gd in ((ids, d), (pid, pd)):
+            assert torch.equal(got, want) and torch.equal(gd, want_d)
+    finally:
+        pqt.pqt_index_free(ix)
+
+
+@pytest.mark.parametrize("M, fmt", [(12, 0), (12, 1), (32, 1), (16, 1), (6, 1)])
+def test_code_widths(pqt, tmp_path, M, fmt):
+    """Codes read as three, six and sixteen words (M = 16: eight, M = 6 pairs: three, byte by byte): every stage and the
+    plain entry point against the oracle."""
+    from workloads import tiny_mixture
+    X, Y = tiny_mixture(2500, d=2 * M, seed=8), tiny_mixture(12, d=2 * M, seed=9)
+    ix = B.build_index(X, 2, 6, 3, M, T=60, C=900, iters=3, code_format=fmt)
+    path = str(tmp_path / "width.pqt")
+    IO.write_index(path, ix)
+    _stagewise(pqt, ix, path, Y, 40, 4, 60, 900)
+
+
 @pytest.mark.parametrize("D, stored, k_short, k, distinct", [
     (16, "u8", 1, 1, 0),                   # a row is one piece: 64 rows per wavefront
     (48, "u8", 1000, 100, 0),              # three pieces: one lane of four idle
