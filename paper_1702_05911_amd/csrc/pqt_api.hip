@@ -115,13 +115,26 @@ int rerank_runs_in_lds(const pqt_index* ix) {
     return r;
 }
 
+// From which mean number of needed tuples on (see run_query) the head pass does not pay.  A large batch waits for the sum of
+// the work: the line lies where most queries come back from 64 tuples unfinished.  A small one waits for its slowest
+// query, so there it lies where one of nq is likely to: the share that 64 tuples leave over falls from about 0.4 at 160 to
+// 0.1 at 96, 0.03 at 64 and 0.005 at 48.  Measured (us a batch, with the head pass and without): 4,000 queries at 80: 100
+// and 129, at 110: 149 and 131; 1,500 at 33: 56 and 68, at 50: 83 and 73; 300 at 33: 46 and 54, at 50: 65 and 55; 16 at 67: 45 and
+// 34; one query at 67: 22 and 29 if it finishes, 41 and 30 if not.  Far above: 3,000 queries at 655: 307 and 182.
+double headless_from(int64_t nq) {
+    if (nq < 4) return 160.0;
+    if (nq < 16) return 96.0;
+    if (nq < 96) return 64.0;
+    return nq <= 2048 ? 48.0 : 96.0;
+}
+
 // Can the re-rank kernel also run the full bin ranking of the queries the head pass leaves over?
 // (two tree parts; few enough tuples per thread of the re-rank workgroup; the LDS of both fits)
 bool can_fuse_ranking(const pqt_index* ix, int k, int w, int64_t nq) {
     if (ix->P != 2) return false;
     const int R = w * (int)ix->k2;
     const int threads = rerank_threads(ix, nullptr, nq);
-    const pqt::RankOffsets ro = pqt::rank_offsets(ix->P, R, ix->T, ix->hashed, false);
+    const pqt::RankOffsets ro = pqt::rank_offsets(ix->P, R, ix->T, ix->hashed, false, pqt::kMidT);
     if (ro.Tcap > pqt::rerank_fused_tuples_per_thread() * threads) return false;
     return pqt::rerank_lds_bytes(ix->M, ix->k1, ix->T, ix->C, k, threads, ro.total, (int)ix->code_format,
                                  rerank_runs_in_lds(ix)) <= ix->lds_limit;
@@ -595,6 +608,14 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     ra.H_inv = ix->H >= 2 ? (uint64_t)((((unsigned __int128)1) << 64) / ix->H) : 0;
     ra.offsets = ix->offsets; ra.L_d = ws.Ld; ra.L_id = ws.Lid;
     ra.runs = ws.runs; ra.meta = ws.meta; ra.counters = ws.counters; ra.order = ws.order;
+    // Two parts: tuples whose lists would fill the budget if every slot were as long as the mean one (near a query they are
+    // longer: about 0.4 times as many do).  The full ranking tries twice as many first, all T if those do not fill it.
+    const double mean_need = ix->N ? (double)ix->C * (double)ix->H / (double)ix->N : 0.0;
+    ra.t_mid = pqt::kMidT;
+    while (ra.t_mid < (int)ix->T && ra.t_mid < 2.0 * mean_need) ra.t_mid *= 2;
+    // The head pass is left out where it would leave much to do: every query is then ranked by a workgroup of its own in
+    // a kernel of its own, by placing, which the re-rank kernel has no registers for.
+    if (mean_need >= headless_from(nq)) ra.order = nullptr;
     ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
     const bool rerank_taps = tp.n_cand || tp.cand_ids || tp.scores || tp.lut || tp.n_slots;
     const bool head = !fixed_order && pqt::rank_has_head(ra);

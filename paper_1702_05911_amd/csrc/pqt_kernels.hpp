@@ -11,6 +11,7 @@ namespace pqt {
 constexpr int kQueryTile = 16;          // queries per workgroup of the traversal kernel (MFMA rows)
 constexpr int kTraverseMaxThreads = 1024; // workgroup size grows with the number of tree parts
 constexpr int kRankThreads = 1024;        // full ranking pass: one workgroup per query
+constexpr int kRankFewQueries = 512;     // up to two queries per compute unit
 constexpr int kRankThreadsFourParts = 512;  // the same for four tree parts (up to 4096 tuples)
 constexpr int kRankHeadThreads = 256;     // head pass: one wavefront per query
 constexpr size_t kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
@@ -72,9 +73,12 @@ hipError_t launch_votes(const PlaceArgs& a, hipStream_t s);
 // c1n of level-1 centroids on the GPU
 hipError_t launch_subpart_norms(const float* C1, int D, int P, int k1, int M, float* c1n, hipStream_t s);
 
+constexpr int kMidT = 128;               // tuples the full ranking of two parts tries first, unless RankArgs::t_mid says more
+
 struct RankArgs {
     int64_t nq;
     int P, R, T, C;
+    int t_mid;                // two parts: tuples the full ranking tries first (all T only if those do not fill C)
     uint32_t k1k2;
     uint64_t H;
     uint64_t H_inv;           // floor(2^64 / H) for H >= 2 (slot_of_bin divides by multiplying), else 0
@@ -97,7 +101,8 @@ constexpr uint32_t kMetaTodo = 0xffffffffu;
 
 struct RankOffsets {   // LDS layout of the full ranking pass (computed once on the host)
     int Tcap, cap, npair, nreg, nreg_pair, Tmid, nreg_mid;
-    int force;             // 1: rank every query (taps wanted, or no head pass ran)
+    int all;               // 1: rank every query (no head pass ran)
+    int force;             // 1: all Tcap tuples at once (taps want them, or the first attempt has been made elsewhere)
     uint32_t keys, hist, Ld, Lid, ps, pt, len, slot, part, misc;
     uint32_t total;        // bytes
 };
@@ -106,7 +111,7 @@ int rank_region_size(int R, int T);
 // LDS of the stand-alone ranking kernel / layout of a ranking (place: with the room the stand-alone kernels
 // use for placing keys by bin; without: the ranking inside the re-rank kernel)
 size_t rank_lds_bytes(int P, int R, int T, int hashed);
-RankOffsets rank_offsets(int P, int R, int T, int hashed, bool place);
+RankOffsets rank_offsets(int P, int R, int T, int hashed, bool place, int t_mid);
 // does a head pass exist for these arguments (two tree parts, no taps of the ranking)?
 bool rank_has_head(const RankArgs& a);
 // defer_full: only the head pass is launched; the caller runs the full pass of the unfinished

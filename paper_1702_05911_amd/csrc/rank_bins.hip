@@ -45,7 +45,8 @@ struct RankLds {
 
 // hashed: slots may repeat (their lengths and numbers go through LDS); 2: the slots tap also wants the numbers
 // place: room for placing the keys by bin (the stand-alone kernels; see rank_pairs)
-static RankLds rank_layout(int P, int R, int T, int hashed, bool place) {
+// t_mid: tuples of the first attempt (two parts)
+static RankLds rank_layout(int P, int R, int T, int hashed, bool place, int t_mid = kMidT) {
     RankLds L;
     long total_tuples = 1;
     for (int p = 0; p < P; ++p) total_tuples = (total_tuples * R > (1L << 40)) ? (1L << 40) : total_tuples * R;
@@ -59,7 +60,7 @@ static RankLds rank_layout(int P, int R, int T, int hashed, bool place) {
         L.nreg = L.Tcap;
     } else if (P == 2) {
         L.nreg = (int)region_size(R, R, L.Tcap);
-        L.Tmid = L.Tcap < kMidT ? L.Tcap : kMidT;
+        L.Tmid = L.Tcap < t_mid ? L.Tcap : t_mid;
         L.nreg_mid = (int)region_size(R, R, L.Tmid);
     } else {
         L.npair = (int)((long)T < (long)R * R ? (long)T : (long)R * R);
@@ -112,17 +113,17 @@ __global__ __launch_bounds__(kRankHeadThreads) void rank_head_kernel(RankArgs g,
 // Full pass: workgroups take the queries the head pass listed (or every query when forced).
 // ------------------------------------------------------------------------------------------------
 
-// MAXPER: tuples a thread may have to hold (T <= MAXPER * kRankThreads).  The variant for at most four is
-// compiled for 64 registers, so that two workgroups fit a compute unit: the pass is a chain of dependent
-// steps with many barriers, and a second resident query hides most of them.
-// PF: the number of tree parts when it is compiled in (4), 0: read from the arguments.
+// MAXPER: tuples a thread may have to hold (T <= MAXPER * the workgroup).  The pass is a chain of dependent
+// steps with many barriers, which other resident queries hide: the variants for at most four tuples get 80 registers (two
+// parts: 64 were 3 to 8 % slower, the ranking spilled in its hot loops), six wavefronts a SIMD.
+// PF: the number of tree parts when it is compiled in (2, 4), 0: read from the arguments.
 template <int MAXPER, int PF = 0, int MODE = kRankPlace>
 __global__ __launch_bounds__(PF == 4 && MAXPER <= 4 ? kRankThreadsFourParts : kRankThreads,
-                             MAXPER > 4 ? 4 : (PF == 4 ? 6 : 8)) void rank_kernel(RankArgs g, RankOffsets L) {
+                             MAXPER > 4 ? 4 : (PF == 0 ? 8 : 6)) void rank_kernel(RankArgs g, RankOffsets L) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t count = L.force ? (uint32_t)g.nq : g.counters[0];
+    const uint32_t count = L.all ? (uint32_t)g.nq : g.counters[0];
     for (uint32_t item = blockIdx.x; item < count; item += gridDim.x) {
-        const int64_t q = L.force ? (int64_t)item : (int64_t)g.order[item];
+        const int64_t q = L.all ? (int64_t)item : (int64_t)g.order[item];
         rank_query<PF, false, MAXPER, MODE>(g, L, q, smem, nullptr);
     }
 }
@@ -204,12 +205,13 @@ hipError_t launch_rank_static(const RankArgs& a, const StaticOrder& so, hipStrea
     return hipGetLastError();
 }
 
-RankOffsets rank_offsets(int P, int R, int T, int hashed, bool place) {
-    const RankLds L = rank_layout(P, R, T, hashed, place);
+RankOffsets rank_offsets(int P, int R, int T, int hashed, bool place, int t_mid) {
+    const RankLds L = rank_layout(P, R, T, hashed, place, t_mid);
     RankOffsets o;
     o.Tcap = L.Tcap; o.cap = L.cap; o.npair = L.npair; o.nreg = L.nreg; o.nreg_pair = L.nreg_pair;
     o.Tmid = L.Tmid; o.nreg_mid = L.nreg_mid;
     o.force = 0;
+    o.all = 0;
     o.keys = (uint32_t)L.off_keys; o.hist = (uint32_t)L.off_hist;
     o.Ld = (uint32_t)L.off_Ld; o.Lid = (uint32_t)L.off_Lid; o.ps = (uint32_t)L.off_ps; o.pt = (uint32_t)L.off_pt;
     o.len = (uint32_t)L.off_len; o.slot = (uint32_t)L.off_slot;
@@ -225,10 +227,12 @@ bool rank_has_head(const RankArgs& a) {
 
 hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
     if (a.nq <= 0) return hipSuccess;
-    RankOffsets o = rank_offsets(a.P, a.R, a.T, a.hashed ? 1 : (a.slots ? 2 : 0), true);
+    RankOffsets o = rank_offsets(a.P, a.R, a.T, a.hashed ? 1 : (a.slots ? 2 : 0), true, a.t_mid);
     const bool head = rank_has_head(a);
     if (defer_full && !head) return hipErrorInvalidValue;
-    o.force = head ? 0 : 1;
+    const bool taps = a.n_tuples || a.tuples || a.tuple_keys || a.slots;
+    o.all = head ? 0 : 1;
+    o.force = taps ? 1 : 0;                // taps want every tuple
     if (head) {
         constexpr int per = kRankHeadThreads / kWave;
         HeadLevels lv;
@@ -258,14 +262,25 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
             hipLaunchKernelGGL((rank_kernel<4, 4>), dim3(grid), dim3(threads), o.total, s, a, o);
         else
             hipLaunchKernelGGL((rank_kernel<8, 4>), dim3(grid), dim3(threads), o.total, s, a, o);
-    } else if (o.Tcap <= 4 * kRankThreads) hipLaunchKernelGGL(rank_kernel<4>, dim3(grid), dim3(kRankThreads), o.total, s, a, o);
-    else hipLaunchKernelGGL(rank_kernel<8>, dim3(grid), dim3(kRankThreads), o.total, s, a, o);
+    } else {
+        // A batch that fills the chip takes the smallest workgroups that hold the tuples (four a thread): more queries
+        // per compute unit hide each other's barriers; a few queries take the largest and are answered sooner.
+        int threads = kRankThreads;
+        if (!head && a.nq > kRankFewQueries)
+            while (threads > 256 && o.Tcap <= 2 * threads) threads /= 2;
+        if (o.Tcap > 4 * kRankThreads) hipLaunchKernelGGL(rank_kernel<8>, dim3(grid), dim3(threads), o.total, s, a, o);
+        else if (a.P == 2) hipLaunchKernelGGL((rank_kernel<4, 2>), dim3(grid), dim3(threads), o.total, s, a, o);
+        else hipLaunchKernelGGL(rank_kernel<4>, dim3(grid), dim3(threads), o.total, s, a, o);
+    }
     return hipGetLastError();
 }
 
 hipError_t configure_rank(size_t max_dynamic_lds) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<4>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dynamic_lds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<4, 2>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)max_dynamic_lds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)max_dynamic_lds);

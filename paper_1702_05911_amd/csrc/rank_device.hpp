@@ -14,7 +14,6 @@ __host__ __device__ inline int region_row_count(int a, int R, int T) {
 
 constexpr int kSelBits = 10;
 constexpr int kSelBins = 1 << kSelBits;
-constexpr int kMidT = 128;         // tuples ranked first by the full pass; all T only if they do not fill C
 constexpr int kRegionSplit = 64;   // rows below it are walked along b, the rest of the region along a
 constexpr int kBinRankMax = 64;    // placing keys by histogram bin: most keys a bin may hold (each is ranked against its bin)
 constexpr int kKeySlack = 64;      // entries of the key buffer beyond its power-of-two capacity (the last bin's excess)

@@ -64,12 +64,13 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
     if (fused) {
         if (taps || fused->P != 2) return hipErrorInvalidValue;
         rk = *fused;
-        RL = rank_offsets(rk.P, rk.R, rk.T, rk.hashed, false);
+        RL = rank_offsets(rk.P, rk.R, rk.T, rk.hashed, false, rk.t_mid);
         if (RL.Tcap > rerank_fused_tuples_per_thread() * a.threads) return hipErrorInvalidValue;
         // the wavefront's two lists lie at the start of the workgroup's LDS (table, survivor list and
         // histogram are not in use yet, and the arrays that receive the result come after them)
         static_assert(sizeof(HeadLds) <= sizeof(uint32_t) * kHistSize, "the lists must end before the arrays that are live");
         a.mid_T1 = RL.Tcap < kHeadT ? RL.Tcap : kHeadT;
+        RL.force = RL.Tmid <= a.mid_T1 ? 1 : 0;       // so many tuples have been tried by then
         a.mid_npairs = head_pair_count(a.mid_T1);
     }
     if (a.keys_per_thread != kKeysPerThread || a.C > a.keys_per_thread * a.threads) return hipErrorInvalidValue;

@@ -506,6 +506,27 @@ def test_code_widths(pqt, tmp_path, M, fmt):
     _stagewise(pqt, ix, path, Y, 40, 4, 60, 900)
 
 
+@pytest.mark.parametrize("H", [None, 4099])
+@pytest.mark.parametrize("C", [30, 60, 120, 400, 3000])
+def test_ranking_routes_agree(pqt, C, H):
+    """Sparse to full two-part indexes and batches on both sides of every line of the choice between head pass and
+    headless ranking: the plain entry point returns what the debug one does, which always ranks all T tuples."""
+    import torch
+    ix, X = _whole_number_index(pqt, 12_000, 16, 2, 16, 8, 4, H=H, T=700, C=C)
+    try:
+        for nq in (1, 3, 4, 15, 16, 95, 96, 513, 2048, 2049):
+            Y = X[:nq] + 0.25
+            ids, d, _ = pqt.pqt_query_batch_debug(ix, Y, min(C, 20), 5, taps=("n_tuples",))
+            pid, pd = pqt.pqt_query_batch(ix, Y, min(C, 20), 5)
+            assert torch.equal(ids, pid) and torch.equal(d, pd), nq
+            if nq <= 513:
+                nid, nd = torch.empty_like(ids), torch.empty_like(d)
+                pqt.pqt_query_batch_noalloc(ix, Y, min(C, 20), 5, nid, nd)
+                assert torch.equal(ids, nid) and torch.equal(d, nd), nq
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 @pytest.mark.parametrize("D, stored, k_short, k, distinct", [
     (16, "u8", 1, 1, 0),                   # a row is one piece: 64 rows per wavefront
     (48, "u8", 1000, 100, 0),              # three pieces: one lane of four idle
