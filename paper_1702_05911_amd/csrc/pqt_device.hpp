@@ -118,6 +118,17 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v, int lane) {
     return v;
 }
 
+// Inclusive prefix maximum across the 64 lanes of a wavefront, the same way.
+__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v) {
+    v = max(v, dpp_or_zero<0x111, 0xf>(v));
+    v = max(v, dpp_or_zero<0x112, 0xf>(v));
+    v = max(v, dpp_or_zero<0x114, 0xf>(v));
+    v = max(v, dpp_or_zero<0x118, 0xf>(v));
+    v = max(v, dpp_or_zero<0x142, 0xa>(v));
+    v = max(v, dpp_or_zero<0x143, 0xc>(v));
+    return v;
+}
+
 // Exclusive prefix of v over the threads of the workgroup in thread order; total = sum over all
 // threads.  part: one word of LDS per wavefront.  One barrier inside; every thread must call it.
 // part may be written again only after a later barrier.

@@ -241,12 +241,10 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
             lv.T1[l] = o.Tcap < t ? o.Tcap : t;
             lv.npairs[l] = head_pair_count(lv.T1[l]);
         }
-        if (defer_full) {
-            // the re-rank workgroups rank what is left in full: the third level, one long chain of dependent
-            // steps in a single wavefront for a few queries, would only set the duration of this kernel
-            lv.T1[2] = lv.T1[1];
-            lv.npairs[2] = lv.npairs[1];
-        }
+        // what 64 tuples leave over goes to a workgroup per query: the third level, one long chain of dependent steps
+        // in a single wavefront for a few queries, would only set the duration of this kernel
+        lv.T1[2] = lv.T1[1];
+        lv.npairs[2] = lv.npairs[1];
         hipLaunchKernelGGL(rank_head_kernel, dim3((unsigned)((a.nq + per - 1) / per)), dim3(kRankHeadThreads), 0, s, a,
                            o.Tcap, lv);
         hipError_t e = hipGetLastError();
@@ -266,7 +264,7 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
         // A batch that fills the chip takes the smallest workgroups that hold the tuples (four a thread): more queries
         // per compute unit hide each other's barriers; a few queries take the largest and are answered sooner.
         int threads = kRankThreads;
-        if (!head && a.nq > kRankFewQueries)
+        if (a.nq > kRankFewQueries)
             while (threads > 256 && o.Tcap <= 2 * threads) threads /= 2;
         if (o.Tcap > 4 * kRankThreads) hipLaunchKernelGGL(rank_kernel<8>, dim3(grid), dim3(threads), o.total, s, a, o);
         else if (a.P == 2) hipLaunchKernelGGL((rank_kernel<4, 2>), dim3(grid), dim3(threads), o.total, s, a, o);

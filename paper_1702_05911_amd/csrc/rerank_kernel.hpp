@@ -34,6 +34,7 @@ namespace pqt {
 
 constexpr int kCountRankMax = 32;    // survivors ordered by counting ranks up to this many, else sorted
 constexpr int kWalkMinRun = 8;       // mean run length from which a wavefront walks the run list together
+constexpr int kMarkMinRun = 5, kMarkMaxRun = 32;   // and from which to which it marks it (see MarkedRuns)
 constexpr int kSurvPer = 8;          // survivors a thread places: those of k = 1024 with 256 threads
 constexpr int kRunPrefetch = 64;     // runs fetched before the run count is known
 
@@ -196,6 +197,75 @@ struct WaveRuns {
     }
 };
 
+// The same walk for runs of medium length, where a window of 64 positions meets several boundaries and each cost the walk above
+// half a dozen vector instructions.  Lane l holds run first + l, `first` being the run the group of windows starts in; the
+// lanes whose run starts inside the group put their number at that position of a byte array in LDS, and a prefix maximum
+// along the positions names every position's run: a dozen instructions per window, whatever the number of boundaries.
+// 5,003 queries x 10,000 candidates in runs of ten: the whole call 553 -> 518 us.
+struct MarkedRuns {
+    uint32_t v_start, v_delta;   // run first + lane: start (0xffffffff past the list), position in ids/codes - candidate position
+    int first;
+    uint32_t carry;              // run (counted from first) of the last position looked up
+    bool many;                   // the group may reach past the 64 runs held: every thread searches the list
+    __device__ __forceinline__ void load(const RunList& R, int f, int lane) {
+        first = f;
+        const int idx = f + lane;
+        v_start = 0xffffffffu;
+        v_delta = 0u;
+        if (idx < R.nr) {
+            v_start = R.start_at(idx);
+            v_delta = R.src_at(idx) - v_start;
+        }
+    }
+    // the run of position p, not below the last one asked for
+    __device__ __forceinline__ void seek(const RunList& R, uint32_t p, int lane) {
+        for (;;) {
+            const int cnt = __popcll(__ballot(v_start <= p));      // runs held that start at or before p: at least one
+            if (cnt == 1) return;
+            load(R, first + cnt - 1, lane);
+        }
+    }
+    // positions [p0, p0 + span) come next; marks: this wavefront's bytes, span <= 256
+    __device__ __forceinline__ void group(const RunList& R, uint32_t p0, int span, int lane, uint32_t marks) {
+        typedef __attribute__((address_space(3))) uint32_t lds_word;
+        typedef __attribute__((address_space(3))) uint8_t lds_byte;
+        seek(R, p0, lane);
+        carry = 0u;
+        many = first + kWave < R.nr && (uint32_t)__builtin_amdgcn_readlane((int)v_start, kWave - 1) < p0 + (uint32_t)span;
+        wave_lds_order();
+        *reinterpret_cast<lds_word*>((uintptr_t)(marks + 4u * (uint32_t)lane)) = 0u;
+        wave_lds_order();
+        const uint32_t at = v_start - p0;                        // lane 0: not inside (its run starts at or before p0)
+        if (lane > 0 && at < (uint32_t)span) *reinterpret_cast<lds_byte*>((uintptr_t)(marks + at)) = (uint8_t)lane;
+        wave_lds_order();
+    }
+    // offset of position p = p0 + 64 * w + lane of the group
+    __device__ __forceinline__ uint32_t window(const RunList& R, uint32_t p, bool wanted, int w, int lane, uint32_t marks) {
+        typedef __attribute__((address_space(3))) const uint8_t lds_cbyte;
+        if (many) {                                              // the same for the wavefront
+            uint32_t delta = 0u;
+            if (wanted) {
+                int lo = first, hi = R.nr;
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    const bool ge = R.start_at(mid) <= p;
+                    lo = ge ? mid : lo;
+                    hi = ge ? hi : mid;
+                }
+                delta = R.src_at(lo) - R.start_at(lo);
+            }
+            return delta;
+        }
+        const uint32_t mark = *reinterpret_cast<lds_cbyte*>((uintptr_t)(marks + (uint32_t)lane + (uint32_t)(w * kWave)));
+        const uint32_t run = max(wave_inclusive_max(mark), carry);
+        carry = (uint32_t)__builtin_amdgcn_readlane((int)run, kWave - 1);
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(run << 2), (int)v_delta);
+    }
+};
+
+// How a wavefront finds its candidates' places (RUNS of score_batch)
+enum { kSearchRuns, kWalkRuns, kMarkRuns };
+
 // (pair, lambda level) codes: the summand of Eq. 9 for one sub-part from the pair's LDS entry
 // (b^2, a^2 - b^2, c^2) and the level; lambda = (level - 96) / 16 is exact in fp32.
 constexpr int kPairLambda = -1;      // MW < 0 selects this code format: -1 any M (byte loads), else -(words per code)
@@ -208,11 +278,11 @@ __device__ __forceinline__ float pair_lambda_term(const float4* plut, int shift,
 // Scores U candidate positions per thread (wb + u * 64 + lane: a wavefront walks its own contiguous
 // piece of the candidate list, U windows of 64 positions at a time) and leaves their keys (ordered
 // score bits) in key[0..U).  CHECK: positions may reach pend (their keys are left alone).
-// WALK: the wavefront walks the run list (long runs); else every thread searches it (short runs).
-template <int MW, int U, bool CHECK, bool TAPS, bool WALK>
+// RUNS: every thread searches the run list (short runs), the wavefront walks it (long ones) or marks it (between).
+template <int MW, int U, bool CHECK, bool TAPS, int RUNS>
 __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int wb, int lane, int pend,
-                                            const float* lut, uint32_t* key, const RunList& R, WaveRuns& wr,
-                                            RunCursor& cur, uint32_t& kmin, uint32_t& kmax) {
+                                            const float* lut, uint32_t* key, const RunList& R, WaveRuns& wr, MarkedRuns& mr,
+                                            uint32_t marks, RunCursor& cur, uint32_t& kmin, uint32_t& kmax) {
     const int p0 = wb + lane;
     constexpr int NW = MW > 0 ? MW : (MW < -1 ? -MW : 0);      // code words fetched up front (0: byte loads)
     const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M);
@@ -221,7 +291,14 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const uint32_t p = (uint32_t)(p0 + u * kWave);
-        if (WALK) {
+        if (RUNS == kMarkRuns) {
+            constexpr int G = U < 4 ? U : 4;                   // windows marked together
+            if (u % G == 0) mr.group(R, (uint32_t)(wb + u * kWave), G * kWave, lane, marks);
+            const bool wanted = !CHECK || p < (uint32_t)pend;
+            const uint32_t delta = mr.window(R, p, wanted, u % G, lane, marks);
+            src[u] = wanted ? p + delta
+                            : (uint32_t)__builtin_amdgcn_readlane((int)(mr.v_start + mr.v_delta), 0);   // as below
+        } else if (RUNS == kWalkRuns) {
             const uint32_t delta = wr.window(R, (uint32_t)(wb + u * kWave), lane);
             // a position past the end reads the first candidate of a run the wavefront holds
             src[u] = (!CHECK || p < (uint32_t)pend) ? p + delta : (uint32_t)__builtin_amdgcn_readlane((int)wr.v_src, 0);
@@ -324,7 +401,9 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
 // MW < 0 = codes hold (centroid pair, lambda level) per sub-part, scored by Eq. 9 directly.
 // FUSED: a query whose meta.x is kMetaTodo (the ranking head pass could not finish it) is first
 // ranked in full by this workgroup.
-template <int MW, bool TAPS, bool FUSED>
+// LONG: results may outnumber the workgroup's threads (apart, because that end costs the usual lists 1 % in the kernel that
+// ranks as well).
+template <int MW, bool TAPS, bool FUSED, bool LONG>
 __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) void rerank_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long* surv = reinterpret_cast<unsigned long long*>(smem + L.surv);
@@ -415,7 +494,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
         misc[kMin] = 0xffffffffu;
         misc[kMax] = 0u;
         misc[kNumSurv] = 0u;
-        misc[kFullBin] = 0u;
+        if (LONG) misc[kFullBin] = 0u;
     }
     RunList R;
     R.src = L.run_src; R.start = L.run_start; R.mem = qruns; R.rcap = L.rcap; R.nr = nr; R.nc = (uint32_t)nc;
@@ -480,34 +559,40 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
         constexpr int UB = MW <= -16 ? 2 : ((MW >= 4 || MW <= -2) ? 4 : 8);
         static_assert(kKeysPerThread % 4 == 0, "batches of two, four or eight");
         WaveRuns wr;
+        MarkedRuns mr;                         // (not in the kernel that ranks as well)
+        const uint32_t marks = L.part + (uint32_t)(tid & ~(kWave - 1)) * 4u;      // 256 bytes a wavefront: its words of part[]
         RunCursor cur;                         // positions of a thread only grow
-        auto score_all = [&](auto walk) {
-            constexpr bool WALK = decltype(walk)::value;
+        auto score_all = [&](auto how) {
+            constexpr int RUNS = decltype(how)::value;
 #pragma unroll
             for (int b = 0; b * UB + UB <= kKeysPerThread; ++b) {
                 const int base = wbase + b * UB * kWave;
                 if (base + UB * kWave <= pend)
-                    score_batch<MW, UB, false, TAPS, WALK>(g, q, base, lane, pend, lut, key + b * UB, R, wr, cur, kmin, kmax);
+                    score_batch<MW, UB, false, TAPS, RUNS>(g, q, base, lane, pend, lut, key + b * UB, R, wr, mr, marks, cur, kmin, kmax);
                 else if (base < pend)
-                    score_batch<MW, UB, true, TAPS, WALK>(g, q, base, lane, pend, lut, key + b * UB, R, wr, cur, kmin, kmax);
+                    score_batch<MW, UB, true, TAPS, RUNS>(g, q, base, lane, pend, lut, key + b * UB, R, wr, mr, marks, cur, kmin, kmax);
             }
             if (kKeysPerThread % UB) {         // a last batch of four
                 constexpr int done = kKeysPerThread / UB * UB;
                 const int base = wbase + done * kWave;
                 if (base + 4 * kWave <= pend)
-                    score_batch<MW, 4, false, TAPS, WALK>(g, q, base, lane, pend, lut, key + done, R, wr, cur, kmin, kmax);
+                    score_batch<MW, 4, false, TAPS, RUNS>(g, q, base, lane, pend, lut, key + done, R, wr, mr, marks, cur, kmin, kmax);
                 else if (base < pend)
-                    score_batch<MW, 4, true, TAPS, WALK>(g, q, base, lane, pend, lut, key + done, R, wr, cur, kmin, kmax);
+                    score_batch<MW, 4, true, TAPS, RUNS>(g, q, base, lane, pend, lut, key + done, R, wr, mr, marks, cur, kmin, kmax);
             }
         };
-        if (nr * kWalkMinRun <= nc) {          // runs long enough that a window of 64 positions meets few of them
+        // (the kernel that ranks as well has no registers to spare for the marks)
+        if (!FUSED && nr * kMarkMinRun <= nc && nr * kMarkMaxRun > nc) {
+            mr.load(R, 0, lane);
+            score_all(std::integral_constant<int, kMarkRuns>{});
+        } else if (nr * kWalkMinRun <= nc) {   // runs long enough that a window of 64 positions meets few of them
             wr.seek(R, (uint32_t)wbase, lane);
-            score_all(std::true_type{});
+            score_all(std::integral_constant<int, kWalkRuns>{});
         } else {
             cur.run = 0;
             cur.next_start = R.start_at(1);
             cur.delta = R.src_at(0) - R.start_at(0);
-            score_all(std::false_type{});
+            score_all(std::integral_constant<int, kSearchRuns>{});
         }
     }
     if (TAPS && g.n_cand && tid == 0) g.n_cand[q] = (uint32_t)nc;
@@ -554,7 +639,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
             for (int j = 0; j < bpt; ++j) {
                 const uint32_t cnt = hist[tid * bpt + j];
                 hist[tid * bpt + j] = c;
-                if (k > nt && c < (uint32_t)kk && cnt > (uint32_t)kBinRankMax) misc[kFullBin] = 1u;
+                if (LONG && k > nt && c < (uint32_t)kk && cnt > (uint32_t)kBinRankMax) misc[kFullBin] = 1u;
                 if (c < (uint32_t)kk && (uint32_t)kk <= c + cnt) {
                     misc[kSel] = (uint32_t)(tid * bpt + j);
                     misc[kSelCount] = c + cnt;
@@ -570,7 +655,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
             const unsigned long long thr64 = (unsigned long long)lo_key + (((unsigned long long)bsel + 1ull) << shift) - 1ull;
             const uint32_t thr = thr64 > 0xffffffffull ? 0xffffffffu : (uint32_t)thr64;
             // (long lists: a bin of many, ties, would keep its threads long; those are sorted)
-            by_bin = thr != 0xffffffffu && (count_le <= (uint32_t)nt || (k > nt && count_le <= (uint32_t)(kSurvPer * nt) && misc[kFullBin] == 0u));
+            by_bin = thr != 0xffffffffu && (count_le <= (uint32_t)nt || (LONG && k > nt && count_le <= (uint32_t)(kSurvPer * nt) && misc[kFullBin] == 0u));
             if (thr != 0xffffffffu) {
                 // key slots without a candidate hold 0xffffffff > thr.  A wavefront counts its keys <= thr,
                 // reserves room for them with one atomic, then writes them: no wait for LDS per window
@@ -684,7 +769,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
 
     // ---- long result lists: the same with up to eight survivors a thread, and the output written in order -------------
     // (1,000 results of 4,096 candidates, 10,000 queries: 243 us; sorting 2,048 keys with 256 threads 309)
-    if (by_bin) {
+    if (LONG && by_bin) {
         unsigned long long mine[kSurvPer];
         uint32_t at[kSurvPer];
 #pragma unroll
@@ -782,22 +867,25 @@ template <int MW, bool HAS_TAPS>
 inline hipError_t launch_rerank_variant(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL,
                                         bool taps, bool fused, hipStream_t s) {
     const dim3 grid((unsigned)(a.nq + a.early)), block(a.threads);
-    if (fused) {
-        hipLaunchKernelGGL((rerank_kernel<MW, false, true>), grid, block, L.total, s, a, L, rk, RL);
+    if (fused && a.k > a.threads) {
+        hipLaunchKernelGGL((rerank_kernel<MW, false, true, true>), grid, block, L.total, s, a, L, rk, RL);
+    } else if (fused) {
+        hipLaunchKernelGGL((rerank_kernel<MW, false, true, false>), grid, block, L.total, s, a, L, rk, RL);
     } else if (taps) {
-        if constexpr (HAS_TAPS) hipLaunchKernelGGL((rerank_kernel<MW, true, false>), grid, block, L.total, s, a, L, rk, RL);
+        if constexpr (HAS_TAPS) hipLaunchKernelGGL((rerank_kernel<MW, true, false, true>), grid, block, L.total, s, a, L, rk, RL);
         else return hipErrorInvalidValue;
     } else {
-        hipLaunchKernelGGL((rerank_kernel<MW, false, false>), grid, block, L.total, s, a, L, rk, RL);
+        hipLaunchKernelGGL((rerank_kernel<MW, false, false, true>), grid, block, L.total, s, a, L, rk, RL);
     }
     return hipGetLastError();
 }
 
 template <int MW, bool HAS_TAPS>
 inline hipError_t configure_rerank_variant(size_t max_dynamic_lds) {
-    const void* kernels[3] = {reinterpret_cast<const void*>(rerank_kernel<MW, false, false>),
-                              reinterpret_cast<const void*>(rerank_kernel<MW, false, true>), nullptr};
-    if constexpr (HAS_TAPS) kernels[2] = reinterpret_cast<const void*>(rerank_kernel<MW, true, false>);
+    const void* kernels[4] = {reinterpret_cast<const void*>(rerank_kernel<MW, false, false, true>),
+                              reinterpret_cast<const void*>(rerank_kernel<MW, false, true, false>),
+                              reinterpret_cast<const void*>(rerank_kernel<MW, false, true, true>), nullptr};
+    if constexpr (HAS_TAPS) kernels[3] = reinterpret_cast<const void*>(rerank_kernel<MW, true, false, true>);
     for (const void* kfn : kernels) {
         if (!kfn) continue;
         hipFuncAttributes attr;
