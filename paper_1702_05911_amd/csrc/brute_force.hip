@@ -5,9 +5,9 @@
 // distance.  The contraction runs on the bf16 matrix cores, eight times the flops of the fp32 ones: a number is
 // cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly, queries of bytes too.
 // With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), every value s~ that the
-// matrix cores give is within E(q) of s: dropped piece products, one rounding of the running sum per matrix
-// instruction, and the norm (see error_terms in launch_brute_force).  If a is an upper bound of the k-th smallest s~
-// among the vectors seen, every vector of the true result has s~ <= a + 2E.  So
+// matrix cores give is within E(q) of s: dropped piece products, the rounding of the sums, and the norm (see
+// pqt_host::brute_error).  If a is an upper bound of the k-th smallest s~ among the vectors seen, every vector of the
+// true result has s~ <= a + 2E.  So
 //   * the database is walked in chunks, in the order i -> (i * step) mod N with step / N near the golden ratio: every
 //     prefix of the order is spread evenly over the database, whatever order the vectors are stored in;
 //   * bf_filter_*_kernel contracts a chunk with all queries.  Vectors go from memory through registers, where they are
@@ -26,6 +26,7 @@
 // the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
 // 0.90 ms (contraction 0.79 = 1.0 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
 #include "pqt_device.hpp"
+#include "pqt_host.hpp"
 #include "pqt_kernels.hpp"
 #include "row_distance.hpp"
 
@@ -820,15 +821,9 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
     a.step = (uint64_t)((double)N * 0.6180339887498949) | 1u;
     while (gcd_u64(a.step, N) != 1) a.step += 2;
-    // |s~ - s|: with u = 2^-9 the rounding unit of bf16, a second piece leaves u^2 of a number, the product of two second
-    // pieces is u^2 of a product: u^2 for byte vectors (the query's remainder), 3 u^2 for floats, each times ||q|| ||x||
-    // (Cauchy-Schwarz), with 3 % for the terms of higher order.  The running sum is rounded once per matrix
-    // instruction (2^-23 covers truncation; 16 more for what happens inside one), and its size is at most
-    // ||q|| ||x|| + ||x||^2 / 2.  The norm's own sum has D / 64 + 16 roundings.
-    const int pieces = elem_bytes == 1 ? 2 : 3;
-    const float u2 = 1.03f / 262144.0f, rounding = (float)(pieces * p.KS + 16) / 8388608.0f;
-    a.err_dot = (elem_bytes == 1 ? 1.0f : 3.0f) * u2 + rounding;
-    a.err_norm = 0.5f * (rounding + (float)(D / 64 + 16) / 16777216.0f);
+    const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
+    a.err_dot = err.dot;
+    a.err_norm = err.norm;
     return elem_bytes == 1 ? run<uint8_t>(p, a, queries, nq, out_ids, out_dists, s) : run<float>(p, a, queries, nq, out_ids, out_dists, s);
 }
 

@@ -191,6 +191,16 @@ int read_index_file(const char* path, IndexFile& out, std::string& err) {
     return PQT_OK;
 }
 
+BruteError brute_error(int elem_bytes, int D) {
+    const int pieces = elem_bytes == 1 ? 2 : 3;                      // products of pieces per product
+    const double cut = elem_bytes == 1 ? 1.0 / 131072.0 : 1.0 / 32768.0;
+    const double adding = (16.0 * pieces * ((D + 15) / 16) + 16.0) / 8388608.0;
+    BruteError e;
+    e.dot = (float)(1.03 * (cut + adding));
+    e.norm = (float)(0.515 * (adding + (D / 64 + 24) / 16777216.0));
+    return e;
+}
+
 long region_size(int nA, int nB, int Tn) {
     long n = 0;
     for (int a = 0; a < nA && a < Tn; ++a) {

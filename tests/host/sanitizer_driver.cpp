@@ -4,6 +4,7 @@
 //   sizes D P k1 k2 M N H T C format     check_sizes                             -> "rc <code> <message>"
 //   static <R> <T>                       make_static_order                       -> "Tn <n>", 9 thresholds (hex floats), 10 table rows
 //   region <nA> <nB> <Tn>                region_size                             -> "n <count>"
+//   bound <elem_bytes> <D>               brute_error                             -> "<dot> <norm>" (hex floats)
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -52,6 +53,11 @@ int main(int argc, char** argv) {
     }
     if (mode == "region" && argc == 5) {
         printf("n %ld\n", pqt_host::region_size(atoi(argv[2]), atoi(argv[3]), atoi(argv[4])));
+        return 0;
+    }
+    if (mode == "bound" && argc == 4) {
+        const pqt_host::BruteError e = pqt_host::brute_error(atoi(argv[2]), atoi(argv[3]));
+        printf("%a %a\n", (double)e.dot, (double)e.norm);
         return 0;
     }
     return 2;

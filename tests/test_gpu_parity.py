@@ -1029,6 +1029,40 @@ def test_brute_force_edges(pqt, kind, N, D, nq, k):
         pqt.pqt_index_free(ix)
 
 
+def _vectors_only_index(pqt, N, D):
+    """An index that holds no more than a collection to search exactly: one bin."""
+    return pqt.pqt_index_from_arrays(dict(
+        N=N, H=1, D=D, P=1, k1=1, k2=1, M=1, T=1, C=256, C1=np.zeros((1, 1, D)), C2=np.zeros((1, 1, 1, D)),
+        tbl_i=np.zeros((1, 256)), tbl_j=np.zeros((1, 256)), tbl_lam=np.zeros((1, 256)), cc=np.zeros((1, 1, 1)),
+        offsets=np.array([0, N]), ids=np.arange(N), codes=np.zeros((N, 1))))
+
+
+@pytest.mark.parametrize("D", [16, 128, 192])
+def test_brute_force_keeps_what_the_cut_moves_most(pqt, D):
+    """The filter's values of two vectors may be off in opposite directions by all that cutting numbers into pieces can
+    cost.  The nearest vector's value is too large, the second nearest's too small, and the nearest comes last in the
+    database order (place i is vector i * step mod N), when the list of the best holds the other one only."""
+    import math
+    import torch
+    N = 300_001                                                      # three chunks with one query and one result
+    near, second, q = np.float32(1.00388336), np.float32(1.00392914), np.float32(1.00389862)
+    assert abs(near - q) < abs(second - q)
+    step = int(N * 0.6180339887498949) | 1
+    while math.gcd(step, N) != 1:
+        step += 2
+    last = (N - 1) * step % N
+    X = torch.full((N, D), 0.5, device="cuda")                       # (short: the bound grows with the norms)
+    X[0] = float(second)
+    X[last] = float(near)
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X)
+        ids, _ = pqt.pqt_brute_force(ix, torch.full((1, D), float(q), device="cuda"), 1)
+        assert ids.item() == last
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture

@@ -167,3 +167,49 @@ def test_region_size_counts_the_hyperbolic_region(driver):
     for nA, nB, Tn in ((8, 8, 64), (64, 64, 1024), (128, 16, 300), (5, 1000, 37), (1024, 1024, 8192)):
         want = sum(1 for a in range(min(nA, Tn)) for b in range(min(nB, Tn // (a + 1))))
         assert int(driver("region", nA, nB, Tn).split()[1]) == want
+
+
+def _bf16(x):
+    """float32 -> nearest bf16 (ties to even), as float32."""
+    u = np.asarray(x, np.float32).view(np.uint32).astype(np.uint64)
+    return (((u + 0x7FFF + ((u >> 16) & 1)) >> 16) << 16).astype(np.uint32).view(np.float32)
+
+
+def _truncate(x):
+    """float64 -> float32 towards zero."""
+    r = np.asarray(x, np.float64).astype(np.float32)
+    over = np.abs(r.astype(np.float64)) > np.abs(x)
+    return np.where(over, np.nextafter(r, np.float32(0)), r)
+
+
+@pytest.mark.parametrize("elem_bytes, D", [(4, 4), (4, 16), (4, 128), (4, 192), (4, 320), (4, 960), (1, 16), (1, 96), (1, 128), (1, 160)])
+def test_brute_force_error_bound(driver, elem_bytes, D):
+    """The bound that lets the brute-force filter drop a vector, against the filter's arithmetic written out: numbers cut
+    into bf16 pieces, piece products added in fp32 with every addition truncated, against float64.  All coordinates of a
+    vector are equal (the Cauchy-Schwarz bound is then reached) and their significands the worst of 60,000 for the cut,
+    together with the ends of the range."""
+    dot, norm = (float.fromhex(v) for v in driver("bound", elem_bytes, D).split())
+    grid = (1.0 + np.arange(60_000) / 60_000).astype(np.float32)
+    first = _bf16(grid)
+    second = _bf16(grid - first)
+    left = (grid - first).astype(np.float64) / grid, (grid.astype(np.float64) - first - second) / grid
+    worst = np.concatenate([[i for v in left for i in (np.argmax(v), np.argmin(v))], np.argsort(-np.abs(left[0]))[:40],
+                            np.argsort(-np.abs(left[1]))[:40], [0, len(grid) - 1]])
+    q = grid[worst.astype(int)]
+    x = np.array([1, 3, 127, 129, 253, 255], np.float32) if elem_bytes == 1 else q
+    q, x = (v.ravel() for v in np.meshgrid(q, x))
+    half = _truncate(0.5 * D * x.astype(np.float64) ** 2)             # (its own sum is not what is tested here)
+    for order in (1, -1):                                            # products first added to the norm, or last
+        hq, hx = _bf16(q), _bf16(x)
+        mq, mx = _bf16(q - hq), _bf16(x - hx)
+        products = [hx * hq, hx * mq] + ([mx * hq] if elem_bytes == 4 else [])
+        s = -half if order == 1 else np.zeros_like(q)
+        for p in products:
+            p = p.astype(np.float64)
+            for _ in range(D):
+                s = _truncate(s.astype(np.float64) + p)
+        if order == -1:
+            s = _truncate(s.astype(np.float64) - half)
+        true = D * q.astype(np.float64) * x - 0.5 * D * x.astype(np.float64) ** 2
+        bound = dot * D * np.abs(q.astype(np.float64) * x) + norm * D * x.astype(np.float64) ** 2
+        assert (np.abs(s - true) <= bound).all(), (np.abs(s - true) / bound).max()
