@@ -32,15 +32,16 @@ struct PlaceLds {
     size_t off_x, off_a, off_d1, off_sel, off_leaf, off_code, total;
 };
 
-__host__ __device__ inline PlaceLds place_layout(int ds, int P, int k1, int code_bytes, int waves, bool votes) {
-    PlaceLds L;
+__host__ __device__ constexpr PlaceLds place_layout(int ds, int P, int k1, int code_bytes, int waves, bool votes) {
+    PlaceLds L = {};
     const int pieces = ((ds < kSlab ? ds : kSlab) + 3) / 4;
     L.st = 4 * (pieces | 1);
     size_t o = 0;
     L.off_x = o;    o += sizeof(float) * waves * kPlaceRows * L.st;
     // the distances of up to 32 centroids come out of one pass over the staged values and take their place
     const size_t x_bytes = sizeof(float) * kPlaceRows * L.st, a_bytes = sizeof(float) * k1 * kRowStride;
-    L.a_stride = (k1 <= 32 && x_bytes > a_bytes ? x_bytes : a_bytes) / sizeof(float);
+    // (whole 16-byte pieces: every wavefront's staged values are written in them)
+    L.a_stride = ((k1 <= 32 && x_bytes > a_bytes ? x_bytes : a_bytes) + 15) / 16 * 4;
     if (k1 <= 32) o = 0;
     L.off_a = o;    o += sizeof(float) * waves * L.a_stride;
     L.off_d1 = o;   o += votes ? 0 : sizeof(float) * k1 * kRowStride;
@@ -51,6 +52,20 @@ __host__ __device__ inline PlaceLds place_layout(int ds, int P, int k1, int code
     L.total = (o + 15) & ~size_t(15);
     return L;
 }
+
+// Where a wavefront stages its values
+__host__ __device__ constexpr size_t staging_stride(const PlaceLds& L, int k1) {
+    return k1 <= 32 ? L.a_stride : (size_t)kPlaceRows * L.st;
+}
+constexpr bool staging_is_aligned() {
+    for (int ds = 4; ds <= 36; ds += 4)
+        for (int k1 = 1; k1 <= 40; ++k1) {
+            const PlaceLds L = place_layout(ds, 2, k1, 4, 4, false);
+            if (L.off_x % 16 || L.st % 4 || staging_stride(L, k1) % 4) return false;
+        }
+    return true;
+}
+static_assert(staging_is_aligned(), "16-byte writes");
 
 // Level-1 distances of the workgroup's vectors in sub-part m, by one wavefront: at[i * kRowStride + v].
 // WIDE: rows are read in 16-byte pieces.  Vectors past the end repeat the last one.
@@ -244,7 +259,7 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
     const int D = g.D, P = g.P, k1 = g.k1, k2 = g.k2, M = g.M, dp = D / P, per = M / P;
     const int64_t v0 = (int64_t)blockIdx.x * kPlaceRows;
     const int nv = (int)(g.n - v0 < kPlaceRows ? g.n - v0 : kPlaceRows);
-    float* xs = reinterpret_cast<float*>(smem + L.off_x) + (size_t)wave * (k1 <= 32 ? L.a_stride : (size_t)kPlaceRows * L.st);
+    float* xs = reinterpret_cast<float*>(smem + L.off_x) + wave * staging_stride(L, k1);
     float* a0 = reinterpret_cast<float*>(smem + L.off_a);
     float* d1 = reinterpret_cast<float*>(smem + L.off_d1);
     unsigned long long* sel = reinterpret_cast<unsigned long long*>(smem + L.off_sel);

@@ -730,6 +730,9 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
     (70, 16, 1, 256, 2, 2, 0, 0),          # the most centroids
     (131, 12, 1, 4, 300, 3, 0, 0),         # more children than threads
     (67, 16, 2, 20, 7, 4, 1, 0),           # (pair, lambda) codes
+    (130, 16, 2, 7, 3, 4, 0, 0),           # 16-byte rows and numbers of centroids that are no multiple of four, so that a
+    (77, 64, 2, 21, 2, 4, 0, 0),           # wavefront's distances outgrow its staged values by an odd number of words
+    (70, 32, 4, 15, 4, 4, 1, 0),
     (90, 6, 2, 3, 2, 6, 1, 1),             # sub-parts of one dimension
 ])
 def test_builder_edges(pqt, N, D, P, k1, k2, M, fmt, offset):
@@ -966,6 +969,25 @@ def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
             sub = Xp[lab == i]
             want = B.lloyd(sub, k2, iters) if len(sub) else np.repeat(got["C1"][p, i][None], k2, axis=0)
             np.testing.assert_allclose(got["C2"][p, i], want, rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8)])
+def test_line_table_edges(pqt, n, D, P, k1, M):
+    """Line votes where 16-byte rows meet numbers of centroids that are no multiple of four (and at sub-parts of five
+    dimensions).  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
+    Shares as in test_training_on_the_gpu: within one of the quota, and a near tie of two lines may move a vote or two."""
+    import torch
+    rng = np.random.default_rng(17)
+    X = rng.integers(0, 64, (n, D)).astype(np.float32)
+    got = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=2, M=M, iters=0, n_table=n)
+    pairs, ds = Q.centroid_pairs(k1), D // M
+    for m in range(M):
+        line, _, _ = B.best_lines(X[:, m * ds:(m + 1) * ds].astype(np.float64), B.subpart_centroids(got["C1"], M, m))
+        quota = np.bincount(line, minlength=len(pairs)) * 256.0 / n
+        have = np.zeros(len(pairs))
+        for i, j in zip(got["tbl_i"][m].tolist(), got["tbl_j"][m].tolist()):
+            have[pairs.index((i, j))] += 1
+        assert have.sum() == 256 and np.abs(have - quota).max() <= 1.0 + 256.0 * 3 / n, m
 
 
 @pytest.mark.parametrize("kind, N, D, nq, k", [
