@@ -145,7 +145,9 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
 }
 
 // bound of |s~ - s| for a query of norm qn and database vectors of norm up to xm
-__device__ __forceinline__ float error_bound(const BruteArgs& g, float qn, float xm) { return g.err_dot * qn * xm + g.err_norm * xm * xm; }
+__device__ __forceinline__ float error_bound(const BruteArgs& g, float qn, float xm) {
+    return g.err_dot * qn * xm + g.err_norm * xm * xm + pqt_host::kBruteUnderflow;
+}
 
 // -(a + 2E) of a query: what an accumulator has to reach to be kept
 __device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {

@@ -1085,6 +1085,28 @@ def test_brute_force_keeps_what_the_cut_moves_most(pqt, D):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -66, 2.0 ** -70])
+@pytest.mark.parametrize("D", [32, 128])
+def test_brute_force_tiny_values(pqt, D, scale):
+    """Squares and products near and below the smallest normal fp32 number (2^-126), where the matrix cores need not keep
+    what fp32 does: whole numbers times a power of two, so that every exact distance is a multiple of the smallest fp32
+    number and results are those of the whole numbers."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    N, nq, k = 9000, 5, 20
+    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda").float()
+    Y = torch.randint(0, 256, (nq, D), generator=gen, device="cuda").float()
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X * scale)
+        ids, d = pqt.pqt_brute_force(ix, Y * scale, k)
+        true = torch.stack([((X.double() - y) ** 2).sum(1) for y in Y.double()])
+        assert torch.equal(ids, (true * N + torch.arange(N, device="cuda")).sort(1).indices[:, :k])
+        assert torch.equal(d.double(), true.gather(1, ids) * scale ** 2)
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
