@@ -4,19 +4,22 @@
 // A dense contraction finds the few vectors that can be among the k nearest, and only those get their exact fp32
 // distance.  The contraction runs on the bf16 matrix cores, eight times the flops of the fp32 ones: a number is
 // cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly, queries of bytes too.
-// With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), every value s~ that the
-// matrix cores give is within E(q) of s: dropped piece products, the rounding of the sums, and the norm (see
-// pqt_host::brute_error).  If a is an upper bound of the k-th smallest s~ among the vectors seen, every vector of the
-// true result has s~ <= a + 2E.  So
+// With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), the sum of the matrix cores is within
+// a ||q||^2 + b ||x||^2 of s: dropped piece products, the rounding of the sums, and the norm (see pqt_host::brute_error).
+// The filter's value v is that sum less b ||x||^2 (it starts from the norm), so that v <= s + a ||q||^2: the length of one
+// vector widens nothing for the others.  The other way round v >= s - a ||q||^2 - 2 b ||x||^2, and a vector near the query
+// is at most ||q|| + its distance long, so an upper bound of the k-th smallest v gives one of the k-th smallest s, and
+// from that what v may be at most for every vector of the true result (keep_up_to).  Floats are taken relative to
+// a centre where they have one, the median of 64 of them in every dimension: a common offset would count as length.  So
 //   * the database is walked in chunks, in the order i -> (i * step) mod N with step / N near the golden ratio: every
 //     prefix of the order is spread evenly over the database, whatever order the vectors are stored in;
 //   * bf_filter_*_kernel contracts a chunk with all queries.  Vectors go from memory through registers, where they are
 //     cut, into LDS in the operand layout of v_mfma_f32_32x32x16_bf16 (the queries are laid out once, by
 //     pack_queries_kernel): no copy of the database in another format exists.  The first chunk (kDense vectors) is written
-//     out; from then on only pairs with s~ <= a + 2E are kept: the accumulators start at -||x||^2 / 2, a maximum of 16
+//     out; from then on only pairs whose value may matter are kept: the accumulators start from the norm, a maximum of 16
 //     values and one comparison decide for 16 pairs, and a lane appends what passes to a list of its own, so that no
 //     counter is shared (a query belongs to one column of one wavefront);
-//   * bf_select_kernel, one workgroup per query, bounds the k-th smallest s~ by a 1024-bin histogram and keeps what
+//   * bf_select_kernel, one workgroup per query, bounds the k-th smallest value by a 1024-bin histogram and keeps what
 //     can still matter; after the last chunk it computes the exact distances sum (y - x)^2 of that list
 //     (k and a few more) in fp32 and sorts them.
 // Chunks grow by a factor, so that about k times that factor pairs pass per chunk and query.  A query whose lists
@@ -25,6 +28,8 @@
 // Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 2.9 = 0.88 PFLOP/s, selection 0.49); with
 // the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
 // 0.90 ms (contraction 0.79 = 1.0 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
+#include <type_traits>
+
 #include "pqt_device.hpp"
 #include "pqt_host.hpp"
 #include "pqt_kernels.hpp"
@@ -81,7 +86,13 @@ __global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
         const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         const float4 v0 = d < D ? *reinterpret_cast<const float4*>(row + d) : z;
         const float4 v1 = d + 4 < D ? *reinterpret_cast<const float4*>(row + d + 4) : z;
-        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+        if (g.centre) {                                      // (zeros where it is not used)
+            const float4 c0 = d < D ? *reinterpret_cast<const float4*>(g.centre + d) : z;
+            const float4 c1 = d + 4 < D ? *reinterpret_cast<const float4*>(g.centre + d + 4) : z;
+            v[0] -= c0.x; v[1] -= c0.y; v[2] -= c0.z; v[3] -= c0.w;
+            v[4] -= c1.x; v[5] -= c1.y; v[6] -= c1.z; v[7] -= c1.w;
+        }
         u32x4 h, m;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -106,10 +117,81 @@ __global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
     if (__any(second != 0) && lane == 0) g.control[kBfSecond] = 1u;
 }
 
-// Half squared norms of the database vectors and, in the word behind them, the bits of the largest norm (a little
-// enlarged; never negative, so bits order as values).  A group of lanes per row, 16 bytes per lane and step.
+// The centre of float vectors: in every dimension the median of 64 vectors spread over the database (places 0 .. 63 of the
+// database order), which a few long ones do not move.  64 dimensions per workgroup.
+constexpr int kCentreRows = 64;
+__global__ __launch_bounds__(kBfThreads) void centre_kernel(const float* x, uint64_t N, uint64_t step, int D, float* centre) {
+    constexpr int kWaves = kBfThreads / kWave, kPer = kCentreRows / kWaves;
+    __shared__ uint32_t key[kCentreRows][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, d = blockIdx.x * kWave + lane;
+    float mine[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        mine[u] = x[((uint64_t)(wave + u * kWaves) * step % N) * (uint64_t)D + (d < D ? d : 0)];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) key[wave + u * kWaves][lane] = mono_key(mine[u]);
+    __syncthreads();
+    int below[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) below[u] = 0;
+    for (int o = 0; o < kCentreRows; ++o) {
+        const uint32_t other = key[o][lane];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const uint32_t own = mono_key(mine[u]);
+            below[u] += other < own || (other == own && o < wave + u * kWaves) ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (below[u] == kCentreRows / 2 && d < D) centre[d] = fabsf(mine[u]) < 1e18f ? mine[u] : 0.0f;
+}
+
+// The centre is used (*use = 1) where it halves the norms of most of these vectors: 48 of the 64.  Else it becomes zero, and
+// the filter need not subtract it (777 x 150,001 x 960: 810 us, subtracting in every step 888).  One workgroup.
+__global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64_t N, uint64_t step, int D, float* centre, uint32_t* use) {
+    __shared__ uint32_t halved;
+    constexpr int kWaves = 1024 / kWave, kPer = kCentreRows / kWaves;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    if (threadIdx.x == 0) halved = 0u;
+    __syncthreads();
+    const float* row[kPer];
+    float with[kPer], without[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        row[u] = x + ((uint64_t)(wave + u * kWaves) * step % N) * (uint64_t)D;
+        with[u] = without[u] = 0.0f;
+    }
+#pragma unroll 4
+    for (int d = lane; d < D; d += kWave) {
+        const float at = centre[d];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const float v = row[u][d];
+            with[u] = fmaf(v - at, v - at, with[u]);
+            without[u] = fmaf(v, v, without[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        for (int off = 1; off < kWave; off <<= 1) {
+            with[u] += __shfl_xor(with[u], off, kWave);
+            without[u] += __shfl_xor(without[u], off, kWave);
+        }
+        if (lane == 0 && 4.0f * with[u] < without[u]) atomicAdd(&halved, 1u);
+    }
+    __syncthreads();
+    const bool yes = halved >= kCentreRows * 3 / 4;
+    if (!yes)
+        for (int d = threadIdx.x; d < D; d += 1024) centre[d] = 0.0f;
+    if (threadIdx.x == 0) *use = yes ? 1u : 0u;
+}
+
+// What the accumulators start from, `part` (1 - 2 b) of the half squared norms of the database vectors, and, in the word behind
+// them, the bits of the largest norm (a little enlarged; never negative, so bits order as values).  A group of lanes per
+// row, 16 bytes per lane and step.
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, float* out) {
+__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float part, float* out) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     constexpr int pe = 16 / (int)sizeof(Elem);
     const int npieces = D / pe, lpr = lanes_per_row(npieces), per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
@@ -118,13 +200,16 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
     for (int64_t r0 = ((int64_t)blockIdx.x * (kBfThreads / kWave) + wave) * per_wave; r0 < n; r0 += nwaves * per_wave) {
         const int64_t r = r0 + sub;
         float s = 0.0f;
-        if (r < n)
+        if (r < n) {
+#pragma unroll 4
             for (int piece = l; piece < npieces; piece += lpr) {
                 const u32x4 w = reinterpret_cast<const u32x4*>(x + (size_t)r * D)[piece];
+                u32x4 c = {0u, 0u, 0u, 0u};
+                if constexpr (sizeof(Elem) == 4) c = reinterpret_cast<const u32x4*>(centre)[piece];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     if constexpr (sizeof(Elem) == 4) {
-                        const float v = __uint_as_float(w[j]);
+                        const float v = __uint_as_float(w[j]) - __uint_as_float(c[j]);
                         s = fmaf(v, v, s);
                     } else {
 #pragma unroll
@@ -135,24 +220,39 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
                     }
                 }
             }
+        }
         for (int off = 1; off < lpr; off <<= 1) s += __shfl_xor(s, off, kWave);
-        if (r < n && l == 0) out[r] = 0.5f * s;
+        if (r < n && l == 0) out[r] = part * (0.5f * s);
         top = fmaxf(top, r < n ? s : 0.0f);
         if (r < n && s != s) top = __builtin_inff();
     }
+    // (one atomic per workgroup: one per wavefront took longer than the rest)
+    __shared__ uint32_t wave_top[kBfThreads / kWave];
     const uint32_t bits = wave_max_u32(__float_as_uint(1.001f * sqrtf(top)));
-    if (lane == 0) atomicMax(reinterpret_cast<uint32_t*>(out) + n, bits);
+    if (lane == 0) wave_top[wave] = bits;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t most = bits;
+        for (int w = 1; w < kBfThreads / kWave; ++w) most = max(most, wave_top[w]);
+        atomicMax(reinterpret_cast<uint32_t*>(out) + n, most);
+    }
 }
 
-// bound of |s~ - s| for a query of norm qn and database vectors of norm up to xm
-__device__ __forceinline__ float error_bound(const BruteArgs& g, float qn, float xm) {
-    return g.err_dot * qn * xm + g.err_norm * xm * xm + pqt_host::kBruteUnderflow;
+// What the value of a vector of the true result may be at most, when k vectors seen have values of at most v.
+// With `own` for a ||q||^2 the k-th smallest s is at most v + own + 2 b r^2, r the largest norm that a vector with value v
+// can have: from s >= r^2 / 2 - qn r follows (1 - 4 b) r^2 / 2 - qn r <= v + own.  A query longer than all vectors has the
+// tighter 2 a ||q|| X, X the largest norm.  0.1 % on r and 3 % on the sum for the rounding here.
+__device__ __forceinline__ float keep_up_to(const BruteArgs& g, float qn, float v) {
+    const float top = g.xhalf[g.N];
+    const float own = g.err_query * qn * fminf(qn, 2.0f * top) + pqt_host::kBruteUnderflow;
+    const float slim = 1.0f - 4.0f * g.err_row;
+    const float r = fminf(top, 1.001f * (qn + sqrtf(fmaxf(qn * qn + 2.0f * slim * (v + own), 0.0f))) / slim);
+    return v + 1.03f * (2.0f * own + 2.0f * g.err_row * r * r);
 }
 
-// -(a + 2E) of a query: what an accumulator has to reach to be kept
+// -keep_up_to of a query: what an accumulator has to reach to be kept
 __device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {
-    if (q >= g.nq || g.flagged[q]) return __builtin_inff();
-    return -(g.edge[q] + 2.0f * error_bound(g, g.qnorm[q], g.xhalf[g.N]));
+    return q >= g.nq || g.flagged[q] ? __builtin_inff() : -g.keep[q];
 }
 
 // One 32 x 32 tile of accumulators: lane l holds query column l % 32 and database rows 8 * (r / 4) + 4 * (l / 32) + r % 4.
@@ -352,6 +452,7 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
     for (int i = 0; i < kXPieces; ++i) id[i] = ((g.chunk_pos + (uint64_t)split * kGenRows + rl + 64 * i) % g.N) * g.step % g.N;
     hid = ((g.chunk_pos + (uint64_t)split * kGenRows + tid) % g.N) * g.step % g.N;
     struct Step { u32x4 x[kXPieces], q[kQPieces]; };
+    const bool centred = kFloats && g.use_centre[0] != 0u;
     int fks = 0;                               // the step fetched next, of the tile the ids stand for
     auto fetch = [&](Step& f) {                // (past the last tile: some vectors, unused; always loading keeps the pieces in registers)
         const int d = fks * 16 + 4 * c4;
@@ -377,8 +478,16 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
         }
     };
     v16f acc[2][kQ];
-    auto step = [&](Step& f, int buf, bool first, float hx, float* hs) {
+    auto step = [&](Step& f, int buf, int ks, float hx, float* hs) {
+        const bool first = ks == 0;
         if constexpr (kFloats) {
+            if (centred && ks * 16 + 4 * c4 < g.D) {           // (the zeros past the last dimension stay what they are)
+                const u32x4 c = *reinterpret_cast<const u32x4*>(g.centre + ks * 16 + 4 * c4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) f.x[i][j] = __float_as_uint(__uint_as_float(f.x[i][j]) - __uint_as_float(c[j]));
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {      // row r = rl + 64 i: 8 bytes of either piece
                 const int r = rl + 64 * i;
@@ -450,15 +559,15 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
         hid -= hid >= g.N ? g.N : 0;
         int ks = 0;
         if (odd) {
-            step(f1, 1, true, hx, hs[half]);
+            step(f1, 1, 0, hx, hs[half]);
             ks = 1;
         }
         for (; ks + 1 < KS; ks += 2) {
-            step(f0, 0, ks == 0, hx, hs[half]);
-            step(f1, 1, false, hx, hs[half]);
+            step(f0, 0, ks, hx, hs[half]);
+            step(f1, 1, ks + 1, hx, hs[half]);
         }
         odd = ks < KS;
-        if (odd) step(f0, 0, ks == 0, hx, hs[half]);
+        if (odd) step(f0, 0, ks, hx, hs[half]);
 #pragma unroll
         for (int ct = 0; ct < kQ; ++ct) {
             const int64_t q = q0 + ct * 32 + (lane & 31);
@@ -491,7 +600,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     __shared__ uint32_t hist[kSelectBins];
     __shared__ uint32_t part[kBfThreads / kWave];
     __shared__ float bounds[2 * kBfThreads / kWave];
-    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow
+    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow, 5, 6 entries before and up to its end
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k;
     const int64_t q = blockIdx.x;
     if (g.flagged[q]) return;
@@ -527,60 +636,89 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         }
     }
     __syncthreads();
-    const float xm = g.xhalf[g.N];
-    const float err = error_bound(g, g.qnorm[q], xm);
+    const float qn = g.qnorm[q];
     auto give_up = [&]() {                           // to the exact scan
         if (tid == 0) {
             g.flagged[q] = 1u;
             g.todo[atomicAdd(&g.control[kBfTodo], 1u)] = (uint32_t)q;
         }
     };
-    if (misc[4] || !(err < 1e30f)) {                 // the same for the whole workgroup; below it every s~ is finite
+    // the same for the whole workgroup; with these norms all values are finite
+    if (misc[4] || !(qn < 1e18f) || !(g.xhalf[g.N] < 1e18f)) {
         give_up();
         return;
     }
     // ---- an upper bound of the k-th smallest: the end of its bin ---------------------------------------------------
-    auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
-    float lo = __builtin_inff(), hi = -__builtin_inff();
-    for (int e = tid; e < n; e += kBfThreads) {
-        lo = fminf(lo, value(e));
-        hi = fmaxf(hi, value(e));
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        lo = fminf(lo, __shfl_xor(lo, off, kWave));
-        hi = fmaxf(hi, __shfl_xor(hi, off, kWave));
-    }
-    if (lane == 0) {
-        bounds[2 * wave] = lo;
-        bounds[2 * wave + 1] = hi;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kBfThreads / kWave; ++w) {
-        lo = fminf(lo, bounds[2 * w]);
-        hi = fmaxf(hi, bounds[2 * w + 1]);
-    }
-    const float scale = hi > lo ? (float)kSelectBins / (hi - lo) : 0.0f;
-    for (int e = tid; e < n; e += kBfThreads) atomicAdd(&hist[min((int)((value(e) - lo) * scale), kSelectBins - 1)], 1u);
-    __syncthreads();
-    {
-        constexpr int bpt = kSelectBins / kBfThreads;
-        uint32_t h[bpt], sum = 0, total;
-#pragma unroll
-        for (int j = 0; j < bpt; ++j) sum += h[j] = hist[tid * bpt + j];
-        uint32_t c = block_exclusive_sum(sum, part, total);
-#pragma unroll
-        for (int j = 0; j < bpt; ++j) {
-            if (c < (uint32_t)k && (uint32_t)k <= c + h[j]) misc[2] = (uint32_t)(tid * bpt + j);
-            c += h[j];
-        }
-    }
-    __syncthreads();
-    // the end of the bin, and E for the rounding of the bin numbers (a few units of the values' last place; E is more)
-    const float edge = fminf(hi, lo + (scale > 0.0f ? (float)(misc[2] + 1u) / scale : 0.0f) + err);
-    const float keep = edge + 2.0f * err;
-    // ---- keep what can still be among the k nearest ---------------------------------------------------------------
+    // One histogram over the values' range; where a few long vectors stretch the range, so that the bin of the k-th holds more
+    // than may be kept, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
+    // among those that are divided.
     const int cap = best_capacity(k);
+    auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
+    static_assert(kDense <= 32 * kBfThreads, "a bit per entry");
+    uint32_t members = 0xffffffffu, below = 0u;
+    float edge = 0.0f;
+    auto divide = [&](auto all) {                    // one histogram; false: the bin's entries are to be divided
+        constexpr bool ALL = decltype(all)::value;   // every entry is a member
+        float lo = __builtin_inff(), hi = -__builtin_inff();
+        for (int e = tid, u = 0; e < n; e += kBfThreads, ++u)
+            if (ALL || (members >> u & 1u)) {
+                lo = fminf(lo, value(e));
+                hi = fmaxf(hi, value(e));
+            }
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off, kWave));
+            hi = fmaxf(hi, __shfl_xor(hi, off, kWave));
+        }
+        if (lane == 0) {
+            bounds[2 * wave] = lo;
+            bounds[2 * wave + 1] = hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kBfThreads / kWave; ++w) {
+            lo = fminf(lo, bounds[2 * w]);
+            hi = fmaxf(hi, bounds[2 * w + 1]);
+        }
+        edge = hi;
+        if (!(hi - lo > 1e-30f)) return true;        // equal, or next to it
+        const float scale = (float)kSelectBins / (hi - lo);
+        auto bin_of = [&](float v) { return (int)fminf((v - lo) * scale, (float)(kSelectBins - 1)); };
+        for (int e = tid, u = 0; e < n; e += kBfThreads, ++u)
+            if (ALL || (members >> u & 1u)) atomicAdd(&hist[bin_of(value(e))], 1u);
+        __syncthreads();
+        {
+            constexpr int bpt = kSelectBins / kBfThreads;
+            uint32_t h[bpt], sum = 0, total;
+#pragma unroll
+            for (int j = 0; j < bpt; ++j) {
+                sum += h[j] = hist[tid * bpt + j];
+                hist[tid * bpt + j] = 0u;
+            }
+            uint32_t c = below + block_exclusive_sum(sum, part, total);
+#pragma unroll
+            for (int j = 0; j < bpt; ++j) {
+                if (c < (uint32_t)k && (uint32_t)k <= c + h[j]) {
+                    misc[2] = (uint32_t)(tid * bpt + j);
+                    misc[5] = c;
+                    misc[6] = c + h[j];
+                }
+                c += h[j];
+            }
+        }
+        __syncthreads();
+        // the end of the bin, a little behind it for the rounding of the bin numbers
+        const int bin = (int)misc[2];
+        below = misc[5];
+        edge = fminf(hi, lo + (float)(bin + 1) / scale * 1.000002f + 4e-7f * fabsf(lo));
+        if (2u * misc[6] <= (uint32_t)cap) return true;
+        for (int e = tid, u = 0; e < n; e += kBfThreads, ++u)
+            if (bin_of(value(e)) != bin) members &= ~(1u << u);
+        return false;
+    };
+    bool done = divide(std::true_type{});
+    for (int level = 0; level < 3 && !done; ++level) done = divide(std::false_type{});
+    const float keep = keep_up_to(g, qn, edge);
+    // ---- keep what can still be among the k nearest ---------------------------------------------------------------
     for (int e0 = 0; e0 < n; e0 += kBfThreads) {     // in place: entry e moves to a place <= e that has been read
         const int e = e0 + tid;
         const unsigned long long key = e < n ? keys[e] : ~0ull;
@@ -602,7 +740,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         for (int e = tid; e < n; e += kBfThreads) best[e] = keys[e];
         if (tid == 0) {
             g.best_count[q] = (uint32_t)n;
-            g.edge[q] = edge;
+            g.keep[q] = keep;
         }
         return;
     }
@@ -690,6 +828,9 @@ uint64_t gcd_u64(uint64_t a, uint64_t b) {
     return a;
 }
 
+// where the centre stands behind the N half norms, the largest norm and the word that says whether it is used: at a 16-byte boundary
+size_t centre_at(uint64_t N) { return (size_t)(N + 5) / 4 * 4; }
+
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // How one call is cut: sizes of the workspace's pieces and the launch shapes.
@@ -742,7 +883,7 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.flagged = c.take<uint32_t>(p.batch_pad);
     v.todo = c.take<uint32_t>(p.batch_pad);
     v.qnorm = c.take<float>(p.batch_pad);
-    v.edge = c.take<float>(p.batch_pad);
+    v.keep = c.take<float>(p.batch_pad);
     v.best_count = c.take<uint32_t>(p.batch_pad);
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
     v.dense = c.take<float>((size_t)p.batch_pad * kDense);
@@ -806,11 +947,27 @@ size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k) {
     return carve(make_plan(nq, D, elem_bytes, k), k, nullptr, nullptr);
 }
 
+uint64_t brute_force_step(uint64_t N) {
+    uint64_t step = (uint64_t)((double)N * 0.6180339887498949) | 1u;
+    while (gcd_u64(step, N) != 1) step += 2;
+    return step;
+}
+
+size_t brute_force_norm_words(uint64_t N, int D) { return centre_at(N) + (size_t)D; }
+
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s) {
     hipLaunchKernelGGL(fill_word_kernel, dim3(1), dim3(1), 0, s, reinterpret_cast<uint32_t*>(out) + N, 0u);
-    const dim3 grid((unsigned)(N / 16 + 1 < 4096 ? N / 16 + 1 : 4096)), block(kBfThreads);
-    if (elem_bytes == 1) hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, out);
-    else hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, static_cast<const float*>(vectors), (int64_t)N, D, out);
+    const dim3 grid((unsigned)(N / 16 + 1 < 2048 ? N / 16 + 1 : 2048)), block(kBfThreads);
+    const float part = (float)(1.0 - 2.0 * (double)pqt_host::brute_error(elem_bytes, D).row);
+    float* centre = out + centre_at(N);
+    if (elem_bytes == 1) {
+        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, part, out);
+    } else {
+        const float* x = static_cast<const float*>(vectors);
+        hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((D + kWave - 1) / kWave)), block, 0, s, x, N, brute_force_step(N), D, centre);
+        hipLaunchKernelGGL(use_centre_kernel, dim3(1), dim3(1024), 0, s, x, N, brute_force_step(N), D, centre, reinterpret_cast<uint32_t*>(out) + N + 1);
+        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, part, out);
+    }
     return hipGetLastError();
 }
 
@@ -820,12 +977,13 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     BruteArgs a;
     carve(p, k, static_cast<unsigned char*>(workspace), &a);
     a.vectors = vectors; a.xhalf = half_norms; a.N = N; a.D = D; a.k = k; a.KS = p.KS;
+    a.centre = elem_bytes == 4 ? half_norms + centre_at(N) : nullptr;
+    a.use_centre = reinterpret_cast<const uint32_t*>(half_norms) + N + 1;
     a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
-    a.step = (uint64_t)((double)N * 0.6180339887498949) | 1u;
-    while (gcd_u64(a.step, N) != 1) a.step += 2;
+    a.step = brute_force_step(N);
     const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
-    a.err_dot = err.dot;
-    a.err_norm = err.norm;
+    a.err_query = err.query;
+    a.err_row = err.row;
     return elem_bytes == 1 ? run<uint8_t>(p, a, queries, nq, out_ids, out_dists, s) : run<float>(p, a, queries, nq, out_ids, out_dists, s);
 }
 

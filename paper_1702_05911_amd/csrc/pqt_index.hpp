@@ -67,7 +67,7 @@ struct pqt_index {
     const void* vectors = nullptr;
     void* vectors_owned = nullptr;      // set when the library holds its own copy
     int vector_elem_bytes = 0;
-    float* half_norms = nullptr;        // of the attached vectors, and their largest norm (made on first brute-force call)
+    float* half_norms = nullptr;        // of the attached vectors, their largest norm and centre (made on first brute-force call)
     void* bf_ws = nullptr;              // brute-force workspace
     size_t bf_ws_bytes = 0;
     int64_t* ws_short_ids = nullptr;    // nq x k_short results of the line-quantisation re-ranking

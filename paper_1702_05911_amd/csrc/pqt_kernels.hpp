@@ -201,11 +201,13 @@ struct BruteArgs {
     int D, k, KS;                 // KS: steps of 16 dimensions
     const float* queries;         // nq x D
     const void* vectors;          // N x D
-    const float* xhalf;           // ||x||^2 / 2 of every vector, and behind them the largest ||x||
+    const float* xhalf;           // what a vector's values start from, and behind them the largest ||x||
+    const float* centre;          // D: what floats are taken relative to (null for bytes)
+    const uint32_t* use_centre;   // floats: 0 where that is zero
     int64_t* out_ids;             // nq x k
     float* out_dists;             // nq x k
     uint64_t step;                // the database order: place i is vector (i * step) mod N
-    float err_dot, err_norm;      // error bound: err_dot ||q|| X + err_norm X^2, X the largest ||x||
+    float err_query, err_row;     // error bound: err_query ||q||^2 + err_row ||x||^2
     // the current chunk: chunk_rows vectors from place chunk_pos on
     uint64_t chunk_pos;
     int64_t chunk_rows;
@@ -214,7 +216,7 @@ struct BruteArgs {
     uint32_t* flagged;            // nq: 1 = left to the exact scan
     uint32_t* todo;               // those queries
     float* qnorm;                 // ||q||
-    float* edge;                  // upper bound of the k-th smallest value so far
+    float* keep;                  // largest value that still matters
     uint32_t* best_count;         // entries of best
     uint16_t* qfrag;              // queries, two bf16 pieces, operand layout
     float* dense;                 // values of the first chunk, a row per query
@@ -226,7 +228,8 @@ struct BruteArgs {
 };
 // workspace of one call, in bytes
 size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k);
-// half squared norms of the vectors and, behind them, the largest norm: N + 1 floats
+// what the filter needs to know of the vectors, whatever the queries: half squared norms, the largest norm, the centre
+size_t brute_force_norm_words(uint64_t N, int D);
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s);
 // the k nearest of N vectors (4: fp32, 1: uint8 elements) to every query; k <= min(N, 256)
 hipError_t launch_brute_force(const void* vectors, const float* half_norms, int elem_bytes, uint64_t N, int D, const float* queries,

@@ -1074,6 +1074,7 @@ def test_brute_force_keeps_what_the_cut_moves_most(pqt, D):
         step += 2
     last = (N - 1) * step % N
     X = torch.full((N, D), 0.5, device="cuda")                       # (short: the bound grows with the norms)
+    X[::2] = -0.5                                                    # (no common centre)
     X[0] = float(second)
     X[last] = float(near)
     ix = _vectors_only_index(pqt, N, D)
@@ -1105,6 +1106,52 @@ def test_brute_force_tiny_values(pqt, D, scale):
         assert torch.equal(d.double(), true.gather(1, ids) * scale ** 2)
     finally:
         pqt.pqt_index_free(ix)
+
+
+@pytest.mark.parametrize("kind", ["one long vector", "long vectors", "an offset", "a long query", "norms of all sizes"])
+def test_brute_force_whatever_the_norms(pqt, kind):
+    """Norms that differ and coordinates far from zero: the results are right, and they take about as long as on even data
+    (left to the exact scan, which would be right as well, they take more than ten times as long; a factor of four leaves
+    room for a busy machine)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(21)
+    N, D, nq, k = 60_000, 256, 512, 10
+    X = torch.rand((N, D), generator=gen, device="cuda") - 0.5
+    Y = torch.rand((nq, D), generator=gen, device="cuda") - 0.5
+
+    def timed(X, Y):
+        ix = _vectors_only_index(pqt, N, D)
+        try:
+            pqt.pqt_index_set_vectors(ix, X)
+            times = []
+            for _ in range(4):
+                begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                begin.record()
+                ids, d = pqt.pqt_brute_force(ix, Y, k)
+                end.record()
+                end.synchronize()
+                times.append(begin.elapsed_time(end))
+            return min(times[1:]), ids, d
+        finally:
+            pqt.pqt_index_free(ix)
+    even = timed(X, Y)[0]
+    if kind == "one long vector":
+        X[777] *= 300
+    elif kind == "long vectors":
+        X[::500] *= 50
+    elif kind == "an offset":
+        X, Y = X + 15, Y + 15
+    elif kind == "a long query":
+        Y = Y * 100
+    else:
+        X = X * torch.exp(torch.randn((N, 1), generator=gen, device="cuda"))
+    t, ids, d = timed(X, Y)
+    true = torch.cat([((X.double()[None] - y[:, None]) ** 2).sum(2) for y in Y[:40].double().split(4)])
+    bound = (D + 2) * 2.0 ** -24
+    own = true.gather(1, ids[:40])
+    assert (d[:40].double() - own).abs().le(bound * own).all()
+    assert (own - true.sort(1).values[:, :k]).abs().le(2 * bound * own).all()
+    assert t < 4 * even, (t, even)
 
 
 def test_four_part_index(pqt, tmp_path):
