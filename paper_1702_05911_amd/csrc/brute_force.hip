@@ -23,7 +23,8 @@
 //     can still matter; after the last chunk it computes the exact distances sum (y - x)^2 of that list
 //     (k and a few more) in fp32 and sorts them.
 // Chunks grow by a factor, so that about k times that factor pairs pass per chunk and query.  A query whose lists
-// overflow (heavily tied or non-finite data) is searched by bf_scan_kernel, exact distances to all vectors.
+// overflow (more than about two thousand vectors tied with the k-th, or non-finite data) is searched by bf_scan_kernel, exact
+// distances to all vectors.
 //
 // Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 2.9 = 0.88 PFLOP/s, selection 0.49); with
 // the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
@@ -587,7 +588,7 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
 
 constexpr int kSelectBins = 1024;
 
-__host__ __device__ inline int best_capacity(int k) { return 2 * k + 256 < 1024 ? 2 * k + 256 : 1024; }
+constexpr int kBest = 2048;            // entries kept of a query between chunks: the k best and what may tie with them
 
 // One workgroup per query: what is kept of the list so far and of the chunk's new pairs (dense: of the first chunk's
 // values); after the last chunk the exact distances of the kept vectors and the k best of them.
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k;
     const int64_t q = blockIdx.x;
     if (g.flagged[q]) return;
-    unsigned long long* best = g.best + (size_t)q * best_capacity(k);
+    unsigned long long* best = g.best + (size_t)q * kBest;
     if (tid == 0) {
         misc[3] = misc[4] = 0u;
     }
@@ -649,10 +650,10 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         return;
     }
     // ---- an upper bound of the k-th smallest: the end of its bin ---------------------------------------------------
-    // One histogram over the values' range; where a few long vectors stretch the range, so that the bin of the k-th holds more
-    // than may be kept, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
+    // One histogram over the values' range; where a few long vectors stretch the range, so that the bin of the k-th holds many
+    // more, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
     // among those that are divided.
-    const int cap = best_capacity(k);
+    const uint32_t few = (uint32_t)k + 128u;         // entries up to the bin's end that need no division
     auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
     static_assert(kDense <= 32 * kBfThreads, "a bit per entry");
     uint32_t members = 0xffffffffu, below = 0u;
@@ -710,7 +711,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         const int bin = (int)misc[2];
         below = misc[5];
         edge = fminf(hi, lo + (float)(bin + 1) / scale * 1.000002f + 4e-7f * fabsf(lo));
-        if (2u * misc[6] <= (uint32_t)cap) return true;
+        if (misc[6] <= few) return true;
         for (int e = tid, u = 0; e < n; e += kBfThreads, ++u)
             if (bin_of(value(e)) != bin) members &= ~(1u << u);
         return false;
@@ -732,7 +733,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     }
     __syncthreads();
     n = (int)misc[3];
-    if (n > cap) {
+    if (n > kBest) {
         give_up();
         return;
     }
@@ -760,7 +761,8 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         const float d = row_distance(reinterpret_cast<const Elem*>(g.vectors), id, D, reinterpret_cast<const float*>(sy), lpr, l);
         if (e < n && l == 0) keys[e] = ((unsigned long long)mono_key(d) << 32) | (uint32_t)id;
     }
-    block_sort_lds<4>(keys, npad, tid, kBfThreads);
+    if (npad <= 4 * kBfThreads) block_sort_lds<4>(keys, npad, tid, kBfThreads);
+    else block_sort_lds<8>(keys, npad, tid, kBfThreads);
     for (int e = tid; e < k; e += kBfThreads) {
         const unsigned long long key = keys[e];
         g.out_ids[(size_t)q * k + e] = (int64_t)(uint32_t)key;
@@ -769,52 +771,168 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
 }
 
 // The queries the filter gave up on: exact distances to every vector, what beats the k-th best so far is kept in LDS and
-// the k best are selected again whenever that may fill.  One workgroup per query at a time.
-template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void bf_scan_kernel(BruteArgs g) {
+// the k best are selected again whenever that may fill.  A workgroup has QB queries, which share the rows it reads (two at a
+// time in registers: each of the queries' values in LDS is read once for both), and one of `splits` parts of the database, as many
+// as give every workgroup of the launch work; with more than one part bf_merge_kernel joins their results.
+// 2,000 queries that all tie, 1M x 128 bytes: 20.6 ms (one workgroup per query, a row read for one query: 47); one such query:
+// 0.36 ms (20.7).
+constexpr int kScanQueries = 4;
+constexpr int kScanSplits = 256;       // parts of the database at most
+constexpr int kScanKeys = 1024;        // entries a workgroup holds per query: the k best and what is pending
+constexpr int kScanStep = 512;         // rows between two looks at the number of pending entries, at most
+
+constexpr size_t scan_lds(int queries, int D) { return (size_t)queries * (sizeof(unsigned long long) * kScanKeys + sizeof(float) * D) + 64; }
+
+__device__ __forceinline__ uint32_t scan_splits(uint32_t ntodo, uint32_t queries, uint32_t grid, uint64_t N) {
+    const uint32_t blocks = (ntodo + queries - 1) / queries;
+    const uint32_t rows = (uint32_t)((N + kScanStep - 1) / kScanStep);
+    return max(1u, min(min(grid / blocks, (uint32_t)kScanSplits), rows));
+}
+
+template <typename Elem, int QB>
+__global__ __launch_bounds__(kBfThreads, 4) void bf_scan_kernel(BruteArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // kBfScanKeys
-    float4* sy = reinterpret_cast<float4*>(smem + sizeof(unsigned long long) * kBfScanKeys);
-    __shared__ uint32_t pending;
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // [QB][kScanKeys]
+    float* sy = reinterpret_cast<float*>(smem + sizeof(unsigned long long) * QB * kScanKeys);      // [QB][D]
+    __shared__ uint32_t pending[QB];
+    constexpr int kRows = 2;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k, D = g.D;
-    const int lpr = lanes_per_row(D / Piece<Elem>::kElems);
-    const int per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
-    const int per_iter = per_wave * (kBfThreads / kWave);
     const uint32_t ntodo = g.control[kBfTodo];
-    for (uint32_t i = blockIdx.x; i < ntodo; i += gridDim.x) {
-        const int64_t q = g.todo[i];
+    if (ntodo == 0) return;
+    const int npieces = D / Piece<Elem>::kElems, lpr = lanes_per_row(npieces);
+    const int per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
+    const int per_iter = kRows * per_wave * (kBfThreads / kWave), iters = kScanStep / per_iter;      // 4 .. 512 rows, 1 .. 64 of them
+    const uint32_t splits = scan_splits(ntodo, QB, gridDim.x, g.N), blocks = (ntodo + QB - 1) / QB;
+    const Elem* X = reinterpret_cast<const Elem*>(g.vectors);
+    for (uint32_t item = blockIdx.x; item < blocks * splits; item += gridDim.x) {
+        const uint32_t first = item / splits * QB, split = item % splits;
+        const int64_t x_end = (int64_t)(g.N * (split + 1) / splits);
         __syncthreads();
-        for (int c4 = tid; c4 < D / 4; c4 += kBfThreads) sy[c4] = reinterpret_cast<const float4*>(g.queries + (size_t)q * D)[c4];
+        for (int e = tid; e < QB * (D / 4); e += kBfThreads) {
+            const int j = e / (D / 4), c4 = e - j * (D / 4);
+            const int64_t q = g.todo[min(first + (uint32_t)j, ntodo - 1)];     // (past the last query: it once more)
+            reinterpret_cast<float4*>(sy)[e] = reinterpret_cast<const float4*>(g.queries + (size_t)q * D)[c4];
+        }
+        for (int j = 0; j < QB; ++j)
+            for (int e = tid; e < k; e += kBfThreads) keys[j * kScanKeys + e] = ~0ull;
+        if (tid < QB) pending[tid] = 0u;
+        __syncthreads();
+        uint32_t tau[QB];
+#pragma unroll
+        for (int j = 0; j < QB; ++j) tau[j] = 0xffffffffu;
+        for (int64_t x0 = (int64_t)(g.N * split / splits); x0 < x_end; x0 += (int64_t)iters * per_iter) {
+            for (int it = 0; it < iters; ++it) {
+                int64_t row[kRows];
+                const Elem* x[kRows];
+                float acc[kRows][QB];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    row[r] = x0 + it * per_iter + (wave * kRows + r) * per_wave + sub;
+                    x[r] = X + (size_t)(row[r] < x_end ? row[r] : x_end - 1) * D;
+#pragma unroll
+                    for (int j = 0; j < QB; ++j) acc[r][j] = 0.0f;
+                }
+                for (int piece = l; piece < npieces; piece += lpr) {
+                    uint4 raw[kRows];
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r) raw[r] = reinterpret_cast<const uint4*>(x[r])[piece];
+#pragma unroll
+                    for (int j = 0; j < QB; ++j)
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) acc[r][j] = Piece<Elem>::add(raw[r], piece, sy + j * D, acc[r][j]);
+                }
+                for (int off = 1; off < lpr; off <<= 1)
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+                        for (int j = 0; j < QB; ++j) acc[r][j] += __shfl_xor(acc[r][j], off, kWave);
+                // vectors come in id order: an equal distance that arrives later has the larger id and never wins
+#pragma unroll
+                for (int r = 0; r < kRows; ++r)
+#pragma unroll
+                    for (int j = 0; j < QB; ++j) {
+                        const uint32_t kb = mono_key(acc[r][j]);
+                        if (l == 0 && row[r] < x_end && kb < tau[j])
+                            keys[j * kScanKeys + k + atomicAdd(&pending[j], 1u)] = ((unsigned long long)kb << 32) | (uint32_t)row[r];
+                    }
+            }
+            __syncthreads();
+            uint32_t np[QB];
+#pragma unroll
+            for (int j = 0; j < QB; ++j) np[j] = pending[j];
+            __syncthreads();
+            const bool last = x0 + (int64_t)iters * per_iter >= x_end;
+#pragma unroll
+            for (int j = 0; j < QB; ++j) {
+                if (np[j] + (uint32_t)kScanStep <= (uint32_t)(kScanKeys - k) && !last) continue;
+                unsigned long long* own = keys + j * kScanKeys;
+                const int n = k + (int)np[j], npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
+                for (int e = n + tid; e < npad; e += kBfThreads) own[e] = ~0ull;
+                if (tid == 0) pending[j] = 0u;
+                block_sort_lds<4>(own, npad, tid, kBfThreads);
+                tau[j] = (uint32_t)(own[k - 1] >> 32);
+                __syncthreads();
+            }
+        }
+        for (int j = 0; j < QB; ++j) {
+            const uint32_t at = first + (uint32_t)j;
+            if (at >= ntodo) break;
+            const size_t q = g.todo[at];
+            for (int e = tid; e < k; e += kBfThreads) {
+                const unsigned long long key = keys[j * kScanKeys + e];
+                if (splits > 1) {
+                    g.parts[((size_t)at * splits + split) * k + e] = key;
+                } else {
+                    g.out_ids[q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
+                    g.out_dists[q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
+                }
+            }
+        }
+    }
+}
+
+// The k best of the parts of a scanned query.  One workgroup per query at a time.
+constexpr int kMergeKeys = 2048, kMergeStep = 1024;
+__global__ __launch_bounds__(kBfThreads) void bf_merge_kernel(BruteArgs g, int scan_queries, int scan_grid) {
+    __shared__ unsigned long long keys[kMergeKeys];
+    __shared__ uint32_t pending;
+    const int tid = threadIdx.x, k = g.k;
+    const uint32_t ntodo = g.control[kBfTodo];
+    if (ntodo == 0) return;
+    const uint32_t splits = scan_splits(ntodo, (uint32_t)scan_queries, (uint32_t)scan_grid, g.N);
+    if (splits == 1) return;
+    const int total = (int)splits * k;
+    for (uint32_t i = blockIdx.x; i < ntodo; i += gridDim.x) {
+        const unsigned long long* parts = g.parts + (size_t)i * total;
+        __syncthreads();
         for (int e = tid; e < k; e += kBfThreads) keys[e] = ~0ull;
         if (tid == 0) pending = 0u;
         __syncthreads();
-        uint32_t tau = 0xffffffffu;
-        for (int64_t x0 = 0; x0 < (int64_t)g.N; x0 += 4 * per_iter) {
-#pragma unroll 2
-            for (int it = 0; it < 4; ++it) {
-                const int64_t row = x0 + it * per_iter + wave * per_wave + sub;
-                const bool have = row < (int64_t)g.N;
-                const float d = row_distance(reinterpret_cast<const Elem*>(g.vectors), have ? row : -1, D, reinterpret_cast<const float*>(sy), lpr, l);
-                const uint32_t kb = mono_key(d);
-                // vectors come in id order: an equal distance that arrives later has the larger id and never wins
-                if (have && l == 0 && kb < tau) keys[k + atomicAdd(&pending, 1u)] = ((unsigned long long)kb << 32) | (uint32_t)row;
+        unsigned long long tau = ~0ull;
+        for (int e0 = 0; e0 < total; e0 += kMergeStep) {
+#pragma unroll
+            for (int u = 0; u < kMergeStep / kBfThreads; ++u) {
+                const int e = e0 + u * kBfThreads + tid;
+                const unsigned long long key = e < total ? parts[e] : ~0ull;
+                if (key < tau) keys[k + atomicAdd(&pending, 1u)] = key;
             }
             __syncthreads();
             const uint32_t np = pending;
             __syncthreads();
-            if (np + 4u * (uint32_t)per_iter > (uint32_t)(kBfScanKeys - k) || x0 + 4 * per_iter >= (int64_t)g.N) {
+            if (np + (uint32_t)kMergeStep > (uint32_t)(kMergeKeys - k) || e0 + kMergeStep >= total) {
                 const int n = k + (int)np, npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
                 for (int e = n + tid; e < npad; e += kBfThreads) keys[e] = ~0ull;
                 if (tid == 0) pending = 0u;
                 block_sort_lds<8>(keys, npad, tid, kBfThreads);
-                tau = (uint32_t)(keys[k - 1] >> 32);
+                tau = keys[k - 1];
                 __syncthreads();
             }
         }
+        const size_t q = g.todo[i];
         for (int e = tid; e < k; e += kBfThreads) {
             const unsigned long long key = keys[e];
-            g.out_ids[(size_t)q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
-            g.out_dists[(size_t)q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
+            g.out_ids[q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
+            g.out_dists[q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
         }
     }
 }
@@ -840,6 +958,7 @@ struct Plan {
     int64_t batch, batch_pad;        // queries at a time, padded to whole workgroup tiles
     int groups, splits, segs, seg_cap;
     int growth;
+    int scan_queries, scan_grid;     // of the exact scan: queries and workgroups
 };
 
 Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
@@ -861,7 +980,11 @@ Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
     // select workgroup's LDS allows (twice k * growth + the list kept so far).
     const int most = 1600 / k < 2 ? 2 : (1600 / k > 64 ? 64 : 1600 / k);
     p.growth = p.batch * k < 200000 ? most : (most < 4 ? most : 4);
-    p.seg_cap = 4 * ((k * p.growth + p.segs - 1) / p.segs) + 16;
+    // room for the pairs that pass and for the ties that may be kept
+    p.seg_cap = 4 * ((k * p.growth + p.segs - 1) / p.segs) + 16 + kBest / p.segs;
+    p.scan_queries = scan_lds(kScanQueries, D) <= 64 * 1024 ? kScanQueries : 1;
+    const int64_t most_items = (p.batch + p.scan_queries - 1) / p.scan_queries * kScanSplits;
+    p.scan_grid = (int)(most_items < 1024 ? most_items : 1024);
     return p;
 }
 
@@ -888,8 +1011,9 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
     v.dense = c.take<float>((size_t)p.batch_pad * kDense);
     v.seg_count = c.take<uint32_t>((size_t)p.batch_pad * p.segs);
-    v.lists = c.take<uint2>((size_t)p.batch_pad * p.segs * p.seg_cap);
-    v.best = c.take<unsigned long long>((size_t)p.batch_pad * best_capacity(k));
+    v.lists = c.take<uint2>((size_t)p.batch * p.segs * p.seg_cap);
+    v.best = c.take<unsigned long long>((size_t)p.batch * kBest);
+    v.parts = c.take<unsigned long long>((size_t)p.scan_grid * p.scan_queries * k);
     if (a) *a = v;
     return c.used;
 }
@@ -911,12 +1035,9 @@ void launch_filter(const Plan& p, const BruteArgs& a, hipStream_t s) {
 template <typename Elem>
 hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int64_t* out_ids, float* out_dists, hipStream_t s) {
     const size_t select_lds = sizeof(unsigned long long) * kDense + sizeof(float) * a.D;
-    const size_t scan_lds = sizeof(unsigned long long) * kBfScanKeys + sizeof(float) * a.D;
     hipError_t e;
-    if (select_lds + 8192 > 64 * 1024 || scan_lds + 64 > 64 * 1024) {
+    if (select_lds + 8192 > 64 * 1024)
         if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(bf_select_kernel<Elem>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)select_lds)) != hipSuccess) return e;
-        if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(bf_scan_kernel<Elem>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)scan_lds)) != hipSuccess) return e;
-    }
     for (int64_t b0 = 0; b0 < nq; b0 += p.batch) {
         a.nq = nq - b0 < p.batch ? nq - b0 : p.batch;
         a.queries = queries + (size_t)b0 * a.D;
@@ -935,7 +1056,10 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
             pos += rows;
             hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, pos >= a.N ? 1 : 0);
         }
-        hipLaunchKernelGGL((bf_scan_kernel<Elem>), dim3((unsigned)(a.nq < 1024 ? a.nq : 1024)), dim3(kBfThreads), scan_lds, s, a);
+        const dim3 scan((unsigned)p.scan_grid), merge((unsigned)(a.nq < 256 ? a.nq : 256)), block(kBfThreads);
+        if (p.scan_queries == 1) hipLaunchKernelGGL((bf_scan_kernel<Elem, 1>), scan, block, scan_lds(1, a.D), s, a);
+        else hipLaunchKernelGGL((bf_scan_kernel<Elem, kScanQueries>), scan, block, scan_lds(kScanQueries, a.D), s, a);
+        hipLaunchKernelGGL(bf_merge_kernel, merge, block, 0, s, a, p.scan_queries, p.scan_grid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

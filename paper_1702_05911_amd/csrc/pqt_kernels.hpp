@@ -194,7 +194,6 @@ hipError_t launch_exact_rerank(const ExactArgs& a, hipStream_t s);
 enum { kBfSecond = 0,          // a query has a second bf16 piece
        kBfTodo = 1,            // queries in todo[]
        kBfControl = 64 };
-constexpr int kBfScanKeys = 2048;   // entries a scanning workgroup holds: the k best and what is pending
 struct BruteArgs {
     int64_t nq;                   // queries of the batch
     uint64_t N;
@@ -225,6 +224,7 @@ struct BruteArgs {
     uint32_t* seg_count;          // nq x segs: pairs that passed (may exceed seg_cap: overflow)
     uint2* lists;                 // nq x segs x seg_cap: (row of the chunk, value)
     unsigned long long* best;     // what is kept between chunks
+    unsigned long long* parts;    // the exact scan's results of every part of the database
 };
 // workspace of one call, in bytes
 size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k);

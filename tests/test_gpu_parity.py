@@ -1154,6 +1154,51 @@ def test_brute_force_whatever_the_norms(pqt, kind):
     assert t < 4 * even, (t, even)
 
 
+@pytest.mark.parametrize("stored, N, D, nq, k, same", [
+    ("f32", 60_000, 64, 300, 10, 1000),    # more ties than results, kept to the end
+    ("u8", 60_000, 128, 300, 100, 2000),
+    ("u8", 60_000, 96, 300, 256, 20_000),  # more than are kept: the exact scan, a part of the database a workgroup
+    ("f32", 60_000, 20, 1, 7, 60_000),     # one query, all tied
+    ("f32", 700, 2048, 3, 200, 700),       # rows of which the scan holds one query at a time
+    ("u8", 4500, 16, 5000, 3, 4500),       # more queries than the scan has workgroups
+])
+def test_brute_force_ties(pqt, stored, N, D, nq, k, same):
+    """Groups of equal vectors spread over the database: the smallest ids win, and queries near such a group take at most ten
+    times as long as others (measured: 1.5 to 3.6 times; scanned by one workgroup per query 12 to 30 times)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda").float()
+    Y = torch.randint(0, 256, (nq, D), generator=gen, device="cuda").float()
+
+    def timed(X, Y):
+        ix = _vectors_only_index(pqt, N, D)
+        try:
+            pqt.pqt_index_set_vectors(ix, X.to(torch.uint8) if stored == "u8" else X)
+            times = []
+            for _ in range(4):
+                begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                begin.record()
+                ids, d = pqt.pqt_brute_force(ix, Y, k)
+                end.record()
+                end.synchronize()
+                times.append(begin.elapsed_time(end))
+            return min(times[1:]), ids, d
+        finally:
+            pqt.pqt_index_free(ix)
+    even = timed(X, Y)[0]
+    group = torch.randperm(N, generator=gen, device="cuda")[:same]
+    X[group] = X[group[0]].clone()
+    Y[::2] = X[group[0]] + (torch.rand((len(Y[::2]), D), generator=gen, device="cuda") < 0.1).float()
+    t, ids, d = timed(X, Y)
+    for q in range(0, nq, max(1, nq // 50)):
+        true = ((X.double() - Y[q].double()) ** 2).sum(1)             # whole numbers: exact in any order
+        want = (true * N + torch.arange(N, device="cuda")).sort().indices[:k]
+        assert torch.equal(ids[q], want) and torch.equal(d[q].double(), true[want]), q
+    print(f"{t:.3f} ms, without ties {even:.3f} ms", flush=True)
+    if nq < 1000:
+        assert t < 10 * even, (t, even)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
