@@ -121,12 +121,17 @@ int rerank_runs_in_lds(const pqt_index* ix) {
 // 0.1 at 96, 0.03 at 64 and 0.005 at 48.  Measured (us a batch, with the head pass and without): 4,000 queries at 80: 100
 // and 129, at 110: 149 and 131; 1,500 at 33: 56 and 68, at 50: 83 and 73; 300 at 33: 46 and 54, at 50: 65 and 55; 16 at 67: 45 and
 // 34; one query at 67: 22 and 29 if it finishes, 41 and 30 if not.  Far above: 3,000 queries at 655: 307 and 182.
-double headless_from(int64_t nq) {
+// More than 2,048 tuples take workgroups of 512 threads, two per compute unit, so that batches of more than two rounds of those
+// gain by the head pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at
+// 67: 85 and 114, at 90: 109 and 131; T = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536.
+double headless_from(int64_t nq, uint32_t T) {
     if (nq < 4) return 160.0;
     if (nq < 16) return 96.0;
     if (nq < 96) return 64.0;
+    if (T > 2048 && nq > 1024) return nq <= 2048 ? 96.0 : 160.0;
     return nq <= 2048 ? 48.0 : 96.0;
 }
+constexpr double kThirdLevelFrom = 72.0;     // the same mean, for the head pass's 128 tuples (see launch_rank)
 
 // Can the re-rank kernel also run the full bin ranking of the queries the head pass leaves over?
 // (two tree parts; few enough tuples per thread of the re-rank workgroup; the LDS of both fits)
@@ -611,11 +616,12 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     // Two parts: tuples whose lists would fill the budget if every slot were as long as the mean one (near a query they are
     // longer: about 0.4 times as many do).  The full ranking tries twice as many first, all T if those do not fill it.
     const double mean_need = ix->N ? (double)ix->C * (double)ix->H / (double)ix->N : 0.0;
+    ra.third_level = mean_need >= kThirdLevelFrom ? 1 : 0;
     ra.t_mid = pqt::kMidT;
     while (ra.t_mid < (int)ix->T && ra.t_mid < 2.0 * mean_need) ra.t_mid *= 2;
     // The head pass is left out where it would leave much to do: every query is then ranked by a workgroup of its own in
     // a kernel of its own, by placing, which the re-rank kernel has no registers for.
-    if (mean_need >= headless_from(nq)) ra.order = nullptr;
+    if (mean_need >= headless_from(nq, ix->T)) ra.order = nullptr;
     ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
     const bool rerank_taps = tp.n_cand || tp.cand_ids || tp.scores || tp.lut || tp.n_slots;
     const bool head = !fixed_order && pqt::rank_has_head(ra);

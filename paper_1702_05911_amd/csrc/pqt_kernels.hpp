@@ -11,8 +11,8 @@ namespace pqt {
 constexpr int kQueryTile = 16;          // queries per workgroup of the traversal kernel (MFMA rows)
 constexpr int kTraverseMaxThreads = 1024; // workgroup size grows with the number of tree parts
 constexpr int kRankThreads = 1024;        // full ranking pass: one workgroup per query
-constexpr int kRankFewQueries = 512;     // up to two queries per compute unit
-constexpr int kRankThreadsFourParts = 512;  // the same for four tree parts (up to 4096 tuples)
+constexpr int kRankFewQueries = 256;     // one query per compute unit
+constexpr int kRankThreadsHalf = 512;    // four tree parts (up to 4096 tuples), two with more than 2048
 constexpr int kRankHeadThreads = 256;     // head pass: one wavefront per query
 constexpr size_t kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
 
@@ -79,6 +79,7 @@ struct RankArgs {
     int64_t nq;
     int P, R, T, C;
     int t_mid;                // two parts: tuples the full ranking tries first (all T only if those do not fill C)
+    int third_level;          // two parts: the head pass tries 128 tuples before it leaves a query to a full pass of its own launch
     uint32_t k1k2;
     uint64_t H;
     uint64_t H_inv;           // floor(2^64 / H) for H >= 2 (slot_of_bin divides by multiplying), else 0

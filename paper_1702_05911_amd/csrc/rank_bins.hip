@@ -7,9 +7,9 @@
 // The first T tuples of the order (sum, r1, r2) are found without a priority queue: a pair
 // (r1, r2) can only be among the first T if (r1+1)(r2+1) <= T, because every pair that is
 // component-wise smaller precedes it.  Only that hyperbolic region (about T ln T pairs) is ever
-// evaluated.  A head pass (one wavefront per query) ranks the first 32, then 64, then 128 tuples and
-// stops as soon as the candidate budget is filled, which it is for nearly every query; the full pass
-// handles the rest: if the region fits the sort buffer it is sorted directly, otherwise the T-th
+// evaluated.  A head pass (one wavefront per query) ranks the first 32, then 64 tuples (then 128, where the
+// rest gets a launch of its own and is large) and stops as soon as the candidate budget is filled, which it is for nearly every
+// query of a dense index (a sparse one skips it); the full pass handles the rest: if the region fits the sort buffer it is sorted directly, otherwise the T-th
 // smallest key is located by a histogram over the key range (keys recomputed on the fly, never
 // stored; an exact radix select when the keys tie heavily) and only the T smallest are collected
 // and sorted.
@@ -114,11 +114,13 @@ __global__ __launch_bounds__(kRankHeadThreads) void rank_head_kernel(RankArgs g,
 // ------------------------------------------------------------------------------------------------
 
 // MAXPER: tuples a thread may have to hold (T <= MAXPER * the workgroup).  The pass is a chain of dependent
-// steps with many barriers, which other resident queries hide: the variants for at most four tuples get 80 registers (two
-// parts: 64 were 3 to 8 % slower, the ranking spilled in its hot loops), six wavefronts a SIMD.
+// steps with many barriers, which other resident queries hide: the variants for at most four tuples get 80 registers, six
+// wavefronts a SIMD (two parts with 64: 3 to 8 % slower in workgroups of 256 and 512 threads, the ranking spilled in its hot
+// loops).  Two parts with up to eight tuples: 128 registers for 512 threads (80: 10 to 17 % slower, T = 2500, 1,000 to 6,000
+// queries).
 // PF: the number of tree parts when it is compiled in (2, 4), 0: read from the arguments.
 template <int MAXPER, int PF = 0, int MODE = kRankPlace>
-__global__ __launch_bounds__(PF == 4 && MAXPER <= 4 ? kRankThreadsFourParts : kRankThreads,
+__global__ __launch_bounds__((PF == 4 && MAXPER <= 4) || (PF == 2 && MAXPER > 4) ? kRankThreadsHalf : kRankThreads,
                              MAXPER > 4 ? 4 : (PF == 0 ? 8 : 6)) void rank_kernel(RankArgs g, RankOffsets L) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t count = L.all ? (uint32_t)g.nq : g.counters[0];
@@ -241,10 +243,14 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
             lv.T1[l] = o.Tcap < t ? o.Tcap : t;
             lv.npairs[l] = head_pair_count(lv.T1[l]);
         }
-        // what 64 tuples leave over goes to a workgroup per query: the third level, one long chain of dependent steps
-        // in a single wavefront for a few queries, would only set the duration of this kernel
-        lv.T1[2] = lv.T1[1];
-        lv.npairs[2] = lv.npairs[1];
+        // What 64 tuples leave over goes to a workgroup per query; 128 are tried first where much is left over and that
+        // workgroup is launched apart.  Else the third level, one long chain of dependent steps in a single wavefront for a few
+        // queries, would only set the duration of this kernel.  With two and with three levels, T = 2500: 3,000 queries that
+        // need 67 tuples on average 97 and 107 us, 10,000 of them 198 and 189; 3,000 that need 90 141 and 127, 10,000 338 and 259.
+        if (defer_full || !a.third_level) {
+            lv.T1[2] = lv.T1[1];
+            lv.npairs[2] = lv.npairs[1];
+        }
         hipLaunchKernelGGL(rank_head_kernel, dim3((unsigned)((a.nq + per - 1) / per)), dim3(kRankHeadThreads), 0, s, a,
                            o.Tcap, lv);
         hipError_t e = hipGetLastError();
@@ -255,18 +261,24 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full) {
     // unit works on at once: workgroups of 512 threads (their LDS lets three share a compute unit, which is
     // also what the kernel's register budget is set for) as long as a thread then holds at most eight tuples.
     if (a.P == 4) {
-        const int threads = o.Tcap <= 8 * kRankThreadsFourParts ? kRankThreadsFourParts : kRankThreads;
-        if (o.Tcap <= 4 * kRankThreadsFourParts)
+        const int threads = o.Tcap <= 8 * kRankThreadsHalf ? kRankThreadsHalf : kRankThreads;
+        if (o.Tcap <= 4 * kRankThreadsHalf)
             hipLaunchKernelGGL((rank_kernel<4, 4>), dim3(grid), dim3(threads), o.total, s, a, o);
         else
             hipLaunchKernelGGL((rank_kernel<8, 4>), dim3(grid), dim3(threads), o.total, s, a, o);
     } else {
-        // A batch that fills the chip takes the smallest workgroups that hold the tuples (four a thread): more queries
-        // per compute unit hide each other's barriers; a few queries take the largest and are answered sooner.
+        // A batch that fills the chip takes the smallest workgroups that hold the tuples (four a thread; more than 2,048
+        // of two parts eight): more queries per compute unit hide each other's barriers.  A few queries take the largest and
+        // are answered sooner: as many as run at once, one per compute unit of the kernel for two parts (by its registers), two
+        // of the other.  512 queries, T = 1024: 67 us in workgroups of 1,024 threads, which run in two rounds, 51 of 256; 2,040
+        // queries, T = 2500: 158 us of 1,024 threads, 114 of 512.
+        const bool few = a.nq <= (a.P == 2 ? kRankFewQueries : 2 * kRankFewQueries);
         int threads = kRankThreads;
-        if (a.nq > kRankFewQueries)
+        if (!few)
             while (threads > 256 && o.Tcap <= 2 * threads) threads /= 2;
         if (o.Tcap > 4 * kRankThreads) hipLaunchKernelGGL(rank_kernel<8>, dim3(grid), dim3(threads), o.total, s, a, o);
+        else if (a.P == 2 && !few && o.Tcap > 4 * kRankThreadsHalf)
+            hipLaunchKernelGGL((rank_kernel<8, 2>), dim3(grid), dim3(kRankThreadsHalf), o.total, s, a, o);
         else if (a.P == 2) hipLaunchKernelGGL((rank_kernel<4, 2>), dim3(grid), dim3(threads), o.total, s, a, o);
         else hipLaunchKernelGGL(rank_kernel<4>, dim3(grid), dim3(threads), o.total, s, a, o);
     }
@@ -278,6 +290,9 @@ hipError_t configure_rank(size_t max_dynamic_lds) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dynamic_lds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<4, 2>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)max_dynamic_lds);
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<8, 2>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)max_dynamic_lds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(rank_kernel<4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -527,6 +527,26 @@ def test_ranking_routes_agree(pqt, C, H):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("T", [1500, 2500, 6000])
+@pytest.mark.parametrize("H, budgets", [(None, (20, 26, 40, 100)), (4099, (150, 240, 400, 900))])
+def test_ranking_routes_agree_for_long_lists(pqt, H, budgets, T):
+    """As above with more than 1,024 tuples, which no re-rank workgroup ranks: every workgroup size of the full pass, with and
+    without a head pass of two and of three levels (the budgets stand for mean numbers of needed tuples on both sides of
+    each line)."""
+    import torch
+    ix, X = _whole_number_index(pqt, 12_000, 16, 2, 16, 12, 4, H=H, T=T, C=1000)
+    try:
+        for C in budgets:
+            pqt.pqt_set_budget(ix, T, C)
+            for nq in (1, 256, 257, 512, 513, 1025, 2049):
+                Y = X[:nq] + 0.25
+                ids, d, _ = pqt.pqt_query_batch_debug(ix, Y, min(C, 20), 8, taps=("n_tuples",))
+                pid, pd = pqt.pqt_query_batch(ix, Y, min(C, 20), 8)
+                assert torch.equal(ids, pid) and torch.equal(d, pd), (C, nq)
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 @pytest.mark.parametrize("D, stored, k_short, k, distinct", [
     (16, "u8", 1, 1, 0),                   # a row is one piece: 64 rows per wavefront
     (48, "u8", 1000, 100, 0),              # three pieces: one lane of four idle
