@@ -5,12 +5,15 @@
 // distance.  The contraction runs on the bf16 matrix cores, eight times the flops of the fp32 ones: a number is
 // cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly, queries of bytes too.
 // With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), the sum of the matrix cores is within
-// a ||q||^2 + b ||x||^2 of s: dropped piece products, the rounding of the sums, and the norm (see pqt_host::brute_error).
-// The filter's value v is that sum less b ||x||^2 (it starts from the norm), so that v <= s + a ||q||^2: the length of one
-// vector widens nothing for the others.  The other way round v >= s - a ||q||^2 - 2 b ||x||^2, and a vector near the query
-// is at most ||q|| + its distance long, so an upper bound of the k-th smallest v gives one of the k-th smallest s, and
-// from that what v may be at most for every vector of the true result (keep_up_to).  Floats are taken relative to
-// a centre where they have one, the median of 64 of them in every dimension: a common offset would count as length.  So
+// a ||q|| ||x|| + b ||x||^2 of s: dropped piece products, the rounding of the sums, and the norm (see pqt_host::brute_error).
+// 2 ||q|| ||x|| <= ||q||^2 + ||x||^2 parts that, and the filter's value v is the sum less the vector's part (it starts from the
+// norm), so that v <= s + a ||q||^2 / 2: the length of one vector widens nothing for the others.  The other way round v is
+// at least s less the query's and twice the vector's part, and a vector near the query is at most ||q|| + its
+// distance long, so an upper bound of the k-th smallest v gives one of the k-th smallest s, and from that what v may be at
+// most for every vector of the true result (keep_up_to).
+// Floats often have a common offset, which would count as length: norms and queries are taken relative to a centre c, the
+// median of 64 vectors in every dimension.  (q - c).(x - c) differs from (q - c).x by a number that is the same for all
+// vectors, so the vectors need not be changed; where the offset is large they are all the same, in registers.  So
 //   * the database is walked in chunks, in the order i -> (i * step) mod N with step / N near the golden ratio: every
 //     prefix of the order is spread evenly over the database, whatever order the vectors are stored in;
 //   * bf_filter_*_kernel contracts a chunk with all queries.  Vectors go from memory through registers, where they are
@@ -54,13 +57,7 @@ __device__ __forceinline__ v16f mfma(bf16x8 a, bf16x8 b, v16f c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16v8, a), __builtin_bit_cast(bf16v8, b), c, 0, 0, 0);
 }
 
-__global__ void fill_word_kernel(uint32_t* out, uint32_t value) { *out = value; }
-
-__global__ void bf_begin_kernel(BruteArgs g) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kBfControl) g.control[i] = 0u;
-    if (i < g.nq) g.flagged[i] = 0u;
-}
+__global__ void clear_words_kernel(uint32_t* out) { out[threadIdx.x] = 0u; }
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {      // two floats to bf16, nearest even
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -71,18 +68,25 @@ __device__ __forceinline__ float low_value(uint32_t pair) { return __uint_as_flo
 __device__ __forceinline__ float high_value(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
 // Queries -> fragments of two pieces (h, then m): one workgroup per tile of 32 queries, its wavefronts share the steps of
-// 16 dimensions; lane l holds query l % 32, dimensions 8 * (l / 32) .. + 8 of a step.  Also ||q||, and control[kBfSecond]
-// is set when a query has a second piece that is not zero.
-__global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
-    __shared__ float red[kBfThreads / kWave][32];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, D = g.D, KS = g.KS;
+// 16 dimensions (16 of them where there are many steps); lane l holds query l % 32, dimensions 8 * (l / 32) .. + 8 of a step.
+// Also ||q||, whether a query of the tile has a second piece that is not zero, and the state of the call: no query is left to
+// the exact scan.
+__global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
+    __shared__ float red[2][1024 / kWave][32];
+    __shared__ uint32_t any_second;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, nwaves = (int)blockDim.x / kWave, D = g.D, KS = g.KS;
+    if (tid == 0) {
+        any_second = 0u;
+        if (blockIdx.x == 0) g.control[kBfTodo] = 0u;
+    }
+    __syncthreads();
     const int64_t tile = blockIdx.x, q = tile * 32 + (lane & 31);
     const bool have = q < g.nq;
     const float* row = g.queries + (have ? (size_t)q * D : 0);
-    float norm = 0.0f;
+    float norm = 0.0f, shift = 0.0f;
     uint32_t second = 0;
 #pragma unroll 4
-    for (int ks = wave; ks < KS; ks += kBfThreads / kWave) {
+    for (int ks = wave; ks < KS; ks += nwaves) {
         const int d = have ? ks * 16 + 8 * (lane >> 5) : D;               // D is a multiple of four
         const float4 z = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         const float4 v0 = d < D ? *reinterpret_cast<const float4*>(row + d) : z;
@@ -93,6 +97,8 @@ __global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
             const float4 c1 = d + 4 < D ? *reinterpret_cast<const float4*>(g.centre + d + 4) : z;
             v[0] -= c0.x; v[1] -= c0.y; v[2] -= c0.z; v[3] -= c0.w;
             v[4] -= c1.x; v[5] -= c1.y; v[6] -= c1.z; v[7] -= c1.w;
+            shift = fmaf(v[0], c0.x, fmaf(v[1], c0.y, fmaf(v[2], c0.z, fmaf(v[3], c0.w, shift))));
+            shift = fmaf(v[4], c1.x, fmaf(v[5], c1.y, fmaf(v[6], c1.z, fmaf(v[7], c1.w, shift))));
         }
         u32x4 h, m;
 #pragma unroll
@@ -107,15 +113,24 @@ __global__ __launch_bounds__(kBfThreads) void pack_queries_kernel(BruteArgs g) {
         out[kFrag / 8] = m;
     }
     norm += __shfl_xor(norm, 32, kWave);
-    if (lane < 32) red[wave][lane] = norm;
+    shift += __shfl_xor(shift, 32, kWave);
+    if (lane < 32) {
+        red[0][wave][lane] = norm;
+        red[1][wave][lane] = shift;
+    }
+    if (__any(second != 0) && lane == 0) any_second = 1u;
     __syncthreads();
     if (tid < 32) {
-        float n2 = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kBfThreads / kWave; ++w) n2 += red[w][tid];
+        float n2 = 0.0f, c = 0.0f;
+        for (int w = 0; w < nwaves; ++w) {
+            n2 += red[0][w][tid];
+            c += red[1][w][tid];
+        }
         g.qnorm[q] = sqrtf(n2);
+        g.qshift[q] = g.use_centre[0] ? 0.0f : c;
+        g.flagged[q] = 0u;
     }
-    if (__any(second != 0) && lane == 0) g.control[kBfSecond] = 1u;
+    if (tid == 0) g.second[tile] = any_second;
 }
 
 // The centre of float vectors: in every dimension the median of 64 vectors spread over the database (places 0 .. 63 of the
@@ -148,13 +163,16 @@ __global__ __launch_bounds__(kBfThreads) void centre_kernel(const float* x, uint
         if (below[u] == kCentreRows / 2 && d < D) centre[d] = fabsf(mine[u]) < 1e18f ? mine[u] : 0.0f;
 }
 
-// The centre is used (*use = 1) where it halves the norms of most of these vectors: 48 of the 64.  Else it becomes zero, and
-// the filter need not subtract it (777 x 150,001 x 960: 810 us, subtracting in every step 888).  One workgroup.
-__global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64_t N, uint64_t step, int D, float* centre, uint32_t* use) {
-    __shared__ uint32_t halved;
+// How the centre is used, from the norms of the same vectors with and without it: not at all (it becomes zero) unless it takes
+// two thirds off the squared norms of most of them, 48 of the 64; subtracted from the vectors too (*use = 1) where
+// it takes 24 of 25 parts off, which costs the contraction 10 to 15 % (in small batches more), and otherwise the values'
+// window grows with the centre's norm (*mu).  One workgroup.
+__global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64_t N, uint64_t step, int D, float* centre, uint32_t* use, float* mu) {
+    __shared__ uint32_t shorter[2];
+    __shared__ float square[1024 / kWave];
     constexpr int kWaves = 1024 / kWave, kPer = kCentreRows / kWaves;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (threadIdx.x == 0) halved = 0u;
+    if (threadIdx.x < 2) shorter[threadIdx.x] = 0u;
     __syncthreads();
     const float* row[kPer];
     float with[kPer], without[kPer];
@@ -179,28 +197,40 @@ __global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64
             with[u] += __shfl_xor(with[u], off, kWave);
             without[u] += __shfl_xor(without[u], off, kWave);
         }
-        if (lane == 0 && 4.0f * with[u] < without[u]) atomicAdd(&halved, 1u);
+        if (lane == 0 && 3.0f * with[u] < without[u]) atomicAdd(&shorter[0], 1u);
+        if (lane == 0 && 25.0f * with[u] < without[u]) atomicAdd(&shorter[1], 1u);
     }
+    float own = 0.0f;
+    for (int d = threadIdx.x; d < D; d += 1024) own = fmaf(centre[d], centre[d], own);
+    for (int off = 1; off < kWave; off <<= 1) own += __shfl_xor(own, off, kWave);
+    if (lane == 0) square[wave] = own;
     __syncthreads();
-    const bool yes = halved >= kCentreRows * 3 / 4;
-    if (!yes)
+    const bool any = shorter[0] >= kCentreRows * 3 / 4, all = shorter[1] >= kCentreRows * 3 / 4;
+    if (!any)
         for (int d = threadIdx.x; d < D; d += 1024) centre[d] = 0.0f;
-    if (threadIdx.x == 0) *use = yes ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        float sum = 0.0f;
+        for (int w = 0; w < kWaves; ++w) sum += square[w];
+        *use = any && all ? 1u : 0u;
+        *mu = any && !all ? 1.001f * sqrtf(sum) : 0.0f;
+    }
 }
 
-// What the accumulators start from, `part` (1 - 2 b) of the half squared norms of the database vectors, and, in the word behind
-// them, the bits of the largest norm (a little enlarged; never negative, so bits order as values).  A group of lanes per
-// row, 16 bytes per lane and step.
+// What the accumulators start from, the half squared norms of the database vectors less their part of the error bound, and, in the
+// word behind them, the bits of the largest norm (a little enlarged; never negative, so bits order as values).  A group of
+// lanes per row, 16 bytes per lane and step.
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float part, float* out) {
+__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float err_dot, float err_norm, float* out) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     constexpr int pe = 16 / (int)sizeof(Elem);
     const int npieces = D / pe, lpr = lanes_per_row(npieces), per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
     const int64_t nwaves = (int64_t)gridDim.x * (kBfThreads / kWave);
     float top = 0.0f;
+    bool as_they_are = false;                  // the filter's products are with vectors that are not centred
+    if constexpr (sizeof(Elem) == 4) as_they_are = out[n + 2] != 0.0f;
     for (int64_t r0 = ((int64_t)blockIdx.x * (kBfThreads / kWave) + wave) * per_wave; r0 < n; r0 += nwaves * per_wave) {
         const int64_t r = r0 + sub;
-        float s = 0.0f;
+        float s = 0.0f, raw = 0.0f;
         if (r < n) {
 #pragma unroll 4
             for (int piece = l; piece < npieces; piece += lpr) {
@@ -212,6 +242,7 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
                     if constexpr (sizeof(Elem) == 4) {
                         const float v = __uint_as_float(w[j]) - __uint_as_float(c[j]);
                         s = fmaf(v, v, s);
+                        raw = fmaf(__uint_as_float(w[j]), __uint_as_float(w[j]), raw);
                     } else {
 #pragma unroll
                         for (int b = 0; b < 4; ++b) {
@@ -222,8 +253,11 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
                 }
             }
         }
-        for (int off = 1; off < lpr; off <<= 1) s += __shfl_xor(s, off, kWave);
-        if (r < n && l == 0) out[r] = part * (0.5f * s);
+        for (int off = 1; off < lpr; off <<= 1) {
+            s += __shfl_xor(s, off, kWave);
+            if constexpr (sizeof(Elem) == 4) raw += __shfl_xor(raw, off, kWave);
+        }
+        if (r < n && l == 0) out[r] = (0.5f - err_norm) * s - 0.5f * err_dot * (as_they_are ? raw : s);
         top = fmaxf(top, r < n ? s : 0.0f);
         if (r < n && s != s) top = __builtin_inff();
     }
@@ -240,15 +274,22 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
 }
 
 // What the value of a vector of the true result may be at most, when k vectors seen have values of at most v.
-// With `own` for a ||q||^2 the k-th smallest s is at most v + own + 2 b r^2, r the largest norm that a vector with value v
-// can have: from s >= r^2 / 2 - qn r follows (1 - 4 b) r^2 / 2 - qn r <= v + own.  A query longer than all vectors has the
-// tighter 2 a ||q|| X, X the largest norm.  0.1 % on r and 3 % on the sum for the rounding here.
-__device__ __forceinline__ float keep_up_to(const BruteArgs& g, float qn, float v) {
-    const float top = g.xhalf[g.N];
-    const float own = g.err_query * qn * fminf(qn, 2.0f * top) + pqt_host::kBruteUnderflow;
-    const float slim = 1.0f - 4.0f * g.err_row;
-    const float r = fminf(top, 1.001f * (qn + sqrtf(fmaxf(qn * qn + 2.0f * slim * (v + own), 0.0f))) / slim);
-    return v + 1.03f * (2.0f * own + 2.0f * g.err_row * r * r);
+// Norms are relative to the centre; mu, the norm of the centre, joins them where products are with vectors as they are, and
+// `shift` = (q - c).c turns a value into one of centred vectors.  The k-th smallest s is at most v + own + e(r), `own` the query's
+// part, e(r) twice the part of a vector of norm r, r the largest norm that a vector with value v can have: s >= r^2 / 2 - qn r
+// gives r <= qn + sqrt(qn^2 + 2 (v + shift + own + e(r))), which is applied again and again from the largest norm of all.
+// A query longer than all vectors has the tighter a ||q|| X for its part, X the largest norm.  0.1 % on r and 3 % on the sum for
+// the rounding here.
+__device__ __forceinline__ float keep_up_to(const BruteArgs& g, float qn, float shift, float v) {
+    const float top = g.xhalf[g.N], mu = g.xhalf[g.N + 2];
+    const float own = 0.5f * g.err_dot * qn * fminf(qn, 2.0f * (top + mu)) + pqt_host::kBruteUnderflow;
+    float r = top, e = 0.0f;
+    for (int i = 0; i < 6; ++i) {
+        e = g.err_dot * (r + mu) * (r + mu) + 2.0f * g.err_norm * r * r;
+        const float t = qn * qn + 2.0f * (v + shift + own + e + g.err_dot * qn * mu);
+        r = fminf(r, 1.001f * (qn + sqrtf(fmaxf(t, 0.0f))));
+    }
+    return v + 1.03f * (2.0f * own + e);
 }
 
 // -keep_up_to of a query: what an accumulator has to reach to be kept
@@ -303,7 +344,6 @@ __device__ __forceinline__ void place_of_workgroup(int b, int splits, int groups
 // and would all hit the same banks.
 template <int KS, int QP, bool DENSE>
 __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(BruteArgs g) {
-    if ((QP == 2) != (g.control[kBfSecond] != 0u)) return;         // the launch of the other number of pieces has this work
     __shared__ __align__(16) uint16_t xs[2][kStatRows / 32 * KS * kFrag];
     __shared__ __align__(16) float hs[2][kStatRows];
     constexpr int kPieces = (kStatRows * KS + kBfThreads - 1) / kBfThreads;    // 16-byte pieces of a tile per thread
@@ -311,6 +351,10 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
     const int splits = g.splits;
     int split, group;
     place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
+    uint32_t second = 0;
+#pragma unroll
+    for (int tile = 0; tile < 8; ++tile) second |= g.second[group * 8 + tile];
+    if ((QP == 2) != (second != 0u)) return;                       // the launch of the other number of pieces has this work
     const int64_t q0 = (int64_t)group * 256 + wave * 64;
     bf16x8 bq[QP][2][KS];
     float from[2];
@@ -617,7 +661,18 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     if (dense) {
         n = (int)g.chunk_rows;
         const float* row = g.dense + (size_t)q * kDense;
-        for (int e = tid; e < n; e += kBfThreads) keys[e] = ((unsigned long long)__float_as_uint(row[e]) << 32) | (uint32_t)e;
+        constexpr int kPer = kDense / 4 / kBfThreads;                            // 16 bytes at a time, all asked for at once
+        float4 v[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) v[u] = reinterpret_cast<const float4*>(row)[4 * (tid + u * kBfThreads) < n ? tid + u * kBfThreads : 0];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int e = 4 * (tid + u * kBfThreads);
+            const float w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (e + c < n) keys[e + c] = ((unsigned long long)__float_as_uint(w[c]) << 32) | (uint32_t)(e + c);
+        }
     } else {
         const int nb = (int)g.best_count[q];
         for (int e = tid; e < nb; e += kBfThreads) keys[e] = best[e];
@@ -718,7 +773,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     };
     bool done = divide(std::true_type{});
     for (int level = 0; level < 3 && !done; ++level) done = divide(std::false_type{});
-    const float keep = keep_up_to(g, qn, edge);
+    const float keep = keep_up_to(g, qn, g.qshift[q], edge);
     // ---- keep what can still be among the k nearest ---------------------------------------------------------------
     for (int e0 = 0; e0 < n; e0 += kBfThreads) {     // in place: entry e moves to a place <= e that has been read
         const int e = e0 + tid;
@@ -754,12 +809,35 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     __syncthreads();
     const int lpr = lanes_per_row(D / Piece<Elem>::kElems);
     const int per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
-#pragma unroll 2
-    for (int e0 = 0; e0 < n; e0 += per_wave * (kBfThreads / kWave)) {
-        const int e = e0 + wave * per_wave + sub;
-        const int64_t id = e < n ? (int64_t)(((uint64_t)(uint32_t)keys[e] * g.step) % g.N) : -1;
-        const float d = row_distance(reinterpret_cast<const Elem*>(g.vectors), id, D, reinterpret_cast<const float*>(sy), lpr, l);
-        if (e < n && l == 0) keys[e] = ((unsigned long long)mono_key(d) << 32) | (uint32_t)id;
+    // (four rows on their way, as in the exact re-ranking; a row past the end is the group's first once more)
+    constexpr int kRows = 4;
+    const int npieces = D / Piece<Elem>::kElems, rows_per_iter = per_wave * (kBfThreads / kWave);
+    const float* y = reinterpret_cast<const float*>(sy);
+    for (int e0 = wave * per_wave + sub; e0 < n; e0 += kRows * rows_per_iter) {
+        const uint4* x[kRows];
+        uint32_t id[kRows];
+        float acc[kRows];
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int e = e0 + u * rows_per_iter;
+            const uint32_t place = (uint32_t)keys[e < n ? e : e0];
+            id[u] = (uint32_t)((uint64_t)place * g.step % g.N);
+            x[u] = reinterpret_cast<const uint4*>(static_cast<const Elem*>(g.vectors) + (size_t)id[u] * D);
+            acc[u] = 0.0f;
+        }
+        for (int piece = l; piece < npieces; piece += lpr) {
+            uint4 raw[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) raw[u] = x[u][piece];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) acc[u] = Piece<Elem>::add(raw[u], piece, y, acc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            for (int off = 1; off < lpr; off <<= 1) acc[u] += __shfl_xor(acc[u], off, kWave);
+            const int e = e0 + u * rows_per_iter;
+            if (e < n && l == 0) keys[e] = ((unsigned long long)mono_key(acc[u]) << 32) | id[u];
+        }
     }
     if (npad <= 4 * kBfThreads) block_sort_lds<4>(keys, npad, tid, kBfThreads);
     else block_sort_lds<8>(keys, npad, tid, kBfThreads);
@@ -946,8 +1024,9 @@ uint64_t gcd_u64(uint64_t a, uint64_t b) {
     return a;
 }
 
-// where the centre stands behind the N half norms, the largest norm and the word that says whether it is used: at a 16-byte boundary
-size_t centre_at(uint64_t N) { return (size_t)(N + 5) / 4 * 4; }
+// where the centre stands behind the N half norms, the largest norm, the word that says whether it is subtracted, and its norm where
+// it is not: at a 16-byte boundary
+size_t centre_at(uint64_t N) { return (size_t)(N + 6) / 4 * 4; }
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -1004,8 +1083,10 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     BruteArgs v = {};
     v.control = c.take<uint32_t>(kBfControl);
     v.flagged = c.take<uint32_t>(p.batch_pad);
+    v.second = c.take<uint32_t>(p.batch_pad / 32);
     v.todo = c.take<uint32_t>(p.batch_pad);
     v.qnorm = c.take<float>(p.batch_pad);
+    v.qshift = c.take<float>(p.batch_pad);
     v.keep = c.take<float>(p.batch_pad);
     v.best_count = c.take<uint32_t>(p.batch_pad);
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
@@ -1043,8 +1124,7 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
         a.queries = queries + (size_t)b0 * a.D;
         a.out_ids = out_ids + (size_t)b0 * a.k;
         a.out_dists = out_dists + (size_t)b0 * a.k;
-        hipLaunchKernelGGL(bf_begin_kernel, dim3((unsigned)((a.nq + kBfControl + 255) / 256)), dim3(256), 0, s, a);
-        hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(kBfThreads), 0, s, a);
+        hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(a.KS < 16 ? 256 : 1024), 0, s, a);
         for (uint64_t pos = 0; pos < a.N;) {
             const bool dense = pos == 0;
             uint64_t rows = dense ? (uint64_t)kDense : pos * (uint64_t)p.growth;
@@ -1080,17 +1160,18 @@ uint64_t brute_force_step(uint64_t N) {
 size_t brute_force_norm_words(uint64_t N, int D) { return centre_at(N) + (size_t)D; }
 
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(fill_word_kernel, dim3(1), dim3(1), 0, s, reinterpret_cast<uint32_t*>(out) + N, 0u);
     const dim3 grid((unsigned)(N / 16 + 1 < 2048 ? N / 16 + 1 : 2048)), block(kBfThreads);
-    const float part = (float)(1.0 - 2.0 * (double)pqt_host::brute_error(elem_bytes, D).row);
+    const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
     float* centre = out + centre_at(N);
+    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(3), 0, s, reinterpret_cast<uint32_t*>(out) + N);
     if (elem_bytes == 1) {
-        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, part, out);
+        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, err.dot, err.norm, out);
     } else {
         const float* x = static_cast<const float*>(vectors);
-        hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((D + kWave - 1) / kWave)), block, 0, s, x, N, brute_force_step(N), D, centre);
-        hipLaunchKernelGGL(use_centre_kernel, dim3(1), dim3(1024), 0, s, x, N, brute_force_step(N), D, centre, reinterpret_cast<uint32_t*>(out) + N + 1);
-        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, part, out);
+        const uint64_t step = brute_force_step(N);
+        hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((D + kWave - 1) / kWave)), block, 0, s, x, N, step, D, centre);
+        hipLaunchKernelGGL(use_centre_kernel, dim3(1), dim3(1024), 0, s, x, N, step, D, centre, reinterpret_cast<uint32_t*>(out) + N + 1, out + N + 2);
+        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, err.dot, err.norm, out);
     }
     return hipGetLastError();
 }
@@ -1106,8 +1187,8 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
     a.step = brute_force_step(N);
     const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
-    a.err_query = err.query;
-    a.err_row = err.row;
+    a.err_dot = err.dot;
+    a.err_norm = err.norm;
     return elem_bytes == 1 ? run<uint8_t>(p, a, queries, nq, out_ids, out_dists, s) : run<float>(p, a, queries, nq, out_ids, out_dists, s);
 }
 

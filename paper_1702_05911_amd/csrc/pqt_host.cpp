@@ -196,10 +196,9 @@ BruteError brute_error(int elem_bytes, int D) {
     const double cut = elem_bytes == 1 ? 1.0 / 131072.0 : 1.0 / 32768.0;
     const double adding = (16.0 * pieces * ((D + 15) / 16) + 16.0) / 8388608.0;
     const double centre = elem_bytes == 1 ? 0.0 : 1.0 / 8388608.0;
-    const double dot = cut + adding + centre, norm = 0.5 * (adding + (D / 64 + 26) / 16777216.0 + centre);
     BruteError e;
-    e.query = (float)(1.03 * 0.5 * dot);
-    e.row = (float)(1.03 * (0.5 * dot + norm));
+    e.dot = (float)(1.03 * (cut + adding + centre));
+    e.norm = (float)(1.03 * 0.5 * (adding + (D / 64 + 28) / 16777216.0 + centre));
     return e;
 }
 

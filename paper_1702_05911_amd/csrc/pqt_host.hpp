@@ -50,7 +50,7 @@ int check_arrays(uint32_t k1, uint32_t M, uint64_t N, uint64_t H, uint32_t code_
 constexpr int kSlopes = 10;
 int make_static_order(int R, int T, std::vector<uint32_t>& table, float thr[kSlopes - 1]);
 
-// How far the brute-force filter's sum for a vector x may lie from ||x||^2 / 2 - q.x (brute_force.hip): query * ||q||^2 + row *
+// How far the brute-force filter's sum for a vector x may lie from ||x||^2 / 2 - q.x (brute_force.hip): dot * ||q|| ||x|| + norm *
 // ||x||^2 + kBruteUnderflow.  elem_bytes: 1 for byte vectors, 4 for floats.
 //   * Cutting.  bf16 has eight significant bits: of x = s 2^e, 1 <= s < 2, a first piece leaves at most 2^(e-8), which a second
 //     piece leaves at most 2^(e-17) of.  Floats: the product of two second pieces is dropped, 2^-16 of a product, and
@@ -59,14 +59,14 @@ int make_static_order(int R, int T, std::vector<uint32_t>& table, float thr[kSlo
 //   * Adding up.  16 products a matrix instruction and the running sum are taken to be added one by one in any order, every
 //     addition off by at most 2^-23 of its result (rounded or truncated): nothing is assumed about how an instruction adds
 //     inside.  A partial sum is at most ||q|| ||x|| + ||x||^2 / 2.
-//   * The norm's own sum: at most 24 + D / 64 additions a lane and across lanes, and two roundings of what it starts from.
+//   * The norm's own sum: at most 24 + D / 64 additions a lane and across lanes, and four roundings of what it starts from.
 //   * The centre: both floats lose 2^-24 of themselves when it is subtracted.
 //   * Underflow.  The matrix cores may take numbers below 2^-126, the smallest normal one, for zero: a second piece, a product
 //     or a sum.  At most six such losses per dimension of up to 8,192 (2^-110), and pieces times the other vector, which
 //     the next power of two and the relative terms cover.
-// 2 ||q|| ||x|| <= ||q||^2 + ||x||^2 parts the two.  3 % on top for the terms of higher order and the rounding of the norms.
+// 3 % on top for the terms of higher order and the rounding of the norms.
 struct BruteError {
-    float query, row;
+    float dot, norm;
 };
 constexpr float kBruteUnderflow = 0x1p-109f;
 BruteError brute_error(int elem_bytes, int D);

@@ -192,8 +192,7 @@ size_t exact_lds_bytes(int D, int k_short);
 hipError_t launch_exact_rerank(const ExactArgs& a, hipStream_t s);
 
 // Brute force: see brute_force.hip.  Words of BruteArgs::control:
-enum { kBfSecond = 0,          // a query has a second bf16 piece
-       kBfTodo = 1,            // queries in todo[]
+enum { kBfTodo = 0,            // queries in todo[]
        kBfControl = 64 };
 struct BruteArgs {
     int64_t nq;                   // queries of the batch
@@ -201,21 +200,23 @@ struct BruteArgs {
     int D, k, KS;                 // KS: steps of 16 dimensions
     const float* queries;         // nq x D
     const void* vectors;          // N x D
-    const float* xhalf;           // what a vector's values start from, and behind them the largest ||x||
-    const float* centre;          // D: what floats are taken relative to (null for bytes)
-    const uint32_t* use_centre;   // floats: 0 where that is zero
+    const float* xhalf;           // what a vector's values start from; the largest norm, use_centre, the centre's norm
+    const float* centre;          // D: what norms and queries are taken relative to (null for bytes)
+    const uint32_t* use_centre;   // 1: the vectors too
     int64_t* out_ids;             // nq x k
     float* out_dists;             // nq x k
     uint64_t step;                // the database order: place i is vector (i * step) mod N
-    float err_query, err_row;     // error bound: err_query ||q||^2 + err_row ||x||^2
+    float err_dot, err_norm;      // error bound: err_dot ||q|| ||x|| + err_norm ||x||^2
     // the current chunk: chunk_rows vectors from place chunk_pos on
     uint64_t chunk_pos;
     int64_t chunk_rows;
     // workspace
     uint32_t* control;
     uint32_t* flagged;            // nq: 1 = left to the exact scan
+    uint32_t* second;             // 1 = a query of the tile of 32 has a second bf16 piece
     uint32_t* todo;               // those queries
     float* qnorm;                 // ||q||
+    float* qshift;                // what makes a value one of centred vectors
     float* keep;                  // largest value that still matters
     uint32_t* best_count;         // entries of best
     uint16_t* qfrag;              // queries, two bf16 pieces, operand layout

@@ -4,7 +4,7 @@
 //   sizes D P k1 k2 M N H T C format     check_sizes                             -> "rc <code> <message>"
 //   static <R> <T>                       make_static_order                       -> "Tn <n>", 9 thresholds (hex floats), 10 table rows
 //   region <nA> <nB> <Tn>                region_size                             -> "n <count>"
-//   bound <elem_bytes> <D>               brute_error                             -> "<query> <row>" (hex floats)
+//   bound <elem_bytes> <D>               brute_error                             -> "<dot> <norm>" (hex floats)
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -57,7 +57,7 @@ int main(int argc, char** argv) {
     }
     if (mode == "bound" && argc == 4) {
         const pqt_host::BruteError e = pqt_host::brute_error(atoi(argv[2]), atoi(argv[3]));
-        printf("%a %a\n", (double)e.query, (double)e.row);
+        printf("%a %a\n", (double)e.dot, (double)e.norm);
         return 0;
     }
     return 2;

@@ -188,7 +188,7 @@ def test_brute_force_error_bound(driver, elem_bytes, D):
     into bf16 pieces, piece products added in fp32 with every addition truncated, against float64.  All coordinates of a
     vector are equal (the Cauchy-Schwarz bound is then reached) and their significands the worst of 60,000 for the cut,
     together with the ends of the range."""
-    query, row = (float.fromhex(v) for v in driver("bound", elem_bytes, D).split())
+    dot, norm = (float.fromhex(v) for v in driver("bound", elem_bytes, D).split())
     grid = (1.0 + np.arange(60_000) / 60_000).astype(np.float32)
     first = _bf16(grid)
     second = _bf16(grid - first)
@@ -211,5 +211,5 @@ def test_brute_force_error_bound(driver, elem_bytes, D):
         if order == -1:
             s = _truncate(s.astype(np.float64) - half)
         true = D * q.astype(np.float64) * x - 0.5 * D * x.astype(np.float64) ** 2
-        bound = query * D * q.astype(np.float64) ** 2 + row * D * x.astype(np.float64) ** 2
+        bound = dot * D * np.abs(q.astype(np.float64) * x) + norm * D * x.astype(np.float64) ** 2
         assert (np.abs(s - true) <= bound).all(), (np.abs(s - true) / bound).max()
