@@ -13,6 +13,8 @@
 // 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 2.1 ms; the traversal kernel with w = 1 (one wavefront
 // per list, 8 of 64 lanes at work), its distances written and read back, and one wavefront per vector for the codes took
 // 7.0.  With staged values and distances side by side in LDS three workgroups instead of five fit a compute unit: 2.9.
+#include <type_traits>
+
 #include "pqt_device.hpp"
 #include "pqt_kernels.hpp"
 
@@ -67,17 +69,24 @@ constexpr bool staging_is_aligned() {
 }
 static_assert(staging_is_aligned(), "16-byte writes");
 
-// Level-1 distances of the workgroup's vectors in sub-part m, by one wavefront: at[i * kRowStride + v].
+// Level-1 distances of the workgroup's vectors in sub-part m: at[i * kRowStride + v].  By one wavefront, or (SHARED) by all of
+// the workgroup, which stage the values together and take two tiles of 16 centroids each in turn.
 // WIDE: rows are read in 16-byte pieces.  Vectors past the end repeat the last one.
-template <bool WIDE>
+template <bool WIDE, bool SHARED = false>
 __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0, int nv, int m, int st, float* xs, float* at) {
     const int lane = threadIdx.x & (kWave - 1);
+    const int wave = SHARED ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) : 0, waves = SHARED ? (int)blockDim.x / kWave : 1;
+    auto ordered = [&]() {
+        if (SHARED) __syncthreads(); else wave_lds_order();
+    };
     const int k1 = g.k1, dp = g.D / g.P, ds = g.D / g.M, per = g.M / g.P;
     const int p = m / per, lo = m * ds - p * dp;
     const int ntiles = (k1 + 15) / 16, row = lane & 15, kq = lane >> 4;
     const float* x = g.x + (size_t)v0 * g.D + (size_t)m * ds;
     float norm = 0.0f;                                       // of vector `lane`
-    for (int nt = 0; nt < ntiles; nt += 2) {
+    for (int nt0 = 0; nt0 < ntiles; nt0 += 2 * waves) {
+        const int nt = nt0 + 2 * wave;
+        const bool one = !SHARED || nt < ntiles;
         const bool two = nt + 1 < ntiles;                    // two tiles of 16 centroids per pass over the values
         v4f acc[2][4];
 #pragma unroll
@@ -86,13 +95,14 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
             for (int r = 0; r < 4; ++r) acc[t][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         for (int k0 = 0; k0 < ds; k0 += kSlab) {
             const int width = ds - k0 < kSlab ? ds - k0 : kSlab;
-            if (nt == 0 || ds > kSlab) {
-                wave_lds_order();
+            if (nt0 == 0 || ds > kSlab) {
+                ordered();
                 if (WIDE) {
                     const int pieces = width / 4;
                     int shift = 0;
                     while ((1 << shift) < pieces) ++shift;
-                    const int c = min(lane & ((1 << shift) - 1), pieces - 1), r0 = lane >> shift, step = kWave >> shift;
+                    const int c = min(lane & ((1 << shift) - 1), pieces - 1), step = (kWave >> shift) * waves;
+                    const int r0 = (lane >> shift) + (kWave >> shift) * wave;
 #pragma unroll 4
                     for (int r = r0; r < kPlaceRows; r += step)
                         *reinterpret_cast<float4*>(xs + r * st + 4 * c) =
@@ -100,13 +110,14 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
                 } else {
                     const int c = lane & (kSlab - 1);
                     if (c < ((width + 3) & ~3))
-                        for (int r = lane / kSlab; r < kPlaceRows; r += kWave / kSlab)
+                        for (int r = lane / kSlab + kWave / kSlab * wave; r < kPlaceRows; r += kWave / kSlab * waves)
                             xs[r * st + c] = c < width ? x[(size_t)min(r, nv - 1) * g.D + k0 + c] : 0.0f;
                 }
-                wave_lds_order();
-                if (nt == 0)
+                ordered();
+                if (nt0 == 0)
                     for (int d = 0; d < width; ++d) norm = fmaf(xs[lane * st + d], xs[lane * st + d], norm);
             }
+            if (!one) continue;
             // the centroid values of eight steps are fetched together, so that their latencies overlap
             float bv[2][8];
 #pragma unroll
@@ -131,9 +142,10 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
                 }
             }
         }
-        wave_lds_order();
+        if (!SHARED) wave_lds_order();                       // (the distances may take the staged values' place)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
+            if (!one) break;
             const int col = (nt + t) * 16 + row;
             const float cn = g.c1n[m * k1 + (col < k1 ? col : 0)];
 #pragma unroll
@@ -146,7 +158,7 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
                 }
         }
     }
-    wave_lds_order();
+    ordered();
 }
 
 // The nearest of the 256 code points of a sub-part: the smallest (Eq. 9 value, number).  Eight values at a time only
@@ -221,32 +233,60 @@ __device__ __forceinline__ uint32_t nearest_pair(const CodeEntry* table, int npa
     return (uint32_t)(best < 0 ? 0 : best) | (best_level << 8);
 }
 
-// The nearest line of a training sub-vector (Sec. 3.3 "Offline computation").  With b^2, a^2 its level-1 distances to c_i, c_j
-// and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) / (2 c^2) and misses the vector by
-// b^2 - lambda^2 c^2.  Smallest (error, pair number) wins; pairs of coinciding centroids never do.  Returns
-// pair number << 32 | ordered bits of lambda; pair number 0xffff when the sub-part has no usable pair.
-__device__ __forceinline__ unsigned long long nearest_line(const LinePair* pairs, int npairs, const float* at) {
+// The nearest line of a training sub-vector (Sec. 3.3 "Offline computation") among the pairs c0 .. c1 - 1.  With b^2, a^2 its
+// level-1 distances to c_i, c_j and c^2 = ||c_i - c_j||^2: the projection lies at lambda = (b^2 - a^2 + c^2) / (2 c^2) and
+// misses the vector by b^2 - lambda^2 c^2.  Returns the smallest (ordered bits of the error) << 32 | pair number; pairs of
+// coinciding centroids never win, ~0 when there are no others.  Eight pairs at a time, so that their latencies overlap.
+__device__ __forceinline__ float line_lambda(float b2, float a2, float c2) { return ((b2 - a2) + c2) / (2.0f * c2); }
+
+__device__ __forceinline__ unsigned long long nearest_line(const LinePair* pairs, int c0, int c1, const float* at) {
     const int lane = threadIdx.x & (kWave - 1);
     scalar_words w = (scalar_words)(uintptr_t)pairs;
     uint32_t low = 0xffffffffu;
     int best = -1;
-    for (int c = 0; c < npairs; ++c) {
-        const uint32_t ij = w[2 * c];
-        const float c2 = __uint_as_float(w[2 * c + 1]);
-        if (!(c2 > 0.0f)) continue;                          // the same for the wavefront
-        const float b2 = at[(ij & 0xffffu) * kRowStride + lane], a2 = at[(ij >> 16) * kRowStride + lane];
-        const float lam = ((b2 - a2) + c2) / (2.0f * c2);
-        const uint32_t key = mono_key(fmaf(-lam * lam, c2, b2));
-        if (key < low || best < 0) {
-            low = key;
-            best = c;
+    constexpr int kBlock = 8;
+    auto look_at = [&](int c, auto whole) {
+        uint32_t ij[kBlock], key[kBlock];
+        float c2[kBlock], b2[kBlock], a2[kBlock];
+#pragma unroll
+        for (int u = 0; u < kBlock; ++u) {
+            const int p = decltype(whole)::value ? c + u : min(c + u, c1 - 1);      // (past the end: the last pair again)
+            ij[u] = w[2 * p];
+            c2[u] = __uint_as_float(w[2 * p + 1]);
         }
-    }
-    if (best < 0) return 0xffffffffffffull;
-    const LinePair pr = pairs[best];
-    const float b2 = at[(pr.ij & 0xffffu) * kRowStride + lane], a2 = at[(pr.ij >> 16) * kRowStride + lane];
-    const float lam = ((b2 - a2) + pr.c2) / (2.0f * pr.c2);
-    return ((unsigned long long)(uint32_t)best << 32) | mono_key(lam);
+#pragma unroll
+        for (int u = 0; u < kBlock; ++u) {
+            b2[u] = at[(ij[u] & 0xffffu) * kRowStride + lane];
+            a2[u] = at[(ij[u] >> 16) * kRowStride + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < kBlock; ++u) {
+            const float lam = line_lambda(b2[u], a2[u], c2[u]);
+            key[u] = mono_key(fmaf(-lam * lam, c2[u], b2[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < kBlock; ++u) {
+            if (!(c2[u] > 0.0f)) continue;                   // the same for the wavefront
+            if (key[u] < low || best < 0) {                  // (the last pair again: equal to itself)
+                low = key[u];
+                best = c + u;
+            }
+        }
+    };
+    int c = c0;
+    for (; c + kBlock <= c1; c += kBlock) look_at(c, std::true_type{});
+    if (c < c1) look_at(c, std::false_type{});
+    return best < 0 ? ~0ull : ((unsigned long long)low << 32) | (uint32_t)best;
+}
+
+// The vote: sub-part << 48 | pair number << 32 | ordered bits of lambda; pair number 0xffff when the sub-part has no usable pair.
+__device__ __forceinline__ unsigned long long vote_of(const LinePair* pairs, unsigned long long nearest, int m, const float* at) {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (nearest == ~0ull) return ((unsigned long long)m << 48) | 0xffffffffffffull;
+    const uint32_t p = (uint32_t)nearest;
+    const LinePair pr = pairs[p];
+    const float lam = line_lambda(at[(pr.ij & 0xffffu) * kRowStride + lane], at[(pr.ij >> 16) * kRowStride + lane], pr.c2);
+    return ((unsigned long long)m << 48) | ((unsigned long long)p << 32) | mono_key(lam);
 }
 
 enum { kTableCodes, kPairCodes, kVotes };
@@ -274,8 +314,9 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
         if (m < M) {
             subpart_distances<WIDE>(g, v0, nv, m, L.st, xs, at);
             if (MODE == kVotes) {
-                const unsigned long long vote = nearest_line(g.pairs + (size_t)m * g.npairs, g.npairs, at);
-                if (lane < nv) g.keys[(size_t)m * g.n + v0 + lane] = ((unsigned long long)m << 48) | vote;
+                const LinePair* pairs = g.pairs + (size_t)m * g.npairs;
+                const unsigned long long vote = vote_of(pairs, nearest_line(pairs, 0, g.npairs, at), m, at);
+                if (lane < nv) g.keys[(size_t)m * g.n + v0 + lane] = vote;
             } else if (MODE == kTableCodes) {
                 code[lane * M + m] = (uint8_t)nearest_code(g.table + (size_t)m * 256, at);
             } else {
@@ -350,6 +391,46 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
         for (int e = tid; e < bytes; e += nt) out[e] = code[e];
 }
 
+// Votes with many centroids, whose distances leave room for few wavefronts that have a sub-part each: one workgroup per 64
+// vectors and sub-part, its wavefronts share the distances and the pairs.
+// 20,000 vectors x 128, 256 centroids, M = 8: VOTES ms; a wavefront per sub-part (two per compute unit) 44.1.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void shared_votes_kernel(PlaceArgs g, int st) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ unsigned long long nearest[kPlaceRows];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), waves = blockDim.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int m = blockIdx.y;
+    const int64_t v0 = (int64_t)blockIdx.x * kPlaceRows;
+    const int nv = (int)(g.n - v0 < kPlaceRows ? g.n - v0 : kPlaceRows);
+    float* xs = reinterpret_cast<float*>(smem);
+    float* at = xs + (size_t)kPlaceRows * st;
+    const LinePair* pairs = g.pairs + (size_t)m * g.npairs;
+    if (tid < kPlaceRows) nearest[tid] = ~0ull;
+    subpart_distances<WIDE, true>(g, v0, nv, m, st, xs, at);
+    const int c0 = (int)((int64_t)g.npairs * wave / waves), c1 = (int)((int64_t)g.npairs * (wave + 1) / waves);
+    const unsigned long long mine = c0 < c1 ? nearest_line(pairs, c0, c1, at) : ~0ull;
+    atomicMin(&nearest[lane], mine);
+    __syncthreads();
+    if (tid < nv) g.keys[(size_t)m * g.n + v0 + tid] = vote_of(pairs, nearest[tid], m, at);
+}
+
+hipError_t launch_shared_votes(const PlaceArgs& a, hipStream_t s) {
+    const int ds = a.D / a.M, st = place_layout(ds, a.P, a.k1, 0, 1, true).st;
+    const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && ds % 4 == 0;
+    const size_t lds = sizeof(float) * ((size_t)kPlaceRows * st + (size_t)a.k1 * kRowStride);
+    if (lds > kMaxLds - 1024) return hipErrorInvalidValue;
+    const void* fn = wide ? reinterpret_cast<const void*>(shared_votes_kernel<true>) : reinterpret_cast<const void*>(shared_votes_kernel<false>);
+    if (lds > 64 * 1024 - 1024) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid((unsigned)((a.n + kPlaceRows - 1) / kPlaceRows), (unsigned)a.M), block(256);
+    if (wide) hipLaunchKernelGGL(shared_votes_kernel<true>, grid, block, lds, s, a, st);
+    else hipLaunchKernelGGL(shared_votes_kernel<false>, grid, block, lds, s, a, st);
+    return hipGetLastError();
+}
+
 template <int MODE>
 hipError_t launch_mode(const PlaceArgs& a, hipStream_t s) {
     const int ds = a.D / a.M, cb = a.M * (MODE == kPairCodes ? 2 : 1);
@@ -396,7 +477,11 @@ hipError_t launch_place(const PlaceArgs& a, bool pair_codes, hipStream_t s) {
     return pair_codes ? launch_mode<kPairCodes>(a, s) : launch_mode<kTableCodes>(a, s);
 }
 
-hipError_t launch_votes(const PlaceArgs& a, hipStream_t s) { return a.n > 0 ? launch_mode<kVotes>(a, s) : hipSuccess; }
+// From more than 32 centroids on (two tiles, whose distances no longer take the staged values' place) the wavefronts share.
+hipError_t launch_votes(const PlaceArgs& a, hipStream_t s) {
+    if (a.n <= 0) return hipSuccess;
+    return a.k1 > 32 ? launch_shared_votes(a, s) : launch_mode<kVotes>(a, s);
+}
 
 hipError_t launch_subpart_norms(const float* C1, int D, int P, int k1, int M, float* c1n, hipStream_t s) {
     hipLaunchKernelGGL(subpart_norms_kernel, dim3((unsigned)((M * k1 + 255) / 256)), dim3(256), 0, s, C1, D, P, k1, M, c1n);

@@ -991,10 +991,12 @@ def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
             np.testing.assert_allclose(got["C2"][p, i], want, rtol=1e-6, atol=0)
 
 
-@pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8)])
+@pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8),
+                                            (300, 32, 2, 33, 4), (130, 80, 2, 70, 2), (700, 24, 1, 130, 8), (600, 16, 2, 256, 4)])
 def test_line_table_edges(pqt, n, D, P, k1, M):
     """Line votes where 16-byte rows meet numbers of centroids that are no multiple of four (and at sub-parts of five
-    dimensions).  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
+    dimensions), and of more than 32 centroids, where wavefronts share a sub-part (sub-parts of 40 and of three dimensions, the
+    most centroids).  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
     Shares as in test_training_on_the_gpu: within one of the quota, and a near tie of two lines may move a vote or two."""
     import torch
     rng = np.random.default_rng(17)
