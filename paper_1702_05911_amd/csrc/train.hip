@@ -135,11 +135,16 @@ __global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, i
 // one lane per centroid, all vectors sorted by cell in every iteration: 35.9 ms for the whole of pqt_train on 100,000
 // vectors x 128 (16 and 8 centroids, 20 iterations, line table), against 2.1.  Staging by wavefront with the next slab in
 // registers was slower (41 us an iteration): its registers cost a resident workgroup.
-template <int KB>
+// WAYS: 1, or 4 where there are too few vectors to fill the chip and many centroids (see ways_of): a tile is then 64
+// vectors, and every wavefront has all of them and a quarter of the centroids.
+template <int KB, int WAYS>
 __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) {
     typedef const __attribute__((address_space(4))) float* scalar_floats;
-    __shared__ __align__(16) float sx[kTile * kSlabStride];
-    __shared__ uint32_t srow[kTile], order[kTile], part[kTrainThreads / kWave];
+    constexpr int TILE = kTile / WAYS;
+    static_assert(WAYS == 1 || TILE == kWave, "a wavefront has one share of the centroids");
+    __shared__ __align__(16) float sx[TILE * kSlabStride];
+    __shared__ uint32_t srow[TILE], order[TILE], part[kTrainThreads / kWave];
+    __shared__ unsigned long long nearest[WAYS > 1 ? TILE : 1];
     extern __shared__ uint32_t cnt[];                        // [wavefront][cell]: members, then their first place in `order`
     if (blockIdx.x >= g.chunk_off[g.G]) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -152,13 +157,16 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) 
     const int dp = g.dp, k = g.k, nd4 = (dp + 3) / 4;
     const int p = grp / (g.G / g.P), col0 = p * dp;
     const uint32_t* mem = g.members ? g.members + (size_t)p * g.n : nullptr;
-    for (uint64_t t0 = lo; t0 < hi; t0 += kTile) {
-        const int m = (int)(hi - t0 < kTile ? hi - t0 : kTile);
+    const int way = WAYS > 1 ? wave : 0, mine = WAYS > 1 ? lane : tid;       // share of the centroids, vector of the tile
+    for (uint64_t t0 = lo; t0 < hi; t0 += TILE) {
+        const int m = (int)(hi - t0 < TILE ? hi - t0 : TILE);
         if (tid < m) srow[tid] = mem ? mem[t0 + tid] : (uint32_t)t0 + (uint32_t)tid;
+        if (WAYS > 1 && tid < TILE) nearest[tid] = ~0ull;
         for (int e = tid; e < nwaves * k; e += kTrainThreads) cnt[e] = 0u;
         uint32_t best = 0xffffffffu, cell = 0u;
         bool first = true;
-        for (int j0 = 0; j0 < k; j0 += KB) {
+        for (int first_j = 0; first_j < k; first_j += KB * WAYS) {
+            const int j0 = first_j + way * KB;               // (past the last: nothing to do but bring vectors)
             float acc[KB];
 #pragma unroll
             for (int j = 0; j < KB; ++j) acc[j] = 0.0f;
@@ -166,22 +174,22 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) 
                 __syncthreads();
                 if (first || dp > kSlab) {
                     if (g.wide) {
-// all pieces are asked for before the first is waited for: what a thread may not read it reads from the
+                        // all pieces are asked for before the first is waited for: what a thread may not read it reads from the
                         // start of a row it may
-                        float4 v[kSlab / 4];
+                        float4 v[kSlab / 4 / WAYS];
 #pragma unroll
-                        for (int u = 0; u < kSlab / 4; ++u) {
+                        for (int u = 0; u < kSlab / 4 / WAYS; ++u) {
                             const int e = tid + u * kTrainThreads, r = e / (kSlab / 4), d = d0 + 4 * (e % (kSlab / 4));
                             v[u] = *reinterpret_cast<const float4*>(g.X + (size_t)srow[r < m ? r : 0] * g.D + col0 + (d < dp ? d : 0));
                         }
 #pragma unroll
-                        for (int u = 0; u < kSlab / 4; ++u) {
+                        for (int u = 0; u < kSlab / 4 / WAYS; ++u) {
                             const int e = tid + u * kTrainThreads, r = e / (kSlab / 4), d = d0 + 4 * (e % (kSlab / 4));
                             if (r >= m || d >= dp) v[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                             *reinterpret_cast<float4*>(sx + r * kSlabStride + (d - d0)) = v[u];
                         }
                     } else {
-                        for (int e = tid; e < kTile * kSlab; e += kTrainThreads) {
+                        for (int e = tid; e < TILE * kSlab; e += kTrainThreads) {
                             const int r = e / kSlab, d = d0 + e % kSlab;
                             sx[r * kSlabStride + (d - d0)] = r < m && d < dp ? g.X[(size_t)srow[r] * g.D + col0 + d] : 0.0f;
                         }
@@ -189,10 +197,10 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) 
                 }
                 first = false;
                 __syncthreads();
-                const int steps = min(kSlab / 4, nd4 - d0 / 4);
+                const int steps = WAYS == 1 || j0 < k ? min(kSlab / 4, nd4 - d0 / 4) : 0;
                 scalar_floats c = (scalar_floats)(uintptr_t)(g.cenI + (((size_t)grp * nd4 + d0 / 4) * g.kp + j0) * 4);
                 for (int s = 0; s < steps; ++s, c += (size_t)g.kp * 4) {
-                    const float4 x = *reinterpret_cast<const float4*>(sx + tid * kSlabStride + 4 * s);
+                    const float4 x = *reinterpret_cast<const float4*>(sx + mine * kSlabStride + 4 * s);
 #pragma unroll
                     for (int j = 0; j < KB; ++j) {
                         float diff = x.x - c[4 * j];
@@ -209,15 +217,22 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) 
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
                 const uint32_t key = mono_key(acc[j]);
-                if (j0 + j < k && (key < best || (j0 + j == 0))) {
+                if (j0 + j < k && (key < best || (j == 0 && first_j == 0))) {
                     best = key;
                     cell = (uint32_t)(j0 + j);
                 }
             }
         }
+        if (WAYS > 1) {                                      // the smallest (distance, centroid) of all shares
+            if (way * KB < k) atomicMin(&nearest[mine], ((unsigned long long)best << 32) | cell);
+            __syncthreads();
+            best = (uint32_t)(nearest[mine] >> 32);
+            cell = (uint32_t)nearest[mine];
+        }
         if (tid < m) g.dmin[(size_t)p * g.n + t0 + tid] = mono_inv(best);
         if (g.label) {
             if (tid < m) g.label[(size_t)p * g.n + t0 + tid] = cell;
+            if (WAYS > 1) __syncthreads();                   // (nearest[] has been read)
             continue;
         }
         // ---- the tile's vectors ordered by cell: a lane's place among the same cell's of its wavefront, then the counts ----
@@ -457,10 +472,15 @@ int padded_centroids(int k) {
     return (k + kb - 1) / kb * kb;
 }
 
+// Shares of the centroids in lloyd_step_kernel: four where tiles of 256 vectors are fewer than the compute units and every
+// wavefront gets a round of 32 centroids.  pqt_train of 128 dimensions, 256 centroids, 20 iterations, no line table: 20,000
+// vectors 19.7 -> 14.2 ms, 5,000 vectors 19.7 -> 9.3 (one wavefront per vector: 14.7 and 10.0).
+int ways_of(uint64_t n, int P, int k) { return k >= 128 && (uint64_t)P * ((n + kTile - 1) / kTile) < 256 ? 4 : 1; }
+
 // Vectors per chunk (a workgroup of lloyd_step_kernel): one tile, or more where that would be more chunks than keep the
 // chip busy, or more than 64 MB of cell sums.
 uint64_t chunk_rows(uint64_t n, int P, int G, int k, int dp) {
-    uint64_t rows = kTile;
+    uint64_t rows = kTile / ways_of(n, P, k);
     while (rows < n && rows < (1ull << 30) && ((uint64_t)P * ((n + rows - 1) / rows) > kMaxChunks ||
                         ((uint64_t)P * ((n + rows - 1) / rows) + (uint64_t)G) * (uint64_t)k * (uint64_t)dp > (8ull << 20)))
         rows *= 2;
@@ -471,11 +491,15 @@ uint64_t chunk_limit(uint64_t n, uint64_t rows, int P, int G) { return (uint64_t
 hipError_t launch_step(const LloydArgs& g, uint64_t chunks, hipStream_t st) {
     const dim3 grid((unsigned)chunks), block(kTrainThreads);
     const size_t lds = sizeof(uint32_t) * (kTrainThreads / kWave) * (size_t)g.k;
+    if (ways_of(g.n, g.P, g.k) > 1) {                        // (at least 128 centroids: a block is 32 of them)
+        hipLaunchKernelGGL((lloyd_step_kernel<32, 4>), grid, block, lds, st, g);
+        return hipGetLastError();
+    }
     switch (centroid_block(g.k)) {
-        case 8: hipLaunchKernelGGL(lloyd_step_kernel<8>, grid, block, lds, st, g); break;
-        case 16: hipLaunchKernelGGL(lloyd_step_kernel<16>, grid, block, lds, st, g); break;
-        case 24: hipLaunchKernelGGL(lloyd_step_kernel<24>, grid, block, lds, st, g); break;
-        default: hipLaunchKernelGGL(lloyd_step_kernel<32>, grid, block, lds, st, g); break;
+        case 8: hipLaunchKernelGGL((lloyd_step_kernel<8, 1>), grid, block, lds, st, g); break;
+        case 16: hipLaunchKernelGGL((lloyd_step_kernel<16, 1>), grid, block, lds, st, g); break;
+        case 24: hipLaunchKernelGGL((lloyd_step_kernel<24, 1>), grid, block, lds, st, g); break;
+        default: hipLaunchKernelGGL((lloyd_step_kernel<32, 1>), grid, block, lds, st, g); break;
     }
     return hipGetLastError();
 }

@@ -965,6 +965,9 @@ def test_brute_force(pqt, tiny, tmp_path):
     (300, 8, 2, 20, 4, 6, 0, 3),           # fewer distinct vectors than centroids: cells run empty and are re-seeded
     (5, 8, 2, 7, 3, 0, 0, 2),              # fewer vectors than centroids
     (600_001, 8, 2, 2, 2, 0, 0, 1),        # more tiles than workgroups: a workgroup adds up several
+    (1000, 40, 1, 130, 2, 0, 0, 1),        # many centroids, few vectors: wavefronts share a tile; a last round of two centroids
+    (777, 6, 2, 256, 3, 0, 0, 1),          # the same with odd slices
+    (30_001, 16, 2, 2, 200, 0, 0, 1),      # the same at level 2
 ])
 def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
     """Tile, slab and piece edges of the training kernels against the oracle's Lloyd iterations.  Whole numbers up to 255:
