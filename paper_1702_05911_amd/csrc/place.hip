@@ -71,8 +71,9 @@ static_assert(staging_is_aligned(), "16-byte writes");
 
 // Level-1 distances of the workgroup's vectors in sub-part m: at[i * kRowStride + v].  By one wavefront, or (SHARED) by all of
 // the workgroup, which stage the values together and take two tiles of 16 centroids each in turn.
-// WIDE: rows are read in 16-byte pieces.  Vectors past the end repeat the last one.
-template <bool WIDE, bool SHARED = false>
+// WIDE: rows are read in 16-byte pieces.  ROWS: vectors, 64 or 16 (at: ROWS + 1 values a centroid).  Vectors past the end
+// repeat the last one.
+template <bool WIDE, bool SHARED = false, int ROWS = kPlaceRows>
 __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0, int nv, int m, int st, float* xs, float* at) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = SHARED ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) : 0, waves = SHARED ? (int)blockDim.x / kWave : 1;
@@ -83,16 +84,17 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
     const int p = m / per, lo = m * ds - p * dp;
     const int ntiles = (k1 + 15) / 16, row = lane & 15, kq = lane >> 4;
     const float* x = g.x + (size_t)v0 * g.D + (size_t)m * ds;
-    float norm = 0.0f;                                       // of vector `lane`
+    constexpr int kTiles = ROWS / 16;
+    float norm = 0.0f;                                       // of vector `lane` (mod ROWS)
     for (int nt0 = 0; nt0 < ntiles; nt0 += 2 * waves) {
         const int nt = nt0 + 2 * wave;
         const bool one = !SHARED || nt < ntiles;
         const bool two = nt + 1 < ntiles;                    // two tiles of 16 centroids per pass over the values
-        v4f acc[2][4];
+        v4f acc[2][kTiles];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[t][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int r = 0; r < kTiles; ++r) acc[t][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         for (int k0 = 0; k0 < ds; k0 += kSlab) {
             const int width = ds - k0 < kSlab ? ds - k0 : kSlab;
             if (nt0 == 0 || ds > kSlab) {
@@ -104,18 +106,18 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
                     const int c = min(lane & ((1 << shift) - 1), pieces - 1), step = (kWave >> shift) * waves;
                     const int r0 = (lane >> shift) + (kWave >> shift) * wave;
 #pragma unroll 4
-                    for (int r = r0; r < kPlaceRows; r += step)
+                    for (int r = r0; r < ROWS; r += step)
                         *reinterpret_cast<float4*>(xs + r * st + 4 * c) =
                             *reinterpret_cast<const float4*>(x + (size_t)min(r, nv - 1) * g.D + k0 + 4 * c);
                 } else {
                     const int c = lane & (kSlab - 1);
                     if (c < ((width + 3) & ~3))
-                        for (int r = lane / kSlab + kWave / kSlab * wave; r < kPlaceRows; r += kWave / kSlab * waves)
+                        for (int r = lane / kSlab + kWave / kSlab * wave; r < ROWS; r += kWave / kSlab * waves)
                             xs[r * st + c] = c < width ? x[(size_t)min(r, nv - 1) * g.D + k0 + c] : 0.0f;
                 }
                 ordered();
                 if (nt0 == 0)
-                    for (int d = 0; d < width; ++d) norm = fmaf(xs[lane * st + d], xs[lane * st + d], norm);
+                    for (int d = 0; d < width; ++d) norm = fmaf(xs[lane % ROWS * st + d], xs[lane % ROWS * st + d], norm);
             }
             if (!one) continue;
             // the centroid values of eight steps are fetched together, so that their latencies overlap
@@ -134,7 +136,7 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
             for (int u = 0; u < 8; ++u) {
                 if (4 * u < width) {                         // uniform
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
+                    for (int r = 0; r < kTiles; ++r) {
                         const float av = xs[(r * 16 + row) * st + 4 * u + kq];
                         acc[0][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[0][u], acc[0][r], 0, 0, 0);
                         if (two) acc[1][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[1][u], acc[1][r], 0, 0, 0);
@@ -149,12 +151,12 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
             const int col = (nt + t) * 16 + row;
             const float cn = g.c1n[m * k1 + (col < k1 ? col : 0)];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < kTiles; ++r)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int v = r * 16 + 4 * kq + j;
                     const float xn = __shfl(norm, v, kWave);
-                    if (col < k1 && (t == 0 || two)) at[col * kRowStride + v] = (xn + cn) - 2.0f * acc[t][r][j];
+                    if (col < k1 && (t == 0 || two)) at[col * (ROWS + 1) + v] = (xn + cn) - 2.0f * acc[t][r][j];
                 }
         }
     }
@@ -291,6 +293,59 @@ __device__ __forceinline__ unsigned long long vote_of(const LinePair* pairs, uns
 
 enum { kTableCodes, kPairCodes, kVotes };
 
+// What place_kernel ends with, for ROWS vectors, by the whole workgroup: sel[p * ROWS + v] holds the nearest cluster of every part,
+// code the codes of cb bytes; leaf[] starts as all ones.  (place_kernel has it inline: called from there it was scheduled so
+// that 60,000 vectors x 960 took 690 us instead of 515.)
+template <int ROWS, bool WIDE>
+__device__ __forceinline__ void finish_vectors(const PlaceArgs& g, int64_t v0, int nv, const unsigned long long* sel, unsigned long long* leaf,
+                                               const uint8_t* code, int cb) {
+    const int tid = threadIdx.x, nt = blockDim.x, D = g.D, P = g.P, k1 = g.k1, k2 = g.k2, dp = D / P;
+    // ---- level 2: the children of the nearest cluster, plain squared differences, dimensions in ascending order ----
+    const int nd4 = dp / 4;
+    for (int p = 0; p < P; ++p)
+        for (int e = tid; e < ROWS * k2; e += nt) {
+            const int v = e / k2, j = e - v * k2;
+            if (v >= nv) continue;
+            const uint32_t i = (uint32_t)sel[p * ROWS + v];
+            const float* y = g.x + (size_t)(v0 + v) * D + (size_t)p * dp;
+            float acc = 0.0f;
+            if (WIDE && g.C2t) {
+                const float4* c = reinterpret_cast<const float4*>(g.C2t) + ((size_t)p * k1 + i) * nd4 * k2 + j;
+#pragma unroll 4
+                for (int d = 0; d < nd4; ++d) {
+                    const float4 yv = *reinterpret_cast<const float4*>(y + 4 * d), cv = c[(size_t)d * k2];
+                    float diff = yv.x - cv.x;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.y - cv.y;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.z - cv.z;
+                    acc = fmaf(diff, diff, acc);
+                    diff = yv.w - cv.w;
+                    acc = fmaf(diff, diff, acc);
+                }
+            } else {
+                const float* c = g.C2 + (((size_t)p * k1 + i) * k2 + j) * dp;
+                for (int d = 0; d < dp; ++d) {
+                    const float diff = y[d] - c[d];
+                    acc = fmaf(diff, diff, acc);
+                }
+            }
+            atomicMin(&leaf[p * ROWS + v], ((unsigned long long)mono_key(acc) << 32) | (i * (uint32_t)k2 + (uint32_t)j));
+        }
+    __syncthreads();
+    if (tid < nv) {
+        unsigned long long lin = 0;
+        for (int p = 0; p < P; ++p) lin = lin * g.k1k2 + (uint32_t)leaf[p * ROWS + tid];
+        g.slots[v0 + tid] = (uint32_t)(lin % g.H);
+    }
+    const int bytes = nv * cb;
+    uint8_t* out = g.codes + (size_t)v0 * cb;
+    if (((uintptr_t)out & 3u) == 0 && bytes % 4 == 0)
+        for (int e = tid; e < bytes / 4; e += nt) reinterpret_cast<uint32_t*>(out)[e] = reinterpret_cast<const uint32_t*>(code)[e];
+    else
+        for (int e = tid; e < bytes; e += nt) out[e] = code[e];
+}
+
 template <int MODE, bool WIDE>
 __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -391,9 +446,133 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
         for (int e = tid; e < bytes; e += nt) out[e] = code[e];
 }
 
+// Few vectors: 16 per workgroup instead of 64, all sub-parts' distances at once, and a wavefront takes one vector's sub-part with
+// the code points side by side in its lanes, as lone wavefronts that walk 256 code points take 20 us for a sub-part.  The same
+// values, the smallest (value, number) wins as above.  Up to two workgroups per compute unit: x 128, P = 2, k1 = 16, M = 8,
+// us per call, 64 vectors a workgroup and 16: 1,000 vectors 52 and 16, 8,192 57 and 34, 12,000 60 and 49 (M = 4: 39 and 41; D = 960,
+// P = 4: 204 and 142).
+constexpr int kFewRows = 16, kFewThreads = 1024, kFewVectors = 8192;
+struct FewLds {
+    int st;
+    size_t off_x, off_sel, off_leaf, off_code, total;        // the distances come first: M x k1 x 17
+};
+__host__ __device__ constexpr FewLds few_layout(int ds, int P, int k1, int M, int code_bytes) {
+    FewLds L = {};
+    L.st = place_layout(ds, P, k1, code_bytes, 1, false).st;
+    size_t o = (sizeof(float) * M * k1 * (kFewRows + 1) + 15) & ~size_t(15);
+    L.off_x = o;    o += sizeof(float) * (kFewThreads / kWave) * kFewRows * L.st;
+    L.off_sel = o;  o += sizeof(unsigned long long) * P * kFewRows;
+    L.off_leaf = o; o += sizeof(unsigned long long) * P * kFewRows;
+    L.off_code = o; o += (size_t)kFewRows * code_bytes;
+    L.total = (o + 15) & ~size_t(15);
+    return L;
+}
+
+__device__ __forceinline__ unsigned long long wave_min_key(unsigned long long v) {
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), off, kWave), lo = (uint32_t)__shfl_xor((int)(uint32_t)v, off, kWave);
+        const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+        v = o < v ? o : v;
+    }
+    return v;
+}
+
+template <int MODE, bool WIDE>
+__global__ __launch_bounds__(kFewThreads) void place_few_kernel(PlaceArgs g, FewLds L) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), waves = kFewThreads / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int P = g.P, k1 = g.k1, M = g.M, per = M / P;
+    const int64_t v0 = (int64_t)blockIdx.x * kFewRows;
+    const int nv = (int)(g.n - v0 < kFewRows ? g.n - v0 : kFewRows);
+    float* a = reinterpret_cast<float*>(smem);
+    float* xs = reinterpret_cast<float*>(smem + L.off_x) + (size_t)wave * kFewRows * L.st;
+    unsigned long long* sel = reinterpret_cast<unsigned long long*>(smem + L.off_sel);
+    unsigned long long* leaf = reinterpret_cast<unsigned long long*>(smem + L.off_leaf);
+    uint8_t* code = smem + L.off_code;
+    constexpr int kStride = kFewRows + 1;
+    if (tid < P * kFewRows) sel[tid] = leaf[tid] = ~0ull;
+    for (int m = wave; m < M; m += waves) subpart_distances<WIDE, false, kFewRows>(g, v0, nv, m, L.st, xs, a + (size_t)m * k1 * kStride);
+    __syncthreads();
+    // the parts' distances: sub-parts in ascending order
+    for (int e = tid; e < P * k1 * kFewRows; e += kFewThreads) {
+        const int v = e % kFewRows, i = e / kFewRows % k1, p = e / kFewRows / k1;
+        const float* d = a + ((size_t)p * per * k1 + i) * kStride + v;
+        float sum = d[0];
+        for (int s = 1; s < per; ++s) sum = d[(size_t)s * k1 * kStride] + sum;
+        atomicMin(&sel[p * kFewRows + v], ((unsigned long long)mono_key(sum) << 32) | (unsigned)i);
+    }
+    // codes: the entries of four units are fetched together
+    constexpr int kUnits = 4;
+    for (int u0 = wave; u0 < M * nv; u0 += kUnits * waves) {
+        CodeEntry entry[kUnits][4];
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const int m = min(u0 + u * waves, M * nv - 1) % M;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) entry[u][q] = g.table[(size_t)m * 256 + q * kWave + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+            const int unit = u0 + u * waves, m = unit % M, v = unit / M;
+            if (unit >= M * nv) break;                       // the same for the wavefront
+            const float* at = a + (size_t)m * k1 * kStride + v;
+            unsigned long long best = ~0ull;
+            uint32_t best_level = 96;                        // no usable pair: pair 0 at lambda = 0
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const CodeEntry& e = entry[u][q];
+                const int c = q * kWave + lane;
+                if (MODE == kPairCodes && (c >= g.npairs || !(e.kc > 0.0f))) continue;
+                const float b2 = at[(e.ij & 0xffu) * kStride], a2 = at[((e.ij >> 8) & 0xffu) * kStride];
+                if (MODE == kTableCodes) {
+                    const float value = fmaf(e.lam, a2 - b2, b2) + e.kc;
+                    const unsigned long long key = ((unsigned long long)mono_key(value + 0.0f) << 32) | (unsigned)c;     // (no negative zero)
+                    best = key < best ? key : best;
+                } else {
+                    const float proj = ((b2 - a2) + e.kc) / (2.0f * e.kc);
+                    const float level = fminf(fmaxf(floorf(fmaf(proj, 16.0f, 96.5f)), 0.0f), 255.0f);
+                    const float lam = fmaf(level, 0.0625f, -6.0f);
+                    const uint32_t bits = mono_key(fmaf(fmaf(lam, lam, -lam), e.kc, fmaf(lam, a2 - b2, b2)));
+                    const unsigned long long key = ((unsigned long long)bits << 32) | (unsigned)c;
+                    if (key < best) {
+                        best = key;
+                        best_level = (uint32_t)level;
+                    }
+                }
+            }
+            const unsigned long long nearest = wave_min_key(best);
+            if (MODE == kTableCodes) {
+                if (lane == 0) code[v * M + m] = (uint8_t)nearest;
+            } else if (best == nearest && (nearest != ~0ull || lane == 0)) {         // one lane has the nearest pair
+                code[(v * M + m) * 2] = nearest == ~0ull ? (uint8_t)0 : (uint8_t)nearest;
+                code[(v * M + m) * 2 + 1] = (uint8_t)best_level;
+            }
+        }
+    }
+    __syncthreads();
+    finish_vectors<kFewRows, WIDE>(g, v0, nv, sel, leaf, code, M * (MODE == kPairCodes ? 2 : 1));
+}
+
+template <int MODE>
+hipError_t launch_few(const PlaceArgs& a, const FewLds& L, hipStream_t s) {
+    const int ds = a.D / a.M;
+    const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && ds % 4 == 0;
+    const void* fn = wide ? reinterpret_cast<const void*>(place_few_kernel<MODE, true>) : reinterpret_cast<const void*>(place_few_kernel<MODE, false>);
+    if (L.total > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.total);
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid((unsigned)((a.n + kFewRows - 1) / kFewRows)), block(kFewThreads);
+    if (wide) hipLaunchKernelGGL((place_few_kernel<MODE, true>), grid, block, L.total, s, a, L);
+    else hipLaunchKernelGGL((place_few_kernel<MODE, false>), grid, block, L.total, s, a, L);
+    return hipGetLastError();
+}
+
 // Votes with many centroids, whose distances leave room for few wavefronts that have a sub-part each: one workgroup per 64
 // vectors and sub-part, its wavefronts share the distances and the pairs.
-// 20,000 vectors x 128, 256 centroids, M = 8: VOTES ms; a wavefront per sub-part (two per compute unit) 44.1.
+// pqt_train of 20,000 vectors x 128, 256 centroids, M = 8, five iterations: 19.3 ms; a wavefront per sub-part (two per compute
+// unit) 58.1, 44.1 of them for the votes.
 template <bool WIDE>
 __global__ __launch_bounds__(256) void shared_votes_kernel(PlaceArgs g, int st) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -435,6 +614,10 @@ template <int MODE>
 hipError_t launch_mode(const PlaceArgs& a, hipStream_t s) {
     const int ds = a.D / a.M, cb = a.M * (MODE == kPairCodes ? 2 : 1);
     const bool wide = reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && ds % 4 == 0;
+    if constexpr (MODE != kVotes) {
+        const FewLds L = few_layout(ds, a.P, a.k1, a.M, cb);
+        if (a.n <= kFewVectors && L.total <= kMaxLds) return launch_few<MODE>(a, L, s);
+    }
     // wavefronts per workgroup: those that leave a compute unit the most, none without a sub-part
     int waves = 1;
     size_t most = 0;

@@ -740,6 +740,7 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
         assert e.value.code == pqt.PQT_EFORMAT
 
 
+@pytest.mark.parametrize("many", [0, 12_300])     # more than 8,192 vectors in the second call: 64 per workgroup instead of 16
 @pytest.mark.parametrize("N, D, P, k1, k2, M, fmt, offset", [
     (63, 16, 2, 16, 8, 4, 0, 0),           # one vector short of a workgroup; one tile of centroids
     (65, 24, 2, 17, 3, 4, 0, 0),           # one vector in the second workgroup; a second, nearly empty tile of centroids
@@ -753,14 +754,18 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
     (130, 16, 2, 7, 3, 4, 0, 0),           # 16-byte rows and numbers of centroids that are no multiple of four, so that a
     (77, 64, 2, 21, 2, 4, 0, 0),           # wavefront's distances outgrow its staged values by an odd number of words
     (70, 32, 4, 15, 4, 4, 1, 0),
+    (50, 256, 1, 240, 2, 8, 0, 0),         # distances that do not fit the LDS of the kernel for few vectors
+    (17, 64, 2, 16, 4, 64, 0, 0),          # the most sub-parts; one vector in the second workgroup of 16
+    (15, 48, 4, 12, 3, 12, 1, 0),          # one vector short of such a workgroup
     (90, 6, 2, 3, 2, 6, 1, 1),             # sub-parts of one dimension
 ])
-def test_builder_edges(pqt, N, D, P, k1, k2, M, fmt, offset):
+def test_builder_edges(pqt, N, D, P, k1, k2, M, fmt, offset, many):
     """Bins, codes and lists at the edges of the placing kernel's tiles, slabs and passes, against the oracle.  Codebooks,
     vectors and lambdas are small whole numbers and multiples of 1/16, so that every distance is exact in fp32 and float64
     and the results are equal, ties included; slots are hashed for the odd H."""
     import torch
     rng = np.random.default_rng(5)
+    N += many
     top = 8 if fmt else 16
     dp = D // P
     X = rng.integers(0, top, (N, D)).astype(np.float32)
