@@ -1229,6 +1229,31 @@ def test_brute_force_ties(pqt, stored, N, D, nq, k, same):
         assert t < 10 * even, (t, even)
 
 
+@pytest.mark.parametrize("stored, D", [("u8", 32), ("f32", 20)])
+def test_brute_force_in_rounds(pqt, stored, D):
+    """More queries than one round of the workspace holds (16,384): the queries on both sides of the border and the last ones
+    get what they get by themselves, and what float64 says; a query of the second round that all vectors tie for is scanned."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(41)
+    N, nq, k = 6000, 16_384 + 37, 5
+    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda").float()
+    X[1000:] = torch.where(torch.rand((N - 1000, 1), generator=gen, device="cuda") < 0.7, X[7], X[1000:])
+    Y = torch.randint(0, 256, (nq, D), generator=gen, device="cuda").float()
+    Y[-3] = X[7]
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X.to(torch.uint8) if stored == "u8" else X)
+        ids, d = pqt.pqt_brute_force(ix, Y, k)
+        for part in (slice(0, 9), slice(16_380, 16_390), slice(nq - 9, nq)):
+            few, fd = pqt.pqt_brute_force(ix, Y[part].contiguous(), k)
+            true = ((X.double()[None] - Y[part].double()[:, None]) ** 2).sum(2)
+            want = (true * N + torch.arange(N, device="cuda")).sort(1).indices[:, :k]
+            assert torch.equal(few, want) and torch.equal(ids[part], want)
+            assert torch.equal(fd, d[part]) and torch.equal(fd.double(), true.gather(1, want))
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
