@@ -29,9 +29,12 @@
 // overflow (more than about two thousand vectors tied with the k-th, or non-finite data) is searched by bf_scan_kernel, exact
 // distances to all vectors.
 //
-// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 2.9 = 0.88 PFLOP/s, selection 0.49); with
+// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 3.0 = 0.85 PFLOP/s, selection 0.49); with
 // the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
-// 0.90 ms (contraction 0.79 = 1.0 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
+// 0.80 ms (contraction 0.73 = 0.92 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
+// Data on which a bound by the largest norm of all, a list of 2 k + 256 and a scan by one workgroup per query took 78 ms
+// (the same floats, 777 queries; fp32 matrix cores 2.7): one vector of norm 300 among unit vectors 1.0 ms, an offset of 10 1.0,
+// 1,000 copies of one vector 1.2.
 #include <type_traits>
 
 #include "pqt_device.hpp"

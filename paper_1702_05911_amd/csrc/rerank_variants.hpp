@@ -1,7 +1,8 @@
 // The re-rank kernel is compiled once per code width, each width in a translation unit of its own
 // (rerank_table*.hip: one byte per sub-part, M = 4, 8, 12, 16, 32 or any; rerank_pair*.hip: (pair, lambda)
 // codes, M = 4, 8, 12, 16, 32 word-wise or any byte-wise; the number in the name counts 32-bit words).  Read byte by byte, a
-// candidate costs a load per byte: 3,217 queries x 3,001 candidates of 24 bytes took 456 us, read as words 121.  This header declares their launchers.
+// candidate costs a load per byte: 3,217 queries x 3,001 candidates of 24 bytes, ranking included, took 456 us, read as words 339
+// (and 140 with the ranking in a kernel of its own).  This header declares their launchers.
 #pragma once
 #include "pqt_kernels.hpp"
 
