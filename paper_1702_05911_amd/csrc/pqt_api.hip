@@ -124,12 +124,23 @@ int rerank_runs_in_lds(const pqt_index* ix) {
 // More than 2,048 tuples take workgroups of 512 threads, two per compute unit, so that batches of more than two rounds of those
 // gain by the head pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at
 // 67: 85 and 114, at 90: 109 and 131; T = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536.
-double headless_from(int64_t nq, uint32_t T) {
+// Codes that are not one byte per sub-part read as words leave the re-rank kernel more to do, behind which the ranking inside it
+// hides: with the head pass and without, M = 32 pairs, 1,200 queries at 60: 108 and 134, at 110: 181 and 174; 10,000 at 60: 639
+// and 713, at 80: 834 and 804; M = 6 pairs 2,040 at 60: 59 and 65, 10,000 at 110: 382 and 370; M = 64 4,000 at 60: 327 and 358,
+// at 80: 421 and 409.  One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
+// 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233.
+double headless_from(const pqt_index* ix, int64_t nq) {
+    const uint32_t M = ix->M;
+    const bool pairs = ix->code_format == PQT_CODES_PAIR_LAMBDA;
+    const bool words = !pairs && (M == 4 || M == 8 || M == 12 || M == 16 || M == 32);
     if (nq < 4) return 160.0;
     if (nq < 16) return 96.0;
     if (nq < 96) return 64.0;
-    if (T > 2048 && nq > 1024) return nq <= 2048 ? 96.0 : 160.0;
-    return nq <= 2048 ? 48.0 : 96.0;
+    if (!pairs && M < 4) return 140.0;
+    if (nq <= 512) return 48.0;
+    if (ix->T > 2048 && nq > 1024) return nq <= 2048 ? 96.0 : 160.0;
+    if (nq <= 2048) return words ? 48.0 : 72.0;
+    return words ? 96.0 : 84.0;
 }
 constexpr double kThirdLevelFrom = 72.0;     // the same mean, for the head pass's 128 tuples (see launch_rank)
 
@@ -621,7 +632,7 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     while (ra.t_mid < (int)ix->T && ra.t_mid < 2.0 * mean_need) ra.t_mid *= 2;
     // The head pass is left out where it would leave much to do: every query is then ranked by a workgroup of its own in
     // a kernel of its own, by placing, which the re-rank kernel has no registers for.
-    if (mean_need >= headless_from(nq, ix->T)) ra.order = nullptr;
+    if (mean_need >= headless_from(ix, nq)) ra.order = nullptr;
     ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
     const bool rerank_taps = tp.n_cand || tp.cand_ids || tp.scores || tp.lut || tp.n_slots;
     const bool head = !fixed_order && pqt::rank_has_head(ra);

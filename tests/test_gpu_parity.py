@@ -506,6 +506,23 @@ def test_code_widths(pqt, tmp_path, M, fmt):
     _stagewise(pqt, ix, path, Y, 40, 4, 60, 900)
 
 
+@pytest.mark.parametrize("M, C", [(12, 400), (12, 3000), (32, 300), (32, 4096)])
+def test_wide_pair_codes_by_words_and_bytes(pqt, M, C):
+    """(pair, lambda) codes of six and sixteen words are read byte by byte where workgroups of 1,024 threads would not all run at
+    once: the same results from calls of 100 queries (words), 300 and 1,024 (bytes) and 1,025 (words, smaller workgroups), and
+    from the debug entry point."""
+    import torch
+    ix, X = _whole_number_index(pqt, 6000, 2 * M, 2, 8, 4, M, T=256, C=C, fmt=1)
+    try:
+        Y = X[:1025] + 0.25
+        ids, d, _ = pqt.pqt_query_batch_debug(ix, Y, 50, 4, taps=("n_tuples",))
+        for nq in (100, 300, 1024, 1025):
+            got, gd = pqt.pqt_query_batch(ix, Y[:nq].contiguous(), 50, 4)
+            assert torch.equal(got, ids[:nq]) and torch.equal(gd, d[:nq]), nq
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 @pytest.mark.parametrize("H", [None, 4099])
 @pytest.mark.parametrize("C", [30, 60, 120, 400, 3000])
 def test_ranking_routes_agree(pqt, C, H):
