@@ -1064,7 +1064,7 @@ Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
     p.growth = p.batch * k < 200000 ? most : (most < 4 ? most : 4);
     // room for the pairs that pass and for the ties that may be kept
     p.seg_cap = 4 * ((k * p.growth + p.segs - 1) / p.segs) + 16 + kBest / p.segs;
-    p.scan_queries = scan_lds(kScanQueries, D) <= 64 * 1024 ? kScanQueries : 1;
+    p.scan_queries = scan_lds(kScanQueries, D) <= 63 * 1024 ? kScanQueries : 1;      // (64 KB less what the kernel has itself)
     const int64_t most_items = (p.batch + p.scan_queries - 1) / p.scan_queries * kScanSplits;
     p.scan_grid = (int)(most_items < 1024 ? most_items : 1024);
     return p;

@@ -1207,6 +1207,8 @@ def test_brute_force_whatever_the_norms(pqt, kind):
     ("u8", 60_000, 96, 300, 256, 20_000),  # more than are kept: the exact scan, a part of the database a workgroup
     ("f32", 60_000, 20, 1, 7, 60_000),     # one query, all tied
     ("f32", 700, 2048, 3, 200, 700),       # rows of which the scan holds one query at a time
+    ("f32", 700, 2044, 3, 200, 700),       # four such rows and their entries would fill 64 KB of LDS to the byte
+    ("f32", 700, 1980, 3, 200, 700),       # the longest of which it holds four
     ("u8", 4500, 16, 5000, 3, 4500),       # more queries than the scan has workgroups
 ])
 def test_brute_force_ties(pqt, stored, N, D, nq, k, same):
@@ -1214,8 +1216,11 @@ def test_brute_force_ties(pqt, stored, N, D, nq, k, same):
     times as long as others (measured: 1.5 to 3.6 times; scanned by one workgroup per query 12 to 30 times)."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(31)
-    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda").float()
-    Y = torch.randint(0, 256, (nq, D), generator=gen, device="cuda").float()
+    # distances are whole numbers in fp32 below 2^24 = 16.8e6: numbers below t lie (t^2 - 1) / 6 apart in the mean square,
+    # 1.4e6 for t = 256 and D = 128, 22e6 for D = 2,044, where t = 128 gives 5.6e6
+    top = 256 if D <= 128 else 128
+    X = torch.randint(0, top, (N, D), generator=gen, device="cuda").float()
+    Y = torch.randint(0, top, (nq, D), generator=gen, device="cuda").float()
 
     def timed(X, Y):
         ix = _vectors_only_index(pqt, N, D)
