@@ -3,7 +3,8 @@
 //
 // A dense contraction finds the few vectors that can be among the k nearest, and only those get their exact fp32
 // distance.  The contraction runs on the bf16 matrix cores, eight times the flops of the fp32 ones: a number is
-// cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly, queries of bytes too.
+// cut into bf16 pieces (h = bf16(x), m = bf16(x - h)); byte vectors are one piece exactly.  Byte vectors with queries of bytes
+// run on the int8 ones, where everything is exact (filter_as_bytes); the rest of this is about the others.
 // With s = ||x||^2 / 2 - q.x (half the squared distance but for the query's own term), the sum of the matrix cores is within
 // a ||q|| ||x|| + b ||x||^2 of s: dropped piece products, the rounding of the sums, and the norm (see pqt_host::brute_error).
 // 2 ||q|| ||x|| <= ||q||^2 + ||x||^2 parts that, and the filter's value v is the sum less the vector's part (it starts from the
@@ -29,8 +30,9 @@
 // overflow (more than about two thousand vectors tied with the k-th, or non-finite data) is searched by bf_scan_kernel, exact
 // distances to all vectors.
 //
-// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 3.5 ms (the contraction 3.0 = 0.85 PFLOP/s, selection 0.49); with
-// the fp32 matrix cores and all distances written and read back it was 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
+// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 2.4 ms (the contraction 1.86, 0.5 of it for pairs that pass; selection
+// 0.46); as one bf16 piece 3.5 ms (contraction 3.0), with
+// the fp32 matrix cores and all distances written and read back 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
 // 0.80 ms (contraction 0.73 = 0.92 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
 // Data on which a bound by the largest norm of all, a list of 2 k + 256 and a scan by one workgroup per query took 78 ms
 // (the same floats, 777 queries; fp32 matrix cores 2.7): one vector of norm 300 among unit vectors 1.0 ms, an offset of 10 1.0,
@@ -48,12 +50,17 @@ namespace {
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));    // (arrays of HIP's uint4 end up in scratch memory)
 
 constexpr int kBfThreads = 256;
 constexpr int kDense = 4096;           // vectors of the first chunk; also the entries a select workgroup holds in LDS
 constexpr int kFrag = 512;             // bf16 values of one fragment: 32 rows x 16 dimensions
-constexpr int kStatRows = 64;          // database vectors per LDS tile of the stationary kernel
+constexpr int kStatRows = 64;          // database vectors per LDS tile of the stationary kernel, as bf16 ...
+constexpr int kByteRows = 128;         // ... and as bytes
+constexpr int kStatQueries = 512;      // queries of one of its workgroups
+constexpr uint32_t kSecondPiece = 1u, kNotBytes = 2u;      // a query tile's state: second bf16 pieces; values that are not 0 .. 255
 constexpr int kGenRows = 256, kGenQueries = 128;   // workgroup tile of the general kernel
 
 __device__ __forceinline__ v16f mfma(bf16x8 a, bf16x8 b, v16f c) {
@@ -72,14 +79,15 @@ __device__ __forceinline__ float high_value(uint32_t pair) { return __uint_as_fl
 
 // Queries -> fragments of two pieces (h, then m): one workgroup per tile of 32 queries, its wavefronts share the steps of
 // 16 dimensions (16 of them where there are many steps); lane l holds query l % 32, dimensions 8 * (l / 32) .. + 8 of a step.
-// Also ||q||, whether a query of the tile has a second piece that is not zero, and the state of the call: no query is left to
-// the exact scan.
+// Also ||q||, whether a query of the tile has a second piece that is not zero or is not all bytes, and the state of the call: no
+// query is left to the exact scan.  qbytes (stationary kernel): the values less 128 as they are if they are bytes, in the operand
+// layout of v_mfma_i32_32x32x32_i8, lane l with query l % 32, dimensions 16 * (l / 32) .. + 16 of a step of 32.
 __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
     __shared__ float red[2][1024 / kWave][32];
-    __shared__ uint32_t any_second;
+    __shared__ uint32_t state;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, nwaves = (int)blockDim.x / kWave, D = g.D, KS = g.KS;
     if (tid == 0) {
-        any_second = 0u;
+        state = 0u;
         if (blockIdx.x == 0) g.control[kBfTodo] = 0u;
     }
     __syncthreads();
@@ -88,6 +96,7 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
     const float* row = g.queries + (have ? (size_t)q * D : 0);
     float norm = 0.0f, shift = 0.0f;
     uint32_t second = 0;
+    bool bytes = true;
 #pragma unroll 4
     for (int ks = wave; ks < KS; ks += nwaves) {
         const int d = have ? ks * 16 + 8 * (lane >> 5) : D;               // D is a multiple of four
@@ -114,6 +123,18 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
         u32x4* out = reinterpret_cast<u32x4*>(g.qfrag) + (tile * KS + ks) * (2 * kFrag / 8) + lane;
         out[0] = h;
         out[kFrag / 8] = m;
+        if (g.qbytes) {
+            uint32_t packed[2] = {0u, 0u};
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const bool is_byte = v[c] >= 0.0f && v[c] <= 255.0f && v[c] == truncf(v[c]);
+                bytes = bytes && is_byte;
+                const uint32_t b = is_byte && d + c < D ? ((uint32_t)v[c] & 0xffu) ^ 0x80u : 0u;       // (nothing past the last dimension)
+                packed[c / 4] |= b << (8 * (c % 4));
+            }
+            reinterpret_cast<uint2*>(g.qbytes)[((tile * (KS / 2) + ks / 2) * kWave + (ks & 1) * 32 + (lane & 31)) * 2 + (lane >> 5)] =
+                make_uint2(packed[0], packed[1]);
+        }
     }
     norm += __shfl_xor(norm, 32, kWave);
     shift += __shfl_xor(shift, 32, kWave);
@@ -121,7 +142,8 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
         red[0][wave][lane] = norm;
         red[1][wave][lane] = shift;
     }
-    if (__any(second != 0) && lane == 0) any_second = 1u;
+    const uint32_t found = (__any(second != 0) ? kSecondPiece : 0u) | (__any(!bytes) ? kNotBytes : 0u);
+    if (lane == 0 && found) atomicOr(&state, found);
     __syncthreads();
     if (tid < 32) {
         float n2 = 0.0f, c = 0.0f;
@@ -133,7 +155,7 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
         g.qshift[q] = g.use_centre[0] ? 0.0f : c;
         g.flagged[q] = 0u;
     }
-    if (tid == 0) g.second[tile] = any_second;
+    if (tid == 0) g.second[tile] = state;
 }
 
 // The centre of float vectors: in every dimension the median of 64 vectors spread over the database (places 0 .. 63 of the
@@ -222,8 +244,9 @@ __global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64
 // What the accumulators start from, the half squared norms of the database vectors less their part of the error bound, and, in the
 // word behind them, the bits of the largest norm (a little enlarged; never negative, so bits order as values).  A group of
 // lanes per row, 16 bytes per lane and step.
+// Bytes: in `whole` the same of the vectors less 128, rounded down to a whole number.
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float err_dot, float err_norm, float* out) {
+__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float err_dot, float err_norm, float* out, int* whole) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     constexpr int pe = 16 / (int)sizeof(Elem);
     const int npieces = D / pe, lpr = lanes_per_row(npieces), per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
@@ -234,6 +257,7 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
     for (int64_t r0 = ((int64_t)blockIdx.x * (kBfThreads / kWave) + wave) * per_wave; r0 < n; r0 += nwaves * per_wave) {
         const int64_t r = r0 + sub;
         float s = 0.0f, raw = 0.0f;
+        int signed_norm = 0;
         if (r < n) {
 #pragma unroll 4
             for (int piece = l; piece < npieces; piece += lpr) {
@@ -252,6 +276,8 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
                             const float v = (float)((w[j] >> (8 * b)) & 0xffu);
                             s = fmaf(v, v, s);
                         }
+                        const int less = (int)(w[j] ^ 0x80808080u);
+                        signed_norm = __builtin_amdgcn_sdot4(less, less, signed_norm, false);
                     }
                 }
             }
@@ -259,7 +285,9 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
         for (int off = 1; off < lpr; off <<= 1) {
             s += __shfl_xor(s, off, kWave);
             if constexpr (sizeof(Elem) == 4) raw += __shfl_xor(raw, off, kWave);
+            else signed_norm += __shfl_xor(signed_norm, off, kWave);
         }
+        if (sizeof(Elem) == 1 && r < n && l == 0) whole[r] = signed_norm >> 1;
         if (r < n && l == 0) out[r] = (0.5f - err_norm) * s - 0.5f * err_dot * (as_they_are ? raw : s);
         top = fmaxf(top, r < n ? s : 0.0f);
         if (r < n && s != s) top = __builtin_inff();
@@ -300,27 +328,44 @@ __device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {
     return q >= g.nq || g.flagged[q] ? __builtin_inff() : -g.keep[q];
 }
 
+// Are the queries of this group of the stationary kernel all whole numbers 0 .. 255?
+__device__ __forceinline__ bool group_is_bytes(const BruteArgs& g, int group) {
+    uint32_t state = 0;
+#pragma unroll
+    for (int tile = 0; tile < kStatQueries / 32; ++tile) state |= g.second[group * (kStatQueries / 32) + tile];
+    return !(state & kNotBytes);
+}
+
 // One 32 x 32 tile of accumulators: lane l holds query column l % 32 and database rows 8 * (r / 4) + 4 * (l / 32) + r % 4.
 // DENSE: all values go to out (s~ of the query's row of kDense values).  Else those that reach `from` are appended to the
-// lane's list (row of the chunk, s~).
-template <bool DENSE>
-__device__ __forceinline__ void take_tile(const v16f& acc, float from, uint32_t row0, float* dense, uint2* list, int cap, uint32_t& count) {
+// lane's list (row of the chunk, s~); a maximum of four rows says whether to look at each.
+template <typename Value>
+__device__ __forceinline__ Value larger(Value a, Value b) {
+    if constexpr (std::is_same<Value, float>::value) return fmaxf(a, b);
+    else return a > b ? a : b;
+}
+template <bool DENSE, typename Acc, typename Value>
+__device__ __forceinline__ void take_tile(const Acc& acc, Value from, uint32_t row0, float* dense, uint2* list, int cap, uint32_t& count) {
     if (DENSE) {
         if (!dense) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<float4*>(dense + row0 + 8 * i) = make_float4(-acc[4 * i], -acc[4 * i + 1], -acc[4 * i + 2], -acc[4 * i + 3]);
+            *reinterpret_cast<float4*>(dense + row0 + 8 * i) = make_float4((float)-acc[4 * i], (float)-acc[4 * i + 1], (float)-acc[4 * i + 2], (float)-acc[4 * i + 3]);
         return;
     }
-    float top = acc[0];
+    Value four[4];
 #pragma unroll
-    for (int r = 1; r < 16; ++r) top = fmaxf(top, acc[r]);
-    if (top >= from) {
+    for (int i = 0; i < 4; ++i) four[i] = larger(larger(acc[4 * i], acc[4 * i + 1]), larger(acc[4 * i + 2], acc[4 * i + 3]));
+    if (larger(larger(four[0], four[1]), larger(four[2], four[3])) >= from) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (acc[r] >= from) {
-                if (count < (uint32_t)cap) list[count] = make_uint2(row0 + 8 * (r >> 2) + (r & 3), __float_as_uint(-acc[r]));
-                ++count;
+        for (int i = 0; i < 4; ++i)
+            if (four[i] >= from) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (acc[4 * i + c] >= from) {
+                        if (count < (uint32_t)cap) list[count] = make_uint2(row0 + 8 * i + c, __float_as_uint((float)-acc[4 * i + c]));
+                        ++count;
+                    }
             }
     }
 }
@@ -338,28 +383,64 @@ __device__ __forceinline__ void place_of_workgroup(int b, int splits, int groups
     }
 }
 
-// Byte vectors of at most 128 dimensions: a wavefront keeps its 64 queries in registers (KS steps, QP pieces) for the
-// whole launch, and the workgroup's 256 queries share the database tiles that stream through LDS, two in turn.  Per
-// tile of 64 vectors a wavefront reads 16 KB of LDS for 2 * 2 * KS matrix instructions of 32 cycles each, half the LDS
-// rate, and widens 2 KB of bytes (two instructions per three bytes, a fifth of the matrix time and beside it).  Three
-// workgroups fit a compute unit, so others compute while one passes its barrier or examines its sums.
+// The rows of the database tiles a workgroup of the kernels below brings into LDS: tiles of ROWS vectors, every splits-th
+// of the chunk, as 16-byte pieces (KS of them, 16 dimensions each) that a thread has the same places of in every tile.
+template <int KS, int ROWS>
+struct TileRows {
+    static constexpr int kPieces = (ROWS * KS + kBfThreads - 1) / kBfThreads;           // pieces per thread
+    int row[kPieces], step[kPieces];           // piece i is step[i] of row[i]
+    bool mine[kPieces];
+    u32x4 piece[kPieces];
+    uint64_t at[kPieces], hid, move;           // where in the database those pieces are; the vector of row tid
+    int D16;
+    __device__ __forceinline__ void start(const BruteArgs& g, int split) {
+        const int tid = threadIdx.x;
+        D16 = g.D / 16;
+        move = ((uint64_t)g.splits * ROWS) % g.N * g.step % g.N;
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int e = i * kBfThreads + tid;
+            mine[i] = e < ROWS * KS;
+            // rows four apart within a wavefront's instruction, so that row ^ step takes all sixteen bank groups
+            const int r = e / KS;
+            step[i] = e - r * KS;
+            row[i] = KS == 8 ? (r & ~31) | (r & 7) << 2 | (r >> 3 & 3) : r & (ROWS - 1);
+            at[i] = ((g.chunk_pos + (uint64_t)split * ROWS + row[i]) % g.N) * g.step % g.N * (uint64_t)g.D + (step[i] < D16 ? step[i] * 16 : 0);
+        }
+        hid = ((g.chunk_pos + (uint64_t)split * ROWS + (tid & (ROWS - 1))) % g.N) * g.step % g.N;
+    }
+    // the next tile's pieces, then the ids move on; past the last tile: some vectors, unused (always loading keeps the pieces in
+    // registers).  Returns the vector of row tid.
+    __device__ __forceinline__ uint64_t fetch(const BruteArgs& g) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const uint8_t*>(g.vectors) + at[i]);
+            piece[i] = step[i] < D16 ? v : zero;
+            at[i] += move * (uint64_t)g.D;
+            at[i] -= at[i] >= g.N * (uint64_t)g.D ? g.N * (uint64_t)g.D : 0;       // (a piece lies less than D behind its vector's start)
+        }
+        const uint64_t h = hid;
+        hid += move;
+        hid -= hid >= g.N ? g.N : 0;
+        return h;
+    }
+};
+
+// Byte vectors of at most 128 dimensions, queries that are not all bytes: a wavefront keeps 64 queries in registers (KS steps,
+// two pieces) for the whole launch, and 256 queries share the database tiles that stream through LDS, two in turn.
 // LDS: 16 bytes of (row, step, half) lie in slot row ^ step of the fragment's half: eight lanes bring a row's eight steps
 // and would all hit the same banks.
-template <int KS, int QP, bool DENSE>
-__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(BruteArgs g) {
-    __shared__ __align__(16) uint16_t xs[2][kStatRows / 32 * KS * kFrag];
-    __shared__ __align__(16) float hs[2][kStatRows];
-    constexpr int kPieces = (kStatRows * KS + kBfThreads - 1) / kBfThreads;    // 16-byte pieces of a tile per thread
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int splits = g.splits;
-    int split, group;
-    place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
+template <int KS, bool DENSE>
+__device__ __forceinline__ void filter_as_bf16(const BruteArgs& g, unsigned char* smem, int split, int64_t first_query) {
+    constexpr int kTileBytes = kStatRows / 32 * KS * kFrag * 2;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, splits = g.splits;
+    const int64_t q0 = first_query + wave * 64;
     uint32_t second = 0;
 #pragma unroll
-    for (int tile = 0; tile < 8; ++tile) second |= g.second[group * 8 + tile];
-    if ((QP == 2) != (second != 0u)) return;                       // the launch of the other number of pieces has this work
-    const int64_t q0 = (int64_t)group * 256 + wave * 64;
-    bf16x8 bq[QP][2][KS];
+    for (int tile = 0; tile < 8; ++tile) second |= g.second[first_query / 32 + tile];
+    const bool two = second & kSecondPiece;
+    bf16x8 bq[2][2][KS];
     float from[2];
     uint32_t count[2] = {0, 0};
     uint2* list[2];
@@ -368,7 +449,7 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
     for (int ct = 0; ct < 2; ++ct) {
         const int64_t q = q0 + ct * 32 + (lane & 31);
 #pragma unroll
-        for (int p = 0; p < QP; ++p)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 bq[p][ct][ks] = reinterpret_cast<const bf16x8*>(g.qfrag)[((q0 / 32 + ct) * KS + ks) * (2 * kFrag / 8) + p * (kFrag / 8) + lane];
@@ -376,60 +457,37 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
         list[ct] = g.lists + ((size_t)q * g.segs + split * 2 + (lane >> 5)) * g.seg_cap;
         dense[ct] = DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr;
     }
-    const int ntile = (int)((g.chunk_rows + kStatRows - 1) / kStatRows), D16 = g.D / 16;
-    // the pieces this thread brings: piece i is step sk[i] of row sr[i] of the tile
-    const uint8_t* X = static_cast<const uint8_t*>(g.vectors);
-    int sr[kPieces], sk[kPieces];
-    uint32_t slot[kPieces];
-    bool mine[kPieces];
-    uint64_t id[kPieces], hid;                 // vectors of those rows; of row tid (the norms)
-    const uint64_t move = ((uint64_t)splits * kStatRows) % g.N * g.step % g.N;
-#pragma unroll
-    for (int i = 0; i < kPieces; ++i) {
-        const int e = i * kBfThreads + tid;
-        mine[i] = e < kStatRows * KS;
-        // rows four apart within a wavefront's instruction, so that row ^ step takes all sixteen bank groups
-        const int r = e / KS;
-        sk[i] = e - r * KS;
-        sr[i] = KS == 8 ? (r & 32) | (r & 7) << 2 | (r >> 3 & 3) : r & (kStatRows - 1);
-        slot[i] = (((uint32_t)sr[i] >> 5) * KS + sk[i]) * 64u + (((uint32_t)sr[i] & 31u) ^ (uint32_t)sk[i]);
-        id[i] = ((g.chunk_pos + (uint64_t)split * kStatRows + sr[i]) % g.N) * g.step % g.N;
-    }
-    hid = ((g.chunk_pos + (uint64_t)split * kStatRows + (tid & (kStatRows - 1))) % g.N) * g.step % g.N;
-    u32x4 piece[kPieces];
+    const int ntile = (int)((g.chunk_rows + kStatRows - 1) / kStatRows);
+    TileRows<KS, kStatRows> rows;
+    rows.start(g, split);
     float hx = 0.0f;
-    auto fetch = [&](int t) {                  // tile t, then the ids move on to tile t + splits
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const u32x4 zero = {0u, 0u, 0u, 0u};
-            const u32x4 v = reinterpret_cast<const u32x4*>(X + id[i] * (uint64_t)g.D)[sk[i] < D16 ? sk[i] : 0];
-            piece[i] = sk[i] < D16 ? v : zero;
-            id[i] += move;
-            id[i] -= id[i] >= g.N ? g.N : 0;
-        }
-        hx = (int64_t)t * kStatRows + (tid & (kStatRows - 1)) < g.chunk_rows ? g.xhalf[hid] : __builtin_inff();   // such rows enter no list
-        hid += move;
-        hid -= hid >= g.N ? g.N : 0;
+    auto fetch = [&](int t) {
+        const uint64_t h = rows.fetch(g);
+        hx = (int64_t)t * kStatRows + (tid & (kStatRows - 1)) < g.chunk_rows ? g.xhalf[h] : __builtin_inff();   // such rows enter no list
     };
-    fetch(split);                              // (past the last tile: some vectors, unused; always loading keeps them in registers)
+    fetch(split);
     int buf = 0;
     for (int t = split; t < ntile; t += splits, buf ^= 1) {
+        u32x4* xs = reinterpret_cast<u32x4*>(smem + buf * kTileBytes);
+        float* hs = reinterpret_cast<float*>(smem + 2 * kTileBytes) + buf * kStatRows;
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
+        for (int i = 0; i < TileRows<KS, kStatRows>::kPieces; ++i) {
             u32x4 w0, w1;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t b = piece[i][j];
+                const uint32_t b = rows.piece[i][j];
                 const uint32_t p0 = pack2((float)(b & 0xffu), (float)((b >> 8) & 0xffu)), p1 = pack2((float)((b >> 16) & 0xffu), (float)(b >> 24));
                 if (j < 2) { w0[2 * j] = p0; w0[2 * j + 1] = p1; }
                 else { w1[2 * j - 4] = p0; w1[2 * j - 3] = p1; }
             }
-            if (mine[i]) {
-                reinterpret_cast<u32x4*>(xs[buf])[slot[i]] = w0;
-                reinterpret_cast<u32x4*>(xs[buf])[slot[i] + 32] = w1;
+            const uint32_t r = (uint32_t)rows.row[i], ks = (uint32_t)rows.step[i];
+            const uint32_t slot = ((r >> 5) * KS + ks) * 64u + ((r & 31u) ^ ks);
+            if (rows.mine[i]) {
+                xs[slot] = w0;
+                xs[slot + 32] = w1;
             }
         }
-        if (tid < kStatRows) hs[buf][tid] = -hx;
+        if (tid < kStatRows) hs[tid] = -hx;
         __syncthreads();                       // the tile before the last is read by nobody any more: one barrier per tile
         fetch(t + splits);
 #pragma unroll
@@ -437,17 +495,26 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
             v16f c;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float4 h = *reinterpret_cast<const float4*>(&hs[buf][rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                const float4 h = *reinterpret_cast<const float4*>(&hs[rt * 32 + 8 * i + 4 * (lane >> 5)]);
                 c[4 * i] = h.x; c[4 * i + 1] = h.y; c[4 * i + 2] = h.z; c[4 * i + 3] = h.w;
             }
             v16f acc0 = c, acc1 = c;
+            if (two) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const bf16x8 a = reinterpret_cast<const bf16x8*>(xs[buf])[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 a = reinterpret_cast<const bf16x8*>(xs)[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
 #pragma unroll
-                for (int p = 0; p < QP; ++p) {
-                    acc0 = mfma(a, bq[p][0][ks], acc0);
-                    acc1 = mfma(a, bq[p][1][ks], acc1);
+                    for (int p = 0; p < 2; ++p) {
+                        acc0 = mfma(a, bq[p][0][ks], acc0);
+                        acc1 = mfma(a, bq[p][1][ks], acc1);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const bf16x8 a = reinterpret_cast<const bf16x8*>(xs)[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
+                    acc0 = mfma(a, bq[0][0][ks], acc0);
+                    acc1 = mfma(a, bq[0][1][ks], acc1);
                 }
             }
             const uint32_t row0 = (uint32_t)t * kStatRows + rt * 32 + 4 * (lane >> 5);
@@ -461,6 +528,141 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
             const int64_t q = q0 + ct * 32 + (lane & 31);
             g.seg_count[(size_t)q * g.segs + split * 2 + (lane >> 5)] = count[ct];
         }
+    }
+}
+
+// Byte vectors of at most 128 dimensions and queries of bytes: both less 128, which changes no distance, on the int8 matrix cores at
+// twice the bf16 rate, exactly.  A wavefront keeps 128 queries in registers, the workgroup's 512 share the database
+// tiles that stream through LDS as they are in memory but for the sign bit, two in turn.
+// Per 32 vectors a wavefront reads 4 KB of fragments and 4 of what the sums start from for 16 matrix instructions of 32 cycles:
+// half the LDS rate.  The sums of 64 queries are looked at (eight maxima per 16) while the next 64 queries' are formed, three vector
+// instructions behind each matrix instruction.  488,000 vectors x 10,000 queries that pass nothing: 493 us, 2.5 P operations a
+// second (maxima behind the matrix instructions: 525; without the loads 450, the matrix cores busy 62 % at the 2.0 GHz the
+// card then runs at).
+template <int KS, bool DENSE>
+__device__ __forceinline__ void filter_as_bytes(const BruteArgs& g, unsigned char* smem, int split, int64_t first_query) {
+    constexpr int KB = KS / 2, NC = 4, kTileBytes = kByteRows * KS * 16;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, splits = g.splits;
+    const int64_t q0 = first_query + wave * (NC * 32);
+    const bool active = q0 < g.nq;             // (else the wavefront only brings vectors)
+    i32x4 bq[NC][KB];
+    int from[NC];
+    uint32_t count[NC];
+#pragma unroll
+    for (int ct = 0; ct < NC; ++ct) {
+        count[ct] = 0;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) bq[ct][kb] = reinterpret_cast<const i32x4*>(g.qbytes)[((q0 / 32 + ct) * KB + kb) * kWave + lane];
+        const float f = DENSE ? 0.0f : keep_from(g, q0 + ct * 32 + (lane & 31));
+        from[ct] = f < 1e9f ? (int)ceilf(f) : 0x7fffffff;                     // (values are whole)
+    }
+    auto take = [&](const v16i& acc, auto ct, uint32_t row0) {
+        const int64_t q = q0 + ct * 32 + (lane & 31);
+        take_tile<DENSE>(acc, from[ct], row0, DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr,
+                         g.lists + ((size_t)q * g.segs + split * 2 + (lane >> 5)) * g.seg_cap, g.seg_cap, count[ct]);
+    };
+    auto largest = [](const v16i& acc) {
+        int top = larger(acc[0], acc[1]);
+#pragma unroll
+        for (int r = 2; r < 16; r += 2) top = larger(larger(acc[r], acc[r + 1]), top);
+        return top;
+    };
+    constexpr std::integral_constant<int, 0> c0;
+    constexpr std::integral_constant<int, 2> c2;
+    constexpr std::integral_constant<int, 3> c3;
+    const int ntile = (int)((g.chunk_rows + kByteRows - 1) / kByteRows);
+    TileRows<KS, kByteRows> rows;
+    rows.start(g, split);
+    int hx = 0;
+    auto fetch = [&](int t) {
+        const uint64_t h = rows.fetch(g);
+        hx = (int64_t)t * kByteRows + (tid & (kByteRows - 1)) < g.chunk_rows ? g.ihalf[h] : 0x40000000;   // such rows enter no list
+    };
+    fetch(split);
+    v16i acc[NC];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[2][r] = acc[3][r] = -0x7fffffff;         // (nothing to look at yet)
+    uint32_t row0 = 0;                                                       // of acc[2] and acc[3]
+    bool none = true;
+    int buf = 0;
+    for (int t = split; t < ntile; t += splits, buf ^= 1) {
+        u32x4* xs = reinterpret_cast<u32x4*>(smem + buf * kTileBytes);
+        int* hs = reinterpret_cast<int*>(smem + 2 * kTileBytes) + buf * kByteRows;
+#pragma unroll
+        for (int i = 0; i < TileRows<KS, kByteRows>::kPieces; ++i) {
+            const uint32_t r = (uint32_t)rows.row[i], ks = (uint32_t)rows.step[i];
+            if (rows.mine[i]) xs[((r >> 5) * KS + ks) * 32u + ((r & 31u) ^ ks)] = rows.piece[i] ^ 0x80808080u;
+        }
+        if (tid < kByteRows) hs[tid] = -hx;
+        __syncthreads();                       // the tile before the last is read by nobody any more: one barrier per tile
+        fetch(t + splits);
+        if (!active) continue;
+#pragma unroll 1
+        for (int rt = 0; rt < kByteRows / 32; ++rt) {
+            i32x4 a[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)    // half h of step kb is piece 2 kb + h of its row
+                a[kb] = reinterpret_cast<const i32x4*>(xs)[(rt * KB + kb) * kWave + (lane ^ (2 * kb + (lane >> 5)))];
+            v16i c;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const i32x4 h = *reinterpret_cast<const i32x4*>(&hs[rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                c[4 * i] = h[0]; c[4 * i + 1] = h[1]; c[4 * i + 2] = h[2]; c[4 * i + 3] = h[3];
+            }
+            // sums of tiles ct and ct + 1; meanwhile the largest of tiles was and was + 1
+            auto form = [&](auto ct, auto was, uint32_t was_row0, bool look) {
+                acc[ct] = c;
+                acc[ct + 1] = c;
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) {
+                    acc[ct] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[kb], bq[ct][kb], acc[ct], 0, 0, 0);
+                    acc[ct + 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[kb], bq[ct + 1][kb], acc[ct + 1], 0, 0, 0);
+                }
+                const int x = largest(acc[was]), y = largest(acc[was + 1]);
+                const bool found = DENSE ? look : (x >= from[was]) | (y >= from[was + 1]);
+#pragma unroll
+                for (int i = 0; i < 2 * KB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+                }
+                if (found) {
+                    take(acc[was], was, was_row0);
+                    take(acc[was + 1], std::integral_constant<int, was + 1>{}, was_row0);
+                }
+            };
+            form(c0, c2, row0, !none);
+            none = false;
+            row0 = (uint32_t)t * kByteRows + rt * 32 + 4 * (lane >> 5);
+            form(c2, c0, row0, true);
+        }
+    }
+    if (!active) return;
+    if (!none) {
+        take(acc[2], c2, row0);
+        take(acc[3], c3, row0);
+    }
+    if (!DENSE) {
+#pragma unroll
+        for (int ct = 0; ct < NC; ++ct)
+            g.seg_count[(size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + split * 2 + (lane >> 5)] = count[ct];
+    }
+}
+
+template <int KS, bool DENSE>
+__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(BruteArgs g) {
+    constexpr int kTileBytes = kStatRows * KS * 32 > kByteRows * KS * 16 ? kStatRows * KS * 32 : kByteRows * KS * 16;
+    constexpr int kNorms = kStatRows > kByteRows ? kStatRows : kByteRows;
+    __shared__ __align__(16) unsigned char smem[2 * kTileBytes + 2 * kNorms * sizeof(float)];
+    int split, group;
+    place_of_workgroup(blockIdx.x, g.splits, (int)gridDim.x / g.splits, split, group);
+    const int64_t first_query = (int64_t)group * kStatQueries;
+    if (group_is_bytes(g, group)) {
+        filter_as_bytes<KS, DENSE>(g, smem, split, first_query);
+        return;
+    }
+    for (int64_t q = first_query; q < first_query + kStatQueries && q < g.nq; q += kStatQueries / 2) {
+        __syncthreads();                       // (the first half's last tile has been read)
+        filter_as_bf16<KS, DENSE>(g, smem, split, q);
     }
 }
 
@@ -776,7 +978,9 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     };
     bool done = divide(std::true_type{});
     for (int level = 0; level < 3 && !done; ++level) done = divide(std::false_type{});
-    const float keep = keep_up_to(g, qn, g.qshift[q], edge);
+    // (values of bytes against bytes are exact: half squared distances rounded down, but for a term of the query)
+    const bool exact = sizeof(Elem) == 1 && g.qbytes && group_is_bytes(g, (int)(q / kStatQueries));
+    const float keep = exact ? edge : keep_up_to(g, qn, g.qshift[q], edge);
     // ---- keep what can still be among the k nearest ---------------------------------------------------------------
     for (int e0 = 0; e0 < n; e0 += kBfThreads) {     // in place: entry e moves to a place <= e that has been read
         const int e = e0 + tid;
@@ -1027,7 +1231,7 @@ uint64_t gcd_u64(uint64_t a, uint64_t b) {
     return a;
 }
 
-// where the centre stands behind the N half norms, the largest norm, the word that says whether it is subtracted, and its norm where
+// where the centre (bytes: the whole half norms of the vectors less 128) stands behind the N half norms, the largest norm, the word that says whether it is subtracted, and its norm where
 // it is not: at a 16-byte boundary
 size_t centre_at(uint64_t N) { return (size_t)(N + 6) / 4 * 4; }
 
@@ -1048,12 +1252,12 @@ Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
     p.KS = (D + 15) / 16;
     p.stationary = elem_bytes == 1 && p.KS <= 8;
     if (p.stationary && p.KS != 6) p.KS = 8;                        // compiled for 96 and 128 dimensions
-    const int tile = p.stationary ? 256 : kGenQueries;
+    const int tile = p.stationary ? kStatQueries : kGenQueries;
     p.batch = nq < 16384 ? nq : 16384;
     p.batch_pad = round_up(p.batch, tile);
     p.groups = (int)(p.batch_pad / tile);
-    // as many workgroups as are resident at once (three or two per compute unit): no second round of a few
-    const int slots = p.stationary ? 768 : 512;
+    // as many workgroups as are resident at once (two per compute unit): no second round of a few
+    const int slots = 512;
     p.splits = p.groups >= slots ? 1 : slots / p.groups;
     if (p.splits > 8) p.splits -= p.splits % 8;
     p.segs = p.splits * (p.stationary ? 2 : 8);
@@ -1093,6 +1297,7 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.keep = c.take<float>(p.batch_pad);
     v.best_count = c.take<uint32_t>(p.batch_pad);
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
+    v.qbytes = p.stationary ? c.take<uint8_t>((size_t)p.batch_pad * p.KS * 16) : nullptr;
     v.dense = c.take<float>((size_t)p.batch_pad * kDense);
     v.seg_count = c.take<uint32_t>((size_t)p.batch_pad * p.segs);
     v.lists = c.take<uint2>((size_t)p.batch * p.segs * p.seg_cap);
@@ -1106,11 +1311,9 @@ template <typename Elem, bool DENSE>
 void launch_filter(const Plan& p, const BruteArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)(p.splits * p.groups)), block(kBfThreads);
     if (p.stationary && p.KS == 6) {
-        hipLaunchKernelGGL((bf_filter_stationary_kernel<6, 1, DENSE>), grid, block, 0, s, a);
-        hipLaunchKernelGGL((bf_filter_stationary_kernel<6, 2, DENSE>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<6, DENSE>), grid, block, 0, s, a);
     } else if (p.stationary) {
-        hipLaunchKernelGGL((bf_filter_stationary_kernel<8, 1, DENSE>), grid, block, 0, s, a);
-        hipLaunchKernelGGL((bf_filter_stationary_kernel<8, 2, DENSE>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((bf_filter_stationary_kernel<8, DENSE>), grid, block, 0, s, a);
     } else {
         hipLaunchKernelGGL((bf_filter_kernel<Elem, DENSE>), grid, block, 0, s, a);
     }
@@ -1160,7 +1363,7 @@ uint64_t brute_force_step(uint64_t N) {
     return step;
 }
 
-size_t brute_force_norm_words(uint64_t N, int D) { return centre_at(N) + (size_t)D; }
+size_t brute_force_norm_words(uint64_t N, int D, int elem_bytes) { return centre_at(N) + (elem_bytes == 1 ? (size_t)N : (size_t)D); }
 
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s) {
     const dim3 grid((unsigned)(N / 16 + 1 < 2048 ? N / 16 + 1 : 2048)), block(kBfThreads);
@@ -1168,13 +1371,13 @@ hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, in
     float* centre = out + centre_at(N);
     hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(3), 0, s, reinterpret_cast<uint32_t*>(out) + N);
     if (elem_bytes == 1) {
-        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, err.dot, err.norm, out);
+        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, err.dot, err.norm, out, reinterpret_cast<int*>(centre));
     } else {
         const float* x = static_cast<const float*>(vectors);
         const uint64_t step = brute_force_step(N);
         hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((D + kWave - 1) / kWave)), block, 0, s, x, N, step, D, centre);
         hipLaunchKernelGGL(use_centre_kernel, dim3(1), dim3(1024), 0, s, x, N, step, D, centre, reinterpret_cast<uint32_t*>(out) + N + 1, out + N + 2);
-        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, err.dot, err.norm, out);
+        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, err.dot, err.norm, out, nullptr);
     }
     return hipGetLastError();
 }
@@ -1186,6 +1389,7 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     carve(p, k, static_cast<unsigned char*>(workspace), &a);
     a.vectors = vectors; a.xhalf = half_norms; a.N = N; a.D = D; a.k = k; a.KS = p.KS;
     a.centre = elem_bytes == 4 ? half_norms + centre_at(N) : nullptr;
+    a.ihalf = elem_bytes == 1 ? reinterpret_cast<const int*>(half_norms + centre_at(N)) : nullptr;
     a.use_centre = reinterpret_cast<const uint32_t*>(half_norms) + N + 1;
     a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
     a.step = brute_force_step(N);

@@ -812,7 +812,7 @@ int pqt_brute_force(pqt_index* ix, const float* queries, int64_t nq, int k, int6
         ix->bf_ws_bytes = need;
     }
     if (!ix->half_norms) {
-        HIP_TRY(hipMalloc(reinterpret_cast<void**>(&ix->half_norms), sizeof(float) * pqt::brute_force_norm_words(ix->N, (int)ix->D)));
+        HIP_TRY(hipMalloc(reinterpret_cast<void**>(&ix->half_norms), sizeof(float) * pqt::brute_force_norm_words(ix->N, (int)ix->D, ix->vector_elem_bytes)));
         HIP_TRY(pqt::launch_half_norms(ix->vectors, ix->vector_elem_bytes, ix->N, (int)ix->D, ix->half_norms, stream));
     }
     HIP_TRY(pqt::launch_brute_force(ix->vectors, ix->half_norms, ix->vector_elem_bytes, ix->N, (int)ix->D, queries, nq, k, ix->bf_ws,

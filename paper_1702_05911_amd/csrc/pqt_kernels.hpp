@@ -201,6 +201,7 @@ struct BruteArgs {
     const float* queries;         // nq x D
     const void* vectors;          // N x D
     const float* xhalf;           // what a vector's values start from; the largest norm, use_centre, the centre's norm
+    const int* ihalf;             // bytes: the half squared norms of the vectors less 128, rounded down
     const float* centre;          // D: what norms and queries are taken relative to (null for bytes)
     const uint32_t* use_centre;   // 1: the vectors too
     int64_t* out_ids;             // nq x k
@@ -213,13 +214,14 @@ struct BruteArgs {
     // workspace
     uint32_t* control;
     uint32_t* flagged;            // nq: 1 = left to the exact scan
-    uint32_t* second;             // 1 = a query of the tile of 32 has a second bf16 piece
+    uint32_t* second;             // per tile of 32 queries: has one a second bf16 piece, or a value that is not a byte
     uint32_t* todo;               // those queries
     float* qnorm;                 // ||q||
     float* qshift;                // what makes a value one of centred vectors
     float* keep;                  // largest value that still matters
     uint32_t* best_count;         // entries of best
     uint16_t* qfrag;              // queries, two bf16 pieces, operand layout
+    uint8_t* qbytes;              // the same less 128 as bytes, operand layout (byte vectors of at most 128 dimensions, else null)
     float* dense;                 // values of the first chunk, a row per query
     int splits;                   // workgroups that share a query group's database tiles
     int segs, seg_cap;            // lists per query and entries per list
@@ -231,7 +233,7 @@ struct BruteArgs {
 // workspace of one call, in bytes
 size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k);
 // what the filter needs to know of the vectors, whatever the queries: half squared norms, the largest norm, the centre
-size_t brute_force_norm_words(uint64_t N, int D);
+size_t brute_force_norm_words(uint64_t N, int D, int elem_bytes);
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s);
 // the k nearest of N vectors (4: fp32, 1: uint8 elements) to every query; k <= min(N, 256)
 hipError_t launch_brute_force(const void* vectors, const float* half_norms, int elem_bytes, uint64_t N, int D, const float* queries,

@@ -1098,6 +1098,44 @@ def test_brute_force_edges(pqt, kind, N, D, nq, k):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("N, D, nq, k, other", [
+    (127, 128, 512, 20, ()),                         # less than a tile of 128 vectors, exactly one group of 512 queries
+    (4096 + 129, 96, 513, 100, ()),                  # one vector past a tile of the second chunk; one query past a group
+    (9001, 112, 640, 10, (600,)),                    # padded dimensions; the first group of bytes, the second not
+    (9001, 48, 1024, 10, (255, 1023)),               # the first half of either group, the second half
+    (30_000, 128, 130, 250, (3,)),                   # one wavefront's 128 queries and two more, not of bytes
+])
+@pytest.mark.parametrize("value", [-1.0, 256.0, 127.5, 1e-3])
+def test_brute_force_bytes_and_others(pqt, N, D, nq, k, other, value):
+    """Byte vectors searched by groups of 512 queries of bytes, and by groups in which one value is not a byte (negative, too
+    large, halves with one bf16 piece, with two).  Extreme bytes too: 0 and 255 less 128 are both ends of a signed byte.
+    Whole numbers and halves are exact in fp32: ids and distances are those of float64; 1e-3 leaves (D + 2) 2^-24."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda")
+    X[::7] = torch.where(X[::7] < 128, 0, 255)
+    Y = torch.randint(0, 256, (nq, D), generator=gen, device="cuda").float()
+    Y[::3] = torch.where(Y[::3] < 128, 0.0, 255.0)
+    for q in other:
+        Y[q, q % D] = value
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X.to(torch.uint8))
+        ids, d = pqt.pqt_brute_force(ix, Y, k)
+        x, y = X.double(), Y.double()
+        true = (x * x).sum(1)[None] - 2 * (y @ x.T) + (y * y).sum(1)[:, None]      # below 2^53 / 4: exact but for 1e-3
+        exact = torch.ones(nq, dtype=torch.bool, device="cuda")
+        exact[list(other)] = value != 1e-3
+        want = (true * N + torch.arange(N, device="cuda")).sort(1).indices[:, :k]
+        assert torch.equal(ids[exact], want[exact]) and torch.equal(d[exact].double(), true.gather(1, want)[exact])
+        rest = true[~exact].gather(1, ids[~exact])
+        bound = (D + 2) * 2.0 ** -24
+        assert (d[~exact].double() - rest).abs().le(bound * rest).all()
+        assert (rest - true[~exact].sort(1).values[:, :k]).abs().le(2 * bound * rest).all()
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def _vectors_only_index(pqt, N, D):
     """An index that holds no more than a collection to search exactly: one bin."""
     return pqt.pqt_index_from_arrays(dict(
