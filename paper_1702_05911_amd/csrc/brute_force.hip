@@ -26,17 +26,23 @@
 //   * bf_select_kernel, one workgroup per query, bounds the k-th smallest value by a 1024-bin histogram and keeps what
 //     can still matter; after the last chunk it computes the exact distances sum (y - x)^2 of that list
 //     (k and a few more) in fp32 and sorts them.
-// Chunks grow by a factor, so that about k times that factor pairs pass per chunk and query.  A query whose lists
+// What a vector's value may be at most is a guess between chunks: of the k nearest, about k p are among the first p N vectors, and
+// hardly ever more than rank_at() says, six deviations more; the bound is that of the rank-th smallest value so far, not of
+// the k-th.  It never grows, so the list always holds everything up to it, and if in the end k values are
+// up to it, those nearest were all kept; if not, the query is searched as one whose lists overflow.  A third of the pairs pass
+// that the k-th smallest value lets through (10,000 queries x 1M x 128 bytes, k = 100: 2.35 -> 1.8 ms).
+// A query whose lists
 // overflow (more than about two thousand vectors tied with the k-th, or non-finite data) is searched by bf_scan_kernel, exact
 // distances to all vectors.
 //
-// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 2.4 ms (the contraction 1.86, 0.5 of it for pairs that pass; selection
-// 0.46); as one bf16 piece 3.5 ms (contraction 3.0), with
+// Measured, 10,000 queries x 1M x 128 bytes, k = 100: 1.8 ms (the contraction 1.45, selection
+// 0.35); as one bf16 piece, all up to the k-th smallest so far kept, 3.5 ms (contraction 3.0), with
 // the fp32 matrix cores and all distances written and read back 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
 // 0.80 ms (contraction 0.73 = 0.92 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
 // Data on which a bound by the largest norm of all, a list of 2 k + 256 and a scan by one workgroup per query took 78 ms
 // (the same floats, 777 queries; fp32 matrix cores 2.7): one vector of norm 300 among unit vectors 1.0 ms, an offset of 10 1.0,
 // 1,000 copies of one vector 1.2.
+#include <cmath>
 #include <type_traits>
 
 #include "pqt_device.hpp"
@@ -328,13 +334,14 @@ __device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {
     return q >= g.nq || g.flagged[q] ? __builtin_inff() : -g.keep[q];
 }
 
-// Are the queries of this group of the stationary kernel all whole numbers 0 .. 255?
-__device__ __forceinline__ bool group_is_bytes(const BruteArgs& g, int group) {
+// What the queries of this group of the stationary kernel are, and whether they are all whole numbers 0 .. 255.
+__device__ __forceinline__ uint32_t query_state(const BruteArgs& g, int group) {
     uint32_t state = 0;
 #pragma unroll
     for (int tile = 0; tile < kStatQueries / 32; ++tile) state |= g.second[group * (kStatQueries / 32) + tile];
-    return !(state & kNotBytes);
+    return state;
 }
+__device__ __forceinline__ bool group_is_bytes(const BruteArgs& g, int group) { return !(query_state(g, group) & kNotBytes); }
 
 // One 32 x 32 tile of accumulators: lane l holds query column l % 32 and database rows 8 * (r / 4) + 4 * (l / 32) + r % 4.
 // DENSE: all values go to out (s~ of the query's row of kDense values).  Else those that reach `from` are appended to the
@@ -363,7 +370,7 @@ __device__ __forceinline__ void take_tile(const Acc& acc, Value from, uint32_t r
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
                     if (acc[4 * i + c] >= from) {
-                        if (count < (uint32_t)cap) list[count] = make_uint2(row0 + 8 * i + c, __float_as_uint((float)-acc[4 * i + c]));
+                        list[count < (uint32_t)cap ? count : cap - 1] = make_uint2(row0 + 8 * i + c, __float_as_uint((float)-acc[4 * i + c]));
                         ++count;
                     }
             }
@@ -383,7 +390,7 @@ __device__ __forceinline__ void place_of_workgroup(int b, int splits, int groups
     }
 }
 
-// The rows of the database tiles a workgroup of the kernels below brings into LDS: tiles of ROWS vectors, every splits-th
+// The rows of the database tiles a workgroup of the kernels below brings into LDS: tiles of up to ROWS vectors, every splits-th
 // of the chunk, as 16-byte pieces (KS of them, 16 dimensions each) that a thread has the same places of in every tile.
 template <int KS, int ROWS>
 struct TileRows {
@@ -393,21 +400,21 @@ struct TileRows {
     u32x4 piece[kPieces];
     uint64_t at[kPieces], hid, move;           // where in the database those pieces are; the vector of row tid
     int D16;
-    __device__ __forceinline__ void start(const BruteArgs& g, int split) {
+    __device__ __forceinline__ void start(const BruteArgs& g, int split, int tile_rows) {
         const int tid = threadIdx.x;
         D16 = g.D / 16;
-        move = ((uint64_t)g.splits * ROWS) % g.N * g.step % g.N;
+        move = ((uint64_t)g.splits * tile_rows) % g.N * g.step % g.N;
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             const int e = i * kBfThreads + tid;
-            mine[i] = e < ROWS * KS;
             // rows four apart within a wavefront's instruction, so that row ^ step takes all sixteen bank groups
             const int r = e / KS;
             step[i] = e - r * KS;
             row[i] = KS == 8 ? (r & ~31) | (r & 7) << 2 | (r >> 3 & 3) : r & (ROWS - 1);
-            at[i] = ((g.chunk_pos + (uint64_t)split * ROWS + row[i]) % g.N) * g.step % g.N * (uint64_t)g.D + (step[i] < D16 ? step[i] * 16 : 0);
+            mine[i] = e < ROWS * KS && row[i] < tile_rows;
+            at[i] = ((g.chunk_pos + (uint64_t)split * tile_rows + row[i]) % g.N) * g.step % g.N * (uint64_t)g.D + (step[i] < D16 ? step[i] * 16 : 0);
         }
-        hid = ((g.chunk_pos + (uint64_t)split * ROWS + (tid & (ROWS - 1))) % g.N) * g.step % g.N;
+        hid = ((g.chunk_pos + (uint64_t)split * tile_rows + (tid & (ROWS - 1))) % g.N) * g.step % g.N;
     }
     // the next tile's pieces, then the ids move on; past the last tile: some vectors, unused (always loading keeps the pieces in
     // registers).  Returns the vector of row tid.
@@ -427,39 +434,33 @@ struct TileRows {
     }
 };
 
-// Byte vectors of at most 128 dimensions, queries that are not all bytes: a wavefront keeps 64 queries in registers (KS steps,
-// two pieces) for the whole launch, and 256 queries share the database tiles that stream through LDS, two in turn.
+// Byte vectors of at most 128 dimensions, queries that are not all bytes: a wavefront keeps 64 queries (KS steps,
+// two pieces), or 128 of one piece, in registers for the whole launch, and the workgroup's 256 or 512 share the database tiles that
+// stream through LDS, two in turn.
 // LDS: 16 bytes of (row, step, half) lie in slot row ^ step of the fragment's half: eight lanes bring a row's eight steps
 // and would all hit the same banks.
-template <int KS, bool DENSE>
+template <int KS, int QP, bool DENSE>
 __device__ __forceinline__ void filter_as_bf16(const BruteArgs& g, unsigned char* smem, int split, int64_t first_query) {
-    constexpr int kTileBytes = kStatRows / 32 * KS * kFrag * 2;
+    constexpr int NC = 4 / QP, kTileBytes = kStatRows / 32 * KS * kFrag * 2;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, splits = g.splits;
-    const int64_t q0 = first_query + wave * 64;
-    uint32_t second = 0;
+    const int64_t q0 = first_query + wave * (NC * 32);
+    const bool active = q0 < g.nq;             // (else the wavefront only brings vectors)
+    bf16x8 bq[QP][NC][KS];
+    float from[NC];
+    uint32_t count[NC];
 #pragma unroll
-    for (int tile = 0; tile < 8; ++tile) second |= g.second[first_query / 32 + tile];
-    const bool two = second & kSecondPiece;
-    bf16x8 bq[2][2][KS];
-    float from[2];
-    uint32_t count[2] = {0, 0};
-    uint2* list[2];
-    float* dense[2];
+    for (int ct = 0; ct < NC; ++ct) {
+        count[ct] = 0;
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-        const int64_t q = q0 + ct * 32 + (lane & 31);
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
+        for (int p = 0; p < QP; ++p)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 bq[p][ct][ks] = reinterpret_cast<const bf16x8*>(g.qfrag)[((q0 / 32 + ct) * KS + ks) * (2 * kFrag / 8) + p * (kFrag / 8) + lane];
-        from[ct] = DENSE ? 0.0f : keep_from(g, q);
-        list[ct] = g.lists + ((size_t)q * g.segs + split * 2 + (lane >> 5)) * g.seg_cap;
-        dense[ct] = DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr;
+        from[ct] = DENSE ? 0.0f : keep_from(g, q0 + ct * 32 + (lane & 31));
     }
     const int ntile = (int)((g.chunk_rows + kStatRows - 1) / kStatRows);
     TileRows<KS, kStatRows> rows;
-    rows.start(g, split);
+    rows.start(g, split, kStatRows);
     float hx = 0.0f;
     auto fetch = [&](int t) {
         const uint64_t h = rows.fetch(g);
@@ -490,45 +491,43 @@ __device__ __forceinline__ void filter_as_bf16(const BruteArgs& g, unsigned char
         if (tid < kStatRows) hs[tid] = -hx;
         __syncthreads();                       // the tile before the last is read by nobody any more: one barrier per tile
         fetch(t + splits);
-#pragma unroll
+        if (!active) continue;
+#pragma unroll 1
         for (int rt = 0; rt < kStatRows / 32; ++rt) {
-            v16f c;
+            const uint32_t row0 = (uint32_t)t * kStatRows + rt * 32 + 4 * (lane >> 5);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 h = *reinterpret_cast<const float4*>(&hs[rt * 32 + 8 * i + 4 * (lane >> 5)]);
-                c[4 * i] = h.x; c[4 * i + 1] = h.y; c[4 * i + 2] = h.z; c[4 * i + 3] = h.w;
-            }
-            v16f acc0 = c, acc1 = c;
-            if (two) {
+            for (int c2 = 0; c2 < NC; c2 += 2) {
+                if (c2 && q0 + c2 * 32 >= g.nq) break;
+                asm volatile("" ::: "memory");               // (read from LDS again: both halves' operands do not fit the registers)
+                v16f c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 h = *reinterpret_cast<const float4*>(&hs[rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                    c[4 * i] = h.x; c[4 * i + 1] = h.y; c[4 * i + 2] = h.z; c[4 * i + 3] = h.w;
+                }
+                v16f acc[2] = {c, c};
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     const bf16x8 a = reinterpret_cast<const bf16x8*>(xs)[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        acc0 = mfma(a, bq[p][0][ks], acc0);
-                        acc1 = mfma(a, bq[p][1][ks], acc1);
+                    for (int p = 0; p < QP; ++p) {
+                        acc[0] = mfma(a, bq[p][c2][ks], acc[0]);
+                        acc[1] = mfma(a, bq[p][c2 + 1][ks], acc[1]);
                     }
                 }
-            } else {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    const bf16x8 a = reinterpret_cast<const bf16x8*>(xs)[(rt * KS + ks) * (kFrag / 8) + (lane ^ ks)];
-                    acc0 = mfma(a, bq[0][0][ks], acc0);
-                    acc1 = mfma(a, bq[0][1][ks], acc1);
+                for (int u = 0; u < 2; ++u) {
+                    const int64_t q = q0 + (c2 + u) * 32 + (lane & 31);
+                    take_tile<DENSE>(acc[u], from[c2 + u], row0, DENSE && q < g.nq ? g.dense + (size_t)q * kDense : nullptr,
+                                     g.lists + ((size_t)q * g.segs + split * 2 + (lane >> 5)) * g.seg_cap, g.seg_cap, count[c2 + u]);
                 }
             }
-            const uint32_t row0 = (uint32_t)t * kStatRows + rt * 32 + 4 * (lane >> 5);
-            take_tile<DENSE>(acc0, from[0], row0, dense[0], list[0], g.seg_cap, count[0]);
-            take_tile<DENSE>(acc1, from[1], row0, dense[1], list[1], g.seg_cap, count[1]);
         }
     }
-    if (!DENSE) {
+    if (DENSE || !active) return;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            const int64_t q = q0 + ct * 32 + (lane & 31);
-            g.seg_count[(size_t)q * g.segs + split * 2 + (lane >> 5)] = count[ct];
-        }
-    }
+    for (int ct = 0; ct < NC; ++ct)
+        g.seg_count[(size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + split * 2 + (lane >> 5)] = count[ct];
 }
 
 // Byte vectors of at most 128 dimensions and queries of bytes: both less 128, which changes no distance, on the int8 matrix cores at
@@ -570,13 +569,13 @@ __device__ __forceinline__ void filter_as_bytes(const BruteArgs& g, unsigned cha
     constexpr std::integral_constant<int, 0> c0;
     constexpr std::integral_constant<int, 2> c2;
     constexpr std::integral_constant<int, 3> c3;
-    const int ntile = (int)((g.chunk_rows + kByteRows - 1) / kByteRows);
+    const int tile_rows = g.tile_rows, ntile = (int)((g.chunk_rows + tile_rows - 1) / tile_rows);
     TileRows<KS, kByteRows> rows;
-    rows.start(g, split);
+    rows.start(g, split, tile_rows);
     int hx = 0;
     auto fetch = [&](int t) {
         const uint64_t h = rows.fetch(g);
-        hx = (int64_t)t * kByteRows + (tid & (kByteRows - 1)) < g.chunk_rows ? g.ihalf[h] : 0x40000000;   // such rows enter no list
+        hx = (int64_t)t * tile_rows + (tid & (kByteRows - 1)) < g.chunk_rows ? g.ihalf[h] : 0x40000000;   // such rows enter no list
     };
     fetch(split);
     v16i acc[NC];
@@ -598,7 +597,7 @@ __device__ __forceinline__ void filter_as_bytes(const BruteArgs& g, unsigned cha
         fetch(t + splits);
         if (!active) continue;
 #pragma unroll 1
-        for (int rt = 0; rt < kByteRows / 32; ++rt) {
+        for (int rt = 0; rt < tile_rows / 32; ++rt) {
             i32x4 a[KB];
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)    // half h of step kb is piece 2 kb + h of its row
@@ -632,7 +631,7 @@ __device__ __forceinline__ void filter_as_bytes(const BruteArgs& g, unsigned cha
             };
             form(c0, c2, row0, !none);
             none = false;
-            row0 = (uint32_t)t * kByteRows + rt * 32 + 4 * (lane >> 5);
+            row0 = (uint32_t)t * tile_rows + rt * 32 + 4 * (lane >> 5);
             form(c2, c0, row0, true);
         }
     }
@@ -660,9 +659,13 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
         filter_as_bytes<KS, DENSE>(g, smem, split, first_query);
         return;
     }
+    if (!(query_state(g, group) & kSecondPiece)) {
+        filter_as_bf16<KS, 1, DENSE>(g, smem, split, first_query);
+        return;
+    }
     for (int64_t q = first_query; q < first_query + kStatQueries && q < g.nq; q += kStatQueries / 2) {
         __syncthreads();                       // (the first half's last tile has been read)
-        filter_as_bf16<KS, DENSE>(g, smem, split, q);
+        filter_as_bf16<KS, 2, DENSE>(g, smem, split, q);
     }
 }
 
@@ -844,7 +847,7 @@ constexpr int kBest = 2048;            // entries kept of a query between chunks
 // Entries: bits of s~ << 32 | place in the database order.  (Bins are equal pieces of the value range, not of the bit
 // patterns: s~ changes sign, and most of the patterns between its smallest and largest value are next to zero.)
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int dense, int last) {
+__global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int dense, int last, int rank) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // kDense
     __shared__ uint32_t hist[kSelectBins];
@@ -909,15 +912,23 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         give_up();
         return;
     }
-    // ---- an upper bound of the k-th smallest: the end of its bin ---------------------------------------------------
+    const float before = dense ? __builtin_inff() : g.edge[q];                  // the bound so far: the list holds all up to it, and more
+    // a guess was too small: fewer than k vectors are up to it
+    if (last && n < k) {
+        give_up();
+        return;
+    }
+    // ---- an upper bound of the rank-th smallest: the end of its bin ------------------------------------------------
     // One histogram over the values' range; where a few long vectors stretch the range, so that the bin of the k-th holds many
     // more, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
     // among those that are divided.
-    const uint32_t few = (uint32_t)k + 128u;         // entries up to the bin's end that need no division
+    // entries up to the bin's end that need no division: what they cost is an exact distance each, or, before the last chunk,
+    // pairs that pass
+    const uint32_t few = last ? (uint32_t)k + 128u : (uint32_t)(rank + rank / 8 + 3);
     auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
     static_assert(kDense <= 32 * kBfThreads, "a bit per entry");
     uint32_t members = 0xffffffffu, below = 0u;
-    float edge = 0.0f;
+    float edge = before;
     auto divide = [&](auto all) {                    // one histogram; false: the bin's entries are to be divided
         constexpr bool ALL = decltype(all)::value;   // every entry is a member
         float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -958,7 +969,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
             uint32_t c = below + block_exclusive_sum(sum, part, total);
 #pragma unroll
             for (int j = 0; j < bpt; ++j) {
-                if (c < (uint32_t)k && (uint32_t)k <= c + h[j]) {
+                if (c < (uint32_t)rank && (uint32_t)rank <= c + h[j]) {
                     misc[2] = (uint32_t)(tid * bpt + j);
                     misc[5] = c;
                     misc[6] = c + h[j];
@@ -976,8 +987,26 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
             if (bin_of(value(e)) != bin) members &= ~(1u << u);
         return false;
     };
-    bool done = divide(std::true_type{});
-    for (int level = 0; level < 3 && !done; ++level) done = divide(std::false_type{});
+    if (n >= rank) {                                 // (else the list is as it was)
+        bool done = divide(std::true_type{});
+        for (int level = 0; level < 3 && !done; ++level) done = divide(std::false_type{});
+    }
+    if (edge > before) {                             // the bin's end, or the rank-th itself
+        edge = before;
+        if (last) {
+            __syncthreads();                         // (misc[2] has been read)
+            if (tid == 0) misc[2] = 0u;
+            __syncthreads();
+            uint32_t up_to = 0;
+            for (int e = tid; e < n; e += kBfThreads) up_to += value(e) <= before ? 1u : 0u;
+            atomicAdd(&misc[2], up_to);
+            __syncthreads();
+            if (misc[2] < (uint32_t)k) {             // the guess was too small
+                give_up();
+                return;
+            }
+        }
+    }
     // (values of bytes against bytes are exact: half squared distances rounded down, but for a term of the query)
     const bool exact = sizeof(Elem) == 1 && g.qbytes && group_is_bytes(g, (int)(q / kStatQueries));
     const float keep = exact ? edge : keep_up_to(g, qn, g.qshift[q], edge);
@@ -1003,6 +1032,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         for (int e = tid; e < n; e += kBfThreads) best[e] = keys[e];
         if (tid == 0) {
             g.best_count[q] = (uint32_t)n;
+            g.edge[q] = edge;
             g.keep[q] = keep;
         }
         return;
@@ -1237,17 +1267,26 @@ size_t centre_at(uint64_t N) { return (size_t)(N + 6) / 4 * 4; }
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
+// How many of the k nearest of N vectors the first `pos` places of the database order hold, hardly ever exceeded (less than once in
+// 10^8 for vectors in any order that the golden ratio knows nothing of).
+int rank_at(int k, double pos, double N) {
+    const double p = pos < N ? pos / N : 1.0, mean = k * p;
+    const double most = mean + 6.0 * std::sqrt(mean * (1.0 - p)) + 4.0;
+    return most < k ? (int)most : k;
+}
+
 // How one call is cut: sizes of the workspace's pieces and the launch shapes.
 struct Plan {
     bool stationary;
     int KS;
     int64_t batch, batch_pad;        // queries at a time, padded to whole workgroup tiles
     int groups, splits, segs, seg_cap;
-    int growth;
+    double growth;                   // chunks and what was there before them
+    int hits;                        // pairs that pass in a chunk
     int scan_queries, scan_grid;     // of the exact scan: queries and workgroups
 };
 
-Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
+Plan make_plan(int64_t nq, uint64_t N, int D, int elem_bytes, int k) {
     Plan p;
     p.KS = (D + 15) / 16;
     p.stationary = elem_bytes == 1 && p.KS <= 8;
@@ -1261,13 +1300,29 @@ Plan make_plan(int64_t nq, int D, int elem_bytes, int k) {
     p.splits = p.groups >= slots ? 1 : slots / p.groups;
     if (p.splits > 8) p.splits -= p.splits % 8;
     p.segs = p.splits * (p.stationary ? 2 : 8);
-    // Chunks grow by this factor, and about k times as many pairs pass per chunk and query.  A pair costs a wavefront some
-    // tens of cycles, a chunk more about 15 us: many queries take a small factor, few queries as large a one as the
-    // select workgroup's LDS allows (twice k * growth + the list kept so far).
-    const int most = 1600 / k < 2 ? 2 : (1600 / k > 64 ? 64 : 1600 / k);
-    p.growth = p.batch * k < 200000 ? most : (most < 4 ? most : 4);
+    // As many chunks, each larger by the same factor, as take the least time: a chunk costs a launch of either kernel and a
+    // look at every query's list, a pair that passes some hundred cycles of its wavefront, which takes 128 queries.  Bounded by
+    // the select workgroup's LDS (the pairs, twice the expected number, and the list kept so far).
+    p.growth = 2.0;
+    p.hits = k;
+    double least = 1e30;
+    const double waves = 512.0 * (p.stationary && p.batch < 384 ? (double)((p.batch + 127) / 128) : 4.0);
+    for (int chunks = 1; chunks <= 16 && N > kDense; ++chunks) {
+        const double growth = std::pow((double)N / kDense, 1.0 / chunks) * 1.001;
+        double time = 0.0, most = 0.0, pos = kDense;
+        for (int c = 0; c < chunks; ++c, pos *= growth) {
+            const double hits = rank_at(k, pos, (double)N) * (growth - 1.0);
+            time += 10.0 + 0.005 * (double)p.batch + 0.2 * hits * (double)p.batch / waves;
+            most = hits > most ? hits : most;
+        }
+        if (time < least && (most <= 1600.0 || growth <= 2.0)) {
+            least = time;
+            p.growth = growth;
+            p.hits = (int)most + 1;
+        }
+    }
     // room for the pairs that pass and for the ties that may be kept
-    p.seg_cap = 4 * ((k * p.growth + p.segs - 1) / p.segs) + 16 + kBest / p.segs;
+    p.seg_cap = 4 * ((p.hits + p.segs - 1) / p.segs) + 16 + kBest / p.segs;
     p.scan_queries = scan_lds(kScanQueries, D) <= 63 * 1024 ? kScanQueries : 1;      // (64 KB less what the kernel has itself)
     const int64_t most_items = (p.batch + p.scan_queries - 1) / p.scan_queries * kScanSplits;
     p.scan_grid = (int)(most_items < 1024 ? most_items : 1024);
@@ -1295,6 +1350,7 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.qnorm = c.take<float>(p.batch_pad);
     v.qshift = c.take<float>(p.batch_pad);
     v.keep = c.take<float>(p.batch_pad);
+    v.edge = c.take<float>(p.batch_pad);
     v.best_count = c.take<uint32_t>(p.batch_pad);
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
     v.qbytes = p.stationary ? c.take<uint8_t>((size_t)p.batch_pad * p.KS * 16) : nullptr;
@@ -1333,14 +1389,18 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
         hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(a.KS < 16 ? 256 : 1024), 0, s, a);
         for (uint64_t pos = 0; pos < a.N;) {
             const bool dense = pos == 0;
-            uint64_t rows = dense ? (uint64_t)kDense : pos * (uint64_t)p.growth;
+            uint64_t rows = dense ? (uint64_t)kDense : (uint64_t)((double)pos * (p.growth - 1.0));
+            if (rows < (uint64_t)kDense) rows = kDense;
             if (rows > a.N - pos) rows = a.N - pos;
             a.chunk_pos = pos;
             a.chunk_rows = (int64_t)rows;
+            // tiles of bytes: smaller where there would be fewer than workgroups
+            a.tile_rows = kByteRows;
+            while (a.tile_rows > 32 && rows < (uint64_t)a.tile_rows * p.splits) a.tile_rows /= 2;
             if (dense) launch_filter<Elem, true>(p, a, s);
             else launch_filter<Elem, false>(p, a, s);
             pos += rows;
-            hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, pos >= a.N ? 1 : 0);
+            hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, pos >= a.N ? 1 : 0, rank_at(a.k, (double)pos, (double)a.N));
         }
         const dim3 scan((unsigned)p.scan_grid), merge((unsigned)(a.nq < 256 ? a.nq : 256)), block(kBfThreads);
         if (p.scan_queries == 1) hipLaunchKernelGGL((bf_scan_kernel<Elem, 1>), scan, block, scan_lds(1, a.D), s, a);
@@ -1353,8 +1413,8 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
 
 }  // namespace
 
-size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k) {
-    return carve(make_plan(nq, D, elem_bytes, k), k, nullptr, nullptr);
+size_t brute_force_workspace(int64_t nq, uint64_t N, int D, int elem_bytes, int k) {
+    return carve(make_plan(nq, N, D, elem_bytes, k), k, nullptr, nullptr);
 }
 
 uint64_t brute_force_step(uint64_t N) {
@@ -1384,7 +1444,7 @@ hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, in
 
 hipError_t launch_brute_force(const void* vectors, const float* half_norms, int elem_bytes, uint64_t N, int D, const float* queries,
                               int64_t nq, int k, void* workspace, int64_t* out_ids, float* out_dists, hipStream_t s) {
-    const Plan p = make_plan(nq, D, elem_bytes, k);
+    const Plan p = make_plan(nq, N, D, elem_bytes, k);
     BruteArgs a;
     carve(p, k, static_cast<unsigned char*>(workspace), &a);
     a.vectors = vectors; a.xhalf = half_norms; a.N = N; a.D = D; a.k = k; a.KS = p.KS;

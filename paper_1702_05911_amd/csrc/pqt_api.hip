@@ -803,7 +803,7 @@ int pqt_brute_force(pqt_index* ix, const float* queries, int64_t nq, int k, int6
     DeviceGuard guard(ix->device);
     if (!guard.ok) return fail(PQT_EHIP, "cannot select GPU %d", ix->device);
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    const size_t need = pqt::brute_force_workspace(nq, (int)ix->D, ix->vector_elem_bytes, k);
+    const size_t need = pqt::brute_force_workspace(nq, ix->N, (int)ix->D, ix->vector_elem_bytes, k);
     if (need > ix->bf_ws_bytes) {
         (void)hipFree(ix->bf_ws);
         ix->bf_ws = nullptr;

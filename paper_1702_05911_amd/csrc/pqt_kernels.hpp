@@ -211,6 +211,7 @@ struct BruteArgs {
     // the current chunk: chunk_rows vectors from place chunk_pos on
     uint64_t chunk_pos;
     int64_t chunk_rows;
+    int tile_rows;                // of the stationary kernel's tiles of bytes
     // workspace
     uint32_t* control;
     uint32_t* flagged;            // nq: 1 = left to the exact scan
@@ -218,7 +219,8 @@ struct BruteArgs {
     uint32_t* todo;               // those queries
     float* qnorm;                 // ||q||
     float* qshift;                // what makes a value one of centred vectors
-    float* keep;                  // largest value that still matters
+    float* keep;                  // largest value that still matters ...
+    float* edge;                  // ... if the k-th smallest is at most this
     uint32_t* best_count;         // entries of best
     uint16_t* qfrag;              // queries, two bf16 pieces, operand layout
     uint8_t* qbytes;              // the same less 128 as bytes, operand layout (byte vectors of at most 128 dimensions, else null)
@@ -231,7 +233,7 @@ struct BruteArgs {
     unsigned long long* parts;    // the exact scan's results of every part of the database
 };
 // workspace of one call, in bytes
-size_t brute_force_workspace(int64_t nq, int D, int elem_bytes, int k);
+size_t brute_force_workspace(int64_t nq, uint64_t N, int D, int elem_bytes, int k);
 // what the filter needs to know of the vectors, whatever the queries: half squared norms, the largest norm, the centre
 size_t brute_force_norm_words(uint64_t N, int D, int elem_bytes);
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s);

@@ -1289,6 +1289,39 @@ def test_brute_force_ties(pqt, stored, N, D, nq, k, same):
         assert t < 10 * even, (t, even)
 
 
+@pytest.mark.parametrize("stored, N, D, early, k", [
+    ("u8", 60_000, 128, 60, 100),          # too many of the k nearest come first, the others are not kept: scanned
+    ("u8", 60_000, 128, 100, 100),         # all of them come first
+    ("f32", 60_000, 20, 60, 100),
+    ("f32", 300_000, 16, 0, 256),          # none comes before the last chunk
+])
+def test_brute_force_misleading_order(pqt, stored, N, D, early, k):
+    """Neighbours that are not spread over the database order (place i is vector i * step mod N), so that what the first
+    vectors let expect of the rest is wrong; other queries of the same call are not affected.  Whole numbers: exact."""
+    import math
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(51)
+    step = int(N * 0.6180339887498949) | 1
+    while math.gcd(step, N) != 1:
+        step += 2
+    X = torch.randint(0, 256, (N, D), generator=gen, device="cuda").float()
+    Y = torch.randint(0, 256, (40, D), generator=gen, device="cuda").float()
+    places = torch.cat([torch.arange(early), torch.arange(N - (k - early), N)])
+    near = Y[7].expand(k, D).clone()
+    near[torch.arange(k), torch.arange(k) % D] = (near[torch.arange(k), torch.arange(k) % D] + 1 + torch.arange(k, device="cuda") // D) % 256
+    X[(places * step % N).cuda()] = near
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X.to(torch.uint8) if stored == "u8" else X)
+        ids, d = pqt.pqt_brute_force(ix, Y, k)
+        for q in range(len(Y)):
+            true = ((X.double() - Y[q].double()) ** 2).sum(1)
+            want = (true * N + torch.arange(N, device="cuda")).sort().indices[:k]
+            assert torch.equal(ids[q], want) and torch.equal(d[q].double(), true[want]), q
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 @pytest.mark.parametrize("stored, D", [("u8", 32), ("f32", 20)])
 def test_brute_force_in_rounds(pqt, stored, D):
     """More queries than one round of the workspace holds (16,384): the queries on both sides of the border and the last ones
