@@ -142,6 +142,14 @@ double headless_from(const pqt_index* ix, int64_t nq) {
     if (nq <= 2048) return words ? 48.0 : 72.0;
     return words ? 96.0 : 84.0;
 }
+// Queries that are answered in one launch, one per compute unit.  Three launches and one, us: one query 20.4 and 18.2 (1,500
+// candidates of a dense index), 67 47.6 and 36.3, 256 59.2 and 45.3 (10,000 candidates); 300, which take two rounds, 67.6 and 73.8; four parts, T
+// = 4096: 256 83.3 and 69.8, 300 90 and 122.
+constexpr int64_t kSmallBatch = 256;
+// The same mean, up to which the first wavefront of its workgroup tries 32 and 64 tuples.  With that and without, us: one query at 25: 18.2
+// and 23.1, at 67: 22.0 and 25.9, at 164: 33.2 and 29.1; 7 at 25: 20.0 and 23.8, at 67: 29.5 and 26.2; 67 at 25: 30.6 and 24.9 (one is left
+// over, where none is 22.1 and 24.4), at 67: 40.5 and 34.3.
+double small_head_below(int64_t nq) { return nq < 4 ? 96.0 : (nq < 32 ? 48.0 : 24.0); }
 constexpr double kThirdLevelFrom = 72.0;     // the same mean, for the head pass's 128 tuples (see launch_rank)
 
 // Can the re-rank kernel also run the full bin ranking of the queries the head pass leaves over?
@@ -614,9 +622,6 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     ta.D = ix->D; ta.P = ix->P; ta.k1 = ix->k1; ta.k2 = ix->k2; ta.M = ix->M; ta.w = w;
     ta.C1 = ix->C1; ta.c1n = ix->c1n; ta.C2 = ix->C2; ta.C2t = ix->C2t;
     ta.a = ws.a; ta.L_d = ws.Ld; ta.L_id = ws.Lid; ta.sel_tap = tp.sel; ta.counters = ws.counters;
-    if (ev) HIP_TRY(hipEventRecord(ev[0], stream));
-    HIP_TRY(pqt::launch_traverse(ta, stream));
-    if (ev) HIP_TRY(hipEventRecord(ev[1], stream));
 
     pqt::RankArgs ra;
     ra.nq = nq; ra.P = ix->P; ra.R = R; ra.T = ix->T; ra.C = ix->C;
@@ -630,10 +635,30 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     ra.third_level = mean_need >= kThirdLevelFrom ? 1 : 0;
     ra.t_mid = pqt::kMidT;
     while (ra.t_mid < (int)ix->T && ra.t_mid < 2.0 * mean_need) ra.t_mid *= 2;
+    pqt::RerankArgs ca;
+    ca.nq = nq; ca.M = ix->M; ca.k1 = ix->k1; ca.T = ix->T; ca.C = ix->C; ca.k = k;
+    ca.threads = rerank_threads(ix, &ca.keys_per_thread, nq);
+    ca.code_format = (int)ix->code_format;
+    ca.runs_in_lds = rerank_runs_in_lds(ix);
+    ca.early = 0;
+    ca.a = ws.a; ca.table = ix->table; ca.runs = ws.runs; ca.meta = ws.meta;
+    ca.ids = ix->ids; ca.codes = ix->codes; ca.out_ids = out_ids; ca.out_dists = out_dists;
+    ca.n_cand = tp.n_cand; ca.cand_ids = tp.cand_ids; ca.scores = tp.scores; ca.lut = tp.lut;
+    ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
+    // A small batch in one launch (stage times and intermediate results exist only between launches)
+    if (!taps && !ev && !fixed_order && nq <= kSmallBatch) {
+        const size_t lds = pqt::small_query_lds(ca, ra, ta);
+        if (lds != 0 && lds <= ix->lds_limit) {
+            HIP_TRY(pqt::launch_small_query(ca, ra, ta, mean_need < small_head_below(nq), stream));
+            return PQT_OK;
+        }
+    }
+    if (ev) HIP_TRY(hipEventRecord(ev[0], stream));
+    HIP_TRY(pqt::launch_traverse(ta, stream));
+    if (ev) HIP_TRY(hipEventRecord(ev[1], stream));
     // The head pass is left out where it would leave much to do: every query is then ranked by a workgroup of its own in
     // a kernel of its own, by placing, which the re-rank kernel has no registers for.
     if (mean_need >= headless_from(ix, nq)) ra.order = nullptr;
-    ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
     const bool rerank_taps = tp.n_cand || tp.cand_ids || tp.scores || tp.lut || tp.n_slots;
     const bool head = !fixed_order && pqt::rank_has_head(ra);
     // the few queries the head pass cannot finish are ranked in full by their re-rank workgroup
@@ -659,13 +684,6 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     }
     if (ev) HIP_TRY(hipEventRecord(ev[2], stream));
 
-    pqt::RerankArgs ca;
-    ca.nq = nq; ca.M = ix->M; ca.k1 = ix->k1; ca.T = ix->T; ca.C = ix->C; ca.k = k;
-    ca.threads = rerank_threads(ix, &ca.keys_per_thread, nq);
-    ca.code_format = (int)ix->code_format;
-    ca.runs_in_lds = rerank_runs_in_lds(ix);
-    ca.a = ws.a; ca.table = ix->table; ca.runs = ws.runs; ca.meta = ws.meta;
-    ca.ids = ix->ids; ca.codes = ix->codes; ca.out_ids = out_ids; ca.out_dists = out_dists;
     ca.todo = ws.order; ca.todo_count = ws.counters;
     // Unfinished queries first: they take longest, and one that has no place here is ranked in its turn, at the end in the
     // worst case (416 places on the 1M-vector shape: 193 us a batch instead of 147).  A workgroup that finds none costs
@@ -673,7 +691,6 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     // lists nearly always fill the budget within 64 tuples get fewer.
     const int64_t places = mean_need < 40.0 ? 256 : 1024;
     ca.early = fuse ? (int)std::min(nq, places) : 0;
-    ca.n_cand = tp.n_cand; ca.cand_ids = tp.cand_ids; ca.scores = tp.scores; ca.lut = tp.lut;
     HIP_TRY(pqt::launch_rerank(ca, fuse ? &ra : nullptr, stream));
     if (ev) {
         HIP_TRY(hipEventRecord(ev[3], stream));

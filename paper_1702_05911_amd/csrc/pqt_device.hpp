@@ -365,6 +365,19 @@ __device__ __forceinline__ unsigned long long slot_of_bin(unsigned long long bin
     return r >= H ? r - H : r;
 }
 
+// Where the first runs of a query go if a workgroup keeps them in LDS (cap = 0: none).
+struct RunSink {
+    uint32_t* src = nullptr;
+    uint32_t* start = nullptr;
+    uint32_t cap = 0;
+    __device__ __forceinline__ bool put(uint32_t at, uint32_t first, uint32_t begins) const {
+        if (at >= cap) return false;
+        src[at] = first;
+        start[at] = begins;
+        return true;
+    }
+};
+
 __host__ __device__ inline int next_pow2(int v) {
     int p = 1;
     while (p < v) p <<= 1;

@@ -86,14 +86,14 @@ __device__ __forceinline__ void wave_append(bool take, unsigned long long key, u
 // into its bin's range, and a last step in which every key counts the smaller keys of its own bin -- no
 // comparison network.  Where a bin is too full for that (heavy ties) the Tn-th smallest key is found by
 // a radix select over the region (sums recomputed in every pass, never stored), ties at that key are cut
-// by (a, b), and only the Tn smallest are collected and sorted.  part: 16 words for the prefix sum.  All
-// threads call it; ends with a barrier.
+// by (a, b), and only the Tn smallest are collected and sorted.  part: 16 words for the prefix sum.  cleared: the histogram's
+// kPlaceBins words are zero.  All threads call it; ends with a barrier.
 // MODE: kRankPlace = place by bin where possible (without it: the select-and-sort path only, which needs
 // fewer registers where the ranking is a rarely taken branch of a larger kernel).
 template <int MAXE, int MODE>
 __device__ __forceinline__ void rank_pairs(const float* A, int nA, const float* B, int nB, int Tn, int nreg,
                                            int cap, unsigned long long* keys, uint32_t* hist, uint32_t* misc,
-                                           uint32_t* part) {
+                                           uint32_t* part, bool cleared = false) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, nt = blockDim.x;
     uint32_t tau = 0xffffffffu, a_cut = 0xffffffffu, b_cut = 0xffffffffu;
     const bool all = nreg <= (next_pow2(Tn) < 64 ? 64 : next_pow2(Tn));   // sorting the region costs no more than sorting Tn keys
@@ -106,18 +106,25 @@ __device__ __forceinline__ void rank_pairs(const float* A, int nA, const float* 
         const uint32_t lo_key = mono_key(A[0] + B[0]);
         uint32_t up_key;
         {
+            // Tn / s rounded up (Tn <= 8192): the quotient in floating point is one too small at most
+            auto sides = [&](int s) {
+                int o = max(1, (int)((float)Tn * __builtin_amdgcn_rcpf((float)s) - 0.01f));
+                o += o * s < Tn ? 1 : 0;
+                return o + (o * s < Tn ? 1 : 0);
+            };
             const int s1 = lane == kWave - 1 ? nA : min(lane + 1, nA);
-            const int o1 = (Tn + s1 - 1) / s1;
+            const int o1 = sides(s1);
             up_key = o1 <= nB ? mono_key(A[s1 - 1] + B[o1 - 1]) : 0xffffffffu;
             const int s2 = min(lane + 1, nB);
-            const int o2 = (Tn + s2 - 1) / s2;
+            const int o2 = sides(s2);
             if (o2 <= nA) up_key = min(up_key, mono_key(A[o2 - 1] + B[s2 - 1]));
             up_key = wave_min_u32(up_key);
         }
         const uint32_t prange = up_key - lo_key;
         const int pwidth = 32 - __clz((int)(prange | 1u));
         const int pshift = pwidth > kPlaceBits ? pwidth - kPlaceBits : 0;
-        for (int e = tid; e < kPlaceBins; e += nt) hist[e] = 0;
+        if (!cleared)
+            for (int e = tid; e < kPlaceBins; e += nt) hist[e] = 0;
         if (tid == 0) misc[5] = 0;                       // a bin too full to rank, or more keys than keys[] holds
         __syncthreads();
         for_region<true>(A, nA, B, nB, Tn, wave, lane, up_key, [&](uint32_t k32, uint32_t, uint32_t) {
@@ -313,10 +320,11 @@ __device__ __forceinline__ void rank_pairs(const float* A, int nA, const float* 
 // (the other cases are compiled out).  The run list goes to g.runs.  TO_LDS: (number of runs, number
 // of candidates) go to out_counts[0..1] in LDS instead of g.meta (the caller goes on with the query).
 // MAXPER (2, 4 or 8): tuples a thread may have to hold, L.Tcap <= MAXPER * blockDim.x.
-// smem: the workgroup's LDS, laid out by L.  Every thread calls it; ends with a barrier.
-template <int PF, bool TO_LDS, int MAXPER, int MODE>
+// smem: the workgroup's LDS, laid out by L.  LISTS: the sorted lists are there already and the histogram is zero; runs go to the sink
+// first.  Every thread calls it; ends with a barrier.
+template <int PF, bool TO_LDS, int MAXPER, int MODE, bool LISTS = false>
 __device__ __forceinline__ void rank_query(const RankArgs& g, const RankOffsets& L, int64_t q, unsigned char* smem,
-                                           uint32_t* out_counts) {
+                                           uint32_t* out_counts, RunSink sink = RunSink{}) {
     unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem + L.keys);
     unsigned long long* dkeys = keys;                       // (slot, position) keys reuse the sort buffer
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + L.hist);
@@ -333,11 +341,13 @@ __device__ __forceinline__ void rank_query(const RankArgs& g, const RankOffsets&
     const int P = PF ? PF : g.P, R = g.R, T = g.T;
     const uint32_t C = (uint32_t)g.C;
 
-    for (int e = tid; e < P * R; e += nt) {
-        sLd[e] = g.L_d[q * P * R + e];
-        sLid[e] = g.L_id[q * P * R + e];
+    if (!LISTS) {
+        for (int e = tid; e < P * R; e += nt) {
+            sLd[e] = g.L_d[q * P * R + e];
+            sLid[e] = g.L_id[q * P * R + e];
+        }
+        __syncthreads();
     }
-    __syncthreads();
 
     // Two attempts for two parts: the first Tmid tuples fill the candidate budget for almost every
     // query (tuples after the one that reaches C cannot change the result); all Tcap otherwise.
@@ -353,7 +363,7 @@ __device__ __forceinline__ void rank_query(const RankArgs& g, const RankOffsets&
             __syncthreads();                 // the list is already sorted by (distance, id)
         } else if (P == 2) {
             rank_pairs<MAXPER, MODE>(sLd, R, sLd + R, R, Tn, attempt == 0 ? L.nreg_mid : L.nreg, L.cap, keys, hist, misc,
-                                     part);
+                                     part, LISTS && (attempt == 0 || !staged));
         } else {
             // parts (1,2) and (3,4) first; then pairs of positions in those two lists.  One loop, so that the
             // ranking code exists once in the kernel: three copies of it do not fit the instruction cache.
@@ -365,7 +375,7 @@ __device__ __forceinline__ void rank_query(const RankArgs& g, const RankOffsets&
                 const float* B = last ? ps + np : sLd + (2 * stage + 1) * R;
                 const int n = last ? np : R;
                 rank_pairs<MAXPER, MODE>(A, n, B, n, last ? Tn : np, last ? L.nreg : L.nreg_pair, L.cap, keys, hist, misc,
-                                         part);
+                                         part, LISTS && stage == 0);
                 if (!last) {
                     for (int e = tid; e < np; e += nt) {
                         const unsigned long long key = keys[e];
@@ -501,7 +511,7 @@ __device__ __forceinline__ void rank_query(const RankArgs& g, const RankOffsets&
 #pragma unroll
         for (int i = 0; i < kMaxPer; ++i) {
             if (((flags >> i) & 1u) == 0) continue;
-            g.runs[(size_t)q * T + idx] = make_uint2(o0[i], first[i]);
+            if (!LISTS || !sink.put(idx, o0[i], first[i])) g.runs[(size_t)q * T + idx] = make_uint2(o0[i], first[i]);
             if (!TO_LDS && g.slots) g.slots[(size_t)q * T + idx] = sslot[t0 + i];
             ++idx;
         }

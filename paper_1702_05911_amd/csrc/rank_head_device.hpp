@@ -65,11 +65,12 @@ struct HeadLevels {
 // smallest there.  The table is ordered by (a+1)(b+1), so the entries of a smaller T1 are a prefix.
 // TO_LDS (the caller is a re-rank workgroup): the counts (runs, candidates) go to res[0..1] instead of
 // meta, and a query that needs more tuples is not listed: the level returns 2 and the caller ranks it.
+// sink (TO_LDS): the first runs go to the workgroup's LDS instead of memory.
 template <int E, bool TO_LDS = false>
 __device__ __forceinline__ int head_level(const RankArgs& g, HeadLds& S, int64_t q, int lane, int R1, int T1,
                                           int e_begin, int npairs, int Tn, bool last_level, unsigned long long& carry,
                                           uint32_t* res = nullptr, const uint8_t* tab_a = kHeadPairTable.a,
-                                          const uint8_t* tab_b = kHeadPairTable.b) {
+                                          const uint8_t* tab_b = kHeadPairTable.b, RunSink sink = RunSink{}) {
     const int T = g.T;
     const uint32_t C = (uint32_t)g.C;
     // ---- the T1 smallest keys (ordered sum bits, a, b) of the region, ascending over (register, lane) ----
@@ -152,7 +153,10 @@ __device__ __forceinline__ int head_level(const RankArgs& g, HeadLds& S, int64_t
     for (int r = 0; r < E; ++r) {
         const bool emit = len[r] > 0 && start[r] < C;
         const unsigned long long mask = __ballot(emit);
-        if (emit) g.runs[(size_t)q * T + nruns + __popcll(mask & ((1ull << lane) - 1ull))] = make_uint2(o0[r], start[r]);
+        if (emit) {
+            const uint32_t at = nruns + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+            if (!sink.put(at, o0[r], start[r])) g.runs[(size_t)q * T + at] = make_uint2(o0[r], start[r]);
+        }
         nruns += (uint32_t)__popcll(mask);
     }
     if (lane == 0) {

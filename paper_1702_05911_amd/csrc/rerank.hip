@@ -7,6 +7,7 @@
 #include "pqt_device.hpp"
 #include "rank_head_device.hpp"
 #include "rerank_variants.hpp"
+#include "traverse_one.hpp"
 
 namespace pqt {
 
@@ -101,6 +102,66 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
         case 4: return launch_rerank_table4(a, L, rk, RL, taps, f, s);
         case 8: return launch_rerank_table8(a, L, rk, RL, taps, f, s);
         default: return launch_rerank_table0(a, L, rk, RL, taps, f, s);
+    }
+}
+
+// Layout of the kernel for small batches; false: it does not take these arguments.
+static bool small_query_layout(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, RankOffsets& RL, RerankLds& L, SmallQuery& sm) {
+    if (!traverse_one_possible(tr)) return false;
+    RL = rank_offsets(rk.P, rk.R, rk.T, rk.hashed, true, rk.t_mid);
+    if (RL.Tcap > 4 * 1024 || a.C > kKeysPerThread * 1024) return false;
+    L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, 1024, 0, a.code_format, a.runs_in_lds);
+    size_t o = L.total;
+    sm.off_ranking = (uint32_t)o;   o += (RL.total + 15) & ~size_t(15);
+    sm.off_traverse = (uint32_t)o;  o += traverse_one_layout(tr.D, tr.P, tr.k1, tr.k2, tr.M, tr.w).total;
+    sm.off_head = (uint32_t)o;      o += (sizeof(HeadLds) + 15) & ~size_t(15);
+    sm.off_tables = (uint32_t)o;    o += 2 * kHeadPairs;
+    sm.lds = (uint32_t)o;
+    return o <= kMaxLds;
+}
+
+size_t small_query_lds(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr) {
+    RankOffsets RL;
+    RerankLds L;
+    SmallQuery sm;
+    return small_query_layout(a, rk, tr, RL, L, sm) ? sm.lds : 0;
+}
+
+hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const TraverseArgs& tr, bool head, hipStream_t s) {
+    if (a_in.nq <= 0) return hipSuccess;
+    RerankArgs a = a_in;
+    a.pair_shift = pair_table_shift(a.k1);
+    a.threads = 1024;
+    a.early = 0;
+    RankOffsets RL;
+    RerankLds L;
+    SmallQuery sm;
+    if (a.keys_per_thread != kKeysPerThread || a.n_cand || a.cand_ids || a.scores || a.lut || !small_query_layout(a, rk, tr, RL, L, sm))
+        return hipErrorInvalidValue;
+    sm.levels = HeadLevels{};
+    if (head && rk.P == 2)
+        for (int l = 0; l < 2; ++l) {
+            const int t = 32 << l;
+            sm.levels.T1[l] = RL.Tcap < t ? RL.Tcap : t;
+            sm.levels.npairs[l] = head_pair_count(sm.levels.T1[l]);
+        }
+    if (a.code_format == 1) {
+        switch (a.M % 2 ? 0 : a.M / 2) {
+            case 2: return launch_query_pair2(a, L, rk, RL, tr, sm, s);
+            case 4: return launch_query_pair4(a, L, rk, RL, tr, sm, s);
+            case 6: return launch_query_pair6(a, L, rk, RL, tr, sm, s);
+            case 8: return launch_query_pair8(a, L, rk, RL, tr, sm, s);
+            case 16: return launch_query_pair16(a, L, rk, RL, tr, sm, s);
+            default: return launch_query_pair_bytes(a, L, rk, RL, tr, sm, s);
+        }
+    }
+    switch ((a.M % 4 == 0) ? a.M / 4 : 0) {
+        case 1: return launch_query_table1(a, L, rk, RL, tr, sm, s);
+        case 2: return launch_query_table2(a, L, rk, RL, tr, sm, s);
+        case 3: return launch_query_table3(a, L, rk, RL, tr, sm, s);
+        case 4: return launch_query_table4(a, L, rk, RL, tr, sm, s);
+        case 8: return launch_query_table8(a, L, rk, RL, tr, sm, s);
+        default: return launch_query_table0(a, L, rk, RL, tr, sm, s);
     }
 }
 

@@ -28,6 +28,7 @@
 
 #include "rank_head_device.hpp"
 #include "rerank_variants.hpp"
+#include "traverse_one.hpp"
 
 namespace pqt {
 
@@ -399,13 +400,13 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
 
 // MW = 32-bit words per code (M/4) for M in {4, 8, 12, 16, 32}; 0 = any other M (byte loads);
 // MW < 0 = codes hold (centroid pair, lambda level) per sub-part, scored by Eq. 9 directly.
-// FUSED: a query whose meta.x is kMetaTodo (the ranking head pass could not finish it) is first
-// ranked in full by this workgroup.
 // LONG: results may outnumber the workgroup's threads (apart, because that end costs the usual lists 1 % in the kernel that
 // ranks as well).
-template <int MW, bool TAPS, bool FUSED, bool LONG>
-__global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) void rerank_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL) {
-    extern __shared__ __align__(16) unsigned char smem[];
+// Query q, whose run list of meta.x runs and meta.y candidates is in g.runs.  MARKS: runs of medium length are marked (the kernel
+// that ranks the head pass's left-over queries has no registers to spare for that).  READY: the level-1 distances, the table of Eq. 9
+// and the first runs are in LDS, the histogram is zero.
+template <int MW, bool TAPS, bool MARKS, bool LONG, bool READY>
+__device__ __forceinline__ void rerank_query(const RerankArgs& g, const RerankLds& L, int64_t q, uint2 meta, unsigned char* smem) {
     unsigned long long* surv = reinterpret_cast<unsigned long long*>(smem + L.surv);
     float* lut = reinterpret_cast<float*>(smem);                 // L.lut == 0
     float* sa = reinterpret_cast<float*>(smem + L.a);
@@ -419,45 +420,11 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
     const int lane = tid & (kWave - 1);
     const int M = g.M, k1 = g.k1, T = g.T, k = g.k;
     const int nlut = M * 256;
-
-    int64_t q;
-    uint2 meta;
-    if ((int)blockIdx.x < g.early) {           // one of the queries the head pass left unfinished, if any
-        if (blockIdx.x >= *g.todo_count) return;
-        q = (int64_t)g.todo[blockIdx.x];
-        meta = g.meta[q];
-    } else {
-        q = (int64_t)blockIdx.x - g.early;
-        meta = g.meta[q];
-        if (g.early > 0 && meta.x == kMetaTodo && meta.y < (uint32_t)g.early) return;   // an early workgroup has it
-    }
-    if (FUSED && meta.x == kMetaTodo) {        // same for the whole workgroup
-        // the run list goes to memory (this query's own rows), the counts come back through LDS.
-        // First the head pass's third level (128 tuples) by the first wavefront alone: few vector
-        // instructions, and nearly every left-over query is finished by it; the full ranking by the
-        // whole workgroup only if even those runs do not fill the candidate budget.
-        bool ranked = false;
-        if (g.mid_T1 > 0) {
-            if (tid < kWave) {
-                HeadLds& S = *reinterpret_cast<HeadLds*>(smem);
-                const int R1 = rk.R < kHeadT ? rk.R : kHeadT;
-                head_load_lists(rk, S, q, lane, R1);
-                unsigned long long carry = ~0ull;
-                const int r = head_level<2, true>(rk, S, q, lane, R1, g.mid_T1, 0, g.mid_npairs, RL.Tcap, true, carry, misc + kRanked);
-                if (lane == 0) misc[kRanked + 2] = r == 1 ? 1u : 0u;
-            }
-            __syncthreads();
-            ranked = misc[kRanked + 2] != 0u;
-            __syncthreads();
-        }
-        if (!ranked) rank_query<2, true, kFusedPer, 0>(rk, RL, q, smem, misc + kRanked);
-        meta = make_uint2(misc[kRanked], misc[kRanked + 1]);
-    }
     const uint2* qruns = g.runs + (size_t)q * T;
 
     // ---- issue every load that needs no other result first ------------------------------------------
     uint2 run0 = make_uint2(0u, 0u);
-    if (tid < kRunPrefetch && tid < L.rcap) run0 = qruns[tid];
+    if (!READY && tid < kRunPrefetch && tid < L.rcap) run0 = qruns[tid];
     // table entries: a thread takes code value c = tid mod 256 of the sub-parts m0, m0 + ms, ... (m0 and ms
     // are the same for a wavefront, so which sub-parts exist is decided by scalar code)
     const int lut_c = tid & 255;
@@ -468,23 +435,25 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
     constexpr int kEnt = (MW > 0 && MW <= 2) ? 8 : 4;
     constexpr bool kOneRound = MW > 0 && 4 * MW <= kEnt;
     CodeEntry ent[kEnt];
+    if (!READY) {
 #pragma unroll
-    for (int u = 0; u < kEnt; ++u) {
-        const int m = lut_m0 + u * lut_ms;
-        ent[u] = g.table[(m < Mlut ? m : 0) * 256 + lut_c];
+        for (int u = 0; u < kEnt; ++u) {
+            const int m = lut_m0 + u * lut_ms;
+            ent[u] = g.table[(m < Mlut ? m : 0) * 256 + lut_c];
+        }
+        for (int e = tid; e < M * k1; e += nt) sa[e] = g.a[(size_t)q * M * k1 + e];
+        for (int e = tid; e < kHistSize; e += nt) hist[e] = 0;
     }
-    for (int e = tid; e < M * k1; e += nt) sa[e] = g.a[(size_t)q * M * k1 + e];
-    for (int e = tid; e < kHistSize; e += nt) hist[e] = 0;
     const int nr = __builtin_amdgcn_readfirstlane((int)meta.x);     // the same in every thread
     const int nc = __builtin_amdgcn_readfirstlane((int)meta.y);
     int steps = 0;
     while ((1 << steps) < nr) ++steps;
     const int nr_lds = nr < L.rcap ? nr : L.rcap;
-    if (tid < kRunPrefetch && tid < nr_lds) {
+    if (!READY && tid < kRunPrefetch && tid < nr_lds) {
         run_src[tid] = run0.x;
         run_start[tid] = run0.y;
     }
-    for (int r = kRunPrefetch + tid; r < nr_lds; r += nt) {
+    for (int r = kRunPrefetch + tid; !READY && r < nr_lds; r += nt) {
         const uint2 run = qruns[r];
         run_src[r] = run.x;
         run_start[r] = run.y;
@@ -517,7 +486,8 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
         lut[e] = v;
         if (TAPS && g.lut) g.lut[(size_t)q * nlut + e] = v;
     };
-    if constexpr (kOneRound) {
+    if constexpr (READY) {
+    } else if constexpr (kOneRound) {
 #pragma unroll
         for (int u = 0; u < kEnt; ++u) {
             const int m = lut_m0 + u * lut_ms;
@@ -542,7 +512,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
             }
         }
     }
-    __syncthreads();
+    if (!READY) __syncthreads();
 
     // ---- scores: wavefront v owns positions [v * chunk, (v + 1) * chunk); position pos0 + u * 64 -> key[u] -----
     const int chunk = ((nc + (nt >> 6) - 1) / (nt >> 6) + kWave - 1) & ~(kWave - 1);     // <= 64 * kKeysPerThread
@@ -581,8 +551,7 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
                     score_batch<MW, 4, true, TAPS, RUNS>(g, q, base, lane, pend, lut, key + done, R, wr, mr, marks, cur, kmin, kmax);
             }
         };
-        // (the kernel that ranks as well has no registers to spare for the marks)
-        if (!FUSED && nr * kMarkMinRun <= nc && nr * kMarkMaxRun > nc) {
+        if (MARKS && nr * kMarkMinRun <= nc && nr * kMarkMaxRun > nc) {
             mr.load(R, 0, lane);
             score_all(std::integral_constant<int, kMarkRuns>{});
         } else if (nr * kWalkMinRun <= nc) {   // runs long enough that a window of 64 positions meets few of them
@@ -859,6 +828,130 @@ __global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) v
     }
 }
 
+// FUSED: a query whose meta.x is kMetaTodo (the ranking head pass could not finish it) is first
+// ranked in full by this workgroup.
+template <int MW, bool TAPS, bool FUSED, bool LONG>
+__global__ __launch_bounds__(1024, TAPS ? 1 : ((MW >= 8 || MW <= -6) ? 4 : 8)) void rerank_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L.misc);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int64_t q;
+    uint2 meta;
+    if ((int)blockIdx.x < g.early) {           // one of the queries the head pass left unfinished, if any
+        if (blockIdx.x >= *g.todo_count) return;
+        q = (int64_t)g.todo[blockIdx.x];
+        meta = g.meta[q];
+    } else {
+        q = (int64_t)blockIdx.x - g.early;
+        meta = g.meta[q];
+        if (g.early > 0 && meta.x == kMetaTodo && meta.y < (uint32_t)g.early) return;   // an early workgroup has it
+    }
+    if (FUSED && meta.x == kMetaTodo) {        // same for the whole workgroup
+        // the run list goes to memory (this query's own rows), the counts come back through LDS.
+        // First the head pass's third level (128 tuples) by the first wavefront alone: few vector
+        // instructions, and nearly every left-over query is finished by it; the full ranking by the
+        // whole workgroup only if even those runs do not fill the candidate budget.
+        bool ranked = false;
+        if (g.mid_T1 > 0) {
+            if (tid < kWave) {
+                HeadLds& S = *reinterpret_cast<HeadLds*>(smem);
+                const int R1 = rk.R < kHeadT ? rk.R : kHeadT;
+                head_load_lists(rk, S, q, lane, R1);
+                unsigned long long carry = ~0ull;
+                const int r = head_level<2, true>(rk, S, q, lane, R1, g.mid_T1, 0, g.mid_npairs, RL.Tcap, true, carry, misc + kRanked);
+                if (lane == 0) misc[kRanked + 2] = r == 1 ? 1u : 0u;
+            }
+            __syncthreads();
+            ranked = misc[kRanked + 2] != 0u;
+            __syncthreads();
+        }
+        if (!ranked) rank_query<2, true, kFusedPer, 0>(rk, RL, q, smem, misc + kRanked);
+        meta = make_uint2(misc[kRanked], misc[kRanked + 1]);
+    }
+    rerank_query<MW, TAPS, !FUSED, LONG, false>(g, L, q, meta, smem);
+}
+
+// The table of Eq. 9 summands (see rerank_query) by the threads from `first` on, and the histogram cleared.
+template <int MW>
+__device__ __forceinline__ void prepare_table(const RerankArgs& g, const RerankLds& L, unsigned char* smem, int first) {
+    float* lut = reinterpret_cast<float*>(smem);
+    const float* sa = reinterpret_cast<const float*>(smem + L.a);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + L.hist);
+    const int who = (int)threadIdx.x - first, n = (int)blockDim.x - first;
+    const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M), shift = MW < 0 ? g.pair_shift : 8, entries = M << shift;
+    constexpr int U = 4;                       // entries asked for together
+    for (int e0 = who; e0 < entries; e0 += U * n) {
+        CodeEntry ent[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = min(e0 + u * n, entries - 1);
+            ent[u] = g.table[(e >> shift) * 256 + (e & ((1 << shift) - 1))];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + u * n;
+            if (e >= entries) break;
+            const float* sam = sa + (e >> shift) * g.k1;
+            const float b2 = sam[ent[u].ij & 0xffu], a2 = sam[(ent[u].ij >> 8) & 0xffu];
+            if (MW < 0) reinterpret_cast<float4*>(lut)[e] = make_float4(b2, a2 - b2, ent[u].kc, 0.0f);
+            else lut[e] = fmaf(ent[u].lam, a2 - b2, b2) + ent[u].kc;
+        }
+    }
+    for (int e = who; e < kHistSize; e += n) hist[e] = 0;
+}
+
+// A whole query of a small batch by one workgroup of 1,024 threads, in one launch: traversal, ranking, re-ranking.  Every query has
+// a compute unit of its own, so what it costs is the chain of its steps, and of a launch that starts when the one before
+// has drained (4 us each) there is one instead of three; lists, level-1 distances and runs stay in LDS, and the table of Eq. 9 is
+// built while a wavefront per part sorts its list (the ranking's LDS lies behind everything else).
+template <int MW>
+__global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL, TraverseArgs tr, SmallQuery sm) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L.misc);
+    unsigned char* ranking = smem + sm.off_ranking;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int64_t q = blockIdx.x;
+    float* sLd = reinterpret_cast<float*>(ranking + RL.Ld);
+    uint32_t* sLid = reinterpret_cast<uint32_t*>(ranking + RL.Lid);
+    uint8_t* tab = smem + sm.off_tables;
+    if (sm.levels.T1[0] > 0 && tid < 2 * kHeadPairs / 4)
+        reinterpret_cast<uint32_t*>(tab)[tid] = tid < kHeadPairs / 4 ? reinterpret_cast<const uint32_t*>(kHeadPairTable.a)[tid]
+                                                                     : reinterpret_cast<const uint32_t*>(kHeadPairTable.b)[tid - kHeadPairs / 4];
+    for (int e = tid; e < kPlaceBins; e += 1024) reinterpret_cast<uint32_t*>(ranking + RL.hist)[e] = 0u;
+    traverse_one(tr, q, smem + sm.off_traverse, reinterpret_cast<float*>(smem + L.a), sLd, sLid,
+                 [&](int first) { prepare_table<MW>(g, L, smem, first); });
+    RunSink sink;
+    sink.src = reinterpret_cast<uint32_t*>(smem + L.run_src);
+    sink.start = reinterpret_cast<uint32_t*>(smem + L.run_start);
+    sink.cap = (uint32_t)L.rcap;
+    bool ranked = false;
+    if (sm.levels.T1[0] > 0) {
+        if (tid < kWave) {                     // the head pass's first two levels
+            HeadLds& S = *reinterpret_cast<HeadLds*>(smem + sm.off_head);
+            const int R1 = rk.R < kHeadT ? rk.R : kHeadT;
+            for (int e = lane; e < R1; e += kWave) {
+                S.A[e] = sLd[e];
+                S.Aid[e] = sLid[e];
+                S.B[e] = sLd[rk.R + e];
+                S.Bid[e] = sLid[rk.R + e];
+            }
+            wave_lds_order();
+            unsigned long long carry = ~0ull;
+            int r = head_level<1, true>(rk, S, q, lane, R1, sm.levels.T1[0], 0, sm.levels.npairs[0], RL.Tcap, false, carry, misc + kRanked,
+                                        tab, tab + kHeadPairs, sink);
+            if (r == 0)
+                r = head_level<1, true>(rk, S, q, lane, R1, sm.levels.T1[1], sm.levels.npairs[0], sm.levels.npairs[1], RL.Tcap, true, carry,
+                                        misc + kRanked, tab, tab + kHeadPairs, sink);
+            if (lane == 0) misc[kRanked + 2] = r == 1 ? 1u : 0u;
+        }
+        __syncthreads();
+        ranked = misc[kRanked + 2] != 0u;
+        __syncthreads();
+    }
+    if (!ranked) rank_query<0, true, 4, kRankPlace, true>(rk, RL, q, ranking, misc + kRanked, sink);
+    rerank_query<MW, false, true, true, true>(g, L, q, make_uint2(misc[kRanked], misc[kRanked + 1]), smem);
+}
+
 
 // ---- one translation unit per code width instantiates its kernels through these ------------------------------
 // HAS_TAPS: a variant with the taps exists for this code width (the word-wise (pair, lambda) variants have none:
@@ -880,12 +973,20 @@ inline hipError_t launch_rerank_variant(const RerankArgs& a, const RerankLds& L,
     return hipGetLastError();
 }
 
+template <int MW>
+inline hipError_t launch_query_variant(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL, const TraverseArgs& tr,
+                                       const SmallQuery& sm, hipStream_t s) {
+    hipLaunchKernelGGL((query_kernel<MW>), dim3((unsigned)a.nq), dim3(1024), sm.lds, s, a, L, rk, RL, tr, sm);
+    return hipGetLastError();
+}
+
 template <int MW, bool HAS_TAPS>
 inline hipError_t configure_rerank_variant(size_t max_dynamic_lds) {
-    const void* kernels[4] = {reinterpret_cast<const void*>(rerank_kernel<MW, false, false, true>),
+    const void* kernels[5] = {reinterpret_cast<const void*>(rerank_kernel<MW, false, false, true>),
                               reinterpret_cast<const void*>(rerank_kernel<MW, false, true, false>),
-                              reinterpret_cast<const void*>(rerank_kernel<MW, false, true, true>), nullptr};
-    if constexpr (HAS_TAPS) kernels[3] = reinterpret_cast<const void*>(rerank_kernel<MW, true, false, true>);
+                              reinterpret_cast<const void*>(rerank_kernel<MW, false, true, true>),
+                              reinterpret_cast<const void*>(query_kernel<MW>), nullptr};
+    if constexpr (HAS_TAPS) kernels[4] = reinterpret_cast<const void*>(rerank_kernel<MW, true, false, true>);
     for (const void* kfn : kernels) {
         if (!kfn) continue;
         hipFuncAttributes attr;
@@ -902,6 +1003,10 @@ inline hipError_t configure_rerank_variant(size_t max_dynamic_lds) {
     hipError_t launch_rerank_##NAME(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL,      \
                                     bool taps, bool fused, hipStream_t s) {                                                 \
         return launch_rerank_variant<MW, HAS_TAPS>(a, L, rk, RL, taps, fused, s);                                           \
+    }                                                                                                                       \
+    hipError_t launch_query_##NAME(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL,       \
+                                   const TraverseArgs& tr, const SmallQuery& sm, hipStream_t s) {                           \
+        return launch_query_variant<MW>(a, L, rk, RL, tr, sm, s);                                                           \
     }                                                                                                                       \
     hipError_t configure_rerank_##NAME(size_t max_dynamic_lds) { return configure_rerank_variant<MW, HAS_TAPS>(max_dynamic_lds); }
 

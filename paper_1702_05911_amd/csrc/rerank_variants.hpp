@@ -5,6 +5,7 @@
 // (and 140 with the ranking in a kernel of its own).  This header declares their launchers.
 #pragma once
 #include "pqt_kernels.hpp"
+#include "rank_head_device.hpp"
 
 namespace pqt {
 
@@ -13,9 +14,18 @@ struct RerankLds {
     uint32_t surv, lut, a, run_src, run_start, hist, part, misc, total;
 };
 
+// What the kernel that answers a query of a small batch has besides: its LDS, and the tuples the first wavefront ranks by itself
+// (T1[0] = 0: none).
+struct SmallQuery {
+    HeadLevels levels;
+    uint32_t off_traverse, off_tables, off_ranking, off_head, lds;
+};
+
 #define PQT_RERANK_VARIANT_DECLARE(NAME)                                                                               \
     hipError_t launch_rerank_##NAME(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL, \
                                     bool taps, bool fused, hipStream_t s);                                             \
+    hipError_t launch_query_##NAME(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL,  \
+                                   const TraverseArgs& tr, const SmallQuery& sm, hipStream_t s);                       \
     hipError_t configure_rerank_##NAME(size_t max_dynamic_lds);
 
 PQT_RERANK_VARIANT_DECLARE(table0)

@@ -1347,6 +1347,53 @@ def test_brute_force_in_rounds(pqt, stored, D):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("D, P, k1, k2, M, w, H, T, C, k, codes", [
+    (32, 2, 16, 8, 8, 8, 0, 1024, 4096, 100, "table"),       # lists of 64, M = 8
+    (64, 2, 17, 13, 4, 5, 0, 300, 700, 10, "table"),         # a second tile of one centroid; lists of 65
+    (64, 1, 48, 8, 32, 32, 0, 256, 3000, 50, "table"),       # one part, lists of 256 (four a lane), more jobs than wavefronts
+    (96, 4, 16, 7, 12, 4, 5003, 1024, 2000, 37, "table"),    # four parts, hashed
+    (64, 4, 8, 8, 16, 8, 0, 4096, 16384, 1024, "table"),     # most tuples a workgroup holds, the largest budget and list
+    (48, 2, 20, 7, 12, 5, 999, 500, 3001, 37, "pair"),       # pair codes of six words, hashed
+    (40, 2, 5, 3, 10, 2, 0, 36, 100, 100, "pair"),           # read byte by byte; fewer tuples than 64; fewer candidates than results
+    (96, 2, 16, 16, 6, 16, 0, 128, 5000, 9, "table"),        # read byte by byte
+    (64, 2, 16, 17, 4, 16, 0, 200, 900, 9, "table"),         # lists of 272: three launches
+    (36, 2, 9, 4, 2, 4, 0, 64, 500, 9, "table"),             # part dimensions of 18: three launches
+])
+def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
+    """Batches that are answered in one launch (up to 256 queries) against the launches with intermediate results and a larger
+    batch: the same ids and distance bits, with budgets that 32 tuples fill, that 64 do, and that take the full ranking."""
+    import torch
+    rng = np.random.default_rng(23)
+    N, bins = 20_000, (k1 * k2) ** P
+    H = H or min(bins, 1 << 24)
+    X = rng.integers(0, 64, (N, D)).astype(np.float32)
+    dp, pairs = D // P, k1 * (k1 - 1) // 2
+    counts = rng.multinomial(N, rng.dirichlet(np.full(H, 0.3))) if H <= 70_000 else np.bincount(rng.integers(0, H, N), minlength=H)
+    offsets = np.concatenate([[0], np.cumsum(counts)])
+    C1 = X[rng.permutation(N)[:P * k1]].reshape(P, k1, D)[:, :, :dp]
+    C2 = C1[:, :, None] + rng.integers(-8, 9, (P, k1, k2, dp))
+    cc = rng.integers(1, 500, (M, k1, k1)).astype(np.float32)
+    cc = np.triu(cc, 1) + np.triu(cc, 1).transpose(0, 2, 1)
+    code = rng.integers(0, 256, (N, M, 2))
+    code[:, :, 0] %= pairs
+    ix = pqt.pqt_index_from_arrays(dict(
+        N=N, H=H, D=D, P=P, k1=k1, k2=k2, M=M, T=T, C=C, C1=C1, C2=C2, tbl_i=rng.integers(0, k1, (M, 256)),
+        tbl_j=rng.integers(0, k1, (M, 256)), tbl_lam=rng.normal(0.5, 0.5, (M, 256)), cc=cc, offsets=offsets, ids=rng.permutation(N),
+        codes=code if codes == "pair" else code[:, :, 1], code_format=int(codes == "pair")))
+    try:
+        Y = torch.from_numpy(X[:300] + rng.normal(0, 2, (300, D)).astype(np.float32)).cuda()
+        for c in sorted({k, C, max(k, C // 20)}):
+            pqt.pqt_set_budget(ix, T, c)
+            ids, d = pqt.pqt_query_batch(ix, Y, k, w)                        # three launches
+            for nq in (1, 3, 40, 256):
+                few, fd = pqt.pqt_query_batch(ix, Y[:nq].contiguous(), k, w)
+                assert torch.equal(few, ids[:nq]) and torch.equal(fd, d[:nq]), (c, nq)
+            staged, sd, _ = pqt.pqt_query_batch_debug(ix, Y[:40].contiguous(), k, w, taps=("n_cand",))
+            assert torch.equal(staged, ids[:40]) and torch.equal(sd, d[:40])
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
