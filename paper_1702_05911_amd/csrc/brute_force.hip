@@ -38,10 +38,11 @@
 // Measured, 10,000 queries x 1M x 128 bytes, k = 100: 1.8 ms (the contraction 1.45, selection
 // 0.35); as one bf16 piece, all up to the k-th smallest so far kept, 3.5 ms (contraction 3.0), with
 // the fp32 matrix cores and all distances written and read back 40.0 ms.  777 x 150,001 x 960 floats, k = 10:
-// 0.80 ms (contraction 0.73 = 0.92 PFLOP/s of bf16) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
+// 0.52 ms (contraction 0.47; by bf16 pieces 0.80 and 0.73) against 2.58; 3 x 901,800 x 128 bytes: 0.15 against 0.71.
 // Data on which a bound by the largest norm of all, a list of 2 k + 256 and a scan by one workgroup per query took 78 ms
 // (the same floats, 777 queries; fp32 matrix cores 2.7): one vector of norm 300 among unit vectors 1.0 ms, an offset of 10 1.0,
 // 1,000 copies of one vector 1.2.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -55,6 +56,7 @@ namespace {
 
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfv8 __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -66,8 +68,12 @@ constexpr int kFrag = 512;             // bf16 values of one fragment: 32 rows x
 constexpr int kStatRows = 64;          // database vectors per LDS tile of the stationary kernel, as bf16 ...
 constexpr int kByteRows = 128;         // ... and as bytes
 constexpr int kStatQueries = 512;      // queries of one of its workgroups
-constexpr uint32_t kSecondPiece = 1u, kNotBytes = 2u;      // a query tile's state: second bf16 pieces; values that are not 0 .. 255
-constexpr int kGenRows = 256, kGenQueries = 128;   // workgroup tile of the general kernel
+// a query tile's state: second bf16 pieces; values that are not 0 .. 255; a norm out of the halves' range; more in the halves' window
+// than the kept lists have room for
+constexpr uint32_t kSecondPiece = 1u, kNotBytes = 2u, kNoHalves = 4u, kCrowded = 8u;
+constexpr float kHalfNorms = 0x1p40f;  // norms within this and its reciprocal are scaled to 2^14 .. 2^15 for the halves
+constexpr int kGenRows = 256, kGenQueries = 128;   // workgroup tile of the general kernel ...
+constexpr int kHalfQueries = 256;      // ... and the queries of one of the kernel for halves
 
 __device__ __forceinline__ v16f mfma(bf16x8 a, bf16x8 b, v16f c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16v8, a), __builtin_bit_cast(bf16v8, b), c, 0, 0, 0);
@@ -80,6 +86,19 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {      // two floats
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
+__device__ __forceinline__ v16f mfma_half(bf16x8 a, bf16x8 b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfv8, a), __builtin_bit_cast(halfv8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ uint32_t pack2_half(float a, float b) {         // two floats to half precision, nearest even
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, f16x2));
+}
+// the power of two that takes a norm to 2^14 .. 2^15 (1 for zero)
+__device__ __forceinline__ float half_scale(float norm) {
+    return norm > 0.0f ? __uint_as_float((uint32_t)(127 + 14 + 127 - (int)(__float_as_uint(norm) >> 23)) << 23) : 1.0f;
+}
+__device__ __forceinline__ bool half_norm_ok(float norm) { return norm == 0.0f || (norm >= 1.0f / kHalfNorms && norm <= kHalfNorms); }
 __device__ __forceinline__ float low_value(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float high_value(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }
 
@@ -160,8 +179,29 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
         g.qnorm[q] = sqrtf(n2);
         g.qshift[q] = g.use_centre[0] ? 0.0f : c;
         g.flagged[q] = 0u;
+        if (g.qhalf && (!half_norm_ok(sqrtf(n2)) || !half_norm_ok(g.xhalf[g.N] + g.xhalf[g.N + 2]))) atomicOr(&state, kNoHalves);
     }
+    if (g.qhalf) __syncthreads();
     if (tid == 0) g.second[tile] = state;
+}
+
+// Queries relative to the centre -> fragments of one piece of half precision, scaled.  A thread per eight dimensions.
+__global__ __launch_bounds__(kBfThreads) void pack_halves_kernel(BruteArgs g, int64_t count) {
+    const int64_t e = (int64_t)blockIdx.x * kBfThreads + threadIdx.x;
+    if (e >= count) return;
+    const int lane = (int)(e % kWave), ks = (int)(e / kWave % g.KS), D = g.D, d = ks * 16 + 8 * (lane >> 5);
+    const int64_t q = e / kWave / g.KS * 32 + (lane & 31);
+    const float* row = g.queries + (q < g.nq ? (size_t)q * D : 0);
+    const float scale = half_scale(g.qnorm[q]);
+    u32x4 h = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+        if (q < g.nq && d + 4 * c < D) {                     // D is a multiple of four
+            const float4 v = *reinterpret_cast<const float4*>(row + d + 4 * c), m = *reinterpret_cast<const float4*>(g.centre + d + 4 * c);
+            h[2 * c] = pack2_half((v.x - m.x) * scale, (v.y - m.y) * scale);
+            h[2 * c + 1] = pack2_half((v.z - m.z) * scale, (v.w - m.w) * scale);
+        }
+    reinterpret_cast<u32x4*>(g.qhalf)[e] = h;
 }
 
 // The centre of float vectors: in every dimension the median of 64 vectors spread over the database (places 0 .. 63 of the
@@ -250,9 +290,10 @@ __global__ __launch_bounds__(1024) void use_centre_kernel(const float* x, uint64
 // What the accumulators start from, the half squared norms of the database vectors less their part of the error bound, and, in the
 // word behind them, the bits of the largest norm (a little enlarged; never negative, so bits order as values).  A group of
 // lanes per row, 16 bytes per lane and step.
-// Bytes: in `whole` the same of the vectors less 128, rounded down to a whole number.
+// Bytes: in `whole` the same of the vectors less 128, rounded down to a whole number.  Floats: in `out_half` the same for the products
+// of halves.
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, float err_dot, float err_norm, float* out, int* whole) {
+__global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, int64_t n, int D, const float* centre, pqt_host::BruteError err, pqt_host::BruteError half, float* out, int* whole, float* out_half) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     constexpr int pe = 16 / (int)sizeof(Elem);
     const int npieces = D / pe, lpr = lanes_per_row(npieces), per_wave = kWave / lpr, sub = lane / lpr, l = lane & (lpr - 1);
@@ -294,7 +335,8 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
             else signed_norm += __shfl_xor(signed_norm, off, kWave);
         }
         if (sizeof(Elem) == 1 && r < n && l == 0) whole[r] = signed_norm >> 1;
-        if (r < n && l == 0) out[r] = (0.5f - err_norm) * s - 0.5f * err_dot * (as_they_are ? raw : s);
+        if (r < n && l == 0) out[r] = (0.5f - err.norm) * s - 0.5f * err.dot * (as_they_are ? raw : s);
+        if (sizeof(Elem) == 4 && r < n && l == 0) out_half[r] = (0.5f - half.norm) * s - 0.5f * half.dot * (as_they_are ? raw : s);
         top = fmaxf(top, r < n ? s : 0.0f);
         if (r < n && s != s) top = __builtin_inff();
     }
@@ -317,21 +359,32 @@ __global__ __launch_bounds__(kBfThreads) void half_norms_kernel(const Elem* x, i
 // gives r <= qn + sqrt(qn^2 + 2 (v + shift + own + e(r))), which is applied again and again from the largest norm of all.
 // A query longer than all vectors has the tighter a ||q|| X for its part, X the largest norm.  0.1 % on r and 3 % on the sum for
 // the rounding here.
-__device__ __forceinline__ float keep_up_to(const BruteArgs& g, float qn, float shift, float v) {
+__device__ __forceinline__ float keep_up_to(const BruteArgs& g, const pqt_host::BruteError& err, float qn, float shift, float v) {
     const float top = g.xhalf[g.N], mu = g.xhalf[g.N + 2];
-    const float own = 0.5f * g.err_dot * qn * fminf(qn, 2.0f * (top + mu)) + pqt_host::kBruteUnderflow;
+    const float own = 0.5f * err.dot * qn * fminf(qn, 2.0f * (top + mu)) + err.flush * qn * (top + mu) + pqt_host::kBruteUnderflow;
     float r = top, e = 0.0f;
     for (int i = 0; i < 6; ++i) {
-        e = g.err_dot * (r + mu) * (r + mu) + 2.0f * g.err_norm * r * r;
-        const float t = qn * qn + 2.0f * (v + shift + own + e + g.err_dot * qn * mu);
+        e = err.dot * (r + mu) * (r + mu) + 2.0f * err.norm * r * r;
+        const float t = qn * qn + 2.0f * (v + shift + own + e + err.dot * qn * mu);
         r = fminf(r, 1.001f * (qn + sqrtf(fmaxf(t, 0.0f))));
     }
     return v + 1.03f * (2.0f * own + e);
 }
 
-// -keep_up_to of a query: what an accumulator has to reach to be kept
-__device__ __forceinline__ float keep_from(const BruteArgs& g, int64_t q) {
-    return q >= g.nq || g.flagged[q] ? __builtin_inff() : -g.keep[q];
+// What an accumulator has to reach to be kept, from what bf_select_kernel left of a query
+__device__ __forceinline__ float keep_from(const BruteArgs& g, const float* keep, int64_t q) {
+    return q >= g.nq || g.flagged[q] ? __builtin_inff() : -keep[q];
+}
+
+// Floats: are the values of this query's group those of products of halves (after the first chunk)?  A group is what a workgroup of
+// bf_halves_kernel has.
+__device__ __forceinline__ bool group_is_halves(const BruteArgs& g, int64_t q) {
+    if (!g.qhalf) return false;
+    const int64_t tile = q / kHalfQueries * (kHalfQueries / 32), last = (g.nq - 1) / 32;
+    uint32_t state = 0;
+#pragma unroll
+    for (int u = 0; u < kHalfQueries / 32; ++u) state |= g.second[tile + u < last ? tile + u : last];
+    return !(state & (kNoHalves | kCrowded));
 }
 
 // What the queries of this group of the stationary kernel are, and whether they are all whole numbers 0 .. 255.
@@ -351,8 +404,10 @@ __device__ __forceinline__ Value larger(Value a, Value b) {
     if constexpr (std::is_same<Value, float>::value) return fmaxf(a, b);
     else return a > b ? a : b;
 }
+// unscale: what takes a sum to a value.
 template <bool DENSE, typename Acc, typename Value>
-__device__ __forceinline__ void take_tile(const Acc& acc, Value from, uint32_t row0, float* dense, uint2* list, int cap, uint32_t& count) {
+__device__ __forceinline__ void take_tile(const Acc& acc, Value from, uint32_t row0, float* dense, uint2* list, int cap, uint32_t& count,
+                                          float unscale = 1.0f) {
     if (DENSE) {
         if (!dense) return;
 #pragma unroll
@@ -370,7 +425,7 @@ __device__ __forceinline__ void take_tile(const Acc& acc, Value from, uint32_t r
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
                     if (acc[4 * i + c] >= from) {
-                        list[count < (uint32_t)cap ? count : cap - 1] = make_uint2(row0 + 8 * i + c, __float_as_uint((float)-acc[4 * i + c]));
+                        list[count < (uint32_t)cap ? count : cap - 1] = make_uint2(row0 + 8 * i + c, __float_as_uint((float)-acc[4 * i + c] * unscale));
                         ++count;
                     }
             }
@@ -456,7 +511,7 @@ __device__ __forceinline__ void filter_as_bf16(const BruteArgs& g, unsigned char
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
                 bq[p][ct][ks] = reinterpret_cast<const bf16x8*>(g.qfrag)[((q0 / 32 + ct) * KS + ks) * (2 * kFrag / 8) + p * (kFrag / 8) + lane];
-        from[ct] = DENSE ? 0.0f : keep_from(g, q0 + ct * 32 + (lane & 31));
+        from[ct] = DENSE ? 0.0f : keep_from(g, g.keep, q0 + ct * 32 + (lane & 31));
     }
     const int ntile = (int)((g.chunk_rows + kStatRows - 1) / kStatRows);
     TileRows<KS, kStatRows> rows;
@@ -552,7 +607,7 @@ __device__ __forceinline__ void filter_as_bytes(const BruteArgs& g, unsigned cha
         count[ct] = 0;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) bq[ct][kb] = reinterpret_cast<const i32x4*>(g.qbytes)[((q0 / 32 + ct) * KB + kb) * kWave + lane];
-        const float f = DENSE ? 0.0f : keep_from(g, q0 + ct * 32 + (lane & 31));
+        const float f = DENSE ? 0.0f : keep_from(g, g.keep, q0 + ct * 32 + (lane & 31));
         from[ct] = f < 1e9f ? (int)ceilf(f) : 0x7fffffff;                     // (values are whole)
     }
     auto take = [&](const v16i& acc, auto ct, uint32_t row0) {
@@ -669,6 +724,14 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
     }
 }
 
+// LDS of the general kernel, in bytes: vectors, queries, norms (two of each), thresholds
+template <typename Elem>
+struct GeneralLds {
+    static constexpr int kQueries = 2 * (kGenRows / 32) * (sizeof(Elem) == 4 ? 2 : 1) * kFrag * 2;
+    static constexpr int kNorms = kQueries + 2 * (kGenQueries / 32) * 2 * kFrag * 2;
+    static constexpr int kFrom = kNorms + 2 * kGenRows * 4, kTotal = kFrom + kGenQueries * 4;
+};
+
 // Any dimension: both operands stream through LDS, 16 dimensions a step.  The workgroup's tile is 256 vectors x 128
 // queries, a wavefront's 64 x 128 (128 accumulator registers); with two pieces on both sides a step is 24 matrix
 // instructions (h.h, h.m, m.h) for 12 KB of LDS reads per wavefront.  A workgroup takes every splits-th tile of vectors;
@@ -676,27 +739,29 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
 // Rows arrive as 64 bytes of floats per step, four lanes each, and are cut on their way into LDS (three instructions per
 // element, a quarter of the matrix time and beside it); byte rows (more than 128 dimensions) as 16 bytes, one lane each.
 template <typename Elem, bool DENSE>
-__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
+__device__ __forceinline__ void filter_general(const BruteArgs& g, unsigned char* smem) {
     constexpr bool kFloats = sizeof(Elem) == 4;
     constexpr int XP = kFloats ? 2 : 1;                                        // pieces per value
     constexpr int kX = kGenRows / 32, kQ = kGenQueries / 32;                   // 32-row tiles of the workgroup's tile
     constexpr int kXPieces = kFloats ? 4 : 1, kQPieces = kQ * 2 * kFrag / 8 / kBfThreads;
-    __shared__ __align__(16) uint16_t xs[2][kX * XP * kFrag];
-    __shared__ __align__(16) uint16_t qs[2][kQ * 2 * kFrag];
-    __shared__ __align__(16) float hs[2][kGenRows];
+    typedef GeneralLds<Elem> Lds;
+    uint16_t* xs = reinterpret_cast<uint16_t*>(smem);                          // two of either, step by step in turn
+    uint16_t* qs = reinterpret_cast<uint16_t*>(smem + Lds::kQueries);
+    float* hs = reinterpret_cast<float*>(smem + Lds::kNorms);
+    float* from = reinterpret_cast<float*>(smem + Lds::kFrom);
+    constexpr int kXs = kX * XP * kFrag, kQs = kQ * 2 * kFrag;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int KS = g.KS, splits = g.splits;
     int split, group;
     place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
     const int64_t q0 = (int64_t)group * kGenQueries;
-    __shared__ float from[kGenQueries];
-    if (!DENSE && tid < kGenQueries) from[tid] = keep_from(g, q0 + tid);      // (read after the first step's barrier)
+    if (!DENSE && tid < kGenQueries) from[tid] = keep_from(g, g.keep, q0 + tid);      // (read after the first step's barrier)
     uint32_t count[kQ];
 #pragma unroll
     for (int ct = 0; ct < kQ; ++ct) count[ct] = 0;
     const int ntile = (int)((g.chunk_rows + kGenRows - 1) / kGenRows);
     const u32x4* qf = reinterpret_cast<const u32x4*>(g.qfrag);
-    constexpr int kTileQ = 2 * kFrag / 8;                                      // 16-byte pieces of a 32-query tile's step
+    constexpr int kTileQ = 2 * kFrag / 8;                                     // 16-byte pieces of a 32-query tile's step
     // the rows this thread brings 16 bytes of: (tid / 4) + 64 i, bytes 16 (tid % 4) of a step's 64; or row tid
     const int rl = kFloats ? tid >> 2 : tid, c4 = kFloats ? tid & 3 : 0;
     const uint64_t move = ((uint64_t)splits * kGenRows) % g.N * g.step % g.N;
@@ -746,7 +811,7 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
                 const int r = rl + 64 * i;
                 const float v0 = __uint_as_float(f.x[i][0]), v1 = __uint_as_float(f.x[i][1]), v2 = __uint_as_float(f.x[i][2]), v3 = __uint_as_float(f.x[i][3]);
                 const uint32_t h0 = pack2(v0, v1), h1 = pack2(v2, v3);
-                uint16_t* at = xs[buf] + (r >> 5) * 2 * kFrag + (c4 >> 1) * 256 + (r & 31) * 8 + (c4 & 1) * 4;
+                uint16_t* at = xs + buf * kXs + (r >> 5) * 2 * kFrag + (c4 >> 1) * 256 + (r & 31) * 8 + (c4 & 1) * 4;
                 *reinterpret_cast<uint2*>(at) = make_uint2(h0, h1);
                 *reinterpret_cast<uint2*>(at + kFrag) =
                     make_uint2(pack2(v0 - low_value(h0), v1 - high_value(h0)), pack2(v2 - low_value(h1), v3 - high_value(h1)));
@@ -760,12 +825,12 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
                 if (j < 2) { w0[2 * j] = p0; w0[2 * j + 1] = p1; }
                 else { w1[2 * j - 4] = p0; w1[2 * j - 3] = p1; }
             }
-            u32x4* at = reinterpret_cast<u32x4*>(xs[buf]) + (rl >> 5) * (kFrag / 8) + (rl & 31);
+            u32x4* at = reinterpret_cast<u32x4*>(xs + buf * kXs) + (rl >> 5) * (kFrag / 8) + (rl & 31);
             at[0] = w0;
             at[32] = w1;
         }
 #pragma unroll
-        for (int i = 0; i < kQPieces; ++i) reinterpret_cast<u32x4*>(qs[buf])[i * kBfThreads + tid] = f.q[i];
+        for (int i = 0; i < kQPieces; ++i) reinterpret_cast<u32x4*>(qs + buf * kQs)[i * kBfThreads + tid] = f.q[i];
         if (first) hs[tid] = -hx;
         __syncthreads();
         fetch(f);
@@ -787,11 +852,11 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
             for (int p = 0; p < XP; ++p)
-                a[rt][p] = reinterpret_cast<const bf16x8*>(xs[buf])[((wave * 2 + rt) * XP + p) * (kFrag / 8) + lane];
+                a[rt][p] = reinterpret_cast<const bf16x8*>(xs + buf * kXs)[((wave * 2 + rt) * XP + p) * (kFrag / 8) + lane];
 #pragma unroll
         for (int ct = 0; ct < kQ; ++ct) {
-            const bf16x8 h = reinterpret_cast<const bf16x8*>(qs[buf])[ct * kTileQ + lane];
-            const bf16x8 m = reinterpret_cast<const bf16x8*>(qs[buf])[ct * kTileQ + kFrag / 8 + lane];
+            const bf16x8 h = reinterpret_cast<const bf16x8*>(qs + buf * kQs)[ct * kTileQ + lane];
+            const bf16x8 m = reinterpret_cast<const bf16x8*>(qs + buf * kQs)[ct * kTileQ + kFrag / 8 + lane];
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
                 acc[rt][ct] = mfma(a[rt][0], h, acc[rt][ct]);
@@ -812,15 +877,15 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
         hid -= hid >= g.N ? g.N : 0;
         int ks = 0;
         if (odd) {
-            step(f1, 1, 0, hx, hs[half]);
+            step(f1, 1, 0, hx, hs + half * kGenRows);
             ks = 1;
         }
         for (; ks + 1 < KS; ks += 2) {
-            step(f0, 0, ks, hx, hs[half]);
-            step(f1, 1, ks + 1, hx, hs[half]);
+            step(f0, 0, ks, hx, hs + half * kGenRows);
+            step(f1, 1, ks + 1, hx, hs + half * kGenRows);
         }
         odd = ks < KS;
-        if (odd) step(f0, 0, ks, hx, hs[half]);
+        if (odd) step(f0, 0, ks, hx, hs + half * kGenRows);
 #pragma unroll
         for (int ct = 0; ct < kQ; ++ct) {
             const int64_t q = q0 + ct * 32 + (lane & 31);
@@ -838,6 +903,183 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
     }
 }
 
+// Floats of a collection of up to kHalvesUpTo vectors: after the first chunk the products are of one piece of half precision on both
+// sides, a third of the matrix work.  Eleven significant bits leave 2^-10 of a product, so more pairs pass: a window two to three times as
+// wide where there are many dimensions (the additions of three products are allowed as much there), twelve times at 128.  A
+// group of queries of which one has more vectors of the first chunk in that window than it may (bf_select_kernel), or with norms out
+// of the range that is scaled to halves, keeps to bf16.
+// The workgroup's tile is 256 vectors x 256 queries, two times four wavefronts of 64 x 128; 32 dimensions a step, 16 matrix
+// instructions a wavefront, so that a row is read by whole 128-byte lines.  Bound by LDS reads (half its cycles) and the barrier of a
+// workgroup that has a compute unit to itself; workgroups of 128 queries, two per compute unit, read the vectors twice as often: 446 us
+// for 777 queries x 150,001 x 960, with 16 dimensions a step 483.  LDS: the 16 bytes of a row's dimensions 8 j .. + 8 lie in slot
+// row ^ 2 j (415 us without).
+// The same, k = 10: the contraction after the first chunk 759 us by bf16 pieces, 404 by halves.
+template <int QW>
+struct HalvesLds {
+    static constexpr int kVectors = kGenRows * 32 * 2, kQueries = QW * 128 * 32 * 2;       // a step's
+    static constexpr int kQ = 2 * kVectors, kNorms = kQ + 2 * kQueries, kFrom = kNorms + 2 * kGenRows * 4, kScale = kFrom + QW * 128 * 4;
+    static constexpr int kTotal = kScale + QW * 128 * 4;
+};
+__global__ __launch_bounds__(2 * kBfThreads, 2) void bf_halves_kernel(BruteArgs g) {
+    constexpr int QW = kHalfQueries / kGenQueries;
+    typedef HalvesLds<QW> Lds;
+    __shared__ __align__(16) unsigned char smem[Lds::kTotal];
+    constexpr int kQ = 4, kThreads = QW * kBfThreads, kXPieces = 8 / QW, kQPieces = 2;
+    float* hs = reinterpret_cast<float*>(smem + Lds::kNorms);
+    float* from = reinterpret_cast<float*>(smem + Lds::kFrom);
+    float* scale = reinterpret_cast<float*>(smem + Lds::kScale);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, rw = wave & 3, qw = wave >> 2;
+    const int KS = g.KS, steps = (KS + 1) / 2, splits = g.splits;
+    int split, group;
+    place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
+    const int64_t first_query = (int64_t)group * (QW * kGenQueries), q0 = first_query + qw * kGenQueries;
+    if (!group_is_halves(g, first_query)) return;
+    const float xscale = half_scale(g.xhalf[g.N] + g.xhalf[g.N + 2]);
+    if (tid < QW * kGenQueries) {                                              // (read after the first step's barrier)
+        const bool have = first_query + tid < g.nq;
+        scale[tid] = have ? xscale * half_scale(g.qnorm[first_query + tid]) : 1.0f;
+        from[tid] = have ? keep_from(g, g.keep_halves, first_query + tid) * scale[tid] : __builtin_inff();
+    }
+    uint32_t count[kQ];
+#pragma unroll
+    for (int ct = 0; ct < kQ; ++ct) count[ct] = 0;
+    const int ntile = (int)((g.chunk_rows + kGenRows - 1) / kGenRows);
+    const u32x4* qf = reinterpret_cast<const u32x4*>(g.qhalf);
+    const int last_tile = (int)((g.nq + 31) / 32) - 1;                         // (past it: its queries again, kept by nobody)
+    // the rows this thread brings 16 bytes of: (tid / 8) + 32 QW i, bytes 16 (tid % 8) of a step's 128; row tid's norm
+    const int rl = tid >> 3, c8 = tid & 7;
+    const uint32_t N = (uint32_t)g.N, move = (uint32_t)(((uint64_t)splits * kGenRows) % g.N * g.step % g.N);      // (N is at most kHalvesUpTo)
+    uint32_t id[kXPieces], hid;
+#pragma unroll
+    for (int i = 0; i < kXPieces; ++i) id[i] = (uint32_t)(((g.chunk_pos + (uint64_t)split * kGenRows + rl + 32 * QW * i) % g.N) * g.step % g.N);
+    hid = (uint32_t)(((g.chunk_pos + (uint64_t)split * kGenRows + tid) % g.N) * g.step % g.N);
+    auto advance = [&](uint32_t& at) {
+        at += move;
+        at -= at >= N ? N : 0u;
+    };
+    const bool centred = g.use_centre[0] != 0u;
+    struct Step { u32x4 x[kXPieces], q[kQPieces]; };
+    int fks = 0;                               // the step fetched next, of the tile the ids stand for
+    auto fetch = [&](Step& f) {                // (past the last tile: some vectors, unused; always loading keeps the pieces in registers)
+        const int d = fks * 32 + 4 * c8;
+        const bool in = d < g.D;
+#pragma unroll
+        for (int i = 0; i < kXPieces; ++i) {
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const float*>(g.vectors) + id[i] * (uint64_t)g.D + (in ? d : 0));
+            f.x[i] = in ? v : zero;
+        }
+#pragma unroll
+        for (int i = 0; i < kQPieces; ++i) {   // (an odd last step: the queries' last sixteen dimensions against zeros)
+            const int e = i * kThreads + tid, qt = min((int)(first_query / 32) + e / 128, last_tile), ks = min(2 * fks + (e / 64) % 2, KS - 1);
+            f.q[i] = qf[((size_t)qt * KS + ks) * (kFrag / 8) + e % 64];
+        }
+        if (++fks == steps) {
+            fks = 0;
+#pragma unroll
+            for (int i = 0; i < kXPieces; ++i) advance(id[i]);
+        }
+    };
+    v16f acc[2][kQ];
+    int t = split, ks = 0, half = 0;
+    float hx = 0.0f;
+    auto step = [&](Step& f, int buf) {        // false: that was the last
+        uint16_t* xs = reinterpret_cast<uint16_t*>(smem + buf * Lds::kVectors);
+        u32x4* qs = reinterpret_cast<u32x4*>(smem + Lds::kQ + buf * Lds::kQueries);
+        float* norms = hs + half * kGenRows;
+        if (ks == 0 && tid < kGenRows) {
+            hx = (int64_t)t * kGenRows + tid < g.chunk_rows ? g.xhalf_halves[hid] : __builtin_inff();     // such rows enter no list
+            advance(hid);
+        }
+        const int d = ks * 32 + 4 * c8;
+        u32x4 c = {0u, 0u, 0u, 0u};
+        if (centred && d < g.D) c = *reinterpret_cast<const u32x4*>(g.centre + d);         // (the zeros past the last dimension stay what they are)
+        float less[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) less[j] = -__uint_as_float(c[j]) * xscale;             // (a power of two: rounded as before scaling)
+#pragma unroll
+        for (int i = 0; i < kXPieces; ++i) {
+            const int r = rl + 32 * QW * i;
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = fmaf(__uint_as_float(f.x[i][j]), xscale, less[j]);
+            *reinterpret_cast<uint2*>(xs + ((r >> 5) * 2 + (c8 >> 2)) * kFrag + ((c8 >> 1) & 1) * 256 + ((r & 31) ^ (c8 & 6)) * 8 + (c8 & 1) * 4) =
+                make_uint2(pack2_half(v[0], v[1]), pack2_half(v[2], v[3]));
+        }
+#pragma unroll
+        for (int i = 0; i < kQPieces; ++i) qs[i * kThreads + tid] = f.q[i];
+        if (ks == 0 && tid < kGenRows) norms[tid] = -hx;
+        __syncthreads();
+        fetch(f);
+        if (ks == 0) {
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                v16f start;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float4 h = *reinterpret_cast<const float4*>(&norms[rw * 64 + rt * 32 + 8 * i + 4 * (lane >> 5)]);
+                    start[4 * i] = h.x; start[4 * i + 1] = h.y; start[4 * i + 2] = h.z; start[4 * i + 3] = h.w;
+                }
+#pragma unroll
+                for (int ct = 0; ct < kQ; ++ct) {
+                    const float own = scale[qw * kGenQueries + ct * 32 + (lane & 31)];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[rt][ct][r] = start[r] * own;
+                }
+            }
+        }
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            bf16x8 a[2];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) a[rt] = reinterpret_cast<const bf16x8*>(xs)[((rw * 2 + rt) * 2 + sub) * (kFrag / 8) + (lane ^ (4 * sub + 2 * (lane >> 5)))];
+#pragma unroll
+            for (int ct = 0; ct < kQ; ++ct) {
+                const bf16x8 h = reinterpret_cast<const bf16x8*>(qs)[((qw * kQ + ct) * 2 + sub) * (kFrag / 8) + lane];
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) acc[rt][ct] = mfma_half(a[rt], h, acc[rt][ct]);
+            }
+        }
+        if (++ks < steps) return true;
+        ks = 0;
+#pragma unroll
+        for (int ct = 0; ct < kQ; ++ct) {
+            const int at = qw * kGenQueries + ct * 32 + (lane & 31);
+            const int64_t q = first_query + at;
+            uint2* list = g.lists + ((size_t)q * g.segs + split * 8 + rw * 2 + (lane >> 5)) * g.seg_cap;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+                take_tile<false>(acc[rt][ct], from[at], (uint32_t)t * kGenRows + rw * 64 + rt * 32 + 4 * (lane >> 5), nullptr, list, g.seg_cap, count[ct],
+                                 1.0f / scale[at]);
+        }
+        t += splits;
+        half ^= 1;
+        return t < ntile;
+    };
+    // two steps are under way in registers
+    if (t < ntile) {
+        Step f0, f1;
+        fetch(f0);
+        fetch(f1);
+        while (step(f0, 0) && step(f1, 1)) {}
+    }
+#pragma unroll
+    for (int ct = 0; ct < kQ; ++ct)
+        if (q0 + ct * 32 + (lane & 31) < g.nq)
+            g.seg_count[(size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + split * 8 + rw * 2 + (lane >> 5)] = count[ct];
+}
+
+template <typename Elem, bool DENSE>
+__global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
+    __shared__ __align__(16) unsigned char smem[GeneralLds<Elem>::kTotal];
+    if constexpr (sizeof(Elem) == 4 && !DENSE) {
+        int split, group;
+        place_of_workgroup(blockIdx.x, g.splits, (int)gridDim.x / g.splits, split, group);
+        if (group_is_halves(g, (int64_t)group * kGenQueries)) return;          // bf_halves_kernel has it
+    }
+    filter_general<Elem, DENSE>(g, smem);
+}
+
 constexpr int kSelectBins = 1024;
 
 constexpr int kBest = 2048;            // entries kept of a query between chunks: the k best and what may tie with them
@@ -847,7 +1089,7 @@ constexpr int kBest = 2048;            // entries kept of a query between chunks
 // Entries: bits of s~ << 32 | place in the database order.  (Bins are equal pieces of the value range, not of the bit
 // patterns: s~ changes sign, and most of the patterns between its smallest and largest value are next to zero.)
 template <typename Elem>
-__global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int dense, int last, int rank) {
+__global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int dense, int last, int rank, uint32_t few) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // kDense
     __shared__ uint32_t hist[kSelectBins];
@@ -920,11 +1162,8 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     }
     // ---- an upper bound of the rank-th smallest: the end of its bin ------------------------------------------------
     // One histogram over the values' range; where a few long vectors stretch the range, so that the bin of the k-th holds many
-    // more, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
+    // more than `few` up to its end, its entries get a histogram of their own, and so on.  Bit u of `members`: entry tid + u * 256 is
     // among those that are divided.
-    // entries up to the bin's end that need no division: what they cost is an exact distance each, or, before the last chunk,
-    // pairs that pass
-    const uint32_t few = last ? (uint32_t)k + 128u : (uint32_t)(rank + rank / 8 + 3);
     auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
     static_assert(kDense <= 32 * kBfThreads, "a bit per entry");
     uint32_t members = 0xffffffffu, below = 0u;
@@ -1009,7 +1248,25 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     }
     // (values of bytes against bytes are exact: half squared distances rounded down, but for a term of the query)
     const bool exact = sizeof(Elem) == 1 && g.qbytes && group_is_bytes(g, (int)(q / kStatQueries));
-    const float keep = exact ? edge : keep_up_to(g, qn, g.qshift[q], edge);
+    float keep = exact ? edge : keep_up_to(g, g.err, qn, g.qshift[q], edge);
+    if (!last && tid == 0) g.keep[q] = keep;
+    if (sizeof(Elem) == 4 && g.qhalf && !(dense && last)) {
+        const float wide = keep_up_to(g, g.err_half, qn, g.qshift[q], edge);
+        if (!last && tid == 0) g.keep_halves[q] = wide;
+        if (!dense) {
+            if (group_is_halves(g, q)) keep = wide;
+        } else {                                     // (this chunk's values are those of bf16 pieces)
+            __syncthreads();                         // (misc[2] has been read)
+            if (tid == 0) misc[2] = 0u;
+            __syncthreads();
+            uint32_t up_to = 0;
+            for (int e = tid; e < n; e += kBfThreads) up_to += value(e) <= wide ? 1u : 0u;
+            atomicAdd(&misc[2], up_to);
+            __syncthreads();
+            if (misc[2] <= (uint32_t)(rank + rank / 2 + 6)) keep = wide;
+            else if (tid == 0) atomicOr(&g.second[q / 32], kCrowded);
+        }
+    }
     // ---- keep what can still be among the k nearest ---------------------------------------------------------------
     for (int e0 = 0; e0 < n; e0 += kBfThreads) {     // in place: entry e moves to a place <= e that has been read
         const int e = e0 + tid;
@@ -1033,7 +1290,6 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         if (tid == 0) {
             g.best_count[q] = (uint32_t)n;
             g.edge[q] = edge;
-            g.keep[q] = keep;
         }
         return;
     }
@@ -1265,6 +1521,9 @@ uint64_t gcd_u64(uint64_t a, uint64_t b) {
 // it is not: at a 16-byte boundary
 size_t centre_at(uint64_t N) { return (size_t)(N + 6) / 4 * 4; }
 
+// floats: what values of products of halves start from
+size_t halves_at(uint64_t N, int D) { return centre_at(N) + (size_t)(D + 3) / 4 * 4; }
+
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // How many of the k nearest of N vectors the first `pos` places of the database order hold, hardly ever exceeded (less than once in
@@ -1275,9 +1534,13 @@ int rank_at(int k, double pos, double N) {
     return most < k ? (int)most : k;
 }
 
+// Floats: the largest collection that is filtered by halves.  More vectors in their window than the kept lists hold (kBest) have to
+// show in the first chunk: eight of them.
+constexpr uint64_t kHalvesUpTo = (uint64_t)kBest * kDense / 8;
+
 // How one call is cut: sizes of the workspace's pieces and the launch shapes.
 struct Plan {
-    bool stationary;
+    bool stationary, halves;
     int KS;
     int64_t batch, batch_pad;        // queries at a time, padded to whole workgroup tiles
     int groups, splits, segs, seg_cap;
@@ -1294,10 +1557,14 @@ Plan make_plan(int64_t nq, uint64_t N, int D, int elem_bytes, int k) {
     const int tile = p.stationary ? kStatQueries : kGenQueries;
     p.batch = nq < 16384 ? nq : 16384;
     p.batch_pad = round_up(p.batch, tile);
+    // Halves need the queries a second time and a look at the first chunk, about 6 us: not for what takes less than a few
+    // times that.  (Up to 128 queries the workgroup's second half would idle.)
+    p.halves = elem_bytes == 4 && N >= 8 * kDense && N <= kHalvesUpTo && p.batch > kGenQueries && (double)p.batch_pad * (double)N * D > 6e9;
     p.groups = (int)(p.batch_pad / tile);
     // as many workgroups as are resident at once (two per compute unit): no second round of a few
     const int slots = 512;
     p.splits = p.groups >= slots ? 1 : slots / p.groups;
+    if (p.halves) p.splits = std::max(1, std::min(p.splits, 256 / ((p.groups + 1) / 2)));      // (one workgroup of bf_halves_kernel per compute unit)
     if (p.splits > 8) p.splits -= p.splits % 8;
     p.segs = p.splits * (p.stationary ? 2 : 8);
     // As many chunks, each larger by the same factor, as take the least time: a chunk costs a launch of either kernel and a
@@ -1350,10 +1617,12 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.qnorm = c.take<float>(p.batch_pad);
     v.qshift = c.take<float>(p.batch_pad);
     v.keep = c.take<float>(p.batch_pad);
+    v.keep_halves = p.halves ? c.take<float>(p.batch_pad) : nullptr;
     v.edge = c.take<float>(p.batch_pad);
     v.best_count = c.take<uint32_t>(p.batch_pad);
     v.qfrag = c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16 * 2);
     v.qbytes = p.stationary ? c.take<uint8_t>((size_t)p.batch_pad * p.KS * 16) : nullptr;
+    v.qhalf = p.halves ? c.take<uint16_t>((size_t)p.batch_pad * p.KS * 16) : nullptr;
     v.dense = c.take<float>((size_t)p.batch_pad * kDense);
     v.seg_count = c.take<uint32_t>((size_t)p.batch_pad * p.segs);
     v.lists = c.take<uint2>((size_t)p.batch * p.segs * p.seg_cap);
@@ -1372,6 +1641,7 @@ void launch_filter(const Plan& p, const BruteArgs& a, hipStream_t s) {
         hipLaunchKernelGGL((bf_filter_stationary_kernel<8, DENSE>), grid, block, 0, s, a);
     } else {
         hipLaunchKernelGGL((bf_filter_kernel<Elem, DENSE>), grid, block, 0, s, a);
+        if (!DENSE && p.halves) hipLaunchKernelGGL(bf_halves_kernel, dim3((unsigned)(p.splits * ((p.groups + 1) / 2))), dim3(2 * kBfThreads), 0, s, a);
     }
 }
 
@@ -1387,6 +1657,10 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
         a.out_ids = out_ids + (size_t)b0 * a.k;
         a.out_dists = out_dists + (size_t)b0 * a.k;
         hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(a.KS < 16 ? 256 : 1024), 0, s, a);
+        if (p.halves) {
+            const int64_t count = p.batch_pad / 32 * p.KS * kWave;
+            hipLaunchKernelGGL(pack_halves_kernel, dim3((unsigned)((count + kBfThreads - 1) / kBfThreads)), dim3(kBfThreads), 0, s, a, count);
+        }
         for (uint64_t pos = 0; pos < a.N;) {
             const bool dense = pos == 0;
             uint64_t rows = dense ? (uint64_t)kDense : (uint64_t)((double)pos * (p.growth - 1.0));
@@ -1400,7 +1674,13 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
             if (dense) launch_filter<Elem, true>(p, a, s);
             else launch_filter<Elem, false>(p, a, s);
             pos += rows;
-            hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, pos >= a.N ? 1 : 0, rank_at(a.k, (double)pos, (double)a.N));
+            // Entries up to the end of the rank-th's bin that need no division of the bin, which takes a small batch a microsecond:
+            // what they cost is an exact distance each, or, before the last chunk, the pairs that pass (see make_plan).
+            const bool last = pos >= a.N;
+            const int rank = rank_at(a.k, (double)pos, (double)a.N), least = rank + rank / 8 + 3;
+            const int room = std::min(rank + 64, (int)(1600.0 / p.growth));
+            const uint32_t few = (uint32_t)(last ? a.k + 128 : (a.nq < 1024 ? std::max(least, room) : least));
+            hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, last ? 1 : 0, rank, few);
         }
         const dim3 scan((unsigned)p.scan_grid), merge((unsigned)(a.nq < 256 ? a.nq : 256)), block(kBfThreads);
         if (p.scan_queries == 1) hipLaunchKernelGGL((bf_scan_kernel<Elem, 1>), scan, block, scan_lds(1, a.D), s, a);
@@ -1423,21 +1703,21 @@ uint64_t brute_force_step(uint64_t N) {
     return step;
 }
 
-size_t brute_force_norm_words(uint64_t N, int D, int elem_bytes) { return centre_at(N) + (elem_bytes == 1 ? (size_t)N : (size_t)D); }
+size_t brute_force_norm_words(uint64_t N, int D, int elem_bytes) { return elem_bytes == 1 ? centre_at(N) + (size_t)N : halves_at(N, D) + (size_t)N; }
 
 hipError_t launch_half_norms(const void* vectors, int elem_bytes, uint64_t N, int D, float* out, hipStream_t s) {
     const dim3 grid((unsigned)(N / 16 + 1 < 2048 ? N / 16 + 1 : 2048)), block(kBfThreads);
-    const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
+    const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D), half = pqt_host::brute_error_half(D);
     float* centre = out + centre_at(N);
     hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(3), 0, s, reinterpret_cast<uint32_t*>(out) + N);
     if (elem_bytes == 1) {
-        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, err.dot, err.norm, out, reinterpret_cast<int*>(centre));
+        hipLaunchKernelGGL(half_norms_kernel<uint8_t>, grid, block, 0, s, static_cast<const uint8_t*>(vectors), (int64_t)N, D, centre, err, half, out, reinterpret_cast<int*>(centre), nullptr);
     } else {
         const float* x = static_cast<const float*>(vectors);
         const uint64_t step = brute_force_step(N);
         hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((D + kWave - 1) / kWave)), block, 0, s, x, N, step, D, centre);
         hipLaunchKernelGGL(use_centre_kernel, dim3(1), dim3(1024), 0, s, x, N, step, D, centre, reinterpret_cast<uint32_t*>(out) + N + 1, out + N + 2);
-        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, err.dot, err.norm, out, nullptr);
+        hipLaunchKernelGGL(half_norms_kernel<float>, grid, block, 0, s, x, (int64_t)N, D, centre, err, half, out, nullptr, out + halves_at(N, D));
     }
     return hipGetLastError();
 }
@@ -1453,9 +1733,9 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     a.use_centre = reinterpret_cast<const uint32_t*>(half_norms) + N + 1;
     a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
     a.step = brute_force_step(N);
-    const pqt_host::BruteError err = pqt_host::brute_error(elem_bytes, D);
-    a.err_dot = err.dot;
-    a.err_norm = err.norm;
+    a.err = pqt_host::brute_error(elem_bytes, D);
+    a.err_half = pqt_host::brute_error_half(D);
+    a.xhalf_halves = elem_bytes == 4 ? half_norms + halves_at(N, D) : nullptr;
     return elem_bytes == 1 ? run<uint8_t>(p, a, queries, nq, out_ids, out_dists, s) : run<float>(p, a, queries, nq, out_ids, out_dists, s);
 }
 

@@ -199,6 +199,16 @@ BruteError brute_error(int elem_bytes, int D) {
     BruteError e;
     e.dot = (float)(1.03 * (cut + adding + centre));
     e.norm = (float)(1.03 * 0.5 * (adding + (D / 64 + 28) / 16777216.0 + centre));
+    e.flush = 0.0f;
+    return e;
+}
+
+BruteError brute_error_half(int D) {
+    const double adding = (16.0 * ((D + 15) / 16) + 16.0) / 8388608.0, centre = 1.0 / 8388608.0;
+    BruteError e;
+    e.dot = (float)(1.03 * (1.0 / 1024.0 + adding + centre));
+    e.norm = (float)(1.03 * 0.5 * (adding + (D / 64 + 28) / 16777216.0 + centre));
+    e.flush = (float)(1.03 * 2.0 * std::sqrt((double)D) / 268435456.0);
     return e;
 }
 

@@ -65,11 +65,16 @@ int make_static_order(int R, int T, std::vector<uint32_t>& table, float thr[kSlo
 //     or a sum.  At most six such losses per dimension of up to 8,192 (2^-110), and pieces times the other vector, which
 //     the next power of two and the relative terms cover.
 // 3 % on top for the terms of higher order and the rounding of the norms.
+//   * Halves (brute_error_half): eleven significant bits, so either number loses up to 2^-11 of itself, 2^-10 of a product; one
+//     product instead of three is added up.  Both are scaled so that the query's norm and the largest vector's lie in 2^14 ..
+//     2^15, and what then lies below 2^-14, the smallest normal half, may be taken for zero: sqrt(D) 2^-14 of such numbers against the
+//     other's norm, 2^-28 sqrt(D) ||q|| X for either, X the largest norm of all (flush ||q|| X).
 struct BruteError {
-    float dot, norm;
+    float dot, norm, flush;
 };
 constexpr float kBruteUnderflow = 0x1p-109f;
 BruteError brute_error(int elem_bytes, int D);
+BruteError brute_error_half(int D);
 
 // number of pairs (a, b), a < nA, b < nB, with (a+1)(b+1) <= Tn
 long region_size(int nA, int nB, int Tn);

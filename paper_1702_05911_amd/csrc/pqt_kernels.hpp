@@ -6,6 +6,8 @@
 
 #include <vector>
 
+#include "pqt_host.hpp"
+
 namespace pqt {
 
 constexpr int kQueryTile = 16;          // queries per workgroup of the traversal kernel (MFMA rows)
@@ -211,7 +213,8 @@ struct BruteArgs {
     int64_t* out_ids;             // nq x k
     float* out_dists;             // nq x k
     uint64_t step;                // the database order: place i is vector (i * step) mod N
-    float err_dot, err_norm;      // error bound: err_dot ||q|| ||x|| + err_norm ||x||^2
+    pqt_host::BruteError err, err_half;       // error bounds of bf16 pieces and of halves
+    const float* xhalf_halves;    // floats: as xhalf, for products of halves
     // the current chunk: chunk_rows vectors from place chunk_pos on
     uint64_t chunk_pos;
     int64_t chunk_rows;
@@ -223,11 +226,13 @@ struct BruteArgs {
     uint32_t* todo;               // those queries
     float* qnorm;                 // ||q||
     float* qshift;                // what makes a value one of centred vectors
-    float* keep;                  // largest value that still matters ...
-    float* edge;                  // ... if the k-th smallest is at most this
+    float* edge;                  // the k-th smallest value is taken to be at most this, ...
+    float* keep;                  // ... so that larger values than this do not matter,
+    float* keep_halves;           // or, of products of halves, than this
     uint32_t* best_count;         // entries of best
     uint16_t* qfrag;              // queries, two bf16 pieces, operand layout
     uint8_t* qbytes;              // the same less 128 as bytes, operand layout (byte vectors of at most 128 dimensions, else null)
+    uint16_t* qhalf;              // floats: queries, one piece of half precision, scaled, operand layout (null: not used)
     float* dense;                 // values of the first chunk, a row per query
     int splits;                   // workgroups that share a query group's database tiles
     int segs, seg_cap;            // lists per query and entries per list

@@ -5,6 +5,7 @@
 //   static <R> <T>                       make_static_order                       -> "Tn <n>", 9 thresholds (hex floats), 10 table rows
 //   region <nA> <nB> <Tn>                region_size                             -> "n <count>"
 //   bound <elem_bytes> <D>               brute_error                             -> "<dot> <norm>" (hex floats)
+//   halves <D>                           brute_error_half                        -> "<dot> <norm> <flush>" (hex floats)
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -58,6 +59,11 @@ int main(int argc, char** argv) {
     if (mode == "bound" && argc == 4) {
         const pqt_host::BruteError e = pqt_host::brute_error(atoi(argv[2]), atoi(argv[3]));
         printf("%a %a\n", (double)e.dot, (double)e.norm);
+        return 0;
+    }
+    if (mode == "halves" && argc == 3) {
+        const pqt_host::BruteError e = pqt_host::brute_error_half(atoi(argv[2]));
+        printf("%a %a %a\n", (double)e.dot, (double)e.norm, (double)e.flush);
         return 0;
     }
     return 2;

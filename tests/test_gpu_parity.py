@@ -1322,6 +1322,50 @@ def test_brute_force_misleading_order(pqt, stored, N, D, early, k):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("N, D, nq, kind", [
+    (70_001, 336, 300, "even"),              # products of halves: an odd number of steps of sixteen dimensions, 256 queries and some
+    (40_000, 500, 513, "even"),              # a partial last step; one query past two groups
+    (70_001, 336, 300, "a crowd"),           # one query with thousands of vectors in the halves' window: its group keeps to bf16
+    (70_001, 336, 300, "an offset"),         # vectors relative to their centre
+    (70_001, 336, 300, "small and large"),   # numbers that are zero as scaled halves; a query and vectors far longer than others
+    (70_001, 336, 300, "out of range"),      # norms that are not scaled to halves
+])
+def test_brute_force_halves(pqt, N, D, nq, kind):
+    """Float collections large enough to be filtered by products of halves, against distances in float64: a distance is a sum of D
+    squares in fp32, relative error below (D + 2) 2^-24, and the k-th distance is the true one to that bound."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(61)
+    k = 20
+    X = torch.rand((N, D), generator=gen, device="cuda") - 0.5
+    Y = torch.rand((nq, D), generator=gen, device="cuda") - 0.5
+    if kind == "a crowd":
+        X[::7] = Y[5] * (1 + 1e-4 * torch.rand((len(X[::7]), 1), generator=gen, device="cuda")) + 1e-4 * X[::7]
+    elif kind == "an offset":
+        X, Y = X + 20, Y + 20
+    elif kind == "small and large":
+        X[::3] *= 1e-7
+        X[::1000] *= 1e4
+        Y[7] *= 1e5
+        Y[11] *= 1e-6
+    elif kind == "out of range":
+        X, Y = X * 1e-14, Y * 1e-14
+    ix = _vectors_only_index(pqt, N, D)
+    try:
+        pqt.pqt_index_set_vectors(ix, X)
+        for _ in range(2):
+            ids, d = pqt.pqt_brute_force(ix, Y, k)
+        x = X.double()
+        bound = (D + 2) * 2.0 ** -24
+        for q in list(range(0, nq, 9)) + [5, 7, 11, nq - 1]:
+            true = ((x - Y[q].double()) ** 2).sum(1)
+            own = true[ids[q]]
+            assert len(set(ids[q].tolist())) == k
+            assert (d[q].double() - own).abs().le(bound * own).all(), q
+            assert (d[q].double() - true.sort().values[:k]).abs().le(2 * bound * own).all(), q
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 @pytest.mark.parametrize("stored, D", [("u8", 32), ("f32", 20)])
 def test_brute_force_in_rounds(pqt, stored, D):
     """More queries than one round of the workspace holds (16,384): the queries on both sides of the border and the last ones

@@ -213,3 +213,32 @@ def test_brute_force_error_bound(driver, elem_bytes, D):
         true = D * q.astype(np.float64) * x - 0.5 * D * x.astype(np.float64) ** 2
         bound = dot * D * np.abs(q.astype(np.float64) * x) + norm * D * x.astype(np.float64) ** 2
         assert (np.abs(s - true) <= bound).all(), (np.abs(s - true) / bound).max()
+
+
+@pytest.mark.parametrize("D", [4, 96, 200, 960])
+@pytest.mark.parametrize("small", [1.0, 2.0 ** -12, 2.0 ** -30])
+def test_brute_force_halves_error_bound(driver, D, small):
+    """The same for products of halves: the query and the longest vector (norm X) scaled to norms of 2^14 .. 2^15, numbers rounded
+    to half precision, those below 2^-14 taken for zero, the products added with every addition truncated.  `small`: the other
+    vectors' size against the longest's, down to where all of their numbers are taken for zero."""
+    dot, norm, flush = (float.fromhex(v) for v in driver("halves", D).split())
+    grid = (1.0 + np.arange(40_000) / 40_000).astype(np.float32)
+    left = np.abs(grid - grid.astype(np.float16).astype(np.float32)) / grid
+    worst = grid[np.concatenate([np.argsort(-left)[:40], [0, len(grid) - 1]])]
+    q, x = (v.ravel() for v in np.meshgrid(worst, worst * np.float32(small)))
+    X = np.sqrt(D) * 2.0                                            # longest norm: coordinates of two
+    to = lambda v: 2.0 ** (14 - np.floor(np.log2(v)))
+    sq, sx = to(np.sqrt(D) * q.astype(np.float64)), to(X)
+    hq, hx = (np.where(np.abs(v) < 2.0 ** -14, 0.0, v.astype(np.float16).astype(np.float64)) for v in (q * sq, x * sx))
+    half = 0.5 * D * x.astype(np.float64) ** 2
+    for order in (1, -1):                                            # products first added to the norm, or last
+        start = _truncate(-half * sq * sx)
+        s = start if order == 1 else np.zeros_like(start)
+        for _ in range(D):
+            s = _truncate(s.astype(np.float64) + hq * hx)
+        if order == -1:
+            s = _truncate(s.astype(np.float64) + start)
+        true = D * q.astype(np.float64) * x - half
+        qn, xn = np.sqrt(D) * q.astype(np.float64), np.sqrt(D) * np.abs(x.astype(np.float64))
+        bound = dot * qn * xn + norm * xn ** 2 + flush * qn * X
+        assert (np.abs(s / (sq * sx) - true) <= bound).all(), (np.abs(s / (sq * sx) - true) / bound).max()
