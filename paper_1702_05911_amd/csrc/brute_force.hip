@@ -179,6 +179,7 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
         g.qnorm[q] = sqrtf(n2);
         g.qshift[q] = g.use_centre[0] ? 0.0f : c;
         g.flagged[q] = 0u;
+        g.scan_done[q] = 0u;
         if (g.qhalf && (!half_norm_ok(sqrtf(n2)) || !half_norm_ok(g.xhalf[g.N] + g.xhalf[g.N + 2]))) atomicOr(&state, kNoHalves);
     }
     if (g.qhalf) __syncthreads();
@@ -1344,7 +1345,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
 // The queries the filter gave up on: exact distances to every vector, what beats the k-th best so far is kept in LDS and
 // the k best are selected again whenever that may fill.  A workgroup has QB queries, which share the rows it reads (two at a
 // time in registers: each of the queries' values in LDS is read once for both), and one of `splits` parts of the database, as many
-// as give every workgroup of the launch work; with more than one part bf_merge_kernel joins their results.
+// as give every workgroup of the launch work; the workgroup that ends the last of several parts joins their results.
 // 2,000 queries that all tie, 1M x 128 bytes: 20.6 ms (one workgroup per query, a row read for one query: 47); one such query:
 // 0.36 ms (20.7).
 constexpr int kScanQueries = 4;
@@ -1360,12 +1361,49 @@ __device__ __forceinline__ uint32_t scan_splits(uint32_t ntodo, uint32_t queries
     return max(1u, min(min(grid / blocks, (uint32_t)kScanSplits), rows));
 }
 
+// The k best of the parts of a scanned query, by one workgroup; keys: kScanKeys entries.
+__device__ __forceinline__ void merge_parts(const BruteArgs& g, uint32_t at, int splits, unsigned long long* keys, uint32_t* pending) {
+    constexpr int kStep = kScanKeys / 2;
+    const int tid = threadIdx.x, k = g.k, total = splits * k;
+    const unsigned long long* parts = g.parts + (size_t)at * total;
+    for (int e = tid; e < k; e += kBfThreads) keys[e] = ~0ull;
+    if (tid == 0) *pending = 0u;
+    __syncthreads();
+    unsigned long long tau = ~0ull;
+    for (int e0 = 0; e0 < total; e0 += kStep) {
+#pragma unroll
+        for (int u = 0; u < kStep / kBfThreads; ++u) {
+            const int e = e0 + u * kBfThreads + tid;
+            const unsigned long long key = e < total ? parts[e] : ~0ull;
+            if (key < tau) keys[k + atomicAdd(pending, 1u)] = key;
+        }
+        __syncthreads();
+        const uint32_t np = *pending;
+        __syncthreads();
+        if (np + (uint32_t)kStep > (uint32_t)(kScanKeys - k) || e0 + kStep >= total) {
+            const int n = k + (int)np, npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
+            for (int e = n + tid; e < npad; e += kBfThreads) keys[e] = ~0ull;
+            if (tid == 0) *pending = 0u;
+            block_sort_lds<4>(keys, npad, tid, kBfThreads);
+            tau = keys[k - 1];
+            __syncthreads();
+        }
+    }
+    const size_t q = g.todo[at];
+    for (int e = tid; e < k; e += kBfThreads) {
+        const unsigned long long key = keys[e];
+        g.out_ids[q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
+        g.out_dists[q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
+    }
+    __syncthreads();
+}
+
 template <typename Elem, int QB>
 __global__ __launch_bounds__(kBfThreads, 4) void bf_scan_kernel(BruteArgs g) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem);    // [QB][kScanKeys]
     float* sy = reinterpret_cast<float*>(smem + sizeof(unsigned long long) * QB * kScanKeys);      // [QB][D]
-    __shared__ uint32_t pending[QB];
+    __shared__ uint32_t pending[QB], parts_done;
     constexpr int kRows = 2;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k, D = g.D;
     const uint32_t ntodo = g.control[kBfTodo];
@@ -1459,51 +1497,15 @@ __global__ __launch_bounds__(kBfThreads, 4) void bf_scan_kernel(BruteArgs g) {
                 }
             }
         }
-    }
-}
-
-// The k best of the parts of a scanned query.  One workgroup per query at a time.
-constexpr int kMergeKeys = 2048, kMergeStep = 1024;
-__global__ __launch_bounds__(kBfThreads) void bf_merge_kernel(BruteArgs g, int scan_queries, int scan_grid) {
-    __shared__ unsigned long long keys[kMergeKeys];
-    __shared__ uint32_t pending;
-    const int tid = threadIdx.x, k = g.k;
-    const uint32_t ntodo = g.control[kBfTodo];
-    if (ntodo == 0) return;
-    const uint32_t splits = scan_splits(ntodo, (uint32_t)scan_queries, (uint32_t)scan_grid, g.N);
-    if (splits == 1) return;
-    const int total = (int)splits * k;
-    for (uint32_t i = blockIdx.x; i < ntodo; i += gridDim.x) {
-        const unsigned long long* parts = g.parts + (size_t)i * total;
-        __syncthreads();
-        for (int e = tid; e < k; e += kBfThreads) keys[e] = ~0ull;
-        if (tid == 0) pending = 0u;
-        __syncthreads();
-        unsigned long long tau = ~0ull;
-        for (int e0 = 0; e0 < total; e0 += kMergeStep) {
-#pragma unroll
-            for (int u = 0; u < kMergeStep / kBfThreads; ++u) {
-                const int e = e0 + u * kBfThreads + tid;
-                const unsigned long long key = e < total ? parts[e] : ~0ull;
-                if (key < tau) keys[k + atomicAdd(&pending, 1u)] = key;
-            }
+        if (splits > 1) {                              // the workgroup that ends the last part of these queries joins them
+            __threadfence();
             __syncthreads();
-            const uint32_t np = pending;
+            if (tid == 0) parts_done = atomicAdd(&g.scan_done[item / splits], 1u);
             __syncthreads();
-            if (np + (uint32_t)kMergeStep > (uint32_t)(kMergeKeys - k) || e0 + kMergeStep >= total) {
-                const int n = k + (int)np, npad = next_pow2(n) < 64 ? 64 : next_pow2(n);
-                for (int e = n + tid; e < npad; e += kBfThreads) keys[e] = ~0ull;
-                if (tid == 0) pending = 0u;
-                block_sort_lds<8>(keys, npad, tid, kBfThreads);
-                tau = keys[k - 1];
-                __syncthreads();
+            if (parts_done == splits - 1u) {
+                __threadfence();
+                for (uint32_t at = first; at < first + (uint32_t)QB && at < ntodo; ++at) merge_parts(g, at, (int)splits, keys, pending);
             }
-        }
-        const size_t q = g.todo[i];
-        for (int e = tid; e < k; e += kBfThreads) {
-            const unsigned long long key = keys[e];
-            g.out_ids[q * k + e] = key == ~0ull ? -1 : (int64_t)(uint32_t)key;
-            g.out_dists[q * k + e] = key == ~0ull ? __builtin_inff() : mono_inv((uint32_t)(key >> 32));
         }
     }
 }
@@ -1614,6 +1616,7 @@ size_t carve(const Plan& p, int k, unsigned char* base, BruteArgs* a) {
     v.flagged = c.take<uint32_t>(p.batch_pad);
     v.second = c.take<uint32_t>(p.batch_pad / 32);
     v.todo = c.take<uint32_t>(p.batch_pad);
+    v.scan_done = c.take<uint32_t>(p.batch_pad);
     v.qnorm = c.take<float>(p.batch_pad);
     v.qshift = c.take<float>(p.batch_pad);
     v.keep = c.take<float>(p.batch_pad);
@@ -1682,10 +1685,9 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
             const uint32_t few = (uint32_t)(last ? a.k + 128 : (a.nq < 1024 ? std::max(least, room) : least));
             hipLaunchKernelGGL((bf_select_kernel<Elem>), dim3((unsigned)a.nq), dim3(kBfThreads), select_lds, s, a, dense ? 1 : 0, last ? 1 : 0, rank, few);
         }
-        const dim3 scan((unsigned)p.scan_grid), merge((unsigned)(a.nq < 256 ? a.nq : 256)), block(kBfThreads);
+        const dim3 scan((unsigned)p.scan_grid), block(kBfThreads);
         if (p.scan_queries == 1) hipLaunchKernelGGL((bf_scan_kernel<Elem, 1>), scan, block, scan_lds(1, a.D), s, a);
         else hipLaunchKernelGGL((bf_scan_kernel<Elem, kScanQueries>), scan, block, scan_lds(kScanQueries, a.D), s, a);
-        hipLaunchKernelGGL(bf_merge_kernel, merge, block, 0, s, a, p.scan_queries, p.scan_grid);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -224,6 +224,7 @@ struct BruteArgs {
     uint32_t* flagged;            // nq: 1 = left to the exact scan
     uint32_t* second;             // per tile of 32 queries: has one a second bf16 piece, or a value that is not a byte
     uint32_t* todo;               // those queries
+    uint32_t* scan_done;          // parts of the database that a group of them has been compared with
     float* qnorm;                 // ||q||
     float* qshift;                // what makes a value one of centred vectors
     float* edge;                  // the k-th smallest value is taken to be at most this, ...
