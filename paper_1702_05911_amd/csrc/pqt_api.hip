@@ -551,9 +551,10 @@ size_t carve_workspace(const pqt_index* ix, int64_t nq, int R, unsigned char* ba
 }
 
 // The whole query path.  no_alloc: the workspace is the static scratch array and nothing may be
-// allocated (no workspace growth, no events, no upload of fixed-order tables).
+// allocated (no workspace growth, no events, no upload of fixed-order tables).  set_only: the k best in any order, distances not
+// needed.
 int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int64_t* out_ids, float* out_dists,
-                     void* hip_stream, const pqt_debug_taps* taps, bool no_alloc) {
+                     void* hip_stream, const pqt_debug_taps* taps, bool no_alloc, bool set_only = false) {
     if (!ix) return fail(PQT_EINVAL, "pqt_query_batch: null index");
     if (nq < 0) return fail(PQT_EINVAL, "pqt_query_batch: nq=%lld < 0", (long long)nq);
     if (k < 1 || k > PQT_MAX_K || (uint32_t)k > ix->C)
@@ -641,6 +642,7 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     ca.code_format = (int)ix->code_format;
     ca.runs_in_lds = rerank_runs_in_lds(ix);
     ca.early = 0;
+    ca.set_only = set_only ? 1 : 0;
     ca.a = ws.a; ca.table = ix->table; ca.runs = ws.runs; ca.meta = ws.meta;
     ca.ids = ix->ids; ca.codes = ix->codes; ca.out_ids = out_ids; ca.out_dists = out_dists;
     ca.n_cand = tp.n_cand; ca.cand_ids = tp.cand_ids; ca.scores = tp.scores; ca.lut = tp.lut;
@@ -798,7 +800,7 @@ int pqt_query_batch_exact(pqt_index* ix, const float* queries, int64_t nq, int k
         HIP_TRY(hipMalloc(reinterpret_cast<void**>(&ix->ws_short_dists), entries * sizeof(float)));
         ix->ws_short_entries = entries;
     }
-    const int rc = pqt_query_batch(ix, queries, nq, k_short, w, ix->ws_short_ids, ix->ws_short_dists, hip_stream);
+    const int rc = run_query(ix, queries, nq, k_short, w, ix->ws_short_ids, ix->ws_short_dists, hip_stream, nullptr, false, true);
     if (rc) return rc;
     pqt::ExactArgs ea;
     ea.nq = nq; ea.D = ix->D; ea.k_short = k_short; ea.k = k; ea.elem_bytes = ix->vector_elem_bytes;

@@ -158,6 +158,7 @@ struct RerankArgs {
     const uint32_t* todo;
     const uint32_t* todo_count;
     int early;
+    int set_only = 0;         // the caller wants the k best in any order; long lists (k > threads) may come so, without distances
     // set by launch_rerank when the kernel ranks left-over queries: their first wavefront tries this many
     // tuples (the pairs of the head-pass table up to mid_npairs) before the workgroup ranks in full
     int mid_T1 = 0, mid_npairs = 0;

@@ -1438,6 +1438,42 @@ def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("k_short, k, C, same", [
+    (257, 10, 2000, 0),                    # one more than the workgroup's threads
+    (1000, 1000, 4096, 0),                 # all of the short list is wanted
+    (1000, 100, 1100, 0),                  # queries with fewer candidates than that
+    (600, 50, 4096, 3000),                 # equal codes: bins too full to place by
+])
+def test_exact_rerank_of_long_lists(pqt, k_short, k, C, same):
+    """Short lists longer than the workgroup come without order: exact re-ranking gets the same vectors as from the ordered list
+    of pqt_query_batch, whose exact distances (whole numbers) are taken here."""
+    import torch
+    rng = np.random.default_rng(29)
+    N, D, P, k1, k2, M, H, T, w, nq = 30_000, 32, 2, 16, 8, 8, 2048, 512, 4, 1100
+    X = rng.integers(0, 64, (N, D))
+    offsets = np.concatenate([[0], np.cumsum(rng.multinomial(N, rng.dirichlet(np.full(H, 0.3))))])
+    C1 = X[rng.permutation(N)[:P * k1]].reshape(P, k1, D)[:, :, :D // P]
+    code = rng.integers(0, 256, (N, M))
+    code[rng.permutation(N)[:same * 9]] = code[0]
+    ix = pqt.pqt_index_from_arrays(dict(
+        N=N, H=H, D=D, P=P, k1=k1, k2=k2, M=M, T=T, C=C, C1=C1, C2=C1[:, :, None] + rng.integers(-8, 9, (P, k1, k2, D // P)),
+        tbl_i=rng.integers(0, k1, (M, 256)), tbl_j=rng.integers(0, k1, (M, 256)), tbl_lam=rng.normal(0.5, 0.5, (M, 256)),
+        cc=rng.integers(1, 500, (M, k1, k1)), offsets=offsets, ids=rng.permutation(N), codes=code))
+    try:
+        x = torch.from_numpy(X.astype(np.uint8)).cuda()
+        pqt.pqt_index_set_vectors(ix, x)
+        Y = torch.from_numpy(rng.integers(0, 64, (nq, D)).astype(np.float32)).cuda()
+        short, _ = pqt.pqt_query_batch(ix, Y, k_short, w)
+        ids, d = pqt.pqt_query_batch_exact(ix, Y, k_short, k, w)
+        true = ((x[short.clamp(min=0)].double() - Y.double()[:, None]) ** 2).sum(2)
+        key = torch.where(short >= 0, true * N + short, torch.inf).sort(1).values[:, :k]
+        want = torch.where(key.isinf(), -1.0, torch.remainder(key, N)).long()
+        assert torch.equal(ids, want)
+        assert torch.equal(d.double(), torch.where(key.isinf(), torch.inf, torch.div(key, N, rounding_mode="floor")))
+    finally:
+        pqt.pqt_index_free(ix)
+
+
 def test_four_part_index(pqt, tmp_path):
     """P = 4: parts (1,2) and (3,4) are ranked first, then pairs of positions in those two lists."""
     from workloads import tiny_mixture
