@@ -647,11 +647,27 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     ca.ids = ix->ids; ca.codes = ix->codes; ca.out_ids = out_ids; ca.out_dists = out_dists;
     ca.n_cand = tp.n_cand; ca.cand_ids = tp.cand_ids; ca.scores = tp.scores; ca.lut = tp.lut;
     ra.n_tuples = tp.n_tuples; ra.tuples = tp.tuples; ra.tuple_keys = tp.tuple_keys; ra.slots = tp.slots;
+    pqt::StaticOrder so = {};
+    if (fixed_order) {
+        if (tables_stale) {                                             // tables for this list length and T
+            HIP_TRY(hipStreamSynchronize(stream));                      // an earlier batch may still read the old tables
+            (void)hipFree(ix->static_table);
+            ix->static_table = nullptr;
+            ix->static_R = ix->static_T = 0;
+            HIP_TRY(hipMalloc(reinterpret_cast<void**>(&ix->static_table), static_host.size() * sizeof(uint32_t)));
+            HIP_TRY(hipMemcpy(ix->static_table, static_host.data(), static_host.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+            ix->static_R = R;
+            ix->static_T = (int)ix->T;
+        }
+        so.table = ix->static_table;
+        so.Tn = ix->static_Tn;
+        for (int j = 0; j < pqt::kStaticSlopes - 1; ++j) so.thr[j] = ix->static_thr[j];
+    }
     // A small batch in one launch (stage times and intermediate results exist only between launches)
-    if (!taps && !ev && !fixed_order && nq <= kSmallBatch) {
+    if (!taps && !ev && nq <= kSmallBatch) {
         const size_t lds = pqt::small_query_lds(ca, ra, ta);
         if (lds != 0 && lds <= ix->lds_limit) {
-            HIP_TRY(pqt::launch_small_query(ca, ra, ta, mean_need < small_head_below(nq), stream));
+            HIP_TRY(pqt::launch_small_query(ca, ra, ta, mean_need < small_head_below(nq), fixed_order ? &so : nullptr, stream));
             return PQT_OK;
         }
     }
@@ -666,20 +682,6 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     // the few queries the head pass cannot finish are ranked in full by their re-rank workgroup
     const bool fuse = head && !rerank_taps && can_fuse_ranking(ix, k, w, nq);
     if (fixed_order) {
-        if (tables_stale) {                                             // tables for this list length and T
-            HIP_TRY(hipStreamSynchronize(stream));                      // an earlier batch may still read the old tables
-            (void)hipFree(ix->static_table);
-            ix->static_table = nullptr;
-            ix->static_R = ix->static_T = 0;
-            HIP_TRY(hipMalloc(reinterpret_cast<void**>(&ix->static_table), static_host.size() * sizeof(uint32_t)));
-            HIP_TRY(hipMemcpy(ix->static_table, static_host.data(), static_host.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-            ix->static_R = R;
-            ix->static_T = (int)ix->T;
-        }
-        pqt::StaticOrder so;
-        so.table = ix->static_table;
-        so.Tn = ix->static_Tn;
-        for (int j = 0; j < pqt::kStaticSlopes - 1; ++j) so.thr[j] = ix->static_thr[j];
         HIP_TRY(pqt::launch_rank_static(ra, so, stream));
     } else {
         HIP_TRY(pqt::launch_rank(ra, stream, fuse));

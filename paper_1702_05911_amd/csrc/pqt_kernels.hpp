@@ -125,6 +125,7 @@ hipError_t launch_rank(const RankArgs& a, hipStream_t s, bool defer_full);
 // the rank pairs, one per slope 1.08^k, k = -5..4; a query takes the one whose slope matches how fast
 // its two lists rise.  Two tree parts, unhashed bins.
 constexpr int kStaticSlopes = 10;
+constexpr int kSlopeReferenceRank = 8;    // where a list's rise is measured
 struct StaticOrder {
     const uint32_t* table;     // kStaticSlopes x Tn entries r1 << 16 | r2 (device)
     int Tn;                    // min(T, R^2)
@@ -178,10 +179,11 @@ int rerank_fused_tuples_per_thread();
 // workgroup size and candidates per thread of the re-rank kernel for a candidate budget C
 // (C <= threads * keys_per_thread; the fewest threads that hold the budget)
 void rerank_shape(int C, int M, int code_format, int* threads, int* keys_per_thread);
-// A small batch in one launch, a workgroup of 1,024 threads per query (no taps, order by summed distance).  LDS of a workgroup, 0: these
+// A small batch in one launch, a workgroup of 1,024 threads per query (no taps; `fixed`: in the fixed bin order, else by summed
+// distance).  LDS of a workgroup, 0: these
 // arguments are not taken.  head: the first wavefront tries 32 and 64 tuples by itself (two parts).
 size_t small_query_lds(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr);
-hipError_t launch_small_query(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, bool head, hipStream_t s);
+hipError_t launch_small_query(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, bool head, const StaticOrder* fixed, hipStream_t s);
 // fused: the full ranking pass of the queries whose meta.x is kMetaTodo runs inside the kernel
 hipError_t launch_rerank(const RerankArgs& a, const RankArgs* fused, hipStream_t s);
 

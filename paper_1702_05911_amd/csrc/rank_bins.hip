@@ -139,7 +139,6 @@ __global__ __launch_bounds__((PF == 4 && MAXPER <= 4) || (PF == 2 && MAXPER > 4)
 // One wavefront per query walks its table 64 tuples at a time and stops when the runs fill C.
 // ------------------------------------------------------------------------------------------------
 constexpr int kStaticThreads = 256;
-constexpr int kSlopeReferenceRank = 8;
 
 __global__ __launch_bounds__(kStaticThreads) void rank_static_kernel(RankArgs g, StaticOrder so) {
     const int lane = threadIdx.x & (kWave - 1);

@@ -127,7 +127,8 @@ size_t small_query_lds(const RerankArgs& a, const RankArgs& rk, const TraverseAr
     return small_query_layout(a, rk, tr, RL, L, sm) ? sm.lds : 0;
 }
 
-hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const TraverseArgs& tr, bool head, hipStream_t s) {
+hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const TraverseArgs& tr, bool head, const StaticOrder* fixed,
+                              hipStream_t s) {
     if (a_in.nq <= 0) return hipSuccess;
     RerankArgs a = a_in;
     a.pair_shift = pair_table_shift(a.k1);
@@ -139,7 +140,8 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
     if (a.keys_per_thread != kKeysPerThread || a.n_cand || a.cand_ids || a.scores || a.lut || !small_query_layout(a, rk, tr, RL, L, sm))
         return hipErrorInvalidValue;
     sm.levels = HeadLevels{};
-    if (head && rk.P == 2)
+    sm.fixed = fixed ? *fixed : StaticOrder{};
+    if (head && !fixed && rk.P == 2)
         for (int l = 0; l < 2; ++l) {
             const int t = 32 << l;
             sm.levels.T1[l] = RL.Tcap < t ? RL.Tcap : t;

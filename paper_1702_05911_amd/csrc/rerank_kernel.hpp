@@ -941,6 +941,44 @@ __device__ __forceinline__ void prepare_table(const RerankArgs& g, const RerankL
     for (int e = who; e < kHistSize; e += n) hist[e] = 0;
 }
 
+// The fixed bin order (rank_static_kernel has its definition) of a query whose lists are in LDS, by a workgroup: as many tuples at a
+// time as it has threads.  part: two times 16 words for prefix sums.  Ends with a barrier.
+__device__ __forceinline__ void rank_static_query(const RankArgs& g, const StaticOrder& so, int64_t q, const float* sLd, const uint32_t* sLid,
+                                                  uint32_t* part, uint32_t* out_counts, const RunSink& sink) {
+    const int tid = threadIdx.x, nt = blockDim.x, R = g.R;
+    const uint32_t C = (uint32_t)g.C;
+    const int r0 = R - 1 < kSlopeReferenceRank ? R - 1 : kSlopeReferenceRank;
+    const float g1 = sLd[r0] - sLd[0], g2 = sLd[R + r0] - sLd[R];
+    int slope = 0;
+#pragma unroll
+    for (int j = 0; j < kStaticSlopes - 1; ++j) slope += (g2 > so.thr[j] * g1) ? 1 : 0;
+    const uint32_t* tab = so.table + (size_t)slope * so.Tn;
+    uint32_t total = 0, nruns = 0;
+    for (int base = 0; base < so.Tn && total < C; base += nt) {
+        const int t = base + tid;
+        uint32_t len = 0, o0 = 0;
+        if (t < so.Tn) {
+            const uint32_t ab = tab[t];
+            const unsigned long long slot = (unsigned long long)sLid[ab >> 16] * g.k1k2 + sLid[R + (ab & 0xffffu)];
+            o0 = g.offsets[slot];
+            len = g.offsets[slot + 1] - o0;
+        }
+        uint32_t here, runs;
+        const uint32_t start = total + block_exclusive_sum(len, part, here);
+        const bool emit = len > 0 && start < C;
+        const uint32_t at = nruns + block_exclusive_sum(emit ? 1u : 0u, part + 16, runs);
+        if (emit && !sink.put(at, o0, start)) g.runs[(size_t)q * g.T + at] = make_uint2(o0, start);
+        total += here;
+        nruns += runs;
+        __syncthreads();                       // (the prefix sums' memory)
+    }
+    if (tid == 0) {
+        out_counts[0] = nruns;
+        out_counts[1] = total < C ? total : C;
+    }
+    __syncthreads();
+}
+
 // A whole query of a small batch by one workgroup of 1,024 threads, in one launch: traversal, ranking, re-ranking.  Every query has
 // a compute unit of its own, so what it costs is the chain of its steps, and of a launch that starts when the one before
 // has drained (4 us each) there is one instead of three; lists, level-1 distances and runs stay in LDS, and the table of Eq. 9 is
@@ -966,7 +1004,10 @@ __global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds 
     sink.start = reinterpret_cast<uint32_t*>(smem + L.run_start);
     sink.cap = (uint32_t)L.rcap;
     bool ranked = false;
-    if (sm.levels.T1[0] > 0) {
+    if (sm.fixed.table) {
+        rank_static_query(rk, sm.fixed, q, sLd, sLid, reinterpret_cast<uint32_t*>(ranking + RL.part), misc + kRanked, sink);
+        ranked = true;
+    } else if (sm.levels.T1[0] > 0) {
         if (tid < kWave) {                     // the head pass's first two levels
             HeadLds& S = *reinterpret_cast<HeadLds*>(smem + sm.off_head);
             const int R1 = rk.R < kHeadT ? rk.R : kHeadT;

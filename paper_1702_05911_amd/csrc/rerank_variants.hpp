@@ -15,9 +15,10 @@ struct RerankLds {
 };
 
 // What the kernel that answers a query of a small batch has besides: its LDS, and the tuples the first wavefront ranks by itself
-// (T1[0] = 0: none).
+// (T1[0] = 0: none), or the fixed order.
 struct SmallQuery {
     HeadLevels levels;
+    StaticOrder fixed;               // the fixed bin order (table null: by summed distance)
     uint32_t off_traverse, off_tables, off_ranking, off_head, lds;
 };
 

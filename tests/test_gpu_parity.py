@@ -1434,6 +1434,13 @@ def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
                 assert torch.equal(few, ids[:nq]) and torch.equal(fd, d[:nq]), (c, nq)
             staged, sd, _ = pqt.pqt_query_batch_debug(ix, Y[:40].contiguous(), k, w, taps=("n_cand",))
             assert torch.equal(staged, ids[:40]) and torch.equal(sd, d[:40])
+            if P == 2 and H == bins:                                         # the fixed order
+                pqt.pqt_set_bin_order(ix, pqt.PQT_ORDER_STATIC_SLOPES)
+                ids, d = pqt.pqt_query_batch(ix, Y, k, w)
+                for nq in (1, 256):
+                    few, fd = pqt.pqt_query_batch(ix, Y[:nq].contiguous(), k, w)
+                    assert torch.equal(few, ids[:nq]) and torch.equal(fd, d[:nq]), (c, nq)
+                pqt.pqt_set_bin_order(ix, pqt.PQT_ORDER_SUMMED_DISTANCE)
     finally:
         pqt.pqt_index_free(ix)
 
