@@ -109,8 +109,8 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
 static bool small_query_layout(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, RankOffsets& RL, RerankLds& L, SmallQuery& sm) {
     if (!traverse_one_possible(tr)) return false;
     RL = rank_offsets(rk.P, rk.R, rk.T, rk.hashed, true, rk.t_mid);
-    if (RL.Tcap > 4 * 1024 || a.C > kKeysPerThread * 1024) return false;
-    L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, 1024, 0, a.code_format, a.runs_in_lds);
+    if (RL.Tcap > 4 * a.threads || a.C > kKeysPerThread * a.threads) return false;
+    L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, a.threads, 0, a.code_format, a.runs_in_lds);
     size_t o = L.total;
     sm.off_ranking = (uint32_t)o;   o += (RL.total + 15) & ~size_t(15);
     sm.off_traverse = (uint32_t)o;  o += traverse_one_layout(tr.D, tr.P, tr.k1, tr.k2, tr.M, tr.w).total;
@@ -132,7 +132,6 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
     if (a_in.nq <= 0) return hipSuccess;
     RerankArgs a = a_in;
     a.pair_shift = pair_table_shift(a.k1);
-    a.threads = 1024;
     a.early = 0;
     RankOffsets RL;
     RerankLds L;

@@ -404,9 +404,10 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
 // ranks as well).
 // Query q, whose run list of meta.x runs and meta.y candidates is in g.runs.  MARKS: runs of medium length are marked (the kernel
 // that ranks the head pass's left-over queries has no registers to spare for that).  READY: the level-1 distances, the table of Eq. 9
-// and the first runs are in LDS, the histogram is zero.
+// and the first runs are in LDS, the histogram is zero.  (Arguments by value: by reference the kernels for pair codes of two and four
+// words spilled, 5 to 8 % slower.)
 template <int MW, bool TAPS, bool MARKS, bool LONG, bool READY>
-__device__ __forceinline__ void rerank_query(const RerankArgs& g, const RerankLds& L, int64_t q, uint2 meta, unsigned char* smem) {
+__device__ __forceinline__ void rerank_query(const RerankArgs g, const RerankLds L, int64_t q, uint2 meta, unsigned char* smem) {
     unsigned long long* surv = reinterpret_cast<unsigned long long*>(smem + L.surv);
     float* lut = reinterpret_cast<float*>(smem);                 // L.lut == 0
     float* sa = reinterpret_cast<float*>(smem + L.a);
@@ -979,7 +980,7 @@ __device__ __forceinline__ void rank_static_query(const RankArgs& g, const Stati
     __syncthreads();
 }
 
-// A whole query of a small batch by one workgroup of 1,024 threads, in one launch: traversal, ranking, re-ranking.  Every query has
+// A whole query of a small batch by one workgroup (1,024 threads, fewer where several share a compute unit), in one launch: traversal, ranking, re-ranking.  Every query has
 // a compute unit of its own, so what it costs is the chain of its steps, and of a launch that starts when the one before
 // has drained (4 us each) there is one instead of three; lists, level-1 distances and runs stay in LDS, and the table of Eq. 9 is
 // built while a wavefront per part sorts its list (the ranking's LDS lies behind everything else).
@@ -993,10 +994,11 @@ __global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds 
     float* sLd = reinterpret_cast<float*>(ranking + RL.Ld);
     uint32_t* sLid = reinterpret_cast<uint32_t*>(ranking + RL.Lid);
     uint8_t* tab = smem + sm.off_tables;
-    if (sm.levels.T1[0] > 0 && tid < 2 * kHeadPairs / 4)
-        reinterpret_cast<uint32_t*>(tab)[tid] = tid < kHeadPairs / 4 ? reinterpret_cast<const uint32_t*>(kHeadPairTable.a)[tid]
-                                                                     : reinterpret_cast<const uint32_t*>(kHeadPairTable.b)[tid - kHeadPairs / 4];
-    for (int e = tid; e < kPlaceBins; e += 1024) reinterpret_cast<uint32_t*>(ranking + RL.hist)[e] = 0u;
+    if (sm.levels.T1[0] > 0)
+        for (int e = tid; e < 2 * kHeadPairs / 4; e += (int)blockDim.x)
+            reinterpret_cast<uint32_t*>(tab)[e] = e < kHeadPairs / 4 ? reinterpret_cast<const uint32_t*>(kHeadPairTable.a)[e]
+                                                                     : reinterpret_cast<const uint32_t*>(kHeadPairTable.b)[e - kHeadPairs / 4];
+    for (int e = tid; e < kPlaceBins; e += (int)blockDim.x) reinterpret_cast<uint32_t*>(ranking + RL.hist)[e] = 0u;
     traverse_one(tr, q, smem + sm.off_traverse, reinterpret_cast<float*>(smem + L.a), sLd, sLid,
                  [&](int first) { prepare_table<MW>(g, L, smem, first); });
     RunSink sink;
@@ -1058,7 +1060,7 @@ inline hipError_t launch_rerank_variant(const RerankArgs& a, const RerankLds& L,
 template <int MW>
 inline hipError_t launch_query_variant(const RerankArgs& a, const RerankLds& L, const RankArgs& rk, const RankOffsets& RL, const TraverseArgs& tr,
                                        const SmallQuery& sm, hipStream_t s) {
-    hipLaunchKernelGGL((query_kernel<MW>), dim3((unsigned)a.nq), dim3(1024), sm.lds, s, a, L, rk, RL, tr, sm);
+    hipLaunchKernelGGL((query_kernel<MW>), dim3((unsigned)a.nq), dim3(a.threads), sm.lds, s, a, L, rk, RL, tr, sm);
     return hipGetLastError();
 }
 

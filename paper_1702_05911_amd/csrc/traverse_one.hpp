@@ -157,6 +157,7 @@ __device__ __forceinline__ void traverse_one(const TraverseArgs& g, int64_t q, u
     } else {
         meanwhile(P * kWave);
     }
+    if (P * kWave >= nt) meanwhile(0);                       // (four parts, 256 threads: nobody was left)
     __syncthreads();
 }
 

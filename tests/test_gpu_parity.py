@@ -1404,7 +1404,7 @@ def test_brute_force_in_rounds(pqt, stored, D):
     (36, 2, 9, 4, 2, 4, 0, 64, 500, 9, "table"),             # part dimensions of 18: three launches
 ])
 def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
-    """Batches that are answered in one launch (up to 256 queries) against the launches with intermediate results and a larger
+    """Batches that are answered in one launch (up to 1,024 queries, by workgroups of three sizes) against the launches with intermediate results and a larger
     batch: the same ids and distance bits, with budgets that 32 tuples fill, that 64 do, and that take the full ranking."""
     import torch
     rng = np.random.default_rng(23)
@@ -1425,11 +1425,11 @@ def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
         tbl_j=rng.integers(0, k1, (M, 256)), tbl_lam=rng.normal(0.5, 0.5, (M, 256)), cc=cc, offsets=offsets, ids=rng.permutation(N),
         codes=code if codes == "pair" else code[:, :, 1], code_format=int(codes == "pair")))
     try:
-        Y = torch.from_numpy(X[:300] + rng.normal(0, 2, (300, D)).astype(np.float32)).cuda()
+        Y = torch.from_numpy(X[:1100] + rng.normal(0, 2, (1100, D)).astype(np.float32)).cuda()
         for c in sorted({k, C, max(k, C // 20)}):
             pqt.pqt_set_budget(ix, T, c)
             ids, d = pqt.pqt_query_batch(ix, Y, k, w)                        # three launches
-            for nq in (1, 3, 40, 256):
+            for nq in (1, 3, 40, 256, 257, 512, 513, 1024):
                 few, fd = pqt.pqt_query_batch(ix, Y[:nq].contiguous(), k, w)
                 assert torch.equal(few, ids[:nq]) and torch.equal(fd, d[:nq]), (c, nq)
             staged, sd, _ = pqt.pqt_query_batch_debug(ix, Y[:40].contiguous(), k, w, taps=("n_cand",))
@@ -1437,7 +1437,7 @@ def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
             if P == 2 and H == bins:                                         # the fixed order
                 pqt.pqt_set_bin_order(ix, pqt.PQT_ORDER_STATIC_SLOPES)
                 ids, d = pqt.pqt_query_batch(ix, Y, k, w)
-                for nq in (1, 256):
+                for nq in (1, 256, 257, 513):
                     few, fd = pqt.pqt_query_batch(ix, Y[:nq].contiguous(), k, w)
                     assert torch.equal(few, ids[:nq]) and torch.equal(fd, d[:nq]), (c, nq)
                 pqt.pqt_set_bin_order(ix, pqt.PQT_ORDER_SUMMED_DISTANCE)
