@@ -669,9 +669,9 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
     if (!taps && !ev && nq <= kSmallBatch) {
         pqt::RerankArgs qa = ca;
         qa.threads = nq <= 256 ? 1024 : (nq <= 512 ? 512 : 256);
-        const size_t lds = pqt::small_query_lds(qa, ra, ta), room = pqt::kMaxLds * (size_t)qa.threads / 1024;
-        if (lds != 0 && lds <= std::min(room, ix->lds_limit)) {
-            HIP_TRY(pqt::launch_small_query(qa, ra, ta, mean_need < small_head_below(nq), fixed_order ? &so : nullptr, stream));
+        const size_t room = std::min(pqt::kMaxLds * (size_t)qa.threads / 1024, ix->lds_limit);
+        if (pqt::small_query_fits(qa, ra, ta, room)) {
+            HIP_TRY(pqt::launch_small_query(qa, ra, ta, mean_need < small_head_below(nq), fixed_order ? &so : nullptr, room, stream));
             return PQT_OK;
         }
     }

@@ -179,11 +179,12 @@ int rerank_fused_tuples_per_thread();
 // workgroup size and candidates per thread of the re-rank kernel for a candidate budget C
 // (C <= threads * keys_per_thread; the fewest threads that hold the budget)
 void rerank_shape(int C, int M, int code_format, int* threads, int* keys_per_thread);
-// A small batch in one launch, a workgroup of 1,024 threads per query (no taps; `fixed`: in the fixed bin order, else by summed
-// distance).  LDS of a workgroup, 0: these
-// arguments are not taken.  head: the first wavefront tries 32 and 64 tuples by itself (two parts).
-size_t small_query_lds(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr);
-hipError_t launch_small_query(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, bool head, const StaticOrder* fixed, hipStream_t s);
+// A small batch in one launch, a workgroup of a.threads per query with up to `room` bytes of LDS, if it takes these arguments (no
+// taps; `fixed`: in the fixed bin order, else by summed distance).  head: the first wavefront tries 32 and 64 tuples by itself
+// (two parts).
+bool small_query_fits(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, size_t room);
+hipError_t launch_small_query(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, bool head, const StaticOrder* fixed,
+                              size_t room, hipStream_t s);
 // fused: the full ranking pass of the queries whose meta.x is kMetaTodo runs inside the kernel
 hipError_t launch_rerank(const RerankArgs& a, const RankArgs* fused, hipStream_t s);
 

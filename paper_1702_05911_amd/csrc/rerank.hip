@@ -105,30 +105,36 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
     }
 }
 
-// Layout of the kernel for small batches; false: it does not take these arguments.
-static bool small_query_layout(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, RankOffsets& RL, RerankLds& L, SmallQuery& sm) {
+// Layout of the kernel for small batches within `room` bytes of LDS: the ranking behind the table, or in its place.  False: it does not
+// take these arguments.
+static bool small_query_layout(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, size_t room, RankOffsets& RL, RerankLds& L,
+                               SmallQuery& sm) {
     if (!traverse_one_possible(tr)) return false;
     RL = rank_offsets(rk.P, rk.R, rk.T, rk.hashed, true, rk.t_mid);
     if (RL.Tcap > 4 * a.threads || a.C > kKeysPerThread * a.threads) return false;
-    L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, a.threads, 0, a.code_format, a.runs_in_lds);
-    size_t o = L.total;
-    sm.off_ranking = (uint32_t)o;   o += (RL.total + 15) & ~size_t(15);
-    sm.off_traverse = (uint32_t)o;  o += traverse_one_layout(tr.D, tr.P, tr.k1, tr.k2, tr.M, tr.w).total;
-    sm.off_head = (uint32_t)o;      o += (sizeof(HeadLds) + 15) & ~size_t(15);
-    sm.off_tables = (uint32_t)o;    o += 2 * kHeadPairs;
-    sm.lds = (uint32_t)o;
-    return o <= kMaxLds;
+    const size_t ranking = (RL.total + 15) & ~size_t(15);
+    for (sm.late_table = 0; sm.late_table < 2; ++sm.late_table) {
+        L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, a.threads, sm.late_table ? ranking : 0, a.code_format, a.runs_in_lds);
+        size_t o = L.total;
+        sm.off_ranking = sm.late_table ? 0u : (uint32_t)o;   o += sm.late_table ? 0 : ranking;
+        sm.off_traverse = (uint32_t)o;                       o += traverse_one_layout(tr.D, tr.P, tr.k1, tr.k2, tr.M, tr.w).total;
+        sm.off_head = (uint32_t)o;                           o += (sizeof(HeadLds) + 15) & ~size_t(15);
+        sm.off_tables = (uint32_t)o;                         o += 2 * kHeadPairs;
+        sm.lds = (uint32_t)o;
+        if (o <= room) return true;
+    }
+    return false;
 }
 
-size_t small_query_lds(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr) {
+bool small_query_fits(const RerankArgs& a, const RankArgs& rk, const TraverseArgs& tr, size_t room) {
     RankOffsets RL;
     RerankLds L;
     SmallQuery sm;
-    return small_query_layout(a, rk, tr, RL, L, sm) ? sm.lds : 0;
+    return small_query_layout(a, rk, tr, room, RL, L, sm);
 }
 
 hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const TraverseArgs& tr, bool head, const StaticOrder* fixed,
-                              hipStream_t s) {
+                              size_t room, hipStream_t s) {
     if (a_in.nq <= 0) return hipSuccess;
     RerankArgs a = a_in;
     a.pair_shift = pair_table_shift(a.k1);
@@ -136,7 +142,7 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
     RankOffsets RL;
     RerankLds L;
     SmallQuery sm;
-    if (a.keys_per_thread != kKeysPerThread || a.n_cand || a.cand_ids || a.scores || a.lut || !small_query_layout(a, rk, tr, RL, L, sm))
+    if (a.keys_per_thread != kKeysPerThread || a.n_cand || a.cand_ids || a.scores || a.lut || !small_query_layout(a, rk, tr, room, RL, L, sm))
         return hipErrorInvalidValue;
     sm.levels = HeadLevels{};
     sm.fixed = fixed ? *fixed : StaticOrder{};

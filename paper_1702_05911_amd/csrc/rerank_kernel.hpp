@@ -983,7 +983,7 @@ __device__ __forceinline__ void rank_static_query(const RankArgs& g, const Stati
 // A whole query of a small batch by one workgroup (1,024 threads, fewer where several share a compute unit), in one launch: traversal, ranking, re-ranking.  Every query has
 // a compute unit of its own, so what it costs is the chain of its steps, and of a launch that starts when the one before
 // has drained (4 us each) there is one instead of three; lists, level-1 distances and runs stay in LDS, and the table of Eq. 9 is
-// built while a wavefront per part sorts its list (the ranking's LDS lies behind everything else).
+// built while a wavefront per part sorts its list, if there is LDS for that and the ranking side by side.
 template <int MW>
 __global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds L, RankArgs rk, RankOffsets RL, TraverseArgs tr, SmallQuery sm) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1000,7 +1000,9 @@ __global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds 
                                                                      : reinterpret_cast<const uint32_t*>(kHeadPairTable.b)[e - kHeadPairs / 4];
     for (int e = tid; e < kPlaceBins; e += (int)blockDim.x) reinterpret_cast<uint32_t*>(ranking + RL.hist)[e] = 0u;
     traverse_one(tr, q, smem + sm.off_traverse, reinterpret_cast<float*>(smem + L.a), sLd, sLid,
-                 [&](int first) { prepare_table<MW>(g, L, smem, first); });
+                 [&](int first) {
+                     if (!sm.late_table) prepare_table<MW>(g, L, smem, first);
+                 });
     RunSink sink;
     sink.src = reinterpret_cast<uint32_t*>(smem + L.run_src);
     sink.start = reinterpret_cast<uint32_t*>(smem + L.run_start);
@@ -1033,6 +1035,7 @@ __global__ __launch_bounds__(1024, 4) void query_kernel(RerankArgs g, RerankLds 
         __syncthreads();
     }
     if (!ranked) rank_query<0, true, 4, kRankPlace, true>(rk, RL, q, ranking, misc + kRanked, sink);
+    if (sm.late_table) prepare_table<MW>(g, L, smem, 0);
     rerank_query<MW, false, true, true, true>(g, L, q, make_uint2(misc[kRanked], misc[kRanked + 1]), smem);
 }
 

@@ -20,6 +20,7 @@ struct SmallQuery {
     HeadLevels levels;
     StaticOrder fixed;               // the fixed bin order (table null: by summed distance)
     uint32_t off_traverse, off_tables, off_ranking, off_head, lds;
+    int late_table;                  // the ranking has the table's place: it is built afterwards
 };
 
 #define PQT_RERANK_VARIANT_DECLARE(NAME)                                                                               \
