@@ -9,8 +9,9 @@
 // the wavefront and come through the scalar cache, and nothing is compared across lanes.  Sub-part distances are added to
 // the part's in ascending order; level 2 spreads (vector, child) pairs over the lanes, children of a cluster interleaved.
 //
-// Bound by vector instructions (half of its cycles; six per vector, sub-part and code point) and LDS reads (two of them).
-// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 2.1 ms; the traversal kernel with w = 1 (one wavefront
+// Bound by vector instructions (six per vector, sub-part and code point) and, above 32 centroids, LDS reads (two of them): up to
+// 32 the code search has a lane's distances in registers (2,000,003 vectors, below: the whole call 2.73 -> 2.29 ms).
+// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 1.76 ms; the traversal kernel with w = 1 (one wavefront
 // per list, 8 of 64 lanes at work), its distances written and read back, and one wavefront per vector for the codes took
 // 7.0.  With staged values and distances side by side in LDS three workgroups instead of five fit a compute unit: 2.9.
 #include <type_traits>
@@ -164,13 +165,29 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
 }
 
 // The nearest of the 256 code points of a sub-part: the smallest (Eq. 9 value, number).  Eight values at a time only
-// their minimum is compared; the eight that hold the smallest are looked at again.
-__device__ __forceinline__ uint32_t nearest_code(const CodeEntry* table, const float* at) {
+// their minimum is compared; the eight that hold the smallest are looked at again.  Up to K > 0 centroids the distances stay in
+// registers, which the code points' centroid numbers, the same for the wavefront, index; 0: they are read from LDS.
+template <int K>
+__device__ __forceinline__ uint32_t nearest_code(const CodeEntry* table, const float* at, int k1) {
+    typedef float Distances __attribute__((ext_vector_type(K > 0 ? K : 1)));
     const int lane = threadIdx.x & (kWave - 1);
     scalar_words w = (scalar_words)(uintptr_t)table;
     auto value = [&](uint32_t ij, float lam, float kc) {
         const float b2 = at[(ij & 0xffu) * kRowStride + lane], a2 = at[((ij >> 8) & 0xffu) * kRowStride + lane];
         return fmaf(lam, a2 - b2, b2) + kc;
+    };
+    Distances d;
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) d[i] = at[min(i, k1 - 1) * kRowStride + lane];
+    }
+    auto scalar_value = [&](uint32_t ij, float lam, float kc) {
+        if constexpr (K > 0) {
+            const float b2 = d[ij & (K - 1)], a2 = d[(ij >> 8) & (K - 1)];
+            return fmaf(lam, a2 - b2, b2) + kc;
+        } else {
+            return value(ij, lam, kc);
+        }
     };
     float best = __builtin_inff();
     int block = 0;
@@ -178,7 +195,7 @@ __device__ __forceinline__ uint32_t nearest_code(const CodeEntry* table, const f
         float v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            v[u] = value(w[3 * (c + u)], __uint_as_float(w[3 * (c + u) + 1]), __uint_as_float(w[3 * (c + u) + 2]));
+            v[u] = scalar_value(w[3 * (c + u)], __uint_as_float(w[3 * (c + u) + 1]), __uint_as_float(w[3 * (c + u) + 2]));
         const float low = fminf(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])), fminf(fminf(v[4], v[5]), fminf(v[6], v[7])));
         if (low < best) {
             best = low;
@@ -373,7 +390,10 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
                 const unsigned long long vote = vote_of(pairs, nearest_line(pairs, 0, g.npairs, at), m, at);
                 if (lane < nv) g.keys[(size_t)m * g.n + v0 + lane] = vote;
             } else if (MODE == kTableCodes) {
-                code[lane * M + m] = (uint8_t)nearest_code(g.table + (size_t)m * 256, at);
+                const CodeEntry* table = g.table + (size_t)m * 256;
+                const uint32_t c = k1 <= 16 ? nearest_code<16>(table, at, k1)
+                                   : k1 <= 32 ? nearest_code<32>(table, at, k1) : nearest_code<0>(table, at, k1);
+                code[lane * M + m] = (uint8_t)c;
             } else {
                 const uint32_t c = nearest_pair(g.table + (size_t)m * 256, g.npairs, at);
                 code[(lane * M + m) * 2] = (uint8_t)c;

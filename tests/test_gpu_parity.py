@@ -761,6 +761,7 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
 @pytest.mark.parametrize("N, D, P, k1, k2, M, fmt, offset", [
     (63, 16, 2, 16, 8, 4, 0, 0),           # one vector short of a workgroup; one tile of centroids
     (65, 24, 2, 17, 3, 4, 0, 0),           # one vector in the second workgroup; a second, nearly empty tile of centroids
+    (66, 24, 2, 32, 3, 6, 0, 0),           # as many centroids as a lane keeps distances of in registers (33: not)
     (200, 48, 1, 33, 2, 1, 0, 0),          # one sub-part of two slabs, centroids in two passes over them
     (130, 40, 4, 5, 7, 8, 0, 0),           # four tree parts, pieces of one sub-part each
     (129, 30, 2, 6, 4, 6, 0, 0),           # sub-parts of five dimensions: no 16-byte rows
