@@ -209,6 +209,9 @@ BruteError brute_error_half(int D) {
     e.dot = (float)(1.03 * (1.0 / 1024.0 + adding + centre));
     e.norm = (float)(1.03 * 0.5 * (adding + (D / 64 + 28) / 16777216.0 + centre));
     e.flush = (float)(1.03 * 2.0 * std::sqrt((double)D) / 268435456.0);
+    const BruteError pieces = brute_error(4, D);
+    const double whole = (double)pieces.dot + 2.0 * ((double)pieces.norm - (double)e.norm);
+    if (whole > (double)e.dot) e.dot = std::nextafter((float)whole, 1.0f);
     return e;
 }
 

@@ -69,6 +69,9 @@ int make_static_order(int R, int T, std::vector<uint32_t>& table, float thr[kSlo
 //     product instead of three is added up.  Both are scaled so that the query's norm and the largest vector's lie in 2^14 ..
 //     2^15, and what then lies below 2^-14, the smallest normal half, may be taken for zero: sqrt(D) 2^-14 of such numbers against the
 //     other's norm, 2^-28 sqrt(D) ||q|| X for either, X the largest norm of all (flush ||q|| X).
+//     The first chunk's values are those of pieces, and what the list may hold is bounded for both kinds at once: dot and dot + 2 norm,
+//     the parts of the window (keep_up_to), are no smaller than the pieces', whose three products weigh more than
+//     the shorter numbers from about 2,000 dimensions on.
 struct BruteError {
     float dot, norm, flush;
 };

@@ -1330,6 +1330,9 @@ def test_brute_force_misleading_order(pqt, stored, N, D, early, k):
     (70_001, 336, 300, "an offset"),         # vectors relative to their centre
     (70_001, 336, 300, "small and large"),   # numbers that are zero as scaled halves; a query and vectors far longer than others
     (70_001, 336, 300, "out of range"),      # norms that are not scaled to halves
+    (70_001, 336, 300, "half an offset"),    # norms and queries relative to the centre, vectors as they are
+    (40_000, 3072, 140, "even"),             # so long that three products of pieces may be off by more than one of halves
+    (33_000, 8192, 140, "half an offset"),   # the longest
 ])
 def test_brute_force_halves(pqt, N, D, nq, kind):
     """Float collections large enough to be filtered by products of halves, against distances in float64: a distance is a sum of D
@@ -1343,6 +1346,8 @@ def test_brute_force_halves(pqt, N, D, nq, kind):
         X[::7] = Y[5] * (1 + 1e-4 * torch.rand((len(X[::7]), 1), generator=gen, device="cuda")) + 1e-4 * X[::7]
     elif kind == "an offset":
         X, Y = X + 20, Y + 20
+    elif kind == "half an offset":
+        X, Y = X + 0.5, Y + 0.5
     elif kind == "small and large":
         X[::3] *= 1e-7
         X[::1000] *= 1e4

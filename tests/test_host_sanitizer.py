@@ -242,3 +242,15 @@ def test_brute_force_halves_error_bound(driver, D, small):
         qn, xn = np.sqrt(D) * q.astype(np.float64), np.sqrt(D) * np.abs(x.astype(np.float64))
         bound = dot * qn * xn + norm * xn ** 2 + flush * qn * X
         assert (np.abs(s / (sq * sx) - true) <= bound).all(), (np.abs(s / (sq * sx) - true) / bound).max()
+
+
+@pytest.mark.parametrize("D", [4, 128, 960, 1980, 2048, 3072, 4096, 8192])
+def test_brute_force_halves_bound_covers_the_pieces(driver, D):
+    """The first chunk's values come from bf16 pieces and stay in the list with those of halves, under one window: that of the halves
+    (for a vector of norm r, vectors' offset mu and a query of norm q: dot (r + mu)^2 + 2 norm r^2 and dot q (r + mu)) must be
+    no narrower than that of the pieces, whatever r and mu."""
+    dot, norm, flush = (float.fromhex(v) for v in driver("halves", D).split())
+    piece_dot, piece_norm = (float.fromhex(v) for v in driver("bound", 4, D).split())
+    assert dot >= piece_dot and flush >= 0
+    for mu in (0.0, 0.1, 1.0, 10.0):
+        assert dot * (1 + mu) ** 2 + 2 * norm >= piece_dot * (1 + mu) ** 2 + 2 * piece_norm, mu
