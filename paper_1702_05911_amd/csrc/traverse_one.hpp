@@ -7,20 +7,23 @@
 
 namespace pqt {
 
+// The query comes first: it is read in 16-byte pieces.
 struct TraverseOneLds {
-    size_t off_q, off_qn, off_d1, off_sel, off_key, total;
+    size_t off_q, off_key, off_qn, off_d1, off_sel, total;
 };
-__host__ __device__ inline TraverseOneLds traverse_one_layout(int D, int P, int k1, int k2, int M, int w) {
-    TraverseOneLds L;
+__host__ __device__ constexpr TraverseOneLds traverse_one_layout(int D, int P, int k1, int k2, int M, int w) {
+    TraverseOneLds L = {};
     size_t o = 0;
-    L.off_key = o; o += sizeof(unsigned long long) * P * w * k2;
     L.off_q = o;   o += sizeof(float) * ((D + 3) & ~3);
+    L.off_key = o; o += sizeof(unsigned long long) * P * w * k2;
     L.off_qn = o;  o += sizeof(float) * M;
     L.off_d1 = o;  o += sizeof(float) * P * k1;
     L.off_sel = o; o += sizeof(int) * P * w;
     L.total = (o + 15) & ~size_t(15);
     return L;
 }
+static_assert(traverse_one_layout(96, 1, 16, 7, 8, 5).off_q % 16 == 0 && traverse_one_layout(96, 1, 16, 7, 8, 5).off_key % 8 == 0,
+              "a list of odd length");
 // lists of up to 256 entries from the interleaved codebook
 inline bool traverse_one_possible(const TraverseArgs& a) { return a.C2t != nullptr && a.w * a.k2 <= 4 * kWave; }
 

@@ -1401,6 +1401,7 @@ def test_brute_force_in_rounds(pqt, stored, D):
     (32, 2, 16, 8, 8, 8, 0, 1024, 4096, 100, "table"),       # lists of 64, M = 8
     (64, 2, 17, 13, 4, 5, 0, 300, 700, 10, "table"),         # a second tile of one centroid; lists of 65
     (64, 1, 48, 8, 32, 32, 0, 256, 3000, 50, "table"),       # one part, lists of 256 (four a lane), more jobs than wavefronts
+    (96, 1, 16, 7, 12, 5, 0, 35, 3000, 50, "table"),         # one part, a list of odd length
     (96, 4, 16, 7, 12, 4, 5003, 1024, 2000, 37, "table"),    # four parts, hashed
     (64, 4, 8, 8, 16, 8, 0, 4096, 16384, 1024, "table"),     # most tuples a workgroup holds, the largest budget and list
     (48, 2, 20, 7, 12, 5, 999, 500, 3001, 37, "pair"),       # pair codes of six words, hashed
