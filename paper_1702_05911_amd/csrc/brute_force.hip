@@ -68,9 +68,9 @@ constexpr int kFrag = 512;             // bf16 values of one fragment: 32 rows x
 constexpr int kStatRows = 64;          // database vectors per LDS tile of the stationary kernel, as bf16 ...
 constexpr int kByteRows = 128;         // ... and as bytes
 constexpr int kStatQueries = 512;      // queries of one of its workgroups
-// a query tile's state: second bf16 pieces; values that are not 0 .. 255; a norm out of the halves' range; more in the halves' window
-// than the kept lists have room for
-constexpr uint32_t kSecondPiece = 1u, kNotBytes = 2u, kNoHalves = 4u, kCrowded = 8u;
+// a query tile's state: second bf16 pieces; values that are not 0 .. 255; a norm out of the halves' range
+constexpr uint32_t kSecondPiece = 1u, kNotBytes = 2u, kNoHalves = 4u;
+constexpr uint32_t kHalvesOff = 1u << 31;        // control[kBfCrowded]: no halves for this call, however many queries are crowded
 constexpr float kHalfNorms = 0x1p40f;  // norms within this and its reciprocal are scaled to 2^14 .. 2^15 for the halves
 constexpr int kGenRows = 256, kGenQueries = 128;   // workgroup tile of the general kernel ...
 constexpr int kHalfQueries = 256;      // ... and the queries of one of the kernel for halves
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(1024) void pack_queries_kernel(BruteArgs g) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, nwaves = (int)blockDim.x / kWave, D = g.D, KS = g.KS;
     if (tid == 0) {
         state = 0u;
-        if (blockIdx.x == 0) g.control[kBfTodo] = 0u;
+        if (blockIdx.x == 0) g.control[kBfTodo] = g.control[kBfCrowded] = 0u;
     }
     __syncthreads();
     const int64_t tile = blockIdx.x, q = tile * 32 + (lane & 31);
@@ -377,16 +377,8 @@ __device__ __forceinline__ float keep_from(const BruteArgs& g, const float* keep
     return q >= g.nq || g.flagged[q] ? __builtin_inff() : -keep[q];
 }
 
-// Floats: are the values of this query's group those of products of halves (after the first chunk)?  A group is what a workgroup of
-// bf_halves_kernel has.
-__device__ __forceinline__ bool group_is_halves(const BruteArgs& g, int64_t q) {
-    if (!g.qhalf) return false;
-    const int64_t tile = q / kHalfQueries * (kHalfQueries / 32), last = (g.nq - 1) / 32;
-    uint32_t state = 0;
-#pragma unroll
-    for (int u = 0; u < kHalfQueries / 32; ++u) state |= g.second[tile + u < last ? tile + u : last];
-    return !(state & (kNoHalves | kCrowded));
-}
+// Floats, after the first chunk: are the values of these queries those of products of halves?
+__device__ __forceinline__ bool call_is_halves(const BruteArgs& g) { return g.qhalf && g.control[kBfCrowded] <= g.crowded_most; }
 
 // What the queries of this group of the stationary kernel are, and whether they are all whole numbers 0 .. 255.
 __device__ __forceinline__ uint32_t query_state(const BruteArgs& g, int group) {
@@ -907,8 +899,10 @@ __device__ __forceinline__ void filter_general(const BruteArgs& g, unsigned char
 // Floats of a collection of up to kHalvesUpTo vectors: after the first chunk the products are of one piece of half precision on both
 // sides, a third of the matrix work.  Eleven significant bits leave 2^-10 of a product, so more pairs pass: a window two to three times as
 // wide where there are many dimensions (the additions of three products are allowed as much there), twelve times at 128.  A
-// group of queries of which one has more vectors of the first chunk in that window than it may (bf_select_kernel), or with norms out
-// of the range that is scaled to halves, keeps to bf16.
+// call keeps to bf16 if a norm is out of the range that is scaled to halves, or too many queries are crowded: they have more vectors
+// of the first chunk in that window than they may (bf_select_kernel).  (The call as a whole: a group of 128 queries by itself takes the
+// bf16 kernel as long as all of them, since its workgroups are the same few.  5,000 queries x 1M x 128 of which one in 20 groups of
+// 256 kept to bf16 7.6 ms, all of them 5.6, by halves 3.5.)
 // The workgroup's tile is 256 vectors x 256 queries, two times four wavefronts of 64 x 128; 32 dimensions a step, 16 matrix
 // instructions a wavefront, so that a row is read by whole 128-byte lines.  Bound by LDS reads (half its cycles) and the barrier of a
 // workgroup that has a compute unit to itself; workgroups of 128 queries, two per compute unit, read the vectors twice as often: 446 us
@@ -930,11 +924,11 @@ __global__ __launch_bounds__(2 * kBfThreads, 2) void bf_halves_kernel(BruteArgs 
     float* from = reinterpret_cast<float*>(smem + Lds::kFrom);
     float* scale = reinterpret_cast<float*>(smem + Lds::kScale);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, rw = wave & 3, qw = wave >> 2;
-    const int KS = g.KS, steps = (KS + 1) / 2, splits = g.splits;
+    if (!call_is_halves(g)) return;
+    const int KS = g.KS, steps = (KS + 1) / 2, splits = g.splits_halves;
     int split, group;
     place_of_workgroup(blockIdx.x, splits, (int)gridDim.x / splits, split, group);
     const int64_t first_query = (int64_t)group * (QW * kGenQueries), q0 = first_query + qw * kGenQueries;
-    if (!group_is_halves(g, first_query)) return;
     const float xscale = half_scale(g.xhalf[g.N] + g.xhalf[g.N + 2]);
     if (tid < QW * kGenQueries) {                                              // (read after the first step's barrier)
         const bool have = first_query + tid < g.nq;
@@ -1066,18 +1060,18 @@ __global__ __launch_bounds__(2 * kBfThreads, 2) void bf_halves_kernel(BruteArgs 
     }
 #pragma unroll
     for (int ct = 0; ct < kQ; ++ct)
-        if (q0 + ct * 32 + (lane & 31) < g.nq)
-            g.seg_count[(size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + split * 8 + rw * 2 + (lane >> 5)] = count[ct];
+        if (q0 + ct * 32 + (lane & 31) < g.nq) {
+            uint32_t* counts = g.seg_count + (size_t)(q0 + ct * 32 + (lane & 31)) * g.segs + rw * 2 + (lane >> 5);
+            counts[split * 8] = count[ct];
+            for (int s = split + splits; s < g.splits; s += splits) counts[s * 8] = 0u;    // lists that only the bf16 kernel fills
+        }
 }
 
 template <typename Elem, bool DENSE>
 __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_kernel(BruteArgs g) {
     __shared__ __align__(16) unsigned char smem[GeneralLds<Elem>::kTotal];
-    if constexpr (sizeof(Elem) == 4 && !DENSE) {
-        int split, group;
-        place_of_workgroup(blockIdx.x, g.splits, (int)gridDim.x / g.splits, split, group);
-        if (group_is_halves(g, (int64_t)group * kGenQueries)) return;          // bf_halves_kernel has it
-    }
+    if constexpr (sizeof(Elem) == 4 && !DENSE)
+        if (call_is_halves(g)) return;                                         // bf_halves_kernel has it
     filter_general<Elem, DENSE>(g, smem);
 }
 
@@ -1096,7 +1090,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     __shared__ uint32_t hist[kSelectBins];
     __shared__ uint32_t part[kBfThreads / kWave];
     __shared__ float bounds[2 * kBfThreads / kWave];
-    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow, 5, 6 entries before and up to its end
+    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow, 5, 6 entries before and up to its end; 2, 7 counts
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k;
     const int64_t q = blockIdx.x;
     if (g.flagged[q]) return;
@@ -1168,7 +1162,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     auto value = [&](int e) { return __uint_as_float((uint32_t)(keys[e] >> 32)); };
     static_assert(kDense <= 32 * kBfThreads, "a bit per entry");
     uint32_t members = 0xffffffffu, below = 0u;
-    float edge = before;
+    float edge = before, least = 0.0f;
     auto divide = [&](auto all) {                    // one histogram; false: the bin's entries are to be divided
         constexpr bool ALL = decltype(all)::value;   // every entry is a member
         float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -1192,6 +1186,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
             hi = fmaxf(hi, bounds[2 * w + 1]);
         }
         edge = hi;
+        if (ALL) least = lo;
         if (!(hi - lo > 1e-30f)) return true;        // equal, or next to it
         const float scale = (float)kSelectBins / (hi - lo);
         auto bin_of = [&](float v) { return (int)fminf((v - lo) * scale, (float)(kSelectBins - 1)); };
@@ -1255,17 +1250,31 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
         const float wide = keep_up_to(g, g.err_half, qn, g.qshift[q], edge);
         if (!last && tid == 0) g.keep_halves[q] = wide;
         if (!dense) {
-            if (group_is_halves(g, q)) keep = wide;
+            if (call_is_halves(g)) keep = wide;
+        } else if (g.second[q / 32] & kNoHalves) {
+            if (tid == 0) atomicOr(&g.control[kBfCrowded], kHalvesOff);
         } else {                                     // (this chunk's values are those of bf16 pieces)
+            // Is there room for what the halves' window lets pass?  In the next chunk as much as in this one, in proportion; in the
+            // end what is in the window of the k nearest: as large a share of all vectors as of these, if they are crowded there; where
+            // the values thin out towards the nearest, k times what a window from the nearest of these holds.
+            const float near = keep_up_to(g, g.err_half, qn, g.qshift[q], least);
             __syncthreads();                         // (misc[2] has been read)
-            if (tid == 0) misc[2] = 0u;
+            if (tid == 0) misc[2] = misc[7] = 0u;
             __syncthreads();
-            uint32_t up_to = 0;
-            for (int e = tid; e < n; e += kBfThreads) up_to += value(e) <= wide ? 1u : 0u;
+            uint32_t up_to = 0, up_to_near = 0;
+            for (int e = tid; e < n; e += kBfThreads) {
+                up_to += value(e) <= wide ? 1u : 0u;
+                up_to_near += value(e) <= near ? 1u : 0u;
+            }
             atomicAdd(&misc[2], up_to);
+            atomicAdd(&misc[7], up_to_near);
             __syncthreads();
-            if (misc[2] <= (uint32_t)(rank + rank / 2 + 6)) keep = wide;
-            else if (tid == 0) atomicOr(&g.second[q / 32], kCrowded);
+            const float share = (float)g.N / (float)kDense;
+            const float in_the_end = fminf(share * (float)misc[2], fmaxf(share, (float)k) * (float)misc[7]);
+            const bool full = misc[2] > (uint32_t)kBest;                       // (not even now: this query's list is one for bf16)
+            if (!full) keep = wide;
+            if (tid == 0 && full) atomicOr(&g.control[kBfCrowded], kHalvesOff);
+            else if (tid == 0 && ((int)misc[2] > g.crowded_next || in_the_end > (float)kBest)) atomicAdd(&g.control[kBfCrowded], 1u);
         }
     }
     // ---- keep what can still be among the k nearest ---------------------------------------------------------------
@@ -1536,8 +1545,8 @@ int rank_at(int k, double pos, double N) {
     return most < k ? (int)most : k;
 }
 
-// Floats: the largest collection that is filtered by halves.  More vectors in their window than the kept lists hold (kBest) have to
-// show in the first chunk: eight of them.
+// Floats: the largest collection that is filtered by halves.  Where more vectors than the kept lists hold (kBest) are in their window,
+// some have to show in the first chunk: eight of them in the mean.
 constexpr uint64_t kHalvesUpTo = (uint64_t)kBest * kDense / 8;
 
 // How one call is cut: sizes of the workspace's pieces and the launch shapes.
@@ -1545,7 +1554,7 @@ struct Plan {
     bool stationary, halves;
     int KS;
     int64_t batch, batch_pad;        // queries at a time, padded to whole workgroup tiles
-    int groups, splits, segs, seg_cap;
+    int groups, splits, splits_halves, segs, seg_cap;
     double growth;                   // chunks and what was there before them
     int hits;                        // pairs that pass in a chunk
     int scan_queries, scan_grid;     // of the exact scan: queries and workgroups
@@ -1560,18 +1569,21 @@ Plan make_plan(int64_t nq, uint64_t N, int D, int elem_bytes, int k) {
     p.batch = nq < 16384 ? nq : 16384;
     p.batch_pad = round_up(p.batch, tile);
     // Halves need the queries a second time and a look at the first chunk, about 6 us: not for what takes less than a few
-    // times that.  (Up to 128 queries the workgroup's second half would idle.)
-    p.halves = elem_bytes == 4 && N >= 8 * kDense && N <= kHalvesUpTo && p.batch > kGenQueries && (double)p.batch_pad * (double)N * D > 6e9;
+    // times that.  (Up to 128 queries the workgroup's second half would idle.)  A step is 32 dimensions, one of 16 would be half
+    // padding: 1,000 queries x 1M x 16, k = 100: 262 us by bf16 pieces, 292 by halves; x 64 494 and 373.
+    p.halves = elem_bytes == 4 && D > 32 && N >= 8 * kDense && N <= kHalvesUpTo && p.batch > kGenQueries && (double)p.batch_pad * (double)N * D > 6e9;
     p.groups = (int)(p.batch_pad / tile);
     // as many workgroups as are resident at once (two per compute unit): no second round of a few
     const int slots = 512;
     p.splits = p.groups >= slots ? 1 : slots / p.groups;
-    if (p.halves) p.splits = std::max(1, std::min(p.splits, 256 / ((p.groups + 1) / 2)));      // (one workgroup of bf_halves_kernel per compute unit)
     if (p.splits > 8) p.splits -= p.splits % 8;
+    p.splits_halves = std::max(1, std::min(p.splits, 256 / ((p.groups + 1) / 2)));             // (one workgroup of bf_halves_kernel per compute unit)
+    if (p.splits_halves > 8) p.splits_halves -= p.splits_halves % 8;
     p.segs = p.splits * (p.stationary ? 2 : 8);
     // As many chunks, each larger by the same factor, as take the least time: a chunk costs a launch of either kernel and a
     // look at every query's list, a pair that passes some hundred cycles of its wavefront, which takes 128 queries.  Bounded by
-    // the select workgroup's LDS (the pairs, twice the expected number, and the list kept so far).
+    // the select workgroup's LDS (the pairs, twice the expected number, and the list kept so far; halves let through twice as many).
+    const double room = p.halves ? 800.0 : 1600.0;
     p.growth = 2.0;
     p.hits = k;
     double least = 1e30;
@@ -1584,7 +1596,7 @@ Plan make_plan(int64_t nq, uint64_t N, int D, int elem_bytes, int k) {
             time += 10.0 + 0.005 * (double)p.batch + 0.2 * hits * (double)p.batch / waves;
             most = hits > most ? hits : most;
         }
-        if (time < least && (most <= 1600.0 || growth <= 2.0)) {
+        if (time < least && (most <= room || growth <= 2.0)) {
             least = time;
             p.growth = growth;
             p.hits = (int)most + 1;
@@ -1644,7 +1656,7 @@ void launch_filter(const Plan& p, const BruteArgs& a, hipStream_t s) {
         hipLaunchKernelGGL((bf_filter_stationary_kernel<8, DENSE>), grid, block, 0, s, a);
     } else {
         hipLaunchKernelGGL((bf_filter_kernel<Elem, DENSE>), grid, block, 0, s, a);
-        if (!DENSE && p.halves) hipLaunchKernelGGL(bf_halves_kernel, dim3((unsigned)(p.splits * ((p.groups + 1) / 2))), dim3(2 * kBfThreads), 0, s, a);
+        if (!DENSE && p.halves) hipLaunchKernelGGL(bf_halves_kernel, dim3((unsigned)(p.splits_halves * ((p.groups + 1) / 2))), dim3(2 * kBfThreads), 0, s, a);
     }
 }
 
@@ -1659,6 +1671,9 @@ hipError_t run(const Plan& p, BruteArgs a, const float* queries, int64_t nq, int
         a.queries = queries + (size_t)b0 * a.D;
         a.out_ids = out_ids + (size_t)b0 * a.k;
         a.out_dists = out_dists + (size_t)b0 * a.k;
+        // A crowded query may end in the exact scan, about 30 us in a large batch (1M x 128 floats) and 300 by itself, of which halves
+        // save 0.4 a query: one in 128, none in a small batch, whose few queries are hardly ever taken for crowded by chance.
+        a.crowded_most = a.nq < 1024 ? 0u : (uint32_t)(a.nq / 128);
         hipLaunchKernelGGL(pack_queries_kernel, dim3((unsigned)(p.batch_pad / 32)), dim3(a.KS < 16 ? 256 : 1024), 0, s, a);
         if (p.halves) {
             const int64_t count = p.batch_pad / 32 * p.KS * kWave;
@@ -1733,7 +1748,8 @@ hipError_t launch_brute_force(const void* vectors, const float* half_norms, int 
     a.centre = elem_bytes == 4 ? half_norms + centre_at(N) : nullptr;
     a.ihalf = elem_bytes == 1 ? reinterpret_cast<const int*>(half_norms + centre_at(N)) : nullptr;
     a.use_centre = reinterpret_cast<const uint32_t*>(half_norms) + N + 1;
-    a.splits = p.splits; a.segs = p.segs; a.seg_cap = p.seg_cap;
+    a.splits = p.splits; a.splits_halves = p.splits_halves; a.segs = p.segs; a.seg_cap = p.seg_cap;
+    a.crowded_next = (int)(kBest / p.growth);
     a.step = brute_force_step(N);
     a.err = pqt_host::brute_error(elem_bytes, D);
     a.err_half = pqt_host::brute_error_half(D);

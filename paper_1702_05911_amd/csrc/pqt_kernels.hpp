@@ -203,6 +203,7 @@ hipError_t launch_exact_rerank(const ExactArgs& a, hipStream_t s);
 
 // Brute force: see brute_force.hip.  Words of BruteArgs::control:
 enum { kBfTodo = 0,            // queries in todo[]
+       kBfCrowded = 1,         // queries with too many vectors in the halves' window; its highest bit: no halves
        kBfControl = 64 };
 struct BruteArgs {
     int64_t nq;                   // queries of the batch
@@ -239,7 +240,9 @@ struct BruteArgs {
     uint8_t* qbytes;              // the same less 128 as bytes, operand layout (byte vectors of at most 128 dimensions, else null)
     uint16_t* qhalf;              // floats: queries, one piece of half precision, scaled, operand layout (null: not used)
     float* dense;                 // values of the first chunk, a row per query
-    int splits;                   // workgroups that share a query group's database tiles
+    uint32_t crowded_most;        // floats: as many queries may be crowded before the call keeps to bf16: more vectors of the first chunk
+    int crowded_next;             // in the window than this, or than the kept list will have room for in the end
+    int splits, splits_halves;    // workgroups that share a query group's database tiles
     int segs, seg_cap;            // lists per query and entries per list
     uint32_t* seg_count;          // nq x segs: pairs that passed (may exceed seg_cap: overflow)
     uint2* lists;                 // nq x segs x seg_cap: (row of the chunk, value)
