@@ -143,10 +143,11 @@ double headless_from(const pqt_index* ix, int64_t nq) {
     return words ? 96.0 : 84.0;
 }
 // Queries that are answered in one launch, as many as run at once: a workgroup of 1,024 threads has a compute unit, up to 512 queries
-// are two of 512 threads, up to 1,024 four of 256, where the tuples, the candidates and its share of the LDS allow it.  Three
-// launches and one, us: one query 20.4 and 16.9 (1,500 candidates of a dense index), 67 47.5 and 35.3, 256 59.1 and 43.7 (10,000
-// candidates), 300 67.4 and 49.9 (in workgroups of 1,024 threads, two rounds: 73.8), 512 68.2 and 51.2, 700 66.9 and 52.3, 1,024 74.5
-// and 57.5 (4,096 candidates); four parts, T = 4096: 256 83.3 and 68.9.
+// are two of 512 threads, up to 1,024 four of 256, where the tuples, the candidates and its share of the LDS allow it and the
+// codebooks are not too large for one query by itself (pqt_host::one_launch_pays).  Three launches and one, us: one query 20.4
+// and 16.9 (1,500 candidates of a dense index), 67 47.5 and 35.3, 256 59.1 and 43.7 (10,000 candidates), 300 67.4 and 49.9 (in
+// workgroups of 1,024 threads, two rounds: 73.8), 512 68.2 and 51.2, 700 66.9 and 52.3, 1,024 74.5 and 57.5 (4,096 candidates); four
+// parts, T = 4096: 256 83.3 and 68.9.
 constexpr int64_t kSmallBatch = 1024;
 // The same mean, up to which the first wavefront of its workgroup tries 32 and 64 tuples.  With that and without, us: one query at 25: 18.2
 // and 23.1, at 67: 22.0 and 25.9, at 164: 33.2 and 29.1; 7 at 25: 20.0 and 23.8, at 67: 29.5 and 26.2; 67 at 25: 30.6 and 24.9 (one is left
@@ -666,7 +667,7 @@ int run_query(pqt_index* ix, const float* queries, int64_t nq, int k, int w, int
         for (int j = 0; j < pqt::kStaticSlopes - 1; ++j) so.thr[j] = ix->static_thr[j];
     }
     // A small batch in one launch (stage times and intermediate results exist only between launches)
-    if (!taps && !ev && nq <= kSmallBatch) {
+    if (!taps && !ev && nq <= kSmallBatch && pqt_host::one_launch_pays(ix->D, ix->P, ix->k1, R, ix->C, nq)) {
         pqt::RerankArgs qa = ca;
         qa.threads = nq <= 256 ? 1024 : (nq <= 512 ? 512 : 256);
         const size_t room = std::min(pqt::kMaxLds * (size_t)qa.threads / 1024, ix->lds_limit);

@@ -215,6 +215,17 @@ BruteError brute_error_half(int D) {
     return e;
 }
 
+bool one_launch_pays(uint32_t D, uint32_t P, uint32_t k1, int R, uint32_t C, int64_t nq) {
+    const double own = (double)D * ((double)k1 + 16.0);
+    const bool long_ranking = P == 1 || (P == 2 && R > 64);
+    double most = 0.0;
+    if (nq < 16) most = nq < 4 && P == 2 ? 30e3 : 45e3;
+    else if (nq <= 256) most = P <= 2 ? 150e3 : 75e3;
+    else if (nq <= 512) most = 40e3;
+    else most = 12e3 + 4.0 * (double)C;
+    return own <= (long_ranking ? 2.0 * most : most);
+}
+
 long region_size(int nA, int nB, int Tn) {
     long n = 0;
     for (int a = 0; a < nA && a < Tn; ++a) {

@@ -79,6 +79,20 @@ constexpr float kBruteUnderflow = 0x1p-109f;
 BruteError brute_error(int elem_bytes, int D);
 BruteError brute_error_half(int D);
 
+// Is a small batch faster in one launch, a query a workgroup, than in three?  A workgroup of its own does by itself what the traversal
+// kernel's sixteen queries share: the level-1 products with D k1 codebook values, one row of sixteen used; and the values of a child come
+// one after the other, which weighs about as sixteen centroids more.  Up to 16 queries the traversal's tile is as good as empty,
+// above 256 two or four workgroups have a compute unit; many candidates, one part, or lists of more than 64 entries, whose
+// ranking is long, leave more to gain.  Three launches and one, us (lists of up to 64, two parts, 1,000 candidates unless given):
+//   D = 960, k1 = 64       one query 53 and 60, 12 60 and 61, 256 76 and 68, 300 82 and 94, 700 91 and 129, 1,024 100 and 161
+//   D = 960, k1 = 16       one query 35 and 35 (M = 16: 34 and 35), 4 37 and 35, 300 51 and 48, 1,024 64 and 69 (four parts 300 75 and 67; 4,096 candidates 1,024 82 and 75)
+//   D = 512, k1 = 64       one query 44 and 45, 300 65 and 63, 700 78 and 86, 1,024 87 and 101 (four parts 300 77 and 82)
+//   D = 512, k1 = 16       one query 30 and 28, 1,024 55 and 54;   D = 1,536, k1 = 16 one query 41 and 43, 300 63 and 61, 1,024 77 and 91
+//   D = 1,536, k1 = 64     256 96 and 88, four parts 16 78 and 89
+//   D = 192, k1 = 64       one query 56 and 33, 1,024 76 and 64;   D = 320, k1 = 32  1,024 72 and 58
+//   lists of 128: D = 960, k1 = 16 1,024 104 and 81, k1 = 64 300 106 and 97;  one part: D = 960, k1 = 16 1,024 86 and 64, k1 = 64 113 and 146
+bool one_launch_pays(uint32_t D, uint32_t P, uint32_t k1, int R, uint32_t C, int64_t nq);
+
 // number of pairs (a, b), a < nA, b < nB, with (a+1)(b+1) <= Tn
 long region_size(int nA, int nB, int Tn);
 

@@ -5,6 +5,7 @@
 //   static <R> <T>                       make_static_order                       -> "Tn <n>", 9 thresholds (hex floats), 10 table rows
 //   region <nA> <nB> <Tn>                region_size                             -> "n <count>"
 //   bound <elem_bytes> <D>               brute_error                             -> "<dot> <norm>" (hex floats)
+//   small <D> <P> <k1> <R> <C> <nq>      one_launch_pays                         -> "0" or "1"
 //   halves <D>                           brute_error_half                        -> "<dot> <norm> <flush>" (hex floats)
 #include <cstdio>
 #include <cstdlib>
@@ -59,6 +60,11 @@ int main(int argc, char** argv) {
     if (mode == "bound" && argc == 4) {
         const pqt_host::BruteError e = pqt_host::brute_error(atoi(argv[2]), atoi(argv[3]));
         printf("%a %a\n", (double)e.dot, (double)e.norm);
+        return 0;
+    }
+    if (mode == "small" && argc == 8) {
+        printf("%d\n", pqt_host::one_launch_pays((uint32_t)atoi(argv[2]), (uint32_t)atoi(argv[3]), (uint32_t)atoi(argv[4]), atoi(argv[5]),
+                                                 (uint32_t)atoi(argv[6]), atoi(argv[7])) ? 1 : 0);
         return 0;
     }
     if (mode == "halves" && argc == 3) {

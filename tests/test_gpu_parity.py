@@ -1445,6 +1445,7 @@ def test_brute_force_in_rounds(pqt, stored, D):
     (48, 2, 20, 7, 12, 5, 999, 500, 3001, 37, "pair"),       # pair codes of six words, hashed
     (40, 2, 5, 3, 10, 2, 0, 36, 100, 100, "pair"),           # read byte by byte; fewer tuples than 64; fewer candidates than results
     (96, 2, 16, 16, 6, 16, 0, 128, 5000, 9, "table"),        # read byte by byte
+    (512, 2, 64, 4, 8, 4, 0, 256, 1000, 20, "table"),        # large codebooks: one launch up to 256 queries
     (64, 2, 16, 17, 4, 16, 0, 200, 900, 9, "table"),         # lists of 272: three launches
     (36, 2, 9, 4, 2, 4, 0, 64, 500, 9, "table"),             # part dimensions of 18: three launches
 ])

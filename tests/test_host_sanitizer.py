@@ -169,6 +169,28 @@ def test_region_size_counts_the_hyperbolic_region(driver):
         assert int(driver("region", nA, nB, Tn).split()[1]) == want
 
 
+@pytest.mark.parametrize("shape, nq, want", [
+    # (D, P, k1, list length, C): measured both ways
+    ((128, 2, 16, 64, 4096), (1, 67, 300, 1024), 1),
+    ((128, 2, 64, 128, 8192), (1, 256, 512, 1024), 1),
+    ((960, 2, 64, 64, 2000), (67, 256), 1),
+    ((960, 2, 64, 64, 2000), (1, 12, 300, 512, 700, 1024), 0),
+    ((960, 4, 64, 64, 1000), (16, 256, 300), 0),
+    ((960, 2, 16, 64, 1000), (4, 16, 512), 1),
+    ((960, 2, 16, 64, 1000), (1, 700, 1024), 0),
+    ((960, 4, 16, 64, 1000), (1, 256, 300), 1),
+    ((1024, 2, 16, 64, 2000), (1024,), 0),
+    ((512, 2, 64, 64, 1000), (700, 1024), 0),
+    ((1536, 2, 16, 64, 1000), (1, 1024), 0),
+    ((960, 1, 16, 64, 1000), (1, 1024), 1),
+    ((960, 2, 16, 128, 1000), (1, 1024), 1),
+])
+def test_one_launch_where_it_pays(driver, shape, nq, want):
+    """Small batches take one launch where that measured faster than three, and three launches where not."""
+    for n in nq:
+        assert int(driver("small", *shape, n)) == want, n
+
+
 def _bf16(x):
     """float32 -> nearest bf16 (ties to even), as float32."""
     u = np.asarray(x, np.float32).view(np.uint32).astype(np.uint64)
