@@ -165,7 +165,7 @@ __device__ __forceinline__ void subpart_distances(const PlaceArgs& g, int64_t v0
 }
 
 // The nearest of the 256 code points of a sub-part: the smallest (Eq. 9 value, number).  Eight values at a time only
-// their minimum is compared; the eight that hold the smallest are looked at again.  Up to K > 0 centroids the distances stay in
+// their minimum is compared; the eight that hold the smallest are looked at again.  K > 0: the distances of up to K centroids stay in
 // registers, which the code points' centroid numbers, the same for the wavefront, index; 0: they are read from LDS.
 template <int K>
 __device__ __forceinline__ uint32_t nearest_code(const CodeEntry* table, const float* at, int k1) {
@@ -363,7 +363,8 @@ __device__ __forceinline__ void finish_vectors(const PlaceArgs& g, int64_t v0, i
         for (int e = tid; e < bytes; e += nt) out[e] = code[e];
 }
 
-template <int MODE, bool WIDE>
+// K: centroids whose distances the search for table codes has in registers (nearest_code).
+template <int MODE, bool WIDE, int K>
 __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), nt = blockDim.x, waves = nt / kWave;
@@ -390,10 +391,7 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
                 const unsigned long long vote = vote_of(pairs, nearest_line(pairs, 0, g.npairs, at), m, at);
                 if (lane < nv) g.keys[(size_t)m * g.n + v0 + lane] = vote;
             } else if (MODE == kTableCodes) {
-                const CodeEntry* table = g.table + (size_t)m * 256;
-                const uint32_t c = k1 <= 16 ? nearest_code<16>(table, at, k1)
-                                   : k1 <= 32 ? nearest_code<32>(table, at, k1) : nearest_code<0>(table, at, k1);
-                code[lane * M + m] = (uint8_t)c;
+                code[lane * M + m] = (uint8_t)nearest_code<K>(g.table + (size_t)m * 256, at, k1);
             } else {
                 const uint32_t c = nearest_pair(g.table + (size_t)m * 256, g.npairs, at);
                 code[(lane * M + m) * 2] = (uint8_t)c;
@@ -651,15 +649,21 @@ hipError_t launch_mode(const PlaceArgs& a, hipStream_t s) {
         }
     }
     const PlaceLds L = place_layout(ds, a.P, a.k1, cb, waves, MODE == kVotes);
-    const void* fn = wide ? reinterpret_cast<const void*>(place_kernel<MODE, true>) : reinterpret_cast<const void*>(place_kernel<MODE, false>);
-    if (L.total > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.total);
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid((unsigned)((a.n + kPlaceRows - 1) / kPlaceRows)), block((unsigned)waves * kWave);
-    if (wide) hipLaunchKernelGGL((place_kernel<MODE, true>), grid, block, L.total, s, a, L);
-    else hipLaunchKernelGGL((place_kernel<MODE, false>), grid, block, L.total, s, a, L);
-    return hipGetLastError();
+    auto launch = [&](auto kernel) {
+        if (L.total > 64 * 1024) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.total);
+            if (e != hipSuccess) return e;
+        }
+        const dim3 grid((unsigned)((a.n + kPlaceRows - 1) / kPlaceRows)), block((unsigned)waves * kWave);
+        hipLaunchKernelGGL(kernel, grid, block, L.total, s, a, L);
+        return hipGetLastError();
+    };
+    // Distances in registers and in LDS, us, 524,288 vectors x 96: k1 = 16 M = 12 527 and 697, M = 24 932 and 1,229; k1 = 32 M = 24 1,591 and
+    // 1,861.  Where rows are not read in 16-byte pieces: M = 32 2,237 and 1,926, M = 16 1,600 and 1,413.
+    if (!wide) return launch(place_kernel<MODE, false, 0>);
+    if (MODE == kTableCodes && a.k1 <= 16) return launch(place_kernel<MODE, true, MODE == kTableCodes ? 16 : 0>);
+    if (MODE == kTableCodes && a.k1 <= 32) return launch(place_kernel<MODE, true, MODE == kTableCodes ? 32 : 0>);
+    return launch(place_kernel<MODE, true, 0>);
 }
 
 // squared norms of the level-1 centroids' sub-parts, added up in double precision as the host does
