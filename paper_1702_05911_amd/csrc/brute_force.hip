@@ -483,13 +483,14 @@ struct TileRows {
 };
 
 // Byte vectors of at most 128 dimensions, queries that are not all bytes: a wavefront keeps 64 queries (KS steps,
-// two pieces), or 128 of one piece, in registers for the whole launch, and the workgroup's 256 or 512 share the database tiles that
-// stream through LDS, two in turn.
+// two pieces, or one where the group has no more than 256 queries), or 128 of one piece, in registers for the whole launch, and the
+// workgroup's 256 or 512 share the database tiles that stream through LDS, two in turn.  (67 queries of one piece, 1M x 128, k = 10: 145 us
+// with 128 a wavefront, one of four at work, 118 with 64.)
 // LDS: 16 bytes of (row, step, half) lie in slot row ^ step of the fragment's half: eight lanes bring a row's eight steps
 // and would all hit the same banks.
-template <int KS, int QP, bool DENSE>
+template <int KS, int QP, int NC, bool DENSE>
 __device__ __forceinline__ void filter_as_bf16(const BruteArgs& g, unsigned char* smem, int split, int64_t first_query) {
-    constexpr int NC = 4 / QP, kTileBytes = kStatRows / 32 * KS * kFrag * 2;
+    constexpr int kTileBytes = kStatRows / 32 * KS * kFrag * 2;                // NC: tiles of 32 queries a wavefront has
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, splits = g.splits;
     const int64_t q0 = first_query + wave * (NC * 32);
     const bool active = q0 < g.nq;             // (else the wavefront only brings vectors)
@@ -708,12 +709,13 @@ __global__ __launch_bounds__(kBfThreads, 2) void bf_filter_stationary_kernel(Bru
         return;
     }
     if (!(query_state(g, group) & kSecondPiece)) {
-        filter_as_bf16<KS, 1, DENSE>(g, smem, split, first_query);
+        if (g.nq - first_query > kStatQueries / 2) filter_as_bf16<KS, 1, 4, DENSE>(g, smem, split, first_query);
+        else filter_as_bf16<KS, 1, 2, DENSE>(g, smem, split, first_query);
         return;
     }
     for (int64_t q = first_query; q < first_query + kStatQueries && q < g.nq; q += kStatQueries / 2) {
         __syncthreads();                       // (the first half's last tile has been read)
-        filter_as_bf16<KS, 2, DENSE>(g, smem, split, q);
+        filter_as_bf16<KS, 2, 2, DENSE>(g, smem, split, q);
     }
 }
 
