@@ -7,15 +7,15 @@
 
 namespace pqt {
 
-// The query comes first: it is read in 16-byte pieces.
+// (The query is read in 16-byte pieces.)
 struct TraverseOneLds {
-    size_t off_q, off_key, off_qn, off_d1, off_sel, total;
+    size_t off_key, off_q, off_qn, off_d1, off_sel, total;
 };
 __host__ __device__ constexpr TraverseOneLds traverse_one_layout(int D, int P, int k1, int k2, int M, int w) {
     TraverseOneLds L = {};
     size_t o = 0;
+    L.off_key = o; o += (sizeof(unsigned long long) * P * w * k2 + 15) & ~size_t(15);
     L.off_q = o;   o += sizeof(float) * ((D + 3) & ~3);
-    L.off_key = o; o += sizeof(unsigned long long) * P * w * k2;
     L.off_qn = o;  o += sizeof(float) * M;
     L.off_d1 = o;  o += sizeof(float) * P * k1;
     L.off_sel = o; o += sizeof(int) * P * w;
