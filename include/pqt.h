@@ -354,7 +354,9 @@ int pqt_query_batch_debug(pqt_index* index, const float* queries, int64_t nq, in
 
 /*
  * Per-stage device timing.  With profiling enabled every pqt_query_batch records HIP events
- * on its stream around its three kernels: [0] traversal (level-1 + level-2 distances and
+ * on its stream around three kernels.  (Batches of up to 1,024 queries are mostly answered by one kernel
+ * otherwise, up to a third faster: there the stage times are those of the three kernels, whose results are the
+ * same, and not parts of an unprofiled call's time.)  The stages: [0] traversal (level-1 + level-2 distances and
  * sorts), [1] bin ranking head pass (all of the bin ranking for four tree parts), [2] gather +
  * re-rank + top-k (with the full bin ranking of the queries the head pass left over), [3] exact
  * re-ranking of the short list (pqt_query_batch_exact only, else 0).

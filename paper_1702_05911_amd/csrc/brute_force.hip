@@ -911,6 +911,8 @@ __device__ __forceinline__ void filter_general(const BruteArgs& g, unsigned char
 // for 777 queries x 150,001 x 960, with 16 dimensions a step 483.  LDS: the 16 bytes of a row's dimensions 8 j .. + 8 lie in slot
 // row ^ 2 j (415 us without).
 // The same, k = 10: the contraction after the first chunk 759 us by bf16 pieces, 404 by halves.
+// What is kept gets exact fp32 distances, so that results are the same bits as by pieces (ten collections of 96 to 4,096 dimensions,
+// 40,000 to 1M vectors; distances off from 64 bits by 1.6e-7 at most, the k nearest not at all, by either).
 template <int QW>
 struct HalvesLds {
     static constexpr int kVectors = kGenRows * 32 * 2, kQueries = QW * 128 * 32 * 2;       // a step's

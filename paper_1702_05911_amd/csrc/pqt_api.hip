@@ -129,6 +129,8 @@ int rerank_runs_in_lds(const pqt_index* ix) {
 // and 713, at 80: 834 and 804; M = 6 pairs 2,040 at 60: 59 and 65, 10,000 at 110: 382 and 370; M = 64 4,000 at 60: 327 and 358,
 // at 80: 421 and 409.  One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
 // 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233.
+// (These are times of three launches.  Up to 1,024 queries mostly take one, and come here with stage times or intermediate results asked
+// for, with more than 256 entries a list, or where one launch does not fit or does not pay.)
 double headless_from(const pqt_index* ix, int64_t nq) {
     const uint32_t M = ix->M;
     const bool pairs = ix->code_format == PQT_CODES_PAIR_LAMBDA;

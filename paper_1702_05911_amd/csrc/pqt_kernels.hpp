@@ -227,12 +227,14 @@ struct BruteArgs {
     // workspace
     uint32_t* control;
     uint32_t* flagged;            // nq: 1 = left to the exact scan
-    uint32_t* second;             // per tile of 32 queries: has one a second bf16 piece, or a value that is not a byte
+    uint32_t* second;             // per tile of 32 queries, as its packing finds: bit 0: one has a second bf16 piece, 1: a value that is not
+                                  // a byte, 2: a norm out of the halves' range
     uint32_t* todo;               // those queries
     uint32_t* scan_done;          // parts of the database that a group of them has been compared with
     float* qnorm;                 // ||q||
     float* qshift;                // what makes a value one of centred vectors
-    float* edge;                  // the k-th smallest value is taken to be at most this, ...
+    float* edge;                  // at most this is the value of the rank that the k nearest hardly exceed among the vectors seen, a guess for
+                                  // the k-th nearest of all until the last chunk has k values up to it; ...
     float* keep;                  // ... so that larger values than this do not matter,
     float* keep_halves;           // or, of products of halves, than this
     uint32_t* best_count;         // entries of best

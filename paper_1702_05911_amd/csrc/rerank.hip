@@ -84,7 +84,8 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
         // Codes of six and sixteen words take 128 registers, so that one workgroup of 1,024 threads fits a compute unit and two of
         // the byte-wise kernel do: more queries than compute units in such workgroups go there.  300 and 1,000 queries, M = 32, 600
         // candidates: 46 and 76 us by words, 37 and 54 by bytes; 4,096: 88 and 149, 80 and 130; M = 12, 1,600: 50 and 80, 46 and
-        // 70; 100 queries, M = 32, 10,000: 82 and 85; 4,000 queries (smaller workgroups), 4,096: 462 and 521.
+        // 70; 100 queries, M = 32, 10,000: 82 and 85; 4,000 queries (smaller workgroups), 4,096: 462 and 521.  (Batches of 257 to 1,024
+        // queries come here where they are not answered in one launch.)
         const bool by_bytes = a.threads == 1024 && a.nq > 256 && (a.M == 12 || a.M == 32);
         switch (taps || by_bytes || a.M % 2 ? 0 : a.M / 2) {
             case 2: return launch_rerank_pair2(a, L, rk, RL, taps, f, s);

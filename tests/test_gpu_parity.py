@@ -1450,8 +1450,9 @@ def test_brute_force_in_rounds(pqt, stored, D):
     (36, 2, 9, 4, 2, 4, 0, 64, 500, 9, "table"),             # part dimensions of 18: three launches
 ])
 def test_small_batches(pqt, D, P, k1, k2, M, w, H, T, C, k, codes):
-    """Batches that are answered in one launch (up to 1,024 queries, by workgroups of three sizes) against the launches with intermediate results and a larger
-    batch: the same ids and distance bits, with budgets that 32 tuples fill, that 64 do, and that take the full ranking."""
+    """Batches of up to 1,024 queries (answered in one launch by workgroups of three sizes, unless said otherwise) against the launches with
+    intermediate results and a larger batch: the same ids and distance bits, with budgets that 32 tuples fill, that 64 do, and that
+    take the full ranking."""
     import torch
     rng = np.random.default_rng(23)
     N, bins = 20_000, (k1 * k2) ** P
@@ -1517,12 +1518,13 @@ def test_exact_rerank_of_long_lists(pqt, k_short, k, C, same):
         pqt.pqt_index_set_vectors(ix, x)
         Y = torch.from_numpy(rng.integers(0, 64, (nq, D)).astype(np.float32)).cuda()
         short, _ = pqt.pqt_query_batch(ix, Y, k_short, w)
-        ids, d = pqt.pqt_query_batch_exact(ix, Y, k_short, k, w)
         true = ((x[short.clamp(min=0)].double() - Y.double()[:, None]) ** 2).sum(2)
         key = torch.where(short >= 0, true * N + short, torch.inf).sort(1).values[:, :k]
         want = torch.where(key.isinf(), -1.0, torch.remainder(key, N)).long()
-        assert torch.equal(ids, want)
-        assert torch.equal(d.double(), torch.where(key.isinf(), torch.inf, torch.div(key, N, rounding_mode="floor")))
+        for n in (nq, 600, 300, 7):                                  # three launches; one, in workgroups of 256, 512 and 1,024 threads
+            ids, d = pqt.pqt_query_batch_exact(ix, Y[:n].contiguous(), k_short, k, w)
+            assert torch.equal(ids, want[:n]), n
+            assert torch.equal(d.double(), torch.where(key.isinf(), torch.inf, torch.div(key, N, rounding_mode="floor"))[:n]), n
     finally:
         pqt.pqt_index_free(ix)
 
