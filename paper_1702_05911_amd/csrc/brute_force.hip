@@ -1094,7 +1094,7 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
     __shared__ uint32_t hist[kSelectBins];
     __shared__ uint32_t part[kBfThreads / kWave];
     __shared__ float bounds[2 * kBfThreads / kWave];
-    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow, 5, 6 entries before and up to its end; 2, 7 counts
+    __shared__ uint32_t misc[8];                    // 2 chosen bin, 3 entries kept, 4 overflow, 5, 6 entries before and up to its end
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, k = g.k;
     const int64_t q = blockIdx.x;
     if (g.flagged[q]) return;
@@ -1261,24 +1261,25 @@ __global__ __launch_bounds__(kBfThreads) void bf_select_kernel(BruteArgs g, int 
             // Is there room for what the halves' window lets pass?  In the next chunk as much as in this one, in proportion; in the
             // end what is in the window of the k nearest: as large a share of all vectors as of these, if they are crowded there; where
             // the values thin out towards the nearest, k times what a window from the nearest of these holds.
-            const float near = keep_up_to(g, g.err_half, qn, g.qshift[q], least);
-            __syncthreads();                         // (misc[2] has been read)
-            if (tid == 0) misc[2] = misc[7] = 0u;
-            __syncthreads();
-            uint32_t up_to = 0, up_to_near = 0;
-            for (int e = tid; e < n; e += kBfThreads) {
-                up_to += value(e) <= wide ? 1u : 0u;
-                up_to_near += value(e) <= near ? 1u : 0u;
-            }
-            atomicAdd(&misc[2], up_to);
-            atomicAdd(&misc[7], up_to_near);
-            __syncthreads();
+            auto count_up_to = [&](float bound) {    // (to misc[2])
+                __syncthreads();                     // (misc[2] has been read)
+                if (tid == 0) misc[2] = 0u;
+                __syncthreads();
+                uint32_t up_to = 0;
+                for (int e = tid; e < n; e += kBfThreads) up_to += value(e) <= bound ? 1u : 0u;
+                atomicAdd(&misc[2], up_to);
+                __syncthreads();
+                return misc[2];
+            };
+            const uint32_t up_to = count_up_to(wide);
             const float share = (float)g.N / (float)kDense;
-            const float in_the_end = fminf(share * (float)misc[2], fmaxf(share, (float)k) * (float)misc[7]);
-            const bool full = misc[2] > (uint32_t)kBest;                       // (not even now: this query's list is one for bf16)
+            bool crowded = (int)up_to > g.crowded_next;
+            const bool full = up_to > (uint32_t)kBest;                         // (not even now: this query's list is one for bf16)
+            if (!crowded && share * (float)up_to > (float)kBest)               // (the same for the whole workgroup)
+                crowded = fmaxf(share, (float)k) * (float)count_up_to(keep_up_to(g, g.err_half, qn, g.qshift[q], least)) > (float)kBest;
             if (!full) keep = wide;
             if (tid == 0 && full) atomicOr(&g.control[kBfCrowded], kHalvesOff);
-            else if (tid == 0 && ((int)misc[2] > g.crowded_next || in_the_end > (float)kBest)) atomicAdd(&g.control[kBfCrowded], 1u);
+            else if (tid == 0 && crowded) atomicAdd(&g.control[kBfCrowded], 1u);
         }
     }
     // ---- keep what can still be among the k nearest ---------------------------------------------------------------
