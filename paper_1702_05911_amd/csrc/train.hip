@@ -18,6 +18,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "pqt_device.hpp"
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_init_kernel(LloydArgs g, 
 }
 
 // The chunks of every group: pieces of `rows` members.  One workgroup; at most 1024 groups (four parts, 256 cells).
-__global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, int G, uint32_t rows, uint32_t* chunk_off, uint4* chunks) {
+__global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, int G, uint32_t rows, uint32_t limit, uint32_t* chunk_off, uint4* chunks) {
     __shared__ uint32_t part[1024 / kWave];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const uint2 mine = tid < G ? range[tid] : make_uint2(0u, 0u);
@@ -114,6 +115,7 @@ __global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, i
     const uint32_t at = block_exclusive_sum((uint32_t)(((uint64_t)(mine.y - mine.x) + rows - 1) / rows), part, total);
     if (tid < G) chunk_off[tid] = at;
     if (tid == 0) chunk_off[G] = total;
+    for (uint32_t c = total + tid; c < limit; c += blockDim.x) chunks[c] = make_uint4(0u, 0u, 0u, 0u);     // empty ones
     for (int l = 0; l < kWave; ++l) {                        // a wavefront writes its groups one after the other
         const int grp = wave * kWave + l;
         if (grp >= G) break;
@@ -129,12 +131,8 @@ __global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, i
 // the members of every cell, in double precision, members in ascending order in a fixed split.
 // A thread has one vector, whose values come from LDS 32 dimensions at a time, and KB running distances; the
 // centroids are the same for the whole workgroup and come through the scalar cache.  The sums are taken from the vectors
-// once more (they are in L2): the tile's vectors are ordered by cell, a wavefront adds up one cell's.
-// Bound by the two vector instructions per value and centroid (10 us of an iteration's 36 at 100,000 vectors x 128, 16
-// centroids), the staging of the vectors from the last-level cache (8 us) and the sums (9 us).  One wavefront per vector with
-// one lane per centroid, all vectors sorted by cell in every iteration: 35.9 ms for the whole of pqt_train on 100,000
-// vectors x 128 (16 and 8 centroids, 20 iterations, line table), against 2.1.  Staging by wavefront with the next slab in
-// registers was slower (41 us an iteration): its registers cost a resident workgroup.
+// once more (they are in L2): the tile's vectors are ordered by cell, a wavefront adds up one cell's.  For rows and cells that
+// lloyd_tile_kernel, below, has no room for.
 // WAYS: 1, or 4 where there are too few vectors to fill the chip and many centroids (see ways_of): a tile is then 64
 // vectors, and every wavefront has all of them and a quarter of the centroids.
 template <int KB, int WAYS>
@@ -308,6 +306,212 @@ __global__ __launch_bounds__(kTrainThreads) void lloyd_step_kernel(LloydArgs g) 
     }
 }
 
+// ---- the same step with whole rows and the centroids in LDS ----------------------------------------------------------
+// A lane works on VR vectors (lane mod 16, and 16 further) and on every fourth centroid, so that with VR = 2 six 16-byte reads
+// feed 64 vector instructions (16 centroids).  A cell's sum is taken from the staged rows by the one wavefront that owns the
+// cell, members in ascending order, and stays in its registers from tile to tile.  Rows come to LDS without passing through
+// registers, an odd number of 16-byte pieces apart: a vector per lane (16 bytes) and a dimension per lane (4 bytes) read without
+// conflicts.
+// 100,000 vectors x 128, P = 2, an iteration's step, this kernel and lloyd_step_kernel: 16 centroids 28.7 and 35.8 us, 8 centroids
+// in each of 16 cells 21.6 and 22.8.  Of the 28.7: two vector instructions per value and centroid 10.4, the way to the first
+// vectors and their staging 6, sums 5; the four workgroups of a compute unit go through these steps nearly together.  With the
+// centroids through the scalar cache and a quarter of them per wavefront the distances waited for them (31 to 40 us, also with the next
+// rows on their way); sums added up in LDS, a cell's rows found one by one, took twice as long.
+constexpr int kTileWaves = kTrainThreads / kWave;
+constexpr int kTileDims = 128, kTileCells = 48;              // at most
+constexpr int tile_vectors(int dp) { return dp <= kWave ? 2 : 1; }       // of a lane: the tile leaves room for three workgroups and more
+struct TileLds {
+    int st;                                                  // 16-byte pieces from row to row
+    size_t cen, cell, row, list, total;
+};
+// kp: centroids of a group with the padding
+__host__ __device__ constexpr TileLds tile_layout(int dp, int kp, int vr) {
+    TileLds L = {};
+    const int rows = kTileWaves * 16 * vr;
+    L.st = (dp + 3) / 4 | 1;
+    L.cen = (size_t)rows * L.st * 16;
+    L.cell = L.cen + (size_t)((dp + 3) / 4) * kp * 16;
+    L.row = L.cell + sizeof(uint32_t) * rows;
+    L.list = L.row + sizeof(uint32_t) * rows;                // of every wavefront: rows by cell
+    L.total = L.list + (size_t)kTileWaves * rows;
+    return L;
+}
+
+// KR: centroids of a lane, and cells of a wavefront.  VR: vectors of a lane.  ND: dimensions of a lane when sums are taken.
+template <int KR, int VR, int ND>
+__global__ __launch_bounds__(kTrainThreads, 4) void lloyd_tile_kernel(LloydArgs g) {
+    typedef const __attribute__((address_space(1))) void global_bytes;
+    typedef __attribute__((address_space(3))) void lds_bytes;
+    constexpr int kRows = kTileWaves * 16 * VR;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const uint4 chunk = g.chunks[blockIdx.x];
+    const int grp = __builtin_amdgcn_readfirstlane((int)chunk.x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk.y), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk.z);
+    if (lo == hi) return;                                    // past the last chunk
+    if (!g.label && g.frozen[grp]) return;
+    const int dp = g.dp, k = g.k, kp = g.kp, nd4 = (dp + 3) / 4;
+    const int p = grp / (g.G / g.P), col0 = p * dp;
+    const uint32_t* mem = g.members ? g.members + (size_t)p * g.n : nullptr;
+    const TileLds L = tile_layout(dp, kp, VR);
+    const int st = L.st;
+    const float per_row = 1.0f / (float)st;
+    float* sx = reinterpret_cast<float*>(smem);
+    float4* cen = reinterpret_cast<float4*>(smem + L.cen);
+    uint32_t* cells = reinterpret_cast<uint32_t*>(smem + L.cell);
+    uint32_t* rows = reinterpret_cast<uint32_t*>(smem + L.row);
+    uint8_t* list = smem + L.list + wave * kRows;
+    // the vector of this thread's row of the tile at t0; what lies past the last one is read from there and not used
+    auto row_of = [&](uint32_t t0) {
+        const uint32_t at = min(t0 + (uint32_t)min(tid, kRows - 1), hi - 1);
+        return mem ? mem[at] : at;
+    };
+    uint32_t row = row_of(lo);
+    const float4* from = reinterpret_cast<const float4*>(g.cenI) + (size_t)grp * nd4 * kp;
+    for (int e = tid; e < nd4 * kp; e += kTrainThreads) cen[e] = from[e];
+    double acc[KR][ND];
+    uint32_t cnt[KR];
+#pragma unroll
+    for (int j = 0; j < KR; ++j) {
+        cnt[j] = 0u;
+#pragma unroll
+        for (int d = 0; d < ND; ++d) acc[j][d] = 0.0;
+    }
+    const int v0 = wave * 16 * VR + (lane & 15), column = lane >> 4;
+    const float4* xs = reinterpret_cast<const float4*>(sx) + v0 * st;
+    for (uint32_t t0 = lo; t0 < hi; t0 += (uint32_t)kRows) {
+        const int m = (int)min(hi - t0, (uint32_t)kRows);
+        if (tid < kRows) rows[tid] = row;
+        __syncthreads();                                     // (and the tile before is done with)
+        row = row_of(min(t0 + (uint32_t)kRows, hi - 1));
+        // piece e of the tile is piece e mod st of row e / st
+        if (g.wide) {
+            for (int u = wave; u < kRows * st / kWave; u += kTileWaves) {
+                const int e = u * kWave + lane, r = (int)(((float)e + 0.5f) * per_row), c = e - r * st;
+                __builtin_amdgcn_global_load_lds((global_bytes*)(g.X + (size_t)rows[r] * g.D + col0 + 4 * (c < nd4 ? c : 0)),
+                                                 (lds_bytes*)(sx + (size_t)u * kWave * 4), 16, 0, 0);
+            }
+        } else {
+            for (int e = tid; e < kRows * nd4 * 4; e += kTrainThreads) {
+                const int r = e / (nd4 * 4), d = e - r * (nd4 * 4);
+                sx[r * st * 4 + d] = d < dp ? g.X[(size_t)rows[r] * g.D + col0 + d] : 0.0f;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0);                       // (the loads that write LDS)
+        __syncthreads();
+        if (wave * 16 * VR < m) {                            // the same for the wavefront
+            float dist[VR][KR];
+#pragma unroll
+            for (int j = 0; j < KR; ++j)
+#pragma unroll
+                for (int v = 0; v < VR; ++v) dist[v][j] = 0.0f;
+            const float4* c = cen + column;                  // this lane's centroids: column, column + 4, ...
+#pragma unroll 2
+            for (int s = 0; s < nd4; ++s) {
+                float4 x[VR];
+#pragma unroll
+                for (int v = 0; v < VR; ++v) x[v] = xs[16 * v * st + s];
+#pragma unroll
+                for (int j = 0; j < KR; ++j) {
+                    const float4 y = c[s * kp + 4 * j];
+#pragma unroll
+                    for (int v = 0; v < VR; ++v) {
+                        float diff = x[v].x - y.x;
+                        dist[v][j] = fmaf(diff, diff, dist[v][j]);
+                        diff = x[v].y - y.y;
+                        dist[v][j] = fmaf(diff, diff, dist[v][j]);
+                        diff = x[v].z - y.z;
+                        dist[v][j] = fmaf(diff, diff, dist[v][j]);
+                        diff = x[v].w - y.w;
+                        dist[v][j] = fmaf(diff, diff, dist[v][j]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < VR; ++v) {
+                unsigned long long best = ~0ull;
+#pragma unroll
+                for (int j = 0; j < KR; ++j) {
+                    const unsigned long long key = ((unsigned long long)mono_key(dist[v][j]) << 32) | (uint32_t)(column + 4 * j);
+                    if (column + 4 * j < k && key < best) best = key;
+                }
+                for (int off = 16; off < kWave; off <<= 1) {
+                    const unsigned long long o = __shfl_xor(best, off, kWave);
+                    best = o < best ? o : best;
+                }
+                const int r = v0 + 16 * v;
+                if (column == 0) {
+                    cells[r] = r < m ? (uint32_t)best : 0xffffffffu;
+                    if (r < m) {
+                        g.dmin[(size_t)p * g.n + t0 + r] = mono_inv((uint32_t)(best >> 32));
+                        if (g.label) g.label[(size_t)p * g.n + t0 + r] = (uint32_t)best;
+                    }
+                }
+            }
+        } else if (lane < 16 * VR) {
+            cells[wave * 16 * VR + lane] = 0xffffffffu;
+        }
+        __syncthreads();
+        if (g.label) continue;
+        // the rows of this wavefront's cells, in order, then their sums: four rows on their way
+        constexpr int kHalves = kRows / kWave;
+        uint32_t cell[kHalves];
+        int first[KR + 1];
+        first[0] = 0;
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) cell[h] = cells[h * kWave + lane];
+#pragma unroll
+        for (int j = 0; j < KR; ++j) {
+            int n = first[j];
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) {
+                const bool mine = cell[h] == (uint32_t)(wave + kTileWaves * j);
+                const unsigned long long all = __ballot(mine);
+                if (mine) list[n + __popcll(all & ((1ull << lane) - 1ull))] = (uint8_t)(h * kWave + lane);
+                n += __popcll(all);
+            }
+            first[j + 1] = n;
+            cnt[j] += (uint32_t)(n - first[j]);
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int h = 0; h < kHalves; ++h) {                  // 64 places of the list at a time
+            if (h * kWave >= first[KR]) break;
+            const int place = (int)list[min(h * kWave + lane, first[KR] - 1)] * st * 4;
+#pragma unroll
+            for (int j = 0; j < KR; ++j) {
+                const int from_i = max(first[j] - h * kWave, 0), to_i = min(first[j + 1] - h * kWave, kWave);
+                for (int i = from_i; i < to_i; i += 4) {
+                    float v[4][ND];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const float* x = sx + lane + __builtin_amdgcn_readlane(place, min(i + u, to_i - 1));
+#pragma unroll
+                        for (int d = 0; d < ND; ++d) v[u][d] = x[d * kWave];     // (past the row's end: not written out)
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i + u < to_i)
+#pragma unroll
+                            for (int d = 0; d < ND; ++d) acc[j][d] += (double)v[u][d];
+                }
+            }
+        }
+    }
+    if (g.label) return;
+#pragma unroll
+    for (int j = 0; j < KR; ++j) {
+        const int cell = wave + kTileWaves * j;
+        if (cell >= k) continue;
+        double* out = g.sums + ((size_t)blockIdx.x * k + cell) * dp;
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+            if (lane + d * kWave < dp) out[lane + d * kWave] = acc[j][d];
+        if (lane == 0) g.counts[(size_t)blockIdx.x * k + cell] = cnt[j];
+    }
+}
+
 // Sum over the workgroup, returned to every thread.
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part) {
     uint32_t total;
@@ -316,12 +520,14 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part) {
     return total;
 }
 
-// centroid = mean of its members (the chunks added in ascending order in a fixed split); the cells of a frozen or empty
+// centroid = mean of its members (the chunks added in a fixed split and order); the cells of a frozen or empty
 // group keep what they hold.  An empty cell is re-seeded with the member of its group that lies farthest from its
 // centroid (ties: the smaller vector number); that vector then counts as at distance zero, so the next empty cell of the
-// group takes another one.  One workgroup per cell and 64 dimensions.
+// group takes another one.  One workgroup per cell and 16 dimensions (64: a quarter of the workgroups, of which two parts of
+// 16 cells have few).
+constexpr int kUpdateDims = 16;
 __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
-    __shared__ double red[1024];
+    __shared__ double red[1024 / kWave * kUpdateDims];
     __shared__ uint32_t part[1024 / kWave];
     __shared__ unsigned long long far_part[1024 / kWave];
     const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), k = g.k, dp = g.dp;
@@ -329,7 +535,7 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
     const uint32_t c0 = g.chunk_off[grp], c1 = g.chunk_off[grp + 1];
     const uint8_t keep = g.frozen[grp];
     if (keep || c0 == c1) return;
-    const int d = blockIdx.y * kWave + lane, r = tid / kWave, rl = nt / kWave;
+    const int dl = lane & (kUpdateDims - 1), d = blockIdx.y * kUpdateDims + dl, r = tid / kUpdateDims, rl = nt / kUpdateDims;
     uint32_t mine = 0;
     for (uint32_t c = c0 + tid; c < c1; c += nt) mine += g.counts[(size_t)c * k + j];
     double acc = 0.0;
@@ -343,12 +549,13 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
         for (int u = 0; u < kFlight; ++u)
             if (e + u * rl + r < c1) acc += v[u];
     }
-    red[tid] = acc;
+    for (int off = kUpdateDims; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+    if (lane < kUpdateDims) red[tid / kWave * kUpdateDims + lane] = acc;
     const uint32_t count = block_sum(mine, part);
     if (count > 0) {
         if (r == 0 && d < dp) {
             double t = 0.0;
-            for (int s = 0; s < rl; ++s) t += red[s * kWave + lane];
+            for (int s = 0; s < nt / kWave; ++s) t += red[s * kUpdateDims + dl];
             put_centroid(g, grp, j, d, (float)(t / (double)count));
         }
         return;
@@ -375,7 +582,7 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
         __syncthreads();
         if (lane == 0) far_part[tid / kWave] = best;
         __syncthreads();
-        for (int s = 0; s < rl; ++s) best = far_part[s] > best ? far_part[s] : best;
+        for (int s = 0; s < nt / kWave; ++s) best = far_part[s] > best ? far_part[s] : best;
         if (best == 0ull) {
             at = rg.x;
             break;
@@ -387,31 +594,88 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
         put_centroid(g, grp, j, d, g.X[(size_t)(g.members ? g.members[(size_t)p * g.n + at] : at) * g.D + (size_t)p * dp + d]);
 }
 
-// range[p * k1 + c] = the positions of level-1 cell c in its part's sorted labels
-__global__ void cell_ranges_kernel(const uint32_t* sorted, uint64_t n, int P, int k1, uint2* range) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= P * k1) return;
-    const uint32_t* s = sorted + (size_t)(e / k1) * n;
-    const uint32_t c = (uint32_t)(e % k1);
-    uint32_t at[2];
-    for (int b = 0; b < 2; ++b) {                            // first position whose label is not below c + b
-        uint64_t lo = 0, hi = n;
-        while (lo < hi) {
-            const uint64_t mid = (lo + hi) / 2;
-            if (s[mid] < c + (uint32_t)b) lo = mid + 1; else hi = mid;
+// ---- members of every part's cells, in ascending vector order ---------------------------------------------------------
+// A count per piece of `rows` labels and cell, a prefix sum over (cell, piece), and every vector goes to its place: three short
+// kernels (100,000 vectors, two parts: 9 us; a library sort of (label, vector) pairs per part took 100).
+constexpr int kCellThreads = 1024;
+constexpr int kCellWaves = kCellThreads / kWave;
+
+// counts[p][cell][piece]; blockIdx.y = p
+__global__ __launch_bounds__(kCellThreads) void cell_counts_kernel(const uint32_t* label, uint64_t n, int k, uint32_t rows, uint32_t* counts) {
+    extern __shared__ uint32_t cnt[];
+    const uint32_t* l = label + (size_t)blockIdx.y * n;
+    for (int j = threadIdx.x; j < k; j += kCellThreads) cnt[j] = 0u;
+    __syncthreads();
+    const uint64_t r0 = (uint64_t)blockIdx.x * rows, r1 = min(n, r0 + rows);
+    for (uint64_t r = r0 + threadIdx.x; r < r1; r += kCellThreads) atomicAdd(&cnt[l[r]], 1u);
+    __syncthreads();
+    for (int j = threadIdx.x; j < k; j += kCellThreads) counts[((size_t)blockIdx.y * k + j) * gridDim.x + blockIdx.x] = cnt[j];
+}
+
+// counts -> first places, in place; range[p * k + cell] = the cell's positions.  One workgroup per part.
+__global__ __launch_bounds__(kCellThreads) void cell_places_kernel(uint32_t* counts, uint32_t n, int k, uint32_t pieces, uint2* range) {
+    __shared__ uint32_t part[kCellWaves];
+    const uint32_t items = (uint32_t)k * pieces;
+    uint32_t* c = counts + (size_t)blockIdx.x * items;
+    uint2* rg = range + (size_t)blockIdx.x * k;
+    uint32_t before = 0;
+    for (uint32_t e0 = 0; e0 < items; e0 += kCellThreads) {
+        const uint32_t e = e0 + threadIdx.x;
+        uint32_t total;
+        const uint32_t at = before + block_exclusive_sum(e < items ? c[e] : 0u, part, total);
+        before += total;
+        if (e < items) {
+            c[e] = at;
+            if (e % pieces == 0) {
+                rg[e / pieces].x = at;
+                if (e > 0) rg[e / pieces - 1].y = at;
+            }
         }
-        at[b] = (uint32_t)lo;
+        __syncthreads();
     }
-    range[e] = make_uint2(at[0], at[1]);
+    if (threadIdx.x == 0) rg[k - 1].y = n;
+}
+
+__global__ __launch_bounds__(kCellThreads) void cell_members_kernel(const uint32_t* label, uint64_t n, int k, uint32_t rows, const uint32_t* places,
+                                                                    uint32_t* members) {
+    extern __shared__ uint32_t lds[];
+    uint32_t* next = lds;                                    // [cell]: its next place
+    uint32_t* cnt = lds + k;                                 // [wavefront][cell]
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t* l = label + (size_t)blockIdx.y * n;
+    uint32_t* out = members + (size_t)blockIdx.y * n;
+    for (int j = tid; j < k; j += kCellThreads) next[j] = places[((size_t)blockIdx.y * k + j) * gridDim.x + blockIdx.x];
+    const uint64_t r0 = (uint64_t)blockIdx.x * rows, r1 = min(n, r0 + rows);
+    for (uint64_t t0 = r0; t0 < r1; t0 += kCellThreads) {
+        for (int j = tid; j < kCellWaves * k; j += kCellThreads) cnt[j] = 0u;
+        __syncthreads();
+        const bool have = t0 + tid < r1;
+        const uint32_t cell = have ? l[t0 + tid] : 0u;
+        unsigned long long same = __ballot(have);            // lanes with this lane's cell
+        for (int b = 1; b < k; b <<= 1) {
+            const unsigned long long set = __ballot((cell & (uint32_t)b) != 0u);
+            same &= (cell & (uint32_t)b) ? set : ~set;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        if (have && rank == 0) cnt[wave * k + (int)cell] = (uint32_t)__popcll(same);
+        __syncthreads();
+        for (int j = tid; j < k; j += kCellThreads) {        // counts -> places of the wavefronts, in order
+            uint32_t at = next[j];
+            for (int w = 0; w < kCellWaves; ++w) {
+                const uint32_t c = cnt[w * k + j];
+                cnt[w * k + j] = at;
+                at += c;
+            }
+            next[j] = at;
+        }
+        __syncthreads();
+        if (have) out[cnt[wave * k + (int)cell] + (uint32_t)rank] = (uint32_t)(t0 + tid);
+        __syncthreads();
+    }
 }
 
 __global__ void whole_range_kernel(uint32_t n, int P, uint2* range) {
     if ((int)threadIdx.x < P) range[threadIdx.x] = make_uint2(0u, n);
-}
-
-__global__ void iota_u32_kernel(uint32_t* out, uint32_t n) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = i;
 }
 
 // first[m][q] = where line q's votes start among the sorted votes of sub-part m (m counted within the batch), q = 0..npairs
@@ -467,7 +731,17 @@ int centroid_block(int k) {
     const int rounds = (k + 31) / 32;
     return ((k + rounds - 1) / rounds + 7) / 8 * 8;
 }
-int padded_centroids(int k) {
+
+// Centroids of a lane of lloyd_tile_kernel; 0 where lloyd_step_kernel is the one to take: rows or cells beyond its registers and
+// what leaves room for one workgroup per compute unit only.
+int tile_block(int dp, int k) {
+    if (dp > kTileDims || k > kTileCells) return 0;
+    const int want = (k + 3) / 4;
+    const int kr = want <= 8 ? want : 12;
+    return tile_layout(dp, 4 * kr, tile_vectors(dp)).total <= 64 * 1024 ? kr : 0;
+}
+int padded_centroids(int dp, int k) {
+    if (const int kr = tile_block(dp, k)) return 4 * kr;
     const int kb = centroid_block(k);
     return (k + kb - 1) / kb * kb;
 }
@@ -480,6 +754,15 @@ int ways_of(uint64_t n, int P, int k) { return k >= 128 && (uint64_t)P * ((n + k
 // Vectors per chunk (a workgroup of lloyd_step_kernel): one tile, or more where that would be more chunks than keep the
 // chip busy, or more than 64 MB of cell sums.
 uint64_t chunk_rows(uint64_t n, int P, int G, int k, int dp) {
+    if (const int kr = tile_block(dp, k)) {
+        // as many as the compute units hold at once (the last one of every group is a short one)
+        const uint64_t fit = std::min<uint64_t>(4, kMaxLds / tile_layout(dp, 4 * kr, tile_vectors(dp)).total);
+        uint64_t want = 256 * fit;
+        while (want > 256 && want * (uint64_t)k * (uint64_t)dp > (8ull << 20)) want /= 2;
+        want -= std::min<uint64_t>((uint64_t)G, want / 2);
+        const uint64_t rows = ((uint64_t)P * n + want - 1) / want;
+        return std::max<uint64_t>(rows, 64);
+    }
     uint64_t rows = kTile / ways_of(n, P, k);
     while (rows < n && rows < (1ull << 30) && ((uint64_t)P * ((n + rows - 1) / rows) > kMaxChunks ||
                         ((uint64_t)P * ((n + rows - 1) / rows) + (uint64_t)G) * (uint64_t)k * (uint64_t)dp > (8ull << 20)))
@@ -490,6 +773,26 @@ uint64_t chunk_limit(uint64_t n, uint64_t rows, int P, int G) { return (uint64_t
 
 hipError_t launch_step(const LloydArgs& g, uint64_t chunks, hipStream_t st) {
     const dim3 grid((unsigned)chunks), block(kTrainThreads);
+    if (const int kr = tile_block(g.dp, g.k)) {
+        const size_t lds = tile_layout(g.dp, g.kp, tile_vectors(g.dp)).total;
+        auto launch = [&](auto kr_c) {
+            constexpr int KR = decltype(kr_c)::value;
+            if (tile_vectors(g.dp) == 2) hipLaunchKernelGGL((lloyd_tile_kernel<KR, 2, 1>), grid, block, lds, st, g);
+            else hipLaunchKernelGGL((lloyd_tile_kernel<KR, 1, 2>), grid, block, lds, st, g);
+        };
+        switch (kr) {
+            case 1: launch(std::integral_constant<int, 1>{}); break;
+            case 2: launch(std::integral_constant<int, 2>{}); break;
+            case 3: launch(std::integral_constant<int, 3>{}); break;
+            case 4: launch(std::integral_constant<int, 4>{}); break;
+            case 5: launch(std::integral_constant<int, 5>{}); break;
+            case 6: launch(std::integral_constant<int, 6>{}); break;
+            case 7: launch(std::integral_constant<int, 7>{}); break;
+            case 8: launch(std::integral_constant<int, 8>{}); break;
+            default: launch(std::integral_constant<int, 12>{}); break;
+        }
+        return hipGetLastError();
+    }
     const size_t lds = sizeof(uint32_t) * (kTrainThreads / kWave) * (size_t)g.k;
     if (ways_of(g.n, g.P, g.k) > 1) {                        // (at least 128 centroids: a block is 32 of them)
         hipLaunchKernelGGL((lloyd_step_kernel<32, 4>), grid, block, lds, st, g);
@@ -509,14 +812,14 @@ hipError_t lloyd_run(const LloydArgs& g, const float* parent, uint64_t rows, int
                      hipStream_t st) {
     const uint64_t limit = chunk_limit(g.n, rows, g.P, g.G);
     hipLaunchKernelGGL(lloyd_init_kernel, dim3((unsigned)g.G), dim3(kTrainThreads), 0, st, g, parent);
-    hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, st, g.range, g.G, (uint32_t)rows, chunk_off, chunks);
+    hipLaunchKernelGGL(chunk_table_kernel, dim3(1), dim3(1024), 0, st, g.range, g.G, (uint32_t)rows, (uint32_t)limit, chunk_off, chunks);
     hipError_t e = hipGetLastError();
     // a group's chunks are split over the wavefronts of a workgroup: sixteen where there are many of them
     const unsigned threads = limit / (unsigned)g.G >= 64 ? 1024 : 256;
     for (int it = 0; it < iters && e == hipSuccess; ++it) {
         e = launch_step(g, limit, st);
         if (e != hipSuccess) break;
-        hipLaunchKernelGGL(lloyd_update_kernel, dim3((unsigned)(g.G * g.k), (unsigned)((g.dp + kWave - 1) / kWave)), dim3(threads), 0,
+        hipLaunchKernelGGL(lloyd_update_kernel, dim3((unsigned)(g.G * g.k), (unsigned)((g.dp + kUpdateDims - 1) / kUpdateDims)), dim3(threads), 0,
                            st, g);
         e = hipGetLastError();
     }
@@ -582,22 +885,24 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     l1.X = vectors; l1.n = n; l1.D = (int)D; l1.dp = dp; l1.P = (int)P;
     l1.wide = reinterpret_cast<uintptr_t>(vectors) % 16 == 0 && D % 4 == 0 && dp % 4 == 0;
     l2 = l1;
-    l1.G = (int)P; l1.k = (int)k1; l1.kp = padded_centroids((int)k1);
-    l2.G = (int)(P * k1); l2.k = (int)k2; l2.kp = padded_centroids((int)k2);
+    l1.G = (int)P; l1.k = (int)k1; l1.kp = padded_centroids(dp, (int)k1);
+    l2.G = (int)(P * k1); l2.k = (int)k2; l2.kp = padded_centroids(dp, (int)k2);
     const uint64_t rows1 = chunk_rows(n, (int)P, l1.G, l1.k, dp), rows2 = chunk_rows(n, (int)P, l2.G, l2.k, dp);
     const uint64_t limit1 = chunk_limit(n, rows1, (int)P, l1.G), limit2 = chunk_limit(n, rows2, (int)P, l2.G);
+    // labels are counted in at most 1024 pieces per part
+    const uint32_t piece = (uint32_t)(((uint64_t)n + 1024ull * kCellThreads - 1) / (1024ull * kCellThreads) * kCellThreads);
+    const uint32_t pieces = (uint32_t)(((uint64_t)n + piece - 1) / piece);
     Arena mem;
     double* sums = nullptr;
-    uint32_t *counts = nullptr, *label = nullptr, *label_sorted = nullptr, *idx = nullptr, *members = nullptr, *chunk_off = nullptr;
+    uint32_t *counts = nullptr, *label = nullptr, *places = nullptr, *members = nullptr, *chunk_off = nullptr;
     uint4* chunks = nullptr;
     float* dmin = nullptr;
     uint2 *range1 = nullptr, *range2 = nullptr;
-    unsigned char *cub_temp = nullptr, *sort_temp = nullptr;
+    unsigned char* sort_temp = nullptr;
     mem.want(&sums, (size_t)std::max(limit1 * k1, limit2 * k2) * dp);
     mem.want(&counts, (size_t)std::max(limit1 * k1, limit2 * k2));
     mem.want(&label, (size_t)P * n);
-    mem.want(&label_sorted, (size_t)P * n);
-    mem.want(&idx, n);
+    mem.want(&places, (size_t)P * k1 * pieces);
     mem.want(&members, (size_t)P * n);
     mem.want(&dmin, (size_t)P * n);
     mem.want(&chunk_off, (size_t)l2.G + 1);
@@ -610,9 +915,6 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     mem.want(&l1.cenI, (size_t)P * nd4 * l1.kp * 4);
     mem.want(&l2.cen, (size_t)P * cells2 * dp);
     mem.want(&l2.cenI, (size_t)P * k1 * nd4 * l2.kp * 4);
-    size_t cub_bytes = 0;
-    HIP_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, cub_bytes, label, label_sorted, idx, members, (int)n, 0, log2_ceil(cells1), st));
-    mem.want(&cub_temp, cub_bytes);
     // the line table: the votes of as many sub-parts as fit 2^27 keys are sorted together
     LinePair* pair_dev = nullptr;
     float *c1n_dev = nullptr, *lam_dev = nullptr;
@@ -655,7 +957,6 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     }
 
     const unsigned tb = 256;
-    hipLaunchKernelGGL(iota_u32_kernel, dim3((n + tb - 1) / tb), dim3(tb), 0, st, idx, n);
     hipLaunchKernelGGL(whole_range_kernel, dim3(1), dim3(kWave), 0, st, n, (int)P, range1);
     // ---- level 1: one group per tree part, k1 centroids ------------------------------------------------
     HIP_TRY(lloyd_run(l1, nullptr, rows1, (int)tp->iters, chunk_off, chunks, st));
@@ -663,10 +964,11 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     LloydArgs cells = l1;
     cells.label = label;
     HIP_TRY(launch_step(cells, limit1, st));
-    for (uint32_t p = 0; p < P; ++p)
-        HIP_TRY(hipcub::DeviceRadixSort::SortPairs(cub_temp, cub_bytes, label + (size_t)p * n, label_sorted + (size_t)p * n, idx,
-                                                   members + (size_t)p * n, (int)n, 0, log2_ceil(cells1), st));
-    hipLaunchKernelGGL(cell_ranges_kernel, dim3((P * k1 + tb - 1) / tb), dim3(tb), 0, st, label_sorted, (uint64_t)n, (int)P, (int)k1, range2);
+    const dim3 by_piece(pieces, P);
+    hipLaunchKernelGGL(cell_counts_kernel, by_piece, dim3(kCellThreads), sizeof(uint32_t) * k1, st, label, (uint64_t)n, (int)k1, piece, places);
+    hipLaunchKernelGGL(cell_places_kernel, dim3(P), dim3(kCellThreads), 0, st, places, n, (int)k1, pieces, range2);
+    hipLaunchKernelGGL(cell_members_kernel, by_piece, dim3(kCellThreads), sizeof(uint32_t) * (kCellWaves + 1) * k1, st, label, (uint64_t)n,
+                       (int)k1, piece, places, members);
     HIP_TRY(hipGetLastError());
     // ---- level 2: the cells of all parts, k2 centroids each, trained side by side ---------------------------
     HIP_TRY(lloyd_run(l2, l1.cen, rows2, (int)tp->iters, chunk_off, chunks, st));

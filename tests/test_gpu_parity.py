@@ -721,6 +721,42 @@ def test_training_on_the_gpu(pqt, tiny):
     assert e.value.code in (pqt.PQT_EINVAL, pqt.PQT_EUNSUPPORTED)
 
 
+@pytest.mark.parametrize("n,D,P,k1,k2", [(63, 8, 1, 4, 2), (65, 2, 2, 3, 5), (1000, 64, 1, 16, 8), (257, 66, 1, 5, 3), (4133, 128, 1, 48, 7),
+                                         (700, 129, 1, 49, 2), (3001, 132, 2, 33, 12), (150_001, 24, 2, 12, 13), (2500, 256, 4, 31, 1)])
+def test_training_tile_edges(pqt, n, D, P, k1, k2):
+    """One Lloyd iteration on small whole numbers, where sums and distances are exact: every centroid is the mean of the vectors
+    nearest to the start centroids, rounded once; rows of 1 to 132 values, up to 64 and 128 of them with whole rows on the chip, cells
+    on both sides of what a wavefront owns, samples around a tile and beyond one chunk per compute unit."""
+    import torch
+    dp = D // P
+    X = np.random.default_rng(n).integers(0, 16, (n, D)).astype(np.float32)
+    got = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=k2, M=P, iters=1, n_table=0)
+    again = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=k2, M=P, iters=1, n_table=0)
+    for p in range(P):
+        Xp = X[:, p * dp:(p + 1) * dp].astype(np.float64)
+        start = Xp[(np.arange(k1) * n) // k1]
+        lab = np.argmin(np.stack([((Xp - c) ** 2).sum(axis=1) for c in start], axis=1), axis=1)
+        for i in range(k1):
+            if np.any(lab == i):
+                np.testing.assert_array_equal(got["C1"][p, i], Xp[lab == i].mean(axis=0).astype(np.float32))
+        # the cells of the finished quantiser; a vector halfway between two of them (to rounding) may be in either
+        d1 = np.stack([((Xp - c) ** 2).sum(axis=1) for c in got["C1"][p].astype(np.float64)], axis=1)
+        near = np.sort(d1, axis=1)[:, :2]
+        if k1 > 1 and np.any(near[:, 1] - near[:, 0] <= 1e-5 * (1.0 + near[:, 0])):
+            continue
+        for i in range(k1):
+            sub = Xp[np.argmin(d1, axis=1) == i]
+            if sub.shape[0] <= k2:
+                continue
+            start2 = sub[(np.arange(k2) * sub.shape[0]) // k2]
+            lab2 = np.argmin(np.stack([((sub - c) ** 2).sum(axis=1) for c in start2], axis=1), axis=1)
+            for j in range(k2):
+                if np.any(lab2 == j):
+                    np.testing.assert_array_equal(got["C2"][p, i, j], sub[lab2 == j].mean(axis=0).astype(np.float32))
+    for name in got:
+        assert np.array_equal(got[name], again[name]), f"{name}: training is not deterministic"
+
+
 def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
     """Codes stored as (centroid pair, lambda level): stage-wise parity of the query path on an
     oracle-built index; the lut tap is refused; a pair byte beyond the last pair is a format error."""
