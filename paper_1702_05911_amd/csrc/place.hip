@@ -11,7 +11,7 @@
 //
 // Bound by vector instructions (six per vector, sub-part and code point) and, above 32 centroids, LDS reads (two of them): up to
 // 32 the code search has a lane's distances in registers (2,000,003 vectors, below: the whole call 2.73 -> 2.29 ms).
-// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 1.76 ms; the traversal kernel with w = 1 (one wavefront
+// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 1.62 ms (code search 0.62, level 2 0.3); the traversal kernel with w = 1 (one wavefront
 // per list, 8 of 64 lanes at work), its distances written and read back, and one wavefront per vector for the codes took
 // 7.0.  With staged values and distances side by side in LDS three workgroups instead of five fit a compute unit: 2.9.
 #include <type_traits>
@@ -363,6 +363,76 @@ __device__ __forceinline__ void finish_vectors(const PlaceArgs& g, int64_t v0, i
         for (int e = tid; e < bytes; e += nt) out[e] = code[e];
 }
 
+// The nearest child of cluster i of part p for one vector: (ordered bits of the distance) << 32 | leaf, plain squared differences,
+// dimensions in ascending order.  Four lanes share the vector: each brings every fourth 16 bytes of it, which the others take from its
+// register in the subtraction itself, and works on every fourth child, two at a time.  What bounds it is the 64 bytes a clock that the
+// vector cache returns: 9 loads per 16 dimensions and 128 (vector, child) pairs, 16 with a lane per pair that brings the vector for
+// itself (2,000,003 vectors x 128, P = 2, k2 = 8: the kernel 1.74 -> 1.62 ms).
+template <int U>
+__device__ __forceinline__ float quad_value(float x) {       // of lane U of every four
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), U * 0x55, 0xf, 0xf, true));
+}
+template <int U>
+__device__ __forceinline__ void child_step(const float4& y, const float4& c, float& acc) {
+    float diff = quad_value<U>(y.x) - c.x;
+    acc = fmaf(diff, diff, acc);
+    diff = quad_value<U>(y.y) - c.y;
+    acc = fmaf(diff, diff, acc);
+    diff = quad_value<U>(y.z) - c.z;
+    acc = fmaf(diff, diff, acc);
+    diff = quad_value<U>(y.w) - c.w;
+    acc = fmaf(diff, diff, acc);
+}
+__device__ __forceinline__ unsigned long long nearest_child(const PlaceArgs& g, int64_t v, int p, uint32_t i) {
+    const int l = threadIdx.x & 3, k2 = g.k2, dp = g.D / g.P, nd4 = dp / 4;
+    const float4* y = reinterpret_cast<const float4*>(g.x + (size_t)v * g.D + (size_t)p * dp);
+    const float4* cluster = reinterpret_cast<const float4*>(g.C2t) + ((size_t)p * g.k1 + i) * nd4 * k2;
+    unsigned long long best = ~0ull;
+    for (int j0 = 0; j0 < k2; j0 += 8) {
+        const int j = j0 + l;
+        const bool two = j0 + 4 < k2;                        // the same for all lanes
+        const float4* a = cluster + min(j, k2 - 1);
+        const float4* b = cluster + min(j + 4, k2 - 1);
+        float acc[2] = {0.0f, 0.0f};
+        int d = 0;
+        for (; d + 4 <= nd4; d += 4) {
+            const float4 yv = y[d + l];
+            float4 c[2][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[0][u] = a[(size_t)(d + u) * k2];
+            if (two)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c[1][u] = b[(size_t)(d + u) * k2];
+            child_step<0>(yv, c[0][0], acc[0]);
+            child_step<1>(yv, c[0][1], acc[0]);
+            child_step<2>(yv, c[0][2], acc[0]);
+            child_step<3>(yv, c[0][3], acc[0]);
+            if (two) {
+                child_step<0>(yv, c[1][0], acc[1]);
+                child_step<1>(yv, c[1][1], acc[1]);
+                child_step<2>(yv, c[1][2], acc[1]);
+                child_step<3>(yv, c[1][3], acc[1]);
+            }
+        }
+        for (; d < nd4; ++d) {
+            const float4 yv = y[d];                          // (the same in all four)
+            child_step<0>(yv, a[(size_t)d * k2], acc[0]);
+            if (two) child_step<0>(yv, b[(size_t)d * k2], acc[1]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const unsigned long long key = ((unsigned long long)mono_key(acc[u]) << 32) | (i * (uint32_t)k2 + (uint32_t)(j + 4 * u));
+            if (j + 4 * u < k2 && key < best) best = key;
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < 4; off <<= 1) {
+        const unsigned long long o = __shfl_xor(best, off, kWave);
+        best = o < best ? o : best;
+    }
+    return best;
+}
+
 // K: centroids whose distances the search for table codes has in registers (nearest_code).
 template <int MODE, bool WIDE, int K>
 __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) {
@@ -419,37 +489,28 @@ __global__ __launch_bounds__(256, 5) void place_kernel(PlaceArgs g, PlaceLds L) 
     if (MODE == kVotes) return;
 
     // ---- level 2: the children of the nearest cluster, plain squared differences, dimensions in ascending order ----
-    const int nd4 = dp / 4;
-    for (int p = 0; p < P; ++p)
-        for (int e = tid; e < kPlaceRows * k2; e += nt) {
-            const int v = e / k2, j = e - v * k2;
-            if (v >= nv) continue;
-            const uint32_t i = (uint32_t)sel[p * kPlaceRows + v];
-            const float* y = g.x + (size_t)(v0 + v) * D + (size_t)p * dp;
-            float acc = 0.0f;
-            if (WIDE && g.C2t) {
-                const float4* c = reinterpret_cast<const float4*>(g.C2t) + ((size_t)p * k1 + i) * nd4 * k2 + j;
-#pragma unroll 4
-                for (int d = 0; d < nd4; ++d) {
-                    const float4 yv = *reinterpret_cast<const float4*>(y + 4 * d), cv = c[(size_t)d * k2];
-                    float diff = yv.x - cv.x;
-                    acc = fmaf(diff, diff, acc);
-                    diff = yv.y - cv.y;
-                    acc = fmaf(diff, diff, acc);
-                    diff = yv.z - cv.z;
-                    acc = fmaf(diff, diff, acc);
-                    diff = yv.w - cv.w;
-                    acc = fmaf(diff, diff, acc);
-                }
-            } else {
+    if (WIDE && g.C2t) {
+        for (int p = 0; p < P; ++p)
+            for (int v = tid / 4; v < kPlaceRows; v += nt / 4) {
+                const unsigned long long key = nearest_child(g, v0 + min(v, nv - 1), p, (uint32_t)sel[p * kPlaceRows + v]);
+                if ((tid & 3) == 0 && v < nv) leaf[p * kPlaceRows + v] = key;
+            }
+    } else {
+        for (int p = 0; p < P; ++p)
+            for (int e = tid; e < kPlaceRows * k2; e += nt) {
+                const int v = e / k2, j = e - v * k2;
+                if (v >= nv) continue;
+                const uint32_t i = (uint32_t)sel[p * kPlaceRows + v];
+                const float* y = g.x + (size_t)(v0 + v) * D + (size_t)p * dp;
                 const float* c = g.C2 + (((size_t)p * k1 + i) * k2 + j) * dp;
+                float acc = 0.0f;
                 for (int d = 0; d < dp; ++d) {
                     const float diff = y[d] - c[d];
                     acc = fmaf(diff, diff, acc);
                 }
+                atomicMin(&leaf[p * kPlaceRows + v], ((unsigned long long)mono_key(acc) << 32) | (i * (uint32_t)k2 + (uint32_t)j));
             }
-            atomicMin(&leaf[p * kPlaceRows + v], ((unsigned long long)mono_key(acc) << 32) | (i * (uint32_t)k2 + (uint32_t)j));
-        }
+    }
     __syncthreads();
     if (tid < nv) {
         unsigned long long lin = 0;

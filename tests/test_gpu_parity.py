@@ -793,6 +793,27 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
         assert e.value.code == pqt.PQT_EFORMAT
 
 
+@pytest.mark.parametrize("k1, M", [(2, 3), (3, 12), (4, 1), (12, 24), (16, 8), (17, 4), (20, 12), (23, 2), (23, 6)])
+def test_pair_table_edges(pqt, tmp_path, k1, M):
+    """The table of centroid pairs on the chip: one pair to the most of a byte, odd and even numbers of them (an odd one is
+    padded), codes read by words and by bytes, by the small batches' kernel and the others."""
+    rng = np.random.default_rng(k1)
+    X = rng.integers(0, 32, (900, 24)).astype(np.float32)
+    Y = rng.integers(0, 32, (300, 24)).astype(np.float32)
+    ix = B.build_index(X, 1, k1, 4, M, T=3 * k1, C=500, iters=3, code_format=1)
+    path = str(tmp_path / "pairs.pqt")
+    IO.write_index(path, ix)
+    _stagewise(pqt, ix, path, Y[:6], 10, 2, 3 * k1, 500)
+    import torch
+    gix = pqt.pqt_index_load(path, 0)
+    try:
+        few, _ = pqt.pqt_query_batch(gix, torch.from_numpy(Y[:6]).cuda(), 10, 2)
+        many, _ = pqt.pqt_query_batch(gix, torch.from_numpy(np.tile(Y, (8, 1))).cuda(), 10, 2)
+        assert torch.equal(many[:6], few) and torch.equal(many[:300], many[2100:])
+    finally:
+        pqt.pqt_index_free(gix)
+
+
 @pytest.mark.parametrize("many", [0, 12_300])     # more than 8,192 vectors in the second call: 64 per workgroup instead of 16
 @pytest.mark.parametrize("N, D, P, k1, k2, M, fmt, offset", [
     (63, 16, 2, 16, 8, 4, 0, 0),           # one vector short of a workgroup; one tile of centroids
@@ -804,6 +825,8 @@ def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
     (100, 16, 2, 8, 1, 4, 0, 1),           # vectors that do not start at a multiple of 16 bytes
     (70, 16, 1, 256, 2, 2, 0, 0),          # the most centroids
     (131, 12, 1, 4, 300, 3, 0, 0),         # more children than threads
+    (66, 40, 2, 3, 5, 5 * 2, 0, 0),        # children of four lanes and one more; a part's five 16-byte pieces, one after four
+    (130, 32, 1, 4, 9, 4, 0, 0),           # eight children and one more; eight pieces
     (67, 16, 2, 20, 7, 4, 1, 0),           # (pair, lambda) codes
     (130, 16, 2, 7, 3, 4, 0, 0),           # 16-byte rows and numbers of centroids that are no multiple of four, so that a
     (77, 64, 2, 21, 2, 4, 0, 0),           # wavefront's distances outgrow its staged values by an odd number of words
