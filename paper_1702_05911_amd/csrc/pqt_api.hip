@@ -125,9 +125,9 @@ int rerank_runs_in_lds(const pqt_index* ix) {
 // gain by the head pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at
 // 67: 85 and 114, at 90: 109 and 131; T = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536.
 // Codes that are not one byte per sub-part read as words leave the re-rank kernel more to do, behind which the ranking inside it
-// hides: with the head pass and without, M = 32 pairs, 1,200 queries at 60: 108 and 134, at 110: 181 and 174; 10,000 at 60: 639
-// and 713, at 80: 834 and 804; M = 6 pairs 2,040 at 60: 59 and 65, 10,000 at 110: 382 and 370; M = 64 4,000 at 60: 327 and 358,
-// at 80: 421 and 409.  One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
+// hides: with the head pass and without, M = 32 pairs, 1,200 queries at 60: 99 and 123, at 90: 138 and 131; 10,000 at 60: 593
+// and 655, at 90: 883 and 783; M = 8 pairs 2,000 at 70: 79 and 76, 4,000 at 90: 131 and 125, 10,000 at 90: 241 and 260, at 110: 308
+// and 278; M = 64 table codes 4,000 at 60: 327 and 358, at 80: 421 and 409.  One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
 // 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233.
 // (These are times of three launches.  Up to 1,024 queries mostly take one, and come here with stage times or intermediate results asked
 // for, with more than 256 entries a list, or where one launch does not fit or does not pay.)
@@ -174,8 +174,9 @@ int check_query_limits(const pqt_index* ix, int k, int w, int64_t nq, size_t* ld
     const size_t l1 = pqt::traverse_lds_bytes(ix->D, ix->P, ix->k1, ix->k2, ix->M, w);
     const size_t l2 = pqt::rank_lds_bytes(ix->P, R, ix->T, ix->hashed ? 1 : 2);   // 2: room for the slots tap
     const int threads = rerank_threads(ix, nullptr, nq);
-    const size_t l3 = pqt::rerank_lds_bytes(ix->M, ix->k1, ix->T, ix->C, k, threads, 0, (int)ix->code_format,
-                                            rerank_runs_in_lds(ix));
+    size_t l3 = pqt::rerank_lds_bytes(ix->M, ix->k1, ix->T, ix->C, k, threads, 0, (int)ix->code_format,
+                                      rerank_runs_in_lds(ix));
+    if (ix->code_format == PQT_CODES_PAIR_LAMBDA) l3 += pqt::rerank_pair_reserve(ix->M, ix->k1);
     if (l1 > ix->lds_limit || l2 > ix->lds_limit || l3 > ix->lds_limit)
         return fail(PQT_EUNSUPPORTED,
                     "LDS budget exceeded (traverse %zu, rank %zu, rerank %zu bytes of %zu) for D=%u M=%u k1=%u R=%d T=%u C=%u",

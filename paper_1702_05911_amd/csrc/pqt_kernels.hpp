@@ -145,7 +145,7 @@ struct RerankArgs {
     int code_format;          // 0: codes are entries of the table, one byte per sub-part;
                               // 1: two bytes per sub-part, (centroid pair, lambda level); the table is then
                               //    indexed by pair number and its kc field holds ||c_i - c_j||^2
-    int pair_shift;           // code format 1: log2 of the LDS table's entries per sub-part (set by launch_rerank)
+    int pair_stride;          // code format 1: the LDS table's entries per sub-part (set by launch_rerank)
     int runs_in_lds;          // runs of a query the workgroup keeps in LDS (at least 64, at most T); a longer list
                               // is read from memory past that.  Sized from the index's mean run length so that
                               // the common case fits without spending LDS (and thus resident queries) on it.
@@ -174,6 +174,7 @@ struct RerankArgs {
 // rank_lds: LDS bytes of the full ranking pass when the kernel also runs it (0: it does not)
 size_t rerank_lds_bytes(int M, int k1, int T, int C, int k, int threads, size_t rank_lds, int code_format,
                         int runs_in_lds);
+size_t rerank_pair_reserve(int M, int k1);
 // tuples per thread the in-kernel ranking can hold: fusing needs min(T, R^2) <= that * threads
 int rerank_fused_tuples_per_thread();
 // workgroup size and candidates per thread of the re-rank kernel for a candidate budget C

@@ -21,8 +21,8 @@ static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, 
     L.rcap = T < want ? T : want;
     size_t o = 0;
     // at offset 0: lookups need no base register.
-    // One float per table entry, or (b^2, a^2 - b^2, c^2, -) per centroid pair for (pair, lambda) codes.
-    L.lut = (uint32_t)o;       o += code_format == 1 ? sizeof(float4) * ((size_t)M << pair_table_shift(k1)) : sizeof(float) * M * 256;
+    // One float per table entry, or (b^2, a^2 - b^2) and c^2 per centroid pair for (pair, lambda) codes.
+    L.lut = (uint32_t)o;       o += code_format == 1 ? 3 * sizeof(float) * (size_t)M * pair_table_stride(k1) : sizeof(float) * M * 256;
     // the survivors are collected when the last score is known: they take the table's place
     L.surv = 0;                o = std::max(o, sizeof(unsigned long long) * (size_t)L.scap);
     L.hist = (uint32_t)o;      o += sizeof(uint32_t) * kHistSize;
@@ -44,6 +44,12 @@ size_t rerank_lds_bytes(int M, int k1, int T, int C, int k, int threads, size_t 
     return rerank_layout(M, k1, T, C, k, threads, rank_lds, code_format, runs_in_lds).total;
 }
 
+// The limit of (pair, lambda) codes is a table of 16 bytes an entry, 128 or 256 of them a sub-part; the table takes less.
+size_t rerank_pair_reserve(int M, int k1) {
+    const size_t limit = 16 * (size_t)M * (k1 * (k1 - 1) / 2 <= 128 ? 128 : 256), table = 3 * sizeof(float) * (size_t)M * pair_table_stride(k1);
+    return limit - table;
+}
+
 void rerank_shape(int C, int M, int code_format, int* threads, int* keys_per_thread) {
     int t = 256;
     while (t < 1024 && C > kKeysPerThread * t) t *= 2;
@@ -58,7 +64,7 @@ int rerank_fused_tuples_per_thread() { return kFusedPer; }
 hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStream_t s) {
     if (a_in.nq <= 0) return hipSuccess;
     RerankArgs a = a_in;
-    a.pair_shift = pair_table_shift(a.k1);
+    a.pair_stride = pair_table_stride(a.k1);
     const bool taps = a.n_cand || a.cand_ids || a.scores || a.lut;
     RankArgs rk = {};
     RankOffsets RL = {};
@@ -82,11 +88,11 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
     if (a.code_format == 1) {
         // word-wise variants for the plain entry point; the tapped one takes the byte-wise kernel
         // Codes of six and sixteen words take 128 registers, so that one workgroup of 1,024 threads fits a compute unit and two of
-        // the byte-wise kernel do: more queries than compute units in such workgroups go there.  300 and 1,000 queries, M = 32, 600
-        // candidates: 46 and 76 us by words, 37 and 54 by bytes; 4,096: 88 and 149, 80 and 130; M = 12, 1,600: 50 and 80, 46 and
-        // 70; 100 queries, M = 32, 10,000: 82 and 85; 4,000 queries (smaller workgroups), 4,096: 462 and 521.  (Batches of 257 to 1,024
-        // queries come here where they are not answered in one launch.)
-        const bool by_bytes = a.threads == 1024 && a.nq > 256 && (a.M == 12 || a.M == 32);
+        // the byte-wise kernel do: more queries than compute units in such workgroups go there, those of sixteen words only with few
+        // candidates.  700 and 1,000 queries by words and by bytes, M = 12: 3,001 candidates 69 and 83 us, 64 and 73, 6,000 80 and 98, 73 and
+        // 84; M = 32: 1,600 candidates 63 and 77, 62 and 67, 4,096 95 and 117, 130 and 151, 9,000 141 and 178, 191 and 249.  (Batches of
+        // 257 to 1,024 queries come here where they are not answered in one launch.)
+        const bool by_bytes = a.threads == 1024 && a.nq > 256 && (a.M == 12 || (a.M == 32 && a.C <= 2048));
         switch (taps || by_bytes || a.M % 2 ? 0 : a.M / 2) {
             case 2: return launch_rerank_pair2(a, L, rk, RL, taps, f, s);
             case 4: return launch_rerank_pair4(a, L, rk, RL, taps, f, s);
@@ -138,7 +144,7 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
                               size_t room, hipStream_t s) {
     if (a_in.nq <= 0) return hipSuccess;
     RerankArgs a = a_in;
-    a.pair_shift = pair_table_shift(a.k1);
+    a.pair_stride = pair_table_stride(a.k1);
     a.early = 0;
     RankOffsets RL;
     RerankLds L;

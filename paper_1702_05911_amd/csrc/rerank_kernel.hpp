@@ -267,13 +267,23 @@ struct MarkedRuns {
 // How a wavefront finds its candidates' places (RUNS of score_batch)
 enum { kSearchRuns, kWalkRuns, kMarkRuns };
 
-// (pair, lambda level) codes: the summand of Eq. 9 for one sub-part from the pair's LDS entry
-// (b^2, a^2 - b^2, c^2) and the level; lambda = (level - 96) / 16 is exact in fp32.
+// (pair, lambda level) codes: the summand of Eq. 9 for one sub-part from the pair's LDS entries, (b^2, a^2 - b^2) of all sub-parts and
+// behind them c^2, and the level; lambda = (level - 96) / 16 is exact in fp32.  A read of 8 bytes and one of 4: the pairs of a
+// wavefront are as good as random, and one read of 16 (with a fourth word unused) waits for bank conflicts about as long as both
+// together, its table twice; a sub-part has as many entries as there are pairs, not the next power of two (3,217 queries x 3,001
+// candidates, 190 pairs, M = 12: the kernel 142 -> 88 us; 4 workgroups a compute unit instead of 3).
 constexpr int kPairLambda = -1;      // MW < 0 selects this code format: -1 any M (byte loads), else -(words per code)
-__device__ __forceinline__ float pair_lambda_term(const float4* plut, int shift, int m, uint32_t pair, uint32_t level) {
-    const float4 e = plut[(m << shift) + pair];
+typedef float pair_ends __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const pair_ends lds_cends;
+__device__ __forceinline__ float pair_lambda_term(int M, int stride, int m, uint32_t pair, uint32_t level) {
+    const pair_ends e = *reinterpret_cast<lds_cends*>((uintptr_t)(pair * 8u + (uint32_t)(m * stride * 8)));     // (the table lies at address 0)
+    const float c2 = *reinterpret_cast<lds_cfloat*>((uintptr_t)(pair * 4u + (uint32_t)(M * stride * 8 + m * stride * 4)));
     const float lam = fmaf((float)level, 0.0625f, -6.0f);
-    return fmaf(fmaf(lam, lam, -lam), e.z, fmaf(lam, e.y, e.x));
+    return fmaf(fmaf(lam, lam, -lam), c2, fmaf(lam, e.y, e.x));
+}
+__device__ __forceinline__ void put_pair(float* lut, int M, int stride, int m, int pair, float b2, float d2, float c2) {
+    reinterpret_cast<float2*>(lut)[m * stride + pair] = make_float2(b2, d2);
+    lut[(2 * M + m) * stride + pair] = c2;
 }
 
 // Scores U candidate positions per thread (wb + u * 64 + lane: a wavefront walks its own contiguous
@@ -369,19 +379,18 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
             }
         } else if (MW < -1) {
             // two bytes per sub-part, two sub-parts per word
-            const float4* plut = reinterpret_cast<const float4*>(lut);
             s = 0.0f;
 #pragma unroll
             for (int j = 0; j < NW; ++j) {
                 const uint32_t wv = cw[u][j];
-                s += pair_lambda_term(plut, g.pair_shift, 2 * j, wv & 0xffu, (wv >> 8) & 0xffu);
-                s += pair_lambda_term(plut, g.pair_shift, 2 * j + 1, (wv >> 16) & 0xffu, wv >> 24);
+                s += pair_lambda_term(M, g.pair_stride, 2 * j, wv & 0xffu, (wv >> 8) & 0xffu);
+                s += pair_lambda_term(M, g.pair_stride, 2 * j + 1, (wv >> 16) & 0xffu, wv >> 24);
             }
         } else if (MW == kPairLambda) {
-            const float4* plut = reinterpret_cast<const float4*>(lut);
-            const uint8_t* code = g.codes + (size_t)src[u] * 2 * M;
+            const uint16_t* code = reinterpret_cast<const uint16_t*>(g.codes) + (size_t)src[u] * M;
             s = 0.0f;
-            for (int m = 0; m < M; ++m) s += pair_lambda_term(plut, g.pair_shift, m, code[2 * m], code[2 * m + 1]);
+#pragma unroll 4
+            for (int m = 0; m < M; ++m) s += pair_lambda_term(M, g.pair_stride, m, code[m] & 0xffu, code[m] >> 8);
         } else {
             const uint8_t* code = g.codes + (size_t)src[u] * M;
             s = 0.0f;
@@ -478,8 +487,7 @@ __device__ __forceinline__ void rerank_query(const RerankArgs g, const RerankLds
         const float a2 = sam[(ce.ij >> 8) & 0xffu];
         if (MW < 0) {
             // entry = centroid pair number; its kc field holds c^2
-            if (lut_c < (1 << g.pair_shift))
-                reinterpret_cast<float4*>(lut)[(m << g.pair_shift) + lut_c] = make_float4(b2, a2 - b2, ce.kc, 0.0f);
+            if (lut_c < g.pair_stride) put_pair(lut, Mlut, g.pair_stride, m, lut_c, b2, a2 - b2, ce.kc);
             return;
         }
         // Eq. 9 rearranged: b^2 + lam (a^2 - b^2) + (lam^2 - lam) c^2, the last term folded per code value
@@ -920,22 +928,23 @@ __device__ __forceinline__ void prepare_table(const RerankArgs& g, const RerankL
     const float* sa = reinterpret_cast<const float*>(smem + L.a);
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + L.hist);
     const int who = (int)threadIdx.x - first, n = (int)blockDim.x - first;
-    const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M), shift = MW < 0 ? g.pair_shift : 8, entries = M << shift;
+    const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M), per = MW < 0 ? g.pair_stride : 256, entries = M * per;
     constexpr int U = 4;                       // entries asked for together
     for (int e0 = who; e0 < entries; e0 += U * n) {
         CodeEntry ent[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = min(e0 + u * n, entries - 1);
-            ent[u] = g.table[(e >> shift) * 256 + (e & ((1 << shift) - 1))];
+            const int e = min(e0 + u * n, entries - 1), m = e / per;
+            ent[u] = g.table[m * 256 + (e - m * per)];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * n;
             if (e >= entries) break;
-            const float* sam = sa + (e >> shift) * g.k1;
+            const int m = e / per;
+            const float* sam = sa + m * g.k1;
             const float b2 = sam[ent[u].ij & 0xffu], a2 = sam[(ent[u].ij >> 8) & 0xffu];
-            if (MW < 0) reinterpret_cast<float4*>(lut)[e] = make_float4(b2, a2 - b2, ent[u].kc, 0.0f);
+            if (MW < 0) put_pair(lut, M, per, m, e - m * per, b2, a2 - b2, ent[u].kc);
             else lut[e] = fmaf(ent[u].lam, a2 - b2, b2) + ent[u].kc;
         }
     }

@@ -51,6 +51,6 @@ constexpr int kKeysPerThread = 20;   // candidates a thread scores; C <= kKeysPe
 constexpr int kRunsInLdsMin = 64;    // at least this many runs of a query are kept in LDS (see RerankArgs::runs_in_lds)
 
 // (pair, lambda) codes: entries per sub-part in the LDS table of centroid pairs (128 while the pairs fit)
-inline int pair_table_shift(int k1) { return k1 * (k1 - 1) / 2 <= 128 ? 7 : 8; }
+inline int pair_table_stride(int k1) { return k1 < 3 ? 2 : (k1 * (k1 - 1) / 2 + 1) & ~1; }
 
 }  // namespace pqt
