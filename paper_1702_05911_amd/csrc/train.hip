@@ -11,7 +11,6 @@
 // hardware schedules work: assignments break ties by the smaller centroid number, cell sums are taken
 // over the members in ascending vector order in fixed chunks (double precision), re-seeding takes the
 // farthest vector with the smallest number.
-#include <hipcub/hipcub.hpp>
 
 #include <algorithm>
 #include <cmath>
@@ -596,7 +595,7 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
 
 // ---- members of every part's cells, in ascending vector order ---------------------------------------------------------
 // A count per piece of `rows` labels and cell, a prefix sum over (cell, piece), and every vector goes to its place: three short
-// kernels (100,000 vectors, two parts: 9 us; a library sort of (label, vector) pairs per part took 100).
+// kernels (100,000 vectors, two parts: 14 us; a library sort of (label, vector) pairs per part took 100).
 constexpr int kCellThreads = 1024;
 constexpr int kCellWaves = kCellThreads / kWave;
 
@@ -678,26 +677,92 @@ __global__ void whole_range_kernel(uint32_t n, int P, uint2* range) {
     if ((int)threadIdx.x < P) range[threadIdx.x] = make_uint2(0u, n);
 }
 
-// first[m][q] = where line q's votes start among the sorted votes of sub-part m (m counted within the batch), q = 0..npairs
-__global__ void line_ranges_kernel(const unsigned long long* sorted, uint32_t nt, int m0, int m1, uint32_t npairs, uint32_t* first) {
-    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t per = (uint64_t)npairs + 1;
-    if (e >= (uint64_t)(m1 - m0) * per) return;
-    const int m = (int)(e / per);
-    const unsigned long long want = ((unsigned long long)(m0 + m) << 48) | ((unsigned long long)(e % per) << 32);
-    const unsigned long long* s = sorted + (size_t)m * nt;
-    uint32_t lo = 0, hi = nt;
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (s[mid] < want) lo = mid + 1; else hi = mid;
+// ---- the lambdas of every line's votes, and those at given ranks -----------------------------------------------------
+// Only a few ranks of a line are wanted, so its votes are brought together but not sorted: counts per line, a place for every vote,
+// and a radix select per code point (100,000 vectors x 8 sub-parts: 12, 6 and 19 us; a library sort of all votes took 160).  A workgroup of the
+// first two takes kCellThreads votes of one sub-part; up to kLdsLines lines it counts in LDS and adds up or reserves once per line.
+constexpr int kLdsLines = 8192;
+
+__device__ __forceinline__ int vote_line(unsigned long long key) { return (int)((key >> 32) & 0xffffu); }
+
+// counts[m][line]; votes without a line (number 0xffff) are not counted
+__global__ __launch_bounds__(kCellThreads) void vote_counts_kernel(const unsigned long long* keys, uint32_t nt, int lines, uint32_t* counts) {
+    extern __shared__ uint32_t cnt[];
+    const int m = blockIdx.y, tid = threadIdx.x;
+    const uint32_t v = blockIdx.x * kCellThreads + tid;
+    const int line = v < nt ? vote_line(keys[(size_t)m * nt + v]) : 0xffff;
+    uint32_t* out = counts + (size_t)m * lines;
+    if (lines > kLdsLines) {
+        if (line < lines) atomicAdd(&out[line], 1u);
+        return;
     }
-    first[e] = lo;
+    for (int j = tid; j < lines; j += kCellThreads) cnt[j] = 0u;
+    __syncthreads();
+    if (line < lines) atomicAdd(&cnt[line], 1u);
+    __syncthreads();
+    for (int j = tid; j < lines; j += kCellThreads)
+        if (cnt[j]) atomicAdd(&out[j], cnt[j]);
 }
 
-// lam[e] = the lambda of sorted vote at[e] (the votes of sub-part e / 256 of the batch)
-__global__ void pick_votes_kernel(const unsigned long long* sorted, uint32_t nt, const uint32_t* at, int n, float* lam) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) lam[e] = mono_inv((uint32_t)sorted[(size_t)(e / 256) * nt + at[e]]);
+// lam[m][next[m][line] ...]: the ordered bits of the line's lambdas, in any order; next: the line's first place at the start
+__global__ __launch_bounds__(kCellThreads) void vote_groups_kernel(const unsigned long long* keys, uint32_t nt, int lines, uint32_t* next, uint32_t* lam) {
+    extern __shared__ uint32_t cnt[];
+    const int m = blockIdx.y, tid = threadIdx.x;
+    const uint32_t v = blockIdx.x * kCellThreads + tid;
+    const unsigned long long key = v < nt ? keys[(size_t)m * nt + v] : ~0ull;
+    const int line = vote_line(key);
+    uint32_t* places = next + (size_t)m * lines;
+    uint32_t at = 0u;
+    if (lines > kLdsLines) {
+        if (line < lines) at = atomicAdd(&places[line], 1u);
+    } else {
+        for (int j = tid; j < lines; j += kCellThreads) cnt[j] = 0u;
+        __syncthreads();
+        uint32_t mine = 0u;
+        if (line < lines) mine = atomicAdd(&cnt[line], 1u);
+        __syncthreads();
+        for (int j = tid; j < lines; j += kCellThreads)
+            if (cnt[j]) cnt[j] = atomicAdd(&places[j], cnt[j]);
+        __syncthreads();
+        if (line < lines) at = cnt[line] + mine;
+    }
+    if (line < lines) lam[(size_t)m * nt + at] = (uint32_t)key;
+}
+
+// out[e] = the value of rank `rank` (from 0) among the n lambdas at `first` of sub-part e / 256; pick = (first, n, rank), n = 0: nothing.
+// One workgroup per code point: eight bits a pass, the highest first.
+__global__ __launch_bounds__(256) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, const uint4* picks, float* out) {
+    __shared__ uint32_t hist[256], part[256 / kWave], found[2];
+    const int tid = threadIdx.x;
+    const uint4 pick = picks[blockIdx.x];
+    if (pick.y == 0u) return;
+    const uint32_t* x = lam + (size_t)(blockIdx.x / 256) * nt + pick.x;
+    uint32_t prefix = 0u, mask = 0u, rank = pick.z;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        hist[tid] = 0u;
+        __syncthreads();
+        for (uint32_t e = tid; e < pick.y; e += 256) {
+            const uint32_t key = x[e];
+            if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 0xffu], 1u);
+        }
+        __syncthreads();
+        uint32_t total;
+        const uint32_t cnt = hist[tid], before = block_exclusive_sum(cnt, part, total);
+        if (before <= rank && rank < before + cnt) {
+            found[0] = (uint32_t)tid;
+            found[1] = rank - before;
+        }
+        __syncthreads();
+        prefix |= found[0] << shift;
+        mask |= 0xffu << shift;
+        rank = found[1];
+    }
+    if (tid == 0) out[blockIdx.x] = mono_inv(prefix);
+}
+
+__global__ void clear_counts_kernel(uint32_t* out, size_t n) {
+    const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < n) out[e] = 0u;
 }
 
 // Everything pqt_train holds on the GPU: asked for first, then one allocation.
@@ -718,12 +783,6 @@ struct Arena {
         return e;
     }
 };
-
-int log2_ceil(uint32_t v) {
-    int b = 1;
-    while (b < 32 && (1ull << b) < v) ++b;
-    return b;
-}
 
 // Centroids a thread of lloyd_step_kernel works on at a time: a multiple of eight, at most 32 (its running distances are
 // registers), so that the rounds over k leave less than eight of them unused each.
@@ -898,7 +957,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     uint4* chunks = nullptr;
     float* dmin = nullptr;
     uint2 *range1 = nullptr, *range2 = nullptr;
-    unsigned char* sort_temp = nullptr;
+    
     mem.want(&sums, (size_t)std::max(limit1 * k1, limit2 * k2) * dp);
     mem.want(&counts, (size_t)std::max(limit1 * k1, limit2 * k2));
     mem.want(&label, (size_t)P * n);
@@ -915,24 +974,19 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     mem.want(&l1.cenI, (size_t)P * nd4 * l1.kp * 4);
     mem.want(&l2.cen, (size_t)P * cells2 * dp);
     mem.want(&l2.cenI, (size_t)P * k1 * nd4 * l2.kp * 4);
-    // the line table: the votes of as many sub-parts as fit 2^27 keys are sorted together
     LinePair* pair_dev = nullptr;
     float *c1n_dev = nullptr, *lam_dev = nullptr;
-    unsigned long long *keys = nullptr, *keys_sorted = nullptr;
-    uint32_t *first_dev = nullptr, *at_dev = nullptr;
-    const uint32_t batch = nt ? std::min<uint32_t>(M, std::max<uint32_t>(1, (1u << 27) / nt)) : 0u;
-    const int key_bits = 48 + log2_ceil(M);
-    size_t sort_bytes = 0;
+    unsigned long long* keys = nullptr;
+    uint32_t *lines_dev = nullptr, *lam_keys = nullptr;
+    uint4* picks_dev = nullptr;
     if (nt) {
-        HIP_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, keys, keys_sorted, (int)(batch * nt), 0, key_bits, st));
-        mem.want(&sort_temp, sort_bytes);
         mem.want(&pair_dev, (size_t)M * npairs);
         mem.want(&c1n_dev, (size_t)M * k1);
         mem.want(&keys, (size_t)M * nt);
-        mem.want(&keys_sorted, (size_t)batch * nt);
-        mem.want(&first_dev, (size_t)batch * (npairs + 1));
-        mem.want(&at_dev, (size_t)batch * 256);
-        mem.want(&lam_dev, (size_t)batch * 256);
+        mem.want(&lam_keys, (size_t)M * nt);
+        mem.want(&lines_dev, (size_t)M * npairs);
+        mem.want(&picks_dev, (size_t)M * 256);
+        mem.want(&lam_dev, (size_t)M * 256);
     }
     HIP_TRY(mem.allocate());
     l1.range = range1; l2.range = range2;
@@ -942,16 +996,17 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     l1.sums = l2.sums = sums; l1.counts = l2.counts = counts; l1.dmin = l2.dmin = dmin;
     std::vector<float> C1, C2, cc;
     std::vector<LinePair> pair_host;
-    std::vector<uint32_t> first, at;
+    std::vector<uint32_t> first;
+    std::vector<uint4> picks;
     std::vector<float> lam;
     try {
         C1.resize((size_t)P * k1 * dp);
         C2.resize((size_t)P * cells2 * dp);
         cc.resize((size_t)M * k1 * k1);
         pair_host.resize(nt ? (size_t)M * npairs : 0);
-        first.resize((size_t)batch * (npairs + 1));
-        at.resize((size_t)batch * 256);
-        lam.resize((size_t)batch * 256);
+        first.resize(nt ? (size_t)M * npairs : 0);
+        picks.resize(nt ? (size_t)M * 256 : 0, make_uint4(0u, 0u, 0u, 0u));
+        lam.resize(nt ? (size_t)M * 256 : 0);
     } catch (const std::bad_alloc&) {
         return fail(PQT_ENOMEM, "host allocation failed");
     }
@@ -1012,51 +1067,49 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     pa.C1 = l1.cen; pa.c1n = c1n_dev; pa.pairs = pair_dev; pa.npairs = (int)npairs; pa.keys = keys;
     HIP_TRY(launch_subpart_norms(l1.cen, (int)D, (int)P, (int)k1, (int)M, c1n_dev, st));
     HIP_TRY(launch_votes(pa, st));
-    for (uint32_t m0 = 0; m0 < M; m0 += batch) {
-        const uint32_t m1 = std::min(M, m0 + batch);
-        HIP_TRY(hipcub::DeviceRadixSort::SortKeys(sort_temp, sort_bytes, keys + (size_t)m0 * nt, keys_sorted, (int)((m1 - m0) * nt), 0,
-                                                  key_bits, st));
-        const size_t nfirst = (size_t)(m1 - m0) * (npairs + 1);
-        hipLaunchKernelGGL(line_ranges_kernel, dim3((unsigned)((nfirst + tb - 1) / tb)), dim3(tb), 0, st, keys_sorted, nt, (int)m0, (int)m1,
-                           npairs, first_dev);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(first.data(), first_dev, nfirst * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        // a line's code points sit at the (t + 1/2) / alloc quantiles of its lambdas; lines in pair order and
-        // lambdas ascending, so the entries come out ordered by (i, j, lambda)
-        for (uint32_t m = m0; m < m1; ++m) {
-            const uint32_t* fm = first.data() + (size_t)(m - m0) * (npairs + 1);
-            uint32_t* am = at.data() + (size_t)(m - m0) * 256;
-            std::fill(am, am + 256, 0u);
-            const uint64_t total = fm[npairs];               // sub-vectors without a usable line sort last
-            if (total == 0) continue;
-            std::vector<uint64_t> use(npairs);
-            for (uint32_t q = 0; q < npairs; ++q) use[q] = fm[q + 1] - fm[q];
-            const std::vector<uint32_t> alloc = share_out(use, total, 256);
-            uint32_t c = 0;
-            for (uint32_t q = 0; q < npairs && c < 256; ++q)
-                for (uint32_t t = 0; t < alloc[q] && c < 256; ++t, ++c) {
-                    uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
-                    if (pos >= use[q]) pos = use[q] - 1;
-                    am[c] = fm[q] + (uint32_t)pos;
-                    tbl_i[(size_t)m * 256 + c] = (uint8_t)pair_host[q].ij;
-                    tbl_j[(size_t)m * 256 + c] = (uint8_t)(pair_host[q].ij >> 16);
-                }
-            for (; c > 0 && c < 256; ++c) {                  // (cannot happen when total > 0; kept total)
-                am[c] = am[c - 1];
-                tbl_i[(size_t)m * 256 + c] = tbl_i[(size_t)m * 256 + c - 1];
-                tbl_j[(size_t)m * 256 + c] = tbl_j[(size_t)m * 256 + c - 1];
-            }
+    const dim3 by_vote((nt + kCellThreads - 1) / kCellThreads, M);
+    const size_t nlines = (size_t)M * npairs, lines_lds = npairs <= kLdsLines ? sizeof(uint32_t) * npairs : 0;
+    hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)((nlines + tb - 1) / tb)), dim3(tb), 0, st, lines_dev, nlines);
+    hipLaunchKernelGGL(vote_counts_kernel, by_vote, dim3(kCellThreads), lines_lds, st, keys, nt, (int)npairs, lines_dev);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(first.data(), lines_dev, nlines * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    // a line's code points sit at the (t + 1/2) / alloc quantiles of its lambdas; lines in pair order and
+    // lambdas ascending, so the entries come out ordered by (i, j, lambda)
+    for (uint32_t m = 0; m < M; ++m) {
+        uint32_t* fm = first.data() + (size_t)m * npairs;    // counts, then first places
+        uint4* pick = picks.data() + (size_t)m * 256;
+        std::vector<uint64_t> use(fm, fm + npairs);
+        uint64_t total = 0;
+        for (uint32_t q = 0; q < npairs; ++q) {
+            fm[q] = (uint32_t)total;
+            total += use[q];
         }
-        const int npick = (int)(m1 - m0) * 256;
-        HIP_TRY(hipMemcpyAsync(at_dev, at.data(), sizeof(uint32_t) * npick, hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(pick_votes_kernel, dim3((unsigned)((npick + tb - 1) / tb)), dim3(tb), 0, st, keys_sorted, nt, at_dev, npick, lam_dev);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(lam.data(), lam_dev, sizeof(float) * npick, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        for (uint32_t m = m0; m < m1; ++m)
-            if (first[(size_t)(m - m0) * (npairs + 1) + npairs] > 0)
-                memcpy(tbl_lambda + (size_t)m * 256, lam.data() + (size_t)(m - m0) * 256, 256 * sizeof(float));
+        if (total == 0) continue;                            // (no sub-vector has a usable line)
+        const std::vector<uint32_t> alloc = share_out(use, total, 256);
+        uint32_t c = 0;
+        for (uint32_t q = 0; q < npairs && c < 256; ++q)
+            for (uint32_t t = 0; t < alloc[q] && c < 256; ++t, ++c) {
+                uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
+                if (pos >= use[q]) pos = use[q] - 1;
+                pick[c] = make_uint4(fm[q], (uint32_t)use[q], (uint32_t)pos, 0u);
+                tbl_i[(size_t)m * 256 + c] = (uint8_t)pair_host[(size_t)m * npairs + q].ij;
+                tbl_j[(size_t)m * 256 + c] = (uint8_t)(pair_host[(size_t)m * npairs + q].ij >> 16);
+            }
+        for (; c > 0 && c < 256; ++c) {                      // (cannot happen when total > 0; kept total)
+            pick[c] = pick[c - 1];
+            tbl_i[(size_t)m * 256 + c] = tbl_i[(size_t)m * 256 + c - 1];
+            tbl_j[(size_t)m * 256 + c] = tbl_j[(size_t)m * 256 + c - 1];
+        }
     }
+    HIP_TRY(hipMemcpyAsync(lines_dev, first.data(), nlines * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(picks_dev, picks.data(), picks.size() * sizeof(uint4), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(vote_groups_kernel, by_vote, dim3(kCellThreads), lines_lds, st, keys, nt, (int)npairs, lines_dev, lam_keys);
+    hipLaunchKernelGGL(pick_lambdas_kernel, dim3(M * 256), dim3(256), 0, st, lam_keys, nt, picks_dev, lam_dev);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(lam.data(), lam_dev, lam.size() * sizeof(float), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    for (size_t e = 0; e < lam.size(); ++e)
+        if (picks[e].y > 0) tbl_lambda[e] = lam[e];
     return PQT_OK;
 }

@@ -1076,6 +1076,42 @@ def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
             np.testing.assert_allclose(got["C2"][p, i], want, rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("n, D, k1, M", [(1, 8, 3, 2), (4097, 8, 5, 2), (1024, 48, 24, 8), (3000, 36, 140, 3)])
+def test_line_table_lambdas(pqt, n, D, k1, M):
+    """The lambdas of the line table are those at the (t + 1/2) / alloc quantiles of what was voted on the line, which is not
+    sorted for them: one vote, a vote more than whole workgroups, and (140 centroids) more lines than are counted on the
+    chip.  Distances of whole numbers are exact, a lambda is their quotient rounded (2^-23 at most); an error of a line rounds by
+    2^-22 of b^2 + lambda^2 c^2.  Vectors nearer to a tie than that (the centroids are vectors themselves, and lie on many lines) may
+    or may not have voted on a line: its value of some rank is at least that of all who may and at most that of those who must."""
+    import torch
+    rng = np.random.default_rng(23)
+    X = rng.integers(0, 64, (n, D)).astype(np.float32)
+    got = pqt.pqt_train(torch.from_numpy(X).cuda(), P=1, k1=k1, k2=1, M=M, iters=0, n_table=n)
+    pairs, ds = np.array(Q.centroid_pairs(k1)), D // M
+    for m in range(M):
+        cen = B.subpart_centroids(got["C1"], M, m).astype(np.float64)
+        d = B.sqdist_matrix(X[:, m * ds:(m + 1) * ds].astype(np.float64), cen)
+        b2, a2 = d[:, pairs[:, 0]], d[:, pairs[:, 1]]
+        c2 = B.sqdist_matrix(cen, cen)[pairs[:, 0], pairs[:, 1]]
+        with np.errstate(divide="ignore", invalid="ignore"):
+            lam = (b2 - a2 + c2) / (2.0 * c2)
+        usable = c2 > 0
+        err = np.where(usable, b2 - lam * lam * c2, np.inf)
+        near = err <= err.min(axis=1, keepdims=True) + 2.0 ** -21 * np.where(usable, b2 + lam * lam * c2, 0.0).max(axis=1, keepdims=True)
+        near &= usable
+        ti, tj, tl = (got[a][m] for a in ("tbl_i", "tbl_j", "tbl_lam"))
+        for q, (i, j) in enumerate(pairs):
+            mine = tl[(ti == i) & (tj == j)]
+            if mine.size == 0:
+                continue
+            may, must = np.sort(lam[near[:, q], q]), np.sort(lam[near[:, q] & (near.sum(axis=1) == 1), q])
+            rank = [np.minimum((2 * np.arange(mine.size) + 1) * v.size // (2 * mine.size), v.size - 1) for v in (must, may)]
+            low = may[np.maximum(rank[0], 0)]
+            high = np.where(rank[1] < must.size, np.append(must, np.inf)[np.minimum(rank[1], must.size)], may[-1])
+            slack = 2.0 ** -22 * (1.0 + np.abs(mine))
+            assert np.all(mine >= low - slack) and np.all(mine <= high + slack), (m, i, j)
+
+
 @pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8),
                                             (300, 32, 2, 33, 4), (130, 80, 2, 70, 2), (700, 24, 1, 130, 8), (600, 16, 2, 256, 4)])
 def test_line_table_edges(pqt, n, D, P, k1, M):
