@@ -362,8 +362,9 @@ __global__ __launch_bounds__(kTrainThreads, 4) void lloyd_tile_kernel(LloydArgs 
     uint32_t* rows = reinterpret_cast<uint32_t*>(smem + L.row);
     uint8_t* list = smem + L.list + wave * kRows;
     // the vector of this thread's row of the tile at t0; what lies past the last one is read from there and not used
-    auto row_of = [&](uint32_t t0) {
-        const uint32_t at = min(t0 + (uint32_t)min(tid, kRows - 1), hi - 1);
+    // (64 bits: the last tile may end past 2^32)
+    auto row_of = [&](uint64_t t0) {
+        const uint32_t at = (uint32_t)min(t0 + (uint64_t)min(tid, kRows - 1), (uint64_t)hi - 1);
         return mem ? mem[at] : at;
     };
     uint32_t row = row_of(lo);
@@ -379,11 +380,11 @@ __global__ __launch_bounds__(kTrainThreads, 4) void lloyd_tile_kernel(LloydArgs 
     }
     const int v0 = wave * 16 * VR + (lane & 15), column = lane >> 4;
     const float4* xs = reinterpret_cast<const float4*>(sx) + v0 * st;
-    for (uint32_t t0 = lo; t0 < hi; t0 += (uint32_t)kRows) {
-        const int m = (int)min(hi - t0, (uint32_t)kRows);
+    for (uint64_t t0 = lo; t0 < hi; t0 += kRows) {
+        const int m = (int)min(hi - t0, (uint64_t)kRows);
         if (tid < kRows) rows[tid] = row;
         __syncthreads();                                     // (and the tile before is done with)
-        row = row_of(min(t0 + (uint32_t)kRows, hi - 1));
+        row = row_of(t0 + kRows);
         // piece e of the tile is piece e mod st of row e / st
         if (g.wide) {
             for (int u = wave; u < kRows * st / kWave; u += kTileWaves) {
@@ -741,7 +742,7 @@ __global__ __launch_bounds__(256) void pick_lambdas_kernel(const uint32_t* lam, 
     for (int shift = 24; shift >= 0; shift -= 8) {
         hist[tid] = 0u;
         __syncthreads();
-        for (uint32_t e = tid; e < pick.y; e += 256) {
+        for (uint64_t e = tid; e < pick.y; e += 256) {
             const uint32_t key = x[e];
             if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 0xffu], 1u);
         }
@@ -1067,7 +1068,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     pa.C1 = l1.cen; pa.c1n = c1n_dev; pa.pairs = pair_dev; pa.npairs = (int)npairs; pa.keys = keys;
     HIP_TRY(launch_subpart_norms(l1.cen, (int)D, (int)P, (int)k1, (int)M, c1n_dev, st));
     HIP_TRY(launch_votes(pa, st));
-    const dim3 by_vote((nt + kCellThreads - 1) / kCellThreads, M);
+    const dim3 by_vote((unsigned)(((uint64_t)nt + kCellThreads - 1) / kCellThreads), M);
     const size_t nlines = (size_t)M * npairs, lines_lds = npairs <= kLdsLines ? sizeof(uint32_t) * npairs : 0;
     hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)((nlines + tb - 1) / tb)), dim3(tb), 0, st, lines_dev, nlines);
     hipLaunchKernelGGL(vote_counts_kernel, by_vote, dim3(kCellThreads), lines_lds, st, keys, nt, (int)npairs, lines_dev);

@@ -757,6 +757,31 @@ def test_training_tile_edges(pqt, n, D, P, k1, k2):
         assert np.array_equal(got[name], again[name]), f"{name}: training is not deterministic"
 
 
+def test_training_most_vectors(pqt):
+    """The most training vectors (2^32 - 2): the last tile ends past 2^32.  Values 0 .. 15 but for a start centroid and the last
+    vector, which alone share a cell; sums are whole numbers below 2^53, so every mean is rounded once."""
+    import torch
+    n, far = (1 << 32) - 2, (4096.0, 8192.0)
+    free, _ = torch.cuda.mem_get_info()
+    if free < 80 << 30:
+        pytest.skip("needs 80 GB of GPU memory")
+    X = torch.empty((n, 1), dtype=torch.float32, device="cuda")
+    pattern = (torch.arange(1 << 26, device="cuda") % 16).to(torch.float32).view(-1, 1)
+    for s in range(0, n, 1 << 26):
+        X[s:s + (1 << 26)] = pattern[:n - s]
+    X[n // 2], X[n - 1] = far
+    # 2^28 of every value, but one 14 and one 15 less (i mod 16 ends with 13); two values are replaced
+    total = (1 << 28) * 120 - 14 - 15 - (n // 2) % 16 - (n - 1) % 16
+    want = np.array([[total / (n - 2)], [sum(far) / 2]]).astype(np.float32)
+    try:
+        got = pqt.pqt_train(X, P=1, k1=2, k2=1, M=1, iters=1, n_table=0)
+    finally:
+        del X, pattern
+        torch.cuda.empty_cache()
+    np.testing.assert_array_equal(got["C1"][0], want)
+    np.testing.assert_array_equal(got["C2"][0, :, 0], want)
+
+
 def test_pair_lambda_codes(pqt, tiny_pair, tmp_path):
     """Codes stored as (centroid pair, lambda level): stage-wise parity of the query path on an
     oracle-built index; the lut tap is refused; a pair byte beyond the last pair is a format error."""
