@@ -9,8 +9,8 @@ SOURCES = ("pqt_api.hip", "pqt_host.cpp", "traverse.hip", "rank_bins.hip", "rera
            # the re-rank kernel, one translation unit per code width (they compile side by side)
            "rerank_table2.hip", "rerank_table0.hip", "rerank_table1.hip", "rerank_table3.hip",
            "rerank_table4.hip", "rerank_table8.hip",
-           "rerank_pair_bytes.hip", "rerank_pair2.hip", "rerank_pair4.hip", "rerank_pair6.hip", "rerank_pair8.hip",
-           "rerank_pair16.hip",
+           "rerank_pair_bytes.hip", "rerank_pair_long.hip", "rerank_pair2.hip", "rerank_pair4.hip", "rerank_pair6.hip",
+           "rerank_pair8.hip", "rerank_pair16.hip",
            "exact_rerank.hip", "builder.hip", "place.hip", "train.hip", "brute_force.hip", "peaks.hip")
 OUTPUT = os.path.join(HERE, "libpqt.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

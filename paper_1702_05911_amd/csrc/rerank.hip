@@ -59,6 +59,11 @@ void rerank_shape(int C, int M, int code_format, int* threads, int* keys_per_thr
     *keys_per_thread = kKeysPerThread;
 }
 
+// (pair, lambda) codes of any length: four pieces at a time take registers, and with them half of the wavefronts.  10,000 queries, one
+// and four pieces, us: M = 24, 4 centroids, 1,831 candidates 202 and 291, 7,324 664 and 933; M = 28 253 and 332, 857 and 1,075; M = 36, 6
+// centroids, 813 candidates 228 and 268, 3,255 714 and 638, 6,510 1,221 and 1,065; M = 40, 4 centroids 378 and 376, 1,495 and 1,190.
+static bool long_pair_code(int M) { return M > 32; }
+
 int rerank_fused_tuples_per_thread() { return kFusedPer; }
 
 hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStream_t s) {
@@ -99,7 +104,9 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
             case 6: return launch_rerank_pair6(a, L, rk, RL, taps, f, s);
             case 8: return launch_rerank_pair8(a, L, rk, RL, taps, f, s);
             case 16: return launch_rerank_pair16(a, L, rk, RL, taps, f, s);
-            default: return launch_rerank_pair_bytes(a, L, rk, RL, taps, f, s);
+            default:
+                if (long_pair_code(a.M) && !taps) return launch_rerank_pair_long(a, L, rk, RL, taps, f, s);
+                return launch_rerank_pair_bytes(a, L, rk, RL, taps, f, s);
         }
     }
     switch ((a.M % 4 == 0) ? a.M / 4 : 0) {
@@ -166,7 +173,9 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
             case 6: return launch_query_pair6(a, L, rk, RL, tr, sm, s);
             case 8: return launch_query_pair8(a, L, rk, RL, tr, sm, s);
             case 16: return launch_query_pair16(a, L, rk, RL, tr, sm, s);
-            default: return launch_query_pair_bytes(a, L, rk, RL, tr, sm, s);
+            default:
+                if (long_pair_code(a.M)) return launch_query_pair_long(a, L, rk, RL, tr, sm, s);
+                return launch_query_pair_bytes(a, L, rk, RL, tr, sm, s);
         }
     }
     switch ((a.M % 4 == 0) ? a.M / 4 : 0) {
@@ -182,7 +191,7 @@ hipError_t launch_small_query(const RerankArgs& a_in, const RankArgs& rk, const 
 hipError_t configure_rerank(size_t max_dynamic_lds) {
     hipError_t (*const all[])(size_t) = {configure_rerank_table0, configure_rerank_table1, configure_rerank_table2,
                                          configure_rerank_table3, configure_rerank_table4, configure_rerank_table8,
-                                         configure_rerank_pair_bytes, configure_rerank_pair2, configure_rerank_pair4,
+                                         configure_rerank_pair_bytes, configure_rerank_pair_long, configure_rerank_pair2, configure_rerank_pair4,
                                          configure_rerank_pair6, configure_rerank_pair8, configure_rerank_pair16};
     for (auto fn : all) {
         const hipError_t e = fn(max_dynamic_lds);

@@ -272,7 +272,18 @@ enum { kSearchRuns, kWalkRuns, kMarkRuns };
 // wavefront are as good as random, and one read of 16 (with a fourth word unused) waits for bank conflicts about as long as both
 // together, its table twice; a sub-part has as many entries as there are pairs, not the next power of two (3,217 queries x 3,001
 // candidates, 190 pairs, M = 12: the kernel 142 -> 88 us; 4 workgroups a compute unit instead of 3).
-constexpr int kPairLambda = -1;      // MW < 0 selects this code format: -1 any M (byte loads), else -(words per code)
+// MW < 0 selects this code format: kPairLambda and kPairLong any M, else -(words per code).  Any M: a lane reads its candidate's code
+// in pieces of eight sub-parts, one at a time, of long codes four.  The cache lines of a lane's code have to last from its first load to its
+// last: with a load per sub-part and as many wavefronts as the small tables leave room for they are fetched again and again.  10,000
+// queries, 8 centroids, 7,324 candidates, ms, a load per sub-part, a piece, four pieces: M = 56 -, 3.7 and 1.7, M = 64 11.7, 5.6 and 1.7 (of
+// two bytes and one workgroup a compute unit, as long as a pair had 16 bytes: 3.2 and 3.5); 16 centroids, M = 24, 1,831 candidates
+// 0.52 and 0.47.
+constexpr int kPairLambda = -1, kPairLong = -64;
+constexpr int code_words(int MW) { return MW > 0 ? MW : (MW == kPairLambda || MW == kPairLong ? 0 : -MW); }     // 0: as many as M says
+template <int MW>
+__device__ __forceinline__ int code_parts(int M) {
+    return code_words(MW) == 0 ? M : (MW > 0 ? 4 : 2) * code_words(MW);
+}
 typedef float pair_ends __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) const pair_ends lds_cends;
 __device__ __forceinline__ float pair_lambda_term(int M, int stride, int m, uint32_t pair, uint32_t level) {
@@ -281,6 +292,7 @@ __device__ __forceinline__ float pair_lambda_term(int M, int stride, int m, uint
     const float lam = fmaf((float)level, 0.0625f, -6.0f);
     return fmaf(fmaf(lam, lam, -lam), c2, fmaf(lam, e.y, e.x));
 }
+typedef uint32_t code_piece __attribute__((ext_vector_type(4), aligned(2)));      // eight sub-parts of a code
 __device__ __forceinline__ void put_pair(float* lut, int M, int stride, int m, int pair, float b2, float d2, float c2) {
     reinterpret_cast<float2*>(lut)[m * stride + pair] = make_float2(b2, d2);
     lut[(2 * M + m) * stride + pair] = c2;
@@ -295,8 +307,8 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
                                             const float* lut, uint32_t* key, const RunList& R, WaveRuns& wr, MarkedRuns& mr,
                                             uint32_t marks, RunCursor& cur, uint32_t& kmin, uint32_t& kmax) {
     const int p0 = wb + lane;
-    constexpr int NW = MW > 0 ? MW : (MW < -1 ? -MW : 0);      // code words fetched up front (0: byte loads)
-    const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M);
+    constexpr int NW = code_words(MW);                         // code words fetched up front
+    const int M = code_parts<MW>(g.M);
     uint32_t src[U];
     uint32_t cw[U][NW > 0 ? NW : 1];
 #pragma unroll
@@ -377,7 +389,7 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
                 s += lut_at_byte<2>(j * 4 + 2, wv);
                 s += lut_at_byte<3>(j * 4 + 3, wv);
             }
-        } else if (MW < -1) {
+        } else if (MW < 0 && NW > 0) {
             // two bytes per sub-part, two sub-parts per word
             s = 0.0f;
 #pragma unroll
@@ -386,11 +398,30 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
                 s += pair_lambda_term(M, g.pair_stride, 2 * j, wv & 0xffu, (wv >> 8) & 0xffu);
                 s += pair_lambda_term(M, g.pair_stride, 2 * j + 1, (wv >> 16) & 0xffu, wv >> 24);
             }
-        } else if (MW == kPairLambda) {
+        } else if (MW < 0) {
             const uint16_t* code = reinterpret_cast<const uint16_t*>(g.codes) + (size_t)src[u] * M;
             s = 0.0f;
+            int m = 0;
+            auto pieces = [&](auto count) {                    // asked for together
+                constexpr int n = decltype(count)::value;
+                code_piece v[n];
+#pragma unroll
+                for (int i = 0; i < n; ++i) v[i] = *reinterpret_cast<const code_piece*>(code + m + 8 * i);
+#pragma unroll
+                for (int i = 0; i < 4 * n; ++i) {
+                    const uint32_t wv = v[i / 4][i % 4];
+                    s += pair_lambda_term(M, g.pair_stride, m + 2 * i, wv & 0xffu, (wv >> 8) & 0xffu);
+                    s += pair_lambda_term(M, g.pair_stride, m + 2 * i + 1, (wv >> 16) & 0xffu, wv >> 24);
+                }
+                m += 8 * n;
+            };
+            if constexpr (MW == kPairLong) {
+                while (m + 32 <= M) pieces(std::integral_constant<int, 4>{});
+                if (m + 16 <= M) pieces(std::integral_constant<int, 2>{});
+            }
+            while (m + 8 <= M) pieces(std::integral_constant<int, 1>{});
 #pragma unroll 4
-            for (int m = 0; m < M; ++m) s += pair_lambda_term(M, g.pair_stride, m, code[m] & 0xffu, code[m] >> 8);
+            for (; m < M; ++m) s += pair_lambda_term(M, g.pair_stride, m, code[m] & 0xffu, code[m] >> 8);
         } else {
             const uint8_t* code = g.codes + (size_t)src[u] * M;
             s = 0.0f;
@@ -439,7 +470,7 @@ __device__ __forceinline__ void rerank_query(const RerankArgs g, const RerankLds
     // are the same for a wavefront, so which sub-parts exist is decided by scalar code)
     const int lut_c = tid & 255;
     const int lut_m0 = __builtin_amdgcn_readfirstlane(tid >> 8), lut_ms = nt >> 8;
-    const int Mlut = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : M);
+    const int Mlut = code_parts<MW>(M);
     // entries a thread fetches per round: with codes of up to eight bytes all of a thread's entries at once, so
     // that no load is waited for inside the table phase (256 threads had two rounds of four)
     constexpr int kEnt = (MW > 0 && MW <= 2) ? 8 : 4;
@@ -535,7 +566,7 @@ __device__ __forceinline__ void rerank_query(const RerankArgs g, const RerankLds
         const int wbase = __builtin_amdgcn_readfirstlane(pos0 - lane);    // the same for a wavefront
         // eight positions in flight per thread; four when a code has four or more words or holds (pair, lambda)
         // tuples, whose scoring needs the registers, two of sixteen words
-        constexpr int UB = MW <= -16 ? 2 : ((MW >= 4 || MW <= -2) ? 4 : 8);
+        constexpr int UB = MW == -16 ? 2 : ((MW >= 4 || MW <= -2) ? 4 : 8);
         static_assert(kKeysPerThread % 4 == 0, "batches of two, four or eight");
         WaveRuns wr;
         MarkedRuns mr;                         // (not in the kernel that ranks as well)
@@ -928,7 +959,7 @@ __device__ __forceinline__ void prepare_table(const RerankArgs& g, const RerankL
     const float* sa = reinterpret_cast<const float*>(smem + L.a);
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + L.hist);
     const int who = (int)threadIdx.x - first, n = (int)blockDim.x - first;
-    const int M = MW > 0 ? 4 * MW : (MW < -1 ? -2 * MW : g.M), per = MW < 0 ? g.pair_stride : 256, entries = M * per;
+    const int M = code_parts<MW>(g.M), per = MW < 0 ? g.pair_stride : 256, entries = M * per;
     constexpr int U = 4;                       // entries asked for together
     for (int e0 = who; e0 < entries; e0 += U * n) {
         CodeEntry ent[U];

@@ -1,4 +1,4 @@
-// The re-rank kernel for (pair, lambda) codes of any length (byte loads).
+// The re-rank kernel for (pair, lambda) codes of any length up to 32 sub-parts.
 #include "rerank_kernel.hpp"
 
 namespace pqt {

@@ -1,7 +1,7 @@
 // The re-rank kernel is compiled once per code width, each width in a translation unit of its own
 // (rerank_table*.hip: one byte per sub-part, M = 4, 8, 12, 16, 32 or any; rerank_pair*.hip: (pair, lambda)
-// codes, M = 4, 8, 12, 16, 32 word-wise or any byte-wise; the number in the name counts 32-bit words).  Read byte by byte, a
-// candidate costs a load per byte: 3,217 queries x 3,001 candidates of 24 bytes, ranking included, took 456 us, read as words 339
+// codes, M = 4, 8, 12, 16, 32 word-wise or any in pieces of eight sub-parts; the number in the name counts 32-bit words).  Read byte by
+// byte, a candidate cost a load per byte: 3,217 queries x 3,001 candidates of 24 bytes, ranking included, took 456 us, read as words 339
 // (and 140 with the ranking in a kernel of its own).  This header declares their launchers.
 #pragma once
 #include "pqt_kernels.hpp"
@@ -37,6 +37,7 @@ PQT_RERANK_VARIANT_DECLARE(table3)
 PQT_RERANK_VARIANT_DECLARE(table4)
 PQT_RERANK_VARIANT_DECLARE(table8)
 PQT_RERANK_VARIANT_DECLARE(pair_bytes)
+PQT_RERANK_VARIANT_DECLARE(pair_long)
 PQT_RERANK_VARIANT_DECLARE(pair2)
 PQT_RERANK_VARIANT_DECLARE(pair4)
 PQT_RERANK_VARIANT_DECLARE(pair6)

@@ -839,6 +839,30 @@ def test_pair_table_edges(pqt, tmp_path, k1, M):
         pqt.pqt_index_free(gix)
 
 
+@pytest.mark.parametrize("M", [7, 8, 9, 15, 31, 33, 39, 40, 47, 48, 57, 63, 64])
+def test_pair_codes_in_pieces(pqt, tmp_path, M):
+    """(pair, lambda) codes that are read in pieces of eight sub-parts: lengths around a piece, and around the two and four that
+    long codes are read in.  Whole numbers: a code's score is the same sum in every kernel."""
+    import torch
+    rng = np.random.default_rng(M)
+    X = rng.integers(0, 32, (700, M)).astype(np.float32)
+    Y = torch.from_numpy(np.tile(rng.integers(0, 32, (300, M)).astype(np.float32), (8, 1))).cuda()
+    ix = B.build_index(X, 1, 5, 4, M, T=20, C=400, iters=3, code_format=1)
+    path = str(tmp_path / "pieces.pqt")
+    IO.write_index(path, ix)
+    _stagewise(pqt, ix, path, Y[:4].cpu().numpy(), 10, 3, 20, 400)
+    gix = pqt.pqt_index_load(path, 0)
+    try:
+        want = pqt.pqt_query_batch_debug(gix, Y[:300].contiguous(), 10, 3, taps=("scores",))[:2]
+        for nq in (3, 300, 2400):           # one launch, and three with the largest and the smallest workgroups
+            ids, dists = pqt.pqt_query_batch(gix, Y[:nq].contiguous(), 10, 3)
+            for first in range(0, nq, 300):
+                n = min(300, nq - first)
+                assert torch.equal(ids[first:first + n], want[0][:n]) and torch.equal(dists[first:first + n], want[1][:n])
+    finally:
+        pqt.pqt_index_free(gix)
+
+
 @pytest.mark.parametrize("many", [0, 12_300])     # more than 8,192 vectors in the second call: 64 per workgroup instead of 16
 @pytest.mark.parametrize("N, D, P, k1, k2, M, fmt, offset", [
     (63, 16, 2, 16, 8, 4, 0, 0),           # one vector short of a workgroup; one tile of centroids
