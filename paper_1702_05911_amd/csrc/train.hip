@@ -680,11 +680,36 @@ __global__ void whole_range_kernel(uint32_t n, int P, uint2* range) {
 
 // ---- the lambdas of every line's votes, and those at given ranks -----------------------------------------------------
 // Only a few ranks of a line are wanted, so its votes are brought together but not sorted: counts per line, a place for every vote,
-// and a radix select per code point (100,000 vectors x 8 sub-parts: 12, 6 and 19 us; a library sort of all votes took 160).  A workgroup of the
-// first two takes kCellThreads votes of one sub-part; up to kLdsLines lines it counts in LDS and adds up or reserves once per line.
+// and a radix select for the code points of a line (100,000 vectors x 8 sub-parts, 120 lines: 7, 10 and 22 us; a library sort of all votes
+// took 160).  A workgroup of the first two takes kCellThreads votes of one sub-part; up to kLdsLines lines it counts in LDS and adds up or reserves once per line.
 constexpr int kLdsLines = 8192;
 
 __device__ __forceinline__ int vote_line(unsigned long long key) { return (int)((key >> 32) & 0xffffu); }
+
+// One more in cnt[at] for every lane of the wavefront that has one; the count before it.  Where many lanes have the same, which additions to one
+// address would take one after the other, the first lane's are added at once.
+__device__ __forceinline__ uint32_t count_one(uint32_t* cnt, uint32_t at, bool have) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const unsigned long long all = __ballot(have);
+    if (all == 0ull) return 0u;
+    const int first = __ffsll((long long)all) - 1;
+    const bool mine = have && at == (uint32_t)__builtin_amdgcn_readlane((int)at, first);
+    const unsigned long long same = __ballot(mine);
+    uint32_t before = 0u;
+    if (have && (!mine || lane == first)) before = atomicAdd(&cnt[at], mine ? (uint32_t)__popcll(same) : 1u);
+    const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)before, first);
+    return mine ? base + (uint32_t)__popcll(same & ((1ull << lane) - 1ull)) : before;
+}
+
+// The same without the count before it
+__device__ __forceinline__ void add_one(uint32_t* cnt, uint32_t at, bool have) {
+    const unsigned long long all = __ballot(have);
+    if (all == 0ull) return;
+    const int first = __ffsll((long long)all) - 1;
+    const bool mine = have && at == (uint32_t)__builtin_amdgcn_readlane((int)at, first);
+    const unsigned long long same = __ballot(mine);
+    if (have && (!mine || (int)(threadIdx.x & (kWave - 1)) == first)) atomicAdd(&cnt[at], mine ? (uint32_t)__popcll(same) : 1u);
+}
 
 // counts[m][line]; votes without a line (number 0xffff) are not counted
 __global__ __launch_bounds__(kCellThreads) void vote_counts_kernel(const unsigned long long* keys, uint32_t nt, int lines, uint32_t* counts) {
@@ -694,12 +719,12 @@ __global__ __launch_bounds__(kCellThreads) void vote_counts_kernel(const unsigne
     const int line = v < nt ? vote_line(keys[(size_t)m * nt + v]) : 0xffff;
     uint32_t* out = counts + (size_t)m * lines;
     if (lines > kLdsLines) {
-        if (line < lines) atomicAdd(&out[line], 1u);
+        add_one(out, (uint32_t)line, line < lines);
         return;
     }
     for (int j = tid; j < lines; j += kCellThreads) cnt[j] = 0u;
     __syncthreads();
-    if (line < lines) atomicAdd(&cnt[line], 1u);
+    add_one(cnt, (uint32_t)line, line < lines);
     __syncthreads();
     for (int j = tid; j < lines; j += kCellThreads)
         if (cnt[j]) atomicAdd(&out[j], cnt[j]);
@@ -715,12 +740,11 @@ __global__ __launch_bounds__(kCellThreads) void vote_groups_kernel(const unsigne
     uint32_t* places = next + (size_t)m * lines;
     uint32_t at = 0u;
     if (lines > kLdsLines) {
-        if (line < lines) at = atomicAdd(&places[line], 1u);
+        at = count_one(places, (uint32_t)line, line < lines);
     } else {
         for (int j = tid; j < lines; j += kCellThreads) cnt[j] = 0u;
         __syncthreads();
-        uint32_t mine = 0u;
-        if (line < lines) mine = atomicAdd(&cnt[line], 1u);
+        const uint32_t mine = count_one(cnt, (uint32_t)line, line < lines);
         __syncthreads();
         for (int j = tid; j < lines; j += kCellThreads)
             if (cnt[j]) cnt[j] = atomicAdd(&places[j], cnt[j]);
@@ -730,35 +754,153 @@ __global__ __launch_bounds__(kCellThreads) void vote_groups_kernel(const unsigne
     if (line < lines) lam[(size_t)m * nt + at] = (uint32_t)key;
 }
 
-// out[e] = the value of rank `rank` (from 0) among the n lambdas at `first` of sub-part e / 256; pick = (first, n, rank), n = 0: nothing.
-// One workgroup per code point: eight bits a pass, the highest first.
-__global__ __launch_bounds__(256) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, const uint4* picks, float* out) {
-    __shared__ uint32_t hist[256], part[256 / kWave], found[2];
-    const int tid = threadIdx.x;
-    const uint4 pick = picks[blockIdx.x];
-    if (pick.y == 0u) return;
-    const uint32_t* x = lam + (size_t)(blockIdx.x / 256) * nt + pick.x;
-    uint32_t prefix = 0u, mask = 0u, rank = pick.z;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0u;
-        __syncthreads();
-        for (uint64_t e = tid; e < pick.y; e += 256) {
-            const uint32_t key = x[e];
-            if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 0xffu], 1u);
-        }
-        __syncthreads();
-        uint32_t total;
-        const uint32_t cnt = hist[tid], before = block_exclusive_sum(cnt, part, total);
-        if (before <= rank && rank < before + cnt) {
-            found[0] = (uint32_t)tid;
-            found[1] = rank - before;
-        }
-        __syncthreads();
-        prefix |= found[0] << shift;
-        mask |= 0xffu << shift;
-        rank = found[1];
+// A job: code points of one line, at most kPicks of them; job = (first lambda of the line in its sub-part, lambdas, first code point of the
+// job, code points), and sub-part m has the code points 256 m to 256 m + 255.  ranks[e]: the rank (from 0) of code point e among its line's
+// lambdas, ascending within a job.  Eight bits a pass, the highest first.  The code points of a job that have the same bits so far are a
+// group and share a histogram, so a pass reads the lambdas once whatever their number: a line with most of the votes has most of the
+// 256 code points as well (pqt_train of 100,000 vectors, one iteration, with 16 centroids and nine tenths of the vectors zero 0.92 ms, a walk per code
+// point 3.25; with one line 0.48 and 0.80, 2,000,000 vectors 1.25 and 9.5).
+constexpr int kPicks = 32;
+struct PickLds {
+    uint32_t prefix[kPicks], start[kPicks + 1], rank[kPicks], digit[kPicks];      // of a group: its bits, its first code point
+    uint32_t groups;
+};
+
+// By the first wavefront: the groups, from the bits that code point `lane` has so far.  Ranks ascend, so equal ones lie side by side.
+__device__ __forceinline__ void group_picks(PickLds& s, uint32_t bits, int picks) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t left = (uint32_t)__shfl_up((int)bits, 1, kWave);
+    const bool opens = lane < picks && (lane == 0 || bits != left);
+    const unsigned long long all = __ballot(opens);
+    const int groups = __popcll(all), mine = __popcll(all & ((1ull << lane) - 1ull));
+    if (opens) {
+        s.prefix[mine] = bits;
+        s.start[mine] = (uint32_t)lane;
     }
-    if (tid == 0) out[blockIdx.x] = mono_inv(prefix);
+    if (lane == 0) {
+        s.start[groups] = (uint32_t)picks;
+        s.groups = (uint32_t)groups;
+    }
+}
+
+// By the workgroup: hist[group * 256 + digit] of the lambdas lo .. hi - 1.
+__device__ __forceinline__ void count_digits(const PickLds& s, const uint32_t* x, uint64_t lo, uint64_t hi, int shift, uint32_t* hist) {
+    const int tid = threadIdx.x, threads = blockDim.x, ng = (int)s.groups;
+    int half = 1;
+    while (2 * half < ng) half *= 2;
+    constexpr int kFlight = 4;                               // lambdas asked for before the first is waited for
+    for (uint64_t e0 = lo; e0 < hi; e0 += (uint64_t)kFlight * threads) {
+        uint32_t key[kFlight];
+        int g[kFlight];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            key[u] = x[min(e0 + (uint64_t)(u * threads + tid), hi - 1)];
+            g[u] = 0;
+        }
+        if (shift < 24) {                                    // the group with these bits, if there is one
+            for (int step = half; step > 0; step /= 2)
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u)
+                    if (g[u] + step < ng && s.prefix[g[u] + step] <= key[u] >> (shift + 8)) g[u] += step;
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            const bool have = e0 + (uint64_t)(u * threads + tid) < hi && (shift == 24 || s.prefix[g[u]] == key[u] >> (shift + 8));
+            add_one(hist, (uint32_t)g[u] * 256u + ((key[u] >> shift) & 0xffu), have);
+        }
+    }
+}
+
+// By the workgroup: the next digit of every code point, and its rank among the lambdas that have it.  A wavefront per group, four counts a lane.
+__device__ __forceinline__ void next_digits(PickLds& s, const uint32_t* hist) {
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int g = (int)threadIdx.x / kWave; g < (int)s.groups; g += (int)blockDim.x / kWave) {
+        const uint4 c = *reinterpret_cast<const uint4*>(hist + g * 256 + 4 * lane);
+        uint32_t upto = c.x + c.y + c.z + c.w;
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)upto, off, kWave);
+            if (lane >= off) upto += o;
+        }
+        const uint32_t a0 = upto - c.w - c.z - c.y, a1 = upto - c.w - c.z, a2 = upto - c.w;
+        for (uint32_t t = s.start[g]; t < s.start[g + 1]; ++t) {
+            const uint32_t rank = s.rank[t];
+            if (lane == __popcll(__ballot(upto <= rank))) {
+                const int d = (a0 <= rank) + (a1 <= rank) + (a2 <= rank);
+                s.digit[t] = (uint32_t)(4 * lane + d);
+                s.rank[t] = rank - (d == 0 ? a0 - c.x : (d == 1 ? a0 : (d == 2 ? a1 : a2)));
+            }
+        }
+    }
+}
+
+// out[e]: the lambda of code point e, of a workgroup's job
+constexpr int kPickThreads = 512;                            // (256: 29 us, 1,024: 28)
+__global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, const uint4* jobs, const uint32_t* ranks, float* out) {
+    __shared__ __align__(16) uint32_t hist[kPicks * 256];
+    __shared__ PickLds s;
+    const int tid = threadIdx.x;
+    const uint4 job = jobs[blockIdx.x];
+    const uint32_t* x = lam + (size_t)(job.z / 256) * nt + job.x;
+    const int picks = (int)job.w;
+    uint32_t bits = 0u;                                      // of code point `tid`
+    if (tid < picks) s.rank[tid] = ranks[job.z + tid];
+    if (tid < kWave) group_picks(s, 0u, picks);
+    __syncthreads();
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int e = tid; e < (int)s.groups * 256; e += blockDim.x) hist[e] = 0u;
+        __syncthreads();
+        count_digits(s, x, 0, job.y, shift, hist);
+        __syncthreads();
+        next_digits(s, hist);
+        __syncthreads();
+        if (tid < picks) bits = (bits << 8) | s.digit[tid];
+        if (tid < kWave) group_picks(s, bits, picks);
+        __syncthreads();
+    }
+    if (tid < picks) out[job.z + tid] = mono_inv(bits);
+}
+
+// The same for long lines, whose lambdas many workgroups read: a pass is two kernels (one line of 2,000,000 votes: 256 us instead of 3,800).  bits, ranks: of the code points, from pass to pass;
+// counts[code point * 256 + digit]: the histograms of a job's groups are at its first code points, zero between passes.
+// items: (job, slice)
+__global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam, uint32_t nt, const uint4* jobs, const uint2* items, uint32_t slice,
+                                                            int shift, const uint32_t* bits, uint32_t* counts) {
+    __shared__ __align__(16) uint32_t hist[kPicks * 256];
+    __shared__ PickLds s;
+    const int tid = threadIdx.x;
+    const uint2 item = items[blockIdx.x];
+    const uint4 job = jobs[item.x];
+    const int picks = (int)job.w;
+    if (tid < kWave) group_picks(s, shift < 24 && tid < picks ? bits[job.z + tid] : 0u, picks);
+    __syncthreads();
+    const int cells = (int)s.groups * 256;
+    for (int e = tid; e < cells; e += blockDim.x) hist[e] = 0u;
+    __syncthreads();
+    const uint64_t lo = (uint64_t)item.y * slice;
+    count_digits(s, lam + (size_t)(job.z / 256) * nt + job.x, lo, min(lo + slice, (uint64_t)job.y), shift, hist);
+    __syncthreads();
+    for (int e = tid; e < cells; e += blockDim.x)
+        if (hist[e]) atomicAdd(&counts[(size_t)job.z * 256 + e], hist[e]);
+}
+
+__global__ __launch_bounds__(256) void next_digits_kernel(const uint4* jobs, int shift, uint32_t* ranks, uint32_t* bits, uint32_t* counts, float* out) {
+    __shared__ PickLds s;
+    const int tid = threadIdx.x;
+    const uint4 job = jobs[blockIdx.x];
+    const int picks = (int)job.w;
+    uint32_t mine = shift < 24 && tid < picks ? bits[job.z + tid] : 0u;
+    if (tid < picks) s.rank[tid] = ranks[job.z + tid];
+    if (tid < kWave) group_picks(s, mine, picks);
+    __syncthreads();
+    uint32_t* c = counts + (size_t)job.z * 256;
+    next_digits(s, c);
+    __syncthreads();
+    for (int e = tid; e < (int)s.groups * 256; e += 256) c[e] = 0u;
+    if (tid >= picks) return;
+    mine = (mine << 8) | s.digit[tid];
+    bits[job.z + tid] = mine;
+    ranks[job.z + tid] = s.rank[tid];
+    if (shift == 0) out[job.z + tid] = mono_inv(mine);
 }
 
 __global__ void clear_counts_kernel(uint32_t* out, size_t n) {
@@ -952,6 +1094,8 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     // labels are counted in at most 1024 pieces per part
     const uint32_t piece = (uint32_t)(((uint64_t)n + 1024ull * kCellThreads - 1) / (1024ull * kCellThreads) * kCellThreads);
     const uint32_t pieces = (uint32_t)(((uint64_t)n + piece - 1) / piece);
+    // lambdas of a line that one workgroup reads; longer lines are cut (into less than 2^20 slices in all)
+    const uint32_t slice = (uint32_t)std::max<uint64_t>(16384, (uint64_t)M * nt >> 16);
     Arena mem;
     double* sums = nullptr;
     uint32_t *counts = nullptr, *label = nullptr, *places = nullptr, *members = nullptr, *chunk_off = nullptr;
@@ -979,14 +1123,23 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     float *c1n_dev = nullptr, *lam_dev = nullptr;
     unsigned long long* keys = nullptr;
     uint32_t *lines_dev = nullptr, *lam_keys = nullptr;
-    uint4* picks_dev = nullptr;
+    uint32_t *ranks_dev = nullptr, *bits_dev = nullptr, *digits_dev = nullptr;
+    uint4* jobs_dev = nullptr;
+    uint2* items_dev = nullptr;
     if (nt) {
         mem.want(&pair_dev, (size_t)M * npairs);
         mem.want(&c1n_dev, (size_t)M * k1);
         mem.want(&keys, (size_t)M * nt);
         mem.want(&lam_keys, (size_t)M * nt);
         mem.want(&lines_dev, (size_t)M * npairs);
-        mem.want(&picks_dev, (size_t)M * 256);
+        mem.want(&jobs_dev, (size_t)M * 256);
+        mem.want(&ranks_dev, (size_t)M * 256);
+        // long lines: a line's slices for every kPicks of its code points, at most
+        if (nt > slice) {
+            mem.want(&items_dev, (size_t)M * (256 + (256 / kPicks + 1) * (size_t)(nt / slice)));
+            mem.want(&bits_dev, (size_t)M * 256);
+            mem.want(&digits_dev, (size_t)M * 256 * 256);
+        }
         mem.want(&lam_dev, (size_t)M * 256);
     }
     HIP_TRY(mem.allocate());
@@ -997,8 +1150,9 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     l1.sums = l2.sums = sums; l1.counts = l2.counts = counts; l1.dmin = l2.dmin = dmin;
     std::vector<float> C1, C2, cc;
     std::vector<LinePair> pair_host;
-    std::vector<uint32_t> first;
-    std::vector<uint4> picks;
+    std::vector<uint32_t> first, ranks;
+    std::vector<uint4> jobs, long_jobs;
+    std::vector<uint2> items;
     std::vector<float> lam;
     try {
         C1.resize((size_t)P * k1 * dp);
@@ -1006,7 +1160,10 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
         cc.resize((size_t)M * k1 * k1);
         pair_host.resize(nt ? (size_t)M * npairs : 0);
         first.resize(nt ? (size_t)M * npairs : 0);
-        picks.resize(nt ? (size_t)M * 256 : 0, make_uint4(0u, 0u, 0u, 0u));
+        jobs.reserve(nt ? (size_t)M * 256 : 0);
+        long_jobs.reserve(nt > slice ? (size_t)M * 256 : 0);
+        items.reserve(nt > slice ? (size_t)M * (256 + (256 / kPicks + 1) * (size_t)(nt / slice)) : 0);
+        ranks.resize(nt ? (size_t)M * 256 : 0, 0u);
         lam.resize(nt ? (size_t)M * 256 : 0);
     } catch (const std::bad_alloc&) {
         return fail(PQT_ENOMEM, "host allocation failed");
@@ -1079,7 +1236,6 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     // lambdas ascending, so the entries come out ordered by (i, j, lambda)
     for (uint32_t m = 0; m < M; ++m) {
         uint32_t* fm = first.data() + (size_t)m * npairs;    // counts, then first places
-        uint4* pick = picks.data() + (size_t)m * 256;
         std::vector<uint64_t> use(fm, fm + npairs);
         uint64_t total = 0;
         for (uint32_t q = 0; q < npairs; ++q) {
@@ -1088,29 +1244,45 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
         }
         if (total == 0) continue;                            // (no sub-vector has a usable line)
         const std::vector<uint32_t> alloc = share_out(use, total, 256);
-        uint32_t c = 0;
-        for (uint32_t q = 0; q < npairs && c < 256; ++q)
-            for (uint32_t t = 0; t < alloc[q] && c < 256; ++t, ++c) {
-                uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
-                if (pos >= use[q]) pos = use[q] - 1;
-                pick[c] = make_uint4(fm[q], (uint32_t)use[q], (uint32_t)pos, 0u);
-                tbl_i[(size_t)m * 256 + c] = (uint8_t)pair_host[(size_t)m * npairs + q].ij;
-                tbl_j[(size_t)m * 256 + c] = (uint8_t)(pair_host[(size_t)m * npairs + q].ij >> 16);
+        uint32_t c = m * 256;                                // (the shares of a sub-part add up to 256)
+        for (uint32_t q = 0; q < npairs; ++q)
+            for (uint32_t t = 0; t < alloc[q]; ++t, ++c) {
+                const uint64_t pos = ((2ull * t + 1ull) * use[q]) / (2ull * alloc[q]);
+                ranks[c] = (uint32_t)std::min(pos, use[q] - 1);
+                auto& list = use[q] > slice ? long_jobs : jobs;
+                if (t % kPicks == 0) {
+                    if (use[q] > slice)
+                        for (uint32_t part = 0; (uint64_t)part * slice < use[q]; ++part) items.push_back(make_uint2((uint32_t)long_jobs.size(), part));
+                    list.push_back(make_uint4(fm[q], (uint32_t)use[q], c, 0u));
+                }
+                list.back().w++;
+                tbl_i[c] = (uint8_t)pair_host[(size_t)m * npairs + q].ij;
+                tbl_j[c] = (uint8_t)(pair_host[(size_t)m * npairs + q].ij >> 16);
             }
-        for (; c > 0 && c < 256; ++c) {                      // (cannot happen when total > 0; kept total)
-            pick[c] = pick[c - 1];
-            tbl_i[(size_t)m * 256 + c] = tbl_i[(size_t)m * 256 + c - 1];
-            tbl_j[(size_t)m * 256 + c] = tbl_j[(size_t)m * 256 + c - 1];
-        }
     }
     HIP_TRY(hipMemcpyAsync(lines_dev, first.data(), nlines * sizeof(uint32_t), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(picks_dev, picks.data(), picks.size() * sizeof(uint4), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(ranks_dev, ranks.data(), ranks.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+    const size_t short_jobs = jobs.size();
+    jobs.insert(jobs.end(), long_jobs.begin(), long_jobs.end());
+    HIP_TRY(hipMemcpyAsync(jobs_dev, jobs.data(), jobs.size() * sizeof(uint4), hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(vote_groups_kernel, by_vote, dim3(kCellThreads), lines_lds, st, keys, nt, (int)npairs, lines_dev, lam_keys);
-    hipLaunchKernelGGL(pick_lambdas_kernel, dim3(M * 256), dim3(256), 0, st, lam_keys, nt, picks_dev, lam_dev);
+    if (short_jobs)
+        hipLaunchKernelGGL(pick_lambdas_kernel, dim3((unsigned)short_jobs), dim3(kPickThreads), 0, st, lam_keys, nt, jobs_dev, ranks_dev, lam_dev);
+    if (!long_jobs.empty()) {
+        const size_t digits = (size_t)M * 256 * 256;
+        const uint4* list = jobs_dev + short_jobs;
+        HIP_TRY(hipMemcpyAsync(items_dev, items.data(), items.size() * sizeof(uint2), hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)((digits + tb - 1) / tb)), dim3(tb), 0, st, digits_dev, digits);
+        for (int shift = 24; shift >= 0; shift -= 8) {
+            hipLaunchKernelGGL(slice_digits_kernel, dim3((unsigned)items.size()), dim3(1024), 0, st, lam_keys, nt, list, items_dev, slice, shift,
+                               bits_dev, digits_dev);
+            hipLaunchKernelGGL(next_digits_kernel, dim3((unsigned)long_jobs.size()), dim3(256), 0, st, list, shift, ranks_dev, bits_dev, digits_dev,
+                               lam_dev);
+        }
+    }
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(lam.data(), lam_dev, lam.size() * sizeof(float), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    for (size_t e = 0; e < lam.size(); ++e)
-        if (picks[e].y > 0) tbl_lambda[e] = lam[e];
+    for (const uint4& job : jobs) memcpy(tbl_lambda + job.z, lam.data() + job.z, job.w * sizeof(float));
     return PQT_OK;
 }

@@ -1125,11 +1125,12 @@ def test_training_edges(pqt, n, D, P, k1, k2, distinct, offset, iters):
             np.testing.assert_allclose(got["C2"][p, i], want, rtol=1e-6, atol=0)
 
 
-@pytest.mark.parametrize("n, D, k1, M", [(1, 8, 3, 2), (4097, 8, 5, 2), (1024, 48, 24, 8), (3000, 36, 140, 3)])
+@pytest.mark.parametrize("n, D, k1, M", [(1, 8, 3, 2), (4097, 8, 5, 2), (1024, 48, 24, 8), (3000, 36, 140, 3),
+                                         (16_384, 2, 2, 2), (16_385, 6, 2, 1), (50_001, 4, 3, 2)])
 def test_line_table_lambdas(pqt, n, D, k1, M):
     """The lambdas of the line table are those at the (t + 1/2) / alloc quantiles of what was voted on the line, which is not
-    sorted for them: one vote, a vote more than whole workgroups, and (140 centroids) more lines than are counted on the
-    chip.  Distances of whole numbers are exact, a lambda is their quotient rounded (2^-23 at most); an error of a line rounds by
+    sorted for them: one vote, a vote more than whole workgroups, (140 centroids) more lines than are counted on the
+    chip, and one line or three that have all votes and code points, as many votes as one workgroup reads and more.  Distances of whole numbers are exact, a lambda is their quotient rounded (2^-23 at most); an error of a line rounds by
     2^-22 of b^2 + lambda^2 c^2.  Vectors nearer to a tie than that (the centroids are vectors themselves, and lie on many lines) may
     or may not have voted on a line: its value of some rank is at least that of all who may and at most that of those who must."""
     import torch
