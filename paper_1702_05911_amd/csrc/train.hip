@@ -755,7 +755,7 @@ __global__ __launch_bounds__(kCellThreads) void vote_groups_kernel(const unsigne
 }
 
 // A job: code points of one line, at most kPicks of them; job = (first lambda of the line in its sub-part, lambdas, first code point of the
-// job, code points), and sub-part m has the code points 256 m to 256 m + 255.  ranks[e]: the rank (from 0) of code point e among its line's
+// job, code points), and sub-part m has the code points 256 m to 256 m + 255; lam holds the sub-parts from m0 on.  ranks[e]: the rank (from 0) of code point e among its line's
 // lambdas, ascending within a job.  Eight bits a pass, the highest first.  The code points of a job that have the same bits so far are a
 // group and share a histogram, so a pass reads the lambdas once whatever their number: a line with most of the votes has most of the
 // 256 code points as well (pqt_train of 100,000 vectors, one iteration, with 16 centroids and nine tenths of the vectors zero 0.92 ms, a walk per code
@@ -835,12 +835,13 @@ __device__ __forceinline__ void next_digits(PickLds& s, const uint32_t* hist) {
 
 // out[e]: the lambda of code point e, of a workgroup's job
 constexpr int kPickThreads = 512;                            // (256: 29 us, 1,024: 28)
-__global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, const uint4* jobs, const uint32_t* ranks, float* out) {
+__global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, uint32_t m0, const uint4* jobs, const uint32_t* ranks,
+                                                                    float* out) {
     __shared__ __align__(16) uint32_t hist[kPicks * 256];
     __shared__ PickLds s;
     const int tid = threadIdx.x;
     const uint4 job = jobs[blockIdx.x];
-    const uint32_t* x = lam + (size_t)(job.z / 256) * nt + job.x;
+    const uint32_t* x = lam + (size_t)(job.z / 256 - m0) * nt + job.x;
     const int picks = (int)job.w;
     uint32_t bits = 0u;                                      // of code point `tid`
     if (tid < picks) s.rank[tid] = ranks[job.z + tid];
@@ -863,8 +864,8 @@ __global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32
 // The same for long lines, whose lambdas many workgroups read: a pass is two kernels (one line of 2,000,000 votes: 256 us instead of 3,800).  bits, ranks: of the code points, from pass to pass;
 // counts[code point * 256 + digit]: the histograms of a job's groups are at its first code points, zero between passes.
 // items: (job, slice)
-__global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam, uint32_t nt, const uint4* jobs, const uint2* items, uint32_t slice,
-                                                            int shift, const uint32_t* bits, uint32_t* counts) {
+__global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam, uint32_t nt, uint32_t m0, const uint4* jobs, const uint2* items,
+                                                            uint32_t slice, int shift, const uint32_t* bits, uint32_t* counts) {
     __shared__ __align__(16) uint32_t hist[kPicks * 256];
     __shared__ PickLds s;
     const int tid = threadIdx.x;
@@ -877,7 +878,7 @@ __global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam,
     for (int e = tid; e < cells; e += blockDim.x) hist[e] = 0u;
     __syncthreads();
     const uint64_t lo = (uint64_t)item.y * slice;
-    count_digits(s, lam + (size_t)(job.z / 256) * nt + job.x, lo, min(lo + slice, (uint64_t)job.y), shift, hist);
+    count_digits(s, lam + (size_t)(job.z / 256 - m0) * nt + job.x, lo, min(lo + slice, (uint64_t)job.y), shift, hist);
     __syncthreads();
     for (int e = tid; e < cells; e += blockDim.x)
         if (hist[e]) atomicAdd(&counts[(size_t)job.z * 256 + e], hist[e]);
@@ -1096,6 +1097,8 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     const uint32_t pieces = (uint32_t)(((uint64_t)n + piece - 1) / piece);
     // lambdas of a line that one workgroup reads; longer lines are cut (into less than 2^20 slices in all)
     const uint32_t slice = (uint32_t)std::max<uint64_t>(16384, (uint64_t)M * nt >> 16);
+    // sub-parts whose lambdas are brought together at a time: as many as have 2^27 votes
+    const uint32_t batch = nt ? std::min<uint32_t>(M, std::max<uint32_t>(1, (1u << 27) / nt)) : 0u;
     Arena mem;
     double* sums = nullptr;
     uint32_t *counts = nullptr, *label = nullptr, *places = nullptr, *members = nullptr, *chunk_off = nullptr;
@@ -1130,7 +1133,7 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
         mem.want(&pair_dev, (size_t)M * npairs);
         mem.want(&c1n_dev, (size_t)M * k1);
         mem.want(&keys, (size_t)M * nt);
-        mem.want(&lam_keys, (size_t)M * nt);
+        mem.want(&lam_keys, (size_t)batch * nt);
         mem.want(&lines_dev, (size_t)M * npairs);
         mem.want(&jobs_dev, (size_t)M * 256);
         mem.want(&ranks_dev, (size_t)M * 256);
@@ -1264,20 +1267,29 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     HIP_TRY(hipMemcpyAsync(ranks_dev, ranks.data(), ranks.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st));
     const size_t short_jobs = jobs.size();
     jobs.insert(jobs.end(), long_jobs.begin(), long_jobs.end());
-    HIP_TRY(hipMemcpyAsync(jobs_dev, jobs.data(), jobs.size() * sizeof(uint4), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(vote_groups_kernel, by_vote, dim3(kCellThreads), lines_lds, st, keys, nt, (int)npairs, lines_dev, lam_keys);
-    if (short_jobs)
-        hipLaunchKernelGGL(pick_lambdas_kernel, dim3((unsigned)short_jobs), dim3(kPickThreads), 0, st, lam_keys, nt, jobs_dev, ranks_dev, lam_dev);
+    if (!jobs.empty()) HIP_TRY(hipMemcpyAsync(jobs_dev, jobs.data(), jobs.size() * sizeof(uint4), hipMemcpyHostToDevice, st));
     if (!long_jobs.empty()) {
         const size_t digits = (size_t)M * 256 * 256;
-        const uint4* list = jobs_dev + short_jobs;
         HIP_TRY(hipMemcpyAsync(items_dev, items.data(), items.size() * sizeof(uint2), hipMemcpyHostToDevice, st));
         hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)((digits + tb - 1) / tb)), dim3(tb), 0, st, digits_dev, digits);
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            hipLaunchKernelGGL(slice_digits_kernel, dim3((unsigned)items.size()), dim3(1024), 0, st, lam_keys, nt, list, items_dev, slice, shift,
-                               bits_dev, digits_dev);
-            hipLaunchKernelGGL(next_digits_kernel, dim3((unsigned)long_jobs.size()), dim3(256), 0, st, list, shift, ranks_dev, bits_dev, digits_dev,
+    }
+    size_t job = 0, long_job = short_jobs, item = 0;
+    for (uint32_t m0 = 0; m0 < M; m0 += batch) {
+        const uint32_t m1 = std::min(M, m0 + batch);
+        hipLaunchKernelGGL(vote_groups_kernel, dim3(by_vote.x, m1 - m0), dim3(kCellThreads), lines_lds, st, keys + (size_t)m0 * nt, nt, (int)npairs,
+                           lines_dev + (size_t)m0 * npairs, lam_keys);
+        const size_t j0 = job, l0 = long_job, i0 = item;
+        while (job < short_jobs && jobs[job].z < m1 * 256) ++job;
+        while (long_job < jobs.size() && jobs[long_job].z < m1 * 256) ++long_job;
+        while (item < items.size() && items[item].x < long_job - short_jobs) ++item;
+        if (job > j0)
+            hipLaunchKernelGGL(pick_lambdas_kernel, dim3((unsigned)(job - j0)), dim3(kPickThreads), 0, st, lam_keys, nt, m0, jobs_dev + j0, ranks_dev,
                                lam_dev);
+        for (int shift = 24; shift >= 0 && long_job > l0; shift -= 8) {
+            hipLaunchKernelGGL(slice_digits_kernel, dim3((unsigned)(item - i0)), dim3(1024), 0, st, lam_keys, nt, m0, jobs_dev + short_jobs,
+                               items_dev + i0, slice, shift, bits_dev, digits_dev);
+            hipLaunchKernelGGL(next_digits_kernel, dim3((unsigned)(long_job - l0)), dim3(256), 0, st, jobs_dev + l0, shift, ranks_dev, bits_dev,
+                               digits_dev, lam_dev);
         }
     }
     HIP_TRY(hipGetLastError());

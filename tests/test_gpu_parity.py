@@ -1162,6 +1162,40 @@ def test_line_table_lambdas(pqt, n, D, k1, M):
             assert np.all(mine >= low - slack) and np.all(mine <= high + slack), (m, i, j)
 
 
+def test_line_table_in_batches(pqt):
+    """More votes than are brought together at a time (2^27), in batches of 13 of 64 sub-parts: the values are exact (one line through 0
+    and 8, lambda of x = x / 8), and beside the votes' 8 bytes each the call holds little more than one batch's lambdas."""
+    import threading
+    import torch
+    n, M = 10_000_000, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.empty((n, M), dtype=torch.float32, device="cuda")
+    for s in range(0, n, 1 << 21):
+        X[s:s + (1 << 21)].random_(0, 64, generator=g)
+    X[0], X[n // 2] = 0.0, 8.0
+    torch.cuda.synchronize()
+    free = [torch.cuda.mem_get_info()[0]] * 2                # before, least
+    stop = threading.Event()
+
+    def watch():
+        while not stop.wait(0.002):
+            free[1] = min(free[1], torch.cuda.mem_get_info(0)[0])
+    t = threading.Thread(target=watch)
+    t.start()
+    try:
+        got = pqt.pqt_train(X, P=1, k1=2, k2=1, M=M, iters=0, n_table=n)
+    finally:
+        stop.set()
+        t.join()
+    assert 8 * M * n <= free[0] - free[1] <= 8 * M * n + (1 << 30)
+    rank = torch.from_numpy((2 * np.arange(256) + 1) * n // 512).cuda()
+    for m in (0, 12, 13, 25, 26, 63):
+        values = torch.bincount(X[:, m].to(torch.int64), minlength=64).cumsum(0)
+        want = torch.searchsorted(values, rank, right=True).to(torch.float32).cpu().numpy() / 8.0
+        np.testing.assert_array_equal(got["tbl_lam"][m], want)
+        assert np.all(got["tbl_i"][m] == 0) and np.all(got["tbl_j"][m] == 1)
+
+
 @pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8),
                                             (300, 32, 2, 33, 4), (130, 80, 2, 70, 2), (700, 24, 1, 130, 8), (600, 16, 2, 256, 4)])
 def test_line_table_edges(pqt, n, D, P, k1, M):
