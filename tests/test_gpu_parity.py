@@ -1094,6 +1094,7 @@ def test_brute_force(pqt, tiny, tmp_path):
     (5000, 64, 2, 16, 8, 0, 1, 1),         # vectors that do not start at a multiple of 16 bytes
     (700, 520, 2, 2, 9, 0, 0, 1),          # a wavefront sums a cell in two pieces
     (300, 8, 2, 20, 4, 6, 0, 3),           # fewer distinct vectors than centroids: cells run empty and are re-seeded
+    (300, 200, 1, 20, 4, 6, 0, 3),         # the same with more dimensions than a workgroup re-seeds, a last piece of eight
     (5, 8, 2, 7, 3, 0, 0, 2),              # fewer vectors than centroids
     (600_001, 8, 2, 2, 2, 0, 0, 1),        # more tiles than workgroups: a workgroup adds up several
     (1000, 40, 1, 130, 2, 0, 0, 1),        # many centroids, few vectors: wavefronts share a tile; a last round of two centroids
