@@ -523,11 +523,12 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part) {
 // centroid = mean of its members (the chunks added in a fixed split and order); the cells of a frozen or empty
 // group keep what they hold.  An empty cell is re-seeded with the member of its group that lies farthest from its
 // centroid (ties: the smaller vector number); that vector then counts as at distance zero, so the next empty cell of the
-// group takes another one.  One workgroup per cell and 16 dimensions (64: a quarter of the workgroups, of which two parts of
-// 16 cells have few).
-constexpr int kUpdateDims = 16, kSeedDims = 64;
+// group takes another one.  One workgroup per cell and DIMS dimensions: 64, or 16 where that would be fewer workgroups than compute units
+// (update_dims).
+constexpr int kSeedDims = 64;
+template <int DIMS>
 __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
-    __shared__ double red[1024 / kWave * kUpdateDims];
+    __shared__ double red[1024 / kWave * DIMS];
     __shared__ uint32_t part[1024 / kWave];
     __shared__ unsigned long long far_part[1024 / kWave];
     const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), k = g.k, dp = g.dp;
@@ -535,7 +536,7 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
     const uint32_t c0 = g.chunk_off[grp], c1 = g.chunk_off[grp + 1];
     const uint8_t keep = g.frozen[grp];
     if (keep || c0 == c1) return;
-    const int dl = lane & (kUpdateDims - 1), d = blockIdx.y * kUpdateDims + dl, r = tid / kUpdateDims, rl = nt / kUpdateDims;
+    const int dl = lane & (DIMS - 1), d = blockIdx.y * DIMS + dl, r = tid / DIMS, rl = nt / DIMS;
     uint32_t mine = 0;
     for (uint32_t c = c0 + tid; c < c1; c += nt) mine += g.counts[(size_t)c * k + j];
     double acc = 0.0;
@@ -549,13 +550,13 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
         for (int u = 0; u < kFlight; ++u)
             if (e + u * rl + r < c1) acc += v[u];
     }
-    for (int off = kUpdateDims; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
-    if (lane < kUpdateDims) red[tid / kWave * kUpdateDims + lane] = acc;
+    for (int off = DIMS; off < kWave; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+    if (lane < DIMS) red[tid / kWave * DIMS + lane] = acc;
     const uint32_t count = block_sum(mine, part);
     if (count > 0) {
         if (r == 0 && d < dp) {
             double t = 0.0;
-            for (int s = 0; s < nt / kWave; ++s) t += red[s * kUpdateDims + dl];
+            for (int s = 0; s < nt / kWave; ++s) t += red[s * DIMS + dl];
             put_centroid(g, grp, j, d, (float)(t / (double)count));
         }
         return;
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(1024) void lloyd_update_kernel(LloydArgs g) {
     // this is empty cell number `nth` of its group: it gets the nth farthest member, which one workgroup per kSeedDims dimensions looks for
     // (all of them: 100,000 vectors x 128, nineteen twentieths of them zero, 256 centroids 12.2 -> 20.4 ms), not the same of every cell and
     // piece, as every 256th workgroup is on the same compute unit
-    constexpr int kSeeders = kSeedDims / kUpdateDims;
+    constexpr int kSeeders = kSeedDims / DIMS;
     const int piece = blockIdx.y / kSeeders, seeders = min(kSeeders, (int)gridDim.y - piece * kSeeders);
     if ((int)blockIdx.y - piece * kSeeders != (j + piece) % seeders) return;
     const uint2 rg = g.range[grp];
@@ -1016,6 +1017,11 @@ hipError_t launch_step(const LloydArgs& g, uint64_t chunks, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Dimensions of a workgroup of lloyd_update_kernel.  100,000 vectors, 64 and 16, us: 32 cells x 64 dimensions 7.2 and 5.2, 96 x 128 9.6 and 8.7,
+// 256 x 64 11.3 and 11.9, 512 x 64 11.2 and 17.4; of level 2, smaller workgroups: 256 x 64 4.8 and 4.8, 2,048 x 64 6.1 and 14.8, 4,608 x 128
+// 16.4 and 52.6, 12,288 x 64 36.8 and 134.8.
+int update_dims(const LloydArgs& g) { return (uint64_t)g.G * (uint64_t)g.k * (uint64_t)((g.dp + 63) / 64) < 256 ? 16 : 64; }
+
 // Lloyd iterations for the groups of g, from start centroids to the result in g.cen / g.cenI.
 hipError_t lloyd_run(const LloydArgs& g, const float* parent, uint64_t rows, int iters, uint32_t* chunk_off, uint4* chunks,
                      hipStream_t st) {
@@ -1028,8 +1034,10 @@ hipError_t lloyd_run(const LloydArgs& g, const float* parent, uint64_t rows, int
     for (int it = 0; it < iters && e == hipSuccess; ++it) {
         e = launch_step(g, limit, st);
         if (e != hipSuccess) break;
-        hipLaunchKernelGGL(lloyd_update_kernel, dim3((unsigned)(g.G * g.k), (unsigned)((g.dp + kUpdateDims - 1) / kUpdateDims)), dim3(threads), 0,
-                           st, g);
+        const int dims = update_dims(g);
+        const dim3 grid((unsigned)(g.G * g.k), (unsigned)((g.dp + dims - 1) / dims));
+        if (dims == 16) hipLaunchKernelGGL(lloyd_update_kernel<16>, grid, dim3(threads), 0, st, g);
+        else hipLaunchKernelGGL(lloyd_update_kernel<64>, grid, dim3(threads), 0, st, g);
         e = hipGetLastError();
     }
     return e;

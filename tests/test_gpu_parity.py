@@ -1095,6 +1095,8 @@ def test_brute_force(pqt, tiny, tmp_path):
     (700, 520, 2, 2, 9, 0, 0, 1),          # a wavefront sums a cell in two pieces
     (300, 8, 2, 20, 4, 6, 0, 3),           # fewer distinct vectors than centroids: cells run empty and are re-seeded
     (300, 200, 1, 20, 4, 6, 0, 3),         # the same with more dimensions than a workgroup re-seeds, a last piece of eight
+    (2000, 200, 2, 140, 3, 0, 0, 1),       # more cells than compute units: sums are added up 64 dimensions at a time, a last piece of 36
+    (900, 132, 2, 140, 2, 6, 0, 2),        # re-seeded there
     (5, 8, 2, 7, 3, 0, 0, 2),              # fewer vectors than centroids
     (600_001, 8, 2, 2, 2, 0, 0, 1),        # more tiles than workgroups: a workgroup adds up several
     (1000, 40, 1, 130, 2, 0, 0, 1),        # many centroids, few vectors: wavefronts share a tile; a last round of two centroids
