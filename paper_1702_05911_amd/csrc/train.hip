@@ -943,15 +943,26 @@ int centroid_block(int k) {
 }
 
 // Centroids of a lane of lloyd_tile_kernel; 0 where lloyd_step_kernel is the one to take: rows or cells beyond its registers and
-// what leaves room for one workgroup per compute unit only.
-int tile_block(int dp, int k) {
+// what leaves room for one workgroup per compute unit only, and where it is the faster one.  pqt_train, 10 iterations, level 1 only where one number of
+// centroids is named, this kernel's time over the other's:
+// Rows of few values with few centroids, whose distances are less than a tile's fixed steps: 1,000,000 vectors x 4 with 1, 4, 8, 12 and 16 centroids
+// 1.54, 1.29, 1.16, 1.05, 0.95; x 16 1.39, 1.20, 1.13, 1.03, 0.98; x 32 1.16, 1.07, 1.03, 0.94, 0.96; x 48 0.86 and less; 100,000 x 4
+// 1.24, 1.15, 1.07, 1.00, 0.97, x 32 1.00, 1.11, 1.10, 0.88, 0.85; 60,000 x 8 1.07, 1.06, 1.04, 0.94, 0.94; 30,000 x 8 0.94, 0.99, 1.00, 0.85,
+// 0.84.  Not read in 16-byte pieces: 1,000,000 x 1 1.26, 1.08, 0.98, x 2 1.17, 0.91, 0.88.
+// Long rows and many centroids, of which two workgroups share a compute unit, in so many groups that their last chunks are short: 128
+// dimensions, 40 centroids in each of 256 groups, 75,000 vectors 1.05, 100,000 1.09, 300,000 1.03; of 128 groups 0.91 to 1.03; 120 dimensions
+// and less 0.87 to 1.00.
+int tile_block(uint64_t n, int P, int G, int k, int dp) {
     if (dp > kTileDims || k > kTileCells) return 0;
+    const uint64_t rows = (uint64_t)P * n;
+    if (dp % 4 ? dp * k <= 4 && rows > (1u << 18) : (dp <= 16 ? k <= 12 && rows > (1u << 16) : dp <= 32 && k <= 8 && rows > 90'000)) return 0;
+    if (dp > 120 && k > 32 && G > 128 && rows > (1u << 17)) return 0;
     const int want = (k + 3) / 4;
     const int kr = want <= 8 ? want : 12;
     return tile_layout(dp, 4 * kr, tile_vectors(dp)).total <= 64 * 1024 ? kr : 0;
 }
-int padded_centroids(int dp, int k) {
-    if (const int kr = tile_block(dp, k)) return 4 * kr;
+int padded_centroids(uint64_t n, int P, int G, int k, int dp) {
+    if (const int kr = tile_block(n, P, G, k, dp)) return 4 * kr;
     const int kb = centroid_block(k);
     return (k + kb - 1) / kb * kb;
 }
@@ -964,14 +975,13 @@ int ways_of(uint64_t n, int P, int k) { return k >= 128 && (uint64_t)P * ((n + k
 // Vectors per chunk (a workgroup of lloyd_step_kernel): one tile, or more where that would be more chunks than keep the
 // chip busy, or more than 64 MB of cell sums.
 uint64_t chunk_rows(uint64_t n, int P, int G, int k, int dp) {
-    if (const int kr = tile_block(dp, k)) {
-        // as many as the compute units hold at once (the last one of every group is a short one)
+    if (const int kr = tile_block(n, P, G, k, dp)) {
+        // as many as the compute units hold at once (the last one of every group is a short one): at most 1,024, and some 50 MB of sums
         const uint64_t fit = std::min<uint64_t>(4, kMaxLds / tile_layout(dp, 4 * kr, tile_vectors(dp)).total);
         uint64_t want = 256 * fit;
-        while (want > 256 && want * (uint64_t)k * (uint64_t)dp > (8ull << 20)) want /= 2;
         want -= std::min<uint64_t>((uint64_t)G, want / 2);
         const uint64_t rows = ((uint64_t)P * n + want - 1) / want;
-        return std::max<uint64_t>(rows, 64);
+        return std::max<uint64_t>(rows, 64);                 // (half a tile of 128, and 128, 64 dimensions, 16 centroids: 10,000 vectors 396 and 436 us, 32,000 477 and 510, 50,000 516 and 502)
     }
     uint64_t rows = kTile / ways_of(n, P, k);
     while (rows < n && rows < (1ull << 30) && ((uint64_t)P * ((n + rows - 1) / rows) > kMaxChunks ||
@@ -983,7 +993,7 @@ uint64_t chunk_limit(uint64_t n, uint64_t rows, int P, int G) { return (uint64_t
 
 hipError_t launch_step(const LloydArgs& g, uint64_t chunks, hipStream_t st) {
     const dim3 grid((unsigned)chunks), block(kTrainThreads);
-    if (const int kr = tile_block(g.dp, g.k)) {
+    if (const int kr = tile_block(g.n, g.P, g.G, g.k, g.dp)) {
         const size_t lds = tile_layout(g.dp, g.kp, tile_vectors(g.dp)).total;
         auto launch = [&](auto kr_c) {
             constexpr int KR = decltype(kr_c)::value;
@@ -1102,8 +1112,8 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     l1.X = vectors; l1.n = n; l1.D = (int)D; l1.dp = dp; l1.P = (int)P;
     l1.wide = reinterpret_cast<uintptr_t>(vectors) % 16 == 0 && D % 4 == 0 && dp % 4 == 0;
     l2 = l1;
-    l1.G = (int)P; l1.k = (int)k1; l1.kp = padded_centroids(dp, (int)k1);
-    l2.G = (int)(P * k1); l2.k = (int)k2; l2.kp = padded_centroids(dp, (int)k2);
+    l1.G = (int)P; l1.k = (int)k1; l1.kp = padded_centroids(n, (int)P, l1.G, l1.k, dp);
+    l2.G = (int)(P * k1); l2.k = (int)k2; l2.kp = padded_centroids(n, (int)P, l2.G, l2.k, dp);
     const uint64_t rows1 = chunk_rows(n, (int)P, l1.G, l1.k, dp), rows2 = chunk_rows(n, (int)P, l2.G, l2.k, dp);
     const uint64_t limit1 = chunk_limit(n, rows1, (int)P, l1.G), limit2 = chunk_limit(n, rows2, (int)P, l2.G);
     // labels are counted in at most 1024 pieces per part
@@ -1119,7 +1129,6 @@ extern "C" int pqt_train(const pqt_train_params* tp, const float* vectors, int d
     uint4* chunks = nullptr;
     float* dmin = nullptr;
     uint2 *range1 = nullptr, *range2 = nullptr;
-    
     mem.want(&sums, (size_t)std::max(limit1 * k1, limit2 * k2) * dp);
     mem.want(&counts, (size_t)std::max(limit1 * k1, limit2 * k2));
     mem.want(&label, (size_t)P * n);

@@ -721,47 +721,64 @@ def test_training_on_the_gpu(pqt, tiny):
     assert e.value.code in (pqt.PQT_EINVAL, pqt.PQT_EUNSUPPORTED)
 
 
-@pytest.mark.parametrize("n,D,P,k1,k2", [(63, 8, 1, 4, 2), (65, 2, 2, 3, 5), (1000, 64, 1, 16, 8), (257, 66, 1, 5, 3), (4133, 128, 1, 48, 7),
-                                         (700, 129, 1, 49, 2), (3001, 132, 2, 33, 12), (150_001, 24, 2, 12, 13), (2500, 256, 4, 31, 1)])
+@pytest.mark.parametrize("n,D,P,k1,k2", [
+    (63, 8, 1, 4, 2), (65, 2, 2, 3, 5), (1000, 64, 1, 16, 8), (257, 66, 1, 5, 3), (4133, 128, 1, 48, 7), (700, 129, 1, 49, 2),
+    (3001, 132, 2, 33, 12), (150_001, 24, 2, 12, 13), (2500, 256, 4, 31, 1),
+    (66_001, 16, 1, 13, 12),               # short rows of a large sample: level 1 by whole tiles, level 2 (with fewer centroids) by the step kernel
+    (45_001, 64, 2, 8, 9),                 # the other way round
+    (45_000, 512, 4, 40, 36),              # 128 dimensions: level 1 by tiles, its 160 groups of level 2 by the step kernel
+    (700, 264, 2, 20, 3),                  # rows beyond the tiles': 24 centroids at a time
+    (900, 262, 2, 20, 3),                  # the same where they are not read in 16-byte pieces
+    (36_000, 520, 1, 120, 2),              # chunks of two of the step kernel's tiles, sums of the second added to the first's
+    (36_000, 521, 1, 120, 2),              # the same value by value
+    (20_000, 132, 1, 256, 2),              # the same where wavefronts share a tile
+])
 def test_training_tile_edges(pqt, n, D, P, k1, k2):
     """One Lloyd iteration on small whole numbers, where sums and distances are exact: every centroid is the mean of the vectors
-    nearest to the start centroids, rounded once; rows of 1 to 132 values, up to 64 and 128 of them with whole rows on the chip, cells
-    on both sides of what a wavefront owns, samples around a tile and beyond one chunk per compute unit."""
+    nearest to the start centroids, rounded once; rows of 1 to 521 values, up to 64 and 128 of them with whole rows on the chip, cells
+    on both sides of what a wavefront owns, samples around a tile and beyond one chunk per compute unit.  Level 2 starts from
+    centroids that are not whole: a distance of dp squares is off by (dp + 2) 2^-24 of itself at most, and cells near to a vector that lies
+    halfway between them to twice that are left out."""
     import torch
     dp = D // P
+
+    def sqdist(x, c):                       # exact for whole numbers
+        return (x * x).sum(axis=1)[:, None] + (c * c).sum(axis=1)[None, :] - 2.0 * (x @ c.T)
     X = np.random.default_rng(n).integers(0, 16, (n, D)).astype(np.float32)
     got = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=k2, M=P, iters=1, n_table=0)
     again = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=k2, M=P, iters=1, n_table=0)
+    seen = 0
     for p in range(P):
         Xp = X[:, p * dp:(p + 1) * dp].astype(np.float64)
-        start = Xp[(np.arange(k1) * n) // k1]
-        lab = np.argmin(np.stack([((Xp - c) ** 2).sum(axis=1) for c in start], axis=1), axis=1)
+        lab = np.argmin(sqdist(Xp, Xp[(np.arange(k1) * n) // k1]), axis=1)
         for i in range(k1):
             if np.any(lab == i):
                 np.testing.assert_array_equal(got["C1"][p, i], Xp[lab == i].mean(axis=0).astype(np.float32))
-        # the cells of the finished quantiser; a vector halfway between two of them (to rounding) may be in either
-        d1 = np.stack([((Xp - c) ** 2).sum(axis=1) for c in got["C1"][p].astype(np.float64)], axis=1)
-        near = np.sort(d1, axis=1)[:, :2]
-        if k1 > 1 and np.any(near[:, 1] - near[:, 0] <= 1e-5 * (1.0 + near[:, 0])):
-            continue
-        for i in range(k1):
-            sub = Xp[np.argmin(d1, axis=1) == i]
+        # the cells of the finished quantiser
+        d1 = sqdist(Xp, got["C1"][p].astype(np.float64))
+        lab = np.argmin(d1, axis=1)
+        close = d1 <= d1.min(axis=1, keepdims=True) * (1.0 + (dp + 2) * 2.0 ** -23)
+        open_cells = np.any(close[close.sum(axis=1) > 1], axis=0)
+        for i in np.nonzero(~open_cells)[0]:
+            sub = Xp[lab == i]
             if sub.shape[0] <= k2:
                 continue
-            start2 = sub[(np.arange(k2) * sub.shape[0]) // k2]
-            lab2 = np.argmin(np.stack([((sub - c) ** 2).sum(axis=1) for c in start2], axis=1), axis=1)
+            lab2 = np.argmin(sqdist(sub, sub[(np.arange(k2) * sub.shape[0]) // k2]), axis=1)
             for j in range(k2):
                 if np.any(lab2 == j):
                     np.testing.assert_array_equal(got["C2"][p, i, j], sub[lab2 == j].mean(axis=0).astype(np.float32))
+            seen += 1
+    assert seen > 0, "no cell of level 2 was looked at"
     for name in got:
         assert np.array_equal(got[name], again[name]), f"{name}: training is not deterministic"
 
 
-def test_training_most_vectors(pqt):
-    """The most training vectors (2^32 - 2): the last tile ends past 2^32.  Values 0 .. 15 but for a start centroid and the last
-    vector, which alone share a cell; sums are whole numbers below 2^53, so every mean is rounded once."""
+@pytest.mark.parametrize("k1", [2, 5])           # by the step kernel, and by whole tiles, the last of which ends past 2^32
+def test_training_most_vectors(pqt, k1):
+    """The most training vectors (2^32 - 2).  Values 0 .. 15 but for the start centroids from the second on, far from these and each other,
+    and the last vector, which shares a cell with the last of them; sums are whole numbers below 2^53, so every mean is rounded once."""
     import torch
-    n, far = (1 << 32) - 2, (4096.0, 8192.0)
+    n = (1 << 32) - 2
     free, _ = torch.cuda.mem_get_info()
     if free < 80 << 30:
         pytest.skip("needs 80 GB of GPU memory")
@@ -769,12 +786,15 @@ def test_training_most_vectors(pqt):
     pattern = (torch.arange(1 << 26, device="cuda") % 16).to(torch.float32).view(-1, 1)
     for s in range(0, n, 1 << 26):
         X[s:s + (1 << 26)] = pattern[:n - s]
-    X[n // 2], X[n - 1] = far
-    # 2^28 of every value, but one 14 and one 15 less (i mod 16 ends with 13); two values are replaced
-    total = (1 << 28) * 120 - 14 - 15 - (n // 2) % 16 - (n - 1) % 16
-    want = np.array([[total / (n - 2)], [sum(far) / 2]]).astype(np.float32)
+    far = {n * j // k1: 4096.0 * j for j in range(1, k1)}
+    far[n - 1] = 4096.0 * (k1 - 1) + 1000.0
+    for at, value in far.items():
+        X[at] = value
+    # 2^28 of every value, but one 14 and one 15 less (i mod 16 ends with 13)
+    total = (1 << 28) * 120 - 14 - 15 - sum(at % 16 for at in far)
+    want = np.array([[total / (n - len(far))]] + [[4096.0 * j] for j in range(1, k1 - 1)] + [[4096.0 * (k1 - 1) + 500.0]]).astype(np.float32)
     try:
-        got = pqt.pqt_train(X, P=1, k1=2, k2=1, M=1, iters=1, n_table=0)
+        got = pqt.pqt_train(X, P=1, k1=k1, k2=1, M=1, iters=1, n_table=0)
     finally:
         del X, pattern
         torch.cuda.empty_cache()
@@ -1089,8 +1109,8 @@ def test_brute_force(pqt, tiny, tmp_path):
 
 @pytest.mark.parametrize("n, D, P, k1, k2, distinct, offset, iters", [
     (255, 6, 2, 3, 2, 0, 0, 1),            # odd slices (no 16-byte rows), one vector short of a tile
-    (257, 8, 1, 33, 5, 0, 0, 1),           # one vector in the second tile; centroids in two rounds
-    (1000, 72, 2, 8, 40, 0, 0, 1),         # two slabs of dimensions, the second partial; cells with fewer than k2 members
+    (257, 8, 1, 33, 5, 0, 0, 1),           # one vector in the last tile; twelve centroids a lane, the last of them padding
+    (1000, 72, 2, 8, 40, 0, 0, 1),         # slices of nine 16-byte pieces; cells with fewer than k2 members
     (5000, 64, 2, 16, 8, 0, 1, 1),         # vectors that do not start at a multiple of 16 bytes
     (700, 520, 2, 2, 9, 0, 0, 1),          # a wavefront sums a cell in two pieces
     (300, 8, 2, 20, 4, 6, 0, 3),           # fewer distinct vectors than centroids: cells run empty and are re-seeded
@@ -1098,7 +1118,7 @@ def test_brute_force(pqt, tiny, tmp_path):
     (2000, 200, 2, 140, 3, 0, 0, 1),       # more cells than compute units: sums are added up 64 dimensions at a time, a last piece of 36
     (900, 132, 2, 140, 2, 6, 0, 2),        # re-seeded there
     (5, 8, 2, 7, 3, 0, 0, 2),              # fewer vectors than centroids
-    (600_001, 8, 2, 2, 2, 0, 0, 1),        # more tiles than workgroups: a workgroup adds up several
+    (600_001, 8, 2, 2, 2, 0, 0, 1),        # more of the step kernel's tiles than workgroups: a workgroup adds up several
     (1000, 40, 1, 130, 2, 0, 0, 1),        # many centroids, few vectors: wavefronts share a tile; a last round of two centroids
     (777, 6, 2, 256, 3, 0, 0, 1),          # the same with odd slices
     (30_001, 16, 2, 2, 200, 0, 0, 1),      # the same at level 2
