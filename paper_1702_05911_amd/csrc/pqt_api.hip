@@ -174,9 +174,7 @@ int check_query_limits(const pqt_index* ix, int k, int w, int64_t nq, size_t* ld
     const size_t l1 = pqt::traverse_lds_bytes(ix->D, ix->P, ix->k1, ix->k2, ix->M, w);
     const size_t l2 = pqt::rank_lds_bytes(ix->P, R, ix->T, ix->hashed ? 1 : 2);   // 2: room for the slots tap
     const int threads = rerank_threads(ix, nullptr, nq);
-    size_t l3 = pqt::rerank_lds_bytes(ix->M, ix->k1, ix->T, ix->C, k, threads, 0, (int)ix->code_format,
-                                      rerank_runs_in_lds(ix));
-    if (ix->code_format == PQT_CODES_PAIR_LAMBDA) l3 += pqt::rerank_pair_reserve(ix->M, ix->k1);
+    const size_t l3 = pqt::rerank_limit_bytes(ix->M, ix->k1, ix->T, ix->C, k, threads, (int)ix->code_format, rerank_runs_in_lds(ix));
     if (l1 > ix->lds_limit || l2 > ix->lds_limit || l3 > ix->lds_limit)
         return fail(PQT_EUNSUPPORTED,
                     "LDS budget exceeded (traverse %zu, rank %zu, rerank %zu bytes of %zu) for D=%u M=%u k1=%u R=%d T=%u C=%u",

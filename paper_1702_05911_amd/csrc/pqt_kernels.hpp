@@ -174,7 +174,8 @@ struct RerankArgs {
 // rank_lds: LDS bytes of the full ranking pass when the kernel also runs it (0: it does not)
 size_t rerank_lds_bytes(int M, int k1, int T, int C, int k, int threads, size_t rank_lds, int code_format,
                         int runs_in_lds);
-size_t rerank_pair_reserve(int M, int k1);
+// what the limits of a query are checked against: at least the bytes of any launch
+size_t rerank_limit_bytes(int M, int k1, int T, int C, int k, int threads, int code_format, int runs_in_lds);
 // tuples per thread the in-kernel ranking can hold: fusing needs min(T, R^2) <= that * threads
 int rerank_fused_tuples_per_thread();
 // workgroup size and candidates per thread of the re-rank kernel for a candidate budget C

@@ -11,8 +11,9 @@
 
 namespace pqt {
 
+// pair_bytes: of a centroid pair in the table of (pair, lambda) codes, pair_entries: pairs a sub-part has room for
 static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, size_t rank_lds, int code_format,
-                               int runs_in_lds) {
+                               int runs_in_lds, size_t pair_bytes, int pair_entries) {
     RerankLds L;
     (void)C;
     L.kpad = next_pow2(k);
@@ -22,7 +23,7 @@ static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, 
     size_t o = 0;
     // at offset 0: lookups need no base register.
     // One float per table entry, or (b^2, a^2 - b^2) and c^2 per centroid pair for (pair, lambda) codes.
-    L.lut = (uint32_t)o;       o += code_format == 1 ? 3 * sizeof(float) * (size_t)M * pair_table_stride(k1) : sizeof(float) * M * 256;
+    L.lut = (uint32_t)o;       o += code_format == 1 ? pair_bytes * (size_t)M * pair_entries : sizeof(float) * M * 256;
     // the survivors are collected when the last score is known: they take the table's place
     L.surv = 0;                o = std::max(o, sizeof(unsigned long long) * (size_t)L.scap);
     L.hist = (uint32_t)o;      o += sizeof(uint32_t) * kHistSize;
@@ -39,15 +40,19 @@ static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, 
     return L;
 }
 
+static RerankLds rerank_layout(int M, int k1, int T, int C, int k, int threads, size_t rank_lds, int code_format,
+                               int runs_in_lds) {
+    return rerank_layout(M, k1, T, C, k, threads, rank_lds, code_format, runs_in_lds, 3 * sizeof(float), pair_table_stride(k1));
+}
+
 size_t rerank_lds_bytes(int M, int k1, int T, int C, int k, int threads, size_t rank_lds, int code_format,
                         int runs_in_lds) {
     return rerank_layout(M, k1, T, C, k, threads, rank_lds, code_format, runs_in_lds).total;
 }
 
 // The limit of (pair, lambda) codes is a table of 16 bytes an entry, 128 or 256 of them a sub-part; the table takes less.
-size_t rerank_pair_reserve(int M, int k1) {
-    const size_t limit = 16 * (size_t)M * (k1 * (k1 - 1) / 2 <= 128 ? 128 : 256), table = 3 * sizeof(float) * (size_t)M * pair_table_stride(k1);
-    return limit - table;
+size_t rerank_limit_bytes(int M, int k1, int T, int C, int k, int threads, int code_format, int runs_in_lds) {
+    return rerank_layout(M, k1, T, C, k, threads, 0, code_format, runs_in_lds, 16, k1 * (k1 - 1) / 2 <= 128 ? 128 : 256).total;
 }
 
 void rerank_shape(int C, int M, int code_format, int* threads, int* keys_per_thread) {

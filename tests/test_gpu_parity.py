@@ -859,6 +859,28 @@ def test_pair_table_edges(pqt, tmp_path, k1, M):
         pqt.pqt_index_free(gix)
 
 
+def test_pair_code_limits(pqt, tmp_path):
+    """The most sub-parts of (pair, lambda) codes with the longest result list and few centroids, where the survivors of the selection
+    take more room than the table of pairs, are answered; with the most centroids they are refused (the limit is 16 bytes for each of 256 pairs)."""
+    import torch
+    rng = np.random.default_rng(5)
+    X = rng.integers(0, 32, (3000, 64)).astype(np.float32)
+    Y = rng.integers(0, 32, (3, 64)).astype(np.float32)
+    ix = B.build_index(X, 2, 5, 16, 64, T=2048, C=2000, iters=2, code_format=1)
+    path = str(tmp_path / "few.pqt")
+    IO.write_index(path, ix)
+    _stagewise(pqt, ix, path, Y, 1024, 5, 2048, 2000)
+    path = str(tmp_path / "many.pqt")
+    IO.write_index(path, B.build_index(X, 2, 23, 2, 64, T=64, C=100, iters=1, code_format=1))
+    gix = pqt.pqt_index_load(path, 0)
+    try:
+        with pytest.raises(pqt.PqtError) as e:
+            pqt.pqt_query_batch(gix, torch.from_numpy(Y).cuda(), 10, 2)
+        assert e.value.code == pqt.PQT_EUNSUPPORTED
+    finally:
+        pqt.pqt_index_free(gix)
+
+
 @pytest.mark.parametrize("M", [7, 8, 9, 15, 31, 33, 39, 40, 47, 48, 57, 63, 64])
 def test_pair_codes_in_pieces(pqt, tmp_path, M):
     """(pair, lambda) codes that are read in pieces of eight sub-parts: lengths around a piece, and around the two and four that
