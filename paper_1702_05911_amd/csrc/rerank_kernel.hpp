@@ -961,18 +961,21 @@ __device__ __forceinline__ void prepare_table(const RerankArgs& g, const RerankL
     const int who = (int)threadIdx.x - first, n = (int)blockDim.x - first;
     const int M = code_parts<MW>(g.M), per = MW < 0 ? g.pair_stride : 256, entries = M * per;
     constexpr int U = 4;                       // entries asked for together
+    // the sub-part of an entry: half an entry from the next whole number, which is more than the product is off
+    const float inv = 1.0f / (float)per;
+    auto part_of = [&](int e) { return MW < 0 ? (int)(((float)e + 0.5f) * inv) : e / per; };
     for (int e0 = who; e0 < entries; e0 += U * n) {
         CodeEntry ent[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = min(e0 + u * n, entries - 1), m = e / per;
+            const int e = min(e0 + u * n, entries - 1), m = part_of(e);
             ent[u] = g.table[m * 256 + (e - m * per)];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int e = e0 + u * n;
             if (e >= entries) break;
-            const int m = e / per;
+            const int m = part_of(e);
             const float* sam = sa + m * g.k1;
             const float b2 = sam[ent[u].ij & 0xffu], a2 = sam[(ent[u].ij >> 8) & 0xffu];
             if (MW < 0) put_pair(lut, M, per, m, e - m * per, b2, a2 - b2, ent[u].kc);
