@@ -125,9 +125,10 @@ int rerank_runs_in_lds(const pqt_index* ix) {
 // gain by the head pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at
 // 67: 85 and 114, at 90: 109 and 131; T = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536.
 // Codes that are not one byte per sub-part read as words leave the re-rank kernel more to do, behind which the ranking inside it
-// hides: with the head pass and without, M = 32 pairs, 1,200 queries at 60: 99 and 123, at 90: 138 and 131; 10,000 at 60: 593
-// and 655, at 90: 883 and 783; M = 8 pairs 2,000 at 70: 79 and 76, 4,000 at 90: 131 and 125, 10,000 at 90: 241 and 260, at 110: 308
-// and 278; M = 64 table codes 4,000 at 60: 327 and 358, at 80: 421 and 409.  One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
+// hides: with the head pass and without, 10,000 queries, M = 4 pairs at 84: 296 and 309, at 96: 346 and 310; M = 8 327 and 342, 386 and 349; M = 12
+// (20 centroids) at 60: 316 and 412, at 72: 502 and 434; M = 16 at 72: 406 and 424, at 84: 609 and 468; M = 32 at 60: 836 and 891, at 72: 1,001 and
+// 987; M = 64 (8 centroids) at 72: 631 and 660, at 84: 768 and 730; 2,000 queries at 72: M = 8 91 and 92, M = 12 121 and 121, M = 32 243 and 226; table
+// codes, M = 64 at 72: 924 and 925, at 84: 1,081 and 1,009, M = 24 470 and 466, at 96: 542 and 490, M = 6 at 84: 429 and 446. One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
 // 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233.
 // (These are times of three launches.  Up to 1,024 queries mostly take one, and come here with stage times or intermediate results asked
 // for, with more than 256 entries a list, or where one launch does not fit or does not pay.)
@@ -142,7 +143,8 @@ double headless_from(const pqt_index* ix, int64_t nq) {
     if (nq <= 512) return 48.0;
     if (ix->T > 2048 && nq > 1024) return nq <= 2048 ? 96.0 : 160.0;
     if (nq <= 2048) return words ? 48.0 : 72.0;
-    return words ? 96.0 : 84.0;
+    if (words) return 96.0;
+    return M <= 8 ? 88.0 : (pairs || M > 32 ? 72.0 : 84.0);
 }
 // Queries that are answered in one launch, as many as run at once: a workgroup of 1,024 threads has a compute unit, up to 512 queries
 // are two of 512 threads, up to 1,024 four of 256, where the tuples, the candidates and its share of the LDS allow it and the

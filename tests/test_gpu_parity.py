@@ -544,6 +544,26 @@ def test_ranking_routes_agree(pqt, C, H):
         pqt.pqt_index_free(ix)
 
 
+@pytest.mark.parametrize("M", [8, 12])
+@pytest.mark.parametrize("C", [205, 217, 252, 264])
+def test_ranking_routes_agree_for_pair_codes(pqt, M, C):
+    """The head pass of large batches of (pair, lambda) codes is left out from a mean need of 88 tuples on (up to eight sub-parts) or 72: on both
+    sides of both lines a batch gets what its queries get by themselves."""
+    import torch
+    rng = np.random.default_rng(29)
+    X = rng.integers(0, 64, (3000, 24)).astype(np.float32)
+    Y = torch.from_numpy(rng.integers(0, 64, (2100, 24)).astype(np.float32)).cuda()
+    from paper_1702_05911_amd import builder
+    gix = builder.build_index_native(X, P=2, k1=8, k2=4, M=M, T=500, C=C, train_n=3000, code_format=1)
+    try:
+        ids, dists = pqt.pqt_query_batch(gix, Y, 20, 6)
+        for s in range(0, 2100, 700):
+            few = pqt.pqt_query_batch(gix, Y[s:s + 70].contiguous(), 20, 6)
+            assert torch.equal(few[0], ids[s:s + 70]) and torch.equal(few[1], dists[s:s + 70])
+    finally:
+        pqt.pqt_index_free(gix)
+
+
 @pytest.mark.parametrize("T", [1500, 2500, 6000])
 @pytest.mark.parametrize("H, budgets", [(None, (20, 26, 40, 100)), (4099, (150, 240, 400, 900))])
 def test_ranking_routes_agree_for_long_lists(pqt, H, budgets, T):
