@@ -420,7 +420,7 @@ __device__ __forceinline__ void score_batch(const RerankArgs& g, int64_t q, int 
                 if (m + 16 <= M) pieces(std::integral_constant<int, 2>{});
             }
             while (m + 8 <= M) pieces(std::integral_constant<int, 1>{});
-#pragma unroll 4
+#pragma unroll 2
             for (; m < M; ++m) s += pair_lambda_term(M, g.pair_stride, m, code[m] & 0xffu, code[m] >> 8);
         } else {
             const uint8_t* code = g.codes + (size_t)src[u] * M;
