@@ -1261,16 +1261,25 @@ def test_line_table_in_batches(pqt):
         assert np.all(got["tbl_i"][m] == 0) and np.all(got["tbl_j"][m] == 1)
 
 
-@pytest.mark.parametrize("n, D, P, k1, M", [(700, 16, 2, 7, 4), (333, 64, 2, 21, 4), (500, 32, 4, 15, 8), (900, 40, 2, 16, 8),
-                                            (300, 32, 2, 33, 4), (130, 80, 2, 70, 2), (700, 24, 1, 130, 8), (600, 16, 2, 256, 4)])
-def test_line_table_edges(pqt, n, D, P, k1, M):
+@pytest.mark.parametrize("n, D, P, k1, M, zeros", [(700, 16, 2, 7, 4, 0), (333, 64, 2, 21, 4, 0), (500, 32, 4, 15, 8, 0), (900, 40, 2, 16, 8, 0),
+                                                   (300, 32, 2, 33, 4, 0), (130, 80, 2, 70, 2, 0), (700, 24, 1, 130, 8, 0), (600, 16, 2, 256, 4, 0),
+                                                   (2500, 24, 1, 140, 2, 0.8), (2500, 24, 1, 9, 2, 0.8)])
+def test_line_table_edges(pqt, n, D, P, k1, M, zeros):
     """Line votes where 16-byte rows meet numbers of centroids that are no multiple of four (and at sub-parts of five
     dimensions), and of more than 32 centroids, where wavefronts share a sub-part (sub-parts of 40 and of three dimensions, the
-    most centroids).  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
+    most centroids), and where most vote for one of few lines and of many.  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
     Shares as in test_training_on_the_gpu: within one of the quota, and a near tie of two lines may move a vote or two."""
     import torch
     rng = np.random.default_rng(17)
     X = rng.integers(0, 64, (n, D)).astype(np.float32)
+    # Most vectors zero, but only the first of the centroids: they lie on its lines, with an error of exactly zero, and vote for the first of
+    # them.  (Two zero centroids would make every line through them two lines, of the same error but for rounding.)
+    centroids = (np.arange(k1) * n) // k1
+    none = rng.random(n) < zeros
+    none[centroids] = False
+    X[none] = 0.0
+    if zeros:
+        X[0] = 0.0
     got = pqt.pqt_train(torch.from_numpy(X).cuda(), P=P, k1=k1, k2=2, M=M, iters=0, n_table=n)
     pairs, ds = Q.centroid_pairs(k1), D // M
     for m in range(M):
