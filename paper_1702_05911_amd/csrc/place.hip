@@ -9,11 +9,11 @@
 // the wavefront and come through the scalar cache, and nothing is compared across lanes.  Sub-part distances are added to
 // the part's in ascending order; level 2 spreads (vector, child) pairs over the lanes, children of a cluster interleaved.
 //
-// Bound by vector instructions (six per vector, sub-part and code point) and, above 32 centroids, LDS reads (two of them): up to
-// 32 the code search has a lane's distances in registers (2,000,003 vectors, below: the whole call 2.73 -> 2.29 ms).
-// 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8, M = 8, table codes: 1.62 ms (code search 0.62, level 2 0.3); the traversal kernel with w = 1 (one wavefront
-// per list, 8 of 64 lanes at work), its distances written and read back, and one wavefront per vector for the codes took
-// 7.0.  With staged values and distances side by side in LDS three workgroups instead of five fit a compute unit: 2.9.
+// Bound by vector instructions (six per vector, sub-part and code point) and, above 32 centroids, LDS reads (two of them): up to 32 the code search
+// has a lane's distances in registers (2,000,003 vectors, below: the whole call 2.73 -> 2.29 ms). 2,000,003 vectors x 128, P = 2, k1 = 16, k2 = 8,
+// M = 8, table codes: 1.62 ms (code search 0.62, level 2 0.3); the traversal kernel with w = 1 (one wavefront per list, 8 of 64 lanes at work), its
+// distances written and read back, and one wavefront per vector for the codes took 7.0.  With staged values and distances side by side in LDS three
+// workgroups instead of five fit a compute unit: 2.9.
 #include <type_traits>
 
 #include "pqt_device.hpp"
@@ -310,9 +310,10 @@ __device__ __forceinline__ unsigned long long vote_of(const LinePair* pairs, uns
 
 enum { kTableCodes, kPairCodes, kVotes };
 
-// What place_kernel ends with, for ROWS vectors, by the whole workgroup: sel[p * ROWS + v] holds the nearest cluster of every part,
-// code the codes of cb bytes; leaf[] starts as all ones.  (place_kernel has it inline: called from there it was scheduled so
-// that 60,000 vectors x 960 took 690 us instead of 515.)
+// What place_kernel ends with, for ROWS vectors, by the whole workgroup: sel[p * ROWS + v] holds the nearest cluster of every part, code the codes
+// of cb bytes; leaf[] starts as all ones.  (place_kernel has it inline: called from there it was scheduled so that 60,000 vectors x 960 took 690 us
+// instead of 515.)  A lane per (vector, child) at level 2, as 16 vectors are few: with four lanes a vector (nearest_child), the parts side by side,
+// up to eight children would gain (1,000 x 960, four parts of eight 65 -> 43 us, x 128, two parts 27 -> 25), 32 lose (x 96 28 -> 38).
 template <int ROWS, bool WIDE>
 __device__ __forceinline__ void finish_vectors(const PlaceArgs& g, int64_t v0, int nv, const unsigned long long* sel, unsigned long long* leaf,
                                                const uint8_t* code, int cb) {
@@ -367,7 +368,8 @@ __device__ __forceinline__ void finish_vectors(const PlaceArgs& g, int64_t v0, i
 // dimensions in ascending order.  Four lanes share the vector: each brings every fourth 16 bytes of it, which the others take from its
 // register in the subtraction itself, and works on every fourth child, two at a time.  What bounds it is the 64 bytes a clock that the
 // vector cache returns: 9 loads per 16 dimensions and 128 (vector, child) pairs, 16 with a lane per pair that brings the vector for
-// itself (2,000,003 vectors x 128, P = 2, k2 = 8: the kernel 1.74 -> 1.62 ms).
+// itself (2,000,003 vectors x 128, P = 2, k2 = 8: the kernel 1.74 -> 1.62 ms; 1,000,000 vectors, a call with one child 840 -> 797 us, two 868 and
+// 784, four 845 and 786, 16 1,098 and 900, 32 1,813 and 1,061).
 template <int U>
 __device__ __forceinline__ float quad_value(float x) {       // of lane U of every four
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), U * 0x55, 0xf, 0xf, true));

@@ -115,23 +115,22 @@ int rerank_runs_in_lds(const pqt_index* ix) {
     return r;
 }
 
-// From which mean number of needed tuples on (see run_query) the head pass does not pay.  A large batch waits for the sum of
-// the work: the line lies where most queries come back from 64 tuples unfinished.  A small one waits for its slowest
-// query, so there it lies where one of nq is likely to: the share that 64 tuples leave over falls from about 0.4 at 160 to
-// 0.1 at 96, 0.03 at 64 and 0.005 at 48.  Measured (us a batch, with the head pass and without): 4,000 queries at 80: 100
-// and 129, at 110: 149 and 131; 1,500 at 33: 56 and 68, at 50: 83 and 73; 300 at 33: 46 and 54, at 50: 65 and 55; 16 at 67: 45 and
-// 34; one query at 67: 22 and 29 if it finishes, 41 and 30 if not.  Far above: 3,000 queries at 655: 307 and 182.
-// More than 2,048 tuples take workgroups of 512 threads, two per compute unit, so that batches of more than two rounds of those
-// gain by the head pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at
-// 67: 85 and 114, at 90: 109 and 131; T = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536.
-// Codes that are not one byte per sub-part read as words leave the re-rank kernel more to do, behind which the ranking inside it
-// hides: with the head pass and without, 10,000 queries, M = 4 pairs at 84: 296 and 309, at 96: 346 and 310; M = 8 327 and 342, 386 and 349; M = 12
-// (20 centroids) at 60: 316 and 412, at 72: 502 and 434; M = 16 at 72: 406 and 424, at 84: 609 and 468; M = 32 at 60: 836 and 891, at 72: 1,001 and
-// 987; M = 64 (8 centroids) at 72: 631 and 660, at 84: 768 and 730; 2,000 queries at 72: M = 8 91 and 92, M = 12 121 and 121, M = 32 243 and 226; table
-// codes, M = 64 at 72: 924 and 925, at 84: 1,081 and 1,009, M = 24 470 and 466, at 96: 542 and 490, M = 6 at 84: 429 and 446. One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300 at 45: 66 and 83,
-// 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233.
-// (These are times of three launches.  Up to 1,024 queries mostly take one, and come here with stage times or intermediate results asked
-// for, with more than 256 entries a list, or where one launch does not fit or does not pay.)
+// From which mean number of needed tuples on (see run_query) the head pass does not pay.  A large batch waits for the sum of the work: the line
+// lies where most queries come back from 64 tuples unfinished.  A small one waits for its slowest query, so there it lies where one of nq is likely
+// to: the share that 64 tuples leave over falls from about 0.4 at 160 to 0.1 at 96, 0.03 at 64 and 0.005 at 48.  Measured (us a batch, with the
+// head pass and without): 4,000 queries at 80: 100 and 129, at 110: 149 and 131; 1,500 at 33: 56 and 68, at 50: 83 and 73; 300 at 33: 46 and 54, at
+// 50: 65 and 55; 16 at 67: 45 and 34; one query at 67: 22 and 29 if it finishes, 41 and 30 if not.  Far above: 3,000 queries at 655: 307 and 182.
+// More than 2,048 tuples take workgroups of 512 threads, two per compute unit, so that batches of more than two rounds of those gain by the head
+// pass for longer.  With it and without, T = 2500: 1,000 queries at 67: 98 and 80, at 82: 76 and 82; 2,040 at 67: 85 and 114, at 90: 109 and 131; T
+// = 4096: 3,000 at 120: 125 and 177, at 164: 214 and 185; 10,000 at 164: 524 and 536. Codes that are not one byte per sub-part read as words leave
+// the re-rank kernel more to do, behind which the ranking inside it hides: with the head pass and without, 10,000 queries, M = 4 pairs at 84: 296
+// and 309, at 96: 346 and 310; M = 8 327 and 342, 386 and 349; M = 12 (20 centroids) at 60: 316 and 412, at 72: 502 and 434; M = 16 at 72: 406 and
+// 424, at 84: 609 and 468; M = 32 at 60: 836 and 891, at 72: 1,001 and 987; M = 64 (8 centroids) at 72: 631 and 660, at 84: 768 and 730; 2,000
+// queries at 72: M = 8 91 and 92, M = 12 121 and 121, M = 32 243 and 226; table codes, M = 64 at 72: 924 and 925, at 84: 1,081 and 1,009, M = 24
+// 470 and 466, at 96: 542 and 490, M = 6 at 84: 429 and 446. One to three sub-parts: hardly anything to re-rank but the bytes' latency: M = 2, 300
+// at 45: 66 and 83, 1,200 at 110: 113 and 139, 4,000 at 150: 240 and 233. (These are times of three launches.  Up to 1,024 queries mostly take one,
+// and come here with stage times or intermediate results asked for, with more than 256 entries a list, or where one launch does not fit or does not
+// pay.)
 double headless_from(const pqt_index* ix, int64_t nq) {
     const uint32_t M = ix->M;
     const bool pairs = ix->code_format == PQT_CODES_PAIR_LAMBDA;

@@ -96,13 +96,13 @@ hipError_t launch_rerank(const RerankArgs& a_in, const RankArgs* fused, hipStrea
     const RerankLds L = rerank_layout(a.M, a.k1, a.T, a.C, a.k, a.threads, fused ? RL.total : 0, a.code_format, a.runs_in_lds);
     const bool f = fused != nullptr;
     if (a.code_format == 1) {
-        // word-wise variants for the plain entry point; the tapped one takes the byte-wise kernel
-        // Codes of six and sixteen words take 128 registers, so that one workgroup of 1,024 threads fits a compute unit and two of
-        // the kernel for any length do: more queries than compute units in such workgroups go there, those of sixteen words where the kernel ranks as
-        // well or with few candidates.  700 and 1,000 queries by words and by pieces, ranking too: M = 12: 1,030 candidates 49 and 68 us, 45 and
-        // 61, 2,300 129 and 160, 112 and 131; M = 32: 1,600 candidates 66 and 90, 59 and 70, 4,096 100 and 123, 84 and 105, 9,150 200 and 259, 185 and
-        // 232; without the ranking, 1,000 and 2,000 queries: M = 12: 10,700 candidates 118 and 213, 108 and 187, M = 32: 8,540 165 and 255, 190 and
-        // 299.  (Batches of 257 to 1,024 queries come here where they are not answered in one launch.)
+        // word-wise variants for the plain entry point; the tapped one takes the kernel for any length.  Codes of six and sixteen words take 128
+        // registers, so that one workgroup of 1,024 threads fits a compute unit and two of the kernel for any length do: more queries than compute
+        // units in such workgroups go there, those of sixteen words where the kernel ranks as well or with few candidates.  700 and 1,000 queries
+        // by words and by pieces, ranking too: M = 12: 1,030 candidates 49 and 68 us, 45 and 61, 2,300 129 and 160, 112 and 131; M = 32: 1,600
+        // candidates 66 and 90, 59 and 70, 4,096 100 and 123, 84 and 105, 9,150 200 and 259, 185 and 232; without the ranking, 1,000 and 2,000
+        // queries: M = 12: 10,700 candidates 118 and 213, 108 and 187, M = 32: 8,540 165 and 255, 190 and 299.  (Batches of 257 to 1,024 queries
+        // come here where they are not answered in one launch.)
         const bool by_bytes = a.threads == 1024 && a.nq > 256 && (a.M == 12 || (a.M == 32 && (f || a.C <= 2048)));
         switch (taps || by_bytes || a.M % 2 ? 0 : a.M / 2) {
             case 2: return launch_rerank_pair2(a, L, rk, RL, taps, f, s);

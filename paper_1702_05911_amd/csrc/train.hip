@@ -131,7 +131,7 @@ __global__ __launch_bounds__(1024) void chunk_table_kernel(const uint2* range, i
 // A thread has one vector, whose values come from LDS 32 dimensions at a time, and KB running distances; the
 // centroids are the same for the whole workgroup and come through the scalar cache.  The sums are taken from the vectors
 // once more (they are in L2): the tile's vectors are ordered by cell, a wavefront adds up one cell's.  For rows and cells that
-// lloyd_tile_kernel, below, has no room for.
+// lloyd_tile_kernel, below, has no room for, and where it is the slower one (tile_block).
 // WAYS: 1, or 4 where there are too few vectors to fill the chip and many centroids (see ways_of): a tile is then 64
 // vectors, and every wavefront has all of them and a quarter of the centroids.
 template <int KB, int WAYS>
@@ -686,9 +686,10 @@ __global__ void whole_range_kernel(uint32_t n, int P, uint2* range) {
 }
 
 // ---- the lambdas of every line's votes, and those at given ranks -----------------------------------------------------
-// Only a few ranks of a line are wanted, so its votes are brought together but not sorted: counts per line, a place for every vote,
-// and a radix select for the code points of a line (100,000 vectors x 8 sub-parts, 120 lines: 7, 10 and 22 us; a library sort of all votes
-// took 160).  A workgroup of the first two takes kCellThreads votes of one sub-part; up to kLdsLines lines it counts in LDS and adds up or reserves once per line.
+// Only a few ranks of a line are wanted, so its votes are brought together but not sorted: counts per line, a place for every vote, and a radix
+// select for the code points of a line (100,000 vectors x 8 sub-parts, 120 lines: 7, 10 and 22 us; a library sort of all votes took 160).  A
+// workgroup of the first two takes kCellThreads votes of one sub-part; up to kLdsLines lines it counts in LDS and adds up or reserves once per
+// line.
 constexpr int kLdsLines = 8192;
 
 __device__ __forceinline__ int vote_line(unsigned long long key) { return (int)((key >> 32) & 0xffffu); }
@@ -718,9 +719,8 @@ __device__ __forceinline__ void add_one(uint32_t* cnt, uint32_t at, bool have) {
     if (have && (!mine || (int)(threadIdx.x & (kWave - 1)) == first)) atomicAdd(&cnt[at], mine ? (uint32_t)__popcll(same) : 1u);
 }
 
-// count_one where all workgroups count in the same memory: what thread 0 has is added once for the workgroup (100,000 votes, nine tenths of them for one
-// of 9,730 lines: vote_counts_kernel 117 -> 20 us,
-// vote_groups_kernel 118 -> 21; spread over the lines 14 and 17).
+// count_one where all workgroups count in the same memory: what thread 0 has is added once for the workgroup (100,000 votes, nine tenths of them
+// for one of 9,730 lines: vote_counts_kernel 117 -> 20 us, vote_groups_kernel 118 -> 21; spread over the lines 14 and 17).
 __device__ __forceinline__ uint32_t count_one_of_block(uint32_t* cnt, uint32_t at, bool have) {
     __shared__ uint32_t before[kCellWaves], lead, base;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -787,12 +787,12 @@ __global__ __launch_bounds__(kCellThreads) void vote_groups_kernel(const unsigne
     if (line < lines) lam[(size_t)m * nt + at] = (uint32_t)key;
 }
 
-// A job: code points of one line, at most kPicks of them; job = (first lambda of the line in its sub-part, lambdas, first code point of the
-// job, code points), and sub-part m has the code points 256 m to 256 m + 255; lam holds the sub-parts from m0 on.  ranks[e]: the rank (from 0) of code point e among its line's
-// lambdas, ascending within a job.  Eight bits a pass, the highest first.  The code points of a job that have the same bits so far are a
-// group and share a histogram, so a pass reads the lambdas once whatever their number: a line with most of the votes has most of the
-// 256 code points as well (pqt_train of 100,000 vectors, one iteration, with 16 centroids and nine tenths of the vectors zero 0.92 ms, a walk per code
-// point 3.25; with one line 0.48 and 0.80, 2,000,000 vectors 1.25 and 9.5).
+// A job: code points of one line, at most kPicks of them; job = (first lambda of the line in its sub-part, lambdas, first code point of the job,
+// code points), and sub-part m has the code points 256 m to 256 m + 255; lam holds the sub-parts from m0 on.  ranks[e]: the rank (from 0) of code
+// point e among its line's lambdas, ascending within a job.  Eight bits a pass, the highest first.  The code points of a job that have the same
+// bits so far are a group and share a histogram, so a pass reads the lambdas once whatever their number: a line with most of the votes has most of
+// the 256 code points as well (pqt_train of 100,000 vectors, one iteration, with 16 centroids and nine tenths of the vectors zero 0.92 ms, a walk
+// per code point 3.25; with one line 0.48 and 0.80, 2,000,000 vectors 1.25 and 9.5).
 constexpr int kPicks = 32;
 struct PickLds {
     uint32_t prefix[kPicks], start[kPicks + 1], rank[kPicks], digit[kPicks];      // of a group: its bits, its first code point
@@ -868,8 +868,8 @@ __device__ __forceinline__ void next_digits(PickLds& s, const uint32_t* hist) {
 
 // out[e]: the lambda of code point e, of a workgroup's job
 constexpr int kPickThreads = 512;                            // (256: 29 us, 1,024: 28)
-__global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, uint32_t m0, const uint4* jobs, const uint32_t* ranks,
-                                                                    float* out) {
+__global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32_t* lam, uint32_t nt, uint32_t m0, const uint4* jobs,
+                                                                    const uint32_t* ranks, float* out) {
     __shared__ __align__(16) uint32_t hist[kPicks * 256];
     __shared__ PickLds s;
     const int tid = threadIdx.x;
@@ -894,9 +894,9 @@ __global__ __launch_bounds__(kPickThreads) void pick_lambdas_kernel(const uint32
     if (tid < picks) out[job.z + tid] = mono_inv(bits);
 }
 
-// The same for long lines, whose lambdas many workgroups read: a pass is two kernels (one line of 2,000,000 votes: 256 us instead of 3,800).  bits, ranks: of the code points, from pass to pass;
-// counts[code point * 256 + digit]: the histograms of a job's groups are at its first code points, zero between passes.
-// items: (job, slice)
+// The same for long lines, whose lambdas many workgroups read: a pass is two kernels (one line of 2,000,000 votes: 256 us instead of 3,800).  bits,
+// ranks: of the code points, from pass to pass; counts[code point * 256 + digit]: the histograms of a job's groups are at its first code points,
+// zero between passes. items: (job, slice)
 __global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam, uint32_t nt, uint32_t m0, const uint4* jobs, const uint2* items,
                                                             uint32_t slice, int shift, const uint32_t* bits, uint32_t* counts) {
     __shared__ __align__(16) uint32_t hist[kPicks * 256];
@@ -917,7 +917,8 @@ __global__ __launch_bounds__(1024) void slice_digits_kernel(const uint32_t* lam,
         if (hist[e]) atomicAdd(&counts[(size_t)job.z * 256 + e], hist[e]);
 }
 
-__global__ __launch_bounds__(256) void next_digits_kernel(const uint4* jobs, int shift, uint32_t* ranks, uint32_t* bits, uint32_t* counts, float* out) {
+__global__ __launch_bounds__(256) void next_digits_kernel(const uint4* jobs, int shift, uint32_t* ranks, uint32_t* bits, uint32_t* counts,
+                                                          float* out) {
     __shared__ PickLds s;
     const int tid = threadIdx.x;
     const uint4 job = jobs[blockIdx.x];
@@ -968,16 +969,14 @@ int centroid_block(int k) {
     return ((k + rounds - 1) / rounds + 7) / 8 * 8;
 }
 
-// Centroids of a lane of lloyd_tile_kernel; 0 where lloyd_step_kernel is the one to take: rows or cells beyond its registers and
-// what leaves room for one workgroup per compute unit only, and where it is the faster one.  pqt_train, 10 iterations, level 1 only where one number of
-// centroids is named, this kernel's time over the other's:
-// Rows of few values with few centroids, whose distances are less than a tile's fixed steps: 1,000,000 vectors x 4 with 1, 4, 8, 12 and 16 centroids
-// 1.54, 1.29, 1.16, 1.05, 0.95; x 16 1.39, 1.20, 1.13, 1.03, 0.98; x 32 1.16, 1.07, 1.03, 0.94, 0.96; x 48 0.86 and less; 100,000 x 4
-// 1.24, 1.15, 1.07, 1.00, 0.97, x 32 1.00, 1.11, 1.10, 0.88, 0.85; 60,000 x 8 1.07, 1.06, 1.04, 0.94, 0.94; 30,000 x 8 0.94, 0.99, 1.00, 0.85,
-// 0.84.  Not read in 16-byte pieces: 1,000,000 x 1 1.26, 1.08, 0.98, x 2 1.17, 0.91, 0.88.
-// Long rows and many centroids, of which two workgroups share a compute unit, in so many groups that their last chunks are short: 128
-// dimensions, 40 centroids in each of 256 groups, 75,000 vectors 1.05, 100,000 1.09, 300,000 1.03; of 128 groups 0.91 to 1.03; 120 dimensions
-// and less 0.87 to 1.00.
+// Centroids of a lane of lloyd_tile_kernel; 0 where lloyd_step_kernel is the one to take: rows or cells beyond its registers and what leaves room
+// for one workgroup per compute unit only, and where it is the faster one.  pqt_train, 10 iterations, level 1 only where one number of centroids is
+// named, this kernel's time over the other's: Rows of few values with few centroids, whose distances are less than a tile's fixed steps: 1,000,000
+// vectors x 4 with 1, 4, 8, 12 and 16 centroids 1.54, 1.29, 1.16, 1.05, 0.95; x 16 1.39, 1.20, 1.13, 1.03, 0.98; x 32 1.16, 1.07, 1.03, 0.94, 0.96;
+// x 48 0.86 and less; 100,000 x 4 1.24, 1.15, 1.07, 1.00, 0.97, x 32 1.00, 1.11, 1.10, 0.88, 0.85; 60,000 x 8 1.07, 1.06, 1.04, 0.94, 0.94; 30,000
+// x 8 0.94, 0.99, 1.00, 0.85, 0.84.  Not read in 16-byte pieces: 1,000,000 x 1 1.26, 1.08, 0.98, x 2 1.17, 0.91, 0.88. Long rows and many
+// centroids, of which two workgroups share a compute unit, in so many groups that their last chunks are short: 128 dimensions, 40 centroids in each
+// of 256 groups, 75,000 vectors 1.05, 100,000 1.09, 300,000 1.03; of 128 groups 0.91 to 1.03; 120 dimensions and less 0.87 to 1.00.
 int tile_block(uint64_t n, int P, int G, int k, int dp) {
     if (dp > kTileDims || k > kTileCells) return 0;
     const uint64_t rows = (uint64_t)P * n;
@@ -1007,7 +1006,9 @@ uint64_t chunk_rows(uint64_t n, int P, int G, int k, int dp) {
         uint64_t want = 256 * fit;
         want -= std::min<uint64_t>((uint64_t)G, want / 2);
         const uint64_t rows = ((uint64_t)P * n + want - 1) / want;
-        return std::max<uint64_t>(rows, 64);                 // (half a tile of 128, and 128, 64 dimensions, 16 centroids: 10,000 vectors 396 and 436 us, 32,000 477 and 510, 50,000 516 and 502)
+        // (at least half a tile of 128; half and whole, 64 dimensions, 16 centroids: 10,000 vectors 396 and 436 us, 32,000 477 and 510, 50,000
+        // 516 and 502)
+        return std::max<uint64_t>(rows, 64);
     }
     uint64_t rows = kTile / ways_of(n, P, k);
     while (rows < n && rows < (1ull << 30) && ((uint64_t)P * ((n + rows - 1) / rows) > kMaxChunks ||
