@@ -1267,7 +1267,8 @@ def test_line_table_in_batches(pqt):
 def test_line_table_edges(pqt, n, D, P, k1, M, zeros):
     """Line votes where 16-byte rows meet numbers of centroids that are no multiple of four (and at sub-parts of five
     dimensions), and of more than 32 centroids, where wavefronts share a sub-part (sub-parts of 40 and of three dimensions, the
-    most centroids), and where most vote for one of few lines and of many.  Without iterations the centroids are training vectors, whole numbers, so that all distances are exact.
+    most centroids), and where most vote for one of few lines and of many.  Without iterations the centroids are training
+    vectors, whole numbers, so that all distances are exact.
     Shares as in test_training_on_the_gpu: within one of the quota, and a near tie of two lines may move a vote or two."""
     import torch
     rng = np.random.default_rng(17)
